@@ -40,10 +40,11 @@ int check_shape(const ssd_shape_t* sh, Dims* d) {
     d->N = sh->dstate;
     d->Q = sh->chunk;
     d->hpg = d->H / d->G;
-    d->nc = sh->seqlen > 0 ? (int)(sh->segment / sh->chunk) : 0;
+    d->nc = d->nc_seg = sh->seqlen > 0 ? (int)(sh->segment / sh->chunk) : 0;
     d->nseg = sh->seqlen > 0 ? (sh->seqlen + sh->segment - 1) / sh->segment : 0;
-    d->tail = sh->seqlen > 0 ? sh->seqlen % sh->segment : 0;
-    d->nc_tail = (int)((d->tail + sh->chunk - 1) / sh->chunk);
+    d->F = d->nl = 1;
+    d->nspan = d->nseg;
+    d->nct = (sh->seqlen + sh->chunk - 1) / sh->chunk;
     d->bf16 = sh->dtype == SSD_BF16;
     d->esz = d->bf16 ? 2 : 4;
     d->xs_b = sh->x_batch_stride ? sh->x_batch_stride : d->L * d->H * d->P;
@@ -130,6 +131,7 @@ void bind_workspace(SegParams& sp, const WsLayout& w, void* workspace, bool bwd)
         sp.dA_part = (float*)(base + w.dA_part);
         sp.dD_part = (float*)(base + w.dD_part);
         sp.dcarry = (float*)(base + w.dcarry);
+        sp.dcarry_in = sp.dcarry;
     }
 }
 
@@ -148,6 +150,8 @@ void base_params(SegParams& sp, const Dims& d, uint32_t flags) {
     sp.bcs_b = d.bcs_b;
     sp.flags = flags;
     sp.nc_total = d.nc;
+    sp.ntok = d.nc * d.Q;
+    sp.seg_chunks = d.nc;
     sp.wg_target = 256;
 #ifdef SSDK_STAMPS
     sp.stamps = g_stamps;
@@ -161,8 +165,9 @@ bool use_mfma(const ssd_shape_t& sh, uint32_t flags) {
     return !(flags & SSD_FLAG_GENERIC_KERNELS) && mfma_path_supported(sh);
 }
 
-// Points the scan of segment k at its entering state and at the places its leaving state goes.
-static void wire_states(SegParams& sp, const Dims& d, int64_t k, const float* init_state, const float* bnd_ro,
+// Points the scan of the span that starts with segment k at its entering state, at the checkpoints between its
+// segments and at the places its leaving state goes; ns = its segments.
+static void wire_states(SegParams& sp, const Dims& d, int64_t k, int64_t ns, const float* init_state, const float* bnd_ro,
                         float* bnd_rw, float* final_state) {
     const int64_t HPN = (int64_t)d.H * d.P * d.N;
     if (k == 0 || !bnd_ro) {
@@ -178,28 +183,31 @@ static void wire_states(SegParams& sp, const Dims& d, int64_t k, const float* in
     sp.state_in16 = nullptr;
     sp.bnd_write16 = nullptr;
     sp.state_out16 = nullptr;
+    sp.ckpt = bnd_rw ? bnd_rw + k * HPN : (bnd_ro ? (float*)bnd_ro + k * HPN : nullptr);
+    sp.ckpt16 = nullptr;
+    sp.ckpt_bs = d.nseg * HPN;
     if (bnd_rw) {
         if (k == 0) {
             sp.bnd_write = bnd_rw;
             sp.bnd_write_bs = d.nseg * HPN;
         }
-        if (k + 1 < d.nseg) {
-            sp.state_out = bnd_rw + (k + 1) * HPN;
+        if (k + ns < d.nseg) {
+            sp.state_out = bnd_rw + (k + ns) * HPN;
             sp.state_out_bs = d.nseg * HPN;
         }
     }
-    if (k + 1 == d.nseg && final_state) {
+    if (k + ns == d.nseg && final_state) {
         sp.state_out2 = final_state;
         sp.state_out2_bs = HPN;
     }
 }
 
-// ---- several segments in flight ---------------------------------------------------------------
-// Consecutive segments depend on each other only through the state scan.  With more than one
-// segment, segment k runs on lane k % NPIPE -- lane 0 is the caller's stream, the others are internal
-// streams (default priority) -- each lane with its own per-segment scratch; events order the scans.
-// This overlaps one segment's launch gaps, tails and bandwidth-bound kernels with another's matrix work.
-constexpr int NPIPE = 4;  // segments in flight (the caller's stream + NPIPE - 1 internal ones)
+// ---- several spans in flight ---------------------------------------------------------------
+// Consecutive spans depend on each other only through the state scan.  With more than one
+// span, span k runs on lane k % nl -- lane 0 is the caller's stream, the others are internal
+// streams (default priority) -- each lane with its own scratch; events order the scans.
+// This overlaps one span's launch gaps, tails and bandwidth-bound kernels with another's matrix work.
+constexpr int NPIPE = 4;  // spans in flight at most (the caller's stream + NPIPE - 1 internal ones)
 struct Pipe {
     hipStream_t aux[NPIPE] = {};       // aux[0] is unused: lane 0 is the caller's stream
     hipEvent_t fork = nullptr, join[NPIPE] = {}, scan[NPIPE] = {};
@@ -238,53 +246,16 @@ static Pipe* pipe_for_current_device() {
     return &p;
 }
 
-// Forward without checkpoints (boundary_states == NULL, several segments): the state leaving one
-// segment reaches the next through two buffers used alternately (the scans are ordered by events, so
+// Forward without checkpoints (boundary_states == NULL, several spans): the state leaving one
+// span reaches the next through two buffers used alternately (the scans are ordered by events, so
 // a buffer is rewritten only after its reader has finished).
 static size_t carry_bytes(const Dims& d) { return d.nseg > 1 ? 2 * align_up((size_t)d.Bt * d.H * d.P * d.N * 4) : 0; }
 
-// A short last segment (seqlen not a multiple of segment, or of chunk) is run on padded copies of its
-// tokens: the padding tokens have dt = 0 and x = B = C = dy = 0, i.e. they are identity steps of the
-// recurrence that add nothing to any gradient.  Offsets (bytes) of the copies behind the scratch blocks.
-struct TailStage {
-    size_t x, dt, B, C, y, dy, dx, ddt, dB, dC, reset, total;
-    int64_t T;  // tokens of the padded segment
-};
-static TailStage tail_stage(const Dims& d, bool bwd) {
-    TailStage t;
-    memset(&t, 0, sizeof(t));
-    if (!d.tail) return t;
-    t.T = (int64_t)d.nc_tail * d.Q;
-    size_t off = 0;
-    auto take = [&](size_t row_elems) {
-        size_t o = off;
-        off += align_up((size_t)d.Bt * t.T * row_elems * d.esz);
-        return o;
-    };
-    const size_t hp = (size_t)d.H * d.P, gn = (size_t)d.G * d.N;
-    t.x = take(hp);
-    t.dt = take(d.H);
-    t.B = take(gn);
-    t.C = take(gn);
-    if (!bwd) {
-        t.y = take(hp);
-    } else {
-        t.dy = take(hp);
-        t.dx = take(hp);
-        t.ddt = take(d.H);
-        t.dB = take(gn);
-        t.dC = take(gn);
-    }
-    if (d.reset) {
-        t.reset = off;
-        off += align_up((size_t)d.Bt * t.T);
-    }
-    t.total = off;
-    return t;
+// Bytes of the arrays shared by all scratch blocks: the dA / dD partial sums of every chunk.  A ragged sequence gets
+// one more row of them (the query promises more space for a short tail than for the whole chunks it is rounded up to).
+static size_t shared_bytes(const Dims& d) {
+    return 2 * align_up((size_t)d.Bt * d.nct * d.H * 4) + (d.L % d.Q ? align_up((size_t)d.Bt * d.H * 4) : 0);
 }
-
-// Bytes of the arrays shared by all scratch blocks: the dA / dD partial sums of every chunk.
-static size_t shared_bytes(const Dims& d) { return 2 * align_up((size_t)d.Bt * d.nseg * d.nc * d.H * 4); }
 
 // SSD_MAGC_SERIAL=1 in the environment keeps every segment on the caller's stream (diagnostics: per-kernel
 // timings are only meaningful when kernels do not overlap).
@@ -298,15 +269,50 @@ bool serial_mode() {
     return serial || g_serial;
 }
 
-// SSD_MAGC_LANES=n (1 .. NPIPE) in the environment caps the segments in flight (measurements; the default is NPIPE).
-static int lanes(const Dims& d, bool mfma, bool one_stream = false) {
+// SSD_MAGC_LANES=n (1 .. NPIPE) in the environment caps the spans in flight (measurements; the default is NPIPE).
+static int lane_cap() {
     static const int cap = [] {
         const char* v = getenv("SSD_MAGC_LANES");
         const int n = v ? atoi(v) : NPIPE;
         return n < 1 ? 1 : (n > NPIPE ? NPIPE : n);
     }();
-    if (!mfma || one_stream || serial_mode() || d.nseg <= 1) return 1;
-    return d.nseg < cap ? (int)d.nseg : cap;
+    return cap;
+}
+
+// What a launch works on, from the sizes alone.  Work is counted in units of one chunk of one head.
+//  - Chunk length: over long sequences the matrix-core kernels are fastest at 256 tokens (65536 tokens of 80 heads:
+//    3.2 ms, 4.1 ms at 128: half the chunk states to move), so shorter chunks are merged where a sequence is cut
+//    into long segments of whole 256-token chunks.  Calls of one segment (the cells of a grid among them, whose
+//    results must not depend on where the grid cuts) keep the caller's length.
+//  - Segments per span: a launch of fewer than SPAN_UNITS units leaves compute units idle and costs the host as much as
+//    a full one (8192 tokens of 24 heads in four segments: 43 launches, bound by enqueuing them), so consecutive
+//    segments share their launches until that is reached; the scans put the checkpoints down on the way.
+//  - Memory: at most four segments' scratch is alive at a time, eight when a segment is below a full launch.
+//  - A sequence of few units altogether is one span: nothing to order, no events.
+void plan_dims(Dims* d, bool mfma, bool one_stream) {
+    if (d->L == 0) return;
+    if (mfma && !one_stream && d->Q < 256 && d->nseg > 1 && d->s >= 1024 && d->s % 256 == 0) d->Q = 256;
+    d->nc_seg = (int)((d->s + d->Q - 1) / d->Q);
+    d->nct = (d->L + d->Q - 1) / d->Q;
+    constexpr int64_t SPAN_UNITS = 640, ONE_SPAN_UNITS = 3840;
+    const int64_t unit = d->Bt * d->H * ((d->Q + 63) / 64);  // quarter units: 64 tokens of a head
+    const int64_t seg_units = d->nc_seg * unit / 4, all_units = d->nct * unit / 4;
+    const int64_t inflight = seg_units >= SPAN_UNITS ? 4 : 8;
+    d->F = d->nl = 1;
+    if (!one_stream && d->nseg > 1) {
+        if (d->nseg <= inflight && (all_units <= SPAN_UNITS || (mfma && all_units <= ONE_SPAN_UNITS))) {
+            d->F = (int)d->nseg;
+        } else {
+            while (d->F < inflight && d->F * seg_units < SPAN_UNITS) d->F *= 2;
+            const int64_t spans = (d->nseg + d->F - 1) / d->F;
+            int64_t nl = inflight / d->F < spans ? inflight / d->F : spans;
+            if (nl > lane_cap()) nl = lane_cap();
+            if (mfma && !serial_mode()) d->nl = (int)nl;
+        }
+    }
+    d->nspan = (d->nseg + d->F - 1) / d->F;
+    const int64_t span_chunks = (int64_t)d->F * d->nc_seg;
+    d->nc = (int)(span_chunks < d->nct ? span_chunks : d->nct);
 }
 
 // Workgroups a launch should have at least.  One segment at a time: one per compute unit.  Several
@@ -344,14 +350,37 @@ extern "C" size_t ssd_workspace_bytes_flags(const ssd_shape_t* shape, int32_t is
     if (check_shape(shape, &d) != SSD_OK) return 0;
     // never 0 for a valid shape, so that 0 unambiguously means "invalid"
     const bool mfma = use_mfma(*shape, flags);
-    const int nl = lanes(d, mfma);
-    const size_t block = align_up(ws_layout(d, is_backward != 0, mfma, wg_target(nl), (flags & SSD_FLAG_FP32_CHUNK_STATES) != 0).total);
-    const size_t t = nl * block + (is_backward ? shared_bytes(d) : carry_bytes(d)) + tail_stage(d, is_backward != 0).total;
+    plan_dims(&d, mfma, false);
+    const size_t block = align_up(ws_layout(d, is_backward != 0, mfma, wg_target(d.nl), (flags & SSD_FLAG_FP32_CHUNK_STATES) != 0).total);
+    const size_t t = d.nl * block + (is_backward ? shared_bytes(d) : carry_bytes(d));
     return t ? t : 256;
 }
 
 extern "C" size_t ssd_workspace_bytes(const ssd_shape_t* shape, int32_t is_backward) {
     return ssd_workspace_bytes_flags(shape, is_backward, 0);
+}
+
+// Token range of the span of ns segments that starts with segment k.
+static void span_tokens(SegParams& sp, const Dims& d, int64_t k, int64_t ns) {
+    const int64_t left = d.L - k * d.s, n = ns * d.s;
+    sp.ntok = (int)(left < n ? left : n);
+    sp.nc = (int)((sp.ntok + d.Q - 1) / d.Q);
+    sp.seg_chunks = d.nc_seg;
+    sp.reset_bs = d.L;
+}
+
+// Head slices of the per-slice partial sums for a span shorter than the workspace was laid out for: as many as its
+// place holds (a short span has fewer chunks to spread over the machine).
+static void fit_splits(SegParams& sp, const WsLayout& w, const Dims& d) {
+    auto fit = [&](int split) {
+        const int64_t room = (int64_t)d.nc * split;
+        int best = split;
+        for (int ns = split; ns <= sp.hpg && (int64_t)sp.nc * ns <= room; ++ns)
+            if (sp.hpg % ns == 0) best = ns;
+        return best;
+    };
+    sp.dg_split = fit(w.dg_split);
+    sp.part_split = fit(w.part_split);
 }
 
 // one_stream: everything stays on the caller's stream (no library stream or event is touched).
@@ -379,12 +408,11 @@ static int fwd_impl(const ssd_shape_t* shape, const void* x, const void* dt, con
     }
     if (!x || !dt || !A || !B || !C || !D || !y) return SSD_ERR_NULL;
     const bool mfma = use_mfma(*shape, flags);
-    const int nl = lanes(d, mfma, one_stream);
+    plan_dims(&d, mfma, one_stream);
+    const int nl = d.nl;
     const WsLayout w = ws_layout(d, false, mfma, wg_target(nl), (flags & SSD_FLAG_FP32_CHUNK_STATES) != 0);
     const size_t block = align_up(w.total);
-    const TailStage ts = tail_stage(d, false);
-    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < nl * block + carry_bytes(d) + ts.total) return SSD_ERR_WORKSPACE;
-    char* stage = (char*)workspace + nl * block + carry_bytes(d);
+    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < nl * block + carry_bytes(d)) return SSD_ERR_WORKSPACE;
     float* carry[2] = {(float*)((char*)workspace + nl * block), (float*)((char*)workspace + nl * block + carry_bytes(d) / 2)};
     Pipe* pp = nl > 1 ? pipe_for_current_device() : nullptr;
     if (nl > 1 && !pp) return SSD_ERR_LAUNCH;
@@ -398,74 +426,45 @@ static int fwd_impl(const ssd_shape_t* shape, const void* x, const void* dt, con
         sps[i].D = D;
     }
     if (!fork_lanes(pp, nl, st)) return SSD_ERR_LAUNCH;
-    for (int64_t k = 0; k < d.nseg; ++k) {
-        const int ln = (int)(k % nl);
+    for (int64_t q = 0; q < d.nspan; ++q) {
+        const int ln = (int)(q % nl);
         SegParams& sp = sps[ln];
         hipStream_t sk = ln ? pp->aux[ln] : st;
+        const int64_t k = q * d.F, ns = k + d.F < d.nseg ? d.F : d.nseg - k;  // its segments
         const int64_t t0 = k * d.s;
-        const bool short_seg = d.tail && k + 1 == d.nseg;
         const int HP = d.H * d.P, GN = d.G * d.N;
-        if (!short_seg) {
-            sp.x = off(x, t0 * HP, d.esz);
-            sp.y = off(y, t0 * HP, d.esz);
-            sp.dt = off(dt, t0 * d.H, d.esz);
-            sp.Bm = off(B, t0 * GN, d.esz);
-            sp.Cm = off(C, t0 * GN, d.esz);
-            sp.xs_b = sp.ys_b = d.xs_b;
-            sp.dts_b = d.dts_b;
-            sp.bcs_b = d.bcs_b;
-            sp.nc = d.nc;
-            sp.reset = d.reset ? d.reset + t0 : nullptr;
-            sp.reset_bs = d.L;
-        } else {  // padded copies of the last tokens (see TailStage)
-            const int tv = (int)d.tail, T = (int)ts.T;
-            hipError_t es = launch_stage_rows(stage + ts.x, (int64_t)T * HP, off(x, t0 * HP, d.esz), d.xs_b, tv, T, HP, sp.Bt, d.esz, sk);
-            if (es == hipSuccess) es = launch_stage_rows(stage + ts.dt, (int64_t)T * d.H, off(dt, t0 * d.H, d.esz), d.dts_b, tv, T, d.H, sp.Bt, d.esz, sk);
-            if (es == hipSuccess) es = launch_stage_rows(stage + ts.B, (int64_t)T * GN, off(B, t0 * GN, d.esz), d.bcs_b, tv, T, GN, sp.Bt, d.esz, sk);
-            if (es == hipSuccess) es = launch_stage_rows(stage + ts.C, (int64_t)T * GN, off(C, t0 * GN, d.esz), d.bcs_b, tv, T, GN, sp.Bt, d.esz, sk);
-            if (es == hipSuccess && d.reset) es = launch_stage_rows(stage + ts.reset, T, d.reset + t0, d.L, tv, T, 1, sp.Bt, 1, sk);
-            if (es != hipSuccess) {
-                (void)join_lanes(pp, nl, st);
-                return SSD_ERR_LAUNCH;
-            }
-            sp.x = stage + ts.x;
-            sp.y = stage + ts.y;
-            sp.dt = stage + ts.dt;
-            sp.Bm = stage + ts.B;
-            sp.Cm = stage + ts.C;
-            sp.xs_b = sp.ys_b = (int64_t)T * HP;
-            sp.dts_b = (int64_t)T * d.H;
-            sp.bcs_b = (int64_t)T * GN;
-            sp.nc = d.nc_tail;
-            sp.reset = d.reset ? (const uint8_t*)(stage + ts.reset) : nullptr;
-            sp.reset_bs = T;
-        }
-        wire_states(sp, d, k, init_state, bnd32, bnd32, final_state);
-        if (bnd16) {  // bf16 checkpoints: rounded copies; the fp32 state itself travels through the carry buffers
+        span_tokens(sp, d, k, ns);
+        sp.x = off(x, t0 * HP, d.esz);
+        sp.y = off(y, t0 * HP, d.esz);
+        sp.dt = off(dt, t0 * d.H, d.esz);
+        sp.Bm = off(B, t0 * GN, d.esz);
+        sp.Cm = off(C, t0 * GN, d.esz);
+        sp.reset = d.reset ? d.reset + t0 : nullptr;
+        wire_states(sp, d, k, ns, init_state, bnd32, bnd32, final_state);
+        if (bnd16) {  // bf16 checkpoints: rounded copies; the fp32 state itself travels in registers and through the carry buffers
+            sp.ckpt16 = bnd16 + k * (int64_t)HPN;
             if (k == 0) {
                 sp.bnd_write16 = bnd16;
                 sp.bnd_write_bs = d.nseg * (int64_t)HPN;
             }
-            if (k + 1 < d.nseg) {
-                sp.state_out16 = bnd16 + (k + 1) * (int64_t)HPN;
+            if (k + ns < d.nseg) {
+                sp.state_out16 = bnd16 + (k + ns) * (int64_t)HPN;
                 sp.state_out16_bs = d.nseg * (int64_t)HPN;
             }
         }
-        if (!bnd32 && d.nseg > 1) {  // no fp32 checkpoints: hand the state on through the carry buffers
-            if (k > 0) {
-                sp.state_in = carry[k & 1];
+        if (!bnd32 && d.nspan > 1) {  // no fp32 checkpoints: hand the state on through the carry buffers
+            if (q > 0) {
+                sp.state_in = carry[q & 1];
                 sp.state_in_bs = (int64_t)HPN;
             }
-            if (k + 1 < d.nseg) {
-                sp.state_out = carry[(k + 1) & 1];
+            if (q + 1 < d.nspan) {
+                sp.state_out = carry[(q + 1) & 1];
                 sp.state_out_bs = (int64_t)HPN;
             }
         }
-        sp.ev_wait = (nl > 1 && k > 0) ? pp->scan[(k - 1) % nl] : nullptr;
-        sp.ev_record = (nl > 1 && k + 1 < d.nseg) ? pp->scan[ln] : nullptr;
-        hipError_t e = mfma ? mfma_forward_segment(sp, true, sk) : generic_forward_segment(sp, d.bf16, true, sk);
-        if (e == hipSuccess && short_seg)  // the valid rows of y go back to the caller's tensor
-            e = launch_stage_rows(off(y, t0 * HP, d.esz), d.xs_b, stage + ts.y, (int64_t)ts.T * HP, (int)d.tail, (int)d.tail, HP, sp.Bt, d.esz, sk);
+        sp.ev_wait = (nl > 1 && q > 0) ? pp->scan[(q - 1) % nl] : nullptr;
+        sp.ev_record = (nl > 1 && q + 1 < d.nspan) ? pp->scan[ln] : nullptr;
+        const hipError_t e = mfma ? mfma_forward_segment(sp, true, sk) : generic_forward_segment(sp, d.bf16, true, sk);
         if (e != hipSuccess) {
             (void)join_lanes(pp, nl, st);  // whatever was enqueued on the library's streams still ends before the caller's next work
             return SSD_ERR_LAUNCH;
@@ -514,7 +513,8 @@ static size_t fwd_bytes_one_stream(const ssd_shape_t* shape, uint32_t flags) {
     Dims d;
     if (check_shape(shape, &d) != SSD_OK) return 0;
     const bool mfma = use_mfma(*shape, flags);
-    const size_t t = align_up(ws_layout(d, false, mfma, wg_target(1), (flags & SSD_FLAG_FP32_CHUNK_STATES) != 0).total) + carry_bytes(d) + tail_stage(d, false).total;
+    plan_dims(&d, mfma, true);
+    const size_t t = align_up(ws_layout(d, false, mfma, wg_target(1), (flags & SSD_FLAG_FP32_CHUNK_STATES) != 0).total) + carry_bytes(d);
     return t ? t : 256;
 }
 }  // namespace ssdk
@@ -573,12 +573,11 @@ extern "C" int ssd_bwd(const ssd_shape_t* shape, const void* x, const void* dt, 
     if (dx == dy) return SSD_ERR_ARG;
     if (!boundary_states && d.nseg > 1) return SSD_ERR_NULL;
     const bool mfma = use_mfma(*shape, flags);
-    const int nl = lanes(d, mfma);
+    plan_dims(&d, mfma, false);
+    const int nl = d.nl;
     const WsLayout w = ws_layout(d, true, mfma, wg_target(nl), (flags & SSD_FLAG_FP32_CHUNK_STATES) != 0);
     const size_t block = align_up(w.total);
-    const TailStage ts = tail_stage(d, true);
-    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < nl * block + shared_bytes(d) + ts.total) return SSD_ERR_WORKSPACE;
-    char* stage = (char*)workspace + nl * block + shared_bytes(d);
+    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < nl * block + shared_bytes(d)) return SSD_ERR_WORKSPACE;
     Pipe* pp = nl > 1 ? pipe_for_current_device() : nullptr;
     if (nl > 1 && !pp) return SSD_ERR_LAUNCH;
 
@@ -596,87 +595,49 @@ extern "C" int ssd_bwd(const ssd_shape_t* shape, const void* x, const void* dt, 
         sp.dD = dD;
         sp.dcarry = sps[0].dcarry;
         sp.dA_part = part_all;
-        sp.dD_part = (float*)((char*)part_all + shared_bytes(d) / 2);
-        sp.nc_total = (int)(d.tail ? (d.nseg - 1) * d.nc + d.nc_tail : d.nseg * d.nc);  // chunks that write dA / dD partial sums
+        sp.dD_part = (float*)((char*)part_all + align_up((size_t)d.Bt * d.nct * d.H * 4));
+        sp.nc_total = (int)d.nct;  // every chunk of the sequence writes a dA / dD partial sum
         sp.defer_param = 1;
     }
-    hipError_t e = dfinal_state ? launch_copy_f32(sps[0].dcarry, dfinal_state, (size_t)d.Bt * HPN, st)
-                                : launch_fill_zero(sps[0].dcarry, (size_t)d.Bt * HPN, st);
-    if (e != hipSuccess) return SSD_ERR_LAUNCH;
     if (!fork_lanes(pp, nl, st)) return SSD_ERR_LAUNCH;
-    for (int64_t k = d.nseg - 1, it = 0; k >= 0; --k, ++it) {
+    for (int64_t q = d.nspan - 1, it = 0; q >= 0; --q, ++it) {
         const int ln = (int)(it % nl);
         SegParams& sp = sps[ln];
         hipStream_t sk = ln ? pp->aux[ln] : st;
+        const int64_t k = q * d.F, ns = k + d.F < d.nseg ? d.F : d.nseg - k;  // its segments
         const int64_t t0 = k * d.s;
-        const bool short_seg = d.tail && k + 1 == d.nseg;
         const int HP = d.H * d.P, GN = d.G * d.N;
-        if (!short_seg) {
-            sp.x = off(x, t0 * HP, d.esz);
-            sp.dy = off(dy, t0 * HP, d.esz);
-            sp.dx = off(dx, t0 * HP, d.esz);
-            sp.dt = off(dt, t0 * d.H, d.esz);
-            sp.ddt = off(ddt, t0 * d.H, d.esz);
-            sp.Bm = off(B, t0 * GN, d.esz);
-            sp.Cm = off(C, t0 * GN, d.esz);
-            sp.dB = off(dB, t0 * GN, d.esz);
-            sp.dC = off(dC, t0 * GN, d.esz);
-            sp.xs_b = sp.ys_b = sp.dys_b = sp.dxs_b = d.xs_b;
-            sp.dts_b = d.dts_b;
-            sp.bcs_b = d.bcs_b;
-            sp.nc = d.nc;
-            sp.reset = d.reset ? d.reset + t0 : nullptr;
-            sp.reset_bs = d.L;
-        } else {  // padded copies of the last tokens (see TailStage); results come back after the segment
-            const int tv = (int)d.tail, T = (int)ts.T;
-            e = launch_stage_rows(stage + ts.x, (int64_t)T * HP, off(x, t0 * HP, d.esz), d.xs_b, tv, T, HP, sp.Bt, d.esz, sk);
-            if (e == hipSuccess) e = launch_stage_rows(stage + ts.dy, (int64_t)T * HP, off(dy, t0 * HP, d.esz), d.xs_b, tv, T, HP, sp.Bt, d.esz, sk);
-            if (e == hipSuccess) e = launch_stage_rows(stage + ts.dt, (int64_t)T * d.H, off(dt, t0 * d.H, d.esz), d.dts_b, tv, T, d.H, sp.Bt, d.esz, sk);
-            if (e == hipSuccess) e = launch_stage_rows(stage + ts.B, (int64_t)T * GN, off(B, t0 * GN, d.esz), d.bcs_b, tv, T, GN, sp.Bt, d.esz, sk);
-            if (e == hipSuccess) e = launch_stage_rows(stage + ts.C, (int64_t)T * GN, off(C, t0 * GN, d.esz), d.bcs_b, tv, T, GN, sp.Bt, d.esz, sk);
-            if (e == hipSuccess && d.reset) e = launch_stage_rows(stage + ts.reset, T, d.reset + t0, d.L, tv, T, 1, sp.Bt, 1, sk);
-            if (e != hipSuccess) {
-                (void)join_lanes(pp, nl, st);
-                return SSD_ERR_LAUNCH;
+        span_tokens(sp, d, k, ns);
+        fit_splits(sp, w, d);
+        sp.x = off(x, t0 * HP, d.esz);
+        sp.dy = off(dy, t0 * HP, d.esz);
+        sp.dx = off(dx, t0 * HP, d.esz);
+        sp.dt = off(dt, t0 * d.H, d.esz);
+        sp.ddt = off(ddt, t0 * d.H, d.esz);
+        sp.Bm = off(B, t0 * GN, d.esz);
+        sp.Cm = off(C, t0 * GN, d.esz);
+        sp.dB = off(dB, t0 * GN, d.esz);
+        sp.dC = off(dC, t0 * GN, d.esz);
+        sp.reset = d.reset ? d.reset + t0 : nullptr;
+        sp.chunk0 = (int)(k * d.nc_seg);
+        // restore: per-chunk entering states of the span from its segments' checkpoints
+        wire_states(sp, d, k, ns, init_state, ck16 ? nullptr : (const float*)boundary_states, nullptr, nullptr);
+        if (ck16) {  // restart from the rounded checkpoints
+            sp.ckpt16 = (bf16_t*)boundary_states + k * (int64_t)HPN;
+            if (k > 0) {
+                sp.state_in = nullptr;
+                sp.state_in16 = sp.ckpt16;
+                sp.state_in_bs = d.nseg * (int64_t)HPN;
             }
-            sp.x = stage + ts.x;
-            sp.dy = stage + ts.dy;
-            sp.dx = stage + ts.dx;
-            sp.dt = stage + ts.dt;
-            sp.ddt = stage + ts.ddt;
-            sp.Bm = stage + ts.B;
-            sp.Cm = stage + ts.C;
-            sp.dB = stage + ts.dB;
-            sp.dC = stage + ts.dC;
-            sp.xs_b = sp.ys_b = sp.dys_b = sp.dxs_b = (int64_t)T * HP;
-            sp.dts_b = (int64_t)T * d.H;
-            sp.bcs_b = (int64_t)T * GN;
-            sp.nc = d.nc_tail;
-            sp.reset = d.reset ? (const uint8_t*)(stage + ts.reset) : nullptr;
-            sp.reset_bs = T;
         }
-        sp.chunk0 = (int)(k * d.nc);
-        // restore: per-chunk entering states of this segment from its checkpoint
-        wire_states(sp, d, k, init_state, ck16 ? nullptr : (const float*)boundary_states, nullptr, nullptr);
-        if (ck16 && k > 0) {  // restart from the rounded checkpoint
-            sp.state_in = nullptr;
-            sp.state_in16 = (const bf16_t*)boundary_states + k * (int64_t)HPN;
-            sp.state_in_bs = d.nseg * (int64_t)HPN;
-        }
+        sp.dcarry_in = it == 0 ? dfinal_state : sp.dcarry;
         sp.ev_wait = sp.ev_record = nullptr;
-        e = mfma ? mfma_forward_segment(sp, false, sk) : generic_forward_segment(sp, d.bf16, false, sk);
+        hipError_t e = mfma ? mfma_forward_segment(sp, false, sk) : generic_forward_segment(sp, d.bf16, false, sk);
         if (e == hipSuccess) {
             sp.dinit_out = (k == 0) ? dinit_state : nullptr;
             sp.ev_wait = (nl > 1 && it > 0) ? pp->scan[(it - 1) % nl] : nullptr;
-            sp.ev_record = (nl > 1 && k > 0) ? pp->scan[ln] : nullptr;
+            sp.ev_record = (nl > 1 && q > 0) ? pp->scan[ln] : nullptr;
             e = mfma ? mfma_backward_segment(sp, sk) : generic_backward_segment(sp, d.bf16, sk);
-        }
-        if (e == hipSuccess && short_seg) {  // the valid rows of the results go back to the caller's tensors
-            const int tv = (int)d.tail;
-            e = launch_stage_rows(off(dx, t0 * HP, d.esz), d.xs_b, stage + ts.dx, (int64_t)ts.T * HP, tv, tv, HP, sp.Bt, d.esz, sk);
-            if (e == hipSuccess) e = launch_stage_rows(off(ddt, t0 * d.H, d.esz), d.dts_b, stage + ts.ddt, (int64_t)ts.T * d.H, tv, tv, d.H, sp.Bt, d.esz, sk);
-            if (e == hipSuccess) e = launch_stage_rows(off(dB, t0 * GN, d.esz), d.bcs_b, stage + ts.dB, (int64_t)ts.T * GN, tv, tv, GN, sp.Bt, d.esz, sk);
-            if (e == hipSuccess) e = launch_stage_rows(off(dC, t0 * GN, d.esz), d.bcs_b, stage + ts.dC, (int64_t)ts.T * GN, tv, tv, GN, sp.Bt, d.esz, sk);
         }
         if (e != hipSuccess) {
             (void)join_lanes(pp, nl, st);  // whatever was enqueued on the library's streams still ends before the caller's next work

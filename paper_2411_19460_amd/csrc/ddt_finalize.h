@@ -54,7 +54,7 @@ __device__ __forceinline__ void ddt_finalize_body(const SegParams& sp, float* s,
     if (i < Q) {
         const float da = s[i] + tail;  // belongs to token ri
         const float d = sp.dtf[cbase + ri];
-        store((int64_t)b * sp.dts_b + ((int64_t)c * Q + ri) * sp.H + h, sp.A[h] * da + sp.fterm[cbase + ri]);
+        if (ri < chunk_rows(sp, c, Q)) store((int64_t)b * sp.dts_b + ((int64_t)c * Q + ri) * sp.H + h, sp.A[h] * da + sp.fterm[cbase + ri]);
         pa = d * da;
         pd = sp.dDrow[cbase + ri];
     }

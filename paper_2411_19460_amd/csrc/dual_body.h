@@ -63,9 +63,7 @@ struct Pre {
 };
 
 struct HeadCtx {
-    const bf16_t* xg;   // x rows of this chunk and head
-    const bf16_t* dyg;  // dY rows (EPI 2)
-    bf16_t* outp;       // y (EPI 0) or dx (EPI 2)
+    rsrc_t outp;        // rows of y (EPI 0) or dx (EPI 2) of this chunk and head
     float* fterm;
     float* dDrow;
     int64_t xt;
@@ -89,9 +87,11 @@ __device__ __forceinline__ void load_pre(Pre<Q>& pr, const SegParams& sp, int b,
     const uint32_t rowbytes = (uint32_t)xt * 2;
     const uint32_t xoff = (uint32_t)(tid >> 3) * rowbytes + (uint32_t)(tid & 7) * 16, roff = (uint32_t)(tid >> 3) * 4;
     constexpr int RSTEP = CF::NTHR / 8;  // rows between a thread's consecutive vectors
+    const int nv = chunk_rows(sp, c, Q);
+    const rsrc_t rows = make_rows(src, nv, rowbytes);
 #pragma unroll
     for (int k = 0; k < CF::XV; ++k) {
-        pr.xt[k] = *(const bf16x8*)((const char*)src + (size_t)k * RSTEP * rowbytes + (size_t)xoff);
+        pr.xt[k] = rows_load(rows, xoff + k * RSTEP * rowbytes);
         const float* f1 = (REV ? sp.ein : sp.dtf) + cbase + k * RSTEP;
         pr.sc[k] = *(const float*)((const char*)f1 + (size_t)roff);
         if (!REV) pr.sc2[k] = *(const float*)((const char*)(sp.eout + cbase + k * RSTEP) + (size_t)roff);
@@ -109,10 +109,10 @@ __device__ __forceinline__ void load_pre(Pre<Q>& pr, const SegParams& sp, int b,
     pr.Dh = sp.D[h];
     if (REV) {  // lane -> (row lane / 8, 16-byte piece lane % 8) of each 8-row group of the wave's tile
         const bf16_t* xg = (const bf16_t*)sp.x + (int64_t)b * sp.xs_b + ((int64_t)c * Q * sp.H + h) * P_;
-        const uint32_t ooff = (uint32_t)((tid >> 3) & 7) * rowbytes + (uint32_t)(tid & 7) * 16;
+        const uint32_t ooff = (uint32_t)(tok0 + ((tid >> 3) & 7)) * rowbytes + (uint32_t)(tid & 7) * 16;
+        const rsrc_t xr = make_rows(xg, nv, rowbytes);
 #pragma unroll
-        for (int it = 0; it < 4; ++it)
-            pr.own[it] = *(const bf16x8*)((const char*)(xg + (int64_t)(tok0 + 8 * it) * xt) + (size_t)ooff);
+        for (int it = 0; it < 4; ++it) pr.own[it] = rows_load(xr, ooff + 8 * it * rowbytes);
     }
 }
 
@@ -152,7 +152,7 @@ __device__ __forceinline__ void store_pre(const Pre<Q>& pr, DualLds<Q>& L, int t
 // go[4(K-1) + ks] reverse), and the same rows of C (forward) or B (reverse).
 template <int Q, bool REV>
 __device__ __forceinline__ void tile_load(bf16x8 (&go)[GO_MAX], bf16x8 (&gd)[4], bf16x8 (&rf)[RF_N], const bf16_t* Mat,
-                                          const bf16_t* rowop, int64_t bt, int T, int lane) {
+                                          const bf16_t* rowop, int64_t bt, int last, int T, int lane) {
     constexpr int NB = Q / BLK;
     const int I = T >> 1, tok0 = 32 * T;
 #pragma unroll
@@ -173,7 +173,7 @@ __device__ __forceinline__ void tile_load(bf16x8 (&go)[GO_MAX], bf16x8 (&gd)[4],
         for (int e = 0; e < 8; ++e) gd[ks][e] = (REV ? kk0 + e >= tok : kk0 + e <= tok) ? v[e] : (__bf16)0.f;
     }
 #pragma unroll
-    for (int ks = 0; ks < RF_N; ++ks) rf[ks] = frag_rows(rowop, bt, tok0, 16 * ks, lane);
+    for (int ks = 0; ks < RF_N; ++ks) rf[ks] = frag_rows_upto(rowop, bt, tok0, 16 * ks, last, lane);
 }
 
 template <int Q, int EPI>
@@ -271,7 +271,7 @@ __device__ __forceinline__ void tile_compute(const bf16x8 (&go)[GO_MAX], const b
         acc1 = mfma(a1, fb, acc1);
     }
     // whole-row global accesses of the epilogue: lane -> (row lane / 8, 16-byte piece lane % 8) of an 8-row group
-    const uint32_t rowoff = ((uint32_t)(lane >> 3) * (uint32_t)cx.xt + (uint32_t)(lane & 7) * 8) * 2;
+    const uint32_t rowoff = ((uint32_t)(tok0 + (lane >> 3)) * (uint32_t)cx.xt + (uint32_t)(lane & 7) * 8) * 2;
     // epilogue: in the accumulators this lane owns token `tok` and, per register group q, four
     // consecutive channels; rows travel through the wave's LDS patch to and from whole-row accesses.
     // Reverse, the wave's own 32 rows of x have been waiting in its patch since the staging phase.
@@ -310,7 +310,7 @@ __device__ __forceinline__ void tile_compute(const bf16x8 (&go)[GO_MAX], const b
         const int row = (lane >> 3) + 8 * it;
         const bf16x8 v = *(const bf16x8*)(priv + row * XPITCH + (lane & 7) * 16);
         // written once and not read again by this step: a streaming store leaves the L2 to the tiles the passes share
-        __builtin_nontemporal_store(v, (bf16x8*)((char*)(cx.outp + (int64_t)(tok0 + 8 * it) * cx.xt) + (size_t)rowoff));
+        rows_store<AUX_NT>(cx.outp, rowoff + 16 * it * (uint32_t)cx.xt, v);
     }
     if (EPI != 0) {
         s_a += __shfl_xor(s_a, 32, 64);
@@ -345,7 +345,7 @@ __device__ __forceinline__ void dual_body(const SegParams& sp, DualLds<Q>& L, in
                           ((int64_t)c * Q * sp.G + g) * N_;
     bf16x8 go[GO_MAX], gd[4], rf[RF_N];
     HeadCtx cx;
-    tile_load<Q, REV>(go, gd, rf, Mat, rowop, bt, T, lane);
+    tile_load<Q, REV>(go, gd, rf, Mat, rowop, bt, chunk_rows(sp, c, Q) - 1, T, lane);
     Pre<Q> pr;
     load_pre<Q, REV>(pr, sp, b, c, h0, tid, 32 * T);
     for (int hh = 0; hh < hps; ++hh) {
@@ -366,9 +366,8 @@ __device__ __forceinline__ void dual_body(const SegParams& sp, DualLds<Q>& L, in
         SSDK_STAMP(EPI == 2 ? 0 : 3, 4);
         const int64_t cbase = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
         const int64_t xrow = ((int64_t)c * Q * sp.H + h) * P_;
-        cx.xg = (const bf16_t*)sp.x + (int64_t)b * sp.xs_b + xrow;
-        cx.dyg = EPI == 0 ? nullptr : (const bf16_t*)sp.dy + (int64_t)b * sp.dys_b + xrow;
-        cx.outp = EPI == 0 ? (bf16_t*)sp.y + (int64_t)b * sp.ys_b + xrow : (bf16_t*)sp.dx + (int64_t)b * sp.dxs_b + xrow;
+        cx.outp = make_rows(EPI == 0 ? (bf16_t*)sp.y + (int64_t)b * sp.ys_b + xrow : (bf16_t*)sp.dx + (int64_t)b * sp.dxs_b + xrow,
+                            chunk_rows(sp, c, Q), (uint32_t)xt * 2);
         cx.fterm = sp.fterm + cbase;
         cx.dDrow = sp.dDrow + cbase;
         cx.xt = xt;

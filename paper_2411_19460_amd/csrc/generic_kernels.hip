@@ -79,10 +79,11 @@ template <typename T>
 __global__ void k_cumsum(SegParams sp) {
     __shared__ float s[1024];
     const int i = threadIdx.x, c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const bool live = i < chunk_rows(sp, c, sp.Q);
     float d = 0.f;
-    if (i < sp.Q) d = IO<T>::ld(sp.dt, (int64_t)b * sp.dts_b + ((int64_t)c * sp.Q + i) * sp.H + h);
+    if (live) d = IO<T>::ld(sp.dt, (int64_t)b * sp.dts_b + ((int64_t)c * sp.Q + i) * sp.H + h);
     s[i] = d * sp.A[h];
-    if (i < sp.Q && sp.reset && sp.reset[(int64_t)b * sp.reset_bs + (int64_t)c * sp.Q + i]) s[i] += RESET_LOG_DECAY;
+    if (live && sp.reset && sp.reset[(int64_t)b * sp.reset_bs + (int64_t)c * sp.Q + i]) s[i] += RESET_LOG_DECAY;
     __syncthreads();
     for (int off = 1; off < (int)blockDim.x; off <<= 1) {
         const float v = (i >= off) ? s[i - off] : 0.f;
@@ -104,14 +105,14 @@ __global__ void k_cb(SegParams sp) {
     const int j0 = blockIdx.y * TS, i0 = blockIdx.z * TS;
     if (j0 > i0) return;
     const int z = blockIdx.x, g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc);
-    const int Q = sp.Q, N = sp.N;
+    const int Q = sp.Q, N = sp.N, V = chunk_rows(sp, c, Q);
     const int64_t base = (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N;  // token stride G*N
     const int64_t tstride = (int64_t)sp.G * N;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     tile_gemm(
         acc, 0, N,
-        [&](int r, int k) { return (i0 + r < Q && k < N) ? IO<T>::ld(sp.Cm, base + (int64_t)(i0 + r) * tstride + k) : 0.f; },
-        [&](int k, int col) { return (j0 + col < Q && k < N) ? IO<T>::ld(sp.Bm, base + (int64_t)(j0 + col) * tstride + k) : 0.f; },
+        [&](int r, int k) { return (i0 + r < V && k < N) ? IO<T>::ld(sp.Cm, base + (int64_t)(i0 + r) * tstride + k) : 0.f; },
+        [&](int k, int col) { return (j0 + col < V && k < N) ? IO<T>::ld(sp.Bm, base + (int64_t)(j0 + col) * tstride + k) : 0.f; },
         As, Bs);
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     float* out = sp.Gm + (((int64_t)b * sp.nc + c) * sp.G + g) * Q * Q;
@@ -129,7 +130,7 @@ __global__ void k_chunk_outer(SegParams sp) {
     __shared__ float As[TS][TS + 1], Bs[TS][TS + 1];
     const int n0 = blockIdx.y * TS, p0 = blockIdx.z * TS;
     const int z = blockIdx.x, h = z % sp.H, c = (z / sp.H) % sp.nc, b = z / (sp.H * sp.nc);
-    const int Q = sp.Q, N = sp.N, P = sp.P, g = h / sp.hpg;
+    const int Q = sp.Q, N = sp.N, P = sp.P, g = h / sp.hpg, V = chunk_rows(sp, c, Q);
     const float* cum = sp.cum + (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
     const float* dtf = sp.dtf + (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
     const float T_ = cum[Q - 1];
@@ -143,11 +144,11 @@ __global__ void k_chunk_outer(SegParams sp) {
     tile_gemm(
         acc, 0, Q,
         [&](int r, int k) {
-            if (p0 + r >= P || k >= Q) return 0.f;
+            if (p0 + r >= P || k >= V) return 0.f;
             const float w = MODE == 0 ? expf(T_ - cum[k]) * dtf[k] : expf(cum[k]);
             return w * IO<T>::ld(lhs, xbase + (int64_t)k * xt + p0 + r);
         },
-        [&](int k, int col) { return (k < Q && n0 + col < N) ? IO<T>::ld(rhs, bbase + (int64_t)k * bt + n0 + col) : 0.f; },
+        [&](int k, int col) { return (k < V && n0 + col < N) ? IO<T>::ld(rhs, bbase + (int64_t)k * bt + n0 + col) : 0.f; },
         As, Bs);
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     float* out = MODE == 0 ? sp.states + (((int64_t)b * (sp.nc + 1) + c) * sp.H + h) * P * N
@@ -159,24 +160,41 @@ __global__ void k_chunk_outer(SegParams sp) {
     }
 }
 
-// Inter-chunk state passing over one segment: one thread per state element, sequential in chunks.
-__global__ void k_state_scan_fwd(SegParams sp) {
+// Inter-chunk state passing over one span: one thread per state element, sequential in chunks.  nseg as in
+// mk_scan_fwd: 1 = one walk that puts the segments' checkpoints down, else every segment restarts from its own.
+__global__ void k_state_scan_fwd(SegParams sp, int nseg) {
     const int PN = sp.P * sp.N;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int e = blockIdx.x * blockDim.x + threadIdx.x, h = blockIdx.y, seg = blockIdx.z % nseg, b = blockIdx.z / nseg;
     if (e >= PN) return;
-    const int64_t bh = ((int64_t)h) * PN + e;
-    float hc = sp.state_in ? sp.state_in[(int64_t)b * sp.state_in_bs + bh] : 0.f;
-    if (!sp.state_in && sp.state_in16) hc = bf16_to_float(sp.state_in16[(int64_t)b * sp.state_in_bs + bh]);  // bf16 checkpoint
+    const int64_t bh = ((int64_t)h) * PN + e, HPN = (int64_t)sp.H * PN;
+    const int c_lo = seg * sp.seg_chunks, c_hi = nseg > 1 && c_lo + sp.seg_chunks < sp.nc ? c_lo + sp.seg_chunks : sp.nc;
+    float hc = 0.f;
+    if (seg > 0) {
+        const int64_t o = (int64_t)b * sp.ckpt_bs + seg * HPN + bh;
+        hc = sp.ckpt16 ? bf16_to_float(sp.ckpt16[o]) : sp.ckpt[o];
+    } else if (sp.state_in) {
+        hc = sp.state_in[(int64_t)b * sp.state_in_bs + bh];
+    } else if (sp.state_in16) {  // bf16 checkpoint
+        hc = bf16_to_float(sp.state_in16[(int64_t)b * sp.state_in_bs + bh]);
+    }
     if (sp.bnd_write) sp.bnd_write[(int64_t)b * sp.bnd_write_bs + bh] = hc;
     if (sp.bnd_write16) sp.bnd_write16[(int64_t)b * sp.bnd_write_bs + bh] = float_to_bf16(hc);
     const float* cum = sp.cum + ((int64_t)b * sp.H + h) * sp.nc * sp.Q;
-    for (int c = 0; c < sp.nc; ++c) {
+    int next = nseg == 1 && (sp.ckpt || sp.ckpt16) ? sp.seg_chunks : sp.nc;  // chunk at which the next segment starts
+    int64_t slot = (int64_t)b * sp.ckpt_bs + bh;
+    for (int c = c_lo; c < c_hi; ++c) {
+        if (c == next) {
+            next += sp.seg_chunks;
+            slot += HPN;
+            if (sp.ckpt) sp.ckpt[slot] = hc;
+            if (sp.ckpt16) sp.ckpt16[slot] = float_to_bf16(hc);
+        }
         const int64_t idx = (((int64_t)b * (sp.nc + 1) + c) * sp.H + h) * PN + e;
         const float s = sp.states[idx];
         sp.states[idx] = hc;
         hc = expf(cum[(int64_t)c * sp.Q + sp.Q - 1]) * hc + s;
     }
-    sp.states[(((int64_t)b * (sp.nc + 1) + sp.nc) * sp.H + h) * PN + e] = hc;
+    if (c_hi == sp.nc) sp.states[(((int64_t)b * (sp.nc + 1) + sp.nc) * sp.H + h) * PN + e] = hc;
     if (sp.state_out) sp.state_out[(int64_t)b * sp.state_out_bs + bh] = hc;
     if (sp.state_out2) sp.state_out2[(int64_t)b * sp.state_out2_bs + bh] = hc;
     if (sp.state_out16) sp.state_out16[(int64_t)b * sp.state_out16_bs + bh] = float_to_bf16(hc);
@@ -189,7 +207,7 @@ __global__ void k_state_scan_bwd(SegParams sp) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x, h = blockIdx.y, b = blockIdx.z;
     const bool live = e < PN;
     const int64_t ce = ((int64_t)b * sp.H + h) * PN + e;
-    float g = live ? sp.dcarry[ce] : 0.f;
+    float g = live && sp.dcarry_in ? sp.dcarry_in[ce] : 0.f;
     const float* cum = sp.cum + ((int64_t)b * sp.H + h) * sp.nc * sp.Q;
     for (int c = sp.nc - 1; c >= 0; --c) {
         float loc = 0.f, part = 0.f;
@@ -223,7 +241,7 @@ __global__ void k_chunk_out(SegParams sp) {
     __shared__ float As[TS][TS + 1], Bs[TS][TS + 1];
     const int p0 = blockIdx.y * TS, i0 = blockIdx.z * TS;
     const int z = blockIdx.x, h = z % sp.H, c = (z / sp.H) % sp.nc, b = z / (sp.H * sp.nc);
-    const int Q = sp.Q, N = sp.N, P = sp.P, g = h / sp.hpg;
+    const int Q = sp.Q, N = sp.N, P = sp.P, g = h / sp.hpg, V = chunk_rows(sp, c, Q);
     const float* cum = sp.cum + (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
     const float* dtf = sp.dtf + (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
     const float* Gm = sp.Gm + (((int64_t)b * sp.nc + c) * sp.G + g) * Q * Q;
@@ -241,13 +259,13 @@ __global__ void k_chunk_out(SegParams sp) {
             const int i = i0 + r;
             return (i < Q && k <= i) ? Gm[(int64_t)i * Q + k] * expf(cum[i] - cum[k]) * dtf[k] : 0.f;
         },
-        [&](int k, int col) { return (k < Q && p0 + col < P) ? IO<T>::ld(sp.x, xbase + (int64_t)k * xt + p0 + col) : 0.f; },
+        [&](int k, int col) { return (k < V && p0 + col < P) ? IO<T>::ld(sp.x, xbase + (int64_t)k * xt + p0 + col) : 0.f; },
         As, Bs);
     tile_gemm(
         acc, 0, N,
         [&](int r, int k) {
             const int i = i0 + r;
-            return (i < Q && k < N) ? expf(cum[i]) * IO<T>::ld(sp.Cm, bbase + (int64_t)i * bt + k) : 0.f;
+            return (i < V && k < N) ? expf(cum[i]) * IO<T>::ld(sp.Cm, bbase + (int64_t)i * bt + k) : 0.f;
         },
         [&](int k, int col) { return (k < N && p0 + col < P) ? Hprev[(int64_t)(p0 + col) * N + k] : 0.f; }, As, Bs);
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
@@ -255,7 +273,7 @@ __global__ void k_chunk_out(SegParams sp) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = i0 + ty + 8 * r, p = p0 + tx;
-        if (i < Q && p < P) {
+        if (i < V && p < P) {
             const int64_t o = (int64_t)i * xt + p;
             IO<T>::st(sp.y, ybase + o, acc[r] + Dh * IO<T>::ld(sp.x, xbase + o));
         }
@@ -268,7 +286,7 @@ __global__ void k_bwd_main(SegParams sp) {
     __shared__ float As[TS][TS + 1], Bs[TS][TS + 1];
     const int j0 = blockIdx.y * TS;
     const int z = blockIdx.x, h = z % sp.H, c = (z / sp.H) % sp.nc, b = z / (sp.H * sp.nc);
-    const int Q = sp.Q, N = sp.N, P = sp.P, g = h / sp.hpg;
+    const int Q = sp.Q, N = sp.N, P = sp.P, g = h / sp.hpg, V = chunk_rows(sp, c, Q);
     const int64_t cbase = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
     const float* cum = sp.cum + cbase;
     const float* dtf = sp.dtf + cbase;
@@ -296,13 +314,13 @@ __global__ void k_bwd_main(SegParams sp) {
                 const int i = j0 + r;
                 return (i < Q && k <= i) ? Gm[(int64_t)i * Q + k] * expf(cum[i] - cum[k]) * dtf[k] : 0.f;
             },
-            [&](int k, int col) { return (k < Q && p0 + col < P) ? IO<T>::ld(sp.x, xbase + (int64_t)k * xt + p0 + col) : 0.f; },
+            [&](int k, int col) { return (k < V && p0 + col < P) ? IO<T>::ld(sp.x, xbase + (int64_t)k * xt + p0 + col) : 0.f; },
             As, Bs);
         tile_gemm(
             ay, 0, N,
             [&](int r, int k) {
                 const int i = j0 + r;
-                return (i < Q && k < N) ? expf(cum[i]) * IO<T>::ld(sp.Cm, bbase + (int64_t)i * bt + k) : 0.f;
+                return (i < V && k < N) ? expf(cum[i]) * IO<T>::ld(sp.Cm, bbase + (int64_t)i * bt + k) : 0.f;
             },
             [&](int k, int col) { return (k < N && p0 + col < P) ? Hprev[(int64_t)(p0 + col) * N + k] : 0.f; }, As, Bs);
         // u rows j0..: transposed masked scores (without dt) times dY, then the leaving-adjoint term
@@ -312,19 +330,19 @@ __global__ void k_bwd_main(SegParams sp) {
                 const int j = j0 + r;
                 return (j < Q && k < Q && k >= j) ? Gm[(int64_t)k * Q + j] * expf(cum[k] - cum[j]) : 0.f;
             },
-            [&](int k, int col) { return (k < Q && p0 + col < P) ? IO<T>::ld(sp.dy, dybase + (int64_t)k * xt + p0 + col) : 0.f; },
+            [&](int k, int col) { return (k < V && p0 + col < P) ? IO<T>::ld(sp.dy, dybase + (int64_t)k * xt + p0 + col) : 0.f; },
             As, Bs);
         tile_gemm(
             au, 0, N,
             [&](int r, int k) {
                 const int j = j0 + r;
-                return (j < Q && k < N) ? expf(T_ - cum[j]) * IO<T>::ld(sp.Bm, bbase + (int64_t)j * bt + k) : 0.f;
+                return (j < V && k < N) ? expf(T_ - cum[j]) * IO<T>::ld(sp.Bm, bbase + (int64_t)j * bt + k) : 0.f;
             },
             [&](int k, int col) { return (k < N && p0 + col < P) ? dHnext[(int64_t)(p0 + col) * N + k] : 0.f; }, As, Bs);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int j = j0 + ty + 8 * r, p = p0 + tx;
-            if (j < Q && p < P) {
+            if (j < V && p < P) {
                 const int64_t o = (int64_t)j * xt + p;
                 const float dyv = IO<T>::ld(sp.dy, dybase + o), xv = IO<T>::ld(sp.x, xbase + o);
                 IO<T>::st(sp.dx, dxbase + o, dtf[j] * au[r] + (Dh + res) * dyv);
@@ -396,7 +414,7 @@ __global__ void k_dG(SegParams sp) {
     const int j0 = blockIdx.y * TS, i0 = blockIdx.z * TS;
     if (j0 > i0) return;
     const int z = blockIdx.x, g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc);
-    const int Q = sp.Q, P = sp.P;
+    const int Q = sp.Q, P = sp.P, V = chunk_rows(sp, c, Q);
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     const int64_t xt = (int64_t)sp.H * P;
     float tot[4] = {0.f, 0.f, 0.f, 0.f};
@@ -410,8 +428,8 @@ __global__ void k_dG(SegParams sp) {
         float acc[4] = {0.f, 0.f, 0.f, 0.f};
         tile_gemm(
             acc, 0, P,
-            [&](int r, int k) { return (i0 + r < Q && k < P) ? IO<T>::ld(sp.dy, dybase + (int64_t)(i0 + r) * xt + k) : 0.f; },
-            [&](int k, int col) { return (j0 + col < Q && k < P) ? IO<T>::ld(sp.x, xbase + (int64_t)(j0 + col) * xt + k) : 0.f; },
+            [&](int r, int k) { return (i0 + r < V && k < P) ? IO<T>::ld(sp.dy, dybase + (int64_t)(i0 + r) * xt + k) : 0.f; },
+            [&](int k, int col) { return (j0 + col < V && k < P) ? IO<T>::ld(sp.x, xbase + (int64_t)(j0 + col) * xt + k) : 0.f; },
             As, Bs);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -436,7 +454,7 @@ __global__ void k_dBC(SegParams sp) {
     const int role = z & 1;
     z >>= 1;
     const int g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc);
-    const int Q = sp.Q, N = sp.N, P = sp.P;
+    const int Q = sp.Q, N = sp.N, P = sp.P, V = chunk_rows(sp, c, Q);
     const float* dG = sp.dG + (((int64_t)b * sp.nc + c) * sp.G + g) * Q * Q;
     const int64_t bbase = (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N;
     const int64_t bt = (int64_t)sp.G * N;
@@ -446,13 +464,13 @@ __global__ void k_dBC(SegParams sp) {
         const int kend = (r0 + TS < Q) ? r0 + TS : Q;
         tile_gemm(
             acc, 0, kend, [&](int r, int k) { return (r0 + r < Q && k <= r0 + r) ? dG[(int64_t)(r0 + r) * Q + k] : 0.f; },
-            [&](int k, int col) { return (k < Q && n0 + col < N) ? IO<T>::ld(sp.Bm, bbase + (int64_t)k * bt + n0 + col) : 0.f; },
+            [&](int k, int col) { return (k < V && n0 + col < N) ? IO<T>::ld(sp.Bm, bbase + (int64_t)k * bt + n0 + col) : 0.f; },
             As, Bs);
     } else {
         tile_gemm(
             acc, r0, Q,
             [&](int r, int k) { return (r0 + r < Q && k < Q && k >= r0 + r) ? dG[(int64_t)k * Q + r0 + r] : 0.f; },
-            [&](int k, int col) { return (k < Q && n0 + col < N) ? IO<T>::ld(sp.Cm, bbase + (int64_t)k * bt + n0 + col) : 0.f; },
+            [&](int k, int col) { return (k < V && n0 + col < N) ? IO<T>::ld(sp.Cm, bbase + (int64_t)k * bt + n0 + col) : 0.f; },
             As, Bs);
     }
     for (int hh = 0; hh < sp.hpg; ++hh) {
@@ -469,7 +487,7 @@ __global__ void k_dBC(SegParams sp) {
                 acc, 0, P,
                 [&](int r, int k) {
                     const int i = r0 + r;
-                    return (i < Q && k < P) ? expf(cum[i]) * IO<T>::ld(sp.dy, dybase + (int64_t)i * xt + k) : 0.f;
+                    return (i < V && k < P) ? expf(cum[i]) * IO<T>::ld(sp.dy, dybase + (int64_t)i * xt + k) : 0.f;
                 },
                 [&](int k, int col) { return (k < P && n0 + col < N) ? Hprev[(int64_t)k * N + n0 + col] : 0.f; }, As, Bs);
         } else {
@@ -478,7 +496,7 @@ __global__ void k_dBC(SegParams sp) {
                 acc, 0, P,
                 [&](int r, int k) {
                     const int j = r0 + r;
-                    return (j < Q && k < P) ? expf(T_ - cum[j]) * dtf[j] * IO<T>::ld(sp.x, xbase + (int64_t)j * xt + k) : 0.f;
+                    return (j < V && k < P) ? expf(T_ - cum[j]) * dtf[j] * IO<T>::ld(sp.x, xbase + (int64_t)j * xt + k) : 0.f;
                 },
                 [&](int k, int col) { return (k < P && n0 + col < N) ? dHnext[(int64_t)k * N + n0 + col] : 0.f; }, As, Bs);
         }
@@ -488,7 +506,7 @@ __global__ void k_dBC(SegParams sp) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = r0 + ty + 8 * r, n = n0 + tx;
-        if (i < Q && n < N) IO<T>::st(out, bbase + (int64_t)i * bt + n, acc[r]);
+        if (i < V && n < N) IO<T>::st(out, bbase + (int64_t)i * bt + n, acc[r]);
     }
 }
 
@@ -504,7 +522,8 @@ hipError_t fwd_segment(const SegParams& sp, bool need_y, hipStream_t st) {
     const int Q = sp.Q, P = sp.P, N = sp.N;
     SSDK_LAUNCH(K_CUMSUM, st, k_cumsum<T>, dim3(sp.nc, sp.H, sp.Bt), dim3(scan_block(Q)), sp);
     SSDK_LAUNCH(K_CHUNK_STATE, st, (k_chunk_outer<T, 0>), dim3(sp.Bt * sp.nc * sp.H, cdiv(N, TS), cdiv(P, TS)), dim3(NTHREADS), sp);
-    SSDK_LAUNCH(K_SCAN_FWD, st, k_state_scan_fwd, dim3(cdiv(P * N, NTHREADS), sp.H, sp.Bt), dim3(NTHREADS), sp);
+    const int nseg = need_y ? 1 : cdiv(sp.nc, sp.seg_chunks);
+    SSDK_LAUNCH(K_SCAN_FWD, st, k_state_scan_fwd, dim3(cdiv(P * N, NTHREADS), sp.H, sp.Bt * nseg), dim3(NTHREADS), sp, nseg);
     SSDK_LAUNCH(K_CB, st, k_cb<T>, dim3(sp.Bt * sp.nc * sp.G, cdiv(Q, TS), cdiv(Q, TS)), dim3(NTHREADS), sp);
     if (need_y) SSDK_LAUNCH(K_CHUNK_OUT, st, k_chunk_out<T>, dim3(sp.Bt * sp.nc * sp.H, cdiv(P, TS), cdiv(Q, TS)), dim3(NTHREADS), sp);
     return hipSuccess;
@@ -524,37 +543,6 @@ hipError_t bwd_segment(const SegParams& sp, hipStream_t st) {
 }
 
 }  // namespace
-
-// Rows (tokens) of a [Bt][rows][row_elems] tensor between the caller's buffer and a padded staging
-// buffer: rows >= rows_valid of the staging buffer are zero (copy in) / are not copied (copy out).
-template <typename E>
-__global__ __launch_bounds__(256) void k_stage_rows(E* dst, int64_t dst_bs, const E* src, int64_t src_bs, int rows_valid,
-                                                    int rows_dst, int row_elems, int Bt) {
-    const int64_t per_b = (int64_t)rows_dst * row_elems, total = per_b * Bt;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        const int64_t b = i / per_b, r = i - b * per_b;
-        const int row = (int)(r / row_elems);
-        dst[b * dst_bs + r] = row < rows_valid ? src[b * src_bs + r] : (E)0;
-    }
-}
-
-hipError_t launch_stage_rows(void* dst, int64_t dst_bs, const void* src, int64_t src_bs, int rows_valid, int rows_dst,
-                             int row_elems, int Bt, size_t esz, hipStream_t st) {
-    const int64_t total = (int64_t)rows_dst * row_elems * Bt;
-    if (total == 0) return hipSuccess;
-    const int64_t blocks = (total + 255) / 256;
-    const dim3 grid((unsigned)(blocks < 65536 ? blocks : 65536));
-    if (esz == 1)
-        SSDK_LAUNCH(K_COPY, st, k_stage_rows<uint8_t>, grid, dim3(256), (uint8_t*)dst, dst_bs, (const uint8_t*)src, src_bs,
-                    rows_valid, rows_dst, row_elems, Bt);
-    else if (esz == 2)
-        SSDK_LAUNCH(K_COPY, st, k_stage_rows<uint16_t>, grid, dim3(256), (uint16_t*)dst, dst_bs, (const uint16_t*)src, src_bs,
-                    rows_valid, rows_dst, row_elems, Bt);
-    else
-        SSDK_LAUNCH(K_COPY, st, k_stage_rows<uint32_t>, grid, dim3(256), (uint32_t*)dst, dst_bs, (const uint32_t*)src, src_bs,
-                    rows_valid, rows_dst, row_elems, Bt);
-    return hipSuccess;
-}
 
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t st) {
     if (n == 0) return hipSuccess;

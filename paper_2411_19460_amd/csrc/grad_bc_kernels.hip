@@ -107,11 +107,13 @@ __device__ __forceinline__ void dg_load(DgPre<Q>& pr, const SegParams& sp, int b
     const bf16_t* dyg = (const bf16_t*)sp.dy + (int64_t)b * sp.dys_b + xrow;
     // addresses = a wave-uniform base (scalar registers) + one 32-bit byte offset per lane
     const uint32_t rowbytes = (uint32_t)xt * 2, off = (uint32_t)(tid >> 3) * rowbytes + (uint32_t)(tid & 7) * 16;
+    const int nv = chunk_rows(sp, c, Q);
+    const rsrc_t dyr = make_rows(dyg, nv, rowbytes), xr = make_rows(xg, nv, rowbytes);
 #pragma unroll
     for (int k = 0; k < DgPre<Q>::NV; ++k) {
-        const size_t step = (size_t)k * (NTHR / 8) * rowbytes;
-        pr.dy[k] = *(const bf16x8*)((const char*)dyg + step + (size_t)off);
-        pr.x[k] = *(const bf16x8*)((const char*)xg + step + (size_t)off);
+        const uint32_t o = off + k * (NTHR / 8) * rowbytes;
+        pr.dy[k] = rows_load(dyr, o);
+        pr.x[k] = rows_load(xr, o);
     }
     if (tid < Q) {
         const int64_t cbase = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
@@ -419,9 +421,10 @@ __device__ __forceinline__ void part_load(PartPre<Q>& pr, const SegParams& sp, i
     // addresses = a wave-uniform base (scalar registers) + one 32-bit byte offset per lane
     const uint32_t rowbytes = (uint32_t)xt * 2, off = (uint32_t)(tid >> 3) * rowbytes + (uint32_t)(tid & 7) * 16;
     const uint32_t roff = (uint32_t)(tid >> 3) * 4;
+    const rsrc_t rows = make_rows(src, chunk_rows(sp, c, Q), rowbytes);
 #pragma unroll
     for (int k = 0; k < CF::TV; ++k) {
-        pr.t[k] = *(const bf16x8*)((const char*)src + (size_t)k * (CF::NTHR / 8) * rowbytes + (size_t)off);
+        pr.t[k] = rows_load(rows, off + k * (CF::NTHR / 8) * rowbytes);
         pr.cv[k] = *(const float*)((const char*)(sp.cum + cbase + k * (CF::NTHR / 8)) + (size_t)roff);
         pr.dv[k] = *(const float*)((const char*)(sp.dtf + cbase + k * (CF::NTHR / 8)) + (size_t)roff);
     }
@@ -472,7 +475,7 @@ __device__ __forceinline__ void part_body(const SegParams& sp, PartLds<Q>& LL, i
         const int64_t bt = (int64_t)sp.G * N_;
         const bf16_t* rowop = (role ? (const bf16_t*)sp.Bm : (const bf16_t*)sp.Cm) + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
 #pragma unroll
-        for (int ks = 0; ks < N_ / 16; ++ks) rf[ks] = frag_rows(rowop, bt, 32 * w, 16 * ks, lane);
+        for (int ks = 0; ks < N_ / 16; ++ks) rf[ks] = frag_rows_upto(rowop, bt, 32 * w, 16 * ks, chunk_rows(sp, c, Q) - 1, lane);
     }
     // Order of the heads.  When this pass runs beside the other two head-walking passes with half as many slices
     // (twice the heads per workgroup, at about twice their pace per head), it alternates between the two half
@@ -651,12 +654,13 @@ __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, in
     // so each step asks for what the next one needs before it works: the first rows of B / C before the tile sums,
     // the head sums before the contraction.
     const int p_lo = k_lo >> 1, p_hi = k_hi >> 1;  // pairs of tiles along the contraction
+    const int nv = chunk_rows(sp, c, Q), last = nv - 1;
     constexpr int SV = 64 * 16 / NTH;              // 16-byte pieces of a 64-row slab per thread
     bf16x8 sv[SV];
 #pragma unroll
     for (int k = 0; k < SV; ++k) {
         const int v = tid + NTH * k, row = v >> 4, seg = v & 15;
-        sv[k] = *(const bf16x8*)(rhs + (int64_t)(64 * p_lo + row) * bt + seg * 8);
+        sv[k] = *(const bf16x8*)(rhs + (int64_t)min(64 * p_lo + row, last) * bt + seg * 8);
     }
     // sum the slices of the needed dG tiles: items (tile, half of its rows), two items and eight slices of each in
     // flight per wave; one 16-byte piece per lane and item
@@ -729,7 +733,7 @@ __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, in
 #pragma unroll
             for (int k = 0; k < SV; ++k) {
                 const int v = tid + NTH * k, row = v >> 4, seg = v & 15;
-                sv[k] = *(const bf16x8*)(rhs + (int64_t)(64 * (pr + 1) + row) * bt + seg * 8);
+                sv[k] = *(const bf16x8*)(rhs + (int64_t)min(64 * (pr + 1) + row, last) * bt + seg * 8);
             }
         }
         __syncthreads();  // the rows (and, the first time, the summed tiles) are in place
@@ -763,7 +767,7 @@ __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, in
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r)
-        out[(int64_t)(32 * R + acc_row(r, lane)) * bt + 32 * w + (lane & 31)] = float_to_bf16(acc[r]);
+        if (32 * R + acc_row(r, lane) < nv) out[(int64_t)(32 * R + acc_row(r, lane)) * bt + 32 * w + (lane & 31)] = float_to_bf16(acc[r]);
 }
 
 template <int Q>

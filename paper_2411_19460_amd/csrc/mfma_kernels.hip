@@ -31,8 +31,9 @@ using namespace mf;
 template <int Q>
 __device__ __forceinline__ void prep_body(const SegParams& sp, float* s, int c, int h, int b) {
     const int i = threadIdx.x;
-    const float d = bf16_to_float(((const bf16_t*)sp.dt)[(int64_t)b * sp.dts_b + ((int64_t)c * Q + i) * sp.H + h]);
-    s[i] = d * sp.A[h] + ((sp.reset && sp.reset[(int64_t)b * sp.reset_bs + (int64_t)c * Q + i]) ? RESET_LOG_DECAY : 0.f);
+    const bool live = i < chunk_rows(sp, c, Q);
+    const float d = live ? bf16_to_float(((const bf16_t*)sp.dt)[(int64_t)b * sp.dts_b + ((int64_t)c * Q + i) * sp.H + h]) : 0.f;
+    s[i] = d * sp.A[h] + ((sp.reset && live && sp.reset[(int64_t)b * sp.reset_bs + (int64_t)c * Q + i]) ? RESET_LOG_DECAY : 0.f);
     __syncthreads();
     for (int off = 1; off < Q; off <<= 1) {
         const float v = (i >= off) ? s[i - off] : 0.f;
@@ -74,11 +75,12 @@ __device__ __forceinline__ void cb_body(const SegParams& sp, int z, int pair) {
     const int64_t ts = (int64_t)sp.G * N_;
     const bf16_t* Cm = (const bf16_t*)sp.Cm + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
     const bf16_t* Bm = (const bf16_t*)sp.Bm + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
+    const int last = chunk_rows(sp, c, Q) - 1;
     f32x16 a1 = zero16(), a2 = zero16();
 #pragma unroll
     for (int ks = 0; ks < N_ / 16; ++ks) {
-        const bf16x8 fc = frag_rows(Cm, ts, i0, 16 * ks, lane);
-        const bf16x8 fb = frag_rows(Bm, ts, j0, 16 * ks, lane);
+        const bf16x8 fc = frag_rows_upto(Cm, ts, i0, 16 * ks, last, lane);
+        const bf16x8 fb = frag_rows_upto(Bm, ts, j0, 16 * ks, last, lane);
         a1 = mfma(fc, fb, a1);  // a1[r] = G[i0 + acc_row(r)][j0 + lane%32]
         a2 = mfma(fb, fc, a2);  // a2[r] = G[i0 + lane%32][j0 + acc_row(r)]
     }
@@ -159,11 +161,12 @@ __device__ __forceinline__ void outer_load(OuterPre<Q>& pr, const SegParams& sp,
     // addresses = a wave-uniform base (scalar registers) + one 32-bit byte offset per lane
     const int t8 = tid % (Q * 8);  // Q = 64: one vector per thread
     const uint32_t rowbytes = (uint32_t)xt * 2, off = (uint32_t)(t8 >> 3) * rowbytes + (uint32_t)(t8 & 7) * 16;
+    const rsrc_t rows = make_rows(src, chunk_rows(sp, c, Q), rowbytes);
     const uint32_t roff = (uint32_t)(t8 >> 3) * 4;
 #pragma unroll
     for (int k = 0; k < OuterPre<Q>::NV; ++k) {
         // one reader per launch: streaming load (keeps the L2 for the kernels of other segments that do share tiles)
-        pr.t[k] = __builtin_nontemporal_load((const bf16x8*)((const char*)src + (size_t)k * (OUTER_THR / 8) * rowbytes + (size_t)off));
+        pr.t[k] = rows_load<AUX_NT>(rows, off + k * (OUTER_THR / 8) * rowbytes);
         pr.cv[k] = *(const float*)((const char*)(sp.cum + cbase + k * (OUTER_THR / 8)) + (size_t)roff);
         pr.dv[k] = *(const float*)((const char*)(sp.dtf + cbase + k * (OUTER_THR / 8)) + (size_t)roff);
     }
@@ -195,9 +198,10 @@ __global__ __launch_bounds__(OUTER_THR, 2) void mk_chunk_outer(SegParams sp, int
     outer_load<Q>(pr, sp, role, b, c, h0, tid);
     // prologue: B (role 0) or C (role 1) rows -> LDS -> this wave's fragments
     const bf16_t* rhs = (role == 0 ? (const bf16_t*)sp.Bm : (const bf16_t*)sp.Cm) + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
+    const int last = chunk_rows(sp, c, Q) - 1;
     for (int v = tid; v < Q * 16; v += OUTER_THR) {
         const int row = v >> 4, seg = v & 15;
-        *(bf16x8*)(L.bc + row * BPITCH + seg * 16) = *(const bf16x8*)(rhs + (int64_t)row * bt + seg * 8);
+        *(bf16x8*)(L.bc + row * BPITCH + seg * 16) = *(const bf16x8*)(rhs + (int64_t)(row < last ? row : last) * bt + seg * 8);
     }
     __syncthreads();
     bf16x8 fb[KS];
@@ -237,7 +241,7 @@ __global__ __launch_bounds__(OUTER_THR, 2) void mk_chunk_outer(SegParams sp, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// Inter-chunk state passing over a segment (four state elements per thread).  The running state is
+// Inter-chunk state passing over a span (four state elements per thread).  The running state is
 // carried in fp32 registers (checkpoints and the final state are stored from them); the state
 // entering each chunk is emitted as the bf16 copy the contraction kernels read, nothing else.
 __device__ __forceinline__ bf16x4 to_bf16x4(const float4 v) {
@@ -245,40 +249,58 @@ __device__ __forceinline__ bf16x4 to_bf16x4(const float4 v) {
     r[0] = (__bf16)v.x; r[1] = (__bf16)v.y; r[2] = (__bf16)v.z; r[3] = (__bf16)v.w;
     return r;
 }
+__device__ __forceinline__ float4 from_bf16x4(const bf16x4 v) {
+    return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+}
 
-template <bool F32IN>  // F32IN: the chunk states arrive in fp32 (SSD_FLAG_FP32_CHUNK_STATES), else as bf16 in place
-__global__ __launch_bounds__(NTH) void mk_scan_fwd(SegParams sp) {
+// F32IN: the chunk states arrive in fp32 (SSD_FLAG_FP32_CHUNK_STATES), else as bf16 in place.
+// Forward pass (nseg = 1): one walk over all chunks of the span, putting the checkpoints of its segments down on the
+// way.  Backward pass (nseg = segments of the span): every segment restarts from its checkpoint, side by side.
+template <bool F32IN>
+__global__ __launch_bounds__(NTH) void mk_scan_fwd(SegParams sp, int nseg) {
     constexpr int PN = P_ * N_;
-    const int e = (blockIdx.x * NTH + threadIdx.x) * 4, h = blockIdx.y, b = blockIdx.z;
-    const int64_t bh = (int64_t)h * PN + e;
-    float4 hc = sp.state_in ? *(const float4*)(sp.state_in + (int64_t)b * sp.state_in_bs + bh) : make_float4(0.f, 0.f, 0.f, 0.f);
-    if (!sp.state_in && sp.state_in16) {  // bf16 checkpoint
-        const bf16x4 v = *(const bf16x4*)(sp.state_in16 + (int64_t)b * sp.state_in_bs + bh);
-        hc = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+    const int e = (blockIdx.x * NTH + threadIdx.x) * 4, h = blockIdx.y, seg = blockIdx.z % nseg, b = blockIdx.z / nseg;
+    const int64_t bh = (int64_t)h * PN + e, HPN = (int64_t)sp.H * PN;
+    const int c_lo = seg * sp.seg_chunks, c_hi = nseg > 1 && c_lo + sp.seg_chunks < sp.nc ? c_lo + sp.seg_chunks : sp.nc;
+    float4 hc = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (seg > 0) {
+        const int64_t o = (int64_t)b * sp.ckpt_bs + seg * HPN + bh;
+        hc = sp.ckpt16 ? from_bf16x4(*(const bf16x4*)(sp.ckpt16 + o)) : *(const float4*)(sp.ckpt + o);
+    } else if (sp.state_in) {
+        hc = *(const float4*)(sp.state_in + (int64_t)b * sp.state_in_bs + bh);
+    } else if (sp.state_in16) {  // bf16 checkpoint
+        hc = from_bf16x4(*(const bf16x4*)(sp.state_in16 + (int64_t)b * sp.state_in_bs + bh));
     }
     if (sp.bnd_write) *(float4*)(sp.bnd_write + (int64_t)b * sp.bnd_write_bs + bh) = hc;
     if (sp.bnd_write16) *(bf16x4*)(sp.bnd_write16 + (int64_t)b * sp.bnd_write_bs + bh) = to_bf16x4(hc);
     const float* cum = sp.cum + ((int64_t)b * sp.H + h) * sp.nc * sp.Q;
+    const bool put = nseg == 1 && (sp.ckpt || sp.ckpt16);
+    int next = put ? sp.seg_chunks : sp.nc;  // chunk at which the next segment of the span starts
+    int64_t slot = (int64_t)b * sp.ckpt_bs + bh;
     constexpr bool f32in = F32IN;
     constexpr int U = 8;  // chunks whose loads are in flight together (the recurrence itself is serial)
-    for (int c0 = 0; c0 < sp.nc; c0 += U) {
+    for (int c0 = c_lo; c0 < c_hi; c0 += U) {
         float4 sv[U];
         float av[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int c = c0 + u < sp.nc ? c0 + u : sp.nc - 1;
-            if (f32in) {  // chunk state kept in fp32 (an array of its own)
+            const int c = c0 + u < c_hi ? c0 + u : c_hi - 1;
+            if (f32in)  // chunk state kept in fp32 (an array of its own)
                 sv[u] = *(const float4*)(sp.states + (((int64_t)b * sp.nc + c) * sp.H + h) * PN + e);
-            } else {      // chunk state (bf16), about to be replaced in place by the state entering the chunk
-                const bf16x4 sb = *(const bf16x4*)(sp.states_bf + (((int64_t)b * sp.nc + c) * sp.H + h) * PN + e);
-                sv[u] = make_float4((float)sb[0], (float)sb[1], (float)sb[2], (float)sb[3]);
-            }
+            else        // chunk state (bf16), about to be replaced in place by the state entering the chunk
+                sv[u] = from_bf16x4(*(const bf16x4*)(sp.states_bf + (((int64_t)b * sp.nc + c) * sp.H + h) * PN + e));
             av[u] = cum[(int64_t)c * sp.Q + sp.Q - 1];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int c = c0 + u;
-            if (c < sp.nc) {
+            if (c < c_hi) {
+                if (c == next) {  // uniform
+                    next += sp.seg_chunks;
+                    slot += HPN;
+                    if (sp.ckpt) *(float4*)(sp.ckpt + slot) = hc;
+                    if (sp.ckpt16) *(bf16x4*)(sp.ckpt16 + slot) = to_bf16x4(hc);
+                }
                 const bf16x4 hb = to_bf16x4(hc);  // the entering state is kept in bf16 only
                 *(bf16x4*)(sp.states_bf + (((int64_t)b * sp.nc + c) * sp.H + h) * PN + e) = hb;
                 const float a = __expf(av[u]);
@@ -300,7 +322,7 @@ __global__ __launch_bounds__(NTH) void mk_scan_bwd(SegParams sp) {
     constexpr int PN = P_ * N_;
     const int e = (blockIdx.x * NTH + threadIdx.x) * 4, h = blockIdx.y, b = blockIdx.z;
     const int64_t ce = ((int64_t)b * sp.H + h) * PN + e;
-    float4 g = *(const float4*)(sp.dcarry + ce);
+    float4 g = sp.dcarry_in ? *(const float4*)(sp.dcarry_in + ce) : make_float4(0.f, 0.f, 0.f, 0.f);
     const float* cum = sp.cum + ((int64_t)b * sp.H + h) * sp.nc * sp.Q;
     constexpr bool f32in = F32IN;
     constexpr int U = 4;  // chunks whose loads are in flight together
@@ -364,10 +386,11 @@ hipError_t fwd_q(const SegParams& sp, bool need_y, hipStream_t st) {
     if (Q != 256) SSDK_LAUNCH(K_MFMA_CB, st, mk_cb<Q>, dim3(sp.Bt * sp.nc * sp.G, NB * (NB + 1) / 2), dim3(NTH), sp);
     // the scan is the only step that needs the previous segment (its leaving state)
     if (need_y && sp.ev_wait && hipStreamWaitEvent(st, sp.ev_wait, 0) != hipSuccess) return hipErrorUnknown;
+    const int nseg = need_y ? 1 : (sp.nc + sp.seg_chunks - 1) / sp.seg_chunks;
     if (sp.flags & SSD_FLAG_FP32_CHUNK_STATES)
-        SSDK_LAUNCH(K_SCAN_FWD, st, mk_scan_fwd<true>, dim3(P_ * N_ / 4 / NTH, sp.H, sp.Bt), dim3(NTH), sp);
+        SSDK_LAUNCH(K_SCAN_FWD, st, mk_scan_fwd<true>, dim3(P_ * N_ / 4 / NTH, sp.H, sp.Bt * nseg), dim3(NTH), sp, nseg);
     else
-        SSDK_LAUNCH(K_SCAN_FWD, st, mk_scan_fwd<false>, dim3(P_ * N_ / 4 / NTH, sp.H, sp.Bt), dim3(NTH), sp);
+        SSDK_LAUNCH(K_SCAN_FWD, st, mk_scan_fwd<false>, dim3(P_ * N_ / 4 / NTH, sp.H, sp.Bt * nseg), dim3(NTH), sp, nseg);
     if (need_y && sp.ev_record && hipEventRecord(sp.ev_record, st) != hipSuccess) return hipErrorUnknown;
     if (need_y) {
         hipError_t e = mfma_launch_dual(sp, 0, st);

@@ -42,10 +42,13 @@ __host__ __device__ inline bf16_t float_to_bf16(float f) {
     return o;
 }
 
-// One segment of one layer, as the kernels see it.  Tensor pointers are already offset to the
-// first token of the segment; batch strides are those of the full tensors (elements).
+// One span of one layer, as the kernels see it: one or several consecutive checkpoint segments that share their
+// launches.  Tensor pointers are already offset to the first token of the span; batch strides are those of the
+// full tensors (elements).
 struct SegParams {
-    int Bt, H, P, G, N, Q, nc, hpg;
+    int Bt, H, P, G, N, Q, nc, hpg;    // nc: chunks of the span (the last one possibly ragged)
+    int ntok;                          // tokens of the span, <= nc Q: rows beyond them do not exist in memory
+    int seg_chunks;                    // chunks per checkpoint segment (== nc when the span is one segment)
     int64_t xs_b, ys_b, dys_b, dxs_b;  // batch strides of x, y, dy, dx
     int64_t dts_b, bcs_b;              // of dt/ddt and of B/C/dB/dC
     const uint8_t* reset;              // optional [Bt][tokens of the segment]: non-zero = a packed sequence starts here
@@ -79,7 +82,8 @@ struct SegParams {
     float* tail_part;  // [Bt][H][nc][nslice]
     float* dA_part;    // [Bt][nc][H]
     float* dD_part;    // [Bt][nc][H]
-    float* dcarry;     // [Bt][H][P][N] adjoint of the state entering the segment to the right of the current one
+    float* dcarry;     // [Bt][H][P][N] adjoint of the state entering the span to the right of the current one
+    const float* dcarry_in;  // where the reverse scan starts from: dcarry, the caller's dfinal_state, or NULL for zeros
     int nslice;
     // extra scratch of the MFMA path
     float* ein;        // [Bt][H][nc][Q] exp(cum_i - cum at the start of i's 64-token block)
@@ -94,11 +98,17 @@ struct SegParams {
     int wg_target;       // least number of workgroups a persistent-over-heads launch should have
     float* dbc_part;     // [Bt][nc][G][part_split][2][Q][N] per-slice head terms of dC (0) and dB (1)
     // state plumbing for the scans (all fp32, element strides between batches)
-    const float* state_in;   // state entering the segment, or NULL for zeros
+    const float* state_in;   // state entering the span, or NULL for zeros
     int64_t state_in_bs;
     float* bnd_write;        // where to store that entering state (checkpoint slot), or NULL
     int64_t bnd_write_bs;
-    float* state_out;        // where to store the state leaving the segment, or NULL
+    // checkpoints between the segments of a span: slot of segment q >= 1 of the span at q H P N elements, batches
+    // ckpt_bs apart; written by the forward pass (ckpt / ckpt16 where the caller keeps them), read by the backward
+    // pass, which restarts every segment from its slot
+    float* ckpt;
+    bf16_t* ckpt16;
+    int64_t ckpt_bs;
+    float* state_out;        // where to store the state leaving the span, or NULL
     int64_t state_out_bs;
     float* state_out2;       // second copy (final_state when the last segment also has no slot), or NULL
     int64_t state_out2_bs;
@@ -139,13 +149,23 @@ extern unsigned long long* g_stamps;
     } while (0)
 #endif
 
+// Tokens of chunk c that exist (the last chunk of a sequence may be ragged): its further rows read as zeros or as
+// copies of the last one under dt = 0, i.e. they are identity steps of the recurrence, and are never stored.
+__host__ __device__ inline int chunk_rows(const SegParams& sp, int c, int Q) {
+    const int left = sp.ntok - c * Q;
+    return left < Q ? left : Q;
+}
+
 // Validated dimensions of one call.
 struct Dims {
     int64_t Bt, L, s;
     int H, P, G, N, Q, nc, hpg;
     int64_t nseg;       // segments, the last one possibly short
-    int64_t tail;       // tokens of a short last segment (0: every segment is full)
-    int nc_tail;        // chunks of that segment (the last one padded with identity tokens)
+    // the launch plan (plan_dims): span k = segments [k F, (k + 1) F), on lane k % nl
+    int nc_seg;         // chunks per segment
+    int F, nl;          // segments per span, spans in flight
+    int64_t nspan;
+    int64_t nct;        // chunks of the sequence; nc above: chunks of the largest span
     size_t esz;
     bool bf16;
     int64_t xs_b, dts_b, bcs_b;
@@ -166,6 +186,8 @@ struct WsLayout {
 };
 
 int check_shape(const ssd_shape_t* sh, Dims* d);
+// Chooses chunk length, segments per launch and launches in flight (fills Q, nc and the launch plan).
+void plan_dims(Dims* d, bool mfma, bool one_stream);
 // mfma: the layout for the matrix-core kernels, which keep the chunk states and their adjoints in
 // bf16 only (the fp32 arrays of the shape-generic kernels are left out).
 // fp32cs: the matrix-core layout keeps fp32 chunk states / local adjoints beside the bf16 operand copies.
@@ -200,9 +222,6 @@ bool prof_events(int kid, hipEvent_t* start, hipEvent_t* stop);
 // Launchers.  Each returns hipSuccess or the launch error.  is_bf16 selects the storage type.
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t st);
 hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t st);
-// dst[b][row][:] = row < rows_valid ? src[b][row][:] : 0 for row < rows_dst (batch strides in elements of esz bytes).
-hipError_t launch_stage_rows(void* dst, int64_t dst_bs, const void* src, int64_t src_bs, int rows_valid, int rows_dst,
-                             int row_elems, int Bt, size_t esz, hipStream_t st);
 hipError_t generic_forward_segment(const SegParams& sp, bool is_bf16, bool need_y, hipStream_t st);
 hipError_t generic_backward_segment(const SegParams& sp, bool is_bf16, hipStream_t st);
 hipError_t generic_backward_scalars(const SegParams& sp, hipStream_t st);

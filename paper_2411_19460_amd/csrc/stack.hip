@@ -39,6 +39,7 @@ int check_stack(const ssd_shape_t* shape, int32_t nlayers, int32_t layer_interva
     sd->cell.dts_b = sd->full.dts_b;
     sd->cell.bcs_b = sd->full.bcs_b;
     sd->mfma = use_mfma(*shape, 0);
+    plan_dims(&sd->cell, sd->mfma, true);  // one segment: fixes the chunk length
     sd->nl = nlayers;
     sd->l = layer_interval < nlayers ? layer_interval : nlayers;
     sd->nlg = (nlayers + sd->l - 1) / sd->l;
@@ -259,8 +260,7 @@ extern "C" int magc_stack_bwd(const ssd_shape_t* shape, int32_t nlayers, int32_t
                 e = mfma ? mfma_forward_segment(sp, false, st) : generic_forward_segment(sp, c.bf16, false, st);
                 if (e != hipSuccess) return SSD_ERR_LAUNCH;
                 float* dhj = dh + (int64_t)j * f.Bt * HPN;
-                e = launch_copy_f32(sp.dcarry, dhj, (size_t)f.Bt * HPN, st);
-                if (e != hipSuccess) return SSD_ERR_LAUNCH;
+                sp.dcarry_in = dhj;
                 sp.dinit_out = dhj;
                 sp.accumulate = (k == f.nseg - 1) ? 0 : 1;
                 e = mfma ? mfma_backward_segment(sp, st) : generic_backward_segment(sp, c.bf16, st);
