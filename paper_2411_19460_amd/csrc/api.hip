@@ -69,32 +69,43 @@ WsLayout ws_layout(const Dims& d, bool bwd, bool mfma, int wg_target, bool fp32c
     };
     const size_t tok = (size_t)d.Bt * d.H * d.nc * d.Q * 4;
     const size_t PN = (size_t)d.P * d.N;
-    w.nslice = (int)((PN + 255) / 256);
+    w.nslice = (int)((PN + 255) / 256) * 4;  // partial sums of a reverse scan: one per wave
+    w.tok = tok;
     w.cum = take(tok);
     w.dtf = take(tok);
     w.states = w.states_bf = w.dstates = w.dstates_bf = w.dbc_part = WS_NONE;  // present on one path only
     if (!mfma) w.states = take((size_t)d.Bt * (d.nc + 1) * d.H * PN * 4);
     if (mfma && fp32cs) w.states = take((size_t)d.Bt * d.nc * d.H * PN * 4);  // slot c: chunk state c (scan input)
     w.Gm = take((size_t)d.Bt * d.nc * d.G * d.Q * d.Q * 4);
-    w.ein = take(tok);
-    w.eout = take(tok);
+    w.ein = w.eout = w.gintra = w.erow = w.ecol = WS_NONE;
+    if (mfma) w.ein = take(tok);
+    if (mfma) w.eout = take(tok);
     if (mfma) w.states_bf = take((size_t)d.Bt * d.nc * d.H * PN * 2);
     const int64_t groups = d.Bt * (int64_t)d.nc * d.G;
-    w.dg_split = pick_split(d.hpg, groups, wg_target);
-    w.part_split = pick_split(d.hpg, groups * 2, wg_target);
+    // generic kernels: 64 x 64 tiles, several workgroups per compute unit
+    const int64_t nt = (d.Q + 63) / 64, nn = (d.N + 63) / 64, np = (d.P + 63) / 64;
+    auto few = [&](int ns) {  // largest divisor not above ns or GENERIC_SLICES: the last pass adds the slices up in registers
+        ns = ns < GENERIC_SLICES ? ns : GENERIC_SLICES;
+        while (d.hpg % ns) --ns;
+        return ns;
+    };
+    w.dg_split = mfma ? pick_split(d.hpg, groups, wg_target) : few(pick_split(d.hpg, groups * (nt * (nt + 1) / 2), 256));
+    w.part_split = mfma ? pick_split(d.hpg, groups * 2, wg_target) : few(pick_split(d.hpg, groups * 2 * nt * nn, 256));
     if (bwd) {
         if (!mfma || fp32cs) w.dstates = take((size_t)d.Bt * d.nc * d.H * PN * 4);
         if (mfma) w.dstates_bf = take((size_t)d.Bt * d.nc * d.H * PN * 2);
-        {   // fp32 head sum (generic kernels) or one bf16 partial sum per head slice (MFMA kernels)
-            const size_t per = mfma ? (size_t)d.Q * d.Q * 2 * w.dg_split : (size_t)d.Q * d.Q * 4;
+        {   // one partial sum per head slice: fp32 (generic kernels) or bf16 (MFMA kernels)
+            const size_t per = (size_t)d.Q * d.Q * (mfma ? 2 : 4) * w.dg_split;
             w.dG = take((size_t)d.Bt * d.nc * d.G * per);
         }
-        if (mfma) w.dbc_part = take((size_t)d.Bt * d.nc * d.G * w.part_split * 2 * d.Q * d.N * 4);
-        w.gterm = take(tok);
-        w.sterm = take(tok);
-        w.gintra = take(tok);
-        w.fterm = take(tok);
-        w.dDrow = take(tok);
+        w.dbc_part = take((size_t)d.Bt * d.nc * d.G * w.part_split * 2 * d.Q * d.N * 4);
+        w.gterm = take(tok * (mfma ? 1 : 2 * nn));
+        w.sterm = take(tok * (mfma ? 1 : 2 * nn));
+        if (mfma) w.gintra = take(tok);
+        if (!mfma) w.erow = take(tok * 2 * nt);
+        if (!mfma) w.ecol = take(tok * 2 * nt);
+        w.fterm = take(tok * (mfma ? 1 : 2 * np));
+        w.dDrow = take(tok * (mfma ? 1 : 2 * np));
         w.tail_part = take((size_t)d.Bt * d.H * d.nc * w.nslice * 4);
         w.dA_part = take((size_t)d.Bt * d.nc * d.H * 4);
         w.dD_part = take((size_t)d.Bt * d.nc * d.H * 4);
@@ -112,8 +123,9 @@ void bind_workspace(SegParams& sp, const WsLayout& w, void* workspace, bool bwd)
     sp.states = (float*)at(w.states);
     sp.Gm = (float*)(base + w.Gm);
     sp.nslice = w.nslice;
-    sp.ein = (float*)(base + w.ein);
-    sp.eout = (float*)(base + w.eout);
+    sp.ein = (float*)at(w.ein);
+    sp.eout = (float*)at(w.eout);
+    sp.tok_stride = (int64_t)(w.tok / 4);
     sp.states_bf = (bf16_t*)at(w.states_bf);
     sp.dg_split = w.dg_split;
     sp.part_split = w.part_split;
@@ -124,7 +136,9 @@ void bind_workspace(SegParams& sp, const WsLayout& w, void* workspace, bool bwd)
         sp.dG = (float*)(base + w.dG);
         sp.gterm = (float*)(base + w.gterm);
         sp.sterm = (float*)(base + w.sterm);
-        sp.gintra = (float*)(base + w.gintra);
+        sp.gintra = (float*)at(w.gintra);
+        sp.erow = (float*)at(w.erow);
+        sp.ecol = (float*)at(w.ecol);
         sp.fterm = (float*)(base + w.fterm);
         sp.dDrow = (float*)(base + w.dDrow);
         sp.tail_part = (float*)(base + w.tail_part);
@@ -371,7 +385,8 @@ static void span_tokens(SegParams& sp, const Dims& d, int64_t k, int64_t ns) {
 
 // Head slices of the per-slice partial sums for a span shorter than the workspace was laid out for: as many as its
 // place holds (a short span has fewer chunks to spread over the machine).
-static void fit_splits(SegParams& sp, const WsLayout& w, const Dims& d) {
+static void fit_splits(SegParams& sp, const WsLayout& w, const Dims& d, bool mfma) {
+    if (!mfma) return;  // a few slices whatever the span
     auto fit = [&](int split) {
         const int64_t room = (int64_t)d.nc * split;
         int best = split;
@@ -608,7 +623,7 @@ extern "C" int ssd_bwd(const ssd_shape_t* shape, const void* x, const void* dt, 
         const int64_t t0 = k * d.s;
         const int HP = d.H * d.P, GN = d.G * d.N;
         span_tokens(sp, d, k, ns);
-        fit_splits(sp, w, d);
+        fit_splits(sp, w, d, mfma);
         sp.x = off(x, t0 * HP, d.esz);
         sp.dy = off(dy, t0 * HP, d.esz);
         sp.dx = off(dx, t0 * HP, d.esz);

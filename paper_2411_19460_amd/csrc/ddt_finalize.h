@@ -6,73 +6,102 @@
 
 namespace ssdk {
 
-// One workgroup (blockDim.x threads, a power of two >= Q) per (chunk c, head h, batch b); s and s2 are two arrays
-// of blockDim.x floats in LDS; store(index into ddt, value) writes one element of ddt in its storage type.
-template <class Store>
-__device__ __forceinline__ void ddt_finalize_body(const SegParams& sp, float* s, float* s2, int c, int h, int b, Store store) {
-    const int i = threadIdx.x;
-    const int Q = sp.Q;
+constexpr int DDT_THREADS = 256, DDT_E = 4;  // threads per workgroup; tokens per thread at most (chunks of up to 1024)
+
+struct DdtLds {
+    float tot[DDT_THREADS / 64], stot[DDT_THREADS / 64], tail[DDT_THREADS / 64], pa[DDT_THREADS / 64], pd[DDT_THREADS / 64];
+};
+
+// Per token: g = gradient of cum without the state term s (dcum = g - s), f = the direct part of ddt, d = dY . x.
+struct DdtIn {
+    float g, s, f, d;
+};
+
+static __device__ __forceinline__ float wave_sum(float v) {
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// One workgroup of DDT_THREADS per (chunk c, head h, batch b).  load(offset of the chunk and head + i, i) returns what
+// the passes before left for token i; store(index into ddt, value) writes one element of ddt in its storage type.
+// Sums run inside the waves (lane exchanges) and then over the four waves: three barriers in all, where a scan over LDS
+// took two per doubling (it was half of the launch it rides in for a few chunks).
+template <class Load, class Store>
+__device__ __forceinline__ void ddt_finalize_body(const SegParams& sp, DdtLds& L, int c, int h, int b, Load load, Store store) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int Q = sp.Q, V = chunk_rows(sp, c, Q), E = (Q + DDT_THREADS - 1) / DDT_THREADS;
     const int64_t cbase = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
-    // reverse order so that an inclusive forward scan yields the suffix sums
-    const int ri = Q - 1 - i;
-    // Matrix-core path: the gradient of cum_i arrives as gterm_i + gintra_i - sterm_i, and the gradient of
-    // cum at the chunk end carries + sum_j sterm_j (the chunk state depends on T - cum_j): the very same
-    // sterm values enter with both signs, so their cancellation in the suffix sums is exact.
-    float gt = 0.f, st_sum = 0.f;
-    const bool split = sp.flags & SSD_INTERNAL_SPLIT_GTERM;
-    if (i < Q) {
-        gt = sp.gterm[cbase + ri];
-        if (split) {
-            const float sv = sp.sterm[cbase + ri];
-            gt += sp.gintra[cbase + ri] - sv;
-            st_sum = sv;
-        }
+    // The gradient of cum_i arrives as g - s, and the gradient of cum at the chunk end carries + sum_j s_j (the chunk
+    // state depends on T - cum_j): the very same s values enter with both signs, so their cancellation in the suffix
+    // sums is exact.  Thread t owns tokens Q - 1 - t E - e: a prefix sum over the threads is a suffix sum over tokens.
+    float da[DDT_E], f[DDT_E], d[DDT_E], run = 0.f, ssum = 0.f;
+#pragma unroll
+    for (int e = 0; e < DDT_E; ++e) {
+        const int i = Q - 1 - (tid * E + e);
+        DdtIn v = {0.f, 0.f, 0.f, 0.f};
+        if (e < E && i >= 0 && i < V) v = load(cbase + i, i);
+        run += v.g - v.s;
+        ssum += v.s;
+        da[e] = run;
+        f[e] = v.f;
+        d[e] = v.d;
     }
-    if (split) {
-        s2[i] = st_sum;
-        __syncthreads();
-        for (int off = blockDim.x >> 1; off > 0; off >>= 1) {
-            if (i < off) s2[i] += s2[i + off];
-            __syncthreads();
-        }
-        st_sum = s2[0];
-        __syncthreads();
+    float incl = run;
+    for (int off = 1; off < 64; off <<= 1) {
+        const float v = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += v;
     }
-    s[i] = gt;
-    __syncthreads();
-    for (int off = 1; off < (int)blockDim.x; off <<= 1) {
-        const float v = (i >= off) ? s[i - off] : 0.f;
-        __syncthreads();
-        s[i] += v;
-        __syncthreads();
-    }
+    const float* tp = sp.tail_part + (((int64_t)b * sp.H + h) * sp.nc + c) * sp.nslice;
     float tail = 0.f;
-    const float* tp = sp.tail_part + ((((int64_t)b * sp.H + h) * sp.nc + c)) * sp.nslice;
-    for (int k = 0; k < sp.nslice; ++k) tail += tp[k];
-    tail += st_sum;
+    for (int k = tid; k < sp.nslice; k += DDT_THREADS) tail += tp[k];
+    tail = wave_sum(tail);
+    ssum = wave_sum(ssum);
+    if (lane == 63) {
+        L.tot[w] = incl;
+        L.stot[w] = ssum;
+        L.tail[w] = tail;
+    }
+    __syncthreads();
+    float before = incl - run, end = 0.f;
+#pragma unroll
+    for (int q = 0; q < DDT_THREADS / 64; ++q) {
+        before += q < w ? L.tot[q] : 0.f;
+        end += L.stot[q] + L.tail[q];
+    }
     float pa = 0.f, pd = 0.f;
-    if (i < Q) {
-        const float da = s[i] + tail;  // belongs to token ri
-        const float d = sp.dtf[cbase + ri];
-        if (ri < chunk_rows(sp, c, Q)) store((int64_t)b * sp.dts_b + ((int64_t)c * Q + ri) * sp.H + h, sp.A[h] * da + sp.fterm[cbase + ri]);
-        pa = d * da;
-        pd = sp.dDrow[cbase + ri];
-    }
-    __syncthreads();
-    s[i] = pa;
-    s2[i] = pd;
-    __syncthreads();
-    for (int off = blockDim.x >> 1; off > 0; off >>= 1) {
-        if (i < off) {
-            s[i] += s[i + off];
-            s2[i] += s2[i + off];
+    const float A = sp.A[h];
+#pragma unroll
+    for (int e = 0; e < DDT_E; ++e) {
+        const int i = Q - 1 - (tid * E + e);
+        if (e < E && i >= 0 && i < V) {
+            const float g = before + da[e] + end;
+            store((int64_t)b * sp.dts_b + ((int64_t)c * Q + i) * sp.H + h, A * g + f[e]);
+            pa += sp.dtf[cbase + i] * g;
+            pd += d[e];
         }
-        __syncthreads();
     }
-    if (i == 0) {
-        sp.dA_part[((int64_t)b * sp.nc_total + sp.chunk0 + c) * sp.H + h] = s[0];
-        sp.dD_part[((int64_t)b * sp.nc_total + sp.chunk0 + c) * sp.H + h] = s2[0];
+    pa = wave_sum(pa);
+    pd = wave_sum(pd);
+    if (lane == 0) {
+        L.pa[w] = pa;
+        L.pd[w] = pd;
     }
+    __syncthreads();
+    if (tid == 0) {
+        float a = 0.f, s = 0.f;
+#pragma unroll
+        for (int q = 0; q < DDT_THREADS / 64; ++q) {
+            a += L.pa[q];
+            s += L.pd[q];
+        }
+        sp.dA_part[((int64_t)b * sp.nc_total + sp.chunk0 + c) * sp.H + h] = a;
+        sp.dD_part[((int64_t)b * sp.nc_total + sp.chunk0 + c) * sp.H + h] = s;
+    }
+}
+
+// What the matrix-core passes leave per token.
+static __device__ __forceinline__ DdtIn ddt_load_mfma(const SegParams& sp, int64_t o) {
+    return {sp.gterm[o] + sp.gintra[o], sp.sterm[o], sp.fterm[o], sp.dDrow[o]};
 }
 
 }  // namespace ssdk

@@ -13,7 +13,7 @@
 //                 cancellation in the reverse cumulative sum is exact.
 //   mk_dBC_part : the two head sums on the right, same organisation, accumulators [Q x 128] per
 //                 (chunk, role, slice); the per-token weight is folded into the staged operand.
-//   mk_dBC_final: sums the slices, contracts dG with B / dG^T with C, adds the head sums, rounds once.
+//   mk_final_ddt: sums the slices, contracts dG with B / dG^T with C, adds the head sums, rounds once.
 // The decay of an off-diagonal tile is the product of a per-row factor, a per-column factor and a
 // per-tile scalar, all <= 1 (32-token granularity); diagonal tiles evaluate exp() per element.
 #include "ddt_finalize.h"
@@ -770,30 +770,26 @@ __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, in
         if (32 * R + acc_row(r, lane) < nv) out[(int64_t)(32 * R + acc_row(r, lane)) * bt + 32 * w + (lane & 31)] = float_to_bf16(acc[r]);
 }
 
-template <int Q>
-__global__ __launch_bounds__(NTH) void mk_dBC_final(SegParams sp) {
-    __shared__ __attribute__((aligned(16))) FinLds<Q> L;
-    final_body<Q>(sp, L, blockIdx.x);
-}
-
 // The two steps behind the head-walking passes -- dB / dC from the partial sums, and ddt with the chunk's dA / dD
-// partial sums from the per-token scalars -- as one launch (chunk 256: both run 256 threads per workgroup): the
+// partial sums from the per-token scalars -- as one launch (both run 256 threads per workgroup): the
 // first n_final workgroups do the former, the rest one (chunk, head) of the latter each.
+template <int Q>
 union FinDdtLds {
-    FinLds<256> fin;
-    float s[2][256];
+    FinLds<Q> fin;
+    DdtLds ddt;
 };
 
+template <int Q>
 __global__ __launch_bounds__(NTH) void mk_final_ddt(SegParams sp, int n_final) {
-    __shared__ __attribute__((aligned(16))) FinDdtLds L;
+    __shared__ __attribute__((aligned(16))) FinDdtLds<Q> L;
     int z = blockIdx.x;
     if (z < n_final) {
-        final_body<256>(sp, L.fin, z);
+        final_body<Q>(sp, L.fin, z);
     } else {
         z -= n_final;
         const int c = z % sp.nc;
         z /= sp.nc;
-        ddt_finalize_body(sp, L.s[0], L.s[1], c, z % sp.H, z / sp.H,
+        ddt_finalize_body(sp, L.ddt, c, z % sp.H, z / sp.H, [&](int64_t o, int) { return ddt_load_mfma(sp, o); },
                           [&](int64_t idx, float v) { ((bf16_t*)sp.ddt)[idx] = float_to_bf16(v); });
     }
 }
@@ -813,10 +809,7 @@ hipError_t grad_bc_q(const SegParams& sp0, bool with_dual, hipStream_t st) {
         SSDK_LAUNCH(K_MFMA_DBC, st, mk_dBC_part<Q>, dim3(n_part), dim3(PartCfg<Q>::NTHR), sp);
     }
     const int n_final = sp.Bt * sp.nc * sp.G * 2 * (Q / 32);
-    if (Q == 256 && (sp.flags & SSD_INTERNAL_SPLIT_GTERM))  // the caller has asked for the scalar step in the same launch
-        SSDK_LAUNCH(K_MFMA_FINAL_DDT, st, mk_final_ddt, dim3(n_final + sp.nc * sp.H * sp.Bt), dim3(NTH), sp, n_final);
-    else
-        SSDK_LAUNCH(K_MFMA_DBC_FINAL, st, mk_dBC_final<Q>, dim3(n_final), dim3(NTH), sp);
+    SSDK_LAUNCH(K_MFMA_FINAL_DDT, st, mk_final_ddt<Q>, dim3(n_final + sp.nc * sp.H * sp.Bt), dim3(NTH), sp, n_final);
     return hipSuccess;
 }
 

@@ -415,13 +415,9 @@ hipError_t bwd_q(const SegParams& sp0, hipStream_t st) {
     const bool trio = Q == 256;
     hipError_t e = trio ? hipSuccess : mfma_launch_dual(sp, 2, st);
     if (e != hipSuccess) return e;
-    sp.flags |= SSD_INTERNAL_SPLIT_GTERM;  // the gradient of cum arrives in three pieces
-    e = mfma_launch_grad_bc(sp, trio, st);   // chunk 256: ddt and the dA / dD partial sums ride in its last launch
+    e = mfma_launch_grad_bc(sp, trio, st);   // ddt and the dA / dD partial sums ride in its last launch
     if (e != hipSuccess) return e;
-    if (Q != 256) {
-        e = generic_backward_scalars(sp, st);
-        if (e != hipSuccess) return e;
-    } else if (!sp.defer_param) {
+    if (!sp.defer_param) {
         e = launch_param_reduce(sp, st);
         if (e != hipSuccess) return e;
     }

@@ -9,10 +9,6 @@
 
 namespace ssdk {
 
-// Internal flag (never accepted from callers): the gradient of cum arrives in three pieces,
-// gterm - sterm + gintra (matrix-core path).
-constexpr uint32_t SSD_INTERNAL_SPLIT_GTERM = 1u << 31;
-
 // bf16 storage as raw bits; conversion is round-to-nearest-even.
 struct bf16_t {
     uint16_t v;
@@ -73,10 +69,15 @@ struct SegParams {
     float* states;     // generic path only: [Bt][nc+1][H][P][N]  slot c: state entering chunk c; slot nc: state leaving the segment
     float* dstates;    // generic path only: [Bt][nc][H][P][N]    slot c: adjoint of the state leaving chunk c
     float* Gm;         // [Bt][nc][G][Q][Q]    C_i . B_j   (generic path: fp32)
-    float* dG;         // generic path: [Bt][nc][G][Q][Q] fp32 head-summed masked dY X^T; MFMA path: [Bt][nc][G][dg_split][Q/32][Q/32][32][32] bf16 per-slice sums, tile by tile
-    float* gterm;      // [Bt][H][nc][Q]  gradient of cum, per token (MFMA path: the part through the entering state)
-    float* sterm;      // [Bt][H][nc][Q]  MFMA path: dt_j x_j . (part of u_j through the leaving adjoint); subtracted
+    float* dG;         // generic path: [Bt][nc][G][dg_split][Q][Q] fp32 per-slice sums of masked dY X^T; MFMA path: [Bt][nc][G][dg_split][Q/32][Q/32][32][32] bf16 per-slice sums, tile by tile
+    // Per-token scalars; on the generic path gterm, sterm, erow, ecol, fterm and dDrow are partial sums over pieces of 32
+    // columns (or rows) of a tile, piece k at k tok_stride.
+    int64_t tok_stride;
+    float* gterm;      // [Bt][H][nc][Q]  gradient of cum, per token: the part through the entering state
+    float* sterm;      // [Bt][H][nc][Q]  dt_j x_j . (part of u_j through the leaving adjoint); subtracted
     float* gintra;     // [Bt][H][nc][Q]  MFMA path: chunk-local part (row sums minus column sums of E); added
+    float* erow;       // generic path: row sums of E, piece k = columns 32 k ..
+    float* ecol;       // generic path: column sums of E, piece k = rows 32 k ..
     float* fterm;      // [Bt][H][nc][Q]
     float* dDrow;      // [Bt][H][nc][Q]
     float* tail_part;  // [Bt][H][nc][nslice]
@@ -179,9 +180,10 @@ constexpr float RESET_LOG_DECAY = -100.f;
 // Byte offsets of the per-segment scratch arrays inside the caller's workspace (WS_NONE: the array
 // does not exist on the chosen kernel path and its pointer stays null).
 constexpr size_t WS_NONE = ~(size_t)0;
+constexpr int GENERIC_SLICES = 4;  // head slices of the shape-generic kernels' partial sums, at most
 struct WsLayout {
     size_t cum, dtf, states, Gm, dstates, dG, gterm, fterm, dDrow, tail_part, dA_part, dD_part, dcarry, total;
-    size_t ein, eout, states_bf, dstates_bf, dbc_part, sterm, gintra;
+    size_t ein, eout, states_bf, dstates_bf, dbc_part, sterm, gintra, erow, ecol, tok;
     int nslice, dg_split, part_split;
 };
 
@@ -208,23 +210,23 @@ enum KernelId {
 bool prof_events(int kid, hipEvent_t* start, hipEvent_t* stop);
 
 // Launch on `st`, timed when enabled; returns the launch error from the enclosing function.
-#define SSDK_LAUNCH(kid, st, kernel, grid, block, ...)                                        \
+#define SSDK_LAUNCH_LDS(kid, st, kernel, grid, block, lds, ...)                               \
     do {                                                                                      \
         hipEvent_t ea_ = nullptr, eb_ = nullptr;                                              \
         if (::ssdk::prof_events(kid, &ea_, &eb_))                                             \
-            hipExtLaunchKernelGGL(kernel, grid, block, 0, st, ea_, eb_, 0, __VA_ARGS__);      \
+            hipExtLaunchKernelGGL(kernel, grid, block, lds, st, ea_, eb_, 0, __VA_ARGS__);    \
         else                                                                                  \
-            hipLaunchKernelGGL(kernel, grid, block, 0, st, __VA_ARGS__);                      \
+            hipLaunchKernelGGL(kernel, grid, block, lds, st, __VA_ARGS__);                    \
         hipError_t e_ = hipGetLastError();                                                    \
         if (e_ != hipSuccess) return e_;                                                      \
     } while (0)
+#define SSDK_LAUNCH(kid, st, kernel, grid, block, ...) SSDK_LAUNCH_LDS(kid, st, kernel, grid, block, 0, __VA_ARGS__)
 
 // Launchers.  Each returns hipSuccess or the launch error.  is_bf16 selects the storage type.
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t st);
 hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t st);
 hipError_t generic_forward_segment(const SegParams& sp, bool is_bf16, bool need_y, hipStream_t st);
 hipError_t generic_backward_segment(const SegParams& sp, bool is_bf16, hipStream_t st);
-hipError_t generic_backward_scalars(const SegParams& sp, hipStream_t st);
 // dA, dD = (or +=, under sp.accumulate) the sum of the partial sums of all sp.nc_total chunks.
 hipError_t launch_param_reduce(const SegParams& sp, hipStream_t st);
 
