@@ -181,9 +181,35 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+_raw_stream = None
+
+
 def _stream(t) -> Optional[int]:
-    import torch
-    return torch.cuda.current_stream(t.device).cuda_stream or None
+    # the raw handle: building a torch.cuda.Stream object costs as much as a whole launch
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        _raw_stream = torch._C._cuda_getCurrentRawStream
+    return _raw_stream(t.get_device()) or None
+
+
+# Shape descriptors by what they are made from, with the by-reference argument the library takes: filling the 13 fields
+# anew costs more than launching the recurrence kernel of one token.  Read only; bounded; an entry is replaced, never changed.
+_shapes: dict = {}
+
+
+def _shape_ref(x, Bm, chunk: int, segment: Optional[int], seq_reset):
+    if seq_reset is not None:   # holds a pointer: made for the call
+        shape = make_shape(x, Bm, chunk, segment, seq_reset)
+        return shape, ctypes.byref(shape)
+    key = (x.dtype, x.shape, Bm.shape, chunk, segment)
+    hit = _shapes.get(key)
+    if hit is None:
+        if len(_shapes) >= 256:
+            _shapes.clear()
+        shape = make_shape(x, Bm, chunk, segment)
+        hit = _shapes[key] = (shape, ctypes.byref(shape))
+    return hit
 
 
 def make_shape(x, Bm, chunk: int, segment: Optional[int] = None, seq_reset=None) -> ssd_shape_t:
@@ -209,6 +235,22 @@ def ssd_workspace_bytes(shape: ssd_shape_t, is_backward: bool, flags: int = 0) -
 
 
 def _check_inputs(x, dt, A, Bm, Cm, D, *more):
+    d = x.dtype
+    if (x.is_cuda and dt.is_cuda and Bm.is_cuda and Cm.is_cuda and A.is_cuda and D.is_cuda and dt.dtype is d and Bm.dtype is d
+            and Cm.dtype is d and x.is_contiguous() and dt.is_contiguous() and Bm.is_contiguous() and Cm.is_contiguous()
+            and A.is_contiguous() and D.is_contiguous()):
+        for t in more:
+            if t is not None and not (t.is_cuda and t.is_contiguous()):
+                break
+        else:
+            import torch
+            if A.dtype is torch.float32 and D.dtype is torch.float32:
+                return
+    _refuse_inputs(x, dt, A, Bm, Cm, D, *more)
+
+
+def _refuse_inputs(x, dt, A, Bm, Cm, D, *more):
+    """Names what is wrong with them."""
     import torch
     for t in (x, dt, Bm, Cm) + tuple(m for m in more if m is not None):
         if not t.is_cuda or not t.is_contiguous():
@@ -240,7 +282,7 @@ def ssd_fwd(x, dt, A, B, C, D, chunk, segment=None, init_state=None, flags=0, wo
     `out` may carry preallocated tensors under the keys y, final_state, boundary_states."""
     import torch
     _check_inputs(x, dt, A, B, C, D, init_state)
-    shape = make_shape(x, B, chunk, segment, seq_reset)
+    shape, ref = _shape_ref(x, B, chunk, segment, seq_reset)
     Bt, L, H, P = x.shape
     N = B.shape[3]
     out = out or {}
@@ -254,10 +296,9 @@ def ssd_fwd(x, dt, A, B, C, D, chunk, segment=None, init_state=None, flags=0, wo
         ck = torch.bfloat16 if flags & SSD_FLAG_BF16_CHECKPOINTS else torch.float32
         bnd = torch.empty((Bt, nseg, H, P, N), dtype=ck, device=x.device)
     _check_boundary(bnd, flags)
-    need = ssd_workspace_bytes(shape, False, flags)
-    if workspace is None:
-        workspace = _workspace(need, x.device)
-    rc = lib().ssd_fwd(ctypes.byref(shape), _ptr(x), _ptr(dt), _ptr(A), _ptr(B), _ptr(C), _ptr(D), _ptr(init_state),
+    if workspace is None:   # the library checks the size of a given one
+        workspace = _workspace(int(lib().ssd_workspace_bytes_flags(ref, 0, flags)), x.device)
+    rc = lib().ssd_fwd(ref, _ptr(x), _ptr(dt), _ptr(A), _ptr(B), _ptr(C), _ptr(D), _ptr(init_state),
                        _ptr(y), _ptr(final), _ptr(bnd), _ptr(workspace), workspace.numel(), flags, _stream(x))
     if rc != 0:
         raise SSDError(rc, "ssd_fwd")
@@ -293,12 +334,12 @@ def ssd_decode(x, dt, A, B, C, D, state, flags=0, out=None, seq_reset=None):
     updated in place."""
     import torch
     _check_inputs(x, dt, A, B, C, D, state)
-    if state.dtype != torch.float32:
+    if state.dtype is not torch.float32:
         raise TypeError("state must be fp32")
-    shape = make_shape(x, B, 1, None, seq_reset)
+    _, ref = _shape_ref(x, B, 1, None, seq_reset)
     y = out if out is not None else torch.empty_like(x)
-    rc = lib().ssd_decode(ctypes.byref(shape), _ptr(x), _ptr(dt), _ptr(A), _ptr(B), _ptr(C), _ptr(D), _ptr(state),
-                          _ptr(y), flags, _stream(x))
+    rc = (_lib or lib()).ssd_decode(ref, x.data_ptr(), dt.data_ptr(), A.data_ptr(), B.data_ptr(), C.data_ptr(), D.data_ptr(), state.data_ptr(),
+                                    y.data_ptr(), flags, _stream(x))
     if rc != 0:
         raise SSDError(rc, "ssd_decode")
     return y
@@ -675,7 +716,7 @@ def ssd_bwd(x, dt, A, B, C, D, dy, chunk, segment=None, init_state=None, dfinal_
     dinit_state."""
     import torch
     _check_inputs(x, dt, A, B, C, D, dy, init_state, dfinal_state, boundary_states)
-    shape = make_shape(x, B, chunk, segment, seq_reset)
+    shape, ref = _shape_ref(x, B, chunk, segment, seq_reset)
     Bt, L, H, P = x.shape
     N = B.shape[3]
     out = out or {}
@@ -691,10 +732,9 @@ def ssd_bwd(x, dt, A, B, C, D, dy, chunk, segment=None, init_state=None, dfinal_
     if dinit is None and want_dinit:
         dinit = torch.empty((Bt, H, P, N), dtype=torch.float32, device=x.device)
     _check_boundary(boundary_states, flags)
-    need = ssd_workspace_bytes(shape, True, flags)
     if workspace is None:
-        workspace = _workspace(need, x.device)
-    rc = lib().ssd_bwd(ctypes.byref(shape), _ptr(x), _ptr(dt), _ptr(A), _ptr(B), _ptr(C), _ptr(D), _ptr(init_state),
+        workspace = _workspace(int(lib().ssd_workspace_bytes_flags(ref, 1, flags)), x.device)
+    rc = lib().ssd_bwd(ref, _ptr(x), _ptr(dt), _ptr(A), _ptr(B), _ptr(C), _ptr(D), _ptr(init_state),
                        _ptr(dy), _ptr(dfinal_state), _ptr(boundary_states), _ptr(dx), _ptr(ddt), _ptr(dA), _ptr(dB),
                        _ptr(dC), _ptr(dD), _ptr(dinit), _ptr(workspace), workspace.numel(), flags, _stream(x))
     if rc != 0:
