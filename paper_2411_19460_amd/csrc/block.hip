@@ -166,6 +166,7 @@ struct BlockWs {
     size_t un, zx, x, B, C, dt, y, yn;                      // forward activations of the segment
     size_t dun, dyn, dy, dzx, dx, dB, dC, ddt;              // backward
     size_t dssm[2], dconv[2], dtpart, inner, total;
+    size_t xp, gp, xsq, gsq;                                // generation: packed operands of the two products and their sums of squares
     size_t cssm[2], cconv[2];                               // states handed from segment to segment when no checkpoints are kept
     size_t inner_bytes;
 };
@@ -216,6 +217,12 @@ BlockWs layout(const BlockDims& d, bool bwd) {
         inner = b > inner ? b : inner;
         inner = c > inner ? c : inner;
         inner = e > inner ? e : inner;
+    }
+    if (!bwd) {
+        w.xp = take((size_t)FEW_ROWS * d.dm * 2);
+        w.gp = take((size_t)FEW_ROWS * d.d_inner * 2);
+        w.xsq = take((size_t)FEW_ROWS * ((d.dm + 15) / 16) * 4);
+        w.gsq = take((size_t)FEW_ROWS * d.H * ((d.P + 7) / 8) * 4);
     }
     for (int i = 0; i < 2; ++i) w.cssm[i] = take(d.HPN * 4);
     for (int i = 0; i < 2; ++i) w.cconv[i] = take((size_t)3 * d.conv_dim * 2);
@@ -315,6 +322,10 @@ struct FewSeqs {
     int64_t ssm_bs = 0, conv_in_bs = 0, conv_out_bs = 0;
     void* conv_final = nullptr;
     size_t conv_final_bs = 0;
+    // a stack's layers with more rows than the vector-ALU kernels take: the input is packed already (by the layer before),
+    // and the output is to be packed for the layer behind, whose norm weight (null: none) is next_norm
+    bool packed_in = false, pack_next = false;
+    const float* next_norm = nullptr;
 };
 
 int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_block_params_t* p, char* ws, const BlockWs& w,
@@ -322,51 +333,21 @@ int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_blo
                 const void* res, const FewSeqs& sq, hipStream_t st) {
     const int rows = (int)tokens * sq.nb;  // rows of every product: sequence-major, the tokens of a sequence in order
     if (sq.nb > 1 && ssm_in != ssm_out) return SSD_ERR_ARG;
-    const bool fold = rows <= FEW_ROWS_VALU;  // few enough rows for the normalisations to ride on the products
     FewRowsJob in;
     memset(&in, 0, sizeof(in));
     in.rows = rows;
     in.K = d.dm;
     in.N = d.d_in_proj;
-    in.mode = p->pre_norm_w && fold ? 1 : 0;
+    in.mode = p->pre_norm_w ? 1 : 0;
     in.x = u;
-    if (p->pre_norm_w && !fold) {
-        const void* un;
-        BLK_TRY(seg_pre_norm(d, sh->eps, p, ws, w, u, rows, &un, st));
-        in.x = un;
-    }
-    in.ldx = d.dm;
-    in.w = p->W_in;
-    in.out = ws + w.zx;
-    in.ldo = d.d_in_proj;
-    in.in_w = p->pre_norm_w;
-    in.eps = sh->eps;
-    BLK_HIP(launch_linear_few_rows(in, st));
-    if (ssm_in != ssm_out) BLK_HIP(ssm_in ? launch_copy_f32(ssm_out, ssm_in, d.HPN, st) : launch_fill_zero(ssm_out, d.HPN, st));
-    // many sequences, a token each, their convolution states updated where they are: two kernels (see ConvStepJob)
-    const bool split_mid = sq.nb > FEW_ROWS_VALU && tokens == 1 && conv_in && sq.conv_final == conv_in && sq.conv_final_bs == (size_t)sq.conv_in_bs * 2;
-    if (split_mid) {
-        ConvStepJob cj;
-        memset(&cj, 0, sizeof(cj));
-        cj.nb = sq.nb;
-        cj.H = d.H;
-        cj.P = d.P;
-        cj.G = d.G;
-        cj.N = d.N;
-        cj.zx = ws + w.zx;
-        cj.ld = d.d_in_proj;
-        cj.conv_w = p->conv_w;
-        cj.conv_b = p->conv_b;
-        cj.dt_bias = p->dt_bias;
-        cj.cs = sq.conv_final;
-        cj.cs_bs = sq.conv_in_bs;
-        cj.x = ws + w.x;
-        cj.B = ws + w.B;
-        cj.C = ws + w.C;
-        cj.dt = ws + w.dt;
-        BLK_HIP(launch_conv_step(cj, st));
-        BLK_HIP(launch_decode_strided(sq.nb, d.H, d.P, d.G, d.N, ws + w.x, ws + w.dt, p->A, ws + w.B, ws + w.C, p->D, ssm_out, sq.ssm_bs,
-                                      ws + w.y, st));
+    if (sq.packed_in) {
+        in.mode = 2;
+        in.x = ws + w.xp;
+        if (p->pre_norm_w) {
+            in.ssq = (const float*)(ws + w.xsq);
+            in.nparts = (d.dm + 15) / 16;
+            in.groups = 1;
+        }
     }
     DecodeMidJob mid;
     memset(&mid, 0, sizeof(mid));
@@ -390,7 +371,38 @@ int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_blo
     mid.cs_out = conv_out;
     mid.state = ssm_out;
     mid.y = ws + w.y;
-    if (!split_mid) BLK_HIP(launch_decode_mid(mid, st));
+    const bool stepped = tokens == 1 && conv_in && sq.conv_final == conv_in && (sq.nb == 1 || sq.conv_final_bs == (size_t)sq.conv_in_bs * 2) &&
+                         step_supported(mid);
+    mid.stepped = stepped;
+    in.ldx = d.dm;
+    in.w = p->W_in;
+    in.out = ws + w.zx;
+    in.ldo = d.d_in_proj;
+    in.in_w = p->pre_norm_w;
+    in.eps = sh->eps;
+    // one token per sequence with the convolution states updated where they are: the step rides on the product
+    if (stepped) {
+        in.cs = sq.conv_final;
+        in.cs_bs = sq.conv_in_bs;
+        in.conv_w = p->conv_w;
+        in.conv_b = p->conv_b;
+        in.dt_bias = p->dt_bias;
+        in.off_xbc = d.off_xbc;
+        in.off_dt = d.off_dt;
+    }
+    BLK_HIP(launch_linear_few_rows(in, st));
+    if (ssm_in != ssm_out) BLK_HIP(ssm_in ? launch_copy_f32(ssm_out, ssm_in, d.HPN, st) : launch_fill_zero(ssm_out, d.HPN, st));
+    // the gate rides on the recurrence kernel, the normalisation on the output product: few rows of one group on the
+    // vector ALUs, more on the matrix cores with the operand packed by the recurrence kernel
+    const bool valu = rows <= FEW_ROWS_VALU;
+    const bool pack = stepped && !valu && (d.G == 1 || (d.G <= 8 && d.d_inner / d.G % 256 == 0));
+    mid.gate = pack || (valu && d.G == 1);
+    if (pack) {
+        mid.pack = ws + w.gp;
+        mid.pack_w = p->norm_w;
+        mid.pack_ssq = (float*)(ws + w.gsq);
+    }
+    BLK_HIP(launch_decode_mid(mid, st));
     FewRowsJob o;
     memset(&o, 0, sizeof(o));
     o.rows = rows;
@@ -402,12 +414,22 @@ int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_blo
     o.ldx = d.d_inner;
     o.res = res;
     o.ldres = d.dm;
-    if (d.G == 1 && fold) {  // one group: the gated normalisation rides on the product
+    if (sq.pack_next) {
+        o.pack_out = ws + w.xp;
+        o.pack_w = sq.next_norm;
+        o.pack_ssq = (float*)(ws + w.xsq);
+    }
+    if (pack) {
         o.mode = 2;
+        o.x = ws + w.gp;
+        o.ssq = (const float*)(ws + w.gsq);
+        o.nparts = step_parts(mid) / d.G;
+        o.groups = d.G;
+        o.eps = sh->eps;
+    } else if (mid.gate) {
+        o.mode = 1;
         o.x = ws + w.y;
         o.in_w = p->norm_w;
-        o.z = ws + w.zx;
-        o.ldz = d.d_in_proj;
         o.eps = sh->eps;
     } else {
         BLK_TRY(seg_norm(d, sh, p, ws, w, ws + w.zx, ws + w.y, rows, st));
@@ -416,7 +438,7 @@ int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_blo
     // the new convolution states move to their place on the back of the last launch where its threads suffice
     const size_t cs_bytes = (size_t)3 * d.conv_dim * 2;
     bool moved = false;
-    if (sq.conv_final && !split_mid) {
+    if (sq.conv_final && !stepped) {
         o.copy_src = conv_out;
         o.copy_dst = sq.conv_final;
         o.copy_bytes = cs_bytes;
@@ -431,7 +453,7 @@ int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_blo
         }
     }
     BLK_HIP(launch_linear_few_rows(o, st));
-    if (sq.conv_final && !moved && !split_mid)
+    if (sq.conv_final && !stepped && !moved)
         for (int b = 0; b < sq.nb; ++b)  // bf16 pairs as words
             BLK_HIP(launch_copy_f32((float*)((char*)sq.conv_final + b * sq.conv_final_bs),
                                     (const float*)((const char*)conv_out + (size_t)b * sq.conv_out_bs * 2), cs_bytes / 4, st));
@@ -926,6 +948,7 @@ extern "C" int magc_blockstack_infer(const magc_blockstack_shape_t* sh, const ma
         const bool zero = fresh && k == 0;
         // a few tokens: the recurrence runs on the layer's SSM state itself; a segment: through a spare state
         const bool in_place = rows <= DECODE_ROWS;
+        bool packed = false;  // the layer before has left this one's packed input
         const char* cur = (const char*)x0 + (size_t)t0 * row;
         for (int j = 0; j < d.NL; ++j) {
             float* sj = ssm_state + (size_t)j * d.b.HPN;
@@ -938,6 +961,12 @@ extern "C" int magc_blockstack_infer(const magc_blockstack_shape_t* sh, const ma
                 // generation: the residual and the move of the convolution state ride on the output product
                 FewSeqs sq;
                 sq.conv_final = cj;
+                if (rows > FEW_ROWS_VALU) {
+                    const bool next = j + 1 < d.NL && few_path(dc, &params[j + 1], rows, ssm_out, nxt, out);
+                    sq.packed_in = packed;
+                    sq.pack_next = packed = next;
+                    sq.next_norm = next ? params[j + 1].pre_norm_w : nullptr;
+                }
                 conv_moved = true;
                 BLK_TRY(forward_few(dc, &c, &params[j], bws, bw, cur, rows, zero ? nullptr : sj, zero ? nullptr : cj, ssm_out,
                                     ws + w.fin_conv, nxt, cur, sq, st));
@@ -998,6 +1027,11 @@ extern "C" int magc_blockstack_decode(const magc_blockstack_shape_t* sh_in, cons
         sq.conv_out_bs = (int64_t)3 * d.b.conv_dim;
         sq.conv_final = cj;
         sq.conv_final_bs = (size_t)d.NL * d.conv_state;
+        if (nseq > FEW_ROWS_VALU) {
+            sq.packed_in = j > 0;
+            sq.pack_next = j + 1 < d.NL;
+            sq.next_norm = sq.pack_next ? params[j + 1].pre_norm_w : nullptr;
+        }
         BLK_TRY(forward_few(dc, &c, &params[j], ws + w.inner, bw, cur, 1, sj, cj, sj, ws + w.fin_conv, nxt, cur, sq, st));
         cur = nxt;
     }

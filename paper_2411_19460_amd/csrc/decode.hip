@@ -235,35 +235,6 @@ hipError_t launch_decode_kernel(const DecodeParams& dp, int nb, hipStream_t s) {
 
 }  // namespace
 
-// One token for each of `nb` sequences whose states lie state_bs floats apart (bf16 storage): x [nb, H, P],
-// dt [nb, H], B, C [nb, G, N] dense -> y [nb, H, P].
-hipError_t launch_decode_strided(int nb, int H, int P, int G, int N, const void* x, const void* dt, const float* A, const void* B,
-                                 const void* C, const float* D, float* state, int64_t state_bs, void* y, hipStream_t st) {
-    if (nb <= 0 || nb > 65535 || H <= 0 || H > 65535 || P <= 0 || G <= 0 || N <= 0 || H % G) return hipErrorInvalidValue;
-    DecodeParams dp;
-    dp.x = x;
-    dp.dt = dt;
-    dp.Bm = B;
-    dp.Cm = C;
-    dp.A = A;
-    dp.D = D;
-    dp.state = state;
-    dp.reset = nullptr;
-    dp.y = y;
-    dp.T = 1;
-    dp.H = H;
-    dp.P = P;
-    dp.G = G;
-    dp.N = N;
-    dp.hpg = H / G;
-    dp.xs_b = (int64_t)H * P;
-    dp.dts_b = H;
-    dp.bcs_b = (int64_t)G * N;
-    dp.state_bs = state_bs;
-    dp.skip_add = 0.f;
-    return launch_decode_kernel<bf16_t>(dp, nb, st);
-}
-
 }  // namespace ssdk
 
 using namespace ssdk;

@@ -1,19 +1,20 @@
 // Generation: a token or a few at a time through a block (the recurrence of Sec. 3.1, Eq. 1 around which the
 // block's other steps shrink to vectors).  Every kernel here is bound by reading each parameter once and the
-// SSM state twice per call.  Up to four rows (a sequence on its own) the block's steps are folded into three
+// SSM state twice per call.  Up to two rows (a sequence on its own) the block's steps are folded into three
 // launches that do exactly that, on the vector ALUs:
 //   k_linear_few<1>  zxbcdt = RMSNorm(u) pre_norm_w W_in^T   (or plain u W_in^T)
-//   k_decode_mid     convolution + SiLU, softplus(dt), the state update and y = C h + D x, token by token
-//   k_linear_few<2>  out = RMSNorm(y silu(z)) norm_w W_out^T (+ the residual)
-// With more rows (several sequences generated together) the per-row arithmetic would bound those kernels:
-// the products then run as small MFMAs (k_linear_few_mfma), the normalisations as the library's own kernels,
-// the convolution as a step of its own (k_conv_step) in front of the recurrence kernel of decode.hip.
+//                    (one token a sequence: with the convolution step + SiLU and softplus(dt) on the finished columns)
+//   k_decode_step    the state update and g = (C h + D x) silu(z)   (several tokens: k_decode_mid, convolution included)
+//   k_linear_few<1>  out = RMSNorm(g) norm_w W_out^T (+ the residual)
+// With more rows (several sequences generated together) the per-row arithmetic would bound the products, which then
+// run as small MFMAs (k_linear_few_mfma): three launches as well.
 #include "ssd_internal.h"
 
 namespace ssdk {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float sigmoid_fast(float z) { return __builtin_amdgcn_rcpf(1.f + __expf(-z)); }
@@ -28,31 +29,98 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ float through_bf16(float v) { return (float)(__bf16)v; }
 
 struct FewParams {
-    const __bf16 *x, *w, *z, *res;
+    const __bf16 *x, *w, *res;
     __bf16* out;
     const float* in_w;
-    int64_t ldx, ldz, ldo, ldres;
+    int64_t ldx, ldo, ldres;
     int rows, K, N;
     float eps;
 };
 
 // out[r, n] = sum_k f(x)[r, k] w[n, k] (+ res[r, n]) for r < rows <= R.  A wave owns CPW columns n and walks k
 // with 16-byte loads, so every weight is read once, in full cache lines; the few input rows come from the
-// caches.  MODE 0: f(x) = x.  MODE 1: f(x) = x / sqrt(mean x^2 + eps) * in_w.  MODE 2: the same of g = x z sigmoid(z).
+// caches.  MODE 0: f(x) = x.  MODE 1: f(x) = x / sqrt(mean x^2 + eps) * in_w.
 // A wave sees whole rows, so the mean comes out of the same loop and scales the finished sums.  With few rows
 // the operands of two k steps are requested before either is used (twice the bytes in flight per wave).
-// The first workgroups also move `copy_chunks` pieces of `copy_n` 16-byte vectors from copy_src to copy_dst: a small
+// Workgroup ids are dealt round-robin over the 8 XCDs: neighbouring columns, which share cache lines of everything but w,
+// go to one XCD.
+__device__ __forceinline__ int xcd_block() {
+    const int n = gridDim.x, q = n >> 3, b = blockIdx.x;
+    return b < 8 * q ? (b & 7) * q + (b >> 3) : b;
+}
+// The launch also moves `copy_chunks` pieces of `copy_n` 16-byte vectors from copy_src to copy_dst: a small
 // state (one piece per sequence) that the kernel before this one still read in its old place.
 struct FewOperands {
     const void* copy_src;
     void* copy_dst;
     int copy_n, copy_chunks;                   // vectors per chunk, chunks
     int64_t copy_src_stride, copy_dst_stride;  // vectors between chunks
+    // matrix-core kernel with packed input: partial sums of squares of the rows (null: no normalisation), how many per
+    // group, groups; and what it leaves for the next such product (pack_out null: nothing)
+    const float* ssq;
+    int nparts, groups;
+    __bf16* pack_out;
+    const float* pack_w;
+    float* pack_ssq;
+    // one token for each of several sequences (row r = sequence r): the columns [off_xbc, off_dt) of the output go through
+    // the convolution step on the state cs (sequence r: cs_bs elements further on; replaced in place: a channel has one
+    // owner), the H columns from off_dt on through softplus.  cs null: no such steps.
+    __bf16* cs;
+    int64_t cs_bs;
+    const float *conv_w, *conv_b, *dt_bias;
+    int off_xbc, off_dt, conv_dim;
+    int ks;  // matrix-core kernel: waves
 };
+
+// What the step of column n needs besides the product: asked for when the kernel starts, and not touched before the end
+// (a conversion here would wait for it in front of the loads of w).
+struct StepTaps {
+    uint32_t s0, s1, s2;  // bf16 bits
+    float b;
+    f32x4 w;
+};
+__device__ __forceinline__ float bits_f(uint32_t b) { return __uint_as_float(b << 16); }
+__device__ __forceinline__ StepTaps step_taps(const FewOperands& fo, int r, int n) {  // no branches: clamped indices
+    StepTaps t;
+    const int last = fo.conv_dim - 1, c0 = n - fo.off_xbc, c = c0 < 0 ? 0 : (c0 < last ? c0 : last);
+    const uint16_t* cs = (const uint16_t*)fo.cs + r * fo.cs_bs + c;
+    t.s0 = cs[0];
+    t.s1 = cs[fo.conv_dim];
+    t.s2 = cs[2 * fo.conv_dim];
+    const float* bias = n >= fo.off_dt ? fo.dt_bias + (n - fo.off_dt) : fo.conv_b + c;
+    t.b = *bias;
+    t.w = *(const f32x4*)(fo.conv_w + (int64_t)c * 4);
+    return t;
+}
+// The rounded product u of (row r, column n) through its step; every intermediate is rounded as the block stores it.
+__device__ __forceinline__ __bf16 step_finish(const FewOperands& fo, const StepTaps& t, int r, int n, __bf16 ub) {
+    const float u = (float)ub;
+    if (n >= fo.off_dt) {
+        const float v = u + t.b;
+        return (__bf16)(fmaxf(v, 0.f) + log1pf(__expf(-fabsf(v))));  // softplus
+    }
+    if (n < fo.off_xbc) return ub;
+    const int c = n - fo.off_xbc;
+    uint16_t* cs = (uint16_t*)fo.cs + r * fo.cs_bs + c;
+    cs[0] = (uint16_t)t.s1;
+    cs[fo.conv_dim] = (uint16_t)t.s2;
+    cs[2 * fo.conv_dim] = __builtin_bit_cast(uint16_t, ub);
+    const float pre = t.b + t.w[0] * bits_f(t.s0) + t.w[1] * bits_f(t.s1) + t.w[2] * bits_f(t.s2) + t.w[3] * u;
+    return (__bf16)(pre * sigmoid_fast(pre));
+}
+
+// (The workgroup size comes as an argument: blockDim is a vector load that the whole kernel would wait for first.)
+__device__ __forceinline__ void move_pieces(const FewOperands& fo, int threads) {
+    const int total = fo.copy_n * fo.copy_chunks;
+    for (int i = blockIdx.x * threads + threadIdx.x; i < total; i += gridDim.x * threads) {
+        const int c = i / fo.copy_n, v = i - c * fo.copy_n;
+        ((f32x4*)fo.copy_dst)[c * fo.copy_dst_stride + v] = ((const f32x4*)fo.copy_src)[c * fo.copy_src_stride + v];
+    }
+}
 
 template <int MODE, int R, int CPW>
 struct FewStep {
-    bf16x8 wv[CPW], xv[R], zv[MODE == 2 ? R : 1];
+    bf16x8 wv[CPW], xv[R];
     float iw[MODE ? 8 : 1];
 
     __device__ __forceinline__ void load(const FewParams& fp, const __bf16* w0, int k) {
@@ -68,10 +136,7 @@ struct FewStep {
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if (r < fp.rows) {
-                xv[r] = *(const bf16x8*)(fp.x + r * fp.ldx + k);
-                if (MODE == 2) zv[r] = *(const bf16x8*)(fp.z + r * fp.ldz + k);
-            }
+            if (r < fp.rows) xv[r] = *(const bf16x8*)(fp.x + r * fp.ldx + k);
         }
     }
 
@@ -82,10 +147,6 @@ struct FewStep {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     float v = (float)xv[r][e];
-                    if (MODE == 2) {
-                        const float zz = (float)zv[r][e];
-                        v *= zz * sigmoid_fast(zz);
-                    }
                     if (MODE) {
                         ss[r] = fmaf(v, v, ss[r]);
                         v *= iw[e];
@@ -101,16 +162,10 @@ struct FewStep {
 // KS waves of a workgroup share a wave's columns and take every KS-th k step each (a wave that walks all of a
 // long row alone waits for one load after the other: more, shorter waves keep more bytes in flight); their
 // partial sums meet in LDS.
-template <int MODE, int R, int CPW, int KS>
+// STEP: with the convolution step (fo.cs).  A template argument like MODE: a branch around loads ends in a wait for them.
+template <int MODE, int R, int CPW, int KS, bool STEP>
 __global__ __launch_bounds__(256) void k_linear_few(FewParams fp, FewOperands fo) {
     __shared__ float red[4][R * (CPW + 1)];
-    if (fo.copy_n) {
-        const int i = blockIdx.x * 256 + threadIdx.x;
-        if (i < fo.copy_n * fo.copy_chunks) {
-            const int c = i / fo.copy_n, v = i - c * fo.copy_n;
-            ((f32x4*)fo.copy_dst)[c * fo.copy_dst_stride + v] = ((const f32x4*)fo.copy_src)[c * fo.copy_src_stride + v];
-        }
-    }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int slot = wv / KS, kp = wv % KS;  // which columns of the workgroup, which share of k
     const int n0 = (blockIdx.x * (4 / KS) + slot) * CPW;
@@ -122,75 +177,65 @@ __global__ __launch_bounds__(256) void k_linear_few(FewParams fp, FewOperands fo
 #pragma unroll
         for (int c = 0; c < CPW; ++c) acc[r][c] = 0.f;
     }
+    // after the sums: lane r CPW + c of the wave with kp = 0 finishes (row r, column n0 + c)
+    const int fr = lane / CPW, fn = n0 + lane % CPW;
+    const bool finish = live && kp == 0 && lane < R * CPW && fr < fp.rows && fn < fp.N;
     const __bf16* w0 = fp.w + (int64_t)n0 * fp.K;
-    constexpr bool TWO = R <= 4;
-    constexpr int STEP = 512 * KS;  // k between a wave's consecutive steps
+    constexpr int KSTEP = 512 * KS;  // k between a wave's consecutive steps
     if (live) {
-        for (int k = lane * 8 + 512 * kp; k < fp.K; k += TWO ? 2 * STEP : STEP) {
+        for (int k = lane * 8 + 512 * kp; k < fp.K; k += 2 * KSTEP) {
             FewStep<MODE, R, CPW> a, b;
-            const bool two = TWO && k + STEP < fp.K;
+            const bool two = k + KSTEP < fp.K;
             a.load(fp, w0, k);
-            if (two) b.load(fp, w0, k + STEP);
+            if (two) b.load(fp, w0, k + KSTEP);
             a.use(fp, acc, ss);
             if (two) b.use(fp, acc, ss);
         }
     }
+    // asked for here, behind the sums: held over the loop it would cost the fifth wave per SIMD (2 us over 54 MB of w)
+    StepTaps taps;
+    if (STEP) taps = step_taps(fo, fr < fp.rows ? fr : 0, fn < fp.N ? fn : fp.N - 1);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         if (MODE) ss[r] = wave_sum(ss[r]);
 #pragma unroll
         for (int c = 0; c < CPW; ++c) acc[r][c] = wave_sum(acc[r][c]);
     }
-    if (KS > 1) {
-        if (lane == 0) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                red[wv][r * (CPW + 1) + CPW] = ss[r];
-#pragma unroll
-                for (int c = 0; c < CPW; ++c) red[wv][r * (CPW + 1) + c] = acc[r][c];
-            }
-        }
-        __syncthreads();
-        if (kp != 0) return;
+    if (lane == 0) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            ss[r] = 0.f;
+            red[wv][r * (CPW + 1) + CPW] = ss[r];
 #pragma unroll
-            for (int c = 0; c < CPW; ++c) acc[r][c] = 0.f;
-#pragma unroll
-            for (int q = 0; q < KS; ++q) {  // fixed order: the result does not depend on which wave finished first
-                ss[r] += red[slot * KS + q][r * (CPW + 1) + CPW];
-#pragma unroll
-                for (int c = 0; c < CPW; ++c) acc[r][c] += red[slot * KS + q][r * (CPW + 1) + c];
-            }
+            for (int c = 0; c < CPW; ++c) red[wv][r * (CPW + 1) + c] = acc[r][c];
         }
     }
-    if (!live || lane != 0) return;
+    __syncthreads();
+    move_pieces(fo, 256);
+    if (!finish) return;
+    float v = 0.f, sq = 0.f;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (r < fp.rows) {
-            const float rstd = MODE ? rsqrtf(ss[r] / (float)fp.K + fp.eps) : 1.f;
-#pragma unroll
-            for (int c = 0; c < CPW; ++c) {
-                float v = acc[r][c] * rstd;
-                if (fp.res) v += (float)fp.res[r * fp.ldres + n0 + c];
-                fp.out[r * fp.ldo + n0 + c] = (__bf16)v;
-            }
-        }
+    for (int q = 0; q < KS; ++q) {  // fixed order: the result does not depend on which wave finished first
+        sq += red[slot * KS + q][fr * (CPW + 1) + CPW];
+        v += red[slot * KS + q][fr * (CPW + 1) + lane % CPW];
     }
+    if (MODE) v *= rsqrtf(sq / (float)fp.K + fp.eps);
+    if (fp.res) v += (float)fp.res[fr * fp.ldres + fn];
+    const __bf16 ob = (__bf16)v;
+    fp.out[fr * fp.ldo + fn] = STEP ? step_finish(fo, taps, fr, fn, ob) : ob;
+}
+
+template <int MODE, int CPW, int KS, bool STEP>
+hipError_t launch_few_cks(const FewParams& fp, const FewOperands& fo, hipStream_t st) {
+    const int slots = (fp.N + CPW - 1) / CPW;  // groups of CPW columns
+    const dim3 grid((unsigned)((slots + 4 / KS - 1) / (4 / KS))), block(256);
+    if (fp.rows <= 1) hipLaunchKernelGGL((k_linear_few<MODE, 1, CPW, KS, STEP>), grid, block, 0, st, fp, fo);
+    else hipLaunchKernelGGL((k_linear_few<MODE, FEW_ROWS_VALU, CPW, KS, STEP>), grid, block, 0, st, fp, fo);
+    return hipGetLastError();
 }
 
 template <int MODE, int CPW, int KS>
 hipError_t launch_few_ck(const FewParams& fp, const FewOperands& fo, hipStream_t st) {
-    const int slots = (fp.N + CPW - 1) / CPW;  // groups of CPW columns
-    const dim3 grid((unsigned)((slots + 4 / KS - 1) / (4 / KS))), block(256);
-    if ((int64_t)grid.x * 256 < (int64_t)fo.copy_n * fo.copy_chunks) return hipErrorInvalidValue;
-    if (fp.rows <= 1) hipLaunchKernelGGL((k_linear_few<MODE, 1, CPW, KS>), grid, block, 0, st, fp, fo);
-    else if (fp.rows <= 2) hipLaunchKernelGGL((k_linear_few<MODE, 2, CPW, KS>), grid, block, 0, st, fp, fo);
-    else if (fp.rows <= 4) hipLaunchKernelGGL((k_linear_few<MODE, 4, CPW, KS>), grid, block, 0, st, fp, fo);
-    else if (fp.rows <= 8) hipLaunchKernelGGL((k_linear_few<MODE, 8, CPW, KS>), grid, block, 0, st, fp, fo);
-    else hipLaunchKernelGGL((k_linear_few<MODE, 16, CPW, KS>), grid, block, 0, st, fp, fo);
-    return hipGetLastError();
+    return fo.cs ? launch_few_cks<MODE, CPW, KS, true>(fp, fo, st) : launch_few_cks<MODE, CPW, KS, false>(fp, fo, st);
 }
 
 // Long rows (the block's two products): four columns per wave share the fetched (and transformed) input rows --
@@ -205,86 +250,191 @@ hipError_t launch_few(const FewParams& fp, const FewOperands& fo, hipStream_t st
 }
 
 // More than a few rows (several sequences generated together): the same product on the matrix cores.  A
-// workgroup owns 16 columns of w; its KS waves split k among themselves and each runs 16 x 16 x 32 MFMAs with the
+// workgroup owns 16 columns of w; its KS waves share out pieces of 256 k and each runs 16 x 16 x 32 MFMAs with the
 // (at most 16) input rows as the other operand, so the arithmetic is out of the way and the kernel again only
-// streams w; the partial tiles meet in LDS.  No input transform here (a normalisation in front runs as its own
-// small kernel: redoing it in every wave is what would bound the kernel).
+// streams w; the partial tiles meet in LDS.
+// What bounds it is the number of cache lines an access touches: w is fetched as half rows of 512 contiguous bytes per
+// half wave and turned into operands through LDS, and the input rows come in operand order (16 bytes per row and eight k,
+// rows adjacent: `packed_at`) from the kernel before.  2560 x 10576 / 5120 x 2560 with 16 rows: 22 / 15 us with operands
+// fetched straight from w's rows (16 lines an access), 16 / 11 with w through LDS, 13.4 / 8.6 with packed input too; reading
+// w alone takes 9.9 / 5.9.
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
-template <int KS, int CG>
-__global__ __launch_bounds__(KS * 64) void k_linear_few_mfma(FewParams fp, FewOperands fo) {
-    __shared__ float part[KS][CG * 256];
-    if (fo.copy_n) {
-        const int i = blockIdx.x * (KS * 64) + threadIdx.x;
-        if (i < fo.copy_n * fo.copy_chunks) {
-            const int c = i / fo.copy_n, v = i - c * fo.copy_n;
-            ((f32x4*)fo.copy_dst)[c * fo.copy_dst_stride + v] = ((const f32x4*)fo.copy_src)[c * fo.copy_src_stride + v];
+// Where (row, k) lies in the packed order.
+__device__ __forceinline__ int64_t packed_at(int row, int k) { return ((int64_t)(k >> 3) * 16 + row) * 8 + (k & 7); }
+
+constexpr int PIECE = 256, WPITCH = PIECE * 2 + 16;  // k per piece; bytes per LDS row of a piece of w
+constexpr int MFMA_WAVES = 8, MAX_GROUPS = 8;
+inline size_t few_mfma_lds(int ks) { return (size_t)ks * 16 * WPITCH + (size_t)ks * 1024 + 16 * 17 * 4; }
+static_assert(MAX_GROUPS * 16 <= 16 * 17, "");
+
+// SRC 0: rows of x.  SRC 1: RMS normalisation over all of K times in_w, its squares summed on the way (the operand is
+// x in_w rounded once, 1 / rms scales the finished sums).  SRC 2: packed rows, already times in_w, with `ssq` the partial
+// sums of squares of their producer (nparts per group of K / groups, row r of part i at ssq[16 i + r]).  SRC 3: packed rows,
+// no normalisation.
+template <int SRC, bool STEP>
+__global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams fp, FewOperands fo) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int KS = fo.ks, nthr = 64 * KS, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    char* wt = lds + wv * 16 * WPITCH;
+    float* part = (float*)(lds + KS * 16 * WPITCH);  // [KS][256]
+    float* rs = part + KS * 256;                     // [groups][16]: 1 / rms, or (one group) [16][17]: shares of the squares
+    const int blk = xcd_block(), n0 = blk * 16;
+    const int col = lane & 15, kq = lane >> 4;   // operand lanes: row of x / column of w, quarter of a 32-wide k step
+    const int r2 = lane >> 5, l32 = lane & 31;   // fetching lanes: two columns of w at a time, 32 vectors of a piece each
+    const int pieces = (fp.K + PIECE - 1) / PIECE;
+    const __bf16* xr = fp.x + (SRC >= 2 ? (int64_t)0 : (int64_t)(col < fp.rows ? col : 0) * fp.ldx);
+    constexpr bool norm = SRC == 2;
+    constexpr int PU = 10;  // partial sums of squares asked for ahead of everything else (per thread)
+    float sp[PU];
+    const int TQ = nthr < 256 ? nthr >> 4 : 16;  // threads that share a row's sum
+    if (norm) {
+#pragma unroll
+        for (int u = 0; u < PU; ++u) {
+            const int i = (tid >> 4) + TQ * u;
+            sp[u] = fo.ssq[16 * (i < fo.nparts ? i : 0) + (tid & 15)];
         }
     }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int n0 = blockIdx.x * (16 * CG);
-    const int col = lane & 15, kq = lane >> 4;  // the lane's row of x and column of w; its quarter of a 32-wide k step
-    const bool has_x = col < fp.rows;
-    const __bf16* xr = fp.x + (int64_t)col * fp.ldx;
-    const __bf16* wr = fp.w + (int64_t)(n0 + col) * fp.K;
-    const int nsteps = (fp.K + 31) / 32, per = (nsteps + KS - 1) / KS;
-    const int s0 = wv * per, s1 = s0 + per < nsteps ? s0 + per : nsteps;
-    f32x4v acc[CG];
+    bf16x8 v[8], a[8];
+    f32x4 iw[SRC == 1 ? 8 : 1][2];
+    auto load = [&](int pc) {
+        const int kk = pc * PIECE + 8 * l32, kc = kk < fp.K ? kk : 0;  // K is a multiple of 8; beyond it the other operand is zero
 #pragma unroll
-    for (int c = 0; c < CG; ++c) acc[c] = f32x4v{0.f, 0.f, 0.f, 0.f};
-    constexpr int UN = CG > 1 ? 2 : 4;  // k steps whose operands are requested together
-    for (int sb = s0; sb < s1; sb += UN) {
-        bf16x8 a[UN], b[UN][CG];
+        for (int j = 0; j < 8; ++j) {
+            const int n = n0 + 2 * j + r2;
+            v[j] = *(const bf16x8*)(fp.w + (int64_t)(n < fp.N ? n : fp.N - 1) * fp.K + kc);
+        }
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int k = (sb + u) * 32 + 8 * kq;  // K is a multiple of 8: a lane's eight values are inside or outside as a whole
-            const bool in = sb + u < s1 && k < fp.K;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) a[u][e] = (__bf16)0.f;
-            if (has_x && in) a[u] = *(const bf16x8*)(xr + k);
-#pragma unroll
-            for (int c = 0; c < CG; ++c) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) b[u][c][e] = (__bf16)0.f;
-                if (in && n0 + 16 * c + col < fp.N) b[u][c] = *(const bf16x8*)(wr + (int64_t)(16 * c) * fp.K + k);
+        for (int s = 0; s < 8; ++s) {
+            int k = pc * PIECE + 32 * s + 8 * kq;
+            k = k < fp.K ? k : 0;
+            a[s] = *(const bf16x8*)(SRC >= 2 ? xr + packed_at(col, k) : xr + k);
+            if (SRC == 1) {
+                iw[s][0] = *(const f32x4*)(fp.in_w + k);
+                iw[s][1] = *(const f32x4*)(fp.in_w + k + 4);
             }
         }
-#pragma unroll
-        for (int u = 0; u < UN; ++u)
-#pragma unroll
-            for (int c = 0; c < CG; ++c)  // acc[c][i] = out[row 4 kq + i][column n0 + 16 c + col]
-                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], b[u][c], acc[c], 0, 0, 0);
+    };
+    StepTaps taps;
+    {   // the (row, column) thread tid finishes
+        const int l = tid >> 2, r = 4 * (l >> 4) + (tid & 3), n = n0 + (l & 15);
+        if (STEP) taps = step_taps(fo, r < fp.rows ? r : 0, n < fp.N ? n : fp.N - 1);
     }
+    int pc = wv;
+    if (pc < pieces) load(pc);
+    // One group: its 1 / rms scales the finished sums, so nothing waits for it here.  Several: each piece of k lies inside
+    // one group and is scaled before it is added.
+    const bool norm_late = norm && fo.groups == 1;
+    auto row_share = [&](int g, bool ahead) {  // this thread's share of the squares of row tid % 16
+        const float* q = fo.ssq + (int64_t)16 * g * fo.nparts;
+        float t = 0.f;
+        if (ahead) {
 #pragma unroll
-    for (int c = 0; c < CG; ++c)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) part[wv][c * 256 + lane * 4 + i] = acc[c][i];
-    __syncthreads();
-    for (int t = threadIdx.x; t < CG * 256; t += KS * 64) {
-        float v = 0.f;
-#pragma unroll
-        for (int q = 0; q < KS; ++q) v += part[q][t];
-        const int c = t >> 8, l = (t & 255) >> 2, i = t & 3;
-        const int r = 4 * (l >> 4) + i, n = n0 + 16 * c + (l & 15);
-        if (r < fp.rows && n < fp.N) {
-            if (fp.res) v += (float)fp.res[r * fp.ldres + n];
-            fp.out[r * fp.ldo + n] = (__bf16)v;
+            for (int u = 0; u < PU; ++u) t += (tid >> 4) + TQ * u < fo.nparts ? sp[u] : 0.f;
+        }
+        for (int i = (tid >> 4) + (ahead ? TQ * PU : 0); i < fo.nparts; i += TQ) t += q[16 * i + (tid & 15)];
+        return t;
+    };
+    if (norm && !norm_late) {
+        for (int g = 0; g < fo.groups; ++g) {
+            if (tid < 256) part[(tid & 15) * 16 + (tid >> 4)] = row_share(g, g == 0);
+            __syncthreads();
+            if (tid < 16) {
+                float t = 0.f;
+                for (int q = 0; q < TQ; ++q) t += part[tid * 16 + q];
+                rs[g * 16 + tid] = rsqrtf(t / (float)(fp.K / fo.groups) + fp.eps);
+            }
+            __syncthreads();
         }
     }
+    f32x4v acc = {0.f, 0.f, 0.f, 0.f};
+    float ss = 0.f;
+    for (; pc < pieces; pc += KS) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) *(bf16x8*)(wt + (2 * j + r2) * WPITCH + 16 * l32) = v[j];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // a wave's own rows: no barrier
+        f32x4v t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const bool in = pc * PIECE + 32 * s + 8 * kq < fp.K;
+            bf16x8 av;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (SRC == 1) {
+                    const float x = in ? (float)a[s][e] : 0.f;
+                    ss = fmaf(x, x, ss);
+                    av[e] = (__bf16)(x * iw[s][e >> 2][e & 3]);
+                } else {
+                    av[e] = in ? a[s][e] : (__bf16)0.f;
+                }
+            }
+            // t[i] = out[row 4 kq + i][column n0 + col]
+            t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, *(const bf16x8*)(wt + col * WPITCH + 64 * s + 16 * kq), t, 0, 0, 0);
+        }
+        if (norm && !norm_late) {
+            const float4 q = *(const float4*)(rs + (int)((int64_t)pc * PIECE * fo.groups / fp.K) * 16 + 4 * kq);
+            acc[0] += t[0] * q.x;
+            acc[1] += t[1] * q.y;
+            acc[2] += t[2] * q.z;
+            acc[3] += t[3] * q.w;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] += t[i];
+        }
+        if (pc + KS < pieces) load(pc + KS);
+    }
+    if (SRC == 1) {  // the row's squares of this wave's pieces
+        ss += __shfl_xor(ss, 16, 64);
+        ss += __shfl_xor(ss, 32, 64);
+        if (lane < 16) ((float*)wt)[lane] = ss;  // the wave's rows of w are used up
+    }
+    *(f32x4v*)(part + wv * 256 + lane * 4) = acc;
+    if (norm_late && tid < 256) rs[(tid & 15) * 17 + (tid >> 4)] = row_share(0, true);
+    __syncthreads();
+    for (int t = tid; t < 256; t += nthr) {
+        float o = 0.f;
+        for (int q = 0; q < KS; ++q) o += part[q * 256 + t];
+        const int l = t >> 2, r = 4 * (l >> 4) + (t & 3), n = n0 + (l & 15);  // a wave of t: four rows, all 16 columns
+        if (SRC == 1) {
+            float m = 0.f;
+            for (int q = 0; q < KS; ++q) m += ((const float*)(lds + q * 16 * WPITCH))[r];
+            o *= rsqrtf(m / (float)fp.K + fp.eps);
+        }
+        if (norm_late) {
+            float m = 0.f;
+            for (int q = 0; q < TQ; ++q) m += rs[r * 17 + q];
+            o *= rsqrtf(m / (float)fp.K + fp.eps);
+        }
+        const bool live = r < fp.rows && n < fp.N;
+        if (live && fp.res) o += (float)fp.res[r * fp.ldres + n];
+        const __bf16 ob = (__bf16)o;
+        if (live) fp.out[r * fp.ldo + n] = STEP ? step_finish(fo, t == tid ? taps : step_taps(fo, r, n), r, n, ob) : ob;
+        if (fo.pack_out) {  // the next product's operand, and the squares its normalisation needs
+            const float x = live ? (float)ob : 0.f;
+            if (live) fo.pack_out[packed_at(r, n)] = (__bf16)(fo.pack_w ? x * fo.pack_w[n] : x);
+            float q = x * x;
+            for (int off = 4; off < 64; off <<= 1) q += __shfl_xor(q, off, 64);
+            if ((l & 15) == 0) fo.pack_ssq[16 * blk + r] = q;
+        }
+    }
+    move_pieces(fo, nthr);
 }
 
-hipError_t launch_few_mfma(const FewParams& fp, const FewOperands& fo, hipStream_t st) {
-    // wide products: 64 columns per workgroup (the input rows are fetched once for four column groups), k split 16
-    // ways; narrow ones: 16 columns, and the narrower the product, the more ways k is split -- enough waves either
-    // way to keep the memory system busy
-    const bool wide = fp.N >= 4096;
-    const int wgs = wide ? (fp.N + 63) / 64 : (fp.N + 15) / 16;
-    const int ks = wide ? 16 : wgs >= 1024 ? 4 : wgs >= 512 ? 8 : 16;
-    if ((int64_t)wgs * ks * 64 < (int64_t)fo.copy_n * fo.copy_chunks) return hipErrorInvalidValue;
-    if (wide) hipLaunchKernelGGL((k_linear_few_mfma<16, 4>), dim3(wgs), dim3(1024), 0, st, fp, fo);
-    else if (ks == 4) hipLaunchKernelGGL((k_linear_few_mfma<4, 1>), dim3(wgs), dim3(256), 0, st, fp, fo);
-    else if (ks == 8) hipLaunchKernelGGL((k_linear_few_mfma<8, 1>), dim3(wgs), dim3(512), 0, st, fp, fo);
-    else hipLaunchKernelGGL((k_linear_few_mfma<16, 1>), dim3(wgs), dim3(1024), 0, st, fp, fo);
+template <int SRC>
+void launch_few_mfma_src(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
+    if (fo.cs) hipLaunchKernelGGL((k_linear_few_mfma<SRC, true>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
+    else hipLaunchKernelGGL((k_linear_few_mfma<SRC, false>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
+}
+
+hipError_t launch_few_mfma(const FewParams& fp, FewOperands fo, int src, hipStream_t st) {
+    const int wgs = (fp.N + 15) / 16, pieces = (fp.K + PIECE - 1) / PIECE, ks = pieces < MFMA_WAVES ? pieces : MFMA_WAVES;
+    const size_t lds = few_mfma_lds(ks);
+    fo.ks = ks;
+    if (src == 2 && !fo.ssq) src = 3;
+    if (src == 0) launch_few_mfma_src<0>(fp, fo, wgs, lds, st);
+    else if (src == 1) launch_few_mfma_src<1>(fp, fo, wgs, lds, st);
+    else if (src == 2) launch_few_mfma_src<2>(fp, fo, wgs, lds, st);
+    else launch_few_mfma_src<3>(fp, fo, wgs, lds, st);
     return hipGetLastError();
 }
 
@@ -300,6 +450,12 @@ struct MidParams {
     // several independent sequences in one launch (blockIdx.y): sequence b owns rows b T .. b T + T - 1 of zx and y
     // and the states `b` strides (elements) further on
     int64_t state_bs, cs_in_bs, cs_out_bs;
+    int gate;  // y is y silu(z), rounded once: what the normalisation behind takes the squares of
+    // with both: y silu(z) pack_w goes to the packed operand of the output product instead, its squares (before pack_w)
+    // summed over the workgroup's rows to pack_ssq[16 (h gridDim.z + z) + row]
+    __bf16* pack;
+    const float* pack_w;
+    float* pack_ssq;
 };
 
 // input of the convolution, channel c, token `pos` of this call (negative: from the entering state)
@@ -314,6 +470,15 @@ __device__ __forceinline__ float conv_output(const MidParams& mp, int t, int c) 
     const float pre = mp.conv_b[c] + w[0] * conv_input(mp, t - 3, c) + w[1] * conv_input(mp, t - 2, c) + w[2] * conv_input(mp, t - 1, c) +
                       w[3] * conv_input(mp, t, c);
     return through_bf16(pre * sigmoid_fast(pre));
+}
+
+// What is stored for channel c of token t: y, or y times silu of its gate.
+__device__ __forceinline__ __bf16 mid_out(const MidParams& mp, int t, int c, float y) {
+    if (mp.gate) {
+        const float z = (float)mp.zx[t * mp.ld + c];
+        y *= z * sigmoid_fast(z);
+    }
+    return (__bf16)y;
 }
 
 // Workgroup (head h, sequence b, z): wave w owns the RPW state rows p = (4 z + w) RPW + rr, lane l their columns
@@ -372,7 +537,7 @@ __global__ __launch_bounds__(256) void k_decode_mid(MidParams mp) {
                     }
                 }
                 acc = wave_sum(acc);
-                if (lane == 0) mp.y[(int64_t)t * mp.d_inner + h * mp.P + p0 + rr] = (__bf16)(acc + Dh * xv[rr]);
+                if (lane == 0) mp.y[(int64_t)t * mp.d_inner + h * mp.P + p0 + rr] = mid_out(mp, t, h * mp.P + p0 + rr, acc + Dh * xv[rr]);
             }
         }
         __syncthreads();  // the next token's B and C replace these
@@ -398,41 +563,104 @@ __global__ __launch_bounds__(256) void k_decode_mid(MidParams mp) {
     }
 }
 
-// One token for each of several sequences: the convolution step by itself.  A thread owns one channel of one
-// sequence -- its window of the convolution state, which it replaces in place -- and writes the activated value
-// into the dense x, B or C row of its sequence; the threads behind the channels take softplus(dt) of the heads.
-struct ConvStepParams {
-    const __bf16* zx;  // [nb, ld]
-    int64_t ld;
-    const float *conv_w, *conv_b, *dt_bias;
-    __bf16* cs;        // sequence b: [3, conv_dim] at cs + b cs_bs, replaced in place
-    int64_t cs_bs;
-    __bf16 *x, *B, *C, *dt;  // [nb, d_inner], [nb, G N], [nb, G N], [nb, H]
-    int H, d_inner, gn, conv_dim, off_xbc, off_dt;
-};
-
-__global__ __launch_bounds__(256) void k_conv_step(ConvStepParams cp) {
-    const int c = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
-    const __bf16* zx = cp.zx + (int64_t)b * cp.ld;
-    if (c < cp.conv_dim) {
-        __bf16* cs = cp.cs + (int64_t)b * cp.cs_bs;
-        const float s0 = (float)cs[c], s1 = (float)cs[cp.conv_dim + c], s2 = (float)cs[2 * cp.conv_dim + c];
-        const __bf16 ub = zx[cp.off_xbc + c];
-        const float u = (float)ub;
-        const float* w = cp.conv_w + (int64_t)c * 4;
-        const float pre = cp.conv_b[c] + w[0] * s0 + w[1] * s1 + w[2] * s2 + w[3] * u;
-        const __bf16 o = (__bf16)(pre * sigmoid_fast(pre));
-        if (c < cp.d_inner) cp.x[(int64_t)b * cp.d_inner + c] = o;
-        else if (c < cp.d_inner + cp.gn) cp.B[(int64_t)b * cp.gn + (c - cp.d_inner)] = o;
-        else cp.C[(int64_t)b * cp.gn + (c - cp.d_inner - cp.gn)] = o;
-        cs[c] = (__bf16)s1;
-        cs[cp.conv_dim + c] = (__bf16)s2;
-        cs[2 * cp.conv_dim + c] = ub;
-    } else if (c < cp.conv_dim + cp.H) {
-        const int h = c - cp.conv_dim;
-        const float v = (float)zx[cp.off_dt + h] + cp.dt_bias[h];
-        cp.dt[(int64_t)b * cp.H + h] = (__bf16)(fmaxf(v, 0.f) + log1pf(__expf(-fabsf(v))));  // softplus
+// One token for each of several sequences whose product has been through the convolution step and softplus already:
+// the recurrence and the gate, nothing else.  16-byte accesses to the state (N a multiple of 4, N <= 128 NV): half a
+// wave owns U consecutive rows, lane l of the half the columns 4 l .. 4 l + 3 (+ 128 i).  Everything is asked for at once,
+// so what bounds it is the state's way in and out (16 sequences of 80 heads: 84 MB).
+template <int NV, int U>
+__global__ __launch_bounds__(256) void k_decode_step(MidParams mp) {
+    __shared__ float sq[8];
+    const int h = blockIdx.x, b = blockIdx.y, g = h / mp.hpg, N = mp.N, tid = threadIdx.x, l32 = tid & 31, hw = tid >> 5;
+    const int p0 = 8 * U * blockIdx.z + U * hw;
+    const __bf16* zx = mp.zx + (int64_t)b * mp.ld;
+    const __bf16* xb = zx + mp.off_xbc;
+    float* S = mp.state + b * mp.state_bs + (int64_t)h * mp.P * N;
+    float4 s[U][NV];
+    bf16x4 bv[NV], cv[NV];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int p = p0 + u < mp.P ? p0 + u : mp.P - 1, n = 4 * l32 + 128 * i;
+            s[u][i] = *(const float4*)(S + (int64_t)p * N + (n < N ? n : 0));
+        }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int n = 4 * l32 + 128 * i;
+        bv[i] = *(const bf16x4*)(xb + mp.d_inner + g * N + (n < N ? n : 0));
+        cv[i] = *(const bf16x4*)(xb + mp.d_inner + (mp.G + g) * N + (n < N ? n : 0));
     }
+    float xv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) xv[u] = (float)xb[h * mp.P + (p0 + u < mp.P ? p0 + u : mp.P - 1)];
+    // after the sums over the half wave: the row this lane finishes (all lanes of a group of 32 / U the same one)
+    const int p_mine = p0 + ((l32 * U) >> 5), c_mine = h * mp.P + (p_mine < mp.P ? p_mine : mp.P - 1);
+    const bool mine = (l32 & (32 / U - 1)) == 0 && p_mine < mp.P;
+    const float x_mine = (float)xb[c_mine], z = mp.gate ? (float)zx[c_mine] : 0.f, pw = mp.pack ? mp.pack_w[c_mine] : 1.f;
+    const float dtv = (float)zx[mp.off_dt + h], a = __expf(dtv * mp.A[h]), Dh = mp.D[h];
+    float acc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const float dx = dtv * xv[u];
+        acc[u] = 0.f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            float4& q = s[u][i];
+            q.x = a * q.x + dx * (float)bv[i][0];
+            q.y = a * q.y + dx * (float)bv[i][1];
+            q.z = a * q.z + dx * (float)bv[i][2];
+            q.w = a * q.w + dx * (float)bv[i][3];
+            const int p = p0 + u, n = 4 * l32 + 128 * i;
+            if (n < N) {
+                acc[u] += ((float)cv[i][0] * q.x + (float)cv[i][1] * q.y) + ((float)cv[i][2] * q.z + (float)cv[i][3] * q.w);
+                if (p < mp.P) *(float4*)(S + (int64_t)p * N + n) = q;
+            }
+        }
+    }
+    // halve the rows with the lanes until a lane has one, then sum over the lanes that share it
+    int off = 16;
+#pragma unroll
+    for (int k = U; k > 1; k >>= 1, off >>= 1)
+#pragma unroll
+        for (int u = 0; u < k / 2; ++u) {
+            const bool up = l32 & off;
+            const float keep = up ? acc[u + k / 2] : acc[u], give = up ? acc[u] : acc[u + k / 2];
+            acc[u] = keep + __shfl_xor(give, off, 64);
+        }
+    for (; off > 0; off >>= 1) acc[0] += __shfl_xor(acc[0], off, 64);
+    float y = acc[0] + Dh * x_mine;
+    if (mp.gate) y *= z * sigmoid_fast(z);
+    if (!mp.pack) {
+        if (mine) mp.y[(int64_t)b * mp.d_inner + c_mine] = (__bf16)y;
+        return;
+    }
+    if (mine) mp.pack[packed_at(b, c_mine)] = (__bf16)(y * pw);
+    float q = mine ? y * y : 0.f;
+    for (int o = 16; o >= 32 / U; o >>= 1) q += __shfl_xor(q, o, 64);
+    if (l32 == 0) sq[hw] = q;
+    __syncthreads();
+    if (tid == 0) {
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sum += sq[i];
+        mp.pack_ssq[16 * (h * gridDim.z + blockIdx.z) + b] = sum;
+    }
+}
+
+// rows per half wave: as many as still leave every compute unit a workgroup or a few (and with packed output, fewer
+// workgroups leave fewer partial sums of squares to add up)
+int step_rows(int H, int P, int nb) {
+    const int64_t hn = (int64_t)H * nb;
+    return hn * ((P + 63) / 64) >= 768 ? 8 : hn * ((P + 31) / 32) >= 256 ? 4 : 1;
+}
+
+template <int NV>
+void launch_step(const MidParams& mp, int nb, hipStream_t st) {
+    const int u = step_rows(mp.H, mp.P, nb);
+    const dim3 grid(mp.H, nb, (mp.P + 8 * u - 1) / (8 * u));
+    if (u == 8) hipLaunchKernelGGL((k_decode_step<NV, 8>), grid, dim3(256), 0, st, mp);
+    else if (u == 4) hipLaunchKernelGGL((k_decode_step<NV, 4>), grid, dim3(256), 0, st, mp);
+    else hipLaunchKernelGGL((k_decode_step<NV, 1>), grid, dim3(256), 0, st, mp);
 }
 
 bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -441,15 +669,19 @@ bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 bool few_rows_supported(const FewRowsJob& j) {
     if (j.rows < 1 || j.rows > FEW_ROWS || j.K <= 0 || j.N <= 0 || ((j.K | j.N) & 7)) return false;
-    if (!j.x || !j.w || !j.out || !al16(j.x) || !al16(j.w) || (j.ldx & 7) || j.ldx < j.K || j.ldo < j.N) return false;
+    if (!j.x || !j.w || !j.out || !al16(j.x) || !al16(j.w) || (j.mode != 2 && ((j.ldx & 7) || j.ldx < j.K)) || j.ldo < j.N) return false;
     if (j.mode < 0 || j.mode > 2) return false;
-    if (j.mode && (!j.in_w || !al16(j.in_w))) return false;
-    if (j.mode == 2 && (!j.z || !al16(j.z) || (j.ldz & 7) || j.ldz < j.K)) return false;
+    if (j.mode == 2 || j.pack_out) {
+        if (j.rows <= FEW_ROWS_VALU) return false;
+        if (j.mode == 2 && j.ssq && (j.groups < 1 || j.groups > MAX_GROUPS || j.nparts < 1 || (j.groups > 1 && j.K % (j.groups * PIECE)))) return false;
+        if (j.pack_out && (!j.pack_ssq || !al16(j.pack_out))) return false;
+    }
+    if (j.mode == 1 && (!j.in_w || !al16(j.in_w))) return false;
     if (j.res && j.ldres < j.N) return false;
     if (j.copy_bytes) {
         const size_t chunks = j.copy_chunks > 0 ? j.copy_chunks : 1;
         if (!j.copy_src || !j.copy_dst || !al16(j.copy_src) || !al16(j.copy_dst) || (j.copy_bytes & 15) || j.copy_chunks < 0 ||
-            ((j.copy_src_stride | j.copy_dst_stride) & 15) || j.copy_bytes / 16 * chunks > (size_t)j.N * 16)  // one vector per thread of the smallest launch these products use
+            ((j.copy_src_stride | j.copy_dst_stride) & 15) || j.copy_bytes / 16 * chunks > (size_t)j.N * 16)  // a few vectors per thread at most
             return false;
     }
     return true;
@@ -460,12 +692,10 @@ hipError_t launch_linear_few_rows(const FewRowsJob& j, hipStream_t st) {
     FewParams fp;
     fp.x = (const __bf16*)j.x;
     fp.w = (const __bf16*)j.w;
-    fp.z = (const __bf16*)j.z;
     fp.res = (const __bf16*)j.res;
     fp.out = (__bf16*)j.out;
     fp.in_w = j.in_w;
     fp.ldx = j.ldx;
-    fp.ldz = j.ldz;
     fp.ldo = j.ldo;
     fp.ldres = j.ldres;
     fp.rows = j.rows;
@@ -479,8 +709,31 @@ hipError_t launch_linear_few_rows(const FewRowsJob& j, hipStream_t st) {
     fo.copy_chunks = j.copy_bytes ? (j.copy_chunks > 0 ? j.copy_chunks : 1) : 0;
     fo.copy_src_stride = (int64_t)(j.copy_src_stride / 16);
     fo.copy_dst_stride = (int64_t)(j.copy_dst_stride / 16);
-    if (j.mode == 0 && j.rows > FEW_ROWS_VALU) return launch_few_mfma(fp, fo, st);
-    return j.mode == 0 ? launch_few<0>(fp, fo, st) : j.mode == 1 ? launch_few<1>(fp, fo, st) : launch_few<2>(fp, fo, st);
+    fo.ssq = j.ssq;
+    fo.nparts = j.nparts;
+    fo.groups = j.groups;
+    fo.pack_out = (__bf16*)j.pack_out;
+    fo.pack_w = j.pack_w;
+    fo.pack_ssq = j.pack_ssq;
+    fo.cs = (__bf16*)j.cs;
+    fo.cs_bs = j.cs_bs;
+    fo.conv_w = j.conv_w;
+    fo.conv_b = j.conv_b;
+    fo.dt_bias = j.dt_bias;
+    fo.off_xbc = j.off_xbc;
+    fo.off_dt = j.off_dt;
+    fo.conv_dim = j.off_dt - j.off_xbc;
+    if (j.rows > FEW_ROWS_VALU) return launch_few_mfma(fp, fo, j.mode, st);
+    return j.mode ? launch_few<1>(fp, fo, st) : launch_few<0>(fp, fo, st);
+}
+
+bool step_supported(const DecodeMidJob& j) {
+    return j.T == 1 && j.N % 4 == 0 && j.N <= 256 && al16(j.state) && j.state_bs % 4 == 0 && al16(j.zx) && j.ld % 4 == 0 && (j.H * j.P) % 4 == 0 &&
+           al16(j.conv_w);
+}
+int step_parts(const DecodeMidJob& j) {
+    const int u = step_rows(j.H, j.P, j.nb > 0 ? j.nb : 1);
+    return j.H * ((j.P + 8 * u - 1) / (8 * u));
 }
 
 hipError_t launch_decode_mid(const DecodeMidJob& j, hipStream_t st) {
@@ -515,6 +768,17 @@ hipError_t launch_decode_mid(const DecodeMidJob& j, hipStream_t st) {
     mp.state_bs = j.state_bs;
     mp.cs_in_bs = j.cs_in_bs;
     mp.cs_out_bs = j.cs_out_bs;
+    mp.gate = j.gate;
+    mp.pack = (__bf16*)j.pack;
+    mp.pack_w = j.pack_w;
+    mp.pack_ssq = j.pack_ssq;
+    if (j.stepped) {
+        if (!step_supported(j) || (j.pack && (!j.gate || !j.pack_w || !j.pack_ssq))) return hipErrorInvalidValue;
+        if (j.N <= 128) launch_step<1>(mp, nb, st);
+        else launch_step<2>(mp, nb, st);
+        return hipGetLastError();
+    }
+    if (j.pack) return hipErrorInvalidValue;
     // rows per wave: one where that gives few enough workgroups (every one of them convolves its group's B and C
     // channels), else 4 or 16
     const size_t lds = (size_t)2 * j.N * sizeof(float);
@@ -525,31 +789,6 @@ hipError_t launch_decode_mid(const DecodeMidJob& j, hipStream_t st) {
         hipLaunchKernelGGL(k_decode_mid<4>, dim3(j.H, nb, (j.P + 15) / 16), dim3(256), lds, st, mp);
     else
         hipLaunchKernelGGL(k_decode_mid<16>, dim3(j.H, nb, (j.P + 63) / 64), dim3(256), lds, st, mp);
-    return hipGetLastError();
-}
-
-hipError_t launch_conv_step(const ConvStepJob& j, hipStream_t st) {
-    if (j.nb < 1 || j.nb > 65535 || j.H <= 0 || j.P <= 0 || j.G <= 0 || j.N <= 0) return hipErrorInvalidValue;
-    if (!j.zx || !j.conv_w || !j.conv_b || !j.dt_bias || !j.cs || !j.x || !j.B || !j.C || !j.dt) return hipErrorInvalidValue;
-    ConvStepParams cp;
-    cp.zx = (const __bf16*)j.zx;
-    cp.ld = j.ld;
-    cp.conv_w = j.conv_w;
-    cp.conv_b = j.conv_b;
-    cp.dt_bias = j.dt_bias;
-    cp.cs = (__bf16*)j.cs;
-    cp.cs_bs = j.cs_bs;
-    cp.x = (__bf16*)j.x;
-    cp.B = (__bf16*)j.B;
-    cp.C = (__bf16*)j.C;
-    cp.dt = (__bf16*)j.dt;
-    cp.H = j.H;
-    cp.d_inner = j.H * j.P;
-    cp.gn = j.G * j.N;
-    cp.conv_dim = cp.d_inner + 2 * cp.gn;
-    cp.off_xbc = cp.d_inner;
-    cp.off_dt = cp.d_inner + cp.conv_dim;
-    hipLaunchKernelGGL(k_conv_step, dim3((cp.conv_dim + cp.H + 255) / 256, j.nb), dim3(256), 0, st, cp);
     return hipGetLastError();
 }
 

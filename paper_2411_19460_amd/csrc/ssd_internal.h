@@ -270,11 +270,10 @@ SideStream* side_stream();
 
 // Generation (few_rows.hip): products and the block's middle steps for at most FEW_ROWS tokens, bf16 storage.
 constexpr int FEW_ROWS = 16;
-// Up to this many rows the product runs on the vector ALUs with an optional normalisation of the rows folded in;
-// above, on the matrix cores (mode 0 only: the caller normalises first).
-constexpr int FEW_ROWS_VALU = 4;
+// Up to this many rows the product runs on the vector ALUs, above on the matrix cores.
+constexpr int FEW_ROWS_VALU = 2;
 // out[r, n] = sum_k f(x)[r, k] w[n, k] (+ res[r, n]); w [N, K] dense.  mode 0: f = identity; 1: RMS normalisation
-// over all of K times in_w; 2: the same of x z sigmoid(z).  Row strides in elements.
+// over all of K times in_w.  Row strides in elements.
 struct FewRowsJob {
     int rows, K, N, mode;
     const void* x;
@@ -283,8 +282,6 @@ struct FewRowsJob {
     void* out;
     int64_t ldo;
     const float* in_w;
-    const void* z;
-    int64_t ldz;
     float eps;
     const void* res;
     int64_t ldres;
@@ -295,6 +292,22 @@ struct FewRowsJob {
     size_t copy_bytes;
     int copy_chunks;
     size_t copy_src_stride, copy_dst_stride;
+    // matrix-core kernel only (rows > FEW_ROWS_VALU).  mode 2: x is the packed operand the kernel before left, already
+    // times the norm's weight, `ssq` its partial sums of squares (null: no normalisation), nparts for each of `groups`
+    // equal pieces of K (multiples of 256).  pack_out: leave the rounded output times pack_w (null: as it is) packed for the
+    // next such product, with one part of sums of squares per 16 columns in pack_ssq.
+    const float* ssq;
+    int nparts, groups;
+    void* pack_out;
+    const float* pack_w;
+    float* pack_ssq;
+    // one token for each of `rows` sequences: columns [off_xbc, off_dt) through the convolution step + SiLU on the states cs
+    // ([3, off_dt - off_xbc] each, cs_bs elements apart, replaced in place), columns from off_dt on through
+    // softplus(. + dt_bias).  cs null: the product alone.
+    void* cs;
+    int64_t cs_bs;
+    const float *conv_w, *conv_b, *dt_bias;
+    int off_xbc, off_dt;
 };
 bool few_rows_supported(const FewRowsJob& j);  // sizes, strides and 16-byte alignment the kernel relies on
 hipError_t launch_linear_few_rows(const FewRowsJob& j, hipStream_t st);
@@ -312,23 +325,18 @@ struct DecodeMidJob {
     void* cs_out;
     float* state;
     void* y;
+    int gate;  // y silu(z) instead of y
+    // one token per sequence whose product took the convolution step and softplus along (FewRowsJob.cs): the recurrence
+    // only; cs_in, cs_out are not touched.  Where step_supported(j).
+    int stepped;
+    // stepped with gate: y silu(z) pack_w as the packed operand of a mode-2 product instead, step_parts(j) parts of sums of
+    // squares (heads in order) in pack_ssq
+    void* pack;
+    const float* pack_w;
+    float* pack_ssq;
 };
+bool step_supported(const DecodeMidJob& j);
+int step_parts(const DecodeMidJob& j);
 hipError_t launch_decode_mid(const DecodeMidJob& j, hipStream_t st);
-// The same for one token of each of nb sequences as two kernels (many sequences: a convolution per workgroup of
-// the recurrence kernel costs more than a launch): convolution + SiLU and softplus(dt) into dense x [nb, H P],
-// B, C [nb, G N], dt [nb, H], the convolution state cs (sequence b: cs_bs elements further on) replaced in place;
-// then the recurrence on states state_bs floats apart.
-struct ConvStepJob {
-    int nb, H, P, G, N;
-    const void* zx;
-    int64_t ld;
-    const float *conv_w, *conv_b, *dt_bias;
-    void* cs;
-    int64_t cs_bs;
-    void *x, *B, *C, *dt;
-};
-hipError_t launch_conv_step(const ConvStepJob& j, hipStream_t st);
-hipError_t launch_decode_strided(int nb, int H, int P, int G, int N, const void* x, const void* dt, const float* A, const void* B,
-                                 const void* C, const float* D, float* state, int64_t state_bs, void* y, hipStream_t st);
 
 }  // namespace ssdk
