@@ -8,7 +8,6 @@ from __future__ import annotations
 
 import ctypes
 import os
-import weakref
 from typing import Optional
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -511,7 +510,8 @@ def ssd_linear_bwd(x, w, dout, want_dx=True, want_dw=True, flags=0, dx=None, dw=
     return {"dx": dx, "dw": dw}
 
 
-def _block_setup(u, params, nheads, headdim, ngroups, dstate, chunk, segment, eps):
+def _block_layout(u, params, nheads, headdim, ngroups, dstate, chunk, segment, eps):
+    """The shape descriptor of a block over u, what its parameters must be, its segments and convolved channels."""
     import torch
     if u.dim() != 2 or u.dtype != torch.bfloat16 or not u.is_cuda or not u.is_contiguous():
         raise ValueError("u must be a dense [L, d_model] bf16 device tensor")
@@ -523,15 +523,27 @@ def _block_setup(u, params, nheads, headdim, ngroups, dstate, chunk, segment, ep
             "norm_w": ((d_inner,), torch.float32), "W_out": ((dm, d_inner), torch.bfloat16)}
     if params.get("pre_norm_w") is not None:
         want["pre_norm_w"] = ((dm,), torch.float32)
-    for k, (shp, dty) in want.items():
-        t = params[k]
-        if tuple(t.shape) != shp or t.dtype != dty or not t.is_cuda or not t.is_contiguous():
-            raise ValueError(f"params[{k!r}] must be a dense {dty} device tensor of shape {shp}")
     seg = segment if segment is not None else max(chunk, -(-L // chunk) * chunk)
-    shape = magc_block_shape_t(dm, nheads, headdim, ngroups, dstate, chunk, eps, L, seg)
-    par = magc_block_params_t(*[_ptr(params.get(k)) for k in BLOCK_PARAMS])
-    nseg = max(1, -(-L // seg))
-    return shape, par, want, nseg, conv_dim
+    return magc_block_shape_t(dm, nheads, headdim, ngroups, dstate, chunk, eps, L, seg), want, max(1, -(-L // seg)), conv_dim
+
+
+def _block_pointers(params, want) -> list:
+    """The addresses of a block's parameters, each checked against what it must be."""
+    ptrs = []
+    for k in BLOCK_PARAMS:
+        if k not in want:
+            ptrs.append(None)
+            continue
+        t, (shp, dty) = params[k], want[k]
+        if t.shape != shp or t.dtype is not dty or not t.is_cuda or not t.is_contiguous():
+            raise ValueError(f"params[{k!r}] must be a dense {dty} device tensor of shape {shp}")
+        ptrs.append(t.data_ptr())
+    return ptrs
+
+
+def _block_setup(u, params, nheads, headdim, ngroups, dstate, chunk, segment, eps):
+    shape, want, nseg, conv_dim = _block_layout(u, params, nheads, headdim, ngroups, dstate, chunk, segment, eps)
+    return shape, magc_block_params_t(*_block_pointers(params, want)), want, nseg, conv_dim
 
 
 def _block_states(init_ssm, init_conv, nheads, headdim, dstate, conv_dim, conv_dtype):
@@ -598,50 +610,15 @@ def magc_block_bwd(u, params, dout, ssm_ckpt, conv_ckpt, nheads, headdim, ngroup
     return res
 
 
-# Parameter tables of stacks that have been checked: found again, a generation step spends a few microseconds on them instead
-# of 5 per layer.  An entry is used only while every tensor is the very object it was made from (weak references: nothing is
-# kept alive) at the address it had; bounded.
-_stacks: dict = {}
-
-
-def _same_layers(layers, refs, ptrs):
-    i = 0
-    for p in layers:
-        for k in BLOCK_PARAMS:
-            t = p.get(k)
-            if t is None:
-                if ptrs[i] is not None:
-                    return False
-            elif refs[i] is None or refs[i]() is not t or t.data_ptr() != ptrs[i]:
-                return False
-            i += 1
-    return True
-
-
 def _blockstack_setup(x0, layers, nheads, headdim, ngroups, dstate, chunk, segment, layer_interval, eps):
-    import torch
-    if x0.dim() != 2 or x0.dtype is not torch.bfloat16 or not x0.is_cuda or not x0.is_contiguous():
-        raise ValueError("u must be a dense [L, d_model] bf16 device tensor")
-    L, dm = x0.shape
-    key = (id(layers[0]["W_in"]), len(layers), dm, nheads, headdim, ngroups, dstate)
-    hit = _stacks.get(key)
-    if hit is not None and _same_layers(layers, hit[0], hit[1]):
-        _, _, pars, want, conv_dim = hit
-        seg = segment if segment is not None else max(chunk, -(-L // chunk) * chunk)
-        shape = magc_block_shape_t(dm, nheads, headdim, ngroups, dstate, chunk, eps, L, seg)
-        return magc_blockstack_shape_t(shape, len(layers), layer_interval), pars, want, max(1, -(-L // seg)), conv_dim
-    shape, _, want, nseg, conv_dim = _block_setup(x0, layers[0], nheads, headdim, ngroups, dstate, chunk, segment, eps)
-    for p in layers[1:]:
-        _block_setup(x0, p, nheads, headdim, ngroups, dstate, chunk, segment, eps)
-    if any((p.get("pre_norm_w") is None) != (layers[0].get("pre_norm_w") is None) for p in layers):
-        raise ValueError("either every layer has pre_norm_w or none")
-    pars = (magc_block_params_t * len(layers))(*[magc_block_params_t(*[_ptr(p.get(k)) for k in BLOCK_PARAMS]) for p in layers])
-    sshape = magc_blockstack_shape_t(shape, len(layers), layer_interval)
-    flat = [p.get(k) for p in layers for k in BLOCK_PARAMS]
-    if len(_stacks) >= 64:
-        _stacks.clear()
-    _stacks[key] = ([None if t is None else weakref.ref(t) for t in flat], [_ptr(t) for t in flat], pars, want, conv_dim)
-    return sshape, pars, want, nseg, conv_dim
+    shape, want, nseg, conv_dim = _block_layout(x0, layers[0], nheads, headdim, ngroups, dstate, chunk, segment, eps)
+    norm, ptrs = "pre_norm_w" in want, []
+    for p in layers:
+        if (p.get("pre_norm_w") is not None) != norm:
+            raise ValueError("either every layer has pre_norm_w or none")
+        ptrs += _block_pointers(p, want)
+    pars = (magc_block_params_t * len(layers)).from_buffer((ctypes.c_void_p * len(ptrs))(*ptrs))
+    return magc_blockstack_shape_t(shape, len(layers), layer_interval), pars, want, nseg, conv_dim
 
 
 def magc_blockstack_fwd(x0, layers, nheads, headdim, ngroups, dstate, chunk, segment, layer_interval, eps=1e-5):
