@@ -9,11 +9,11 @@
 // contiguous ("k-major": rows of x for the forward product) or with it as the row index (x and dout for
 // dw, w for dx).  Both kinds are staged in LDS exactly as they lie in memory (16-byte vectors); k-major
 // tiles are read back as plain 16-byte operands, the others through the transposing LDS read.
-// Two tilings: 256 x 256 per workgroup (four waves of 128 x 128: the whole accumulator file, one workgroup per
-// compute unit, hand-laid-out K step; k_gemm_big) wherever that yields enough tiles, else 256 x 128 (two
-// workgroups per compute unit; k_gemm).  Workgroup ids are remapped so that each XCD works on a compact
+// One kernel, three tilings: 256 x 256, 256 x 192 or 256 x 128 per workgroup (four waves of 128 x 128 / 96 / 64, one
+// workgroup per compute unit, hand-laid-out K step); the launch rule below chooses the one whose tiles fit the
+// machine best.  Workgroup ids are remapped so that each XCD works on a compact
 // block of the tile grid (its L2 then holds the A and B panels that block shares).
-#include <stdlib.h>
+#include <stdint.h>
 #include <string.h>
 
 #include <mutex>
@@ -94,6 +94,28 @@ __device__ __forceinline__ void load_tile(const bf16_t* origin, int64_t ld, uint
     }
 }
 
+// The same for a whole K step as a buffer access: the descriptor spans the memory rows of the step that exist, and of a
+// tile with the contraction index as the row index the threads outside its columns start beyond that span (their
+// offset, see edge_voff).  Whatever lies outside reads as zeros, without a branch: the tiles at the edges of the
+// matrices take the straight-line loop like all others (1905 x 10576 -> 2560: 279 -> 213 us).  Offsets stay below 2^31 for row strides up to MAX_LD.
+constexpr int64_t MAX_LD = 1 << 22;
+template <int ROWS, bool KMAJOR>
+__device__ __forceinline__ uint32_t edge_voff(int64_t ld, int rows_left, int tid) {
+    return !KMAJOR && (tid % (ROWS / 8)) * 8 >= rows_left ? 0x80000000u : tile_voff<ROWS, KMAJOR>(ld, tid);
+}
+template <int ROWS, bool KMAJOR>
+__device__ __forceinline__ rsrc_t step_rows(const bf16_t* origin, int64_t ld, int rows_left) {
+    const int rows = rows_left < ROWS ? rows_left : ROWS;
+    const uint32_t bytes = KMAJOR ? (uint32_t)(rows - 1) * (uint32_t)(ld * 2) + 2 * BKK : (BKK - 1) * (uint32_t)(ld * 2) + 2 * ROWS;
+    return __builtin_amdgcn_make_buffer_rsrc((void*)origin, 0, bytes, 0x00020000);
+}
+template <int ROWS, bool KMAJOR, int I>
+__device__ __forceinline__ void load_step(rsrc_t r, int64_t ld, uint32_t voff, bf16x8 (&reg)[ROWS / 32]) {
+    constexpr int VPR = KMAJOR ? 8 : ROWS / 8;
+    static_assert(256 % VPR == 0, "a thread's vectors share a column");
+    reg[I] = rows_load(r, voff + (uint32_t)(I * (256 / VPR)) * (uint32_t)(ld * 2));
+}
+
 template <int ROWS, bool KMAJOR, int I0 = 0, int I1 = ROWS / 32>
 __device__ __forceinline__ void store_tile(char* lds, int tid, const bf16x8 (&reg)[ROWS / 32]) {
 #pragma unroll
@@ -152,70 +174,9 @@ __device__ __forceinline__ void store_acc(const GemmParams& gp, const f32x16 (&a
     }
 }
 
-// WI x WJ MFMA tiles per wave, 2 x 2 waves: workgroup tile (64 WI) x (64 WJ), one LDS buffer, two barriers per
-// K step; registers and LDS leave room for two workgroups per compute unit, which cover each other's waits.
-// Used where the large tiles below would be too few to fill the machine.
-template <bool AK, bool BK, int WI, int WJ>
-__global__ __launch_bounds__(256, 2) void k_gemm(GemmParams gp) {
-    constexpr int BM = 64 * WI, BN = 64 * WJ;
-    constexpr int A_BYTES = tile_bytes<BM, AK>();
-    extern __shared__ __attribute__((aligned(16))) char lds[];  // A tile, B tile
-    char* As = lds;
-    char* Bs = lds + A_BYTES;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int wm = w >> 1, wn = w & 1;
-    int tm, tn;
-    tile_of(gp, tm, tn);
-    const int m0 = tm * BM, n0 = tn * BN;
-
-    f32x16 acc[WI][WJ];
-#pragma unroll
-    for (int i = 0; i < WI; ++i)
-#pragma unroll
-        for (int j = 0; j < WJ; ++j) acc[i][j] = zero16();
-
-    // tiles that lie wholly inside the matrices take the unmasked loads for every whole K step
-    const bool interior = m0 + BM <= gp.M && n0 + BN <= gp.N;
-    const uint32_t va = tile_voff<BM, AK>(gp.lda, tid), vb = tile_voff<BN, BK>(gp.ldb, tid);
-    bf16x8 ra[BM / 32], rb[BN / 32];
-    auto fetch = [&](int k0) {
-        const bf16_t* ao = AK ? gp.A + (int64_t)m0 * gp.lda + k0 : gp.A + (int64_t)k0 * gp.lda + m0;
-        const bf16_t* bo = BK ? gp.B + (int64_t)n0 * gp.ldb + k0 : gp.B + (int64_t)k0 * gp.ldb + n0;
-        if (interior && k0 + BKK <= gp.K) {
-            load_tile<BM, AK, false>(ao, gp.lda, va, 0, 0, tid, ra);
-            load_tile<BN, BK, false>(bo, gp.ldb, vb, 0, 0, tid, rb);
-        } else {
-            load_tile<BM, AK, true>(ao, gp.lda, va, gp.M - m0, gp.K - k0, tid, ra);
-            load_tile<BN, BK, true>(bo, gp.ldb, vb, gp.N - n0, gp.K - k0, tid, rb);
-        }
-    };
-    fetch(0);
-    for (int k0 = 0; k0 < gp.K; k0 += BKK) {
-        store_tile<BM, AK>(As, tid, ra);
-        store_tile<BN, BK>(Bs, tid, rb);
-        __syncthreads();
-        if (k0 + BKK < gp.K) fetch(k0 + BKK);  // next step's loads fly during the products
-#pragma unroll
-        for (int kk = 0; kk < BKK; kk += 16) {
-            bf16x8 a[WI], b[WJ];
-#pragma unroll
-            for (int i = 0; i < WI; ++i) a[i] = operand<BM, AK>(As, wm * 32 * WI + i * 32, kk, lane);
-#pragma unroll
-            for (int j = 0; j < WJ; ++j) b[j] = operand<BN, BK>(Bs, wn * 32 * WJ + j * 32, kk, lane);
-#pragma unroll
-            for (int i = 0; i < WI; ++i)
-#pragma unroll
-                for (int j = 0; j < WJ; ++j) acc[i][j] = mfma(b[j], a[i], acc[i][j]);
-        }
-        __syncthreads();
-    }
-
-    store_acc<WI, WJ>(gp, acc, m0 + wm * 32 * WI, n0 + wn * 32 * WJ, lane, interior);
-}
-
-// 256 x 256 tile, four waves of 128 x 128 (4 x 4 MFMA tiles: the whole accumulator register file), one
+// 256 x 64 WJ tile, four waves of 128 x 32 WJ (WJ = 4: 4 x 4 MFMA tiles, the whole accumulator register file), one
 // workgroup per compute unit, two LDS buffers.  With a single wave per SIMD nothing else hides latency, so
-// the K step is laid out by hand as 16 units of four MFMAs (one A operand against the four B operands of
+// the K step is laid out by hand as 16 units of WJ MFMAs (one A operand against the WJ B operands of
 // its k slice); behind each MFMA sit the LDS reads of later operands and (last eight units) one vector of
 // the next tile's LDS writes with the global load that refills its register for the tile after that.
 // Registers thus hold the tile two K steps ahead of the one being multiplied: a vector is written to LDS
@@ -225,18 +186,18 @@ struct BigCtx {
     const bf16_t* a_org;  // tile origin at k = 0
     const bf16_t* b_org;
     int64_t lda, ldb, a_kstep, b_kstep;
-    uint32_t va, vb;
+    uint32_t va, vb;      // offsets of the thread's vectors in a K step (buffer accesses)
     int rows_a, rows_b, K;  // extents left from the tile origin (masks)
     int tid, lane, wm, wn;
 };
 
-// One K step.  STEADY: the registers hold a next tile, there is one after it, and neither needs masks --
+// One K step.  STEADY: the registers hold a next tile, there is one after it, and both are whole K steps --
 // straight-line code (no branches: the compiler then counts outstanding loads exactly instead of draining
-// them at every join).  Otherwise the same step with run-time conditions, for the last steps and edge tiles.
-template <bool AK, bool BK, bool STEADY>
-__device__ __forceinline__ void big_step(const BigCtx& cx, f32x16 (&acc)[4][4], bf16x8 (&ra)[8], bf16x8 (&rb)[8], const char* As,
+// them at every join).  Otherwise the same step with run-time conditions, for the last steps.
+template <bool AK, bool BK, int WJ, bool STEADY>
+__device__ __forceinline__ void big_step(const BigCtx& cx, f32x16 (&acc)[4][WJ], bf16x8 (&ra)[8], bf16x8 (&rb)[2 * WJ], const char* As,
                                          char* An, int k0) {
-    constexpr int BM = 256, BN = 256;
+    constexpr int BM = 256, BN = 64 * WJ;
     constexpr int A_BYTES = tile_bytes<BM, AK>();
     const char* Bs = As + A_BYTES;
     char* Bn = An + A_BYTES;
@@ -246,44 +207,49 @@ __device__ __forceinline__ void big_step(const BigCtx& cx, f32x16 (&acc)[4][4], 
     const bf16_t* ao = cx.a_org + (int64_t)k2 * cx.a_kstep;
     const bf16_t* bo = cx.b_org + (int64_t)k2 * cx.b_kstep;
     const int lane = cx.lane, tid = cx.tid;
-    bf16x8 aq[2], bq[2][4];
+    rsrc_t sa, sb;
+    uint32_t va = cx.va, vb = cx.vb;
+    if (STEADY) {
+        // the offsets of the other vectors are added up here: kept over the loop they would cost 16 registers
+        asm volatile("" : "+v"(va), "+v"(vb));
+        sa = step_rows<BM, AK>(ao, cx.lda, cx.rows_a);
+        sb = step_rows<BN, BK>(bo, cx.ldb, cx.rows_b);
+    }
+    bf16x8 aq[2], bq[2][WJ];
     aq[0] = operand<BM, AK>(As, cx.wm * 128, 0, lane);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) bq[0][j] = operand<BN, BK>(Bs, cx.wn * 128 + j * 32, 0, lane);
+    for (int j = 0; j < WJ; ++j) bq[0][j] = operand<BN, BK>(Bs, cx.wn * 32 * WJ + j * 32, 0, lane);
     // An MFMA keeps the matrix pipe busy for 32 cycles but takes only a few to issue: every memory
     // instruction is placed right behind an MFMA, so that it issues in that MFMA's shadow.
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
         const int kk = u >> 2, i = u & 3;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < WJ; ++j) {
             acc[i][j] = mfma(bq[kk & 1][j], aq[u & 1], acc[i][j]);
             // operand reads: the next unit's A operand, and over unit 1 of a k slice the next slice's B operands
             if (j == 0 && u + 1 < 16) aq[(u + 1) & 1] = operand<BM, AK>(As, cx.wm * 128 + ((u + 1) & 3) * 32, ((u + 1) >> 2) * 16, lane);
-            if (i == 1 && kk < 3) bq[(kk + 1) & 1][j] = operand<BN, BK>(Bs, cx.wn * 128 + j * 32, (kk + 1) * 16, lane);
+            if (i == 1 && kk < 3) bq[(kk + 1) & 1][j] = operand<BN, BK>(Bs, cx.wn * 32 * WJ + j * 32, (kk + 1) * 16, lane);
             if (STEADY) {
-                // units 8..15: behind MFMA 0 a vector of A, behind MFMA 2 a vector of B goes to LDS and its register is refilled
-#define GEMM_PART(U, J, OP_A, V)                                                                  \
-    if (u == U && j == J) {                                                                       \
-        if (OP_A) {                                                                               \
-            store_tile<BM, AK, V, V + 1>(An, tid, ra);                                            \
-            load_tile<BM, AK, false, V, V + 1>(ao, cx.lda, cx.va, 0, 0, tid, ra);                 \
-        } else {                                                                                  \
+                // units 8..15: behind MFMA 0 a vector of A, behind a later one a vector of B (while there are any) goes to LDS and its register is refilled
+#define GEMM_PART(V)                                                                              \
+    if (u == 8 + V && j == 0) {                                                                   \
+        store_tile<BM, AK, V, V + 1>(An, tid, ra);                                                \
+        load_step<BM, AK, V>(sa, cx.lda, va, ra);                                              \
+    }                                                                                             \
+    if constexpr (V < 2 * WJ)                                                                     \
+        if (u == 8 + V && j == WJ / 2) {                                                          \
             store_tile<BN, BK, V, V + 1>(Bn, tid, rb);                                            \
-            load_tile<BN, BK, false, V, V + 1>(bo, cx.ldb, cx.vb, 0, 0, tid, rb);                 \
-        }                                                                                         \
-    }
-                GEMM_PART(8, 0, true, 0) GEMM_PART(8, 2, false, 0) GEMM_PART(9, 0, true, 1) GEMM_PART(9, 2, false, 1)
-                GEMM_PART(10, 0, true, 2) GEMM_PART(10, 2, false, 2) GEMM_PART(11, 0, true, 3) GEMM_PART(11, 2, false, 3)
-                GEMM_PART(12, 0, true, 4) GEMM_PART(12, 2, false, 4) GEMM_PART(13, 0, true, 5) GEMM_PART(13, 2, false, 5)
-                GEMM_PART(14, 0, true, 6) GEMM_PART(14, 2, false, 6) GEMM_PART(15, 0, true, 7) GEMM_PART(15, 2, false, 7)
+            load_step<BN, BK, V>(sb, cx.ldb, vb, rb);                                          \
+        }
+                GEMM_PART(0) GEMM_PART(1) GEMM_PART(2) GEMM_PART(3) GEMM_PART(4) GEMM_PART(5) GEMM_PART(6) GEMM_PART(7)
 #undef GEMM_PART
             } else if (u == 8 && j == 0 && more) {
                 store_tile<BM, AK>(An, tid, ra);
                 store_tile<BN, BK>(Bn, tid, rb);
                 if (more2) {
-                    load_tile<BM, AK, true>(ao, cx.lda, cx.va, cx.rows_a, cx.K - k2, tid, ra);
-                    load_tile<BN, BK, true>(bo, cx.ldb, cx.vb, cx.rows_b, cx.K - k2, tid, rb);
+                    load_tile<BM, AK, true>(ao, cx.lda, tile_voff<BM, AK>(cx.lda, tid), cx.rows_a, cx.K - k2, tid, ra);
+                    load_tile<BN, BK, true>(bo, cx.ldb, tile_voff<BN, BK>(cx.ldb, tid), cx.rows_b, cx.K - k2, tid, rb);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -291,9 +257,9 @@ __device__ __forceinline__ void big_step(const BigCtx& cx, f32x16 (&acc)[4][4], 
     }
 }
 
-template <bool AK, bool BK>
+template <bool AK, bool BK, int WJ>
 __global__ __launch_bounds__(256, 1) void k_gemm_big(GemmParams gp) {
-    constexpr int BM = 256, BN = 256;
+    constexpr int BM = 256, BN = 64 * WJ;
     constexpr int A_BYTES = tile_bytes<BM, AK>(), B_BYTES = tile_bytes<BN, BK>();
     extern __shared__ __attribute__((aligned(16))) char lds[];  // 2 x (A tile, B tile)
     const int tid = threadIdx.x, w = tid >> 6;
@@ -301,11 +267,11 @@ __global__ __launch_bounds__(256, 1) void k_gemm_big(GemmParams gp) {
     tile_of(gp, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
 
-    f32x16 acc[4][4];
+    f32x16 acc[4][WJ];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = zero16();
+        for (int j = 0; j < WJ; ++j) acc[i][j] = zero16();
 
     const bool interior = m0 + BM <= gp.M && n0 + BN <= gp.N;
     BigCtx cx;
@@ -315,10 +281,10 @@ __global__ __launch_bounds__(256, 1) void k_gemm_big(GemmParams gp) {
     cx.ldb = gp.ldb;
     cx.a_kstep = AK ? 1 : gp.lda;  // elements per unit of k
     cx.b_kstep = BK ? 1 : gp.ldb;
-    cx.va = tile_voff<BM, AK>(gp.lda, tid);
-    cx.vb = tile_voff<BN, BK>(gp.ldb, tid);
     cx.rows_a = gp.M - m0;
     cx.rows_b = gp.N - n0;
+    cx.va = edge_voff<BM, AK>(gp.lda, cx.rows_a, tid);
+    cx.vb = edge_voff<BN, BK>(gp.ldb, cx.rows_b, tid);
     cx.K = gp.K;
     cx.tid = tid;
     cx.lane = tid & 63;
@@ -326,58 +292,62 @@ __global__ __launch_bounds__(256, 1) void k_gemm_big(GemmParams gp) {
     cx.wn = w & 1;
     const int lane = cx.lane, wm = cx.wm, wn = cx.wn;
 
-    bf16x8 ra[8], rb[8];
-    const bool steady = interior && 3 * BKK <= gp.K;  // at least one step of the straight-line loop
+    bf16x8 ra[8], rb[2 * WJ];
+    const bool steady = 3 * BKK <= gp.K && gp.lda <= MAX_LD && gp.ldb <= MAX_LD;  // at least one step of the straight-line loop
     if (steady) {
         // the same order of loads (A and B vector by vector) as inside the loop, so that the count of
         // loads still outstanding at the loop's first LDS write is the same on entry and on every repeat
-#define GEMM_PRO(P, KOFF)                                                                                          \
-    load_tile<BM, AK, false, P, P + 1>(cx.a_org + (int64_t)(KOFF) * cx.a_kstep, gp.lda, cx.va, 0, 0, tid, ra);      \
-    load_tile<BN, BK, false, P, P + 1>(cx.b_org + (int64_t)(KOFF) * cx.b_kstep, gp.ldb, cx.vb, 0, 0, tid, rb);
-        GEMM_PRO(0, 0) GEMM_PRO(1, 0) GEMM_PRO(2, 0) GEMM_PRO(3, 0) GEMM_PRO(4, 0) GEMM_PRO(5, 0) GEMM_PRO(6, 0) GEMM_PRO(7, 0)
+#define GEMM_PRO(V)                                                       \
+    load_step<BM, AK, V>(sa, gp.lda, cx.va, ra);                          \
+    if constexpr (V < 2 * WJ) load_step<BN, BK, V>(sb, gp.ldb, cx.vb, rb);
+        rsrc_t sa = step_rows<BM, AK>(cx.a_org, gp.lda, cx.rows_a), sb = step_rows<BN, BK>(cx.b_org, gp.ldb, cx.rows_b);
+        GEMM_PRO(0) GEMM_PRO(1) GEMM_PRO(2) GEMM_PRO(3) GEMM_PRO(4) GEMM_PRO(5) GEMM_PRO(6) GEMM_PRO(7)
         store_tile<BM, AK>(lds, tid, ra);
         store_tile<BN, BK>(lds + A_BYTES, tid, rb);
-        GEMM_PRO(0, BKK) GEMM_PRO(1, BKK) GEMM_PRO(2, BKK) GEMM_PRO(3, BKK) GEMM_PRO(4, BKK) GEMM_PRO(5, BKK) GEMM_PRO(6, BKK) GEMM_PRO(7, BKK)
+        sa = step_rows<BM, AK>(cx.a_org + (int64_t)BKK * cx.a_kstep, gp.lda, cx.rows_a);
+        sb = step_rows<BN, BK>(cx.b_org + (int64_t)BKK * cx.b_kstep, gp.ldb, cx.rows_b);
+        GEMM_PRO(0) GEMM_PRO(1) GEMM_PRO(2) GEMM_PRO(3) GEMM_PRO(4) GEMM_PRO(5) GEMM_PRO(6) GEMM_PRO(7)
 #undef GEMM_PRO
     } else {
-        load_tile<BM, AK, true>(cx.a_org, gp.lda, cx.va, cx.rows_a, gp.K, tid, ra);
-        load_tile<BN, BK, true>(cx.b_org, gp.ldb, cx.vb, cx.rows_b, gp.K, tid, rb);
+        load_tile<BM, AK, true>(cx.a_org, gp.lda, tile_voff<BM, AK>(gp.lda, tid), cx.rows_a, gp.K, tid, ra);
+        load_tile<BN, BK, true>(cx.b_org, gp.ldb, tile_voff<BN, BK>(gp.ldb, tid), cx.rows_b, gp.K, tid, rb);
         store_tile<BM, AK>(lds, tid, ra);
         store_tile<BN, BK>(lds + A_BYTES, tid, rb);
         if (BKK < gp.K) {
-            load_tile<BM, AK, true>(cx.a_org + (int64_t)BKK * cx.a_kstep, gp.lda, cx.va, cx.rows_a, gp.K - BKK, tid, ra);
-            load_tile<BN, BK, true>(cx.b_org + (int64_t)BKK * cx.b_kstep, gp.ldb, cx.vb, cx.rows_b, gp.K - BKK, tid, rb);
+            load_tile<BM, AK, true>(cx.a_org + (int64_t)BKK * cx.a_kstep, gp.lda, tile_voff<BM, AK>(gp.lda, tid), cx.rows_a, gp.K - BKK, tid, ra);
+            load_tile<BN, BK, true>(cx.b_org + (int64_t)BKK * cx.b_kstep, gp.ldb, tile_voff<BN, BK>(gp.ldb, tid), cx.rows_b, gp.K - BKK, tid, rb);
         }
     }
     __syncthreads();
     int cur = 0, k0 = 0;
     if (steady) {  // steps whose next two tiles are whole
         for (; k0 + 3 * BKK <= gp.K; k0 += BKK) {
-            big_step<AK, BK, true>(cx, acc, ra, rb, lds + cur * (A_BYTES + B_BYTES), lds + (cur ^ 1) * (A_BYTES + B_BYTES), k0);
+            big_step<AK, BK, WJ, true>(cx, acc, ra, rb, lds + cur * (A_BYTES + B_BYTES), lds + (cur ^ 1) * (A_BYTES + B_BYTES), k0);
             cur ^= 1;
             __syncthreads();
         }
     }
     for (; k0 < gp.K; k0 += BKK) {
-        big_step<AK, BK, false>(cx, acc, ra, rb, lds + cur * (A_BYTES + B_BYTES), lds + (cur ^ 1) * (A_BYTES + B_BYTES), k0);
+        big_step<AK, BK, WJ, false>(cx, acc, ra, rb, lds + cur * (A_BYTES + B_BYTES), lds + (cur ^ 1) * (A_BYTES + B_BYTES), k0);
         cur ^= 1;
         __syncthreads();
     }
 
     if (gp.c_f32) {  // weight gradients: K is the token count, the epilogue does not matter
-        store_acc<4, 4>(gp, acc, m0 + wm * 128, n0 + wn * 128, lane, interior);
+        store_acc<4, WJ>(gp, acc, m0 + wm * 128, n0 + wn * 32 * WJ, lane, interior);
         return;
     }
     // bf16 result: through LDS (free now; every wave has left the K loop behind the last barrier), so that
-    // a store instruction writes whole 256-byte row pieces instead of 32 scattered 16-byte ones.  Each wave
-    // transposes its own 128 x 128 tile in a private patch: lane -> row lane % 32, four consecutive columns
+    // a store instruction writes whole row pieces (256 bytes at WJ = 4) instead of 32 scattered 16-byte ones.  Each wave
+    // transposes its own 128 x 32 WJ tile in a private patch: lane -> row lane % 32, four consecutive columns
     // per register group (see store_acc) on the way in, 16-byte vectors of a row on the way out.
-    constexpr int EPITCH = 256 + 16;
+    constexpr int VPR = 4 * WJ, EPITCH = 16 * VPR + 16;  // vectors per row
+    static_assert(4 * 128 * EPITCH <= 2 * (A_BYTES + B_BYTES), "");
     char* patch = lds + w * (128 * EPITCH);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < WJ; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const f32x16& t = acc[i][j];
@@ -385,60 +355,75 @@ __global__ __launch_bounds__(256, 1) void k_gemm_big(GemmParams gp) {
                 v[0] = (__bf16)t[4 * q]; v[1] = (__bf16)t[4 * q + 1]; v[2] = (__bf16)t[4 * q + 2]; v[3] = (__bf16)t[4 * q + 3];
                 *(bf16x4*)(patch + (i * 32 + (lane & 31)) * EPITCH + (j * 32 + q * 8 + (lane >> 5) * 4) * 2) = v;
             }
-    const int col = n0 + wn * 128 + (lane & 15) * 8;
 #pragma unroll 8
-    for (int it = 0; it < 32; ++it) {
-        const int r = it * 4 + (lane >> 4), row = m0 + wm * 128 + r;
-        const bf16x8 v = *(const bf16x8*)(patch + r * EPITCH + (lane & 15) * 16);
-        if (interior || (row < gp.M && col < gp.N)) *(bf16x8*)((__bf16*)gp.C + (int64_t)row * gp.ldc + col) = v;
+    for (int it = 0; it < 2 * VPR; ++it) {
+        const int v = it * 64 + lane, r = v / VPR, c = v % VPR, row = m0 + wm * 128 + r, col = n0 + wn * 32 * WJ + c * 8;
+        const bf16x8 o = *(const bf16x8*)(patch + r * EPITCH + c * 16);
+        if (interior || (row < gp.M && col < gp.N)) *(bf16x8*)((__bf16*)gp.C + (int64_t)row * gp.ldc + col) = o;
     }
 }
 
 bool ok_ptr(const void* p) { return p && ((uintptr_t)p & 15) == 0; }
 
-template <bool AK, bool BK, int WI, int WJ>
-hipError_t launch_cfg(GemmParams gp, hipStream_t st) {
-    constexpr int BM = 64 * WI, BN = 64 * WJ;
-    constexpr int LDS = tile_bytes<BM, AK>() + tile_bytes<BN, BK>();
-    static_assert(LDS <= 65536, "beyond the default dynamic LDS limit");
-    gp.tiles_m = (gp.M + BM - 1) / BM;
-    gp.tiles_n = (gp.N + BN - 1) / BN;
-    hipLaunchKernelGGL((k_gemm<AK, BK, WI, WJ>), dim3(gp.tiles_m * gp.tiles_n), dim3(256), LDS, st, gp);
-    return hipGetLastError();
-}
-
-template <bool AK, bool BK>
+template <bool AK, bool BK, int WJ>
 hipError_t launch_big(GemmParams gp, hipStream_t st) {
-    constexpr int LDS = 2 * (tile_bytes<256, AK>() + tile_bytes<256, BK>());
+    constexpr int BN = 64 * WJ, LDS = 2 * (tile_bytes<256, AK>() + tile_bytes<BN, BK>());
     static bool raised[64];  // per device: the kernel uses more dynamic LDS than the default limit
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!raised[dev]) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_gemm_big<AK, BK>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        hipError_t e = hipFuncSetAttribute((const void*)k_gemm_big<AK, BK, WJ>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (e != hipSuccess) return e;
         raised[dev] = true;
     }
     gp.tiles_m = (gp.M + 255) / 256;
-    gp.tiles_n = (gp.N + 255) / 256;
-    hipLaunchKernelGGL((k_gemm_big<AK, BK>), dim3(gp.tiles_m * gp.tiles_n), dim3(256), LDS, st, gp);
+    gp.tiles_n = (gp.N + BN - 1) / BN;
+    hipLaunchKernelGGL((k_gemm_big<AK, BK, WJ>), dim3(gp.tiles_m * gp.tiles_n), dim3(256), LDS, st, gp);
     return hipGetLastError();
 }
 
-// 256 x 256 tiles (one workgroup per compute unit) unless there are too few of them to occupy half the
-// machine; then 256 x 128 tiles, two workgroups per compute unit.  SSD_MAGC_GEMM_TILE=128 / 256 in the
-// environment forces one of the two (a diagnostic).
-template <bool AK, bool BK>
-hipError_t launch_gemm(const GemmParams& gp, hipStream_t st) {
-    static const int forced = [] {
-        const char* e = getenv("SSD_MAGC_GEMM_TILE");
-        return e ? atoi(e) : 0;
-    }();
-    bool big = true;
-    if (forced == 128) big = false;
-    if (forced != 128 && forced != 256) {
-        big = (int64_t)((gp.M + 255) / 256) * ((gp.N + 255) / 256) >= 128;
+// Which tile width (64 WJ columns).  A compute unit holds one workgroup, so a product takes ceil(tiles / 256) rounds, and
+// a round with narrower tiles is cheaper, though by less than its share of the arithmetic (more LDS and cache traffic per
+// MFMA).  Cost of a round against 256 columns, measured over 200 ... 16384 rows at widths 768 ... 2560: forward product
+// 0.81-0.88 at 192 columns and 0.66-0.86 (one round) / 0.69-0.74 (several) at 128; the gradients' products 0.68-0.90 at 128.
+// What it gives (us, at 256 columns -> chosen): 4096 x 5120 -> 2560: 114 -> 100 (224 tiles of 192 instead of 160 of 256);
+// 1905 x 2560 -> 10576: 127 -> 105; 1905 x 5120 -> 2560: 98 -> 86; 600 x 1024 -> 4384: 28 -> 21.
+constexpr int64_t UNITS = 256;
+int64_t tile_count(const GemmParams& gp, int wj) { return (int64_t)((gp.M + 255) / 256) * ((gp.N + 64 * wj - 1) / (64 * wj)); }
+int64_t tile_cost(const GemmParams& gp, int percent) { return (int64_t)((gp.K + BKK - 1) / BKK) * percent; }  // of one tile
+constexpr int FWD_PCT[5] = {0, 0, 72, 83, 100}, BWD_PCT[5] = {0, 0, 85, 0, 100};  // by WJ
+
+int forward_width(const GemmParams& gp) {
+    int best = 4;
+    int64_t t = INT64_MAX;
+    for (int wj = 4; wj >= 2; --wj) {
+        const int64_t c = (tile_count(gp, wj) + UNITS - 1) / UNITS * FWD_PCT[wj];
+        if (c < t) t = c, best = wj;
     }
-    return big ? launch_big<AK, BK>(gp, st) : launch_cfg<AK, BK, 4, 2>(gp, st);
+    return best;
+}
+
+// Widths of the gradients' products: 4 or 2 (192 columns do not divide among the threads where the contraction index is the
+// row index).  Side by side they fill the machine together: while all tiles are resident at once the longer chain counts;
+// else the work spread over the machine plus half a chain of ragged end, and no less than a short tile in front of a
+// long one.  2560 <-> 10576, us for both (256 columns for all -> chosen): 200 rows 220 -> 188; 4096 rows stay at 256 columns
+// (417; all at 128: 563); 1024 <-> 4384, 4096 rows: all at 256 116, all at 128 (272 tiles) 167, chosen as here 116.
+void backward_widths(const GemmParams* dx, const GemmParams* dw, bool together, int& wx, int& ww) {
+    int64_t best = INT64_MAX;
+    wx = ww = 4;
+    for (int a = 4; a >= 2; a -= 2)
+        for (int b = 4; b >= 2; b -= 2) {
+            const int64_t ta = dx ? tile_count(*dx, a) : 0, ca = dx ? tile_cost(*dx, BWD_PCT[a]) : 0;
+            const int64_t tb = dw ? tile_count(*dw, b) : 0, cb = dw ? tile_cost(*dw, BWD_PCT[b]) : 0;
+            int64_t t;
+            if (!together) {
+                t = (ta + UNITS - 1) / UNITS * ca + (tb + UNITS - 1) / UNITS * cb;
+            } else {
+                const int64_t longer = ca > cb ? ca : cb, spread = (ta * ca + tb * cb) / UNITS + longer / 2;
+                t = ta + tb <= UNITS ? longer : (spread > ca + cb ? spread : ca + cb);
+            }
+            if (t < best) best = t, wx = a, ww = b;
+        }
 }
 
 // The two gradient products of a call are independent (both read dout; they write dx and dw).  One of them
@@ -533,7 +518,10 @@ extern "C" int ssd_linear_fwd(int64_t rows, int32_t in_dim, int32_t out_dim, con
     gp.M = (int)rows;
     gp.N = out_dim;
     gp.K = in_dim;
-    return launch_gemm<true, true>(gp, (hipStream_t)hip_stream) == hipSuccess ? SSD_OK : SSD_ERR_LAUNCH;
+    const int wj = forward_width(gp);
+    const hipStream_t st = (hipStream_t)hip_stream;
+    const hipError_t e = wj == 4 ? launch_big<true, true, 4>(gp, st) : wj == 3 ? launch_big<true, true, 3>(gp, st) : launch_big<true, true, 2>(gp, st);
+    return e == hipSuccess ? SSD_OK : SSD_ERR_LAUNCH;
 }
 
 extern "C" int ssd_linear_bwd(int64_t rows, int32_t in_dim, int32_t out_dim, const void* x, int64_t x_row_stride,
@@ -551,8 +539,32 @@ extern "C" int ssd_linear_bwd(int64_t rows, int32_t in_dim, int32_t out_dim, con
     }
     if (!dout || (dx && !w) || (dw && !x)) return SSD_ERR_NULL;
     if (!ok_ptr(dout) || (dx && (!ok_ptr(dx) || !ok_ptr(w))) || (dw && (!ok_ptr(x) || !ok_ptr(dw)))) return SSD_ERR_ARG;
-    GemmParams gp;
     const int64_t ldd = dout_row_stride ? dout_row_stride : out_dim;
+    GemmParams px, pw;
+    // dx[rows, in] = dout[rows, out] w[out, in]: contraction over out; w holds it as the row index
+    memset(&px, 0, sizeof(px));
+    px.A = (const bf16_t*)dout;
+    px.B = (const bf16_t*)w;
+    px.C = dx;
+    px.lda = ldd;
+    px.ldb = in_dim;
+    px.ldc = dx_row_stride ? dx_row_stride : in_dim;
+    px.M = (int)rows;
+    px.N = in_dim;
+    px.K = out_dim;
+    // dw[out, in] = dout^T x: contraction over the rows, the row index of both operands
+    memset(&pw, 0, sizeof(pw));
+    pw.A = (const bf16_t*)dout;
+    pw.B = (const bf16_t*)x;
+    pw.C = dw;
+    pw.lda = ldd;
+    pw.ldb = x_row_stride ? x_row_stride : in_dim;
+    pw.ldc = in_dim;
+    pw.M = out_dim;
+    pw.N = in_dim;
+    pw.K = (int)rows;
+    pw.c_f32 = 1;
+    pw.accumulate = accumulate;
     // both products wanted: the weight gradient goes to the side stream (see Side)
     Side* side = dx && dw && !serial_mode() ? side_for_current_device() : nullptr;
     hipStream_t st_w = st;
@@ -560,35 +572,12 @@ extern "C" int ssd_linear_bwd(int64_t rows, int32_t in_dim, int32_t out_dim, con
         if (hipEventRecord(side->fork, st) != hipSuccess || hipStreamWaitEvent(side->st, side->fork, 0) != hipSuccess) return SSD_ERR_LAUNCH;
         st_w = side->st;
     }
+    int wx, ww;
+    backward_widths(dx ? &px : nullptr, dw ? &pw : nullptr, side != nullptr, wx, ww);
     int status = SSD_OK;
-    if (dx) {  // dx[rows, in] = dout[rows, out] w[out, in]: contraction over out; w holds it as the row index
-        memset(&gp, 0, sizeof(gp));
-        gp.A = (const bf16_t*)dout;
-        gp.B = (const bf16_t*)w;
-        gp.C = dx;
-        gp.lda = ldd;
-        gp.ldb = in_dim;
-        gp.ldc = dx_row_stride ? dx_row_stride : in_dim;
-        gp.M = (int)rows;
-        gp.N = in_dim;
-        gp.K = out_dim;
-        if (launch_gemm<true, false>(gp, st) != hipSuccess) status = SSD_ERR_LAUNCH;
-    }
-    if (dw && status == SSD_OK) {  // dw[out, in] = dout^T x: contraction over the rows, the row index of both operands
-        memset(&gp, 0, sizeof(gp));
-        gp.A = (const bf16_t*)dout;
-        gp.B = (const bf16_t*)x;
-        gp.C = dw;
-        gp.lda = ldd;
-        gp.ldb = x_row_stride ? x_row_stride : in_dim;
-        gp.ldc = in_dim;
-        gp.M = out_dim;
-        gp.N = in_dim;
-        gp.K = (int)rows;
-        gp.c_f32 = 1;
-        gp.accumulate = accumulate;
-        if (launch_gemm<false, false>(gp, st_w) != hipSuccess) status = SSD_ERR_LAUNCH;
-    }
+    if (dx && (wx == 4 ? launch_big<true, false, 4>(px, st) : launch_big<true, false, 2>(px, st)) != hipSuccess) status = SSD_ERR_LAUNCH;
+    if (dw && status == SSD_OK && (ww == 4 ? launch_big<false, false, 4>(pw, st_w) : launch_big<false, false, 2>(pw, st_w)) != hipSuccess)
+        status = SSD_ERR_LAUNCH;
     // whatever reached the side stream ends before the caller's next work, also after a failed launch
     if (side && (hipEventRecord(side->join, side->st) != hipSuccess || hipStreamWaitEvent(st, side->join, 0) != hipSuccess)) return SSD_ERR_LAUNCH;
     return status;
