@@ -75,7 +75,7 @@ typedef struct ssd_shape_t {
     int32_t chunk;            /* Q: block length of the dual (quadratic) form; segment % Q == 0 */
     int64_t batch;            /* Bt */
     int64_t seqlen;           /* L (the paper's S), any length >= 0: a short last segment (and a short last chunk
-                                 inside it) is run on zero-padded copies kept in the workspace; the stack driver
+                                 inside it) is read and written in place; the stack driver
                                  needs L % segment == 0 */
     int64_t segment;          /* s: sequence-axis checkpoint interval; s >= L means no checkpoints */
     int64_t x_batch_stride;   /* elements between batches of x, y, dy, dx      (0 = L*H*P) */
