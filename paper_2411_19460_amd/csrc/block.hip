@@ -392,11 +392,14 @@ int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_blo
     }
     BLK_HIP(launch_linear_few_rows(in, st));
     if (ssm_in != ssm_out) BLK_HIP(ssm_in ? launch_copy_f32(ssm_out, ssm_in, d.HPN, st) : launch_fill_zero(ssm_out, d.HPN, st));
-    // the gate rides on the recurrence kernel, the normalisation on the output product: one group's rows as they are, and
-    // on the matrix cores, where a token per sequence is generated, with the operand packed by the recurrence kernel
+    // the gate rides on the recurrence kernel, the normalisation on the output product: with a token per sequence on the
+    // matrix cores the operand is packed by the recurrence kernel; otherwise few rows of one group are read as they are.
+    // Above four such rows a norm kernel of its own is faster, as the matrix-core product then squares every row again in
+    // every workgroup (eight 2.7B blocks, 8 / 16 tokens of a sequence: riding 491 / 677 us, apart 484 / 666); up to four the
+    // operand keeps the 16 bits it would lose on the way through memory.
     const bool valu = rows <= FEW_ROWS_VALU;
     const bool pack = stepped && !valu && (d.G == 1 || (d.G <= 8 && d.d_inner / d.G % 256 == 0));
-    mid.gate = pack || d.G == 1;
+    mid.gate = pack || (d.G == 1 && rows <= 4);
     if (pack) {
         mid.pack = ws + w.gp;
         mid.pack_w = p->norm_w;
