@@ -294,10 +294,9 @@ static int lane_cap() {
 }
 
 // What a launch works on, from the sizes alone.  Work is counted in units of one chunk of one head.
-//  - Chunk length: over long sequences the matrix-core kernels are fastest at 256 tokens (65536 tokens of 80 heads:
-//    3.2 ms, 4.1 ms at 128: half the chunk states to move), so shorter chunks are merged where a sequence is cut
-//    into long segments of whole 256-token chunks.  Calls of one segment (the cells of a grid among them, whose
-//    results must not depend on where the grid cuts) keep the caller's length.
+//  - Chunk length: the caller's.  256 tokens are fastest over long sequences (65536 tokens of 80 heads: 3.2 ms, 4.1 ms at
+//    128, with twice the chunk states to move), but shorter chunks keep the sums of dt A, and with them the rounding of
+//    every decay, smaller, and the results must depend neither on where the checkpoints fall nor on the entry point.
 //  - Segments per span: a launch of fewer than SPAN_UNITS units leaves compute units idle and costs the host as much as
 //    a full one (8192 tokens of 24 heads in four segments: 43 launches, bound by enqueuing them), so consecutive
 //    segments share their launches until that is reached; the scans put the checkpoints down on the way.
@@ -305,9 +304,6 @@ static int lane_cap() {
 //  - A sequence of few units altogether is one span: nothing to order, no events.
 void plan_dims(Dims* d, bool mfma, bool one_stream) {
     if (d->L == 0) return;
-    if (mfma && !one_stream && d->Q < 256 && d->nseg > 1 && d->s >= 1024 && d->s % 256 == 0) d->Q = 256;
-    d->nc_seg = (int)((d->s + d->Q - 1) / d->Q);
-    d->nct = (d->L + d->Q - 1) / d->Q;
     constexpr int64_t SPAN_UNITS = 640, ONE_SPAN_UNITS = 3840;
     const int64_t unit = d->Bt * d->H * ((d->Q + 63) / 64);  // quarter units: 64 tokens of a head
     const int64_t seg_units = d->nc_seg * unit / 4, all_units = d->nct * unit / 4;

@@ -188,7 +188,7 @@ struct WsLayout {
 };
 
 int check_shape(const ssd_shape_t* sh, Dims* d);
-// Chooses chunk length, segments per launch and launches in flight (fills Q, nc and the launch plan).
+// Chooses segments per launch and launches in flight (fills nc and the launch plan).
 void plan_dims(Dims* d, bool mfma, bool one_stream);
 // mfma: the layout for the matrix-core kernels, which keep the chunk states and their adjoints in
 // bf16 only (the fp32 arrays of the shape-generic kernels are left out).

@@ -39,7 +39,6 @@ int check_stack(const ssd_shape_t* shape, int32_t nlayers, int32_t layer_interva
     sd->cell.dts_b = sd->full.dts_b;
     sd->cell.bcs_b = sd->full.bcs_b;
     sd->mfma = use_mfma(*shape, 0);
-    plan_dims(&sd->cell, sd->mfma, true);  // one segment: fixes the chunk length
     sd->nl = nlayers;
     sd->l = layer_interval < nlayers ? layer_interval : nlayers;
     sd->nlg = (nlayers + sd->l - 1) / sd->l;

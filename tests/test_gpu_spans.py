@@ -1,5 +1,5 @@
-"""Launches that cover several checkpoint segments, ragged last chunks read and written in place, and chunks merged to
-256 tokens: every tensor against the oracle at the sizes where these can go wrong, with canaries behind the outputs."""
+"""Launches that cover several checkpoint segments and ragged last chunks read and written in place:
+every tensor against the oracle at the sizes where these can go wrong, with canaries behind the outputs."""
 import pytest
 import torch
 
@@ -24,7 +24,7 @@ def _guarded(like, pad=4096):
     ("bf16", 1, 257, 2, 64, 1, 128, 256, 256),          # a chunk of one row, in a segment of its own
     ("bf16", 1, 19 * 256 + 33, 4, 64, 1, 128, 256, 256),   # three spans of up to eight segments, one lane
     ("bf16", 1, 9 * 1024 + 5, 40, 64, 1, 128, 256, 1024),  # three spans of four segments on two lanes
-    ("bf16", 2, 3077, 4, 64, 2, 128, 128, 1024),        # chunks of 128 merged, one span of four segments
+    ("bf16", 2, 3077, 4, 64, 2, 128, 128, 1024),        # chunks of 128, one span of four segments
     ("bf16", 1, 130, 3, 64, 1, 128, 64, 128),           # chunk 64
     ("f32", 1, 11 * 64 + 7, 3, 16, 1, 24, 64, 64),      # shape-generic kernels, two spans
 ])
