@@ -265,15 +265,20 @@ __device__ __forceinline__ int64_t packed_at(int row, int k) { return ((int64_t)
 
 constexpr int PIECE = 256, WPITCH = PIECE * 2 + 16;  // k per piece; bytes per LDS row of a piece of w
 constexpr int MFMA_WAVES = 8, MAX_GROUPS = 8;
-// Up to eight rows leave half of a tile's rows free: row r + 8 then carries what rounding the operand x in_w to bf16 left of
-// row r, and the two finished sums are added.  The operand is thus good to 16 bits at no cost (three and four rows ran on
-// fp32 operands on the vector ALUs before the matrix cores took them, at twice the time).
-__device__ __forceinline__ bool split_rows(int rows) { return rows <= 8; }
-__device__ __forceinline__ __bf16 low_part(float v, __bf16 hi) { return (__bf16)(v - (float)hi); }
-__device__ __forceinline__ void pack_operand(__bf16* pack, int row, int k, float v, bool split) {
+// Up to eight rows leave rows of a tile free: they carry what rounding the operand x in_w to bf16 left of the live rows, and
+// the finished sums of a row's parts are added.  Up to four rows take three parts (rows r, r + 4, r + 8: all 24 bits, what the
+// vector ALUs compute one and two rows with), up to eight two (r, r + 8: 16 bits); more rows one.  The extra parts cost
+// nothing (three and four rows on fp32 operands on the vector ALUs took twice the time).
+__host__ __device__ __forceinline__ int row_parts(int rows) { return rows <= 4 ? 3 : rows <= 8 ? 2 : 1; }
+__host__ __device__ constexpr int part_step(int parts) { return parts == 3 ? 4 : parts == 2 ? 8 : 16; }  // rows between a row's parts
+__device__ __forceinline__ void pack_operand(__bf16* pack, int row, int k, float v, int parts) {
     const __bf16 hi = (__bf16)v;
     pack[packed_at(row, k)] = hi;
-    if (split) pack[packed_at(row + 8, k)] = low_part(v, hi);
+    if (parts == 1) return;
+    v -= (float)hi;
+    const __bf16 mid = (__bf16)v;
+    pack[packed_at(row + part_step(parts), k)] = mid;
+    if (parts == 3) pack[packed_at(row + 8, k)] = (__bf16)(v - (float)mid);
 }
 inline size_t few_mfma_lds(int ks) { return (size_t)ks * 16 * WPITCH + (size_t)ks * 1024 + 16 * 17 * 4; }
 static_assert(MAX_GROUPS * 16 <= 16 * 17, "");
@@ -281,8 +286,8 @@ static_assert(MAX_GROUPS * 16 <= 16 * 17, "");
 // SRC 0: rows of x.  SRC 1: RMS normalisation over all of K times in_w, its squares summed on the way (the operand is
 // x in_w, 1 / rms scales the finished sums).  SRC 2: packed rows, already times in_w, with `ssq` the partial
 // sums of squares of their producer (nparts per group of K / groups, row r of part i at ssq[16 i + r]).  SRC 3: packed rows,
-// no normalisation.
-template <int SRC, bool STEP>
+// no normalisation.  PARTS: row_parts(rows) (SRC 0: 1, rows of x are bf16 values as they are).
+template <int SRC, bool STEP, int PARTS>
 __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams fp, FewOperands fo) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int KS = fo.ks, nthr = 64 * KS, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -293,8 +298,8 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
     const int col = lane & 15, kq = lane >> 4;   // operand lanes: row of x / column of w, quarter of a 32-wide k step
     const int r2 = lane >> 5, l32 = lane & 31;   // fetching lanes: two columns of w at a time, 32 vectors of a piece each
     const int pieces = (fp.K + PIECE - 1) / PIECE;
-    const bool split = SRC != 0 && split_rows(fp.rows);
-    const int xrow = SRC == 1 && split ? col & 7 : col;
+    constexpr int pstep = part_step(PARTS);
+    const int xrow = SRC == 1 ? col & (pstep - 1) : col;
     const __bf16* xr = fp.x + (SRC >= 2 ? (int64_t)0 : (int64_t)(xrow < fp.rows ? xrow : 0) * fp.ldx);
     constexpr bool norm = SRC == 2;
     constexpr int PU = 10;  // partial sums of squares asked for ahead of everything else (per thread)
@@ -375,9 +380,16 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
                 if (SRC == 1) {
                     const float x = in ? (float)a[s][e] : 0.f;
                     ss = fmaf(x, x, ss);
-                    const float xw = x * iw[s][e >> 2][e & 3];
-                    const __bf16 hi = (__bf16)xw;
-                    av[e] = split && col >= 8 ? low_part(xw, hi) : hi;
+                    float xw = x * iw[s][e >> 2][e & 3];
+                    av[e] = (__bf16)xw;
+                    if (PARTS > 1) {
+                        xw -= (float)av[e];
+                        if (col >= pstep) av[e] = (__bf16)xw;
+                    }
+                    if (PARTS > 2) {
+                        xw -= (float)av[e];
+                        if (col >= 2 * pstep) av[e] = (__bf16)xw;
+                    }
                 } else {
                     av[e] = in ? a[s][e] : (__bf16)0.f;
                 }
@@ -386,7 +398,7 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
             t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, *(const bf16x8*)(wt + col * WPITCH + 64 * s + 16 * kq), t, 0, 0, 0);
         }
         if (norm && !norm_late) {
-            const float4 q = *(const float4*)(rs + (int)((int64_t)pc * PIECE * fo.groups / fp.K) * 16 + 4 * (split ? kq & 1 : kq));
+            const float4 q = *(const float4*)(rs + (int)((int64_t)pc * PIECE * fo.groups / fp.K) * 16 + 4 * (kq & (pstep / 4 - 1)));
             acc[0] += t[0] * q.x;
             acc[1] += t[1] * q.y;
             acc[2] += t[2] * q.z;
@@ -408,8 +420,11 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
     for (int t = tid; t < 256; t += nthr) {
         float o = 0.f;
         for (int q = 0; q < KS; ++q) o += part[q * 256 + t];
-        if (split && t < 128)  // row r + 8
-            for (int q = 0; q < KS; ++q) o += part[q * 256 + t + 128];
+        if (PARTS > 1 && t < 128) {  // row r + pstep
+            for (int q = 0; q < KS; ++q) o += part[q * 256 + t + 16 * pstep];
+            if (PARTS > 2 && t < 64)  // row r + 8
+                for (int q = 0; q < KS; ++q) o += part[q * 256 + t + 128];
+        }
         const int l = t >> 2, r = 4 * (l >> 4) + (t & 3), n = n0 + (l & 15);  // a wave of t: four rows, all 16 columns
         if (SRC == 1) {
             float m = 0.f;
@@ -427,7 +442,7 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
         if (live) fp.out[r * fp.ldo + n] = STEP ? step_finish(fo, t == tid ? taps : step_taps(fo, r, n), r, n, ob) : ob;
         if (fo.pack_out) {  // the next product's operand, and the squares its normalisation needs
             const float x = live ? (float)ob : 0.f;
-            if (live) pack_operand(fo.pack_out, r, n, fo.pack_w ? x * fo.pack_w[n] : x, split_rows(fp.rows));
+            if (live) pack_operand(fo.pack_out, r, n, fo.pack_w ? x * fo.pack_w[n] : x, SRC ? PARTS : row_parts(fp.rows));
             float q = x * x;
             for (int off = 4; off < 64; off <<= 1) q += __shfl_xor(q, off, 64);
             if ((l & 15) == 0) fo.pack_ssq[16 * blk + r] = q;
@@ -436,10 +451,18 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
     move_pieces(fo, nthr);
 }
 
+template <int SRC, int PARTS>
+void launch_few_mfma_parts(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
+    if (fo.cs) hipLaunchKernelGGL((k_linear_few_mfma<SRC, true, PARTS>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
+    else hipLaunchKernelGGL((k_linear_few_mfma<SRC, false, PARTS>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
+}
+
 template <int SRC>
 void launch_few_mfma_src(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
-    if (fo.cs) hipLaunchKernelGGL((k_linear_few_mfma<SRC, true>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
-    else hipLaunchKernelGGL((k_linear_few_mfma<SRC, false>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
+    const int parts = row_parts(fp.rows);
+    if (parts == 3) launch_few_mfma_parts<SRC, 3>(fp, fo, wgs, lds, st);
+    else if (parts == 2) launch_few_mfma_parts<SRC, 2>(fp, fo, wgs, lds, st);
+    else launch_few_mfma_parts<SRC, 1>(fp, fo, wgs, lds, st);
 }
 
 hipError_t launch_few_mfma(const FewParams& fp, FewOperands fo, int src, hipStream_t st) {
@@ -447,7 +470,7 @@ hipError_t launch_few_mfma(const FewParams& fp, FewOperands fo, int src, hipStre
     const size_t lds = few_mfma_lds(ks);
     fo.ks = ks;
     if (src == 2 && !fo.ssq) src = 3;
-    if (src == 0) launch_few_mfma_src<0>(fp, fo, wgs, lds, st);
+    if (src == 0) launch_few_mfma_parts<0, 1>(fp, fo, wgs, lds, st);
     else if (src == 1) launch_few_mfma_src<1>(fp, fo, wgs, lds, st);
     else if (src == 2) launch_few_mfma_src<2>(fp, fo, wgs, lds, st);
     else launch_few_mfma_src<3>(fp, fo, wgs, lds, st);
@@ -650,7 +673,7 @@ __global__ __launch_bounds__(256) void k_decode_step(MidParams mp) {
         if (mine) mp.y[(int64_t)b * mp.d_inner + c_mine] = (__bf16)y;
         return;
     }
-    if (mine) pack_operand(mp.pack, b, c_mine, y * pw, split_rows(gridDim.y));
+    if (mine) pack_operand(mp.pack, b, c_mine, y * pw, row_parts(gridDim.y));
     float q = mine ? y * y : 0.f;
     for (int o = 16; o >= 32 / U; o >>= 1) q += __shfl_xor(q, o, 64);
     if (l32 == 0) sq[hw] = q;
