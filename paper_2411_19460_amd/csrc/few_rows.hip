@@ -271,11 +271,14 @@ constexpr int MFMA_WAVES = 8, MAX_GROUPS = 8;
 // nothing (three and four rows on fp32 operands on the vector ALUs took twice the time).
 __host__ __device__ __forceinline__ int row_parts(int rows) { return rows <= 4 ? 3 : rows <= 8 ? 2 : 1; }
 __host__ __device__ constexpr int part_step(int parts) { return parts == 3 ? 4 : parts == 2 ? 8 : 16; }  // rows between a row's parts
+// What rounding v to b left of it: nothing of an infinity, which the first part carries alone (an operand that goes through a
+// norm is NaN then in any case).
+__device__ __forceinline__ float rest_of(float v, __bf16 b) { return __builtin_isinf((float)b) ? 0.f : v - (float)b; }
 __device__ __forceinline__ void pack_operand(__bf16* pack, int row, int k, float v, int parts) {
     const __bf16 hi = (__bf16)v;
     pack[packed_at(row, k)] = hi;
     if (parts == 1) return;
-    v -= (float)hi;
+    v = rest_of(v, hi);
     const __bf16 mid = (__bf16)v;
     pack[packed_at(row + part_step(parts), k)] = mid;
     if (parts == 3) pack[packed_at(row + 8, k)] = (__bf16)(v - (float)mid);

@@ -67,6 +67,30 @@ def test_up_to_four_sequences_multiply_operands_of_32_bits(nseq, d_model, heads,
         assert off < 1e-3
 
 
+@pytest.mark.parametrize("nseq", [2, 3, 6, 9])
+def test_infinities_pass_through_the_packed_operand(nseq):
+    """No norm between the layers: where the first layer's output overflows to an infinity, the second layer's product of it is
+    an infinity of the weight's sign, not NaN, however many parts the operand is carried in."""
+    H, P, N, dm, g = 8, 64, 128, 512, torch.Generator(device="cuda")
+    g.manual_seed(nseq)
+    normal = lambda *shape, dtype=torch.float32: torch.randn(shape, generator=g, device="cuda", dtype=dtype)  # noqa: E731
+    di, conv = H * P, H * P + 2 * N
+    layers = [{"W_in": normal(2 * di + 2 * N + H, dm, dtype=torch.bfloat16).mul_(dm ** -0.5), "conv_w": normal(conv, 4) * 0.5,
+               "conv_b": normal(conv) * 0.2, "dt_bias": normal(H) - 4, "A": -torch.rand(H, generator=g, device="cuda") * 15 - 1, "D": normal(H),
+               "norm_w": 1 + 0.3 * normal(di), "W_out": normal(dm, di, dtype=torch.bfloat16).mul_(di ** -0.5)} for _ in range(2)]
+    layers[0]["W_out"][77] = 0
+    layers[0]["W_out"][77, 5], layers[0]["norm_w"][5] = 1e37, 3e3
+    x0 = normal(nseq, dm, dtype=torch.bfloat16)
+    ssm, cs = normal(nseq, 2, H, P, N) * 0.3, normal(nseq, 2, 3, conv, dtype=torch.bfloat16)
+    one = pk.magc_blockstack_decode(x0, layers[:1], H, P, 1, N, 64, 64, ssm[:, :1].clone(), cs[:, :1].clone())["out"]
+    pk.magc_blockstack_decode(x0, layers, H, P, 1, N, 64, 64, ssm, cs)
+    torch.cuda.synchronize()
+    hit = torch.isinf(one[:, 77])
+    assert hit.any() and torch.isfinite(one).sum() == one.numel() - hit.sum()
+    want = torch.sign(one[:, 77, None].float() * layers[1]["W_in"][di:di + conv, 77].float()) * float("inf")
+    assert torch.equal(cs[hit, 1, 2].float(), want[hit])
+
+
 def test_parameters_are_checked_on_every_step():
     """A stack that one step accepted is refused once one of its tensors, at the same address, has another shape."""
     from paper_2411_19460_amd import binding
