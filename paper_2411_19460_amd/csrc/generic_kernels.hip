@@ -57,6 +57,9 @@ struct IO<bf16_t> {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// exp of a difference of sums of dt A: at most 0 but for rounding.  A NaN stays one (fminf would take the number).
+__device__ __forceinline__ float decay(float v) { return expf(v > 0.f ? 0.f : v); }
+
 constexpr int NTHREADS = 256;
 constexpr int TM = 64;   // tile edge
 constexpr int TK = 32;   // contraction step
@@ -342,7 +345,7 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_scores_states(SegParams sp, Vec
             const int i = tid * E + e;
             if (e < E && i < Q) {
                 const float cum = before + a[e];
-                wt[i] = role == 0 ? expf(fminf(total - cum, 0.f)) * d[e] : expf(cum);
+                wt[i] = role == 0 ? decay(total - cum) * d[e] : expf(cum);
                 if (keep) {
                     sp.cum[o + i] = i == Q - 1 ? total : cum;
                     sp.dtf[o + i] = d[e];
@@ -497,7 +500,7 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp, Vec vec
             for (int i = threadIdx.x; i < kend; i += NTHREADS) {
                 const float c_ = sp.cum[cbase + i], d_ = sp.dtf[cbase + i];
                 cum[i] = c_;
-                dtf[i] = i < i0 ? expf(fminf(ref - c_, 0.f)) * d_ : d_;
+                dtf[i] = i < i0 ? decay(ref - c_) * d_ : d_;
             }
             __syncthreads();
         });
@@ -505,7 +508,7 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp, Vec vec
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int i = i0 + tile_row(r);
-            acc[r] *= expf(fminf(cum[i < V ? i : i0] - ref, 0.f));
+            acc[r] *= decay(cum[i < V ? i : i0] - ref);
         }
     tile_gemm<true, false>(
         acc, i0, kend, la,
@@ -584,14 +587,14 @@ __device__ __forceinline__ void walk_u(const SegParams& sp, const Vec& vec, Walk
         lb, NoWeight{}, L.t, buf, [&] {
             for (int i = threadIdx.x; i < V; i += NTHREADS) {
                 const float c_ = sp.cum[cbase + i];
-                cum[i] = i < j1 ? c_ : expf(fminf(c_ - ref, 0.f));
+                cum[i] = i < j1 ? c_ : decay(c_ - ref);
                 dtf[i] = sp.dtf[cbase + i];
             }
             __syncthreads();
         });
     if (j1 < V)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] *= expf(fminf(ref - cum[j0 + tile_row(r)], 0.f));
+        for (int r = 0; r < 16; ++r) acc[r] *= decay(ref - cum[j0 + tile_row(r)]);
     tile_gemm<false, false>(
         acc, j0, j1, la,
         [&](float (&v)[4], int r, int k) {
@@ -677,7 +680,7 @@ __device__ __forceinline__ void walk_dg(const SegParams& sp, const Vec& vec, Wal
         tile_store<true>(ra, L.t.a[buf], 0, NoWeight{});
         tile_store<true>(rb, L.t.b[buf], 0, NoWeight{});
         // off the diagonal the decay is a row factor times a column factor, split at the token in front of the rows
-        if (ks == 0 && i0 > j0 && tid < 2 * TM) rc = expf(fminf(tid < TM ? rc - rf : rf - rc, 0.f));
+        if (ks == 0 && i0 > j0 && tid < 2 * TM) rc = decay(tid < TM ? rc - rf : rf - rc);
         if (ks == 0 && tid < 3 * TM) (tid < TM ? L.hd.row[hb] : (tid < 2 * TM ? L.hd.col[hb] : L.hd.dcol[hb]))[tid & (TM - 1)] = rc;
         __syncthreads();
         if (s + 1 < hps * KS) load(s + 1);
@@ -688,7 +691,7 @@ __device__ __forceinline__ void walk_dg(const SegParams& sp, const Vec& vec, Wal
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int row = tile_row(r), i = i0 + row;
-                const float f = i0 > j0 ? L.hd.row[hb][row] * fj : expf(fminf(L.hd.row[hb][row] - cj, 0.f)) * dj;
+                const float f = i0 > j0 ? L.hd.row[hb][row] * fj : decay(L.hd.row[hb][row] - cj) * dj;
                 t[r] = (i < V && j <= i) ? t[r] * f : 0.f;
                 tot[r] += t[r];
                 t[r] *= gv[r];
@@ -766,7 +769,7 @@ __device__ __forceinline__ void walk_part(const SegParams& sp, const Vec& vec, W
     load(0);
     for (int s = 0; s < hps * KS; ++s) {
         const int hh = s / KS, ks = s % KS, buf = s & 1;
-        const float wq[2] = {role ? expf(fminf(rT - rw[0], 0.f)) * rd[0] : expf(rw[0]), role ? expf(fminf(rT - rw[1], 0.f)) * rd[1] : expf(rw[1])};
+        const float wq[2] = {role ? decay(rT - rw[0]) * rd[0] : expf(rw[0]), role ? decay(rT - rw[1]) * rd[1] : expf(rw[1])};
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
