@@ -106,9 +106,13 @@ enum {
 
 /* Bytes of scratch the call needs for this shape (device memory, 256-byte aligned, contents
  * undefined before and after).  It scales with `segment`, not with `seqlen`: this is the
- * per-segment recomputation store (the M_state term of App. C) -- one per segment in flight, up
- * to four when the sequence has that many segments -- plus, for the backward pass, eight
- * bytes per (chunk, head) of the whole sequence for the partial sums of dA and dD.
+ * per-segment recomputation store (the M_state term of App. C) -- one per segment in flight: up to
+ * four when the sequence has that many segments, up to eight when a segment is too short to fill the
+ * GPU (batch * nheads * segment below 163840 tokens of a head: consecutive segments then share their
+ * launches; the shape-generic kernels keep one segment in flight otherwise) -- plus, for the backward
+ * pass, eight bytes per (chunk, head) of the whole sequence for the partial sums of dA and dD.
+ * It never shrinks as seqlen grows with everything else the same: scratch sized for the longest
+ * sequence serves every shorter one.
  * Returns 0 for an invalid shape.  The figure is for flags = 0; a call that passes
  * SSD_FLAG_GENERIC_KERNELS needs ssd_workspace_bytes_flags (the shape-generic kernels keep their
  * chunk states in fp32 and lay the scratch out differently). */

@@ -58,6 +58,40 @@ int check_shape(const ssd_shape_t* sh, Dims* d) {
     return SSD_OK;
 }
 
+namespace {
+// Into how many slices the heads of a group are cut for the partial sums of a span of nc chunks: enough workgroups for the
+// machine, in the place a span of whole segments takes.  That place is what the workspace holds (slots), or less for a span
+// too short to fill it even with a slice per head: it never shrinks as a sequence gets longer.
+struct HeadSlices {
+    int hpg, most, target;
+    int64_t per;   // workgroups per chunk and slice
+    int64_t room;  // (chunk, slice) pairs of a span of whole segments
+    HeadSlices(const Dims& d, int most, int64_t per, int target) : hpg(d.hpg), most(most < d.hpg ? most : d.hpg), target(target), per(per), room(INT64_MAX) {
+        const int64_t full = (int64_t)d.F * d.nc_seg;
+        room = full * split(full);
+    }
+    int split(int64_t nc) const {
+        if (nc <= 0) return 1;
+        const int64_t fits = room / nc;
+        int ns = pick_split(hpg, nc * per, target);
+        ns = ns < most ? ns : most;
+        ns = ns < fits ? ns : (int)fits;
+        while (hpg % ns) --ns;
+        return ns;
+    }
+    int64_t slots(int64_t nc) const { return nc * most < room ? nc * most : room; }
+};
+// shape-generic kernels: 64 x 64 tiles, several workgroups per compute unit; the last pass adds the slices up in registers
+HeadSlices dg_slices(const Dims& d, bool mfma, int wg_target) {
+    const int64_t nt = (d.Q + 63) / 64, bg = d.Bt * d.G;
+    return mfma ? HeadSlices(d, d.hpg, bg, wg_target) : HeadSlices(d, GENERIC_SLICES, bg * (nt * (nt + 1) / 2), 256);
+}
+HeadSlices part_slices(const Dims& d, bool mfma, int wg_target) {
+    const int64_t nt = (d.Q + 63) / 64, nn = (d.N + 63) / 64, bg = d.Bt * d.G;
+    return mfma ? HeadSlices(d, d.hpg, bg * 2, wg_target) : HeadSlices(d, GENERIC_SLICES, bg * 2 * nt * nn, 256);
+}
+}  // namespace
+
 WsLayout ws_layout(const Dims& d, bool bwd, bool mfma, int wg_target, bool fp32cs) {
     WsLayout w;
     memset(&w, 0, sizeof(w));
@@ -81,24 +115,18 @@ WsLayout ws_layout(const Dims& d, bool bwd, bool mfma, int wg_target, bool fp32c
     if (mfma) w.ein = take(tok);
     if (mfma) w.eout = take(tok);
     if (mfma) w.states_bf = take((size_t)d.Bt * d.nc * d.H * PN * 2);
-    const int64_t groups = d.Bt * (int64_t)d.nc * d.G;
-    // generic kernels: 64 x 64 tiles, several workgroups per compute unit
-    const int64_t nt = (d.Q + 63) / 64, nn = (d.N + 63) / 64, np = (d.P + 63) / 64;
-    auto few = [&](int ns) {  // largest divisor not above ns or GENERIC_SLICES: the last pass adds the slices up in registers
-        ns = ns < GENERIC_SLICES ? ns : GENERIC_SLICES;
-        while (d.hpg % ns) --ns;
-        return ns;
-    };
-    w.dg_split = mfma ? pick_split(d.hpg, groups, wg_target) : few(pick_split(d.hpg, groups * (nt * (nt + 1) / 2), 256));
-    w.part_split = mfma ? pick_split(d.hpg, groups * 2, wg_target) : few(pick_split(d.hpg, groups * 2 * nt * nn, 256));
+    const int64_t nt = (d.Q + 63) / 64, nn = (d.N + 63) / 64, np = (d.P + 63) / 64;  // 64 x 64 tiles of the generic kernels
+    const HeadSlices dg = dg_slices(d, mfma, wg_target), part = part_slices(d, mfma, wg_target);
+    w.dg_split = dg.split(d.nc);
+    w.part_split = part.split(d.nc);
     if (bwd) {
         if (!mfma || fp32cs) w.dstates = take((size_t)d.Bt * d.nc * d.H * PN * 4);
         if (mfma) w.dstates_bf = take((size_t)d.Bt * d.nc * d.H * PN * 2);
         {   // one partial sum per head slice: fp32 (generic kernels) or bf16 (MFMA kernels)
-            const size_t per = (size_t)d.Q * d.Q * (mfma ? 2 : 4) * w.dg_split;
-            w.dG = take((size_t)d.Bt * d.nc * d.G * per);
+            const size_t per = (size_t)d.Q * d.Q * (mfma ? 2 : 4);
+            w.dG = take((size_t)d.Bt * dg.slots(d.nc) * d.G * per);
         }
-        w.dbc_part = take((size_t)d.Bt * d.nc * d.G * w.part_split * 2 * d.Q * d.N * 4);
+        w.dbc_part = take((size_t)d.Bt * part.slots(d.nc) * d.G * 2 * d.Q * d.N * 4);
         w.gterm = take(tok * (mfma ? 1 : 2 * nn));
         w.sterm = take(tok * (mfma ? 1 : 2 * nn));
         if (mfma) w.gintra = take(tok);
@@ -222,6 +250,7 @@ static void wire_states(SegParams& sp, const Dims& d, int64_t k, int64_t ns, con
 // streams (default priority) -- each lane with its own scratch; events order the scans.
 // This overlaps one span's launch gaps, tails and bandwidth-bound kernels with another's matrix work.
 constexpr int NPIPE = 4;  // spans in flight at most (the caller's stream + NPIPE - 1 internal ones)
+constexpr int INFLIGHT = 8;  // segments in flight at most
 struct Pipe {
     hipStream_t aux[NPIPE] = {};       // aux[0] is unused: lane 0 is the caller's stream
     hipEvent_t fork = nullptr, join[NPIPE] = {}, scan[NPIPE] = {};
@@ -265,11 +294,8 @@ static Pipe* pipe_for_current_device() {
 // a buffer is rewritten only after its reader has finished).
 static size_t carry_bytes(const Dims& d) { return d.nseg > 1 ? 2 * align_up((size_t)d.Bt * d.H * d.P * d.N * 4) : 0; }
 
-// Bytes of the arrays shared by all scratch blocks: the dA / dD partial sums of every chunk.  A ragged sequence gets
-// one more row of them (the query promises more space for a short tail than for the whole chunks it is rounded up to).
-static size_t shared_bytes(const Dims& d) {
-    return 2 * align_up((size_t)d.Bt * d.nct * d.H * 4) + (d.L % d.Q ? align_up((size_t)d.Bt * d.H * 4) : 0);
-}
+// Bytes of the arrays shared by all scratch blocks: the dA / dD partial sums of every chunk.
+static size_t shared_bytes(const Dims& d) { return 2 * align_up((size_t)d.Bt * d.nct * d.H * 4); }
 
 // SSD_MAGC_SERIAL=1 in the environment keeps every segment on the caller's stream (diagnostics: per-kernel
 // timings are only meaningful when kernels do not overlap).
@@ -300,14 +326,18 @@ static int lane_cap() {
 //  - Segments per span: a launch of fewer than SPAN_UNITS units leaves compute units idle and costs the host as much as
 //    a full one (8192 tokens of 24 heads in four segments: 43 launches, bound by enqueuing them), so consecutive
 //    segments share their launches until that is reached; the scans put the checkpoints down on the way.
-//  - Memory: at most four segments' scratch is alive at a time, eight when a segment is below a full launch.
+//  - Memory: at most four segments' scratch is alive at a time, eight (INFLIGHT) when a segment is below a full launch: eight
+//    of those hold less than four full ones do.  With four, 65536 tokens of 24 heads in segments of 1024 take 2410 us
+//    instead of 1627, 32768 of 80 heads 2107 instead of 1866, 4096 fp32 tokens of 24 heads in segments of 256 578 instead
+//    of 432.
 //  - A sequence of few units altogether is one span: nothing to order, no events.
+// Only the number of segments counts, not where the last one ends: the workspace query goes over these plans.
 void plan_dims(Dims* d, bool mfma, bool one_stream) {
     if (d->L == 0) return;
     constexpr int64_t SPAN_UNITS = 640, ONE_SPAN_UNITS = 3840;
     const int64_t unit = d->Bt * d->H * ((d->Q + 63) / 64);  // quarter units: 64 tokens of a head
-    const int64_t seg_units = d->nc_seg * unit / 4, all_units = d->nct * unit / 4;
-    const int64_t inflight = seg_units >= SPAN_UNITS ? 4 : 8;
+    const int64_t seg_units = d->nc_seg * unit / 4, all_units = d->nseg * seg_units;
+    const int64_t inflight = seg_units >= SPAN_UNITS ? 4 : INFLIGHT;
     d->F = d->nl = 1;
     if (!one_stream && d->nseg > 1) {
         if (d->nseg <= inflight && (all_units <= SPAN_UNITS || (mfma && all_units <= ONE_SPAN_UNITS))) {
@@ -355,15 +385,27 @@ unsigned long long* g_stamps = nullptr;
 extern "C" void ssd_debug_stamps(void* p) { ssdk::g_stamps = (unsigned long long*)p; }
 #endif
 
+static size_t workspace_need(Dims d, bool bwd, bool mfma, uint32_t flags) {
+    plan_dims(&d, mfma, false);
+    const size_t block = align_up(ws_layout(d, bwd, mfma, wg_target(d.nl), (flags & SSD_FLAG_FP32_CHUNK_STATES) != 0).total);
+    return d.nl * block + (bwd ? shared_bytes(d) : carry_bytes(d));
+}
+
+// What the call itself needs, or any shorter sequence if that is more: scratch sized once for the longest serves all.
 extern "C" size_t ssd_workspace_bytes_flags(const ssd_shape_t* shape, int32_t is_backward, uint32_t flags) {
     Dims d;
     if (check_shape(shape, &d) != SSD_OK) return 0;
-    // never 0 for a valid shape, so that 0 unambiguously means "invalid"
-    const bool mfma = use_mfma(*shape, flags);
-    plan_dims(&d, mfma, false);
-    const size_t block = align_up(ws_layout(d, is_backward != 0, mfma, wg_target(d.nl), (flags & SSD_FLAG_FP32_CHUNK_STATES) != 0).total);
-    const size_t t = d.nl * block + (is_backward ? shared_bytes(d) : carry_bytes(d));
-    return t ? t : 256;
+    const bool mfma = use_mfma(*shape, flags), bwd = is_backward != 0;
+    size_t t = workspace_need(d, bwd, mfma, flags);
+    for (int64_t k = 1; k < d.nseg && k <= INFLIGHT; ++k) {  // from INFLIGHT + 1 segments on the plan is the same
+        Dims e = d;
+        e.nseg = k;
+        e.L = k * d.s;
+        e.nct = k * d.nc_seg;
+        const size_t n = workspace_need(e, bwd, mfma, flags);
+        t = n > t ? n : t;
+    }
+    return t ? t : 256;  // never 0 for a valid shape, so that 0 unambiguously means "invalid"
 }
 
 extern "C" size_t ssd_workspace_bytes(const ssd_shape_t* shape, int32_t is_backward) {
@@ -379,19 +421,11 @@ static void span_tokens(SegParams& sp, const Dims& d, int64_t k, int64_t ns) {
     sp.reset_bs = d.L;
 }
 
-// Head slices of the per-slice partial sums for a span shorter than the workspace was laid out for: as many as its
-// place holds (a short span has fewer chunks to spread over the machine).
-static void fit_splits(SegParams& sp, const WsLayout& w, const Dims& d, bool mfma) {
-    if (!mfma) return;  // a few slices whatever the span
-    auto fit = [&](int split) {
-        const int64_t room = (int64_t)d.nc * split;
-        int best = split;
-        for (int ns = split; ns <= sp.hpg && (int64_t)sp.nc * ns <= room; ++ns)
-            if (sp.hpg % ns == 0) best = ns;
-        return best;
-    };
-    sp.dg_split = fit(w.dg_split);
-    sp.part_split = fit(w.part_split);
+// Head slices of the per-slice partial sums for a span that may be shorter than the largest one (fewer chunks to spread
+// over the machine).
+static void fit_splits(SegParams& sp, const Dims& d, bool mfma) {
+    sp.dg_split = dg_slices(d, mfma, wg_target(d.nl)).split(sp.nc);
+    sp.part_split = part_slices(d, mfma, wg_target(d.nl)).split(sp.nc);
 }
 
 // one_stream: everything stays on the caller's stream (no library stream or event is touched).
@@ -619,7 +653,7 @@ extern "C" int ssd_bwd(const ssd_shape_t* shape, const void* x, const void* dt, 
         const int64_t t0 = k * d.s;
         const int HP = d.H * d.P, GN = d.G * d.N;
         span_tokens(sp, d, k, ns);
-        fit_splits(sp, w, d, mfma);
+        fit_splits(sp, d, mfma);
         sp.x = off(x, t0 * HP, d.esz);
         sp.dy = off(dy, t0 * HP, d.esz);
         sp.dx = off(dx, t0 * HP, d.esz);

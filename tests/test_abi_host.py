@@ -44,11 +44,38 @@ def test_workspace_query_and_shape_validation():
     assert pk.ssd_workspace_bytes(long_, False) == pk.ssd_workspace_bytes(short, False)
     extra = pk.ssd_workspace_bytes(long_, True) - pk.ssd_workspace_bytes(short, True)
     assert 0 <= extra <= 2 * 4 * 8 * ((1 << 20) // 256) + 512
-    # a sequence need not be a whole number of segments or chunks: the short tail adds staging space
-    assert pk.ssd_workspace_bytes(shape(seqlen=2000), True) > pk.ssd_workspace_bytes(shape(seqlen=2048), True)
+    # a sequence need not be a whole number of segments or chunks: the short tail is read and written in place
+    assert 0 < pk.ssd_workspace_bytes(shape(seqlen=2000), True) <= pk.ssd_workspace_bytes(shape(seqlen=2048), True)
     for bad in (dict(dtype=7), dict(nheads=0), dict(segment=1000), dict(ngroups=3),
                 dict(chunk=2048), dict(headdim=512), dict(batch=0)):
         assert pk.ssd_workspace_bytes(shape(**bad), True) == 0, bad
+
+
+@pytest.mark.parametrize("flags", [0, 4, 16])     # 4: shape-generic kernels, 16: fp32 chunk states
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_scratch_for_the_longest_sequence_serves_every_shorter_one(dtype, flags):
+    """Scratch is sized once for the longest sequence of a loop: every shorter one asks for no more, and however many
+    segments there are, for no more than four times what one segment asks for, eight times for short segments, and the
+    shape-generic kernels for no more than one for long segments (plus what grows with the sequence)."""
+    L = binding.lib()
+    for heads, groups, chunk, per_seg, batch in ((32, 1, 256, 4, 1), (24, 1, 256, 4, 1), (64, 1, 256, 1, 1), (80, 1, 128, 8, 1), (80, 2, 256, 16, 1),
+                                                 (40, 1, 256, 8, 2), (6, 2, 64, 2, 3), (80, 1, 256, 64, 1)):
+        segment = chunk * per_seg
+        step = max(1, segment // 5)
+        for back in (0, 1):
+            need = lambda n: L.ssd_workspace_bytes_flags(ctypes.byref(shape(dtype=dtype, nheads=heads, ngroups=groups, batch=batch,  # noqa: E731
+                                                                            chunk=chunk, segment=segment, seqlen=n)), back, flags)
+            one = need(segment)
+            sizes = sorted(set(range(1, 7 * segment, step)) | {k * segment + e for k in range(1, 10) for e in (-1, 0, 1)})
+            last = 0
+            for n in sizes:
+                now = need(n)
+                assert now >= last, (heads, chunk, per_seg, back, n, now, last)
+                last = now
+            short = batch * heads * segment < 163840
+            stores = 8 if short else (4 if dtype == 1 and flags != 4 else 1)
+            grows = 2 * (-(-sizes[-1] // chunk) * batch * heads * 4 + 256) if back else 2 * (batch * heads * 64 * 128 * 4 + 256)
+            assert last <= stores * one + grows, (heads, chunk, per_seg, back, last / one)
 
 
 def call_fwd(sh, ptrs, ws=0x1000, ws_bytes=1 << 40, flags=0):
