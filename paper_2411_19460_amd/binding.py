@@ -7,6 +7,7 @@ library is missing, loading fails loudly.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 from typing import Optional
 
@@ -202,6 +203,8 @@ def _shape_ref(x, Bm, chunk: int, segment: Optional[int], seq_reset):
     if seq_reset is not None:   # holds a pointer: made for the call
         shape = make_shape(x, Bm, chunk, segment, seq_reset)
         return shape, ctypes.byref(shape)
+    # plain numbers: 256.0 equals 256 as a key but is refused, and a tensor's hash is its identity, not its value
+    chunk, segment = operator.index(chunk), segment if segment is None else operator.index(segment)
     key = (x.dtype, x.shape, Bm.shape, chunk, segment)
     hit = _shapes.get(key)
     if hit is None:

@@ -237,3 +237,16 @@ def test_planner_budget_too_small_and_regimes():
         pk.magc_plan(0, 10, 1, 1, 1, 0)
     with pytest.raises(pk.SSDError):
         pk.magc_plan(4, 10, -1, 1, 1, 0)
+
+
+def test_a_kept_shape_descriptor_is_found_by_value_only():
+    """What a first call refuses is refused with the descriptor of an equal number at hand, and a length held in a tensor is read
+    on every call."""
+    import torch
+    x, Bm, seg = torch.empty((1, 48, 2, 8)), torch.empty((1, 48, 1, 8)), torch.tensor(16)
+    assert binding._shape_ref(x, Bm, 8, 16, None)[0].segment == 16
+    for chunk, segment in ((8.0, 16), (8, 16.0), (8.0, None)):
+        with pytest.raises(TypeError):
+            binding._shape_ref(x, Bm, chunk, segment, None)
+    assert binding._shape_ref(x, Bm, 8, seg, None)[0].segment == 16
+    assert binding._shape_ref(x, Bm, 8, seg.add_(8), None)[0].segment == 24
