@@ -152,7 +152,7 @@ __device__ __forceinline__ void store_pre(const Pre<Q>& pr, DualLds<Q>& L, int t
 // go[4(K-1) + ks] reverse), and the same rows of C (forward) or B (reverse).
 template <int Q, bool REV>
 __device__ __forceinline__ void tile_load(bf16x8 (&go)[GO_MAX], bf16x8 (&gd)[4], bf16x8 (&rf)[RF_N], const bf16_t* Mat,
-                                          const bf16_t* rowop, int64_t bt, int last, int T, int lane) {
+                                          rsrc_t rowop, uint32_t bcbytes, int T, int lane) {
     constexpr int NB = Q / BLK;
     const int I = T >> 1, tok0 = 32 * T;
 #pragma unroll
@@ -173,7 +173,7 @@ __device__ __forceinline__ void tile_load(bf16x8 (&go)[GO_MAX], bf16x8 (&gd)[4],
         for (int e = 0; e < 8; ++e) gd[ks][e] = (REV ? kk0 + e >= tok : kk0 + e <= tok) ? v[e] : (__bf16)0.f;
     }
 #pragma unroll
-    for (int ks = 0; ks < RF_N; ++ks) rf[ks] = frag_rows_upto(rowop, bt, tok0, 16 * ks, last, lane);
+    for (int ks = 0; ks < RF_N; ++ks) rf[ks] = frag_tokens(rowop, bcbytes, tok0, 16 * ks, lane);
 }
 
 template <int Q, int EPI>
@@ -345,7 +345,7 @@ __device__ __forceinline__ void dual_body(const SegParams& sp, DualLds<Q>& L, in
                           ((int64_t)c * Q * sp.G + g) * N_;
     bf16x8 go[GO_MAX], gd[4], rf[RF_N];
     HeadCtx cx;
-    tile_load<Q, REV>(go, gd, rf, Mat, rowop, bt, chunk_rows(sp, c, Q) - 1, T, lane);
+    tile_load<Q, REV>(go, gd, rf, Mat, make_rows(rowop, chunk_rows(sp, c, Q), (uint32_t)bt * 2), (uint32_t)bt * 2, T, lane);
     Pre<Q> pr;
     load_pre<Q, REV>(pr, sp, b, c, h0, tid, 32 * T);
     for (int hh = 0; hh < hps; ++hh) {

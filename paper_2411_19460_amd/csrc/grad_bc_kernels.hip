@@ -474,8 +474,9 @@ __device__ __forceinline__ void part_body(const SegParams& sp, PartLds<Q>& LL, i
     if (has_dots) {
         const int64_t bt = (int64_t)sp.G * N_;
         const bf16_t* rowop = (role ? (const bf16_t*)sp.Bm : (const bf16_t*)sp.Cm) + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
+        const rsrc_t rows = make_rows(rowop, chunk_rows(sp, c, Q), (uint32_t)bt * 2);
 #pragma unroll
-        for (int ks = 0; ks < N_ / 16; ++ks) rf[ks] = frag_rows_upto(rowop, bt, 32 * w, 16 * ks, chunk_rows(sp, c, Q) - 1, lane);
+        for (int ks = 0; ks < N_ / 16; ++ks) rf[ks] = frag_tokens(rows, (uint32_t)bt * 2, 32 * w, 16 * ks, lane);
     }
     // Order of the heads.  When this pass runs beside the other two head-walking passes with half as many slices
     // (twice the heads per workgroup, at about twice their pace per head), it alternates between the two half
@@ -654,13 +655,14 @@ __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, in
     // so each step asks for what the next one needs before it works: the first rows of B / C before the tile sums,
     // the head sums before the contraction.
     const int p_lo = k_lo >> 1, p_hi = k_hi >> 1;  // pairs of tiles along the contraction
-    const int nv = chunk_rows(sp, c, Q), last = nv - 1;
+    const int nv = chunk_rows(sp, c, Q);
+    const rsrc_t rows = make_rows(rhs, nv, (uint32_t)bt * 2);
     constexpr int SV = 64 * 16 / NTH;              // 16-byte pieces of a 64-row slab per thread
     bf16x8 sv[SV];
 #pragma unroll
     for (int k = 0; k < SV; ++k) {
         const int v = tid + NTH * k, row = v >> 4, seg = v & 15;
-        sv[k] = *(const bf16x8*)(rhs + (int64_t)min(64 * p_lo + row, last) * bt + seg * 8);
+        sv[k] = rows_load(rows, (uint32_t)(64 * p_lo + row) * (uint32_t)bt * 2 + seg * 16);
     }
     // sum the slices of the needed dG tiles: items (tile, half of its rows), two items and eight slices of each in
     // flight per wave; one 16-byte piece per lane and item
@@ -733,7 +735,7 @@ __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, in
 #pragma unroll
             for (int k = 0; k < SV; ++k) {
                 const int v = tid + NTH * k, row = v >> 4, seg = v & 15;
-                sv[k] = *(const bf16x8*)(rhs + (int64_t)min(64 * (pr + 1) + row, last) * bt + seg * 8);
+                sv[k] = rows_load(rows, (uint32_t)(64 * (pr + 1) + row) * (uint32_t)bt * 2 + seg * 16);
             }
         }
         __syncthreads();  // the rows (and, the first time, the summed tiles) are in place

@@ -46,15 +46,9 @@ static __device__ __forceinline__ bf16x8 frag_tr(const char* tile, int pitch, in
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// The same with the row index capped: rows beyond the end of a ragged chunk read as copies of its last one.
-static __device__ __forceinline__ bf16x8 frag_rows_upto(const bf16_t* base, int64_t row_stride, int row0, int k0, int last, int lane) {
-    const int row = row0 + (lane & 31);
-    return *(const bf16x8*)(base + (int64_t)(row < last ? row : last) * row_stride + k0 + 8 * (lane >> 5));
-}
-
-// Token tiles of one chunk and head as buffer accesses: the descriptor (wave-uniform, scalar registers) spans the rows
+// Token rows of one chunk as buffer accesses: the descriptor (wave-uniform, scalar registers) spans the rows
 // of the chunk that exist, so rows beyond the end of a ragged chunk read as zeros and are not written, at no cost in
-// vector instructions.  Offsets are 32-bit: a chunk has at most 256 rows of H x 64 bf16 (< 4 GB for any H taken).
+// vector instructions.  Zeros for every operand: a copy of the last row, infinite, would be a NaN under the dt = 0 of a row that does not exist.  Offsets are 32-bit: a chunk has at most 256 rows of H x 64 bf16 (< 4 GB for any H taken).
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 static __device__ __forceinline__ rsrc_t make_rows(const void* base, int rows, uint32_t rowbytes) {
@@ -68,6 +62,11 @@ static __device__ __forceinline__ bf16x8 rows_load(rsrc_t r, uint32_t off) {
 template <int AUX = 0>
 static __device__ __forceinline__ void rows_store(rsrc_t r, uint32_t off, bf16x8 v) {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, AUX);
+}
+
+// Operand fragment whose row index is a token of the chunk (frag_rows on rows that may end inside the tile).
+static __device__ __forceinline__ bf16x8 frag_tokens(rsrc_t r, uint32_t rowbytes, int row0, int k0, int lane) {
+    return rows_load(r, (uint32_t)(row0 + (lane & 31)) * rowbytes + (uint32_t)(k0 + 8 * (lane >> 5)) * 2);
 }
 
 static __device__ __forceinline__ bf16x8 scale8(bf16x8 v, float s) {

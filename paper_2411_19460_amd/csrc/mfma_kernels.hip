@@ -75,12 +75,14 @@ __device__ __forceinline__ void cb_body(const SegParams& sp, int z, int pair) {
     const int64_t ts = (int64_t)sp.G * N_;
     const bf16_t* Cm = (const bf16_t*)sp.Cm + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
     const bf16_t* Bm = (const bf16_t*)sp.Bm + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
-    const int last = chunk_rows(sp, c, Q) - 1;
+    const int nv = chunk_rows(sp, c, Q);
+    const uint32_t rowbytes = (uint32_t)ts * 2;
+    const rsrc_t cr = make_rows(Cm, nv, rowbytes), br = make_rows(Bm, nv, rowbytes);
     f32x16 a1 = zero16(), a2 = zero16();
 #pragma unroll
     for (int ks = 0; ks < N_ / 16; ++ks) {
-        const bf16x8 fc = frag_rows_upto(Cm, ts, i0, 16 * ks, last, lane);
-        const bf16x8 fb = frag_rows_upto(Bm, ts, j0, 16 * ks, last, lane);
+        const bf16x8 fc = frag_tokens(cr, rowbytes, i0, 16 * ks, lane);
+        const bf16x8 fb = frag_tokens(br, rowbytes, j0, 16 * ks, lane);
         a1 = mfma(fc, fb, a1);  // a1[r] = G[i0 + acc_row(r)][j0 + lane%32]
         a2 = mfma(fb, fc, a2);  // a2[r] = G[i0 + lane%32][j0 + acc_row(r)]
     }
@@ -198,10 +200,10 @@ __global__ __launch_bounds__(OUTER_THR, 2) void mk_chunk_outer(SegParams sp, int
     outer_load<Q>(pr, sp, role, b, c, h0, tid);
     // prologue: B (role 0) or C (role 1) rows -> LDS -> this wave's fragments
     const bf16_t* rhs = (role == 0 ? (const bf16_t*)sp.Bm : (const bf16_t*)sp.Cm) + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
-    const int last = chunk_rows(sp, c, Q) - 1;
+    const rsrc_t rows = make_rows(rhs, chunk_rows(sp, c, Q), (uint32_t)bt * 2);
     for (int v = tid; v < Q * 16; v += OUTER_THR) {
         const int row = v >> 4, seg = v & 15;
-        *(bf16x8*)(L.bc + row * BPITCH + seg * 16) = *(const bf16x8*)(rhs + (int64_t)(row < last ? row : last) * bt + seg * 8);
+        *(bf16x8*)(L.bc + row * BPITCH + seg * 16) = rows_load(rows, (uint32_t)row * (uint32_t)bt * 2 + seg * 16);
     }
     __syncthreads();
     bf16x8 fb[KS];

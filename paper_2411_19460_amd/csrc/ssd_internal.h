@@ -150,8 +150,8 @@ extern unsigned long long* g_stamps;
     } while (0)
 #endif
 
-// Tokens of chunk c that exist (the last chunk of a sequence may be ragged): its further rows read as zeros or as
-// copies of the last one under dt = 0, i.e. they are identity steps of the recurrence, and are never stored.
+// Tokens of chunk c that exist (the last chunk of a sequence may be ragged): its further rows read as zeros
+// under dt = 0, i.e. they are identity steps of the recurrence, and are never stored.
 __host__ __device__ inline int chunk_rows(const SegParams& sp, int c, int Q) {
     const int left = sp.ntok - c * Q;
     return left < Q ? left : Q;
