@@ -454,18 +454,32 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
     move_pieces(fo, nthr);
 }
 
+template <int SRC, bool STEP, int PARTS>
+hipError_t launch_few_mfma_kernel(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
+    static bool raised[64];  // per device: long rows take more dynamic LDS than the default limit
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (!raised[dev]) {
+        const hipError_t e = hipFuncSetAttribute((const void*)k_linear_few_mfma<SRC, STEP, PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)few_mfma_lds(MFMA_WAVES));
+        if (e != hipSuccess) return e;
+        raised[dev] = true;
+    }
+    hipLaunchKernelGGL((k_linear_few_mfma<SRC, STEP, PARTS>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
+    return hipGetLastError();
+}
+
 template <int SRC, int PARTS>
-void launch_few_mfma_parts(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
-    if (fo.cs) hipLaunchKernelGGL((k_linear_few_mfma<SRC, true, PARTS>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
-    else hipLaunchKernelGGL((k_linear_few_mfma<SRC, false, PARTS>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
+hipError_t launch_few_mfma_parts(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
+    return fo.cs ? launch_few_mfma_kernel<SRC, true, PARTS>(fp, fo, wgs, lds, st) : launch_few_mfma_kernel<SRC, false, PARTS>(fp, fo, wgs, lds, st);
 }
 
 template <int SRC>
-void launch_few_mfma_src(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
+hipError_t launch_few_mfma_src(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
     const int parts = row_parts(fp.rows);
-    if (parts == 3) launch_few_mfma_parts<SRC, 3>(fp, fo, wgs, lds, st);
-    else if (parts == 2) launch_few_mfma_parts<SRC, 2>(fp, fo, wgs, lds, st);
-    else launch_few_mfma_parts<SRC, 1>(fp, fo, wgs, lds, st);
+    if (parts == 3) return launch_few_mfma_parts<SRC, 3>(fp, fo, wgs, lds, st);
+    if (parts == 2) return launch_few_mfma_parts<SRC, 2>(fp, fo, wgs, lds, st);
+    return launch_few_mfma_parts<SRC, 1>(fp, fo, wgs, lds, st);
 }
 
 hipError_t launch_few_mfma(const FewParams& fp, FewOperands fo, int src, hipStream_t st) {
@@ -473,11 +487,10 @@ hipError_t launch_few_mfma(const FewParams& fp, FewOperands fo, int src, hipStre
     const size_t lds = few_mfma_lds(ks);
     fo.ks = ks;
     if (src == 2 && !fo.ssq) src = 3;
-    if (src == 0) launch_few_mfma_parts<0, 1>(fp, fo, wgs, lds, st);
-    else if (src == 1) launch_few_mfma_src<1>(fp, fo, wgs, lds, st);
-    else if (src == 2) launch_few_mfma_src<2>(fp, fo, wgs, lds, st);
-    else launch_few_mfma_src<3>(fp, fo, wgs, lds, st);
-    return hipGetLastError();
+    if (src == 0) return launch_few_mfma_parts<0, 1>(fp, fo, wgs, lds, st);
+    if (src == 1) return launch_few_mfma_src<1>(fp, fo, wgs, lds, st);
+    if (src == 2) return launch_few_mfma_src<2>(fp, fo, wgs, lds, st);
+    return launch_few_mfma_src<3>(fp, fo, wgs, lds, st);
 }
 
 struct MidParams {
