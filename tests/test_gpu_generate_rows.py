@@ -1,11 +1,19 @@
 """One generation step for a few sequences at the sizes where its kernels change: two rows (vector ALUs) and three (matrix
 cores), widths that are no multiple of a 256-wide piece, two groups whose norms scale the pieces, state rows of more than
-128 columns, more rows per wave with more sequences.  Checked against the oracle run on each sequence alone."""
+128 columns, eight rows per half wave from 768 pairs of head and sequence on, rows of more than 2048 elements whose pieces
+a wave takes in turn, more partial sums of squares than are asked for ahead.  Checked against the oracle run on each sequence
+alone."""
+import numpy as np
 import pytest
 import torch
 
 import paper_2411_19460_amd as pk
+from oracle import block_ref, linear_ref
+from paper_2411_19460_amd import synth
+from parity_util import TOL, check, host
+from test_gpu_block import BF, F32, dev_bf16, draw, to_dev
 from test_gpu_block import test_stack_generation_for_several_sequences_at_once as check_generation
+from test_gpu_linear import dev as dev_linear, draw as draw_linear
 
 pytestmark = pytest.mark.gpu
 
@@ -19,6 +27,48 @@ pytestmark = pytest.mark.gpu
 ])
 def test_generation_rows(shape):
     check_generation(shape)
+
+
+@pytest.mark.parametrize("shape", [
+    # d_model, H, P, G, N, pre-norm, sequences
+    (2560, 80, 64, 1, 128, True, 1),     # vector ALUs, four columns a wave and k over four waves, convolution step included
+    (2560, 80, 64, 2, 128, True, 2),     # the same for two rows; two groups
+    (2560, 80, 64, 1, 128, True, 16),    # eight state rows per half wave; a wave's second piece of k (K = 2560 and 5120)
+    (2560, 80, 64, 2, 128, True, 16),    # second pieces scaled by their group's norm
+    (768, 24, 64, 1, 128, True, 3),      # 192 partial sums of squares: more than are asked for ahead (160)
+    (1024, 32, 64, 1, 128, False, 3),    # 256 of them, no norm in front
+    (128, 16, 24, 2, 128, True, 4),      # groups of 192 channels: the convolution step rides, the operand is not packed
+    (320, 16, 40, 2, 128, True, 12),     # groups of 320
+])
+def test_generation_step_from_given_states(shape):
+    """One token for each sequence on random states, two layers: output and both states against the oracle run on each sequence
+    alone.  Tolerance as for a stack of two layers."""
+    dm, H, P, G, N, pre, nseq = shape
+    NL, r = 2, np.random.default_rng(78)
+    conv_dim = block_ref.dims(None, H, P, G, N)[1]
+    layers_h = [draw(60 + j, 1, dm, H, P, G, N, pre)["p"] for j in range(NL)]
+    x = BF(r.standard_normal((nseq, dm)) * np.exp(r.uniform(-1.0, 1.0, (nseq, 1))))
+    ssm_h, conv_h = F32(r.standard_normal((nseq, NL, H, P, N)) * 0.3), BF(r.standard_normal((nseq, NL, 3, conv_dim)))
+    ssm, conv = torch.from_numpy(ssm_h.astype(np.float32)).cuda(), dev_bf16(conv_h)
+    out = pk.magc_blockstack_decode(dev_bf16(x), [to_dev(p) for p in layers_h], H, P, G, N, 128, 128, ssm, conv)["out"]
+    torch.cuda.synchronize()
+    tol = 2 * TOL["bf16"]
+    for i in range(nseq):
+        fo = block_ref.stack_fwd(x[i:i + 1], layers_h, H, P, G, N, 1e-5, store=synth.round_bf16, conv_states=conv_h[i], ssm_states=ssm_h[i])
+        check(f"sequence {i} out", host(out[i:i + 1]), fo["out"], tol)
+        for j in range(NL):
+            check(f"sequence {i} layer {j} ssm state", host(ssm[i, j]), fo["ssm_states"][j], tol)
+            check(f"sequence {i} layer {j} conv state", host(conv[i, j]), fo["conv_states"][j], tol)
+
+
+@pytest.mark.parametrize("rows", [3, 16])
+@pytest.mark.parametrize("K", [2048, 2056, 5120])
+def test_products_of_few_long_rows(rows, K):
+    """K at which each of the eight waves has its one piece of 256, one wave a second piece of eight, and all of them several."""
+    x, w, _ = draw_linear(4, rows, K, 136)
+    out = pk.ssd_linear_fwd(dev_linear(x), dev_linear(w))
+    torch.cuda.synchronize()
+    check("out", host(out), linear_ref.linear_fwd(x, w), TOL["bf16"])
 
 
 def _rounded_products(nseq, d_model, heads, groups):

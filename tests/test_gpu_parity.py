@@ -160,9 +160,9 @@ def test_autograd_wrapper_matches_the_direct_calls_and_the_oracle():
 @pytest.mark.parametrize("case", [
     # dtype, Bt, L,    H, P,  G, N,   Q,   segment, flags
     ("f32", 2, 200, 3, 16, 1, 16, 64, 128, 0),                                 # short last segment, short last chunk
-    ("bf16", 2, 1000, 4, 64, 2, 128, 256, 512, 0),                             # matrix-core path, two segments in flight
+    ("bf16", 2, 1000, 4, 64, 2, 128, 256, 512, 0),                             # matrix-core path, two segments in one span
     ("bf16", 1, 300, 2, 64, 1, 128, 256, None, 0),                             # one segment, shorter than two chunks
-    ("bf16", 1, 2148, 2, 64, 1, 128, 128, 512, 0),                             # five segments on four lanes, tail of 100
+    ("bf16", 1, 2148, 2, 64, 1, 128, 128, 512, 0),                             # five segments in one span, tail of 100
     ("bf16", 1, 700, 2, 64, 1, 128, 128, 256, pk.SSD_FLAG_GENERIC_KERNELS),
 ])
 def test_sequence_length_need_not_be_a_multiple_of_segment_or_chunk(case):
@@ -194,7 +194,7 @@ def test_sequence_length_need_not_be_a_multiple_of_segment_or_chunk(case):
     # dtype, Bt, L,   H, P,  G, N,   Q,   segment, flags
     ("f32", 2, 256, 3, 16, 1, 16, 64, 128, 0),
     ("bf16", 2, 1024, 4, 64, 2, 128, 256, 512, 0),
-    ("bf16", 1, 1100, 2, 64, 1, 128, 128, 256, 0),                             # five segments in flight, short tail
+    ("bf16", 1, 1100, 2, 64, 1, 128, 128, 256, 0),                             # five segments in one span, short tail
     ("bf16", 1, 768, 2, 64, 1, 128, 256, 256, pk.SSD_FLAG_GENERIC_KERNELS),
 ])
 def test_packed_sequences(case):
@@ -307,7 +307,7 @@ def test_forward_and_backward_can_be_captured_in_a_graph():
     synchronisation), on the caller's stream and on the library's own streams forked from it: a stream
     capture therefore records them all.  Replays, with eager work in between, must reproduce the eager
     results bit for bit."""
-    d = small_inputs(19, "bf16", 1, 2048, 4, 64, 1, 128)       # four segments of 512: several in flight
+    d = small_inputs(19, "bf16", 1, 2048, 4, 64, 1, 128)       # four segments of 512 in one span (several spans on several streams: test_gpu_spans.py)
     dv = dev_inputs(d, "bf16")
     Q, seg = 256, 512
     shape = pk.make_shape(dv["x"], dv["B"], Q, seg)
