@@ -37,12 +37,15 @@ def kernel_models(cfg, tokens_per_launch, generic=False):
       dG            2QP*H   | x, dy, cum, dt, G -> dG, row-minus-column sums of E       2X + 2R + 2g + R
       dBC           4NP*H   | x, dy, states, adjoints, cum, w, B, C -> dB/dC state terms (fp32), two dot rows
                                                                           2X + 2S + 2R + 2b + 2*G*N*4 + 2R
-      dBC_final     4QN*G   | dG, B, C, state terms -> dB, dC             g + 2b + 2*G*N*4 + 2b
+      final_ddt     4QN*G   | dG, B, C, state terms, scalar rows -> dB, dC, ddt   g + 4b + 2*G*N*4 + 6R + H*e
       bwd_trio = bwd_main + dG + dBC as one launch (chunk 256): flop add up; x and dY count once
+    The shape-generic kernels run the same steps in fewer launches, states and scores in fp32: chunk_state = scores and
+    chunk states (in the backward pass the local adjoints too: the mean of the two launches is given), bwd_main = dx, dG
+    and the state terms, dBC = dB, dC and ddt; their reverse scan walks the states forth and back.
       state scans, per (chunk, head) state of P*N elements (matrix-core path, bf16 in memory):
       forward reads the chunk state and writes the entering state (4 B/element), reverse reads the
       local adjoint and the entering state and writes the total adjoint (6 B/element).
-    A launch covers one segment: tokens_per_launch = batch * segment."""
+    tokens_per_launch: one or several segments (layer_bench counts the launches)."""
     H, P, N, G, Q = cfg.nheads, cfg.headdim, cfg.dstate, cfg.ngroups, cfg.chunk
     t = tokens_per_launch
     esz = 2 if cfg.dtype == "bf16" else 4
@@ -57,18 +60,16 @@ def kernel_models(cfg, tokens_per_launch, generic=False):
         "mfma_bwd_main": ((2 * Q * P + 2 * N * P) * H, 3 * X + S + g + b + 5 * R),
         "mfma_dG": (2 * Q * P * H, 2 * X + 3 * R + 2 * g),
         "mfma_dBC": (4 * N * P * H, 2 * X + 2 * S + 4 * R + 2 * b + 8 * G * N),
-        "mfma_dBC_final": (4 * Q * N * G, g + 4 * b + 8 * G * N),
+        "mfma_final_ddt": (4 * Q * N * G, g + 4 * b + 8 * G * N + 6 * R + H * esz),
         # bwd_main + dG + dBC in one launch (Q = 256): x and dY are read once for the three
         "mfma_bwd_trio": ((4 * Q * P + 6 * N * P) * H, 3 * X + 3 * S + 3 * g + 3 * b + 12 * R + 8 * G * N),
-        # shape-generic fp32 FMA kernels (same operands; their states are fp32)
-        "chunk_state": (2 * N * P * H, X + 2 * R + b + S4), "cb": (2 * Q * N * G, 2 * b + 2 * g),
-        "chunk_out": ((2 * Q * P + 2 * N * P) * H, 2 * X + S4 + g + b + 2 * R),
-        "dstate_local": (2 * N * P * H, X + R + b + S4),
-        "bwd_main": ((4 * Q * P + 4 * N * P) * H, 3 * X + 2 * S4 + 2 * g + 2 * b + 5 * R),
-        "dG": (2 * Q * P * H, 2 * X + 2 * R + g),
-        "dBC": (4 * N * P * H + 4 * Q * N * G, 2 * X + 2 * S4 + 2 * R + g + 4 * b),
-        "cumsum": (0, H * esz + 4 * 4 * H), "ddt_finalize": (0, 6 * 4 * H + H * esz),
-        "state_scan_fwd": (0, (4 if mfma else 8) * st), "state_scan_bwd": (0, (6 if mfma else 12) * st),
+        # shape-generic kernels
+        "chunk_state": (2 * Q * N * G + 3 * N * P * H, 1.5 * X + H * esz + 2 * R + 2 * b + 4 * Q * G + 1.5 * S4),
+        "chunk_out": ((2 * Q * P + 2 * N * P) * H, 2 * X + S4 + 4 * Q * G + b + 2 * R),
+        "bwd_main": ((4 * Q * P + 6 * N * P) * H, 3 * X + 2 * S4 + 8 * Q * G + 2 * b + 8 * R + 8 * G * N),
+        "dBC": (4 * Q * N * G, 4 * Q * G + 4 * b + 8 * G * N + 7 * R + H * esz),
+        "cumsum": (0, H * esz + 4 * 4 * H),
+        "state_scan_fwd": (0, (4 if mfma else 8) * st), "state_scan_bwd": (0, (6 if mfma else 20) * st),
     }
     return {k: (fl * t, by * t) for k, (fl, by) in m.items()}
 
@@ -533,11 +534,10 @@ def block_bench(args, cfg, pk, torch, dev):
 # tensors the method must read and write there once per token (bf16 storage: x-shaped tensors H*P*e, dt-shaped
 # H*e, B/C-shaped G*N*e): forward reads x, dt, B, C and writes y; the restore of a segment re-reads x, dt, B, C;
 # backward reads x, dt, B, C, dy and writes dx, ddt, dB, dC.
-KERNEL_GROUP = {"cumsum": "fwd", "mfma_cb": "fwd", "cb": "fwd", "mfma_chunk_state": "fwd", "chunk_state": "fwd",
-                "state_scan_fwd": "fwd", "mfma_chunk_out": "fwd", "chunk_out": "fwd",
-                "mfma_dstate_local": "restore", "dstate_local": "restore",
+KERNEL_GROUP = {"cumsum": "fwd", "mfma_cb": "fwd", "mfma_chunk_state": "fwd", "chunk_state": "fwd",
+                "state_scan_fwd": "fwd", "mfma_chunk_out": "fwd", "chunk_out": "fwd", "mfma_dstate_local": "restore",
                 "state_scan_bwd": "bwd", "mfma_bwd_trio": "bwd", "mfma_bwd_main": "bwd", "bwd_main": "bwd", "mfma_dG": "bwd",
-                "dG": "bwd", "mfma_dBC": "bwd", "dBC": "bwd", "mfma_dBC_final": "bwd", "ddt_finalize": "bwd"}
+                "mfma_dBC": "bwd", "dBC": "bwd", "mfma_final_ddt": "bwd"}
 
 
 def group_bytes(cfg):
@@ -628,7 +628,8 @@ def layer_bench(cfg, steps, warmup, flags, pk, synth, torch, dev, per_kernel, me
     prof_all = pk.ssd_prof_read()
     pk.ssd_prof_enable(False)
     pk.ssd_prof_serialize(False)
-    models = kernel_models(cfg, Bt * cfg.segment, bool(flags & pk.SSD_FLAG_GENERIC_KERNELS))
+    spans = prof_all["state_scan_bwd"][1] // nser    # launched once for the segments that share their launches
+    models = kernel_models(cfg, Bt * L / spans, bool(flags & pk.SSD_FLAG_GENERIC_KERNELS))
     kernels = {}
     for name, (ms, n) in prof_all.items():
         ent = {"ms_per_step": ms / nser, "launches_per_step": n // nser, "avg_us": ms * 1e3 / n}
@@ -648,7 +649,7 @@ def layer_bench(cfg, steps, warmup, flags, pk, synth, torch, dev, per_kernel, me
     torch.cuda.synchronize()
     pd = pk.ssd_prof_read()
     pk.ssd_prof_enable(False)
-    res.update({"kernels_serialized": kernels, "dominant": dom,
+    res.update({"kernels_serialized": kernels, "dominant": dom, "spans": spans,
                 "dominant_in_flight_us": pd[dom][0] * 1e3 / pd[dom][1] if dom in pd else None})
     return res
 
@@ -852,15 +853,19 @@ def main():
     tok_s, ms_per_step = main["tokens_per_s"], main["ms_per_step"]
     kernels, dom = main["kernels_serialized"], main["dominant"]
     group = KERNEL_GROUP.get(dom, "bwd")
-    gbytes = group_bytes(cfg)[group] * Bt * cfg.segment      # algorithmic bytes of the kernel's group per launch (one segment)
+    spans, nseg = main["spans"], -(-L // cfg.segment)
+    gbytes = group_bytes(cfg)[group] * Bt * L / spans        # algorithmic bytes of the kernel's group per launch
+    # at most eight short segments at a time, four of those that fill the GPU; the shape-generic kernels one launch at a time
+    generic = args.generic or not any(k.startswith("mfma_") for k in kernels)
+    in_flight = -(-nseg // spans) if generic or spans == 1 else min(nseg, 4 if Bt * H * cfg.segment >= 163840 else 8)
     dsec = kernels[dom]["avg_us"] * 1e-6
     roofline = {"kernel": dom, "bound": "hbm", "achieved": gbytes / dsec / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": gbytes / dsec / 1e9 / HBM_PEAK_GBS, "traffic": measured_traffic(dom, cfg.name),
+                "frac": gbytes / dsec / 1e9 / HBM_PEAK_GBS, "traffic": measured_traffic(dom, cfg.name) if not args.segment else None,
                 "algorithmic_bytes_per_launch": gbytes, "avg_launch_us": kernels[dom]["avg_us"],
                 "duration": "kernel alone on the GPU (every segment on one stream), HIP events around each launch, "
                             "untimed pass after the timed region",
                 "bytes": f"{group} group of the path per token ({group_bytes(cfg)[group]:.0f} B: inputs read once, outputs "
-                         f"written once) x {Bt * cfg.segment} tokens per launch",
+                         f"written once) x {Bt * L // spans} tokens per launch",
                 "in_flight_avg_launch_us": main["dominant_in_flight_us"],
                 "share_of_kernel_time": kernels[dom]["ms_per_step"] / sum(k["ms_per_step"] for k in kernels.values()),
                 "tflops": kernels[dom].get("tflops"), "frac_mfma": (kernels[dom].get("tflops") or 0.0) / MFMA_BF16_PEAK_TFLOPS}
@@ -876,8 +881,8 @@ def main():
         "config": {"workload": cfg.name, "batch": Bt, "seqlen": L, "nheads": H, "headdim": P, "dstate": N,
                    "ngroups": G, "chunk": cfg.chunk, "segment": cfg.segment,
                    "checkpoints": "bf16" if args.bf16_checkpoints else "f32",
-                   "kernels": "generic" if args.generic or not any(k.startswith("mfma_") for k in kernels) else "mfma",
-                   "segments_in_flight": min(4, L // cfg.segment) if not args.generic else 1},
+                   "kernels": "generic" if generic else "mfma", "segments_per_launch": -(-nseg // spans),
+                   "segments_in_flight": in_flight},
         "median_ms_per_step": main["median_ms_per_step"], "step_ms": main["step_ms"],
         "roofline": roofline, "roofline_path": roofline_path, "kernels_serialized": kernels, "peak_hbm": main["peak_hbm"],
     }
