@@ -92,7 +92,7 @@ typedef struct ssd_shape_t {
 enum {
     SSD_FLAG_RESIDUAL = 1,        /* fwd: y = x + SSD(x);  bwd: dx = dy + VJP(dy)  (the residual stack's layer) */
     SSD_FLAG_ACCUM_PARAM = 2,     /* bwd: dA, dD are added to instead of overwritten */
-    SSD_FLAG_GENERIC_KERNELS = 4, /* force the shape-generic fp32-FMA kernels even where the MFMA path applies */
+    SSD_FLAG_GENERIC_KERNELS = 4, /* force the shape-generic fp32 kernels even where the bf16 matrix-core path applies */
     SSD_FLAG_BF16_CHECKPOINTS = 8, /* boundary_states holds bf16 instead of fp32 elements: half the S-checkpoint
                                      term of App. C (Tab. 7 counts an fp32 state element as two); see ssd_fwd */
     SSD_FLAG_FP32_CHUNK_STATES = 16 /* matrix-core kernels only (ignored by the shape-generic ones, which always do):

@@ -325,12 +325,18 @@ static int lane_cap() {
 //    every decay, smaller, and the results must depend neither on where the checkpoints fall nor on the entry point.
 //  - Segments per span: a launch of fewer than SPAN_UNITS units leaves compute units idle and costs the host as much as
 //    a full one (8192 tokens of 24 heads in four segments: 43 launches, bound by enqueuing them), so consecutive
-//    segments share their launches until that is reached; the scans put the checkpoints down on the way.
+//    segments share their launches until that is reached; the scans put the checkpoints down on the way.  131072 tokens of
+//    24 heads: segments of 96 units 3.16 ms (4.48 with two segments a launch), of 192 units 2.67 (4.21 with one), of 384 units
+//    2.25 (2.69); 65536 of 64 heads, 512 units: 2.58 (2.99).  Segments of 640 units would gain as well (65536 of 80 heads: 3.12
+//    ms instead of 3.55) but four launches of two hold 379 MB instead of 262; from 1280 units on nothing changes (3.11).
 //  - Memory: at most four segments' scratch is alive at a time, eight (INFLIGHT) when a segment is below a full launch: eight
 //    of those hold less than four full ones do.  With four, 65536 tokens of 24 heads in segments of 1024 take 2410 us
 //    instead of 1627, 32768 of 80 heads 2107 instead of 1866, 4096 fp32 tokens of 24 heads in segments of 256 578 instead
 //    of 432.
-//  - A sequence of few units altogether is one span: nothing to order, no events.
+//  - A sequence of few units altogether (ONE_SPAN_UNITS) is one span: nothing to order, no events.  Matrix-core kernels, 80
+//    heads: 8192 tokens (2560 units) 424 us instead of 526 on lanes, 12288 (3840) 655 instead of 679; 32768 of 24 heads (3072)
+//    555 instead of 649.  Beyond it lanes still cost more where there are few segments (16384 of 80 heads, 5120 units: 856
+//    us, as one span 779); at 24576 (7680) it is 2 %.
 // Only the number of segments counts, not where the last one ends: the workspace query goes over these plans.
 void plan_dims(Dims* d, bool mfma, bool one_stream) {
     if (d->L == 0) return;

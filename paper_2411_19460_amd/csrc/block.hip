@@ -189,7 +189,7 @@ BlockWs layout(const BlockDims& d, bool bwd) {
     w.dt = take(s * d.H * 2);
     w.y = take(s * d.d_inner * 2);
     w.yn = take(s * d.d_inner * 2);
-    // scratch of the inner calls: for a whole segment and for the short last one (which the scan pads)
+    // scratch of the inner calls: for a whole segment and for the short last one (a segment of its own length)
     const ssd_shape_t ss = seg_shape(d, d.s);
     const ssd_shape_t st = seg_shape(d, d.L % d.s ? d.L % d.s : d.s);
     size_t inner = 0;  // the backward pass also runs the forward scan (recomputation)
@@ -748,7 +748,7 @@ StackWs stack_layout(const magc_blockstack_shape_t* sh, const StackDims& d, bool
     }
     const magc_block_shape_t c = cell_shape(sh, d.b.s);
     size_t inner = magc_block_workspace_bytes(&c, bwd ? 1 : 0);
-    if (d.b.L % d.b.s) {  // the short last segment pads the scan: its scratch may differ
+    if (d.b.L % d.b.s) {  // the short last segment is one of its own length: its scratch may differ
         const magc_block_shape_t ct = cell_shape(sh, d.b.L % d.b.s);
         const size_t t = magc_block_workspace_bytes(&ct, bwd ? 1 : 0);
         inner = t > inner ? t : inner;

@@ -24,7 +24,7 @@ static __device__ __forceinline__ float wave_sum(float v) {
 
 // One workgroup of DDT_THREADS per (chunk c, head h, batch b).  load(offset of the chunk and head + i, i) returns what
 // the passes before left for token i; store(index into ddt, value) writes one element of ddt in its storage type.
-// Sums run inside the waves (lane exchanges) and then over the four waves: three barriers in all, where a scan over LDS
+// Sums run inside the waves (lane exchanges) and then over the four waves: two barriers in all, where a scan over LDS
 // took two per doubling (it was half of the launch it rides in for a few chunks).
 template <class Load, class Store>
 __device__ __forceinline__ void ddt_finalize_body(const SegParams& sp, DdtLds& L, int c, int h, int b, Load load, Store store) {

@@ -24,9 +24,10 @@
 // this replaces.  A workgroup of four waves owns a 64 x 64 tile; K goes by in steps of 32, staged through two LDS
 // buffers (one barrier a step) as [row][k] with the next step's global loads in flight during the MFMAs.  The weights
 // (decays, dt, masks) are applied between the load and the LDS store.  Sums over the heads of a group are cut into head
-// slices so that a sequence of a few chunks still fills the machine (1999 tokens of 24 heads, forward + backward: 875 us
-// with FMA tiles and serial heads, 252 us now).  Small problems are bound by launches (512 tokens of 4 heads: 14
-// launches, 113 us): three forward, five backward here, 64 us.
+// slices so that a sequence of a few chunks still fills the machine (1999 tokens of 24 heads in two segments, forward +
+// backward: 1340 us with FMA tiles, serial heads and launches of their own for every segment, 253 us now).  Small problems are
+// bound by launches: three forward, five backward here for segments that share them (512 tokens of 4 heads in two segments: 216
+// us with 14 for each segment, 64 us now).
 #include "ddt_finalize.h"
 #include "ssd_internal.h"
 

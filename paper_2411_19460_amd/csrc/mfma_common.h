@@ -46,9 +46,10 @@ static __device__ __forceinline__ bf16x8 frag_tr(const char* tile, int pitch, in
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// Token rows of one chunk as buffer accesses: the descriptor (wave-uniform, scalar registers) spans the rows
-// of the chunk that exist, so rows beyond the end of a ragged chunk read as zeros and are not written, at no cost in
-// vector instructions.  Zeros for every operand: a copy of the last row, infinite, would be a NaN under the dt = 0 of a row that does not exist.  Offsets are 32-bit: a chunk has at most 256 rows of H x 64 bf16 (< 4 GB for any H taken).
+// Token rows of one chunk as buffer accesses: the descriptor (wave-uniform, scalar registers) spans the rows of the chunk that
+// exist, so rows beyond the end of a ragged chunk read as zeros and are not written, at no cost in vector instructions.
+// Zeros for every operand: a copy of the last row, infinite, would be a NaN under the dt = 0 of a row that does not exist.
+// Offsets are 32-bit: a chunk has at most 256 rows of H x 64 bf16 (< 4 GB for any H taken).
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 static __device__ __forceinline__ rsrc_t make_rows(const void* base, int rows, uint32_t rowbytes) {
