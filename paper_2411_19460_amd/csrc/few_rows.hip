@@ -271,8 +271,8 @@ constexpr int MFMA_WAVES = 8, MAX_GROUPS = 8;
 // nothing (three and four rows on fp32 operands on the vector ALUs took twice the time).
 __host__ __device__ __forceinline__ int row_parts(int rows) { return rows <= 4 ? 3 : rows <= 8 ? 2 : 1; }
 __host__ __device__ constexpr int part_step(int parts) { return parts == 3 ? 4 : parts == 2 ? 8 : 16; }  // rows between a row's parts
-// What rounding v to b left of it: nothing of an infinity, which the first part carries alone (an operand that goes through a
-// norm is NaN then in any case).
+// What rounding v to b left of it: nothing of an infinity (of the row, or of the row times the norm's weight), which the first
+// part carries alone.
 __device__ __forceinline__ float rest_of(float v, __bf16 b) { return __builtin_isinf((float)b) ? 0.f : v - (float)b; }
 __device__ __forceinline__ void pack_operand(__bf16* pack, int row, int k, float v, int parts) {
     const __bf16 hi = (__bf16)v;
@@ -386,11 +386,11 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
                     float xw = x * iw[s][e >> 2][e & 3];
                     av[e] = (__bf16)xw;
                     if (PARTS > 1) {
-                        xw -= (float)av[e];
+                        xw = rest_of(xw, av[e]);
                         if (col >= pstep) av[e] = (__bf16)xw;
                     }
                     if (PARTS > 2) {
-                        xw -= (float)av[e];
+                        xw = rest_of(xw, av[e]);
                         if (col >= 2 * pstep) av[e] = (__bf16)xw;
                     }
                 } else {

@@ -141,6 +141,26 @@ def test_infinities_pass_through_the_packed_operand(nseq):
     assert torch.equal(cs[hit, 1, 2].float(), want[hit])
 
 
+@pytest.mark.parametrize("nseq", [2, 3, 6, 9])
+def test_an_infinite_norm_weight_gives_infinite_products(nseq):
+    """The row times the norm's weight overflows in one element: the products are infinities of its weight's sign, not NaN, however
+    many parts the operand is carried in."""
+    H, P, N, dm, g = 8, 64, 128, 512, torch.Generator(device="cuda")
+    g.manual_seed(nseq)
+    normal = lambda *shape, dtype=torch.float32: torch.randn(shape, generator=g, device="cuda", dtype=dtype)  # noqa: E731
+    di, conv = H * P, H * P + 2 * N
+    layer = {"W_in": normal(2 * di + 2 * N + H, dm, dtype=torch.bfloat16).mul_(dm ** -0.5), "conv_w": normal(conv, 4) * 0.5,
+             "conv_b": normal(conv) * 0.2, "dt_bias": normal(H) - 4, "A": -torch.rand(H, generator=g, device="cuda") * 15 - 1, "D": normal(H),
+             "norm_w": 1 + 0.3 * normal(di), "W_out": normal(dm, di, dtype=torch.bfloat16).mul_(di ** -0.5), "pre_norm_w": 1 + 0.3 * normal(dm)}
+    layer["pre_norm_w"][77] = float("inf")
+    x0 = normal(nseq, dm, dtype=torch.bfloat16)
+    ssm, cs = normal(nseq, 1, H, P, N) * 0.3, normal(nseq, 1, 3, conv, dtype=torch.bfloat16)
+    pk.magc_blockstack_decode(x0, [layer], H, P, 1, N, 64, 64, ssm, cs)
+    torch.cuda.synchronize()
+    want = torch.sign(x0[:, 77, None].float() * layer["W_in"][di:di + conv, 77].float()) * float("inf")
+    assert torch.equal(cs[:, 0, 2].float(), want)
+
+
 def test_parameters_are_checked_on_every_step():
     """A stack that one step accepted is refused once one of its tensors, at the same address, has another shape."""
     from paper_2411_19460_amd import binding
