@@ -41,10 +41,11 @@ def kernel_models(cfg, tokens_per_launch, generic=False):
       bwd_trio = bwd_main + dG + dBC as one launch (chunk 256): flop add up; x and dY count once
     The shape-generic kernels run the same steps in fewer launches, states and scores in fp32: chunk_state = scores and
     chunk states (in the backward pass the local adjoints too: the mean of the two launches is given), bwd_main = dx, dG
-    and the state terms, dBC = dB, dC and ddt; their reverse scan walks the states forth and back.
+    and the state terms, dBC = dB, dC and ddt.
       state scans, per (chunk, head) state of P*N elements (matrix-core path, bf16 in memory):
-      forward reads the chunk state and writes the entering state (4 B/element), reverse reads the
-      local adjoint and the entering state and writes the total adjoint (6 B/element).
+      forward reads the chunk state and writes the entering state (4 B/element); the backward pass's walks forth and back
+      in one launch: chunk state and local adjoint in, entering state and total adjoint out (8 B/element; the way back
+      finds the entering states in cache).
     tokens_per_launch: one or several segments (layer_bench counts the launches)."""
     H, P, N, G, Q = cfg.nheads, cfg.headdim, cfg.dstate, cfg.ngroups, cfg.chunk
     t = tokens_per_launch
@@ -69,7 +70,7 @@ def kernel_models(cfg, tokens_per_launch, generic=False):
         "bwd_main": ((4 * Q * P + 6 * N * P) * H, 3 * X + 2 * S4 + 8 * Q * G + 2 * b + 8 * R + 8 * G * N),
         "dBC": (4 * Q * N * G, 4 * Q * G + 4 * b + 8 * G * N + 7 * R + H * esz),
         "cumsum": (0, H * esz + 4 * 4 * H),
-        "state_scan_fwd": (0, (4 if mfma else 8) * st), "state_scan_bwd": (0, (6 if mfma else 20) * st),
+        "state_scan_fwd": (0, (4 if mfma else 8) * st), "state_scan_bwd": (0, (8 if mfma else 20) * st),
     }
     return {k: (fl * t, by * t) for k, (fl, by) in m.items()}
 

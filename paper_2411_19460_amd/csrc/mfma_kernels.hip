@@ -243,129 +243,158 @@ __global__ __launch_bounds__(OUTER_THR, 2) void mk_chunk_outer(SegParams sp, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// Inter-chunk state passing over a span (four state elements per thread).  The running state is
-// carried in fp32 registers (checkpoints and the final state are stored from them); the state
-// entering each chunk is emitted as the bf16 copy the contraction kernels read, nothing else.
-__device__ __forceinline__ bf16x4 to_bf16x4(const float4 v) {
-    bf16x4 r;
-    r[0] = (__bf16)v.x; r[1] = (__bf16)v.y; r[2] = (__bf16)v.z; r[3] = (__bf16)v.w;
-    return r;
+// Inter-chunk state passing over a span, four state elements per thread.  The running state is carried in fp32 registers
+// (checkpoints and the final state are stored from them); the state entering each chunk is emitted as the bf16 copy the
+// contraction kernels read, nothing else.  Bound by the trips of the chunk states through memory: the recurrence is serial,
+// so the loads of a block of chunks are under way while the block before it is worked on.  (Two elements per thread, twice
+// the waves: no faster at 24 heads, 10 % slower at 64.)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x4 ld_state(const float* p) { return *(const f32x4*)p; }
+__device__ __forceinline__ f32x4 ld_state(const bf16_t* p) { return __builtin_convertvector(*(const bf16x4*)p, f32x4); }
+__device__ __forceinline__ void st_state(float* p, f32x4 v) { *(f32x4*)p = v; }
+__device__ __forceinline__ void st_state(bf16_t* p, f32x4 v) { *(bf16x4*)p = __builtin_convertvector(v, bf16x4); }
+
+// Sum over the wave in lane 63, by lane exchanges of the vector ALUs (rows of 16 lanes, then across the rows).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xF, true));
 }
-__device__ __forceinline__ float4 from_bf16x4(const bf16x4 v) {
-    return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+__device__ __forceinline__ float wave_sum_last(float v) {
+    v = dpp_add<0x111, 0xF>(v);  // row_shr:1
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);  // lane 15 of every row: the row's sum
+    v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return v;
 }
 
-// F32IN: the chunk states arrive in fp32 (SSD_FLAG_FP32_CHUNK_STATES), else as bf16 in place.
-// Forward pass (nseg = 1): one walk over all chunks of the span, putting the checkpoints of its segments down on the
-// way.  Backward pass (nseg = segments of the span): every segment restarts from its checkpoint, side by side.
-template <bool F32IN>
-__global__ __launch_bounds__(NTH) void mk_scan_fwd(SegParams sp, int nseg) {
+// F32IN: the chunk states arrive in fp32 (SSD_FLAG_FP32_CHUNK_STATES, an array of their own), else as bf16 in place.
+// BWD = false: one walk over all chunks of the span, putting the checkpoints of its segments down on the way.
+// BWD = true: the walk to the right again, every segment restarted from its checkpoint, then the walk back over the
+// chunk-state adjoints, which emits the bf16 adjoint leaving each chunk and the per-wave partial sums of
+// exp(T_c) <dHnext_c, Hprev_c>, the gradient of the chunk's total decay through the carried state (fixed summation order).
+// The way back finds the entering states that the same thread has just written in the L2 of its XCD.  As two launches the
+// same work read them from memory and paid a second ramp: 32 chunks of 24 heads 21.5 -> 17.8 us, 24 chunks of 2 x 32 heads
+// 25.6 -> 21.4.
+template <bool BWD, bool F32IN>
+__global__ __launch_bounds__(NTH) void mk_scan(SegParams sp) {
     constexpr int PN = P_ * N_;
-    const int e = (blockIdx.x * NTH + threadIdx.x) * 4, h = blockIdx.y, seg = blockIdx.z % nseg, b = blockIdx.z / nseg;
+    constexpr int U = 8;  // chunks of a block: their loads are in flight together
+    const int e = (blockIdx.x * NTH + threadIdx.x) * 4, h = blockIdx.y, b = blockIdx.z, nc = sp.nc;
     const int64_t bh = (int64_t)h * PN + e, HPN = (int64_t)sp.H * PN;
-    const int c_lo = seg * sp.seg_chunks, c_hi = nseg > 1 && c_lo + sp.seg_chunks < sp.nc ? c_lo + sp.seg_chunks : sp.nc;
-    float4 hc = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (seg > 0) {
-        const int64_t o = (int64_t)b * sp.ckpt_bs + seg * HPN + bh;
-        hc = sp.ckpt16 ? from_bf16x4(*(const bf16x4*)(sp.ckpt16 + o)) : *(const float4*)(sp.ckpt + o);
-    } else if (sp.state_in) {
-        hc = *(const float4*)(sp.state_in + (int64_t)b * sp.state_in_bs + bh);
-    } else if (sp.state_in16) {  // bf16 checkpoint
-        hc = from_bf16x4(*(const bf16x4*)(sp.state_in16 + (int64_t)b * sp.state_in_bs + bh));
-    }
-    if (sp.bnd_write) *(float4*)(sp.bnd_write + (int64_t)b * sp.bnd_write_bs + bh) = hc;
-    if (sp.bnd_write16) *(bf16x4*)(sp.bnd_write16 + (int64_t)b * sp.bnd_write_bs + bh) = to_bf16x4(hc);
-    const float* cum = sp.cum + ((int64_t)b * sp.H + h) * sp.nc * sp.Q;
-    const bool put = nseg == 1 && (sp.ckpt || sp.ckpt16);
-    int next = put ? sp.seg_chunks : sp.nc;  // chunk at which the next segment of the span starts
-    int64_t slot = (int64_t)b * sp.ckpt_bs + bh;
-    constexpr bool f32in = F32IN;
-    constexpr int U = 8;  // chunks whose loads are in flight together (the recurrence itself is serial)
-    for (int c0 = c_lo; c0 < c_hi; c0 += U) {
-        float4 sv[U];
-        float av[U];
+    const float* cum = sp.cum + ((int64_t)b * sp.H + h) * nc * sp.Q + sp.Q - 1;
+    const int64_t base = (int64_t)b * nc * HPN + bh;
+    f32x4 hc = (f32x4)(0.f), nxt = (f32x4)(0.f);
+    struct Block {
+        f32x4 s[U];
+        float a[U];
+    } A, B;
+    auto load = [&](Block& R, int c0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int c = c0 + u < c_hi ? c0 + u : c_hi - 1;
-            if (f32in)  // chunk state kept in fp32 (an array of its own)
-                sv[u] = *(const float4*)(sp.states + (((int64_t)b * sp.nc + c) * sp.H + h) * PN + e);
-            else        // chunk state (bf16), about to be replaced in place by the state entering the chunk
-                sv[u] = from_bf16x4(*(const bf16x4*)(sp.states_bf + (((int64_t)b * sp.nc + c) * sp.H + h) * PN + e));
-            av[u] = cum[(int64_t)c * sp.Q + sp.Q - 1];
+            const int c = c0 + u < nc ? c0 + u : nc - 1;
+            R.s[u] = F32IN ? ld_state(sp.states + base + c * HPN) : ld_state(sp.states_bf + base + c * HPN);
+            R.a[u] = cum[(int64_t)c * sp.Q];
         }
+    };
+    int64_t slot = (int64_t)b * sp.ckpt_bs + bh;
+    // chunk at which the next segment of the span starts; its checkpoint is asked for a segment ahead
+    int next = sp.ckpt || sp.ckpt16 ? sp.seg_chunks : nc;
+    auto ask = [&] {
+        if (BWD && next < nc) nxt = sp.ckpt16 ? ld_state(sp.ckpt16 + slot + HPN) : ld_state(sp.ckpt + slot + HPN);
+    };
+    if (sp.state_in) hc = ld_state(sp.state_in + (int64_t)b * sp.state_in_bs + bh);
+    else if (sp.state_in16) hc = ld_state(sp.state_in16 + (int64_t)b * sp.state_in_bs + bh);  // bf16 checkpoint
+    load(A, 0);
+    ask();
+    if (!BWD) {
+        if (sp.bnd_write) st_state(sp.bnd_write + (int64_t)b * sp.bnd_write_bs + bh, hc);
+        if (sp.bnd_write16) st_state(sp.bnd_write16 + (int64_t)b * sp.bnd_write_bs + bh, hc);
+    }
+    auto walk = [&](const Block& R, int c0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int c = c0 + u;
-            if (c < c_hi) {
-                if (c == next) {  // uniform
-                    next += sp.seg_chunks;
-                    slot += HPN;
-                    if (sp.ckpt) *(float4*)(sp.ckpt + slot) = hc;
-                    if (sp.ckpt16) *(bf16x4*)(sp.ckpt16 + slot) = to_bf16x4(hc);
+            if (c >= nc) break;  // uniform
+            if (c == next) {     // uniform
+                next += sp.seg_chunks;
+                slot += HPN;
+                if (BWD) {
+                    hc = nxt;
+                    ask();
+                } else {
+                    if (sp.ckpt) st_state(sp.ckpt + slot, hc);
+                    if (sp.ckpt16) st_state(sp.ckpt16 + slot, hc);
                 }
-                const bf16x4 hb = to_bf16x4(hc);  // the entering state is kept in bf16 only
-                *(bf16x4*)(sp.states_bf + (((int64_t)b * sp.nc + c) * sp.H + h) * PN + e) = hb;
-                const float a = __expf(av[u]);
-                const float4 s = sv[u];
-                hc.x = a * hc.x + s.x; hc.y = a * hc.y + s.y; hc.z = a * hc.z + s.z; hc.w = a * hc.w + s.w;
             }
+            st_state(sp.states_bf + base + c * HPN, hc);
+            hc = __expf(R.a[u]) * hc + R.s[u];
         }
+    };
+    for (int c0 = 0; c0 < nc; c0 += 2 * U) {
+        if (c0 + U < nc) load(B, c0 + U);
+        walk(A, c0);
+        if (c0 + 2 * U < nc) load(A, c0 + 2 * U);
+        if (c0 + U < nc) walk(B, c0 + U);
     }
-    if (sp.state_out) *(float4*)(sp.state_out + (int64_t)b * sp.state_out_bs + bh) = hc;
-    if (sp.state_out2) *(float4*)(sp.state_out2 + (int64_t)b * sp.state_out2_bs + bh) = hc;
-    if (sp.state_out16) *(bf16x4*)(sp.state_out16 + (int64_t)b * sp.state_out16_bs + bh) = to_bf16x4(hc);
-}
-
-// Reverse pass over the chunk-state adjoints; emits the bf16 copies and the per-wave partial sums
-// of exp(T_c) <dHnext_c, Hprev_c>, the gradient of the chunk's total decay through the carried state
-// (fixed summation order).
-template <bool F32IN>
-__global__ __launch_bounds__(NTH) void mk_scan_bwd(SegParams sp) {
-    constexpr int PN = P_ * N_;
-    const int e = (blockIdx.x * NTH + threadIdx.x) * 4, h = blockIdx.y, b = blockIdx.z;
-    const int64_t ce = ((int64_t)b * sp.H + h) * PN + e;
-    float4 g = sp.dcarry_in ? *(const float4*)(sp.dcarry_in + ce) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float* cum = sp.cum + ((int64_t)b * sp.H + h) * sp.nc * sp.Q;
-    constexpr bool f32in = F32IN;
-    constexpr int U = 4;  // chunks whose loads are in flight together
-    for (int c0 = sp.nc - 1; c0 >= 0; c0 -= U) {
-        float4 lv[U], hv[U];
-        float av[U];
+    if (!BWD) {
+        if (sp.state_out) st_state(sp.state_out + (int64_t)b * sp.state_out_bs + bh, hc);
+        if (sp.state_out2) st_state(sp.state_out2 + (int64_t)b * sp.state_out2_bs + bh, hc);
+        if (sp.state_out16) st_state(sp.state_out16 + (int64_t)b * sp.state_out16_bs + bh, hc);
+        return;
+    }
+    const int64_t ce = (int64_t)b * HPN + bh;
+    f32x4 g = sp.dcarry_in ? ld_state(sp.dcarry_in + ce) : (f32x4)(0.f);
+    constexpr int UB = 4;  // two arrays a chunk on the way back
+    struct Back {
+        f32x4 l[UB], h[UB];
+        float a[UB];
+    } RA, RB;
+    auto loadb = [&](Back& R, int c0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < UB; ++u) {
             const int c = c0 - u >= 0 ? c0 - u : 0;
-            if (f32in) {  // local adjoint kept in fp32 (an array of its own)
-                lv[u] = *(const float4*)(sp.dstates + (((int64_t)b * sp.nc + c) * sp.H + h) * PN + e);
-            } else {      // local adjoint (bf16), about to be replaced in place by the total adjoint leaving the chunk
-                const bf16x4 lb = *(const bf16x4*)(sp.dstates_bf + (((int64_t)b * sp.nc + c) * sp.H + h) * PN + e);
-                lv[u] = make_float4((float)lb[0], (float)lb[1], (float)lb[2], (float)lb[3]);
-            }
-            av[u] = cum[(int64_t)c * sp.Q + sp.Q - 1];
-            // state entering chunk c (bf16 copy)
-            {
-                const bf16x4 hb = *(const bf16x4*)(sp.states_bf + (((int64_t)b * sp.nc + c) * sp.H + h) * PN + e);
-                hv[u] = make_float4((float)hb[0], (float)hb[1], (float)hb[2], (float)hb[3]);
-            }
+            R.l[u] = F32IN ? ld_state(sp.dstates + base + c * HPN) : ld_state(sp.dstates_bf + base + c * HPN);
+            R.h[u] = ld_state(sp.states_bf + base + c * HPN);
+            R.a[u] = cum[(int64_t)c * sp.Q];
         }
+    };
+    float* tail = sp.tail_part + ((int64_t)b * sp.H + h) * nc * sp.nslice + blockIdx.x * (NTH / 64) + (threadIdx.x >> 6);
+    auto walkb = [&](const Back& R, int c0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < UB; ++u) {
             const int c = c0 - u;
             if (c < 0) break;  // uniform
-            bf16x4 gb;  // the total adjoint is kept in bf16 only
-            gb[0] = (__bf16)g.x; gb[1] = (__bf16)g.y; gb[2] = (__bf16)g.z; gb[3] = (__bf16)g.w;
-            *(bf16x4*)(sp.dstates_bf + (((int64_t)b * sp.nc + c) * sp.H + h) * PN + e) = gb;
-            const float a = __expf(av[u]);
-            const float4 hp = hv[u];
-            float part = a * (g.x * hp.x + g.y * hp.y + g.z * hp.z + g.w * hp.w);
-            for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off, 64);
-            if ((threadIdx.x & 63) == 0)  // one partial sum per wave; summed later in a fixed order
-                sp.tail_part[(((int64_t)b * sp.H + h) * sp.nc + c) * sp.nslice + blockIdx.x * (NTH / 64) + (threadIdx.x >> 6)] = part;
-            const float4 loc = lv[u];
-            g.x = a * g.x + loc.x; g.y = a * g.y + loc.y; g.z = a * g.z + loc.z; g.w = a * g.w + loc.w;
+            st_state(sp.dstates_bf + base + c * HPN, g);  // the total adjoint is kept in bf16 only
+            const float a = __expf(R.a[u]);
+            float part = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part += g[i] * R.h[u][i];
+            part = wave_sum_last(a * part);
+            if ((threadIdx.x & 63) == 63) tail[(int64_t)c * sp.nslice] = part;  // one per wave; summed later in a fixed order
+            g = a * g + R.l[u];
         }
+    };
+    loadb(RA, nc - 1);
+    for (int c0 = nc - 1; c0 >= 0; c0 -= 2 * UB) {
+        if (c0 >= UB) loadb(RB, c0 - UB);
+        walkb(RA, c0);
+        if (c0 >= 2 * UB) loadb(RA, c0 - 2 * UB);
+        if (c0 >= UB) walkb(RB, c0 - UB);
     }
-    *(float4*)(sp.dcarry + ce) = g;
-    if (sp.dinit_out) *(float4*)(sp.dinit_out + ce) = g;
+    st_state(sp.dcarry + ce, g);
+    if (sp.dinit_out) st_state(sp.dinit_out + ce, g);
+}
+
+template <bool BWD>
+hipError_t scan(const SegParams& sp, hipStream_t st) {
+    const dim3 grid(P_ * N_ / 4 / NTH, sp.H, sp.Bt);
+    if (sp.flags & SSD_FLAG_FP32_CHUNK_STATES)
+        SSDK_LAUNCH(BWD ? K_SCAN_BWD : K_SCAN_FWD, st, (mk_scan<BWD, true>), grid, dim3(NTH), sp);
+    else
+        SSDK_LAUNCH(BWD ? K_SCAN_BWD : K_SCAN_FWD, st, (mk_scan<BWD, false>), grid, dim3(NTH), sp);
+    return hipSuccess;
 }
 
 template <int Q>
@@ -386,36 +415,28 @@ hipError_t fwd_q(const SegParams& sp, bool need_y, hipStream_t st) {
             SSDK_LAUNCH(need_y ? K_MFMA_CHUNK_STATE : K_MFMA_DSTATE, st, (mk_chunk_outer<Q, false>), dim3(sp.Bt * sp.nc * sp.G * nroles * so.outer_split), dim3(OUTER_THR), so, nroles);
     }
     if (Q != 256) SSDK_LAUNCH(K_MFMA_CB, st, mk_cb<Q>, dim3(sp.Bt * sp.nc * sp.G, NB * (NB + 1) / 2), dim3(NTH), sp);
+    if (!need_y) return hipSuccess;  // the backward pass restores the entering states in the launch of its own scan
     // the scan is the only step that needs the previous segment (its leaving state)
-    if (need_y && sp.ev_wait && hipStreamWaitEvent(st, sp.ev_wait, 0) != hipSuccess) return hipErrorUnknown;
-    const int nseg = need_y ? 1 : (sp.nc + sp.seg_chunks - 1) / sp.seg_chunks;
-    if (sp.flags & SSD_FLAG_FP32_CHUNK_STATES)
-        SSDK_LAUNCH(K_SCAN_FWD, st, mk_scan_fwd<true>, dim3(P_ * N_ / 4 / NTH, sp.H, sp.Bt * nseg), dim3(NTH), sp, nseg);
-    else
-        SSDK_LAUNCH(K_SCAN_FWD, st, mk_scan_fwd<false>, dim3(P_ * N_ / 4 / NTH, sp.H, sp.Bt * nseg), dim3(NTH), sp, nseg);
-    if (need_y && sp.ev_record && hipEventRecord(sp.ev_record, st) != hipSuccess) return hipErrorUnknown;
-    if (need_y) {
-        hipError_t e = mfma_launch_dual(sp, 0, st);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    if (sp.ev_wait && hipStreamWaitEvent(st, sp.ev_wait, 0) != hipSuccess) return hipErrorUnknown;
+    const hipError_t e = scan<false>(sp, st);
+    if (e != hipSuccess) return e;
+    if (sp.ev_record && hipEventRecord(sp.ev_record, st) != hipSuccess) return hipErrorUnknown;
+    return mfma_launch_dual(sp, 0, st);
 }
 
 template <int Q>
 hipError_t bwd_q(const SegParams& sp0, hipStream_t st) {
     SegParams sp = sp0;
-    sp.nslice = P_ * N_ / 4 / 64;  // partial sums written by mk_scan_bwd: one per wave
-    // the reverse scan is the only step that needs the segment to the right (its entering-state adjoint)
+    sp.nslice = P_ * N_ / 4 / 64;  // partial sums of the reverse scan: one per wave
+    // the scan is the only step that needs the segment to the right (its entering-state adjoint)
     if (sp.ev_wait && hipStreamWaitEvent(st, sp.ev_wait, 0) != hipSuccess) return hipErrorUnknown;
-    if (sp.flags & SSD_FLAG_FP32_CHUNK_STATES)
-        SSDK_LAUNCH(K_SCAN_BWD, st, mk_scan_bwd<true>, dim3(P_ * N_ / 4 / NTH, sp.H, sp.Bt), dim3(NTH), sp);
-    else
-        SSDK_LAUNCH(K_SCAN_BWD, st, mk_scan_bwd<false>, dim3(P_ * N_ / 4 / NTH, sp.H, sp.Bt), dim3(NTH), sp);
+    hipError_t e = scan<true>(sp, st);
+    if (e != hipSuccess) return e;
     if (sp.ev_record && hipEventRecord(sp.ev_record, st) != hipSuccess) return hipErrorUnknown;
     // dx, dG and the dB / dC head sums (which also write the chunk-local part of the gradient of cum
     // and the state dot products): one launch when the three share a workgroup size
     const bool trio = Q == 256;
-    hipError_t e = trio ? hipSuccess : mfma_launch_dual(sp, 2, st);
+    if (!trio) e = mfma_launch_dual(sp, 2, st);
     if (e != hipSuccess) return e;
     e = mfma_launch_grad_bc(sp, trio, st);   // ddt and the dA / dD partial sums ride in its last launch
     if (e != hipSuccess) return e;
