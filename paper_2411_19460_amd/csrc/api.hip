@@ -17,6 +17,22 @@ int pick_split(int heads_per_group, int64_t base, int target) {
     return heads_per_group;
 }
 
+// As above for a launch that has the machine to itself: the slices that end soonest.  A compute unit holds per_unit of the
+// workgroups (1 or 2) and a launch goes by in rounds of them; a workgroup takes `prologue` before its first head (both in
+// hundredths of a head), and with a unit to itself where two fit it walks a head in two thirds of the time.
+int pick_rounds(int heads_per_group, int64_t base, int per_unit, int prologue) {
+    constexpr int64_t UNITS = 256;
+    int best = 1;
+    int64_t least = INT64_MAX;
+    for (int ns = 1; ns <= heads_per_group; ++ns) {
+        if (heads_per_group % ns) continue;
+        const int64_t n = base * ns, hps = heads_per_group / ns;
+        const int64_t t = n <= UNITS && per_unit == 2 ? 65 * hps + prologue : (n + UNITS * per_unit - 1) / (UNITS * per_unit) * (100 * hps + prologue);
+        if (t < least) least = t, best = ns;
+    }
+    return best;
+}
+
 // Returns SSD_OK and fills d, or the validation error.
 int check_shape(const ssd_shape_t* sh, Dims* d) {
     if (!sh) return SSD_ERR_NULL;
@@ -92,6 +108,33 @@ HeadSlices part_slices(const Dims& d, bool mfma, int wg_target) {
 }
 }  // namespace
 
+// Slices of the three head-walking passes of the backward sweep (chunks of 256: one launch) for a span of nc chunks.  A
+// compute unit holds one of their workgroups.  With the machine to itself such a launch ends soonest when all its workgroups
+// fit in one round, if slices can be found that make them about equally long: what a workgroup pays around its heads (fetching
+// the scores, storing the partial sums) is paid once, and there are fewer partial sums to write and add up.  In thousands of
+// cycles a workgroup of dx takes 8 + 10 a head, of dG 11 + 12, of the head sums 13 + 5; otherwise every pass gets a workgroup
+// per compute unit and the three alternate.  32 chunks of 24 heads, slices (8, 8, 4) -> (3, 3, 1): 75.2 -> 63.6 us, and
+// the finalisation 19.0 -> 13.6; 16 chunks of 80 heads, (16, 16, 8) -> (5, 5, 2): 114 -> 103 and 19.1 -> 14.2.
+WalkSlices walk_slices(const Dims& d, int64_t nc, bool mfma, int wg_target) {
+    WalkSlices w;
+    w.dg = dg_slices(d, mfma, wg_target).split(nc);
+    w.part = part_slices(d, mfma, wg_target).split(nc);
+    w.dual = 0;
+    if (!mfma || d.Q != 256 || wg_target < 256 || nc <= 0) return w;
+    const int64_t base = d.Bt * nc * d.G;
+    auto longest = [&](int64_t a, int64_t p) {
+        const int64_t ha = d.hpg / a, hp = d.hpg / p, g = 11 + 12 * ha, s = 13 + 5 * hp;
+        return g > s ? g : s;
+    };
+    // what the general rule takes: the work spread over the machine, and half a workgroup of ragged end
+    const int64_t a0 = w.dg, p0 = w.part, work = a0 * (19 + 22 * (d.hpg / a0)) + 2 * p0 * (13 + 5 * (d.hpg / p0));
+    int64_t least = base * work / 256 + longest(a0, p0) / 2;
+    for (int a = 1; a <= w.dg; ++a)
+        for (int p = 1; p <= w.part && d.hpg % a == 0 && base * (2 * a + 2 * p) <= 256; ++p)
+            if (d.hpg % p == 0 && longest(a, p) < least) least = longest(a, p), w.dual = w.dg = a, w.part = p;
+    return w;
+}
+
 WsLayout ws_layout(const Dims& d, bool bwd, bool mfma, int wg_target, bool fp32cs) {
     WsLayout w;
     memset(&w, 0, sizeof(w));
@@ -117,8 +160,7 @@ WsLayout ws_layout(const Dims& d, bool bwd, bool mfma, int wg_target, bool fp32c
     if (mfma) w.states_bf = take((size_t)d.Bt * d.nc * d.H * PN * 2);
     const int64_t nt = (d.Q + 63) / 64, nn = (d.N + 63) / 64, np = (d.P + 63) / 64;  // 64 x 64 tiles of the generic kernels
     const HeadSlices dg = dg_slices(d, mfma, wg_target), part = part_slices(d, mfma, wg_target);
-    w.dg_split = dg.split(d.nc);
-    w.part_split = part.split(d.nc);
+    w.walk = walk_slices(d, d.nc, mfma, wg_target);
     if (bwd) {
         if (!mfma || fp32cs) w.dstates = take((size_t)d.Bt * d.nc * d.H * PN * 4);
         if (mfma) w.dstates_bf = take((size_t)d.Bt * d.nc * d.H * PN * 2);
@@ -155,8 +197,9 @@ void bind_workspace(SegParams& sp, const WsLayout& w, void* workspace, bool bwd)
     sp.eout = (float*)at(w.eout);
     sp.tok_stride = (int64_t)(w.tok / 4);
     sp.states_bf = (bf16_t*)at(w.states_bf);
-    sp.dg_split = w.dg_split;
-    sp.part_split = w.part_split;
+    sp.dual_split = w.walk.dual;
+    sp.dg_split = w.walk.dg;
+    sp.part_split = w.walk.part;
     if (bwd) {
         sp.dstates_bf = (bf16_t*)at(w.dstates_bf);
         sp.dbc_part = (float*)at(w.dbc_part);
@@ -430,8 +473,10 @@ static void span_tokens(SegParams& sp, const Dims& d, int64_t k, int64_t ns) {
 // Head slices of the per-slice partial sums for a span that may be shorter than the largest one (fewer chunks to spread
 // over the machine).
 static void fit_splits(SegParams& sp, const Dims& d, bool mfma) {
-    sp.dg_split = dg_slices(d, mfma, wg_target(d.nl)).split(sp.nc);
-    sp.part_split = part_slices(d, mfma, wg_target(d.nl)).split(sp.nc);
+    const WalkSlices w = walk_slices(d, sp.nc, mfma, wg_target(d.nl));
+    sp.dual_split = w.dual;
+    sp.dg_split = w.dg;
+    sp.part_split = w.part;
 }
 
 // one_stream: everything stays on the caller's stream (no library stream or event is touched).

@@ -15,9 +15,11 @@ __global__ __launch_bounds__(DualCfg<Q>::NTHR) void mk_dual(SegParams sp) {
 template <int Q, int EPI>
 hipError_t launch_dual_q(const SegParams& sp0, int kid, hipStream_t st) {
     SegParams sp = sp0;
-    // as few head slices as still give every compute unit a workgroup: the persistent operands are then
-    // shared by as many heads as possible
-    sp.dual_split = pick_split(sp.hpg, (int64_t)sp.Bt * sp.nc * sp.G, sp.wg_target);
+    // with other launches in flight: as few head slices as still give every compute unit a workgroup, the persistent
+    // operands are then shared by as many heads as possible.  Alone: the fewest rounds over the machine (10007 tokens of 80
+    // heads, eight slices in two rounds -> five in one: 96.6 -> 76.3 us)
+    const int64_t base = (int64_t)sp.Bt * sp.nc * sp.G;
+    sp.dual_split = sp.wg_target < 256 ? pick_split(sp.hpg, base, sp.wg_target) : pick_rounds(sp.hpg, base, Q == 256 ? 1 : 2, 70);
     SSDK_LAUNCH(kid, st, (mk_dual<Q, EPI>), dim3(sp.Bt * sp.nc * sp.G * sp.dual_split), dim3(DualCfg<Q>::NTHR), sp);
     return hipSuccess;
 }

@@ -802,7 +802,7 @@ hipError_t grad_bc_q(const SegParams& sp0, bool with_dual, hipStream_t st) {
     const int n_dg = sp.Bt * sp.nc * sp.G * sp.dg_split, n_part = sp.Bt * sp.nc * sp.G * 2 * sp.part_split;
     if (with_dual) {
         if (Q != 256) return hipErrorInvalidValue;
-        sp.dual_split = pick_split(sp.hpg, (int64_t)sp.Bt * sp.nc * sp.G, sp.wg_target);
+        if (!sp.dual_split) sp.dual_split = pick_split(sp.hpg, (int64_t)sp.Bt * sp.nc * sp.G, sp.wg_target);
         const int n_dual = sp.Bt * sp.nc * sp.G * sp.dual_split;
         sp.part_alternate = sp.dual_split == 2 * sp.part_split && sp.dg_split == sp.dual_split;
         SSDK_LAUNCH(K_MFMA_BWD_TRIO, st, mk_bwd_trio<256>, dim3(n_dual + n_dg + n_part), dim3(512), sp, n_dual, n_dg, n_part);

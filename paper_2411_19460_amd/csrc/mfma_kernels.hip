@@ -408,7 +408,9 @@ hipError_t fwd_q(const SegParams& sp, bool need_y, hipStream_t st) {
     {   // chunk states; on the backward path (need_y false) the local state adjoints ride in the same launch
         SegParams so = sp;
         const int nroles = need_y ? 1 : 2;
-        so.outer_split = pick_split(sp.hpg, (int64_t)sp.Bt * sp.nc * sp.G * nroles, sp.wg_target);
+        // alone on the machine (10007 tokens of 80 heads, eight slices -> ten: 40.2 -> 35.9 us); with others in flight as mk_dual
+        const int64_t base = (int64_t)sp.Bt * sp.nc * sp.G * nroles;
+        so.outer_split = sp.wg_target < 256 ? pick_split(sp.hpg, base, sp.wg_target) : pick_rounds(sp.hpg, base, 2, 140);
         if (sp.flags & SSD_FLAG_FP32_CHUNK_STATES)
             SSDK_LAUNCH(need_y ? K_MFMA_CHUNK_STATE : K_MFMA_DSTATE, st, (mk_chunk_outer<Q, true>), dim3(sp.Bt * sp.nc * sp.G * nroles * so.outer_split), dim3(OUTER_THR), so, nroles);
         else

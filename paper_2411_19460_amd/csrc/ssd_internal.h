@@ -92,7 +92,7 @@ struct SegParams {
     bf16_t* states_bf;   // [Bt][nc][H][P][N] chunk states, replaced in place by the states entering the chunks (bf16 only)
     bf16_t* dstates_bf;  // [Bt][nc][H][P][N] local state adjoints, replaced in place by the adjoints of the leaving states
     int dg_split;        // number of head slices whose dG / dB / dC partial sums are kept apart
-    int dual_split;      // number of head slices per (batch, chunk, group) in the dual-form kernels
+    int dual_split;      // number of head slices per (batch, chunk, group) in the dual-form kernels (backward, 0: chosen at the launch)
     int part_split;      // number of head slices of the dB / dC head sums
     int outer_split;     // number of head slices of the chunk-state / local-adjoint kernel
     int part_alternate;  // the head-sum pass alternates between the halves of its slice (see part_body)
@@ -181,10 +181,14 @@ constexpr float RESET_LOG_DECAY = -100.f;
 // does not exist on the chosen kernel path and its pointer stays null).
 constexpr size_t WS_NONE = ~(size_t)0;
 constexpr int GENERIC_SLICES = 4;  // head slices of the shape-generic kernels' partial sums, at most
+struct WalkSlices {
+    int dual, dg, part;  // head slices of the backward sweep's passes; dual 0: chosen at the launch
+};
 struct WsLayout {
     size_t cum, dtf, states, Gm, dstates, dG, gterm, fterm, dDrow, tail_part, dA_part, dD_part, dcarry, total;
     size_t ein, eout, states_bf, dstates_bf, dbc_part, sterm, gintra, erow, ecol, tok;
-    int nslice, dg_split, part_split;
+    int nslice;
+    WalkSlices walk;
 };
 
 int check_shape(const ssd_shape_t* sh, Dims* d);
@@ -240,6 +244,8 @@ hipError_t mfma_launch_dual(const SegParams& sp, int epi, hipStream_t st);
 hipError_t mfma_launch_grad_bc(const SegParams& sp, bool with_dual, hipStream_t st);
 // Smallest divisor ns of heads_per_group with base * ns >= target workgroups (else heads_per_group).
 int pick_split(int heads_per_group, int64_t base, int target);
+// Slices for a launch that has the machine to itself (see api.hip).
+int pick_rounds(int heads_per_group, int64_t base, int per_unit, int prologue);
 
 // The block's convolution with its output (forward) or the gradient of its output (backward) given as three
 // dense tensors side by side -- channels [0, c1), [c1, c2), [c2, C) with rows c1, c2 - c1, C - c2 apart: the
