@@ -4,14 +4,14 @@
 // grid-cell activations of App. C, Tab. 7, and the output projection behind the gated normalisation).
 // These are dense contractions far above the machine's flop/byte ridge: matrix-core bound.
 //
-// One scheme, C[M,N] = op(A) op(B)^T with fp32 accumulators in v_mfma_f32_32x32x16_bf16 tiles, for the three
+// One scheme, C[M,N] = op(A) op(B)^T with fp32 accumulators in v_mfma_f32_16x16x32_bf16 tiles, for the three
 // operand layouts the three products need: an operand is either stored with the contraction index
 // contiguous ("k-major": rows of x for the forward product) or with it as the row index (x and dout for
 // dw, w for dx).  Both kinds are staged in LDS exactly as they lie in memory (16-byte vectors); k-major
 // tiles are read back as plain 16-byte operands, the others through the transposing LDS read.
-// One kernel, three tilings: 256 x 256, 256 x 192 or 256 x 128 per workgroup (four waves of 128 x 128 / 96 / 64, one
-// workgroup per compute unit, hand-laid-out K step); the launch rule below chooses the one whose tiles fit the
-// machine best.  Workgroup ids are remapped so that each XCD works on a compact
+// One kernel, three tilings: 256 x 256, 256 x 192 or 256 x 128 per workgroup (eight waves of 64 x 128 / 96 / 64, one
+// workgroup per compute unit, loads straight to LDS two K steps ahead); the launch rule below chooses the one whose tiles
+// fit the machine best.  Workgroup ids are remapped so that each XCD works on a compact
 // block of the tile grid (its L2 then holds the A and B panels that block shares).
 #include <stdint.h>
 #include <string.h>
@@ -26,7 +26,6 @@ namespace {
 using namespace mf;
 
 constexpr int BKK = 64;            // K step
-constexpr int KPITCH = 144;        // bytes per LDS row of a k-major tile: 64 k (128 bytes) + 16 pad
 
 struct GemmParams {
     const bf16_t* A;
@@ -54,224 +53,294 @@ __device__ __forceinline__ void tile_of(const GemmParams& gp, int& tm, int& tn) 
     tn = in / gsz;
 }
 
-// bytes of one operand tile in LDS: k-major [ROWS][64 k] (rows padded by 16 bytes) or [64 k][ROWS] (by 64)
-template <int ROWS, bool KMAJOR>
-constexpr int tile_bytes() { return KMAJOR ? ROWS * KPITCH : BKK * (2 * ROWS + 64); }
-// Row pitch of a tile stored [k][ROWS]: 64 bytes of padding put consecutive k rows 16 banks apart, so the four
-// k rows (32 bytes each per half-wave) that one transposing read touches fall into distinct banks.
-template <int ROWS>
-constexpr int tpitch() { return 2 * ROWS + 64; }
-
-// Global -> registers for one K step of one operand.  ROWS = tile extent along the operand's own index (m
-// or n).  k-major: ROWS rows of 8 vectors; otherwise 64 k-rows of ROWS / 8 vectors.  `origin` points at the
-// tile's first element of this K step (wave-uniform: scalar registers); a thread's vectors lie a fixed
-// number of rows apart, so one 32-bit byte offset per thread addresses them all.  MASK: vectors outside
-// rows_left x k_left are zeros (all extents are multiples of 8: a vector is inside or outside as a whole).
-template <int ROWS, bool KMAJOR>
-__device__ __forceinline__ uint32_t tile_voff(int64_t ld, int tid) {
-    constexpr int VPR = KMAJOR ? 8 : ROWS / 8;  // vectors per memory row of the tile
-    return (uint32_t)(tid / VPR) * (uint32_t)(ld * 2) + (uint32_t)(tid % VPR) * 16;
-}
-
-template <int ROWS, bool KMAJOR, bool MASK, int I0 = 0, int I1 = ROWS / 32>
-__device__ __forceinline__ void load_tile(const bf16_t* origin, int64_t ld, uint32_t voff, int rows_left, int k_left, int tid,
-                                          bf16x8 (&reg)[ROWS / 32]) {
-    constexpr int VPR = KMAJOR ? 8 : ROWS / 8;
-    constexpr int RSTEP = 256 / VPR;  // memory rows between a thread's consecutive vectors
-#pragma unroll
-    for (int i = I0; i < I1; ++i) {
-        bool in = true;
-        if (MASK) {
-            const int mrow = tid / VPR + RSTEP * i, mcol = (tid % VPR) * 8;  // memory row / first column of the vector
-            in = KMAJOR ? (mrow < rows_left && mcol < k_left) : (mrow < k_left && mcol < rows_left);
-        }
-        if (in) {
-            reg[i] = *(const bf16x8*)((const char*)origin + (size_t)i * RSTEP * (size_t)(ld * 2) + (size_t)voff);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) reg[i][e] = (__bf16)0.f;
-        }
-    }
-}
-
-// The same for a whole K step as a buffer access: the descriptor spans the memory rows of the step that exist, and of a
-// tile with the contraction index as the row index the threads outside its columns start beyond that span (their
-// offset, see edge_voff).  Whatever lies outside reads as zeros, without a branch: the tiles at the edges of the
-// matrices take the straight-line loop like all others (1905 x 10576 -> 2560: 279 -> 213 us).  Offsets stay below 2^31 for row strides up to MAX_LD.
+// Offsets into K steps stay below 2^31 for row strides up to this.
 constexpr int64_t MAX_LD = 1 << 22;
-template <int ROWS, bool KMAJOR>
-__device__ __forceinline__ uint32_t edge_voff(int64_t ld, int rows_left, int tid) {
-    return !KMAJOR && (tid % (ROWS / 8)) * 8 >= rows_left ? 0x80000000u : tile_voff<ROWS, KMAJOR>(ld, tid);
-}
-template <int ROWS, bool KMAJOR>
-__device__ __forceinline__ rsrc_t step_rows(const bf16_t* origin, int64_t ld, int rows_left) {
-    const int rows = rows_left < ROWS ? rows_left : ROWS;
-    const uint32_t bytes = KMAJOR ? (uint32_t)(rows - 1) * (uint32_t)(ld * 2) + 2 * BKK : (BKK - 1) * (uint32_t)(ld * 2) + 2 * ROWS;
-    return __builtin_amdgcn_make_buffer_rsrc((void*)origin, 0, bytes, 0x00020000);
-}
-template <int ROWS, bool KMAJOR, int I>
-__device__ __forceinline__ void load_step(rsrc_t r, int64_t ld, uint32_t voff, bf16x8 (&reg)[ROWS / 32]) {
-    constexpr int VPR = KMAJOR ? 8 : ROWS / 8;
-    static_assert(256 % VPR == 0, "a thread's vectors share a column");
-    reg[I] = rows_load(r, voff + (uint32_t)(I * (256 / VPR)) * (uint32_t)(ld * 2));
-}
+constexpr int GTHR = 512;
 
-template <int ROWS, bool KMAJOR, int I0 = 0, int I1 = ROWS / 32>
-__device__ __forceinline__ void store_tile(char* lds, int tid, const bf16x8 (&reg)[ROWS / 32]) {
-#pragma unroll
-    for (int i = I0; i < I1; ++i) {
-        const int v = tid + 256 * i;
-        if (KMAJOR) {
-            *(bf16x8*)(lds + (v >> 3) * KPITCH + (v & 7) * 16) = reg[i];
-        } else {
-            constexpr int VPR = ROWS / 8;
-            *(bf16x8*)(lds + (v / VPR) * tpitch<ROWS>() + (v % VPR) * 16) = reg[i];
-        }
-    }
-}
-
-// MFMA operand for rows r0 .. r0+31 of the tile, k = kk .. kk+15
-template <int ROWS, bool KMAJOR>
-__device__ __forceinline__ bf16x8 operand(const char* lds, int r0, int kk, int lane) {
-    if (KMAJOR) return *(const bf16x8*)(lds + (r0 + (lane & 31)) * KPITCH + (kk + 8 * (lane >> 5)) * 2);
-    return frag_tr(lds, tpitch<ROWS>(), kk, r0, lane);
-}
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // The MFMAs are issued with the B operand first, so an accumulator tile holds the transposed product: lane
-// -> row m = lane % 32 of C, registers 4q .. 4q+3 -> the four consecutive columns 8q + 4 (lane / 32) + 0..3.
+// -> row m = lane % 16 of C, its four registers -> the consecutive columns 4 (lane / 16) + 0..3.
 // Every lane thus stores 8 bytes (bf16) or 16 bytes (fp32) at a time.  `whole`: the workgroup's tile lies
 // inside C (no bounds checks; N is a multiple of 8, so a group of four columns is inside or outside as one).
-template <int WI, int WJ>
-__device__ __forceinline__ void store_acc(const GemmParams& gp, const f32x16 (&acc)[WI][WJ], int row0, int col0, int lane, bool whole) {
-    const int row_l = row0 + (lane & 31), col_l = col0 + (lane >> 5) * 4;
+// fp32 results (weight gradients): where they are added to what is there, the old values of four tiles are asked for
+// together, and those of the next four before these are stored.
+template <int WJ>
+__device__ __forceinline__ void store_acc_f32(const GemmParams& gp, const f32x4 (&acc)[4][2 * WJ], int row0, int col0, int lane, bool whole) {
+    const int row_l = row0 + (lane & 15), col_l = col0 + (lane >> 4) * 4;
+    auto at = [&](int i, int j) { return (f32x4*)((float*)gp.C + (int64_t)(row_l + i * 16) * gp.ldc + col_l + j * 16); };
+    auto in = [&](int i, int j) { return whole || (row_l + i * 16 < gp.M && col_l + j * 16 < gp.N); };
+    f32x4 old[2][4];
+    auto ask = [&](int j) {
 #pragma unroll
-    for (int i = 0; i < WI; ++i) {
-        const int row = row_l + i * 32;
-#pragma unroll
-        for (int j = 0; j < WJ; ++j) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int col = col_l + j * 32 + q * 8;
-                if (whole || (row < gp.M && col < gp.N)) {
-                    const int64_t o = (int64_t)row * gp.ldc + col;
-                    const f32x16& t = acc[i][j];
-                    if (gp.c_f32) {
-                        float4* c = (float4*)((float*)gp.C + o);
-                        float4 v = make_float4(t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]);
-                        if (gp.accumulate) {
-                            const float4 old = *c;
-                            v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
-                        }
-                        *c = v;
-                    } else {
-                        bf16x4 v;
-                        v[0] = (__bf16)t[4 * q]; v[1] = (__bf16)t[4 * q + 1]; v[2] = (__bf16)t[4 * q + 2]; v[3] = (__bf16)t[4 * q + 3];
-                        *(bf16x4*)((__bf16*)gp.C + o) = v;
-                    }
-                }
-            }
+        for (int i = 0; i < 4; ++i) {
+            old[j & 1][i] = (f32x4)(0.f);
+            if (gp.accumulate && in(i, j)) old[j & 1][i] = *at(i, j);
         }
+    };
+    ask(0);
+#pragma unroll
+    for (int j = 0; j < 2 * WJ; ++j) {
+        if (j + 1 < 2 * WJ) ask(j + 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (in(i, j)) *at(i, j) = acc[i][j] + old[j & 1][i];
     }
 }
 
-// 256 x 64 WJ tile, four waves of 128 x 32 WJ (WJ = 4: 4 x 4 MFMA tiles, the whole accumulator register file), one
-// workgroup per compute unit, two LDS buffers.  With a single wave per SIMD nothing else hides latency, so
-// the K step is laid out by hand as 16 units of WJ MFMAs (one A operand against the WJ B operands of
-// its k slice); behind each MFMA sit the LDS reads of later operands and (last eight units) one vector of
-// the next tile's LDS writes with the global load that refills its register for the tile after that.
-// Registers thus hold the tile two K steps ahead of the one being multiplied: a vector is written to LDS
-// in the second half of a step and its register is refilled at once, so that a load has a whole step of
-// MFMA time to arrive.
+// One operand tile of a K step in LDS: k-major [ROWS][64 k] (128 bytes a row) or [64 k][ROWS] (2 ROWS bytes a row), filled by
+// loads that go from memory straight to LDS: a wave's load puts 64 consecutive 16-byte pieces down, so there is no room for
+// padding.  Instead the pieces of a row are permuted -- which piece a lane fetches, not where it lands -- so that the rows
+// that one operand read touches fall into distinct banks:
+//   k-major: piece s of row r holds piece s ^ (r / 2 & 7) of the row (a read takes one of four pieces of sixteen rows;
+//   with r & 7 every read took twice as long),
+//   else: piece s of k row k holds piece s ^ 2 h(k), h = k % 4 + 4 (k / 8 % 2) (half a wave's transposing read takes 32 bytes
+//   of each of the k rows 0..3 and 8..11).
+template <int ROWS, bool KMAJOR>
+struct Tile {
+    static constexpr int PITCH = KMAJOR ? 2 * BKK : 2 * ROWS;
+    static constexpr int BYTES = 2 * BKK * ROWS;
+    static constexpr int VPR = PITCH / 16;                 // pieces of a row
+    static constexpr int LOADS = BYTES / (16 * GTHR);      // per thread and K step
+    static constexpr int RSTEP = GTHR / VPR;               // memory rows between a thread's consecutive pieces
+    static __device__ __forceinline__ int row(int tid) { return tid / VPR; }                    // of a thread's first piece
+    static __device__ __forceinline__ int piece(int tid) {                                      // in memory
+        const int r = tid / VPR;
+        return (tid % VPR) ^ (KMAJOR ? r / 2 & 7 : 2 * (r & 3) + (r & 8));
+    }
+    static_assert(RSTEP % 16 == 0 && VPR >= 8 && (KMAJOR || VPR == 16 || VPR == 32), "the permutation is the same for all of a thread's pieces");
+
+    // Offset of a thread's first piece inside a K step.  Row-index-k tiles: threads outside the columns that exist start
+    // beyond the descriptor's span (what they would fetch lands in columns that are not stored).
+    static __device__ __forceinline__ uint32_t voff(int64_t ld, int left, int tid) {
+        return !KMAJOR && piece(tid) * 8 >= left ? 0x80000000u : (uint32_t)row(tid) * (uint32_t)(ld * 2) + (uint32_t)piece(tid) * 16;
+    }
+    // The memory rows of a whole K step that exist: whatever lies outside is not fetched, without a branch.
+    static __device__ __forceinline__ u32x4 span(const bf16_t* origin, int64_t ld, int left) {
+        const int rows = left < ROWS ? left : ROWS;
+        const uint32_t bytes = KMAJOR ? (uint32_t)(rows - 1) * (uint32_t)(ld * 2) + 2 * BKK : (BKK - 1) * (uint32_t)(ld * 2) + 2 * ROWS;
+        const uint64_t a = (uint64_t)origin;
+        u32x4 r;
+        r[0] = (uint32_t)a;
+        r[1] = (uint32_t)(a >> 32) & 0xffffu;
+        r[2] = bytes;
+        r[3] = 0x00020000u;
+        return r;
+    }
+    // Piece I of a K step, memory -> LDS.  The wave's 64 pieces land at m0 in lane order.  As assembly because the compiler
+    // drains every load in flight to LDS before each LDS read it can see; there is no output register, and the step waits for
+    // the loads itself.
+    template <int I>
+    static __device__ __forceinline__ void load(u32x4 r, int64_t ld, uint32_t voff, uint32_t lds, int w) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                     :: "s"(lds + (uint32_t)(I * 16 * GTHR + w * 1024)), "v"(voff + (uint32_t)(I * RSTEP) * (uint32_t)(ld * 2)), "s"(r)
+                     : "memory", "m0");
+    }
+    // The last, partial K step through registers: k beyond the contraction's end has to read as zero.
+    static __device__ __forceinline__ void load_part(const bf16_t* origin, int64_t ld, int left, int k_left, char* lds, int tid) {
+        bf16x8 v[LOADS];
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int r = row(tid) + RSTEP * i, c = piece(tid) * 8;
+            const bool in = KMAJOR ? (r < left && c < k_left) : (r < k_left && c < left);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[i][e] = (__bf16)0.f;
+            if (in) v[i] = *(const bf16x8*)(origin + (int64_t)r * ld + c);
+        }
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) *(bf16x8*)(lds + i * 16 * GTHR + tid * 16) = v[i];
+    }
+    // MFMA operand: rows r0 .. r0+15 (r0 a multiple of 16), k = 32 ks .. 32 ks+31; lane -> row lane % 16, k 8 (lane / 16) .. + 7
+    static __device__ __forceinline__ bf16x8 operand(const char* lds, int r0, int ks, int lane) {
+        const int g = lane >> 4, r = lane & 15;
+        if (KMAJOR) return *(const bf16x8*)(lds + (r0 + r) * PITCH + (((g ^ (r >> 1)) << 4) ^ (ks << 6)));
+        const char* p = lds + (32 * ks + 8 * g + (r >> 2)) * PITCH + (((r0 * 2) ^ (((r >> 2) + 4 * (g & 1)) << 5)) + 8 * (r & 3));  // see frag_tr
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * PITCH));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+};
+
+// 256 x 64 WJ tile, eight waves of 64 x 32 WJ, one workgroup per compute unit.  Two waves share a SIMD: one reads its
+// operands while the other multiplies.  The MFMAs are 16 x 16 x 32: the chip runs at its power limit here, and on random
+// operands in registers they sustain 2075 TFLOP/s where 32 x 32 x 16 sustains 1846 (half the accumulator traffic; on zeros
+// both reach 2450-2470).  A K step is WJ phases of sixteen: all of the wave's A operands (64 rows, 64 k)
+// against 32 columns of B; during a phase the next 32 columns are read, during the last one the A operands of the next step,
+// each right behind its last use.  So A's buffer is free from the second phase of its step on and B's from the last, and with
+// two buffers for A and three for B (all of the LDS at WJ = 4) a load is issued one and a half to two steps before its data
+// are read: the trip through the L2 under load takes longer than a step of MFMAs (0.93 us).  With both loaded one step ahead
+// the same loop ran at 0.68 of what it reaches without loads (8192 x 8192 x 8192, zeros: 1562 against 2299 TFLOP/s).
+// Measured, random operands, against the four waves of 128 x 128 with operands staged through registers that this replaces:
+// 8192 x 8192 x 8192 1269 -> 1498 TFLOP/s, 4096 x 2560 -> 10576 876 -> 1047 (672 tiles in three rounds, power-limited clock).
+// Barriers: X in front of the second phase (every wave has its A operands: A(t + 2) may come in), Y in front of the last
+// (every wave has its B operands and its loads of step t + 1 have landed: B(t + 3) may come in).  At WJ = 2 the two are one,
+// and A has three buffers as well.
 struct BigCtx {
     const bf16_t* a_org;  // tile origin at k = 0
     const bf16_t* b_org;
     int64_t lda, ldb, a_kstep, b_kstep;
-    uint32_t va, vb;      // offsets of the thread's vectors in a K step (buffer accesses)
-    int rows_a, rows_b, K;  // extents left from the tile origin (masks)
-    int tid, lane, wm, wn;
+    uint32_t va, vb;      // offsets of the thread's pieces in a K step
+    int rows_a, rows_b, K;  // extents left from the tile origin
+    int tid, lane, w, wm, wn;
 };
 
-// One K step.  STEADY: the registers hold a next tile, there is one after it, and both are whole K steps --
-// straight-line code (no branches: the compiler then counts outstanding loads exactly instead of draining
-// them at every join).  Otherwise the same step with run-time conditions, for the last steps.
-template <bool AK, bool BK, int WJ, bool STEADY>
-__device__ __forceinline__ void big_step(const BigCtx& cx, f32x16 (&acc)[4][WJ], bf16x8 (&ra)[8], bf16x8 (&rb)[2 * WJ], const char* As,
-                                         char* An, int k0) {
-    constexpr int BM = 256, BN = 64 * WJ;
-    constexpr int A_BYTES = tile_bytes<BM, AK>();
-    const char* Bs = As + A_BYTES;
-    char* Bn = An + A_BYTES;
-    const int k2 = k0 + 2 * BKK;
-    const bool more = STEADY || k0 + BKK < cx.K;
-    const bool more2 = STEADY || k2 < cx.K;
-    const bf16_t* ao = cx.a_org + (int64_t)k2 * cx.a_kstep;
-    const bf16_t* bo = cx.b_org + (int64_t)k2 * cx.b_kstep;
-    const int lane = cx.lane, tid = cx.tid;
-    rsrc_t sa, sb;
-    uint32_t va = cx.va, vb = cx.vb;
-    if (STEADY) {
-        // the offsets of the other vectors are added up here: kept over the loop they would cost 16 registers
-        asm volatile("" : "+v"(va), "+v"(vb));
-        sa = step_rows<BM, AK>(ao, cx.lda, cx.rows_a);
-        sb = step_rows<BN, BK>(bo, cx.ldb, cx.rows_b);
-    }
-    bf16x8 aq[2], bq[2][WJ];
-    aq[0] = operand<BM, AK>(As, cx.wm * 128, 0, lane);
-#pragma unroll
-    for (int j = 0; j < WJ; ++j) bq[0][j] = operand<BN, BK>(Bs, cx.wn * 32 * WJ + j * 32, 0, lane);
-    // An MFMA keeps the matrix pipe busy for 32 cycles but takes only a few to issue: every memory
-    // instruction is placed right behind an MFMA, so that it issues in that MFMA's shadow.
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        const int kk = u >> 2, i = u & 3;
-#pragma unroll
-        for (int j = 0; j < WJ; ++j) {
-            acc[i][j] = mfma(bq[kk & 1][j], aq[u & 1], acc[i][j]);
-            // operand reads: the next unit's A operand, and over unit 1 of a k slice the next slice's B operands
-            if (j == 0 && u + 1 < 16) aq[(u + 1) & 1] = operand<BM, AK>(As, cx.wm * 128 + ((u + 1) & 3) * 32, ((u + 1) >> 2) * 16, lane);
-            if (i == 1 && kk < 3) bq[(kk + 1) & 1][j] = operand<BN, BK>(Bs, cx.wn * 32 * WJ + j * 32, (kk + 1) * 16, lane);
-            if (STEADY) {
-                // units 8..15: behind MFMA 0 a vector of A, behind a later one a vector of B (while there are any) goes to LDS and its register is refilled
-#define GEMM_PART(V)                                                                              \
-    if (u == 8 + V && j == 0) {                                                                   \
-        store_tile<BM, AK, V, V + 1>(An, tid, ra);                                                \
-        load_step<BM, AK, V>(sa, cx.lda, va, ra);                                              \
-    }                                                                                             \
-    if constexpr (V < 2 * WJ)                                                                     \
-        if (u == 8 + V && j == WJ / 2) {                                                          \
-            store_tile<BN, BK, V, V + 1>(Bn, tid, rb);                                            \
-            load_step<BN, BK, V>(sb, cx.ldb, vb, rb);                                          \
-        }
-                GEMM_PART(0) GEMM_PART(1) GEMM_PART(2) GEMM_PART(3) GEMM_PART(4) GEMM_PART(5) GEMM_PART(6) GEMM_PART(7)
-#undef GEMM_PART
-            } else if (u == 8 && j == 0 && more) {
-                store_tile<BM, AK>(An, tid, ra);
-                store_tile<BN, BK>(Bn, tid, rb);
-                if (more2) {
-                    load_tile<BM, AK, true>(ao, cx.lda, tile_voff<BM, AK>(cx.lda, tid), cx.rows_a, cx.K - k2, tid, ra);
-                    load_tile<BN, BK, true>(bo, cx.ldb, tile_voff<BN, BK>(cx.ldb, tid), cx.rows_b, cx.K - k2, tid, rb);
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
+template <int N>
+__device__ __forceinline__ void wait_and_meet() {  // at most N loads to LDS still under way; every operand read done
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 template <bool AK, bool BK, int WJ>
-__global__ __launch_bounds__(256, 1) void k_gemm_big(GemmParams gp) {
+struct Big {
+    typedef Tile<256, AK> TA;
+    typedef Tile<64 * WJ, BK> TB;
+    static constexpr int NA = WJ == 2 ? 3 : 2, NB = 3;     // buffers
+    static constexpr int LDS = NA * TA::BYTES + NB * TB::BYTES;
+    static constexpr int SETS = WJ == 3 ? 3 : 2;           // of B operands: a step starts with set 0
+    static constexpr int AHEAD_A = NA, AHEAD_B = NB;       // steps between a load and its use
+
+    char* lds;
+    uint32_t lds0;
+    int a0, b0;  // buffers of the current step
+    f32x4 acc[4][2 * WJ];
+    bf16x8 a[4][2], b[SETS][2][2];
+
+    static __device__ __forceinline__ int next(int buf, int n) { return buf + 1 == n ? 0 : buf + 1; }
+    __device__ __forceinline__ void read_a(const BigCtx& cx, int buf, int i, int ks) {
+        a[i][ks] = TA::operand(lds + buf * TA::BYTES, cx.wm * 64 + i * 16, ks, cx.lane);
+    }
+    // operand q of phase j: k half q / 2, columns 16 (q % 2) ..
+    __device__ __forceinline__ void read_b(const BigCtx& cx, int buf, int set, int j, int q) {
+        b[set][q & 1][q >> 1] = TB::operand(lds + NA * TA::BYTES + buf * TB::BYTES, cx.wn * 32 * WJ + j * 32 + (q & 1) * 16, q >> 1, cx.lane);
+    }
+    static __device__ __forceinline__ u32x4 span_a(const BigCtx& cx, int k0) { return TA::span(cx.a_org + (int64_t)k0 * cx.a_kstep, cx.lda, cx.rows_a); }
+    static __device__ __forceinline__ u32x4 span_b(const BigCtx& cx, int k0) { return TB::span(cx.b_org + (int64_t)k0 * cx.b_kstep, cx.ldb, cx.rows_b); }
+    template <int I>
+    __device__ __forceinline__ void load_a(const BigCtx& cx, u32x4 s, int buf) {
+        TA::template load<I>(s, cx.lda, cx.va, lds0 + buf * TA::BYTES, cx.w);
+    }
+    template <int I>
+    __device__ __forceinline__ void load_b(const BigCtx& cx, u32x4 s, int buf) {
+        if constexpr (I < TB::LOADS) TB::template load<I>(s, cx.ldb, cx.vb, lds0 + NA * TA::BYTES + buf * TB::BYTES, cx.w);
+    }
+    // A whole or partial K step at k0, or nothing beyond the end.
+    __device__ __forceinline__ void load_step_a(const BigCtx& cx, int k0, int buf, bool direct) {
+        if (k0 >= cx.K) return;
+        if (direct && k0 + BKK <= cx.K) {
+            const u32x4 s = span_a(cx, k0);
+            load_a<0>(cx, s, buf); load_a<1>(cx, s, buf); load_a<2>(cx, s, buf); load_a<3>(cx, s, buf);
+        } else {
+            TA::load_part(cx.a_org + (int64_t)k0 * cx.a_kstep, cx.lda, cx.rows_a, cx.K - k0, lds + buf * TA::BYTES, cx.tid);
+        }
+    }
+    __device__ __forceinline__ void load_step_b(const BigCtx& cx, int k0, int buf, bool direct) {
+        if (k0 >= cx.K) return;
+        if (direct && k0 + BKK <= cx.K) {
+            const u32x4 s = span_b(cx, k0);
+            load_b<0>(cx, s, buf); load_b<1>(cx, s, buf); load_b<2>(cx, s, buf); load_b<3>(cx, s, buf);
+        } else {
+            TB::load_part(cx.b_org + (int64_t)k0 * cx.b_kstep, cx.ldb, cx.rows_b, cx.K - k0, lds + NA * TA::BYTES + buf * TB::BYTES, cx.tid);
+        }
+    }
+
+    // Fills the buffers and reads the first operands.
+    __device__ __forceinline__ void start(const BigCtx& cx, bool direct) {
+        a0 = b0 = 0;
+        load_step_a(cx, 0, 0, direct);
+        load_step_b(cx, 0, 0, direct);
+        load_step_a(cx, BKK, 1, direct);
+        load_step_b(cx, BKK, 1, direct);
+        if (NA == 3) load_step_a(cx, 2 * BKK, 2, direct);
+        load_step_b(cx, 2 * BKK, 2, direct);
+        if (direct && 3 * BKK <= cx.K) wait_and_meet<(NA - 1) * TA::LOADS + 2 * TB::LOADS>();
+        else wait_and_meet<0>();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            read_b(cx, 0, 0, 0, q);
+            read_a(cx, 0, q, 0);
+            read_a(cx, 0, q, 1);
+        }
+    }
+
+    // One K step.  STEADY: the steps whose loads it issues exist and are whole; straight-line code.
+    template <bool STEADY>
+    __device__ __forceinline__ void step(const BigCtx& cx, int k0, bool direct) {
+        const bool more = STEADY || k0 + BKK < cx.K;
+        const int a1 = next(a0, NA), b1 = next(b0, NB);
+        u32x4 sa, sb;
+        if (STEADY) {
+            sa = span_a(cx, k0 + AHEAD_A * BKK);
+            sb = span_b(cx, k0 + AHEAD_B * BKK);
+        }
+#pragma unroll
+        for (int j = 0; j < WJ; ++j) {
+            constexpr bool ONE = WJ == 2;
+            const bool last = j == WJ - 1, first_free = j == 1;
+            if (first_free && !ONE) {  // X
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+                if (!STEADY) load_step_a(cx, k0 + AHEAD_A * BKK, a0, direct);
+            }
+            if (last) {                // Y
+                if (STEADY) wait_and_meet<TA::LOADS + TB::LOADS>();
+                else wait_and_meet<0>();
+                if (!STEADY) {
+                    if (ONE) load_step_a(cx, k0 + AHEAD_A * BKK, a0, direct);
+                    load_step_b(cx, k0 + AHEAD_B * BKK, b0, direct);
+                }
+            }
+            // the last phase issues the most besides its MFMAs: the wave that is in it goes first (2 % of the product)
+            if (j == 0) __builtin_amdgcn_s_setprio(0);
+            if (last) __builtin_amdgcn_s_setprio(1);
+            const int set = j % SETS, nset = last ? 0 : (j + 1) % SETS;
+#pragma unroll
+            for (int m = 0; m < 16; ++m) {
+                const int ks = m >> 3, i = (m >> 1) & 3, jj = m & 1;
+                acc[i][2 * j + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[set][jj][ks], a[i][ks], acc[i][2 * j + jj], 0, 0, 0);
+                if (m < 8 && (m & 1) == 0 && (!last || more)) read_b(cx, last ? b1 : b0, nset, last ? 0 : j + 1, m >> 1);
+                if (last && more && jj == 1) read_a(cx, a1, i, ks);  // its last use is the MFMA above
+                if (STEADY && first_free) {
+                    if (m == 1) load_a<0>(cx, sa, a0);
+                    if (m == 5) load_a<1>(cx, sa, a0);
+                    if (m == 9) load_a<2>(cx, sa, a0);
+                    if (m == 13) load_a<3>(cx, sa, a0);
+                }
+                if (STEADY && last) {
+                    if (m == 0) load_b<0>(cx, sb, b0);
+                    if (m == 4) load_b<1>(cx, sb, b0);
+                    if (m == 8) load_b<2>(cx, sb, b0);
+                    if (m == 12) load_b<3>(cx, sb, b0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        a0 = a1;
+        b0 = b1;
+    }
+};
+
+template <bool AK, bool BK, int WJ>
+__global__ __launch_bounds__(GTHR, 1) void k_gemm_big(GemmParams gp) {
     constexpr int BM = 256, BN = 64 * WJ;
-    constexpr int A_BYTES = tile_bytes<BM, AK>(), B_BYTES = tile_bytes<BN, BK>();
-    extern __shared__ __attribute__((aligned(16))) char lds[];  // 2 x (A tile, B tile)
-    const int tid = threadIdx.x, w = tid >> 6;
+    extern __shared__ __attribute__((aligned(1024))) char lds[];  // the K steps in flight; at the end the patches of the result
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     int tm, tn;
     tile_of(gp, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
 
-    f32x16 acc[4][WJ];
+    typedef Big<AK, BK, WJ> Gemm;
+    Gemm G;
+    f32x4 (&acc)[4][2 * WJ] = G.acc;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < WJ; ++j) acc[i][j] = zero16();
+        for (int j = 0; j < 2 * WJ; ++j) acc[i][j] = (f32x4)(0.f);
+    G.lds = lds;
+    G.lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
     const bool interior = m0 + BM <= gp.M && n0 + BN <= gp.N;
     BigCtx cx;
@@ -283,81 +352,42 @@ __global__ __launch_bounds__(256, 1) void k_gemm_big(GemmParams gp) {
     cx.b_kstep = BK ? 1 : gp.ldb;
     cx.rows_a = gp.M - m0;
     cx.rows_b = gp.N - n0;
-    cx.va = edge_voff<BM, AK>(gp.lda, cx.rows_a, tid);
-    cx.vb = edge_voff<BN, BK>(gp.ldb, cx.rows_b, tid);
+    cx.va = Gemm::TA::voff(gp.lda, cx.rows_a, tid);
+    cx.vb = Gemm::TB::voff(gp.ldb, cx.rows_b, tid);
     cx.K = gp.K;
     cx.tid = tid;
     cx.lane = tid & 63;
+    cx.w = w;
     cx.wm = w >> 1;
     cx.wn = w & 1;
     const int lane = cx.lane, wm = cx.wm, wn = cx.wn;
+    // strides beyond what 32-bit offsets reach: every step goes through registers
+    const bool direct = gp.lda <= MAX_LD && gp.ldb <= MAX_LD;
+    G.start(cx, direct);
+    int k0 = 0;
+    if (direct)
+        for (; k0 + (Gemm::AHEAD_B + 1) * BKK <= gp.K; k0 += BKK) G.template step<true>(cx, k0, true);
+    for (; k0 < gp.K; k0 += BKK) G.template step<false>(cx, k0, direct);
 
-    bf16x8 ra[8], rb[2 * WJ];
-    const bool steady = 3 * BKK <= gp.K && gp.lda <= MAX_LD && gp.ldb <= MAX_LD;  // at least one step of the straight-line loop
-    if (steady) {
-        // the same order of loads (A and B vector by vector) as inside the loop, so that the count of
-        // loads still outstanding at the loop's first LDS write is the same on entry and on every repeat
-#define GEMM_PRO(V)                                                       \
-    load_step<BM, AK, V>(sa, gp.lda, cx.va, ra);                          \
-    if constexpr (V < 2 * WJ) load_step<BN, BK, V>(sb, gp.ldb, cx.vb, rb);
-        rsrc_t sa = step_rows<BM, AK>(cx.a_org, gp.lda, cx.rows_a), sb = step_rows<BN, BK>(cx.b_org, gp.ldb, cx.rows_b);
-        GEMM_PRO(0) GEMM_PRO(1) GEMM_PRO(2) GEMM_PRO(3) GEMM_PRO(4) GEMM_PRO(5) GEMM_PRO(6) GEMM_PRO(7)
-        store_tile<BM, AK>(lds, tid, ra);
-        store_tile<BN, BK>(lds + A_BYTES, tid, rb);
-        sa = step_rows<BM, AK>(cx.a_org + (int64_t)BKK * cx.a_kstep, gp.lda, cx.rows_a);
-        sb = step_rows<BN, BK>(cx.b_org + (int64_t)BKK * cx.b_kstep, gp.ldb, cx.rows_b);
-        GEMM_PRO(0) GEMM_PRO(1) GEMM_PRO(2) GEMM_PRO(3) GEMM_PRO(4) GEMM_PRO(5) GEMM_PRO(6) GEMM_PRO(7)
-#undef GEMM_PRO
-    } else {
-        load_tile<BM, AK, true>(cx.a_org, gp.lda, tile_voff<BM, AK>(gp.lda, tid), cx.rows_a, gp.K, tid, ra);
-        load_tile<BN, BK, true>(cx.b_org, gp.ldb, tile_voff<BN, BK>(gp.ldb, tid), cx.rows_b, gp.K, tid, rb);
-        store_tile<BM, AK>(lds, tid, ra);
-        store_tile<BN, BK>(lds + A_BYTES, tid, rb);
-        if (BKK < gp.K) {
-            load_tile<BM, AK, true>(cx.a_org + (int64_t)BKK * cx.a_kstep, gp.lda, tile_voff<BM, AK>(gp.lda, tid), cx.rows_a, gp.K - BKK, tid, ra);
-            load_tile<BN, BK, true>(cx.b_org + (int64_t)BKK * cx.b_kstep, gp.ldb, tile_voff<BN, BK>(gp.ldb, tid), cx.rows_b, gp.K - BKK, tid, rb);
-        }
-    }
-    __syncthreads();
-    int cur = 0, k0 = 0;
-    if (steady) {  // steps whose next two tiles are whole
-        for (; k0 + 3 * BKK <= gp.K; k0 += BKK) {
-            big_step<AK, BK, WJ, true>(cx, acc, ra, rb, lds + cur * (A_BYTES + B_BYTES), lds + (cur ^ 1) * (A_BYTES + B_BYTES), k0);
-            cur ^= 1;
-            __syncthreads();
-        }
-    }
-    for (; k0 < gp.K; k0 += BKK) {
-        big_step<AK, BK, WJ, false>(cx, acc, ra, rb, lds + cur * (A_BYTES + B_BYTES), lds + (cur ^ 1) * (A_BYTES + B_BYTES), k0);
-        cur ^= 1;
-        __syncthreads();
-    }
-
-    if (gp.c_f32) {  // weight gradients: K is the token count, the epilogue does not matter
-        store_acc<4, WJ>(gp, acc, m0 + wm * 128, n0 + wn * 32 * WJ, lane, interior);
+    if (gp.c_f32) {
+        store_acc_f32<WJ>(gp, acc, m0 + wm * 64, n0 + wn * 32 * WJ, lane, interior);
         return;
     }
-    // bf16 result: through LDS (free now; every wave has left the K loop behind the last barrier), so that
+    // bf16 result: through LDS (every wave has left its last buffer behind the barrier), so that
     // a store instruction writes whole row pieces (256 bytes at WJ = 4) instead of 32 scattered 16-byte ones.  Each wave
-    // transposes its own 128 x 32 WJ tile in a private patch: lane -> row lane % 32, four consecutive columns
-    // per register group (see store_acc) on the way in, 16-byte vectors of a row on the way out.
+    // transposes its own 64 x 32 WJ tile in a private patch: lane -> row lane % 16, four consecutive columns
+    // per tile (see store_acc_f32) on the way in, 16-byte vectors of a row on the way out.
+    __syncthreads();
     constexpr int VPR = 4 * WJ, EPITCH = 16 * VPR + 16;  // vectors per row
-    static_assert(4 * 128 * EPITCH <= 2 * (A_BYTES + B_BYTES), "");
-    char* patch = lds + w * (128 * EPITCH);
+    char* patch = lds + w * (64 * EPITCH);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < WJ; ++j)
+        for (int j = 0; j < 2 * WJ; ++j)
+            *(bf16x4*)(patch + (i * 16 + (lane & 15)) * EPITCH + (j * 16 + (lane >> 4) * 4) * 2) = __builtin_convertvector(acc[i][j], bf16x4);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x16& t = acc[i][j];
-                bf16x4 v;
-                v[0] = (__bf16)t[4 * q]; v[1] = (__bf16)t[4 * q + 1]; v[2] = (__bf16)t[4 * q + 2]; v[3] = (__bf16)t[4 * q + 3];
-                *(bf16x4*)(patch + (i * 32 + (lane & 31)) * EPITCH + (j * 32 + q * 8 + (lane >> 5) * 4) * 2) = v;
-            }
-#pragma unroll 8
-    for (int it = 0; it < 2 * VPR; ++it) {
-        const int v = it * 64 + lane, r = v / VPR, c = v % VPR, row = m0 + wm * 128 + r, col = n0 + wn * 32 * WJ + c * 8;
+    for (int it = 0; it < VPR; ++it) {
+        const int v = it * 64 + lane, r = v / VPR, c = v % VPR, row = m0 + wm * 64 + r, col = n0 + wn * 32 * WJ + c * 8;
         const bf16x8 o = *(const bf16x8*)(patch + r * EPITCH + c * 16);
         if (interior || (row < gp.M && col < gp.N)) *(bf16x8*)((__bf16*)gp.C + (int64_t)row * gp.ldc + col) = o;
     }
@@ -367,7 +397,7 @@ bool ok_ptr(const void* p) { return p && ((uintptr_t)p & 15) == 0; }
 
 template <bool AK, bool BK, int WJ>
 hipError_t launch_big(GemmParams gp, hipStream_t st) {
-    constexpr int BN = 64 * WJ, LDS = 2 * (tile_bytes<256, AK>() + tile_bytes<BN, BK>());
+    constexpr int BN = 64 * WJ, PATCHES = 8 * 64 * (64 * WJ + 16), LDS = Big<AK, BK, WJ>::LDS > PATCHES ? Big<AK, BK, WJ>::LDS : PATCHES;
     static bool raised[64];  // per device: the kernel uses more dynamic LDS than the default limit
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
@@ -378,48 +408,53 @@ hipError_t launch_big(GemmParams gp, hipStream_t st) {
     }
     gp.tiles_m = (gp.M + 255) / 256;
     gp.tiles_n = (gp.N + BN - 1) / BN;
-    hipLaunchKernelGGL((k_gemm_big<AK, BK, WJ>), dim3(gp.tiles_m * gp.tiles_n), dim3(256), LDS, st, gp);
+    hipLaunchKernelGGL((k_gemm_big<AK, BK, WJ>), dim3(gp.tiles_m * gp.tiles_n), dim3(GTHR), LDS, st, gp);
     return hipGetLastError();
 }
 
 // Which tile width (64 WJ columns).  A compute unit holds one workgroup, so a product takes ceil(tiles / 256) rounds, and
 // a round with narrower tiles is cheaper, though by less than its share of the arithmetic (more LDS and cache traffic per
-// MFMA).  Cost of a round against 256 columns, measured over 200 ... 16384 rows at widths 768 ... 2560: forward product
-// 0.81-0.88 at 192 columns and 0.66-0.86 (one round) / 0.69-0.74 (several) at 128; the gradients' products 0.68-0.90 at 128.
-// What it gives (us, at 256 columns -> chosen): 4096 x 5120 -> 2560: 114 -> 100 (224 tiles of 192 instead of 160 of 256);
-// 1905 x 2560 -> 10576: 127 -> 105; 1905 x 5120 -> 2560: 98 -> 86; 600 x 1024 -> 4384: 28 -> 21.
+// MFMA).  Cost of a round against 256 columns, measured over 100 ... 16384 rows at widths 768 ... 2560: forward product
+// 0.82 at 192 columns and 0.61-0.71 at 128.
+// What it gives (us at 128 / 192 / 256 columns): 4096 x 5120 -> 2560: 117 / 84 / 92; 1905 x 2560 -> 10576: 97 / 90 / 105;
+// 1905 x 5120 -> 2560: 56 / 72 / 87; 600 x 1024 -> 4384: 16 / 20 / 23.
 constexpr int64_t UNITS = 256;
 int64_t tile_count(const GemmParams& gp, int wj) { return (int64_t)((gp.M + 255) / 256) * ((gp.N + 64 * wj - 1) / (64 * wj)); }
-int64_t tile_cost(const GemmParams& gp, int percent) { return (int64_t)((gp.K + BKK - 1) / BKK) * percent; }  // of one tile
-constexpr int FWD_PCT[5] = {0, 0, 72, 83, 100}, BWD_PCT[5] = {0, 0, 85, 0, 100};  // by WJ
+constexpr int WIDTH_PCT[5] = {0, 0, 68, 83, 100};  // of a K step, by WJ
 
 int forward_width(const GemmParams& gp) {
     int best = 4;
     int64_t t = INT64_MAX;
     for (int wj = 4; wj >= 2; --wj) {
-        const int64_t c = (tile_count(gp, wj) + UNITS - 1) / UNITS * FWD_PCT[wj];
+        const int64_t c = (tile_count(gp, wj) + UNITS - 1) / UNITS * WIDTH_PCT[wj];
         if (c < t) t = c, best = wj;
     }
     return best;
 }
 
-// Widths of the gradients' products: 4 or 2 (192 columns do not divide among the threads where the contraction index is the
-// row index).  Side by side they fill the machine together: while all tiles are resident at once the longer chain counts;
-// else the work spread over the machine plus half a chain of ragged end, and no less than a short tile in front of a
-// long one.  2560 <-> 10576, us for both (256 columns for all -> chosen): 200 rows 220 -> 188; 4096 rows stay at 256 columns
-// (417; all at 128: 563); 1024 <-> 4384, 4096 rows: all at 256 116, all at 128 (272 tiles) 167, chosen as here 116.
+// Widths of the gradients' products: 4 or 2 (rows of 192 columns do not permute by an exclusive or, see Tile).  A tile takes
+// its K steps and what surrounds them: about four steps' time, and twenty where fp32 results are added to (256 x 256 of them:
+// 512 KB in and out for every compute unit at once), half of that at 128 columns.  Side by side the two products fill the
+// machine together: while all tiles are resident at once the longer chain counts; else the work spread over the machine plus
+// two fifths of a chain of ragged end, and no less than a short tile in front of a long one.  Over six pairs of widths from
+// 768 to 10576 and 100 ... 16384 rows the rule is 1.4 % off the best of the four combinations (6 % with the K steps alone).
+// 2560 <-> 10576, us for (256, 256), chosen: 200 rows 196, 139; 4096 rows 389, 389; 1024 <-> 4384, 4096 rows 113, 96.
+int64_t tile_cost(const GemmParams& gp, int wj) {
+    const int64_t around = gp.c_f32 ? (wj == 4 ? 2000 : 1100) : (wj == 4 ? 400 : 200);
+    return (int64_t)((gp.K + BKK - 1) / BKK) * (wj == 4 ? 100 : 66) + around;
+}
 void backward_widths(const GemmParams* dx, const GemmParams* dw, bool together, int& wx, int& ww) {
     int64_t best = INT64_MAX;
     wx = ww = 4;
     for (int a = 4; a >= 2; a -= 2)
         for (int b = 4; b >= 2; b -= 2) {
-            const int64_t ta = dx ? tile_count(*dx, a) : 0, ca = dx ? tile_cost(*dx, BWD_PCT[a]) : 0;
-            const int64_t tb = dw ? tile_count(*dw, b) : 0, cb = dw ? tile_cost(*dw, BWD_PCT[b]) : 0;
+            const int64_t ta = dx ? tile_count(*dx, a) : 0, ca = dx ? tile_cost(*dx, a) : 0;
+            const int64_t tb = dw ? tile_count(*dw, b) : 0, cb = dw ? tile_cost(*dw, b) : 0;
             int64_t t;
             if (!together) {
                 t = (ta + UNITS - 1) / UNITS * ca + (tb + UNITS - 1) / UNITS * cb;
             } else {
-                const int64_t longer = ca > cb ? ca : cb, spread = (ta * ca + tb * cb) / UNITS + longer / 2;
+                const int64_t longer = ca > cb ? ca : cb, spread = (ta * ca + tb * cb) / UNITS + longer * 2 / 5;
                 t = ta + tb <= UNITS ? longer : (spread > ca + cb ? spread : ca + cb);
             }
             if (t < best) best = t, wx = a, ww = b;
