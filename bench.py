@@ -30,7 +30,6 @@ def kernel_models(cfg, tokens_per_launch, generic=False):
     element size e), S = H*P*N*2/Q (chunk states, bf16 in memory on the matrix-core path), R = 4H (one
     fp32 per-(token, head) array), b = G*N*e (B or C), g = G*Q*e (one row of the Q x Q matrix G):
       chunk_state   2NP*H   | x, cum, w, B -> states                      X + 2R + b + S
-      cb            2QN*G   | B, C -> G and its transpose                 2b + 2g
       chunk_out  (2QP+2NP)H | x, states, G, C, cum, dt -> y               2X + S + g + b + 2R
       dstate_local  4NP*H   | x, dy, cum, w, B, C -> states, local adj.   2X + 2R + 2b + 2S
       bwd_main   (2QP+2NP)H | dy, x, adjoints, G^T, B, cum, dt -> dx + 3 scalar rows   3X + S + g + b + 5R
@@ -38,7 +37,7 @@ def kernel_models(cfg, tokens_per_launch, generic=False):
       dBC           4NP*H   | x, dy, states, adjoints, cum, w, B, C -> dB/dC state terms (fp32), two dot rows
                                                                           2X + 2S + 2R + 2b + 2*G*N*4 + 2R
       final_ddt     4QN*G   | dG, B, C, state terms, scalar rows -> dB, dC, ddt   g + 4b + 2*G*N*4 + 6R + H*e
-      bwd_trio = bwd_main + dG + dBC as one launch (chunk 256): flop add up; x and dY count once
+      bwd_trio = bwd_main + dG + dBC as one launch (chunks of 128 and 256): flop add up; x and dY count once
     The shape-generic kernels run the same steps in fewer launches, states and scores in fp32: chunk_state = scores and
     chunk states (in the backward pass the local adjoints too: the mean of the two launches is given), bwd_main = dx, dG
     and the state terms, dBC = dB, dC and ddt.
@@ -55,21 +54,20 @@ def kernel_models(cfg, tokens_per_launch, generic=False):
     S, S4 = H * P * N * 2 / Q, H * P * N * 4 / Q
     st = P * N * H / Q
     m = {
-        "mfma_chunk_state": (2 * N * P * H, X + 2 * R + b + S), "mfma_cb": (2 * Q * N * G, 2 * b + 2 * g),
+        "mfma_chunk_state": (2 * N * P * H, X + 2 * R + b + S),
         "mfma_chunk_out": ((2 * Q * P + 2 * N * P) * H, 2 * X + S + g + b + 2 * R),
         "mfma_dstate_local": (4 * N * P * H, 2 * X + 2 * R + 2 * b + 2 * S),
         "mfma_bwd_main": ((2 * Q * P + 2 * N * P) * H, 3 * X + S + g + b + 5 * R),
         "mfma_dG": (2 * Q * P * H, 2 * X + 3 * R + 2 * g),
         "mfma_dBC": (4 * N * P * H, 2 * X + 2 * S + 4 * R + 2 * b + 8 * G * N),
         "mfma_final_ddt": (4 * Q * N * G, g + 4 * b + 8 * G * N + 6 * R + H * esz),
-        # bwd_main + dG + dBC in one launch (Q = 256): x and dY are read once for the three
+        # bwd_main + dG + dBC in one launch (Q >= 128): x and dY are read once for the three
         "mfma_bwd_trio": ((4 * Q * P + 6 * N * P) * H, 3 * X + 3 * S + 3 * g + 3 * b + 12 * R + 8 * G * N),
         # shape-generic kernels
         "chunk_state": (2 * Q * N * G + 3 * N * P * H, 1.5 * X + H * esz + 2 * R + 2 * b + 4 * Q * G + 1.5 * S4),
         "chunk_out": ((2 * Q * P + 2 * N * P) * H, 2 * X + S4 + 4 * Q * G + b + 2 * R),
         "bwd_main": ((4 * Q * P + 6 * N * P) * H, 3 * X + 2 * S4 + 8 * Q * G + 2 * b + 8 * R + 8 * G * N),
         "dBC": (4 * Q * N * G, 4 * Q * G + 4 * b + 8 * G * N + 7 * R + H * esz),
-        "cumsum": (0, H * esz + 4 * 4 * H),
         "state_scan_fwd": (0, (4 if mfma else 8) * st), "state_scan_bwd": (0, (8 if mfma else 20) * st),
     }
     return {k: (fl * t, by * t) for k, (fl, by) in m.items()}
@@ -535,7 +533,7 @@ def block_bench(args, cfg, pk, torch, dev):
 # tensors the method must read and write there once per token (bf16 storage: x-shaped tensors H*P*e, dt-shaped
 # H*e, B/C-shaped G*N*e): forward reads x, dt, B, C and writes y; the restore of a segment re-reads x, dt, B, C;
 # backward reads x, dt, B, C, dy and writes dx, ddt, dB, dC.
-KERNEL_GROUP = {"cumsum": "fwd", "mfma_cb": "fwd", "mfma_chunk_state": "fwd", "chunk_state": "fwd",
+KERNEL_GROUP = {"mfma_chunk_state": "fwd", "chunk_state": "fwd",
                 "state_scan_fwd": "fwd", "mfma_chunk_out": "fwd", "chunk_out": "fwd", "mfma_dstate_local": "restore",
                 "state_scan_bwd": "bwd", "mfma_bwd_trio": "bwd", "mfma_bwd_main": "bwd", "bwd_main": "bwd", "mfma_dG": "bwd",
                 "mfma_dBC": "bwd", "dBC": "bwd", "mfma_final_ddt": "bwd"}

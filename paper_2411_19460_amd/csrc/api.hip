@@ -108,29 +108,34 @@ HeadSlices part_slices(const Dims& d, bool mfma, int wg_target) {
 }
 }  // namespace
 
-// Slices of the three head-walking passes of the backward sweep (chunks of 256: one launch) for a span of nc chunks.  A
-// compute unit holds one of their workgroups.  With the machine to itself such a launch ends soonest when all its workgroups
-// fit in one round, if slices can be found that make them about equally long: what a workgroup pays around its heads (fetching
-// the scores, storing the partial sums) is paid once, and there are fewer partial sums to write and add up.  In thousands of
-// cycles a workgroup of dx takes 8 + 10 a head, of dG 11 + 12, of the head sums 13 + 5; otherwise every pass gets a workgroup
-// per compute unit and the three alternate.  32 chunks of 24 heads, slices (8, 8, 4) -> (3, 3, 1): 75.2 -> 63.6 us, and
-// the finalisation 19.0 -> 13.6; 16 chunks of 80 heads, (16, 16, 8) -> (5, 5, 2): 114 -> 103 and 19.1 -> 14.2.
+// Slices of the three head-walking passes of the backward sweep (one launch, chunks of 128 and 256) for a span of nc chunks.
+// A compute unit holds one of their workgroups, two at chunks of 128.  With the machine to itself such a launch ends soonest
+// when all its workgroups fit in one round, if slices can be found that make them about equally long: what a workgroup pays
+// around its heads (fetching the scores, storing the partial sums) is paid once, and there are fewer partial sums to write
+// and add up.  Otherwise every pass gets a workgroup per compute unit and the three alternate.  Slices (dx, dG, head sums) by
+// this rule, 32 chunks of 24 heads: (8, 8, 4) -> (3, 3, 1): 75.2 -> 63.6 us, and the finalisation 19.0 -> 13.6; 16 chunks of
+// 80 heads, (16, 16, 8) -> (5, 5, 2): 114 -> 103 and 19.1 -> 14.2.
 WalkSlices walk_slices(const Dims& d, int64_t nc, bool mfma, int wg_target) {
     WalkSlices w;
     w.dg = dg_slices(d, mfma, wg_target).split(nc);
     w.part = part_slices(d, mfma, wg_target).split(nc);
     w.dual = 0;
-    if (!mfma || d.Q != 256 || wg_target < 256 || nc <= 0) return w;
-    const int64_t base = d.Bt * nc * d.G;
+    if (!mfma || d.Q < 128 || wg_target < 256 || nc <= 0) return w;
+    // thousands of cycles of a workgroup around its heads and for each of them: dx, dG, head sums
+    struct Cost { int64_t around[3], head[3]; };
+    const Cost c = d.Q == 256 ? Cost{{8, 11, 13}, {10, 12, 5}} : Cost{{6, 8, 9}, {11, 8, 5}};
+    const int64_t base = d.Bt * nc * d.G, units = d.Q == 256 ? 256 : 512;
+    auto one = [&](int pass, int64_t slices) { return c.around[pass] + c.head[pass] * (d.hpg / slices); };
     auto longest = [&](int64_t a, int64_t p) {
-        const int64_t ha = d.hpg / a, hp = d.hpg / p, g = 11 + 12 * ha, s = 13 + 5 * hp;
-        return g > s ? g : s;
+        int64_t t = one(0, a);
+        t = one(1, a) > t ? one(1, a) : t;
+        return one(2, p) > t ? one(2, p) : t;
     };
     // what the general rule takes: the work spread over the machine, and half a workgroup of ragged end
-    const int64_t a0 = w.dg, p0 = w.part, work = a0 * (19 + 22 * (d.hpg / a0)) + 2 * p0 * (13 + 5 * (d.hpg / p0));
-    int64_t least = base * work / 256 + longest(a0, p0) / 2;
-    for (int a = 1; a <= w.dg; ++a)
-        for (int p = 1; p <= w.part && d.hpg % a == 0 && base * (2 * a + 2 * p) <= 256; ++p)
+    const int64_t a0 = w.dg, p0 = w.part, work = a0 * (one(0, a0) + one(1, a0)) + 2 * p0 * one(2, p0);
+    int64_t least = base * work / units + longest(a0, p0) / 2;
+    for (int a = 1; a <= a0; ++a)
+        for (int p = 1; p <= p0 && d.hpg % a == 0 && base * (2 * a + 2 * p) <= units; ++p)
             if (d.hpg % p == 0 && longest(a, p) < least) least = longest(a, p), w.dual = w.dg = a, w.part = p;
     return w;
 }

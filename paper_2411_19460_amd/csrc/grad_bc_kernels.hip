@@ -3,7 +3,7 @@
 //   dG[i][j] = sum over the heads of the group of  dt_j decay(i,j) (dY_i . x_j),   j <= i
 //   dC_i     = sum_j dG[i][j] B_j  +  sum_heads exp(cum_i) dY_i^T Hprev
 //   dB_j     = sum_i dG[i][j] C_i  +  sum_heads exp(T - cum_j) dt_j x_j^T dHnext
-// Three kernels:
+// Three passes (the first two, with dx, as one launch for chunks of 128 and 256):
 //   mk_dG       : one workgroup per (batch, chunk, group, head slice); the whole lower triangle of dG
 //                 (36 tiles of 32 x 32 when Q = 256, four or five per wave) stays in accumulators while the workgroup walks
 //                 the heads of its slice; dY and x tiles are staged in LDS once per head (next head
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(64 * DgMap<Q>::NWV) void mk_dG(SegParams sp) {
 // Wave w owns RT row tiles (row group w / 2) and one half of the state columns (w % 2).
 template <int Q>
 struct PartCfg {
-    static constexpr int RT = Q >= 256 ? 2 : 1;       // 32-row tiles per wave
+    static constexpr int RT = Q >= 128 ? 2 : 1;       // 32-row tiles per wave
     static constexpr int NWV = 2 * (Q / 32) / RT;     // waves
     static constexpr int NTHR = 64 * NWV;
     static constexpr int TV = Q * 8 / NTHR;           // 16-byte vectors of the token tile per thread
@@ -588,7 +588,8 @@ __global__ __launch_bounds__(PartCfg<Q>::NTHR) void mk_dBC_part(SegParams sp) {
 // The three head-walking passes of the backward sweep that follow the state scans -- dx (reverse dual
 // form), dG and the dB / dC head sums -- as one launch: they read the same dY and x tiles, and
 // workgroups that run side by side find in cache what their neighbours fetched.  Needs the three
-// passes to use the same workgroup size (Q = 256).  With equal workgroup counts, a multiple of 8, the
+// passes to use the same workgroup size (Q = 128: four waves, two workgroups a compute unit; 2 x 3001 tokens of 32 heads
+// 85.6 us as three launches, 64.5 as one).  With equal workgroup counts, a multiple of 8, the
 // passes alternate in groups of 8 consecutive workgroup ids, so that the workgroups of the three
 // passes that work on one chunk land on the same XCD (ids are dealt round-robin over the 8 XCDs) and are
 // dispatched together.
@@ -600,8 +601,8 @@ union TrioLds {
 };
 
 template <int Q>
-__global__ __launch_bounds__(512) void mk_bwd_trio(SegParams sp, int n_dual, int n_dg, int n_part) {
-    static_assert(dualk::DualCfg<Q>::NTHR == 512 && 64 * DgMap<Q>::NWV == 512 && PartCfg<Q>::NTHR == 512, "one workgroup size");
+__global__ __launch_bounds__(2 * Q, 512 / (2 * Q)) void mk_bwd_trio(SegParams sp, int n_dual, int n_dg, int n_part) {
+    static_assert(dualk::DualCfg<Q>::NTHR == 2 * Q && 64 * DgMap<Q>::NWV == 2 * Q && PartCfg<Q>::NTHR == 2 * Q, "one workgroup size");
     __shared__ __attribute__((aligned(16))) TrioLds<Q> L;
     int z = blockIdx.x, pass;
     if (n_dual == n_dg && n_dg == n_part && (n_dual & 7) == 0) {
@@ -797,15 +798,14 @@ __global__ __launch_bounds__(NTH) void mk_final_ddt(SegParams sp, int n_final) {
 }
 
 template <int Q>
-hipError_t grad_bc_q(const SegParams& sp0, bool with_dual, hipStream_t st) {
+hipError_t grad_bc_q(const SegParams& sp0, hipStream_t st) {
     SegParams sp = sp0;
     const int n_dg = sp.Bt * sp.nc * sp.G * sp.dg_split, n_part = sp.Bt * sp.nc * sp.G * 2 * sp.part_split;
-    if (with_dual) {
-        if (Q != 256) return hipErrorInvalidValue;
+    if constexpr (Q >= 128) {
         if (!sp.dual_split) sp.dual_split = pick_split(sp.hpg, (int64_t)sp.Bt * sp.nc * sp.G, sp.wg_target);
         const int n_dual = sp.Bt * sp.nc * sp.G * sp.dual_split;
         sp.part_alternate = sp.dual_split == 2 * sp.part_split && sp.dg_split == sp.dual_split;
-        SSDK_LAUNCH(K_MFMA_BWD_TRIO, st, mk_bwd_trio<256>, dim3(n_dual + n_dg + n_part), dim3(512), sp, n_dual, n_dg, n_part);
+        SSDK_LAUNCH(K_MFMA_BWD_TRIO, st, mk_bwd_trio<Q>, dim3(n_dual + n_dg + n_part), dim3(2 * Q), sp, n_dual, n_dg, n_part);
     } else {
         SSDK_LAUNCH(K_MFMA_DG, st, mk_dG<Q>, dim3(n_dg), dim3(64 * DgMap<Q>::NWV), sp);
         SSDK_LAUNCH(K_MFMA_DBC, st, mk_dBC_part<Q>, dim3(n_part), dim3(PartCfg<Q>::NTHR), sp);
@@ -817,11 +817,11 @@ hipError_t grad_bc_q(const SegParams& sp0, bool with_dual, hipStream_t st) {
 
 }  // namespace
 
-hipError_t mfma_launch_grad_bc(const SegParams& sp, bool with_dual, hipStream_t st) {
+hipError_t mfma_launch_grad_bc(const SegParams& sp, hipStream_t st) {
     switch (sp.Q) {
-        case 64: return grad_bc_q<64>(sp, with_dual, st);
-        case 128: return grad_bc_q<128>(sp, with_dual, st);
-        case 256: return grad_bc_q<256>(sp, with_dual, st);
+        case 64: return grad_bc_q<64>(sp, st);
+        case 128: return grad_bc_q<128>(sp, st);
+        case 256: return grad_bc_q<256>(sp, st);
         default: return hipErrorInvalidValue;
     }
 }

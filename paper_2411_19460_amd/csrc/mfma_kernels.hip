@@ -27,33 +27,65 @@ namespace {
 using namespace mf;
 
 // ---------------------------------------------------------------------------------------------
-// Decay preparation: cum (chunk-local inclusive cumsum of dt*A), dt in fp32, ein, eout.
-template <int Q>
-__device__ __forceinline__ void prep_body(const SegParams& sp, float* s, int c, int h, int b) {
-    const int i = threadIdx.x;
-    const bool live = i < chunk_rows(sp, c, Q);
-    const float d = live ? bf16_to_float(((const bf16_t*)sp.dt)[(int64_t)b * sp.dts_b + ((int64_t)c * Q + i) * sp.H + h]) : 0.f;
-    s[i] = d * sp.A[h] + ((sp.reset && live && sp.reset[(int64_t)b * sp.reset_bs + (int64_t)c * Q + i]) ? RESET_LOG_DECAY : 0.f);
-    __syncthreads();
-    for (int off = 1; off < Q; off <<= 1) {
-        const float v = (i >= off) ? s[i - off] : 0.f;
-        __syncthreads();
-        s[i] += v;
-        __syncthreads();
-    }
-    const int bs = (i / BLK) * BLK;
-    const float before = bs > 0 ? s[bs - 1] : 0.f;
-    const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q + i;
-    sp.cum[o] = s[i];
-    sp.dtf[o] = d;
-    sp.ein[o] = __expf(s[i] - before);
-    sp.eout[o] = __expf(s[bs + BLK - 1] - s[i]);
+// Sums over a wave by lane exchanges of the vector ALUs: rows of 16 lanes, then across the rows.  Every lane ends with
+// the sum of the lanes up to its own (lane 63: of all).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xF, true));
+}
+__device__ __forceinline__ float wave_prefix(float v) {
+    v = dpp_add<0x111, 0xF>(v);  // row_shr:1
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return v;
 }
 
+// Decay preparation: cum (chunk-local inclusive cumsum of dt*A), dt in fp32, ein, eout.  A wave takes one chunk and head,
+// lane l the tokens E l .. E l + E - 1: nothing waits for other waves, and the four waves of a workgroup read neighbouring
+// heads, i.e. the same cache lines of dt.
+constexpr int PREP_HEADS = NTH / 64;
 template <int Q>
-__global__ __launch_bounds__(Q) void mk_prep(SegParams sp) {
-    __shared__ float s[Q];
-    prep_body<Q>(sp, s, blockIdx.x, blockIdx.y, blockIdx.z);
+__device__ __forceinline__ void prep_body(const SegParams& sp, int c, int h, int b) {
+    constexpr int E = Q / 64;
+    typedef float vec __attribute__((ext_vector_type(E)));
+    const int lane = threadIdx.x & 63, rows = chunk_rows(sp, c, Q);
+    if (h >= sp.H) return;
+    const bf16_t* dt = (const bf16_t*)sp.dt + (int64_t)b * sp.dts_b + (int64_t)c * Q * sp.H + h;
+    const uint8_t* reset = sp.reset ? sp.reset + (int64_t)b * sp.reset_bs + (int64_t)c * Q : nullptr;
+    const float A = sp.A[h];
+    float d[E], a[E], run = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = E * lane + e, il = i < rows ? i : rows - 1;
+        d[e] = bf16_to_float(dt[(int64_t)il * sp.H]);
+        a[e] = reset && reset[il] ? RESET_LOG_DECAY : 0.f;
+        if (i >= rows) d[e] = a[e] = 0.f;
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) a[e] = run += d[e] * A + a[e];
+    const float before = wave_prefix(run) - run;
+#pragma unroll
+    for (int e = 0; e < E; ++e) a[e] += before;
+    // cum at the end of the lane's 64-token block and of the one in front of it
+    constexpr int LPB = 64 / E;  // lanes of a block
+    const float end = __shfl(a[E - 1], lane | (LPB - 1), 64), prev = __shfl(a[E - 1], (lane | (LPB - 1)) - LPB, 64);
+    const float start = lane >= LPB ? prev : 0.f;
+    vec vc, vd, vi, vo;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        vc[e] = a[e];
+        vd[e] = d[e];
+        vi[e] = __expf(a[e] - start);
+        vo[e] = __expf(end - a[e]);
+    }
+    const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q + E * lane;
+    *(vec*)(sp.cum + o) = vc;
+    *(vec*)(sp.dtf + o) = vd;
+    *(vec*)(sp.ein + o) = vi;
+    *(vec*)(sp.eout + o) = vo;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -102,22 +134,16 @@ __device__ __forceinline__ void cb_body(const SegParams& sp, int z, int pair) {
     }
 }
 
+// The two steps that need nothing but the inputs -- decay preparation and scores -- as one launch: the first n_prep
+// workgroups do one chunk of PREP_HEADS heads of the former each, the rest one 64 x 64 block pair of the latter.
 template <int Q>
-__global__ __launch_bounds__(NTH) void mk_cb(SegParams sp) {
-    cb_body<Q>(sp, blockIdx.x, blockIdx.y);
-}
-
-// The two steps that need nothing but the inputs -- decay preparation and scores -- as one launch (chunk 256: both
-// run 256 threads per workgroup): the first n_prep workgroups do one (chunk, head) of the former each, the rest one
-// 64 x 64 block pair of the latter.
 __global__ __launch_bounds__(NTH) void mk_prep_cb(SegParams sp, int n_prep) {
-    constexpr int Q = 256, NPAIR = (Q / BLK) * (Q / BLK + 1) / 2;
-    __shared__ float s[Q];
+    constexpr int NPAIR = (Q / BLK) * (Q / BLK + 1) / 2;
     int z = blockIdx.x;
     if (z < n_prep) {
-        const int c = z % sp.nc;
+        const int c = z % sp.nc, nh = (sp.H + PREP_HEADS - 1) / PREP_HEADS;
         z /= sp.nc;
-        prep_body<Q>(sp, s, c, z % sp.H, z / sp.H);
+        prep_body<Q>(sp, c, z % nh * PREP_HEADS + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), z / nh);
     } else {
         z -= n_prep;
         cb_body<Q>(sp, z / NPAIR, z % NPAIR);
@@ -254,21 +280,6 @@ __device__ __forceinline__ f32x4 ld_state(const bf16_t* p) { return __builtin_co
 __device__ __forceinline__ void st_state(float* p, f32x4 v) { *(f32x4*)p = v; }
 __device__ __forceinline__ void st_state(bf16_t* p, f32x4 v) { *(bf16x4*)p = __builtin_convertvector(v, bf16x4); }
 
-// Sum over the wave in lane 63, by lane exchanges of the vector ALUs (rows of 16 lanes, then across the rows).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_add(float v) {
-    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xF, true));
-}
-__device__ __forceinline__ float wave_sum_last(float v) {
-    v = dpp_add<0x111, 0xF>(v);  // row_shr:1
-    v = dpp_add<0x112, 0xF>(v);
-    v = dpp_add<0x114, 0xF>(v);
-    v = dpp_add<0x118, 0xF>(v);  // lane 15 of every row: the row's sum
-    v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
 // F32IN: the chunk states arrive in fp32 (SSD_FLAG_FP32_CHUNK_STATES, an array of their own), else as bf16 in place.
 // BWD = false: one walk over all chunks of the span, putting the checkpoints of its segments down on the way.
 // BWD = true: the walk to the right again, every segment restarted from its checkpoint, then the walk back over the
@@ -371,7 +382,7 @@ __global__ __launch_bounds__(NTH) void mk_scan(SegParams sp) {
             float part = 0.f;
 #pragma unroll
             for (int i = 0; i < 4; ++i) part += g[i] * R.h[u][i];
-            part = wave_sum_last(a * part);
+            part = wave_prefix(a * part);
             if ((threadIdx.x & 63) == 63) tail[(int64_t)c * sp.nslice] = part;  // one per wave; summed later in a fixed order
             g = a * g + R.l[u];
         }
@@ -400,11 +411,8 @@ hipError_t scan(const SegParams& sp, hipStream_t st) {
 template <int Q>
 hipError_t fwd_q(const SegParams& sp, bool need_y, hipStream_t st) {
     constexpr int NB = Q / BLK;
-    const int n_prep = sp.nc * sp.H * sp.Bt, n_cb = sp.Bt * sp.nc * sp.G * (NB * (NB + 1) / 2);
-    if (Q == 256)
-        SSDK_LAUNCH(K_MFMA_PREP_CB, st, mk_prep_cb, dim3(n_prep + n_cb), dim3(NTH), sp, n_prep);
-    else
-        SSDK_LAUNCH(K_CUMSUM, st, mk_prep<Q>, dim3(sp.nc, sp.H, sp.Bt), dim3(Q), sp);
+    const int n_prep = sp.nc * ((sp.H + PREP_HEADS - 1) / PREP_HEADS) * sp.Bt, n_cb = sp.Bt * sp.nc * sp.G * (NB * (NB + 1) / 2);
+    SSDK_LAUNCH(K_MFMA_PREP_CB, st, mk_prep_cb<Q>, dim3(n_prep + n_cb), dim3(NTH), sp, n_prep);
     {   // chunk states; on the backward path (need_y false) the local state adjoints ride in the same launch
         SegParams so = sp;
         const int nroles = need_y ? 1 : 2;
@@ -416,7 +424,6 @@ hipError_t fwd_q(const SegParams& sp, bool need_y, hipStream_t st) {
         else
             SSDK_LAUNCH(need_y ? K_MFMA_CHUNK_STATE : K_MFMA_DSTATE, st, (mk_chunk_outer<Q, false>), dim3(sp.Bt * sp.nc * sp.G * nroles * so.outer_split), dim3(OUTER_THR), so, nroles);
     }
-    if (Q != 256) SSDK_LAUNCH(K_MFMA_CB, st, mk_cb<Q>, dim3(sp.Bt * sp.nc * sp.G, NB * (NB + 1) / 2), dim3(NTH), sp);
     if (!need_y) return hipSuccess;  // the backward pass restores the entering states in the launch of its own scan
     // the scan is the only step that needs the previous segment (its leaving state)
     if (sp.ev_wait && hipStreamWaitEvent(st, sp.ev_wait, 0) != hipSuccess) return hipErrorUnknown;
@@ -437,10 +444,10 @@ hipError_t bwd_q(const SegParams& sp0, hipStream_t st) {
     if (sp.ev_record && hipEventRecord(sp.ev_record, st) != hipSuccess) return hipErrorUnknown;
     // dx, dG and the dB / dC head sums (which also write the chunk-local part of the gradient of cum
     // and the state dot products): one launch when the three share a workgroup size
-    const bool trio = Q == 256;
+    const bool trio = Q >= 128;
     if (!trio) e = mfma_launch_dual(sp, 2, st);
     if (e != hipSuccess) return e;
-    e = mfma_launch_grad_bc(sp, trio, st);   // ddt and the dA / dD partial sums ride in its last launch
+    e = mfma_launch_grad_bc(sp, st);   // ddt and the dA / dD partial sums ride in its last launch
     if (e != hipSuccess) return e;
     if (!sp.defer_param) {
         e = launch_param_reduce(sp, st);

@@ -204,7 +204,7 @@ bool use_mfma(const ssd_shape_t& sh, uint32_t flags);
 
 // Kernel ids for the optional event timing (see prof.hip).
 enum KernelId {
-    K_CUMSUM, K_CHUNK_STATE, K_SCAN_FWD, K_CHUNK_OUT, K_SCAN_BWD, K_BWD_MAIN, K_PARAM, K_DBC, K_FILL, K_COPY, K_MFMA_CB,
+    K_CHUNK_STATE, K_SCAN_FWD, K_CHUNK_OUT, K_SCAN_BWD, K_BWD_MAIN, K_PARAM, K_DBC, K_FILL, K_COPY,
     K_MFMA_CHUNK_STATE, K_MFMA_CHUNK_OUT, K_MFMA_DSTATE, K_MFMA_BWD_MAIN, K_MFMA_DG, K_MFMA_DBC, K_MFMA_BWD_TRIO,
     K_MFMA_PREP_CB, K_MFMA_FINAL_DDT, K_COUNT
 };
@@ -241,7 +241,7 @@ hipError_t mfma_backward_segment(const SegParams& sp, hipStream_t st);
 // One dual-form pass over a segment: epi 0 = forward output, 2 = the backward pass.
 hipError_t mfma_launch_dual(const SegParams& sp, int epi, hipStream_t st);
 // dG, the head sums and the final contraction that give dB and dC of one segment.
-hipError_t mfma_launch_grad_bc(const SegParams& sp, bool with_dual, hipStream_t st);
+hipError_t mfma_launch_grad_bc(const SegParams& sp, hipStream_t st);
 // Smallest divisor ns of heads_per_group with base * ns >= target workgroups (else heads_per_group).
 int pick_split(int heads_per_group, int64_t base, int target);
 // Slices for a launch that has the machine to itself (see api.hip).
