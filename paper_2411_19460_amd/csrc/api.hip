@@ -108,19 +108,20 @@ HeadSlices part_slices(const Dims& d, bool mfma, int wg_target) {
 }
 }  // namespace
 
-// Slices of the three head-walking passes of the backward sweep (one launch, chunks of 128 and 256) for a span of nc chunks.
+// Slices of the three head-walking passes of the backward sweep (one launch, chunks of 128 and 256) for sp's span of the sequence.
 // A compute unit holds one of their workgroups, two at chunks of 128.  With the machine to itself such a launch ends soonest
 // when all its workgroups fit in one round, if slices can be found that make them about equally long: what a workgroup pays
 // around its heads (fetching the scores, storing the partial sums) is paid once, and there are fewer partial sums to write
 // and add up.  Otherwise every pass gets a workgroup per compute unit and the three alternate.  Slices (dx, dG, head sums) by
 // this rule, 32 chunks of 24 heads: (8, 8, 4) -> (3, 3, 1): 75.2 -> 63.6 us, and the finalisation 19.0 -> 13.6; 16 chunks of
 // 80 heads, (16, 16, 8) -> (5, 5, 2): 114 -> 103 and 19.1 -> 14.2.
-WalkSlices walk_slices(const Dims& d, int64_t nc, bool mfma, int wg_target) {
-    WalkSlices w;
-    w.dg = dg_slices(d, mfma, wg_target).split(nc);
-    w.part = part_slices(d, mfma, wg_target).split(nc);
-    w.dual = 0;
-    if (!mfma || d.Q < 128 || wg_target < 256 || nc <= 0) return w;
+void fit_splits(SegParams& sp, const Dims& d, bool mfma, int wg_target) {
+    const int64_t nc = sp.nc;
+    const int a0 = dg_slices(d, mfma, wg_target).split(nc), p0 = part_slices(d, mfma, wg_target).split(nc);
+    sp.dual_split = 0;
+    sp.dg_split = a0;
+    sp.part_split = p0;
+    if (!mfma || d.Q < 128 || wg_target < 256 || nc <= 0) return;
     // thousands of cycles of a workgroup around its heads and for each of them: dx, dG, head sums
     struct Cost { int64_t around[3], head[3]; };
     const Cost c = d.Q == 256 ? Cost{{8, 11, 13}, {10, 12, 5}} : Cost{{6, 8, 9}, {11, 8, 5}};
@@ -132,12 +133,13 @@ WalkSlices walk_slices(const Dims& d, int64_t nc, bool mfma, int wg_target) {
         return one(2, p) > t ? one(2, p) : t;
     };
     // what the general rule takes: the work spread over the machine, and half a workgroup of ragged end
-    const int64_t a0 = w.dg, p0 = w.part, work = a0 * (one(0, a0) + one(1, a0)) + 2 * p0 * one(2, p0);
+    const int64_t work = a0 * (one(0, a0) + one(1, a0)) + 2 * p0 * one(2, p0);
     int64_t least = base * work / units + longest(a0, p0) / 2;
-    for (int a = 1; a <= a0; ++a)
-        for (int p = 1; p <= p0 && d.hpg % a == 0 && base * (2 * a + 2 * p) <= units; ++p)
-            if (d.hpg % p == 0 && longest(a, p) < least) least = longest(a, p), w.dual = w.dg = a, w.part = p;
-    return w;
+    for (int a = 1; a <= a0 && base * 2 * (a + 1) <= units; ++a) {
+        if (d.hpg % a) continue;
+        for (int p = 1; p <= p0 && base * 2 * (a + p) <= units; ++p)
+            if (d.hpg % p == 0 && longest(a, p) < least) least = longest(a, p), sp.dual_split = sp.dg_split = a, sp.part_split = p;
+    }
 }
 
 WsLayout ws_layout(const Dims& d, bool bwd, bool mfma, int wg_target, bool fp32cs) {
@@ -165,7 +167,6 @@ WsLayout ws_layout(const Dims& d, bool bwd, bool mfma, int wg_target, bool fp32c
     if (mfma) w.states_bf = take((size_t)d.Bt * d.nc * d.H * PN * 2);
     const int64_t nt = (d.Q + 63) / 64, nn = (d.N + 63) / 64, np = (d.P + 63) / 64;  // 64 x 64 tiles of the generic kernels
     const HeadSlices dg = dg_slices(d, mfma, wg_target), part = part_slices(d, mfma, wg_target);
-    w.walk = walk_slices(d, d.nc, mfma, wg_target);
     if (bwd) {
         if (!mfma || fp32cs) w.dstates = take((size_t)d.Bt * d.nc * d.H * PN * 4);
         if (mfma) w.dstates_bf = take((size_t)d.Bt * d.nc * d.H * PN * 2);
@@ -202,9 +203,6 @@ void bind_workspace(SegParams& sp, const WsLayout& w, void* workspace, bool bwd)
     sp.eout = (float*)at(w.eout);
     sp.tok_stride = (int64_t)(w.tok / 4);
     sp.states_bf = (bf16_t*)at(w.states_bf);
-    sp.dual_split = w.walk.dual;
-    sp.dg_split = w.walk.dg;
-    sp.part_split = w.walk.part;
     if (bwd) {
         sp.dstates_bf = (bf16_t*)at(w.dstates_bf);
         sp.dbc_part = (float*)at(w.dbc_part);
@@ -475,15 +473,6 @@ static void span_tokens(SegParams& sp, const Dims& d, int64_t k, int64_t ns) {
     sp.reset_bs = d.L;
 }
 
-// Head slices of the per-slice partial sums for a span that may be shorter than the largest one (fewer chunks to spread
-// over the machine).
-static void fit_splits(SegParams& sp, const Dims& d, bool mfma) {
-    const WalkSlices w = walk_slices(d, sp.nc, mfma, wg_target(d.nl));
-    sp.dual_split = w.dual;
-    sp.dg_split = w.dg;
-    sp.part_split = w.part;
-}
-
 // one_stream: everything stays on the caller's stream (no library stream or event is touched).
 static int fwd_impl(const ssd_shape_t* shape, const void* x, const void* dt, const float* A, const void* B,
                     const void* C, const float* D, const float* init_state, void* y, float* final_state,
@@ -709,7 +698,7 @@ extern "C" int ssd_bwd(const ssd_shape_t* shape, const void* x, const void* dt, 
         const int64_t t0 = k * d.s;
         const int HP = d.H * d.P, GN = d.G * d.N;
         span_tokens(sp, d, k, ns);
-        fit_splits(sp, d, mfma);
+        fit_splits(sp, d, mfma, wg_target(nl));
         sp.x = off(x, t0 * HP, d.esz);
         sp.dy = off(dy, t0 * HP, d.esz);
         sp.dx = off(dx, t0 * HP, d.esz);

@@ -181,14 +181,10 @@ constexpr float RESET_LOG_DECAY = -100.f;
 // does not exist on the chosen kernel path and its pointer stays null).
 constexpr size_t WS_NONE = ~(size_t)0;
 constexpr int GENERIC_SLICES = 4;  // head slices of the shape-generic kernels' partial sums, at most
-struct WalkSlices {
-    int dual, dg, part;  // head slices of the backward sweep's passes; dual 0: chosen at the launch
-};
 struct WsLayout {
     size_t cum, dtf, states, Gm, dstates, dG, gterm, fterm, dDrow, tail_part, dA_part, dD_part, dcarry, total;
     size_t ein, eout, states_bf, dstates_bf, dbc_part, sterm, gintra, erow, ecol, tok;
     int nslice;
-    WalkSlices walk;
 };
 
 int check_shape(const ssd_shape_t* sh, Dims* d);
@@ -199,6 +195,8 @@ void plan_dims(Dims* d, bool mfma, bool one_stream);
 // fp32cs: the matrix-core layout keeps fp32 chunk states / local adjoints beside the bf16 operand copies.
 WsLayout ws_layout(const Dims& d, bool bwd, bool mfma, int wg_target = 256, bool fp32cs = false);
 void bind_workspace(SegParams& sp, const WsLayout& w, void* workspace, bool bwd);
+// Head slices of the backward passes for a span of sp.nc chunks.
+void fit_splits(SegParams& sp, const Dims& d, bool mfma, int wg_target);
 void base_params(SegParams& sp, const Dims& d, uint32_t flags);
 bool use_mfma(const ssd_shape_t& sh, uint32_t flags);
 

@@ -180,6 +180,7 @@ extern "C" int magc_stack_bwd(const ssd_shape_t* shape, int32_t nlayers, int32_t
     SegParams sp;
     base_params(sp, c, SSD_FLAG_RESIDUAL);
     bind_workspace(sp, wl, wsb + w.ssd, true);
+    fit_splits(sp, c, mfma, sp.wg_target);
 
     auto set_layer = [&](int j, int64_t k) {
         const int64_t t0 = k * f.s;
