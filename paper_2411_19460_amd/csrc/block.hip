@@ -13,7 +13,7 @@
 // the same way); all on the caller's stream.
 #include <string.h>
 
-#include "ssd_internal.h"
+#include "column_sums.h"
 
 namespace ssdk {
 namespace {
@@ -56,21 +56,12 @@ __global__ __launch_bounds__(256) void k_dt_bwd(const bf16_t* raw, int64_t raw_r
     }
 }
 
-// out[h] (+)= sum_p part[p][h], in a fixed order: a workgroup owns 64 columns, its four waves sum every
-// fourth part each, wave 0 adds the four results
-__global__ __launch_bounds__(256) void k_colsum(const float* part, int64_t nparts, int H, float* out, int accumulate) {
-    __shared__ float red[4][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int h = blockIdx.x * 64 + lane;
-    float s = 0.f;
-    if (h < H)
-        for (int64_t p = wv; p < nparts; p += 4) s += part[p * H + h];
-    red[wv][lane] = s;
-    __syncthreads();
-    if (wv == 0 && h < H) {
-        s = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
-        out[h] = accumulate ? out[h] + s : s;
-    }
+// out[h] (+)= sum_p part[p][h], in a fixed order
+__global__ __launch_bounds__(COLSUM_THREADS) void k_colsum(const float* part, int64_t nparts, int H, float* out, int accumulate) {
+    __shared__ ColsumLds L;
+    const int h = blockIdx.x * 64 + (threadIdx.x & 63);
+    const float s = column_sum(L, part, nparts, H, h, h < H);
+    if (threadIdx.x < 64 && h < H) out[h] = accumulate ? out[h] + s : s;
 }
 
 struct BlockDims {
@@ -487,7 +478,7 @@ int backward_segment(const BlockDims& d, const magc_block_shape_t* sh, const mag
                        p->dt_bias, (const bf16_t*)(ws + w.ddt), (bf16_t*)(dzx + (size_t)d.off_dt * 2), (int64_t)d.d_in_proj,
                        (float*)(ws + w.dtpart), rows, d.H);
     BLK_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_colsum, dim3((d.H + 63) / 64), dim3(256), 0, st, (const float*)(ws + w.dtpart), (int64_t)ntile, d.H, g->ddt_bias, 1);
+    hipLaunchKernelGGL(k_colsum, dim3((d.H + 63) / 64), dim3(COLSUM_THREADS), 0, st, (const float*)(ws + w.dtpart), (int64_t)ntile, d.H, g->ddt_bias, 1);
     BLK_HIP(hipGetLastError());
     // convolution: reads dx, dB, dC where the scan left them, du into the xBC columns of d zxbcdt
     const ssd_conv_shape_t cs = conv_shape(d, rows);

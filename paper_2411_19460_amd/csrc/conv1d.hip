@@ -8,7 +8,7 @@
 // the window in registers, so every input row is read once (plus a three-row halo per TT tokens).
 #include <string.h>
 
-#include "ssd_internal.h"
+#include "column_sums.h"
 
 namespace ssdk {
 namespace {
@@ -283,32 +283,12 @@ __global__ __launch_bounds__(64) void k_conv_bwd(ConvParams cp) {
         for (int e = 0; e < V; ++e) part[(int64_t)k * cp.C + c0 + e] = acc[k][e];
 }
 
-// dw[c][k] (k < 4) and dbias[c]: sum of the partial sums of all (batch, tile) pairs, in a fixed order.
-// A workgroup owns 64 consecutive entries of the [5][C] rows; its four waves sum every fourth part each
-// (four loads in flight per lane), wave 0 adds the four results.
-__global__ __launch_bounds__(256) void k_conv_reduce(const float* part, int64_t nparts, int C, float* dw, float* dbias, int accumulate) {
-    __shared__ float red[4][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int i = blockIdx.x * 64 + lane;  // over 5 * C
-    const bool live = i < 5 * C;
-    float s = 0.f;
-    if (live) {
-        const float* src = part + i;
-        const int64_t stride = 5 * (int64_t)C;
-        int64_t p = wv;
-        for (; p + 12 < nparts; p += 16) {
-            const float a0 = src[p * stride], a1 = src[(p + 4) * stride], a2 = src[(p + 8) * stride], a3 = src[(p + 12) * stride];
-            s += a0;
-            s += a1;
-            s += a2;
-            s += a3;
-        }
-        for (; p < nparts; p += 4) s += src[p * stride];
-    }
-    red[wv][lane] = s;
-    __syncthreads();
-    if (wv == 0 && live) {
-        s = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+// dw and dbias from the tiles' partial sums, rows of [5][C], in a fixed order.
+__global__ __launch_bounds__(COLSUM_THREADS) void k_conv_reduce(const float* part, int64_t nparts, int C, float* dw, float* dbias, int accumulate) {
+    __shared__ ColsumLds L;
+    const int i = blockIdx.x * 64 + (threadIdx.x & 63);  // over 5 * C
+    const float s = column_sum(L, part, nparts, 5 * (int64_t)C, i, i < 5 * C);
+    if (threadIdx.x < 64 && i < 5 * C) {
         const int k = i / C, c = i - k * C;
         if (k < 4) {
             float* o = dw + (int64_t)c * 4 + k;
@@ -451,7 +431,7 @@ int conv_bwd_impl(const ssd_conv_shape_t* sh, const void* u, const float* w, con
     else if (V == 4) hipLaunchKernelGGL((k_conv_bwd<float, 4>), grid, dim3(64), 0, st, cp);
     else hipLaunchKernelGGL((k_conv_bwd<float, 1>), grid, dim3(64), 0, st, cp);
     if (hipGetLastError() != hipSuccess) return SSD_ERR_LAUNCH;
-    hipLaunchKernelGGL(k_conv_reduce, dim3((5 * cp.C + 63) / 64), dim3(256), 0, st, cp.part, (int64_t)sh->batch * cp.ntiles,
+    hipLaunchKernelGGL(k_conv_reduce, dim3((5 * cp.C + 63) / 64), dim3(COLSUM_THREADS), 0, st, cp.part, (int64_t)sh->batch * cp.ntiles,
                        cp.C, dw, dbias, (flags & SSD_FLAG_ACCUM_PARAM) ? 1 : 0);
     return hipGetLastError() == hipSuccess ? SSD_OK : SSD_ERR_LAUNCH;
 }

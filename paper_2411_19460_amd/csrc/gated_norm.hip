@@ -14,7 +14,7 @@
 
 #include <initializer_list>
 
-#include "ssd_internal.h"
+#include "column_sums.h"
 
 namespace ssdk {
 namespace {
@@ -267,32 +267,12 @@ __global__ __launch_bounds__(256) void k_gated_norm_any(NormParams np) {
     }
 }
 
-// dw[c] = sum over the partial sums, in a fixed order: a workgroup owns 64 channels, its four waves sum
-// every fourth part each (four loads in flight per lane), wave 0 adds the four results.
-__global__ __launch_bounds__(256) void k_norm_reduce(const float* part, int64_t nparts, int C, float* dw, int accumulate) {
-    __shared__ float red[4][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int c = blockIdx.x * 64 + lane;
-    const bool live = c < C;
-    float s = 0.f;
-    if (live) {
-        const float* src = part + c;
-        int64_t p = wv;
-        for (; p + 12 < nparts; p += 16) {
-            const float a0 = src[p * C], a1 = src[(p + 4) * C], a2 = src[(p + 8) * C], a3 = src[(p + 12) * C];
-            s += a0;
-            s += a1;
-            s += a2;
-            s += a3;
-        }
-        for (; p < nparts; p += 4) s += src[p * C];
-    }
-    red[wv][lane] = s;
-    __syncthreads();
-    if (wv == 0 && live) {
-        s = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
-        dw[c] = accumulate ? dw[c] + s : s;
-    }
+// dw[c] = sum over the partial sums, in a fixed order.
+__global__ __launch_bounds__(COLSUM_THREADS) void k_norm_reduce(const float* part, int64_t nparts, int C, float* dw, int accumulate) {
+    __shared__ ColsumLds L;
+    const int c = blockIdx.x * 64 + (threadIdx.x & 63);
+    const float s = column_sum(L, part, nparts, C, c, c < C);
+    if (threadIdx.x < 64 && c < C) dw[c] = accumulate ? dw[c] + s : s;
 }
 
 struct NormDims {
@@ -483,6 +463,6 @@ extern "C" int ssd_gated_norm_bwd(const ssd_norm_shape_t* sh, const void* y, con
     const int64_t nparts = f.vpl ? (int64_t)fast_grid(d, true).nwg * (4 / f.wps) : (int64_t)d.ntiles * 4;
     if ((size_t)nparts * d.C * 4 > workspace_bytes) return SSD_ERR_WORKSPACE;  // cannot happen with the documented size
     if (launch<true>(d, np, f, st) != hipSuccess) return SSD_ERR_LAUNCH;
-    hipLaunchKernelGGL(k_norm_reduce, dim3((d.C + 63) / 64), dim3(256), 0, st, np.part, nparts, d.C, dw, accumulate);
+    hipLaunchKernelGGL(k_norm_reduce, dim3((d.C + 63) / 64), dim3(COLSUM_THREADS), 0, st, np.part, nparts, d.C, dw, accumulate);
     return hipGetLastError() == hipSuccess ? SSD_OK : SSD_ERR_LAUNCH;
 }
