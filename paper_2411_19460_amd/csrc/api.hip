@@ -474,7 +474,7 @@ static void span_tokens(SegParams& sp, const Dims& d, int64_t k, int64_t ns) {
 }
 
 // one_stream: everything stays on the caller's stream (no library stream or event is touched).
-static int fwd_impl(const ssd_shape_t* shape, const void* x, const void* dt, const float* A, const void* B,
+static int fwd_impl(const ssd_shape_t* shape, const void* x, const void* dt, const RawDt& raw, const float* A, const void* B,
                     const void* C, const float* D, const float* init_state, void* y, float* final_state,
                     void* boundary_states, void* workspace, size_t workspace_bytes, uint32_t flags,
                     void* hip_stream, bool one_stream) {
@@ -496,7 +496,8 @@ static int fwd_impl(const ssd_shape_t* shape, const void* x, const void* dt, con
         }
         return SSD_OK;
     }
-    if (!x || !dt || !A || !B || !C || !D || !y) return SSD_ERR_NULL;
+    if (!x || (!dt && !raw.dt) || !A || !B || !C || !D || !y) return SSD_ERR_NULL;
+    if (raw.dt && (d.Bt != 1 || !raw.bias)) return SSD_ERR_ARG;
     const bool mfma = use_mfma(*shape, flags);
     plan_dims(&d, mfma, one_stream);
     const int nl = d.nl;
@@ -527,6 +528,7 @@ static int fwd_impl(const ssd_shape_t* shape, const void* x, const void* dt, con
         sp.x = off(x, t0 * HP, d.esz);
         sp.y = off(y, t0 * HP, d.esz);
         sp.dt = off(dt, t0 * d.H, d.esz);
+        sp.raw = RawDt{off(raw.dt, t0 * raw.rs, d.esz), raw.rs, raw.bias};
         sp.Bm = off(B, t0 * GN, d.esz);
         sp.Cm = off(C, t0 * GN, d.esz);
         sp.reset = d.reset ? d.reset + t0 : nullptr;
@@ -568,8 +570,14 @@ extern "C" int ssd_fwd(const ssd_shape_t* shape, const void* x, const void* dt, 
                        const void* C, const float* D, const float* init_state, void* y, float* final_state,
                        void* boundary_states, void* workspace, size_t workspace_bytes, uint32_t flags,
                        void* hip_stream) {
-    return fwd_impl(shape, x, dt, A, B, C, D, init_state, y, final_state, boundary_states, workspace, workspace_bytes,
+    return fwd_impl(shape, x, dt, RawDt{}, A, B, C, D, init_state, y, final_state, boundary_states, workspace, workspace_bytes,
                     flags, hip_stream, false);
+}
+
+int ssdk::scan_fwd(const ssd_shape_t* shape, const void* x, const void* dt, const RawDt& raw, const float* A, const void* B, const void* C,
+                   const float* D, const float* init_state, void* y, float* final_state, void* boundary_states, void* workspace,
+                   size_t workspace_bytes, uint32_t flags, hipStream_t st) {
+    return fwd_impl(shape, x, dt, raw, A, B, C, D, init_state, y, final_state, boundary_states, workspace, workspace_bytes, flags, st, false);
 }
 
 // ---- forward pass for callers that cannot allocate -------------------------------------------------
@@ -631,14 +639,13 @@ extern "C" int ssd_fwd_static(const ssd_shape_t* shape, const void* x, const voi
     if (!ws) return SSD_ERR_LAUNCH;
     // Nothing in the scratch has to start at zero: every array in it is written by the kernel that
     // precedes its first reader within the same call.
-    return fwd_impl(shape, x, dt, A, B, C, D, init_state, y, final_state, boundary_states, ws, need, flags, hip_stream, true);
+    return fwd_impl(shape, x, dt, RawDt{}, A, B, C, D, init_state, y, final_state, boundary_states, ws, need, flags, hip_stream, true);
 }
 
-extern "C" int ssd_bwd(const ssd_shape_t* shape, const void* x, const void* dt, const float* A, const void* B,
-                       const void* C, const float* D, const float* init_state, const void* dy,
-                       const float* dfinal_state, const void* boundary_states, void* dx, void* ddt, float* dA,
-                       void* dB, void* dC, float* dD, float* dinit_state, void* workspace, size_t workspace_bytes,
-                       uint32_t flags, void* hip_stream) {
+int ssdk::scan_bwd(const ssd_shape_t* shape, const void* x, const void* dt, const RawDt& raw, const float* A, const void* B, const void* C,
+                   const float* D, const float* init_state, const void* dy, const float* dfinal_state, const void* boundary_states,
+                   void* dx, void* ddt, float* dA, void* dB, void* dC, float* dD, float* dinit_state, void* workspace,
+                   size_t workspace_bytes, uint32_t flags, hipStream_t st) {
     Dims d;
     int rc = check_shape(shape, &d);
     if (rc != SSD_OK) return rc;
@@ -646,7 +653,6 @@ extern "C" int ssd_bwd(const ssd_shape_t* shape, const void* x, const void* dt, 
         return SSD_ERR_ARG;
     const bool ck16 = (flags & SSD_FLAG_BF16_CHECKPOINTS) && boundary_states;
     if (!dA || !dD) return SSD_ERR_NULL;
-    hipStream_t st = (hipStream_t)hip_stream;
     const size_t HPN = (size_t)d.H * d.P * d.N;
     if (d.L == 0) {  // empty sequence: the state adjoint passes through, parameter gradients are zero
         hipError_t e = hipSuccess;
@@ -659,8 +665,8 @@ extern "C" int ssd_bwd(const ssd_shape_t* shape, const void* x, const void* dt, 
         }
         return e == hipSuccess ? SSD_OK : SSD_ERR_LAUNCH;
     }
-    if (!x || !dt || !A || !B || !C || !D || !dy || !dx || !ddt || !dB || !dC) return SSD_ERR_NULL;
-    if (dx == dy) return SSD_ERR_ARG;
+    if (!x || (!dt && !raw.dt) || !A || !B || !C || !D || !dy || !dx || !ddt || !dB || !dC) return SSD_ERR_NULL;
+    if (dx == dy || (raw.dt && (d.Bt != 1 || !raw.bias))) return SSD_ERR_ARG;
     if (!boundary_states && d.nseg > 1) return SSD_ERR_NULL;
     const bool mfma = use_mfma(*shape, flags);
     plan_dims(&d, mfma, false);
@@ -703,6 +709,7 @@ extern "C" int ssd_bwd(const ssd_shape_t* shape, const void* x, const void* dt, 
         sp.dy = off(dy, t0 * HP, d.esz);
         sp.dx = off(dx, t0 * HP, d.esz);
         sp.dt = off(dt, t0 * d.H, d.esz);
+        sp.raw = RawDt{off(raw.dt, t0 * raw.rs, d.esz), raw.rs, raw.bias};
         sp.ddt = off(ddt, t0 * d.H, d.esz);
         sp.Bm = off(B, t0 * GN, d.esz);
         sp.Cm = off(C, t0 * GN, d.esz);
@@ -738,6 +745,15 @@ extern "C" int ssd_bwd(const ssd_shape_t* shape, const void* x, const void* dt, 
     sps[0].accumulate = (flags & SSD_FLAG_ACCUM_PARAM) ? 1 : 0;
     if (launch_param_reduce(sps[0], st) != hipSuccess) return SSD_ERR_LAUNCH;
     return SSD_OK;
+}
+
+extern "C" int ssd_bwd(const ssd_shape_t* shape, const void* x, const void* dt, const float* A, const void* B,
+                       const void* C, const float* D, const float* init_state, const void* dy,
+                       const float* dfinal_state, const void* boundary_states, void* dx, void* ddt, float* dA,
+                       void* dB, void* dC, float* dD, float* dinit_state, void* workspace, size_t workspace_bytes,
+                       uint32_t flags, void* hip_stream) {
+    return scan_bwd(shape, x, dt, RawDt{}, A, B, C, D, init_state, dy, dfinal_state, boundary_states, dx, ddt, dA, dB, dC, dD, dinit_state,
+                    workspace, workspace_bytes, flags, (hipStream_t)hip_stream);
 }
 
 extern "C" int ssd_prof_serialize(int32_t on) {

@@ -23,16 +23,15 @@ typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 constexpr int DECODE_ROWS = 16;  // calls of at most this many tokens run the scan as the plain recurrence
 constexpr int DT_ROWS = 16;  // rows per workgroup of the dt kernels (granularity of the ddt_bias partial sums)
 
-// dt[r,h] = softplus(raw[r,h] + bias[h]); raw is a column slice (rows raw_rs apart), dt dense
+// dt[r,h] = softplus(raw[r,h] + bias[h]); raw is a column slice (rows raw_rs apart), dt dense.  For the recurrence of a few
+// tokens; the scan's kernels form dt themselves (RawDt).
 __global__ __launch_bounds__(256) void k_dt_fwd(const bf16_t* raw, int64_t raw_rs, const float* bias, bf16_t* dt, int64_t rows, int H) {
     const int64_t r0 = (int64_t)blockIdx.x * DT_ROWS;
     for (int i = threadIdx.x; i < DT_ROWS * H; i += 256) {
         const int64_t r = r0 + i / H;
         const int h = i % H;
         if (r < rows) {
-            const float v = bf16_to_float(raw[r * raw_rs + h]) + bias[h];
-            // log(1 + e^v) without overflow: max(v, 0) + log1p(e^-|v|)
-            dt[r * H + h] = float_to_bf16(fmaxf(v, 0.f) + log1pf(__expf(-fabsf(v))));
+            dt[r * H + h] = float_to_bf16(softplus(bf16_to_float(raw[r * raw_rs + h]) + bias[h]));
         }
     }
 }
@@ -246,35 +245,42 @@ int seg_pre_norm(const BlockDims& d, float eps, const magc_block_params_t* p, ch
     return ssd_gated_norm_fwd(&ps, u_seg, nullptr, p->pre_norm_w, ws + w.un, st);
 }
 
+// normed: the normalised input is in its place already (see residual)
 int seg_in_proj(const BlockDims& d, float eps, const magc_block_params_t* p, char* ws, const BlockWs& w, const void* u_seg, int64_t rows,
-                char* zx, hipStream_t st) {
-    const void* in;
-    BLK_TRY(seg_pre_norm(d, eps, p, ws, w, u_seg, rows, &in, st));
+                char* zx, hipStream_t st, bool normed = false) {
+    const void* in = ws + w.un;
+    if (!normed) BLK_TRY(seg_pre_norm(d, eps, p, ws, w, u_seg, rows, &in, st));
     return ssd_linear_fwd(rows, d.dm, d.d_in_proj, in, 0, p->W_in, zx, 0, st);
 }
 
-// convolution + SiLU of the xBC columns into dense x / B / C, softplus of the dt columns
+// convolution + SiLU of the xBC columns into dense x / B / C
 int seg_mid(const BlockDims& d, const magc_block_params_t* p, char* ws, const BlockWs& w, const char* zx, int64_t rows,
             const void* conv_in, void* conv_out, hipStream_t st) {
     const ssd_conv_shape_t cs = conv_shape(d, rows);
     const ConvSplit xbc = {{ws + w.x, ws + w.B, ws + w.C}, d.d_inner, d.d_inner + d.gn};  // each part dense, as the scan reads it
-    BLK_TRY(conv1d_fwd_split(&cs, zx + (size_t)d.off_xbc * 2, p->conv_w, p->conv_b, conv_in, xbc, conv_out, st));
-    hipLaunchKernelGGL(k_dt_fwd, dim3((unsigned)((rows + DT_ROWS - 1) / DT_ROWS)), dim3(256), 0, st,
-                       (const bf16_t*)(zx + (size_t)d.off_dt * 2), (int64_t)d.d_in_proj, p->dt_bias, (bf16_t*)(ws + w.dt), rows, d.H);
-    BLK_HIP(hipGetLastError());
-    return SSD_OK;
+    return conv1d_fwd_split(&cs, zx + (size_t)d.off_xbc * 2, p->conv_w, p->conv_b, conv_in, xbc, conv_out, st);
 }
 
-int seg_scan(const BlockDims& d, const magc_block_params_t* p, char* ws, const BlockWs& w, int64_t rows, const float* ssm_in,
+// the dt columns of zxbcdt, as the scan takes them
+RawDt raw_dt(const BlockDims& d, const magc_block_params_t* p, const char* zx) {
+    return {zx + (size_t)d.off_dt * 2, (int64_t)d.d_in_proj, p->dt_bias};
+}
+
+// ssm_out may be ssm_in: one segment's scan reads an element of it before it writes it, in one thread
+int seg_scan(const BlockDims& d, const magc_block_params_t* p, char* ws, const BlockWs& w, const char* zx, int64_t rows, const float* ssm_in,
              float* ssm_out, char* y, hipStream_t st, bool recur_ok = false) {
     const ssd_shape_t ss = seg_shape(d, rows);
     if (recur_ok && rows <= DECODE_ROWS && ssm_out) {
         // a few tokens (inference only: see block_fwd): the recurrence token by token on the state itself instead of a padded chunk
+        hipLaunchKernelGGL(k_dt_fwd, dim3((unsigned)((rows + DT_ROWS - 1) / DT_ROWS)), dim3(256), 0, st,
+                           (const bf16_t*)(zx + (size_t)d.off_dt * 2), (int64_t)d.d_in_proj, p->dt_bias, (bf16_t*)(ws + w.dt), rows, d.H);
+        BLK_HIP(hipGetLastError());
         if (ssm_in != ssm_out)
             BLK_HIP(ssm_in ? launch_copy_f32(ssm_out, ssm_in, d.HPN, st) : launch_fill_zero(ssm_out, d.HPN, st));
         return ssd_decode(&ss, ws + w.x, ws + w.dt, p->A, ws + w.B, ws + w.C, p->D, ssm_out, y, 0, st);
     }
-    return ssd_fwd(&ss, ws + w.x, ws + w.dt, p->A, ws + w.B, ws + w.C, p->D, ssm_in, y, ssm_out, nullptr, ws + w.inner, w.inner_bytes, 0, st);
+    return scan_fwd(&ss, ws + w.x, nullptr, raw_dt(d, p, zx), p->A, ws + w.B, ws + w.C, p->D, ssm_in, y, ssm_out, nullptr, ws + w.inner,
+                    w.inner_bytes, 0, st);
 }
 
 int seg_norm(const BlockDims& d, const magc_block_shape_t* sh, const magc_block_params_t* p, char* ws, const BlockWs& w, const char* zx,
@@ -286,10 +292,10 @@ int seg_norm(const BlockDims& d, const magc_block_shape_t* sh, const magc_block_
 // All of them: everything up to y and the normalised y, from the two states entering the segment.
 int forward_segment(const BlockDims& d, const magc_block_shape_t* sh, const magc_block_params_t* p, char* ws, const BlockWs& w,
                     char* zx, char* y, const void* u_seg, int64_t rows, const float* ssm_in, const void* conv_in, float* ssm_out,
-                    void* conv_out, hipStream_t st, bool recur_ok = false) {
-    BLK_TRY(seg_in_proj(d, sh->eps, p, ws, w, u_seg, rows, zx, st));
+                    void* conv_out, hipStream_t st, bool recur_ok = false, bool normed = false) {
+    BLK_TRY(seg_in_proj(d, sh->eps, p, ws, w, u_seg, rows, zx, st, normed));
     BLK_TRY(seg_mid(d, p, ws, w, zx, rows, conv_in, conv_out, st));
-    BLK_TRY(seg_scan(d, p, ws, w, rows, ssm_in, ssm_out, y, st, recur_ok));
+    BLK_TRY(seg_scan(d, p, ws, w, zx, rows, ssm_in, ssm_out, y, st, recur_ok));
     BLK_TRY(seg_norm(d, sh, p, ws, w, zx, y, rows, st));
     return SSD_OK;
 }
@@ -454,13 +460,50 @@ int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_blo
     return SSD_OK;
 }
 
-// The reverse of every step of a segment, given its forward activations (zx, y from the caller; x / B / C,
-// dt and the normalised y in the workspace): du of the segment, parameter gradients added to `g`, the
-// adjoints of the two states entering the segment.
+// dst = a + b, bf16, 16-byte vectors (n a multiple of 8)
+__global__ __launch_bounds__(256) void k_add_bf16(bf16_t* dst, const bf16_t* a, const bf16_t* b, int64_t n8) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (int64_t)gridDim.x * 256) {
+        const b8 x = *(const b8*)((const __bf16*)a + i * 8), y = *(const b8*)((const __bf16*)b + i * 8);
+        b8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (__bf16)((float)x[e] + (float)y[e]);
+        *(b8*)((__bf16*)dst + i * 8) = o;
+    }
+}
+
+hipError_t add_bf16(void* dst, const void* a, const void* b, int64_t n, hipStream_t st) {
+    if (n == 0) return hipSuccess;
+    const int64_t n8 = n / 8, blocks = (n8 + 255) / 256;
+    hipLaunchKernelGGL(k_add_bf16, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, st, (bf16_t*)dst, (const bf16_t*)a,
+                       (const bf16_t*)b, n8);
+    return hipGetLastError();
+}
+
+// x_{j+1} = x_j + Block_j(x_j): nxt = cur + y, with a few bytes moved along (the convolution state of a layer, from where the
+// block left it), and, where the next layer has a normalisation in front (next_norm), its normalised input into un_next by the
+// same pass; returns whether that is done.
+int residual(const BlockDims& d, float eps, void* nxt, const void* cur, const void* y, int64_t rows, const float* next_norm, void* un_next,
+             const void* copy_src, void* copy_dst, size_t copy_bytes, bool* normed, hipStream_t st) {
+    const ResidualJob j = {rows, d.dm, cur, y, nxt, next_norm, un_next, eps, copy_src, copy_dst, copy_bytes};
+    *normed = next_norm && residual_norm_supported(j);
+    if (*normed) {
+        BLK_HIP(launch_residual_norm(j, st));
+        return SSD_OK;
+    }
+    if (copy_bytes) BLK_HIP(launch_copy_f32((float*)copy_dst, (const float*)copy_src, copy_bytes / 4, st));  // bf16 pairs as words
+    BLK_HIP(add_bf16(nxt, cur, y, rows * d.dm, st));
+    return SSD_OK;
+}
+
+// The reverse of every step of a segment, given its forward activations (zx, y from the caller; x / B / C
+// and the normalised y in the workspace): du of the segment (+ res, if given: the gradient that goes round the block in a
+// residual stream; du_seg may be res), parameter gradients added to `g`, the adjoints of the two states entering the segment.
+// normed: the normalised input of the projection is still in its place.  du_tmp: rows of d_model for a gradient that res is
+// added to in a pass of its own.
 int backward_segment(const BlockDims& d, const magc_block_shape_t* sh, const magc_block_params_t* p, const magc_block_grads_t* g,
                      char* ws, const BlockWs& w, const char* zx, const char* y, const void* u_seg, const void* dout_seg, void* du_seg,
                      int64_t rows, const float* ssm_in, const void* conv_in, const float* dssm_out, const float* dconv_out,
-                     float* dssm_in, float* dconv_in, hipStream_t st) {
+                     float* dssm_in, float* dconv_in, hipStream_t st, const void* res = nullptr, void* du_tmp = nullptr, bool normed = false) {
     const uint32_t acc = SSD_FLAG_ACCUM_PARAM;
     char* dzx = ws + w.dzx;
     // output projection
@@ -470,8 +513,8 @@ int backward_segment(const BlockDims& d, const magc_block_shape_t* sh, const mag
     BLK_TRY(ssd_gated_norm_bwd(&ns, y, zx, p->norm_w, ws + w.dyn, ws + w.dy, dzx, g->dnorm_w, ws + w.inner, w.inner_bytes, acc, st));
     // scan
     const ssd_shape_t ss = seg_shape(d, rows);
-    BLK_TRY(ssd_bwd(&ss, ws + w.x, ws + w.dt, p->A, ws + w.B, ws + w.C, p->D, ssm_in, ws + w.dy, dssm_out, nullptr, ws + w.dx, ws + w.ddt,
-                    g->dA, ws + w.dB, ws + w.dC, g->dD, dssm_in, ws + w.inner, w.inner_bytes, acc, st));
+    BLK_TRY(scan_bwd(&ss, ws + w.x, nullptr, raw_dt(d, p, zx), p->A, ws + w.B, ws + w.C, p->D, ssm_in, ws + w.dy, dssm_out, nullptr, ws + w.dx,
+                     ws + w.ddt, g->dA, ws + w.dB, ws + w.dC, g->dD, dssm_in, ws + w.inner, w.inner_bytes, acc, st));
     // softplus of dt: into the dt columns of d zxbcdt
     const int ntile = (int)((rows + DT_ROWS - 1) / DT_ROWS);
     hipLaunchKernelGGL(k_dt_bwd, dim3(ntile), dim3(256), 0, st, (const bf16_t*)(zx + (size_t)d.off_dt * 2), (int64_t)d.d_in_proj,
@@ -485,15 +528,22 @@ int backward_segment(const BlockDims& d, const magc_block_shape_t* sh, const mag
     const ConvSplit dxbc = {{ws + w.dx, ws + w.dB, ws + w.dC}, d.d_inner, d.d_inner + d.gn};
     BLK_TRY(conv1d_bwd_split(&cs, zx + (size_t)d.off_xbc * 2, p->conv_w, p->conv_b, conv_in, dxbc, dconv_out,
                              dzx + (size_t)d.off_xbc * 2, g->dconv_w, g->dconv_b, dconv_in, ws + w.inner, w.inner_bytes, acc, st));
-    // input projection, and the normalisation in front of it (its output is cheap to redo and other layers of
-    // a grid cell may have used the buffer since this layer's forward steps)
-    if (!p->pre_norm_w) return ssd_linear_bwd(rows, d.dm, d.d_in_proj, u_seg, 0, p->W_in, dzx, 0, du_seg, 0, g->dW_in, acc, st);
-    const void* un;
-    BLK_TRY(seg_pre_norm(d, sh->eps, p, ws, w, u_seg, rows, &un, st));
-    BLK_TRY(ssd_linear_bwd(rows, d.dm, d.d_in_proj, un, 0, p->W_in, dzx, 0, ws + w.dun, 0, g->dW_in, acc, st));
-    const ssd_norm_shape_t ps = pre_norm_shape(d, rows, sh->eps);
-    BLK_TRY(ssd_gated_norm_bwd(&ps, u_seg, nullptr, p->pre_norm_w, ws + w.dun, du_seg, nullptr, g->dpre_norm_w, ws + w.inner, w.inner_bytes,
-                               acc, st));
+    // input projection, and the normalisation in front of it (its output is cheap to redo where other layers of
+    // a grid cell have used the buffer since this layer's forward steps)
+    void* du = res ? du_tmp : du_seg;
+    if (!p->pre_norm_w) {
+        BLK_TRY(ssd_linear_bwd(rows, d.dm, d.d_in_proj, u_seg, 0, p->W_in, dzx, 0, du, 0, g->dW_in, acc, st));
+    } else {
+        const void* un = ws + w.un;
+        if (!normed) BLK_TRY(seg_pre_norm(d, sh->eps, p, ws, w, u_seg, rows, &un, st));
+        BLK_TRY(ssd_linear_bwd(rows, d.dm, d.d_in_proj, un, 0, p->W_in, dzx, 0, ws + w.dun, 0, g->dW_in, acc, st));
+        const ssd_norm_shape_t ps = pre_norm_shape(d, rows, sh->eps);
+        if (res && norm_bwd_residual_supported(&ps, u_seg, ws + w.dun, res, du_seg))
+            return norm_bwd_residual(&ps, u_seg, p->pre_norm_w, ws + w.dun, res, du_seg, g->dpre_norm_w, ws + w.inner, w.inner_bytes, acc, st);
+        BLK_TRY(ssd_gated_norm_bwd(&ps, u_seg, nullptr, p->pre_norm_w, ws + w.dun, du, nullptr, g->dpre_norm_w, ws + w.inner, w.inner_bytes,
+                                   acc, st));
+    }
+    if (res) BLK_HIP(add_bf16(du_seg, res, du, rows * d.dm, st));
     return SSD_OK;
 }
 
@@ -513,9 +563,10 @@ extern "C" size_t magc_block_workspace_bytes(const magc_block_shape_t* sh, int32
 // few_ok: calls of a few tokens may take the generation kernels.  Not while a training pass records checkpoints:
 // those kernels round at other places than the chunked path that the backward pass recomputes the segment with,
 // and the result would depend (in its last bits) on how the sequence is cut into segments.
+// normed: the normalised input of the (first) segment is in the workspace already.
 static int block_fwd(const magc_block_shape_t* sh, const magc_block_params_t* p, const void* u, const float* init_ssm,
                      const void* init_conv, void* out, float* ssm_ckpt, void* conv_ckpt, float* final_ssm, void* final_conv,
-                     void* workspace, size_t workspace_bytes, bool few_ok, void* hip_stream) {
+                     void* workspace, size_t workspace_bytes, bool few_ok, void* hip_stream, bool normed = false) {
     BlockDims d;
     BLK_TRY(check(sh, &d));
     if (!p || !p->W_in || !p->conv_w || !p->conv_b || !p->dt_bias || !p->A || !p->D || !p->norm_w || !p->W_out) return SSD_ERR_NULL;
@@ -559,14 +610,14 @@ static int block_fwd(const magc_block_shape_t* sh, const magc_block_params_t* p,
             continue;
         }
         if (!side) {
-            BLK_TRY(forward_segment(d, sh, p, ws, w, ws + w.zx, ws + w.y, u_seg, rows, ssm_in, conv_in, ssm_out, conv_out, st, few_ok));
+            BLK_TRY(forward_segment(d, sh, p, ws, w, ws + w.zx, ws + w.y, u_seg, rows, ssm_in, conv_in, ssm_out, conv_out, st, few_ok, normed && k == 0));
             BLK_TRY(ssd_linear_fwd(rows, d.d_inner, d.dm, ws + w.yn, 0, p->W_out, out_seg, 0, st));
             continue;
         }
         int rc = SSD_OK;
-        if (k == 0) rc = seg_in_proj(d, sh->eps, p, ws, w, u_seg, rows, ws + w.zx, st);  // later ones were issued a segment ahead
+        if (k == 0) rc = seg_in_proj(d, sh->eps, p, ws, w, u_seg, rows, ws + w.zx, st, normed);  // later ones were issued a segment ahead
         if (rc == SSD_OK) rc = seg_mid(d, p, ws, w, ws + w.zx, rows, conv_in, conv_out, st);
-        if (rc == SSD_OK) rc = seg_scan(d, p, ws, w, rows, ssm_in, ssm_out, ws + w.y, st, few_ok);
+        if (rc == SSD_OK) rc = seg_scan(d, p, ws, w, ws + w.zx, rows, ssm_in, ssm_out, ws + w.y, st, few_ok);
         if (!join_side() && rc == SSD_OK) rc = SSD_ERR_LAUNCH;  // the last output projection has read the normalised y
         if (rc == SSD_OK) rc = seg_norm(d, sh, p, ws, w, ws + w.zx, ws + w.y, rows, st);
         if (rc != SSD_OK) return rc;
@@ -645,7 +696,7 @@ extern "C" int magc_block_bwd(const magc_block_shape_t* sh, const magc_block_par
         // Recompute_Forward: zxbcdt, (x | B | C), dt, y, normalised y of this segment
         BLK_TRY(forward_segment(d, sh, p, ws, w, ws + w.zx, ws + w.y, u_seg, rows, ssm_in, conv_in, nullptr, nullptr, st));
         BLK_TRY(backward_segment(d, sh, p, g, ws, w, ws + w.zx, ws + w.y, u_seg, (const char*)dout + (size_t)t0 * d.dm * 2,
-                                 (char*)du + (size_t)t0 * d.dm * 2, rows, ssm_in, conv_in, dssm_out, dconv_out, dssm_in, dconv_in, st));
+                                 (char*)du + (size_t)t0 * d.dm * 2, rows, ssm_in, conv_in, dssm_out, dconv_out, dssm_in, dconv_in, st, nullptr, nullptr, true));
     }
     return SSD_OK;
 }
@@ -661,25 +712,6 @@ extern "C" int magc_block_bwd(const magc_block_shape_t* sh, const magc_block_par
 // layer's two state adjoints being handed to the cell on its left.
 namespace ssdk {
 namespace {
-
-// dst = a + b, bf16, 16-byte vectors (n a multiple of 8)
-__global__ __launch_bounds__(256) void k_add_bf16(bf16_t* dst, const bf16_t* a, const bf16_t* b, int64_t n8) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (int64_t)gridDim.x * 256) {
-        const b8 x = *(const b8*)((const __bf16*)a + i * 8), y = *(const b8*)((const __bf16*)b + i * 8);
-        b8 o;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = (__bf16)((float)x[e] + (float)y[e]);
-        *(b8*)((__bf16*)dst + i * 8) = o;
-    }
-}
-
-hipError_t add_bf16(void* dst, const void* a, const void* b, int64_t n, hipStream_t st) {
-    if (n == 0) return hipSuccess;
-    const int64_t n8 = n / 8, blocks = (n8 + 255) / 256;
-    hipLaunchKernelGGL(k_add_bf16, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, st, (bf16_t*)dst, (const bf16_t*)a,
-                       (const bf16_t*)b, n8);
-    return hipGetLastError();
-}
 
 struct StackDims {
     BlockDims b;
@@ -792,12 +824,11 @@ extern "C" int magc_blockstack_fwd(const magc_blockstack_shape_t* sh, const magc
         const magc_block_shape_t c = cell_shape(sh, rows);
         const bool last = k + 1 == d.b.nseg;
         const char* cur = (const char*)x0 + (size_t)t0 * row;
+        BlockDims dc;
+        BLK_TRY(check(&c, &dc));
+        char* un = ws + w.inner + layout(dc, false).un;  // where the next layer's block looks for its normalised input
+        bool normed = false;
         for (int j = 0; j < d.NL; ++j) {
-            if (j && j % d.l == 0) {  // layer-axis checkpoint: the input of layer j for these tokens
-                char* slot = (char*)l_ckpt + ((size_t)(j / d.l - 1) * d.b.L + t0) * row;
-                BLK_HIP(launch_copy_f32((float*)slot, (const float*)cur, (size_t)rows * d.b.dm / 2, st));  // bf16 pairs as words
-                cur = slot;
-            }
             // sequence-axis checkpoints of layer j: slot k = the states entering segment k (slot 0 unused: zeros)
             float* sj = ssm_ckpt ? ssm_ckpt + (size_t)j * d.b.nseg * d.b.HPN : nullptr;
             char* cj = conv_ckpt ? (char*)conv_ckpt + (size_t)j * d.b.nseg * d.conv_state : nullptr;
@@ -807,9 +838,11 @@ extern "C" int magc_blockstack_fwd(const magc_blockstack_shape_t* sh, const magc
             void* conv_out = last ? (void*)(ws + w.fin_conv) : (void*)(cj + (size_t)(k + 1) * d.conv_state);
             char* y = ws + w.act[j & 1];
             BLK_TRY(block_fwd(&c, &params[j], cur, ssm_in, conv_in, y, nullptr, nullptr, ssm_out, conv_out, ws + w.inner, w.inner_bytes,
-                              false, st));
-            char* nxt = j + 1 == d.NL ? (char*)out + (size_t)t0 * row : y;  // x_{j+1} = x_j + Block_j(x_j)
-            BLK_HIP(add_bf16(nxt, cur, y, rows * d.b.dm, st));
+                              false, st, normed));
+            // the input of the next layer: the stack's output, a layer-axis checkpoint, or a buffer
+            char* nxt = j + 1 == d.NL ? (char*)out + (size_t)t0 * row
+                                      : (j + 1) % d.l == 0 ? (char*)l_ckpt + ((size_t)((j + 1) / d.l - 1) * d.b.L + t0) * row : y;
+            BLK_TRY(residual(dc, c.eps, nxt, cur, y, rows, j + 1 < d.NL ? params[j + 1].pre_norm_w : nullptr, un, nullptr, nullptr, 0, &normed, st));
             cur = nxt;
         }
     }
@@ -865,20 +898,21 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
             // Recompute_Forward of Alg. 2: from the cell's layer checkpoint and its layers' state checkpoints,
             // the input x_j, zxbcdt_j and y_j of every layer of the cell
             const char* xin = m ? (const char*)l_ckpt + ((size_t)(m - 1) * d.b.L + t0) * row : (const char*)x0 + (size_t)t0 * row;
+            bool normed = false;
             for (int j = j0; j <= j1; ++j) {
                 const float* ssm_in = k ? ssm_ckpt + ((size_t)j * d.b.nseg + k) * d.b.HPN : nullptr;
                 const void* conv_in = k ? (const char*)conv_ckpt + ((size_t)j * d.b.nseg + k) * d.conv_state : nullptr;
                 char* zx = ws + w.zx + (size_t)(j - j0) * w.zx_bytes;
                 char* y = ws + w.y + (size_t)(j - j0) * w.y_bytes;
-                BLK_TRY(seg_in_proj(dc, c.eps, &params[j], bws, bw, xin, rows, zx, st));
+                BLK_TRY(seg_in_proj(dc, c.eps, &params[j], bws, bw, xin, rows, zx, st, normed));
                 BLK_TRY(seg_mid(dc, &params[j], bws, bw, zx, rows, conv_in, nullptr, st));
-                BLK_TRY(seg_scan(dc, &params[j], bws, bw, rows, ssm_in, nullptr, y, st));
+                BLK_TRY(seg_scan(dc, &params[j], bws, bw, zx, rows, ssm_in, nullptr, y, st));
                 if (j < j1) {  // the next layer's input
                     BLK_TRY(seg_norm(dc, &c, &params[j], bws, bw, zx, y, rows, st));
                     char* out = ws + w.act[0];
                     BLK_TRY(ssd_linear_fwd(rows, d.b.d_inner, d.b.dm, bws + bw.yn, 0, params[j].W_out, out, 0, st));
                     char* nxt = ws + w.xs + (size_t)(j - j0 + 1) * d.act;
-                    BLK_HIP(add_bf16(nxt, xin, out, rows * d.b.dm, st));
+                    BLK_TRY(residual(dc, c.eps, nxt, xin, out, rows, params[j + 1].pre_norm_w, bws + bw.un, nullptr, nullptr, 0, &normed, st));
                     xin = nxt;
                 }
             }
@@ -890,18 +924,19 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
                 const void* conv_in = k ? (const char*)conv_ckpt + ((size_t)j * d.b.nseg + k) * d.conv_state : nullptr;
                 const char* zx = ws + w.zx + (size_t)(j - j0) * w.zx_bytes;
                 const char* y = ws + w.y + (size_t)(j - j0) * w.y_bytes;
-                // the cheap steps again from zxbcdt_j and y_j: (x | B | C), dt, the normalised y
-                BLK_TRY(seg_mid(dc, &params[j], bws, bw, zx, rows, conv_in, nullptr, st));
+                // the cheap steps again from zxbcdt_j and y_j: (x | B | C), the normalised y.  The cell's top layer was
+                // restored last: its (x | B | C) and the normalised input of its projection are still in their places
+                const bool top = j == j1;
+                if (!top) BLK_TRY(seg_mid(dc, &params[j], bws, bw, zx, rows, conv_in, nullptr, st));
                 BLK_TRY(seg_norm(dc, &c, &params[j], bws, bw, zx, y, rows, st));
                 // this layer's state adjoints: written for segment k into buffer k % 2, read by segment k - 1 from it
                 float* dssm_w = (float*)(ws + w.dssm + ((size_t)j * 2 + (k & 1)) * d.b.HPN * 4);
                 float* dconv_w = (float*)(ws + w.dconv + ((size_t)j * 2 + (k & 1)) * d.conv_adj);
                 const float* dssm_r = last ? nullptr : (const float*)(ws + w.dssm + ((size_t)j * 2 + ((k + 1) & 1)) * d.b.HPN * 4);
                 const float* dconv_r = last ? nullptr : (const float*)(ws + w.dconv + ((size_t)j * 2 + ((k + 1) & 1)) * d.conv_adj);
-                BLK_TRY(backward_segment(dc, &c, &params[j], &grads[j], bws, bw, zx, y, xj, dcur, ws + w.du, rows, ssm_in, conv_in, dssm_r,
-                                         dconv_r, k ? dssm_w : nullptr, k ? dconv_w : nullptr, st));
                 char* dnext = (j == 0) ? (char*)dx0 + (size_t)t0 * row : ws + w.dcur;
-                BLK_HIP(add_bf16(dnext, dcur, ws + w.du, rows * d.b.dm, st));
+                BLK_TRY(backward_segment(dc, &c, &params[j], &grads[j], bws, bw, zx, y, xj, dcur, dnext, rows, ssm_in, conv_in, dssm_r,
+                                         dconv_r, k ? dssm_w : nullptr, k ? dconv_w : nullptr, st, dcur, ws + w.du, top));
                 dcur = dnext;
             }
         }
@@ -940,17 +975,15 @@ extern "C" int magc_blockstack_infer(const magc_blockstack_shape_t* sh, const ma
         if (bw.total > w.inner_bytes) return SSD_ERR_WORKSPACE;
         char* bws = ws + w.inner;
         const bool zero = fresh && k == 0;
-        // a few tokens: the recurrence runs on the layer's SSM state itself; a segment: through a spare state
-        const bool in_place = rows <= DECODE_ROWS;
+        bool normed = false;  // the layer before has left this one's normalised input
         bool packed = false;  // the layer before has left this one's packed input
         const char* cur = (const char*)x0 + (size_t)t0 * row;
         for (int j = 0; j < d.NL; ++j) {
             float* sj = ssm_state + (size_t)j * d.b.HPN;
             char* cj = (char*)conv_state + (size_t)j * d.conv_state;
-            float* ssm_out = in_place ? sj : (float*)(ws + w.fin_ssm);
+            float* ssm_out = sj;  // in place: the recurrence of a few tokens, or one segment's scan
             char* y = ws + w.act[j & 1];
             char* nxt = j + 1 == d.NL ? (char*)out + (size_t)t0 * row : y;  // x_{j+1} = x_j + Block_j(x_j)
-            bool conv_moved = false;
             if (few_path(dc, &params[j], rows, ssm_out, cur, nxt)) {
                 // generation: the residual and the move of the convolution state ride on the output product
                 FewSeqs sq;
@@ -961,16 +994,15 @@ extern "C" int magc_blockstack_infer(const magc_blockstack_shape_t* sh, const ma
                     sq.pack_next = packed = next;
                     sq.next_norm = next ? params[j + 1].pre_norm_w : nullptr;
                 }
-                conv_moved = true;
+                normed = false;
                 BLK_TRY(forward_few(dc, &c, &params[j], bws, bw, cur, rows, zero ? nullptr : sj, zero ? nullptr : cj, ssm_out,
                                     ws + w.fin_conv, nxt, cur, sq, st));
             } else {
-                BLK_TRY(magc_block_fwd(&c, &params[j], cur, zero ? nullptr : sj, zero ? nullptr : cj, y, nullptr, nullptr, ssm_out,
-                                       ws + w.fin_conv, ws + w.inner, w.inner_bytes, st));
-                BLK_HIP(add_bf16(nxt, cur, y, rows * d.b.dm, st));
+                BLK_TRY(block_fwd(&c, &params[j], cur, zero ? nullptr : sj, zero ? nullptr : cj, y, nullptr, nullptr, ssm_out, ws + w.fin_conv,
+                                  ws + w.inner, w.inner_bytes, true, st, normed));
+                BLK_TRY(residual(dc, c.eps, nxt, cur, y, rows, j + 1 < d.NL ? params[j + 1].pre_norm_w : nullptr, bws + bw.un, ws + w.fin_conv, cj,
+                                 d.conv_state, &normed, st));
             }
-            if (!in_place) BLK_HIP(launch_copy_f32(sj, ssm_out, d.b.HPN, st));
-            if (!conv_moved) BLK_HIP(launch_copy_f32((float*)cj, (const float*)(ws + w.fin_conv), d.conv_state / 4, st));  // bf16 pairs as words
             cur = nxt;
         }
     }

@@ -39,6 +39,7 @@ struct IO;
 template <>
 struct IO<float> {
     static __device__ __forceinline__ float ld(const void* p, size_t i) { return ((const float*)p)[i]; }
+    static __device__ __forceinline__ float round(float v) { return v; }
     static __device__ __forceinline__ void st(void* p, int64_t i, float v) { ((float*)p)[i] = v; }
     static __device__ __forceinline__ void ld4(float (&v)[4], const void* p, size_t i) {  // i a multiple of 4, 16-byte aligned
         const float4 q = *(const float4*)((const float*)p + i);
@@ -48,6 +49,7 @@ struct IO<float> {
 template <>
 struct IO<bf16_t> {
     static __device__ __forceinline__ float ld(const void* p, size_t i) { return bf16_to_float(((const bf16_t*)p)[i]); }
+    static __device__ __forceinline__ float round(float v) { return bf16_to_float(float_to_bf16(v)); }
     static __device__ __forceinline__ void st(void* p, int64_t i, float v) { ((bf16_t*)p)[i] = float_to_bf16(v); }
     static __device__ __forceinline__ void ld4(float (&v)[4], const void* p, size_t i) {
         const uint2 q = *(const uint2*)((const bf16_t*)p + i);
@@ -324,7 +326,8 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_scores_states(SegParams sp, Vec
         for (int e = 0; e < QMAX / NTHREADS; ++e) {
             const int i = tid * E + e;
             const bool live = e < E && i < V;
-            d[e] = live ? IO<T>::ld(sp.dt, (int64_t)b * sp.dts_b + ((int64_t)c * Q + i) * sp.H + h) : 0.f;
+            if (sp.raw.dt) d[e] = live ? IO<T>::round(softplus(IO<T>::ld(sp.raw.dt, ((int64_t)c * Q + i) * sp.raw.rs + h) + sp.raw.bias[h])) : 0.f;
+            else d[e] = live ? IO<T>::ld(sp.dt, (int64_t)b * sp.dts_b + ((int64_t)c * Q + i) * sp.H + h) : 0.f;
             run += d[e] * A + ((live && sp.reset && sp.reset[(int64_t)b * sp.reset_bs + (int64_t)c * Q + i]) ? RESET_LOG_DECAY : 0.f);
             a[e] = run;
         }

@@ -54,17 +54,26 @@ __device__ __forceinline__ void prep_body(const SegParams& sp, int c, int h, int
     typedef float vec __attribute__((ext_vector_type(E)));
     const int lane = threadIdx.x & 63, rows = chunk_rows(sp, c, Q);
     if (h >= sp.H) return;
-    const bf16_t* dt = (const bf16_t*)sp.dt + (int64_t)b * sp.dts_b + (int64_t)c * Q * sp.H + h;
+    const bool raw = sp.raw.dt;
+    const int64_t rs = raw ? sp.raw.rs : sp.H;
+    const bf16_t* dt = (raw ? (const bf16_t*)sp.raw.dt : (const bf16_t*)sp.dt + (int64_t)b * sp.dts_b) + (int64_t)c * Q * rs + h;
     const uint8_t* reset = sp.reset ? sp.reset + (int64_t)b * sp.reset_bs + (int64_t)c * Q : nullptr;
     const float A = sp.A[h];
     float d[E], a[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int i = E * lane + e, il = i < rows ? i : rows - 1;
-        d[e] = bf16_to_float(dt[(int64_t)il * sp.H]);
+        d[e] = bf16_to_float(dt[il * rs]);
         a[e] = reset && reset[il] ? RESET_LOG_DECAY : 0.f;
-        if (i >= rows) d[e] = a[e] = 0.f;
     }
+    if (raw) {  // uniform
+        const float bias = sp.raw.bias[h];
+#pragma unroll
+        for (int e = 0; e < E; ++e) d[e] = bf16_to_float(float_to_bf16(softplus(d[e] + bias)));
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (E * lane + e >= rows) d[e] = a[e] = 0.f;
 #pragma unroll
     for (int e = 0; e < E; ++e) a[e] += d[e] * A;
     // prefix sums by doubling: token i adds token i - off, off = 1, 2, 4, ...

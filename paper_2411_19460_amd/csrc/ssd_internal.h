@@ -38,6 +38,16 @@ __host__ __device__ inline bf16_t float_to_bf16(float f) {
     return o;
 }
 
+// The step sizes as a block's input projection leaves them: dt = softplus(dt + bias), rounded to the storage type; rows rs
+// elements apart, one batch.  dt NULL: none.
+struct RawDt {
+    const void* dt;
+    int64_t rs;
+    const float* bias;
+};
+// max(v, 0) + log(1 + e^-|v|): no overflow
+static __device__ __forceinline__ float softplus(float v) { return fmaxf(v, 0.f) + log1pf(__expf(-fabsf(v))); }
+
 // One span of one layer, as the kernels see it: one or several consecutive checkpoint segments that share their
 // launches.  Tensor pointers are already offset to the first token of the span; batch strides are those of the
 // full tensors (elements).
@@ -47,6 +57,7 @@ struct SegParams {
     int seg_chunks;                    // chunks per checkpoint segment (== nc when the span is one segment)
     int64_t xs_b, ys_b, dys_b, dxs_b;  // batch strides of x, y, dy, dx
     int64_t dts_b, bcs_b;              // of dt/ddt and of B/C/dB/dC
+    RawDt raw;                         // dt as it leaves a projection (raw.dt set: dt is not read)
     const uint8_t* reset;              // optional [Bt][tokens of the segment]: non-zero = a packed sequence starts here
     int64_t reset_bs;                  // its batch stride
     uint32_t flags;
@@ -258,6 +269,36 @@ int conv1d_fwd_split(const ssd_conv_shape_t* sh, const void* u, const float* w, 
 int conv1d_bwd_split(const ssd_conv_shape_t* sh, const void* u, const float* w, const float* bias, const void* state_in,
                      const ConvSplit& dout, const float* dstate_out, void* du, float* dw, float* dbias, float* dstate_in,
                      void* workspace, size_t workspace_bytes, uint32_t flags, hipStream_t st);
+
+// ssd_fwd / ssd_bwd with the step sizes still to be formed (raw.dt set: dt is ignored; batch 1).
+int scan_fwd(const ssd_shape_t* shape, const void* x, const void* dt, const RawDt& raw, const float* A, const void* B, const void* C,
+             const float* D, const float* init_state, void* y, float* final_state, void* boundary_states, void* workspace,
+             size_t workspace_bytes, uint32_t flags, hipStream_t st);
+int scan_bwd(const ssd_shape_t* shape, const void* x, const void* dt, const RawDt& raw, const float* A, const void* B, const void* C,
+             const float* D, const float* init_state, const void* dy, const float* dfinal_state, const void* boundary_states, void* dx,
+             void* ddt, float* dA, void* dB, void* dC, float* dD, float* dinit_state, void* workspace, size_t workspace_bytes,
+             uint32_t flags, hipStream_t st);
+
+// sum = a + b, rounded to bf16, dense rows of `dim`, and out = RMS normalisation of the rounded sum times w, in one pass;
+// copy_bytes bytes (a multiple of 16) moved from copy_src to copy_dst by the same launch.  sum may be a or b.
+struct ResidualJob {
+    int64_t rows;
+    int dim;
+    const void *a, *b;
+    void* sum;
+    const float* w;
+    void* out;
+    float eps;
+    const void* copy_src;
+    void* copy_dst;
+    size_t copy_bytes;
+};
+bool residual_norm_supported(const ResidualJob& j);
+hipError_t launch_residual_norm(const ResidualJob& j, hipStream_t st);
+// ssd_gated_norm_bwd without a gate, with dy = (its dy) + res, rounded once; all rows dense, dy may be res.
+bool norm_bwd_residual_supported(const ssd_norm_shape_t* sh, const void* y, const void* dout, const void* res, const void* dy);
+int norm_bwd_residual(const ssd_norm_shape_t* sh, const void* y, const float* w, const void* dout, const void* res, void* dy, float* dw,
+                      void* workspace, size_t workspace_bytes, uint32_t flags, hipStream_t st);
 
 // True when everything is to stay on the caller's stream (SSD_MAGC_SERIAL=1 in the environment, or ssd_prof_serialize).
 bool serial_mode();
