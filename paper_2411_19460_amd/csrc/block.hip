@@ -323,6 +323,7 @@ struct FewSeqs {
     // and the output is to be packed for the layer behind, whose norm weight (null: none) is next_norm
     bool packed_in = false, pack_next = false;
     const float* next_norm = nullptr;
+    bool stream_w = false, stream_s = false;  // weights, SSM states by streaming accesses
 };
 
 int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_block_params_t* p, char* ws, const BlockWs& w,
@@ -336,6 +337,7 @@ int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_blo
     in.K = d.dm;
     in.N = d.d_in_proj;
     in.mode = p->pre_norm_w ? 1 : 0;
+    in.stream = sq.stream_w;
     in.x = u;
     if (sq.packed_in) {
         in.mode = 2;
@@ -371,6 +373,7 @@ int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_blo
     const bool stepped = tokens == 1 && conv_in && sq.conv_final == conv_in && (sq.nb == 1 || sq.conv_final_bs == (size_t)sq.conv_in_bs * 2) &&
                          step_supported(mid);
     mid.stepped = stepped;
+    mid.stream = sq.stream_s;
     in.ldx = d.dm;
     in.w = p->W_in;
     in.out = ws + w.zx;
@@ -409,6 +412,7 @@ int forward_few(const BlockDims& d, const magc_block_shape_t* sh, const magc_blo
     o.K = d.d_inner;
     o.N = d.dm;
     o.w = p->W_out;
+    o.stream = sq.stream_w;
     o.out = out;
     o.ldo = d.dm;
     o.ldx = d.d_inner;
@@ -944,6 +948,23 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
     return SSD_OK;
 }
 
+// What of layer j the last-level cache (256 MiB) keeps from one generation step to the next.  A step touches the weights and
+// states of every layer once, in the same order: more than fits, fetched the plain way, leaves nothing of it for the next
+// step (each layer finds what the layers behind it left).  So the first layers' weights are fetched plainly, as many as fit
+// beside what else a step writes, and the others by streaming loads, which leave the cache as it is; states likewise stream
+// once they are no small part of it (reading and writing back what the step before wrote costs more than it saves).
+// Microseconds a step of eight layers, plain -> all streamed -> this: 80 heads (645 MB of weights), 1 / 3 / 16 sequences 208 /
+// 282 / 389 -> 197 / 263 / 346 -> 191 / 256 / 338; 64 heads (414 MB), 16: 334 -> 297 -> 280; weights that fit, 32 heads
+// (105 MB), 16: 161 -> 157 -> 150, 3: 131 -> 139 -> 131.
+// States, plain against streamed: 42 MB (80 heads, 2 sequences) 222.3 / 223.2, 59 MB (32, 7) 133.1 / 131.5, 67 MB (64, 4)
+// 231 / 218, 168 MB (64, 16) 301 / 280.
+void cache_plan(const StackDims& d, int nseq, int j, FewSeqs* sq) {
+    const int64_t cache = (int64_t)224 << 20;  // 32 MiB are left to activations and what runs between the steps
+    const int64_t weights = (int64_t)(d.b.d_in_proj + d.b.d_inner) * d.b.dm * 2, states = (int64_t)d.NL * nseq * d.b.HPN * 4;
+    sq->stream_s = states > ((int64_t)48 << 20);
+    sq->stream_w = (j + 1) * weights > cache - (sq->stream_s ? 0 : states);
+}
+
 // Forward only, nothing kept: the stack as a language model runs it at inference.  The states of every layer
 // live in two caller-owned arrays and are replaced by the states behind the last token of the call, so a
 // prompt of any length (in segments: memory does not grow with it) and then single tokens are the same call.
@@ -987,6 +1008,7 @@ extern "C" int magc_blockstack_infer(const magc_blockstack_shape_t* sh, const ma
             if (few_path(dc, &params[j], rows, ssm_out, cur, nxt)) {
                 // generation: the residual and the move of the convolution state ride on the output product
                 FewSeqs sq;
+                cache_plan(d, 1, j, &sq);
                 sq.conv_final = cj;
                 if (rows > FEW_ROWS_VALU) {
                     const bool next = j + 1 < d.NL && few_path(dc, &params[j + 1], rows, ssm_out, nxt, out);
@@ -1047,6 +1069,7 @@ extern "C" int magc_blockstack_decode(const magc_blockstack_shape_t* sh_in, cons
         char* cj = (char*)conv_state + (size_t)j * d.conv_state;
         char* nxt = j + 1 == d.NL ? (char*)out : ws + w.act[j & 1];
         FewSeqs sq;
+        cache_plan(d, nseq, j, &sq);
         sq.nb = nseq;
         sq.ssm_bs = (int64_t)d.NL * d.b.HPN;
         sq.conv_in_bs = (int64_t)d.NL * 3 * d.b.conv_dim;

@@ -28,6 +28,17 @@ __device__ __forceinline__ float wave_sum(float v) {
 // what storing a value in bf16 and reading it back leaves of it
 __device__ __forceinline__ float through_bf16(float v) { return (float)(__bf16)v; }
 
+// Streaming accesses: data that is gone from the last-level cache before it is read again would only push out of it what is not.
+template <bool STREAM, typename V>
+__device__ __forceinline__ V fetch(const V* p) {
+    return STREAM ? __builtin_nontemporal_load(p) : *p;
+}
+template <bool STREAM, typename V>
+__device__ __forceinline__ void put(V* p, V v) {
+    if (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 struct FewParams {
     const __bf16 *x, *w, *res;
     __bf16* out;
@@ -69,7 +80,8 @@ struct FewOperands {
     int64_t cs_bs;
     const float *conv_w, *conv_b, *dt_bias;
     int off_xbc, off_dt, conv_dim;
-    int ks;  // matrix-core kernel: waves
+    int ks;       // matrix-core kernel: waves
+    bool stream;  // w by streaming loads
 };
 
 // What the step of column n needs besides the product: asked for when the kernel starts, and not touched before the end
@@ -118,14 +130,14 @@ __device__ __forceinline__ void move_pieces(const FewOperands& fo, int threads) 
     }
 }
 
-template <int MODE, int R, int CPW>
+template <int MODE, int R, int CPW, bool STREAM>
 struct FewStep {
     bf16x8 wv[CPW], xv[R];
     float iw[MODE ? 8 : 1];
 
     __device__ __forceinline__ void load(const FewParams& fp, const __bf16* w0, int k) {
 #pragma unroll
-        for (int c = 0; c < CPW; ++c) wv[c] = *(const bf16x8*)(w0 + (int64_t)c * fp.K + k);
+        for (int c = 0; c < CPW; ++c) wv[c] = fetch<STREAM>((const bf16x8*)(w0 + (int64_t)c * fp.K + k));
         if (MODE) {
             const f32x4 a = *(const f32x4*)(fp.in_w + k), b = *(const f32x4*)(fp.in_w + k + 4);
 #pragma unroll
@@ -163,7 +175,7 @@ struct FewStep {
 // long row alone waits for one load after the other: more, shorter waves keep more bytes in flight); their
 // partial sums meet in LDS.
 // STEP: with the convolution step (fo.cs).  A template argument like MODE: a branch around loads ends in a wait for them.
-template <int MODE, int R, int CPW, int KS, bool STEP>
+template <int MODE, int R, int CPW, int KS, bool STEP, bool STREAM>
 __global__ __launch_bounds__(256) void k_linear_few(FewParams fp, FewOperands fo) {
     __shared__ float red[4][R * (CPW + 1)];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -184,7 +196,7 @@ __global__ __launch_bounds__(256) void k_linear_few(FewParams fp, FewOperands fo
     constexpr int KSTEP = 512 * KS;  // k between a wave's consecutive steps
     if (live) {
         for (int k = lane * 8 + 512 * kp; k < fp.K; k += 2 * KSTEP) {
-            FewStep<MODE, R, CPW> a, b;
+            FewStep<MODE, R, CPW, STREAM> a, b;
             const bool two = k + KSTEP < fp.K;
             a.load(fp, w0, k);
             if (two) b.load(fp, w0, k + KSTEP);
@@ -224,18 +236,19 @@ __global__ __launch_bounds__(256) void k_linear_few(FewParams fp, FewOperands fo
     fp.out[fr * fp.ldo + fn] = STEP ? step_finish(fo, taps, fr, fn, ob) : ob;
 }
 
-template <int MODE, int CPW, int KS, bool STEP>
+template <int MODE, int CPW, int KS, bool STEP, bool STREAM>
 hipError_t launch_few_cks(const FewParams& fp, const FewOperands& fo, hipStream_t st) {
     const int slots = (fp.N + CPW - 1) / CPW;  // groups of CPW columns
     const dim3 grid((unsigned)((slots + 4 / KS - 1) / (4 / KS))), block(256);
-    if (fp.rows <= 1) hipLaunchKernelGGL((k_linear_few<MODE, 1, CPW, KS, STEP>), grid, block, 0, st, fp, fo);
-    else hipLaunchKernelGGL((k_linear_few<MODE, FEW_ROWS_VALU, CPW, KS, STEP>), grid, block, 0, st, fp, fo);
+    if (fp.rows <= 1) hipLaunchKernelGGL((k_linear_few<MODE, 1, CPW, KS, STEP, STREAM>), grid, block, 0, st, fp, fo);
+    else hipLaunchKernelGGL((k_linear_few<MODE, FEW_ROWS_VALU, CPW, KS, STEP, STREAM>), grid, block, 0, st, fp, fo);
     return hipGetLastError();
 }
 
 template <int MODE, int CPW, int KS>
 hipError_t launch_few_ck(const FewParams& fp, const FewOperands& fo, hipStream_t st) {
-    return fo.cs ? launch_few_cks<MODE, CPW, KS, true>(fp, fo, st) : launch_few_cks<MODE, CPW, KS, false>(fp, fo, st);
+    if (fo.stream) return fo.cs ? launch_few_cks<MODE, CPW, KS, true, true>(fp, fo, st) : launch_few_cks<MODE, CPW, KS, false, true>(fp, fo, st);
+    return fo.cs ? launch_few_cks<MODE, CPW, KS, true, false>(fp, fo, st) : launch_few_cks<MODE, CPW, KS, false, false>(fp, fo, st);
 }
 
 // Long rows (the block's two products): four columns per wave share the fetched (and transformed) input rows --
@@ -290,7 +303,7 @@ static_assert(MAX_GROUPS * 16 <= 16 * 17, "");
 // x in_w, 1 / rms scales the finished sums).  SRC 2: packed rows, already times in_w, with `ssq` the partial
 // sums of squares of their producer (nparts per group of K / groups, row r of part i at ssq[16 i + r]).  SRC 3: packed rows,
 // no normalisation.  PARTS: row_parts(rows) (SRC 0: 1, rows of x are bf16 values as they are).
-template <int SRC, bool STEP, int PARTS>
+template <int SRC, bool STEP, int PARTS, bool STREAM>
 __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams fp, FewOperands fo) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int KS = fo.ks, nthr = 64 * KS, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -322,7 +335,7 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int n = n0 + 2 * j + r2;
-            v[j] = *(const bf16x8*)(fp.w + (int64_t)(n < fp.N ? n : fp.N - 1) * fp.K + kc);
+            v[j] = fetch<STREAM>((const bf16x8*)(fp.w + (int64_t)(n < fp.N ? n : fp.N - 1) * fp.K + kc));
         }
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
@@ -454,24 +467,26 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
     move_pieces(fo, nthr);
 }
 
-template <int SRC, bool STEP, int PARTS>
+template <int SRC, bool STEP, int PARTS, bool STREAM>
 hipError_t launch_few_mfma_kernel(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
     static bool raised[64];  // per device: long rows take more dynamic LDS than the default limit
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!raised[dev]) {
-        const hipError_t e = hipFuncSetAttribute((const void*)k_linear_few_mfma<SRC, STEP, PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        const hipError_t e = hipFuncSetAttribute((const void*)k_linear_few_mfma<SRC, STEP, PARTS, STREAM>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  (int)few_mfma_lds(MFMA_WAVES));
         if (e != hipSuccess) return e;
         raised[dev] = true;
     }
-    hipLaunchKernelGGL((k_linear_few_mfma<SRC, STEP, PARTS>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
+    hipLaunchKernelGGL((k_linear_few_mfma<SRC, STEP, PARTS, STREAM>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
     return hipGetLastError();
 }
 
 template <int SRC, int PARTS>
 hipError_t launch_few_mfma_parts(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
-    return fo.cs ? launch_few_mfma_kernel<SRC, true, PARTS>(fp, fo, wgs, lds, st) : launch_few_mfma_kernel<SRC, false, PARTS>(fp, fo, wgs, lds, st);
+    if (fo.stream)
+        return fo.cs ? launch_few_mfma_kernel<SRC, true, PARTS, true>(fp, fo, wgs, lds, st) : launch_few_mfma_kernel<SRC, false, PARTS, true>(fp, fo, wgs, lds, st);
+    return fo.cs ? launch_few_mfma_kernel<SRC, true, PARTS, false>(fp, fo, wgs, lds, st) : launch_few_mfma_kernel<SRC, false, PARTS, false>(fp, fo, wgs, lds, st);
 }
 
 template <int SRC>
@@ -622,7 +637,7 @@ __global__ __launch_bounds__(256) void k_decode_mid(MidParams mp) {
 // the recurrence and the gate, nothing else.  16-byte accesses to the state (N a multiple of 4, N <= 128 NV): half a
 // wave owns U consecutive rows, lane l of the half the columns 4 l .. 4 l + 3 (+ 128 i).  Everything is asked for at once,
 // so what bounds it is the state's way in and out (16 sequences of 80 heads: 84 MB).
-template <int NV, int U>
+template <int NV, int U, bool STREAM>
 __global__ __launch_bounds__(256) void k_decode_step(MidParams mp) {
     __shared__ float sq[8];
     const int h = blockIdx.x, b = blockIdx.y, g = h / mp.hpg, N = mp.N, tid = threadIdx.x, l32 = tid & 31, hw = tid >> 5;
@@ -630,14 +645,14 @@ __global__ __launch_bounds__(256) void k_decode_step(MidParams mp) {
     const __bf16* zx = mp.zx + (int64_t)b * mp.ld;
     const __bf16* xb = zx + mp.off_xbc;
     float* S = mp.state + b * mp.state_bs + (int64_t)h * mp.P * N;
-    float4 s[U][NV];
+    f32x4 s[U][NV];
     bf16x4 bv[NV], cv[NV];
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int p = p0 + u < mp.P ? p0 + u : mp.P - 1, n = 4 * l32 + 128 * i;
-            s[u][i] = *(const float4*)(S + (int64_t)p * N + (n < N ? n : 0));
+            s[u][i] = fetch<STREAM>((const f32x4*)(S + (int64_t)p * N + (n < N ? n : 0)));
         }
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
@@ -660,15 +675,15 @@ __global__ __launch_bounds__(256) void k_decode_step(MidParams mp) {
         acc[u] = 0.f;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            float4& q = s[u][i];
-            q.x = a * q.x + dx * (float)bv[i][0];
-            q.y = a * q.y + dx * (float)bv[i][1];
-            q.z = a * q.z + dx * (float)bv[i][2];
-            q.w = a * q.w + dx * (float)bv[i][3];
+            f32x4& q = s[u][i];
+            q[0] = a * q[0] + dx * (float)bv[i][0];
+            q[1] = a * q[1] + dx * (float)bv[i][1];
+            q[2] = a * q[2] + dx * (float)bv[i][2];
+            q[3] = a * q[3] + dx * (float)bv[i][3];
             const int p = p0 + u, n = 4 * l32 + 128 * i;
             if (n < N) {
-                acc[u] += ((float)cv[i][0] * q.x + (float)cv[i][1] * q.y) + ((float)cv[i][2] * q.z + (float)cv[i][3] * q.w);
-                if (p < mp.P) *(float4*)(S + (int64_t)p * N + n) = q;
+                acc[u] += ((float)cv[i][0] * q[0] + (float)cv[i][1] * q[1]) + ((float)cv[i][2] * q[2] + (float)cv[i][3] * q[3]);
+                if (p < mp.P) put<STREAM>((f32x4*)(S + (int64_t)p * N + n), q);
             }
         }
     }
@@ -709,13 +724,13 @@ int step_rows(int H, int P, int nb) {
     return hn * ((P + 63) / 64) >= 768 ? 8 : hn * ((P + 31) / 32) >= 256 ? 4 : 1;
 }
 
-template <int NV>
+template <int NV, bool STREAM>
 void launch_step(const MidParams& mp, int nb, hipStream_t st) {
     const int u = step_rows(mp.H, mp.P, nb);
     const dim3 grid(mp.H, nb, (mp.P + 8 * u - 1) / (8 * u));
-    if (u == 8) hipLaunchKernelGGL((k_decode_step<NV, 8>), grid, dim3(256), 0, st, mp);
-    else if (u == 4) hipLaunchKernelGGL((k_decode_step<NV, 4>), grid, dim3(256), 0, st, mp);
-    else hipLaunchKernelGGL((k_decode_step<NV, 1>), grid, dim3(256), 0, st, mp);
+    if (u == 8) hipLaunchKernelGGL((k_decode_step<NV, 8, STREAM>), grid, dim3(256), 0, st, mp);
+    else if (u == 4) hipLaunchKernelGGL((k_decode_step<NV, 4, STREAM>), grid, dim3(256), 0, st, mp);
+    else hipLaunchKernelGGL((k_decode_step<NV, 1, STREAM>), grid, dim3(256), 0, st, mp);
 }
 
 bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -770,6 +785,7 @@ hipError_t launch_linear_few_rows(const FewRowsJob& j, hipStream_t st) {
     fo.pack_out = (__bf16*)j.pack_out;
     fo.pack_w = j.pack_w;
     fo.pack_ssq = j.pack_ssq;
+    fo.stream = j.stream;
     fo.cs = (__bf16*)j.cs;
     fo.cs_bs = j.cs_bs;
     fo.conv_w = j.conv_w;
@@ -829,8 +845,13 @@ hipError_t launch_decode_mid(const DecodeMidJob& j, hipStream_t st) {
     mp.pack_ssq = j.pack_ssq;
     if (j.stepped) {
         if (!step_supported(j) || (j.pack && (!j.gate || !j.pack_w || !j.pack_ssq))) return hipErrorInvalidValue;
-        if (j.N <= 128) launch_step<1>(mp, nb, st);
-        else launch_step<2>(mp, nb, st);
+        if (j.stream) {
+            if (j.N <= 128) launch_step<1, true>(mp, nb, st);
+            else launch_step<2, true>(mp, nb, st);
+        } else {
+            if (j.N <= 128) launch_step<1, false>(mp, nb, st);
+            else launch_step<2, false>(mp, nb, st);
+        }
         return hipGetLastError();
     }
     if (j.pack) return hipErrorInvalidValue;

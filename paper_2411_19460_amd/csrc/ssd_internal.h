@@ -353,6 +353,7 @@ struct FewRowsJob {
     int64_t cs_bs;
     const float *conv_w, *conv_b, *dt_bias;
     int off_xbc, off_dt;
+    bool stream;  // w by streaming loads: it will not be in a cache when it is read again
 };
 bool few_rows_supported(const FewRowsJob& j);  // sizes, strides and 16-byte alignment the kernel relies on
 hipError_t launch_linear_few_rows(const FewRowsJob& j, hipStream_t st);
@@ -379,6 +380,7 @@ struct DecodeMidJob {
     void* pack;
     const float* pack_w;
     float* pack_ssq;
+    bool stream;  // stepped: the states by streaming accesses
 };
 bool step_supported(const DecodeMidJob& j);
 int step_parts(const DecodeMidJob& j);

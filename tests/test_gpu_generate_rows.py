@@ -61,6 +61,34 @@ def test_generation_step_from_given_states(shape):
             check(f"sequence {i} layer {j} conv state", host(conv[i, j]), fo["conv_states"][j], tol)
 
 
+@pytest.mark.parametrize("shape", [
+    # layers, d_model, H, P, N, sequences
+    (3, 2560, 80, 64, 128, 1),   # 242 MB of weights: the last layer's stream
+    (3, 2560, 80, 64, 128, 2),
+    (3, 2560, 80, 64, 128, 5),   # and 63 MB of states: they stream in every layer, four rows per half wave
+    (4, 1024, 32, 64, 256, 8),   # 67 MB of states of 256 columns
+    (7, 64, 120, 64, 248, 1),    # 53 MB of states, a row per half wave, the last columns missing
+])
+def test_generation_step_of_stacks_larger_than_the_cache(shape):
+    """Weights and states fetched by streaming loads: output and both states as above."""
+    NL, dm, H, P, N, nseq = shape
+    r = np.random.default_rng(79)
+    conv_dim = block_ref.dims(None, H, P, 1, N)[1]
+    layers_h = [draw(60 + j, 1, dm, H, P, 1, N, True)["p"] for j in range(NL)]
+    x = BF(r.standard_normal((nseq, dm)))
+    ssm_h, conv_h = F32(r.standard_normal((nseq, NL, H, P, N)) * 0.3), BF(r.standard_normal((nseq, NL, 3, conv_dim)))
+    ssm, conv = torch.from_numpy(ssm_h.astype(np.float32)).cuda(), dev_bf16(conv_h)
+    out = pk.magc_blockstack_decode(dev_bf16(x), [to_dev(p) for p in layers_h], H, P, 1, N, 128, 128, ssm, conv)["out"]
+    torch.cuda.synchronize()
+    tol = NL * TOL["bf16"]
+    for i in range(nseq):
+        fo = block_ref.stack_fwd(x[i:i + 1], layers_h, H, P, 1, N, 1e-5, store=synth.round_bf16, conv_states=conv_h[i], ssm_states=ssm_h[i])
+        check(f"sequence {i} out", host(out[i:i + 1]), fo["out"], tol)
+        for j in range(NL):
+            check(f"sequence {i} layer {j} ssm state", host(ssm[i, j]), fo["ssm_states"][j], tol)
+            check(f"sequence {i} layer {j} conv state", host(conv[i, j]), fo["conv_states"][j], tol)
+
+
 @pytest.mark.parametrize("rows", [3, 16])
 @pytest.mark.parametrize("K", [2048, 2056, 5120])
 def test_products_of_few_long_rows(rows, K):
