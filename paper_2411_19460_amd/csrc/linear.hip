@@ -9,8 +9,8 @@
 // contiguous ("k-major": rows of x for the forward product) or with it as the row index (x and dout for
 // dw, w for dx).  Both kinds are staged in LDS exactly as they lie in memory (16-byte vectors); k-major
 // tiles are read back as plain 16-byte operands, the others through the transposing LDS read.
-// One kernel, three tilings: 256 x 256, 256 x 192 or 256 x 128 per workgroup (eight waves of 64 x 128 / 96 / 64, one
-// workgroup per compute unit, loads straight to LDS two K steps ahead); the launch rule below chooses the one whose tiles
+// One scheme of tiles, three widths: 256 x 256, 256 x 192 or 256 x 128 per workgroup (eight waves of 64 x 128 / 96 / 64, one
+// workgroup per compute unit, loads straight to LDS two K steps ahead); the two gradient products share a launch, and the launch rule below chooses the one whose tiles
 // fit the machine best.  Workgroup ids are remapped so that each XCD works on a compact
 // block of the tile grid (its L2 then holds the A and B panels that block shares).
 #include <stdint.h>
@@ -38,12 +38,11 @@ struct GemmParams {
     int accumulate;  // fp32 only: C += product
 };
 
-// Tile of this workgroup.  Hardware hands consecutive workgroup ids to the eight XCDs in turn; id -> (id % 8,
+// Tile `id` of the product.  Hardware hands consecutive workgroup ids to the eight XCDs in turn; id -> (id % 8,
 // id / 8) gives every XCD a contiguous eighth of a walk that goes down groups of eight row tiles column by
 // column, so the workgroups resident on one XCD at a time share a few A row panels and B column panels.
-__device__ __forceinline__ void tile_of(const GemmParams& gp, int& tm, int& tn) {
+__device__ __forceinline__ void tile_of(const GemmParams& gp, int id, int& tm, int& tn) {
     const int nt = gp.tiles_m * gp.tiles_n;
-    int id = blockIdx.x;
     if (nt % 8 == 0) id = (id & 7) * (nt >> 3) + (id >> 3);
     const int per_group = 8 * gp.tiles_n;
     const int grp = id / per_group, in = id - grp * per_group;
@@ -323,13 +322,14 @@ struct Big {
     }
 };
 
+extern __shared__ __attribute__((aligned(1024))) char lds[];  // the K steps in flight; at the end the patches of the result
+
 template <bool AK, bool BK, int WJ>
-__global__ __launch_bounds__(GTHR, 1) void k_gemm_big(GemmParams gp) {
+__device__ __forceinline__ void gemm_tile(const GemmParams& gp, int id) {
     constexpr int BM = 256, BN = 64 * WJ;
-    extern __shared__ __attribute__((aligned(1024))) char lds[];  // the K steps in flight; at the end the patches of the result
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     int tm, tn;
-    tile_of(gp, tm, tn);
+    tile_of(gp, id, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
 
     typedef Big<AK, BK, WJ> Gemm;
@@ -393,22 +393,68 @@ __global__ __launch_bounds__(GTHR, 1) void k_gemm_big(GemmParams gp) {
     }
 }
 
+template <int WJ>
+__global__ __launch_bounds__(GTHR, 1) void k_gemm_big(GemmParams gp) {
+    gemm_tile<true, true, WJ>(gp, blockIdx.x);
+}
+
+// The gradient products of a call, of the input (64 WX columns a tile) and of the weights (64 WW), in one launch: workgroups
+// first .. run the second.  They are independent (both read dout; they write dx and dw), and one alone often leaves compute
+// units idle: a segment of 4096 rows gives the input gradient of the 2.7B block's input projection 160 tiles for 256 units.
+// As two launches on two streams they met only behind a fork and a join, some 20 us a pair, and in whatever order the queues
+// were served: us at 4096 rows, two launches -> one, 2560 <-> 10576 375 -> 372, 2560 <-> 5120 227 -> 174, 1024 <-> 4384 95 -> 87,
+// 1024 <-> 2048 73 -> 53; 600 rows 154 -> 145, 81 -> 60, 61 -> 50, 40 -> 19.
+template <int WX, int WW>
+__global__ __launch_bounds__(GTHR, 1) void k_gemm_grads(GemmParams px, GemmParams pw, int dw_first, int first) {
+    const bool second = (int)blockIdx.x >= first;
+    const int id = second ? blockIdx.x - first : blockIdx.x;
+    if (second == (dw_first != 0)) gemm_tile<true, false, WX>(px, id);
+    else gemm_tile<false, false, WW>(pw, id);
+}
+
 bool ok_ptr(const void* p) { return p && ((uintptr_t)p & 15) == 0; }
 
 template <bool AK, bool BK, int WJ>
-hipError_t launch_big(GemmParams gp, hipStream_t st) {
-    constexpr int BN = 64 * WJ, PATCHES = 8 * 64 * (64 * WJ + 16), LDS = Big<AK, BK, WJ>::LDS > PATCHES ? Big<AK, BK, WJ>::LDS : PATCHES;
-    static bool raised[64];  // per device: the kernel uses more dynamic LDS than the default limit
+constexpr int big_lds() {
+    constexpr int PATCHES = 8 * 64 * (64 * WJ + 16);
+    return Big<AK, BK, WJ>::LDS > PATCHES ? Big<AK, BK, WJ>::LDS : PATCHES;
+}
+
+// The kernels use more dynamic LDS than the default limit; `raised`: per device.
+hipError_t allow_lds(const void* kernel, int bytes, bool (&raised)[64]) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    if (!raised[dev]) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_gemm_big<AK, BK, WJ>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        if (e != hipSuccess) return e;
-        raised[dev] = true;
-    }
+    if (raised[dev]) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    raised[dev] = e == hipSuccess;
+    return e;
+}
+
+int set_tiles(GemmParams& gp, int wj) {
     gp.tiles_m = (gp.M + 255) / 256;
-    gp.tiles_n = (gp.N + BN - 1) / BN;
-    hipLaunchKernelGGL((k_gemm_big<AK, BK, WJ>), dim3(gp.tiles_m * gp.tiles_n), dim3(GTHR), LDS, st, gp);
+    gp.tiles_n = (gp.N + 64 * wj - 1) / (64 * wj);
+    return gp.tiles_m * gp.tiles_n;
+}
+
+template <int WJ>
+hipError_t launch_big(GemmParams gp, hipStream_t st) {
+    constexpr int LDS = big_lds<true, true, WJ>();
+    static bool raised[64];
+    const hipError_t e = allow_lds((const void*)k_gemm_big<WJ>, LDS, raised);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_gemm_big<WJ>), dim3(set_tiles(gp, WJ)), dim3(GTHR), LDS, st, gp);
+    return hipGetLastError();
+}
+
+// Without dx or dw: the other alone.
+template <int WX, int WW>
+hipError_t launch_grads(GemmParams px, GemmParams pw, bool dx, bool dw, bool dw_first, hipStream_t st) {
+    constexpr int LX = big_lds<true, false, WX>(), LW = big_lds<false, false, WW>(), LDS = LX > LW ? LX : LW;
+    static bool raised[64];
+    const hipError_t e = allow_lds((const void*)k_gemm_grads<WX, WW>, LDS, raised);
+    if (e != hipSuccess) return e;
+    const int tx = dx ? set_tiles(px, WX) : 0, tw = dw ? set_tiles(pw, WW) : 0;
+    hipLaunchKernelGGL((k_gemm_grads<WX, WW>), dim3(tx + tw), dim3(GTHR), LDS, st, px, pw, dw_first, dw_first ? tw : tx);
     return hipGetLastError();
 }
 
@@ -437,53 +483,46 @@ int forward_width(const GemmParams& gp) {
 // 512 KB in and out for every compute unit at once), half of that at 128 columns.  Side by side the two products fill the
 // machine together: while all tiles are resident at once the longer chain counts; else the work spread over the machine plus
 // two fifths of a chain of ragged end, and no less than a short tile in front of a long one.  Over six pairs of widths from
-// 768 to 10576 and 100 ... 16384 rows the rule is 1.4 % off the best of the four combinations (6 % with the K steps alone).
-// 2560 <-> 10576, us for (256, 256), chosen: 200 rows 196, 139; 4096 rows 389, 389; 1024 <-> 4384, 4096 rows 113, 96.
+// 768 to 10576 and 100 ... 16384 rows the rule is 1.5 % off the best of the four combinations (6 % with the K steps alone).
+// The product of the longer tiles goes first: the others then fill the units that its last round leaves idle, instead of the
+// long ones running on alone.  2560 <-> 10576 (longer: the input's), 4096 rows: 379 us, the other way round 458; 2560 <-> 5120
+// (longer: the weights'), 4096 rows 186, the other way round 223.
+// (256, 256), chosen: 2560 <-> 10576, 200 rows 185, 128; 1024 <-> 4384, 4096 rows 92, 89.
 int64_t tile_cost(const GemmParams& gp, int wj) {
     const int64_t around = gp.c_f32 ? (wj == 4 ? 2000 : 1100) : (wj == 4 ? 400 : 200);
     return (int64_t)((gp.K + BKK - 1) / BKK) * (wj == 4 ? 100 : 66) + around;
 }
-void backward_widths(const GemmParams* dx, const GemmParams* dw, bool together, int& wx, int& ww) {
+void backward_widths(const GemmParams* dx, const GemmParams* dw, int& wx, int& ww, bool& dw_first) {
     int64_t best = INT64_MAX;
-    wx = ww = 4;
     for (int a = 4; a >= 2; a -= 2)
         for (int b = 4; b >= 2; b -= 2) {
             const int64_t ta = dx ? tile_count(*dx, a) : 0, ca = dx ? tile_cost(*dx, a) : 0;
             const int64_t tb = dw ? tile_count(*dw, b) : 0, cb = dw ? tile_cost(*dw, b) : 0;
             int64_t t;
-            if (!together) {
+            if (!dx || !dw) {
                 t = (ta + UNITS - 1) / UNITS * ca + (tb + UNITS - 1) / UNITS * cb;
             } else {
                 const int64_t longer = ca > cb ? ca : cb, spread = (ta * ca + tb * cb) / UNITS + longer * 2 / 5;
                 t = ta + tb <= UNITS ? longer : (spread > ca + cb ? spread : ca + cb);
             }
-            if (t < best) best = t, wx = a, ww = b;
+            if (t < best) best = t, wx = a, ww = b, dw_first = cb > ca;
         }
 }
 
-// The two gradient products of a call are independent (both read dout; they write dx and dw).  One of them
-// alone often leaves compute units idle -- a segment of 4096 rows gives the input gradient of the 2.7B block's
-// input projection 160 tiles for 256 units -- so the weight gradient runs on a library stream of default
-// priority, forked from and joined into the caller's stream with events, and the two fill the machine together.
-struct Side {
-    hipStream_t st = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
-    SideStream outer;  // the same stream with a pair of events of its own, for callers inside the library
-    bool ok = false;
-};
 std::mutex g_side_mu;
 
 // Created on first use on a device (or by ssd_init), under a lock; a partial failure releases what was created.
-Side* side_for_current_device() {
-    static Side sides[64];
+SideStream* side_for_current_device() {
+    static SideStream sides[64];
+    static bool ok[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
     std::lock_guard<std::mutex> lock(g_side_mu);
-    Side& s = sides[dev];
-    if (s.ok) return &s;
-    Side q;
+    if (ok[dev]) return &sides[dev];
+    SideStream q;
+    memset(&q, 0, sizeof(q));
     bool good = hipStreamCreateWithFlags(&q.st, hipStreamNonBlocking) == hipSuccess;
-    hipEvent_t* evs[] = {&q.fork, &q.join, &q.outer.fork, &q.outer.join};
+    hipEvent_t* evs[] = {&q.fork, &q.join};
     for (hipEvent_t* e : evs) good = good && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
     if (!good) {
         for (hipEvent_t* e : evs)
@@ -491,19 +530,15 @@ Side* side_for_current_device() {
         if (q.st) (void)hipStreamDestroy(q.st);
         return nullptr;
     }
-    q.outer.st = q.st;
-    q.ok = true;
-    s = q;
-    return &s;
+    sides[dev] = q;
+    ok[dev] = true;
+    return &sides[dev];
 }
 
 }  // namespace
 
-SideStream* side_stream() {
-    if (serial_mode()) return nullptr;
-    Side* s = side_for_current_device();
-    return s ? &s->outer : nullptr;
-}
+// A library stream of default priority, forked from and joined into the caller's stream with events.
+SideStream* side_stream() { return serial_mode() ? nullptr : side_for_current_device(); }
 
 namespace {
 
@@ -555,7 +590,7 @@ extern "C" int ssd_linear_fwd(int64_t rows, int32_t in_dim, int32_t out_dim, con
     gp.K = in_dim;
     const int wj = forward_width(gp);
     const hipStream_t st = (hipStream_t)hip_stream;
-    const hipError_t e = wj == 4 ? launch_big<true, true, 4>(gp, st) : wj == 3 ? launch_big<true, true, 3>(gp, st) : launch_big<true, true, 2>(gp, st);
+    const hipError_t e = wj == 4 ? launch_big<4>(gp, st) : wj == 3 ? launch_big<3>(gp, st) : launch_big<2>(gp, st);
     return e == hipSuccess ? SSD_OK : SSD_ERR_LAUNCH;
 }
 
@@ -600,22 +635,14 @@ extern "C" int ssd_linear_bwd(int64_t rows, int32_t in_dim, int32_t out_dim, con
     pw.K = (int)rows;
     pw.c_f32 = 1;
     pw.accumulate = accumulate;
-    // both products wanted: the weight gradient goes to the side stream (see Side)
-    Side* side = dx && dw && !serial_mode() ? side_for_current_device() : nullptr;
-    hipStream_t st_w = st;
-    if (side) {
-        if (hipEventRecord(side->fork, st) != hipSuccess || hipStreamWaitEvent(side->st, side->fork, 0) != hipSuccess) return SSD_ERR_LAUNCH;
-        st_w = side->st;
-    }
+    if (!dx && !dw) return SSD_OK;
     int wx, ww;
-    backward_widths(dx ? &px : nullptr, dw ? &pw : nullptr, side != nullptr, wx, ww);
-    int status = SSD_OK;
-    if (dx && (wx == 4 ? launch_big<true, false, 4>(px, st) : launch_big<true, false, 2>(px, st)) != hipSuccess) status = SSD_ERR_LAUNCH;
-    if (dw && status == SSD_OK && (ww == 4 ? launch_big<false, false, 4>(pw, st_w) : launch_big<false, false, 2>(pw, st_w)) != hipSuccess)
-        status = SSD_ERR_LAUNCH;
-    // whatever reached the side stream ends before the caller's next work, also after a failed launch
-    if (side && (hipEventRecord(side->join, side->st) != hipSuccess || hipStreamWaitEvent(st, side->join, 0) != hipSuccess)) return SSD_ERR_LAUNCH;
-    return status;
+    bool dw_first;
+    backward_widths(dx ? &px : nullptr, dw ? &pw : nullptr, wx, ww, dw_first);
+    hipError_t e;
+    if (wx == 4) e = ww == 4 ? launch_grads<4, 4>(px, pw, dx, dw, dw_first, st) : launch_grads<4, 2>(px, pw, dx, dw, dw_first, st);
+    else e = ww == 4 ? launch_grads<2, 4>(px, pw, dx, dw, dw_first, st) : launch_grads<2, 2>(px, pw, dx, dw, dw_first, st);
+    return e == hipSuccess ? SSD_OK : SSD_ERR_LAUNCH;
 }
 
 // Calibration: what the matrix cores deliver when nothing else is in the way -- every wave issues

@@ -305,8 +305,6 @@ bool serial_mode();
 
 // The library's side stream of the current device (default priority, created on first use) with a pair of
 // events for the caller to fork it from and join it into its own stream; NULL in serial mode or on failure.
-// ssd_linear_bwd enqueues on the same stream with events of its own, so work given to it here and the
-// products of such a call run in the order they were enqueued.
 struct SideStream {
     hipStream_t st;
     hipEvent_t fork, join;

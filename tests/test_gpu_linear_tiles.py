@@ -61,3 +61,24 @@ def test_linear_weight_gradient_is_added_to():
     acc = one.clone()
     pk.ssd_linear_bwd(x, w, dout, want_dx=False, dw=acc, flags=pk.SSD_FLAG_ACCUM_PARAM)
     assert torch.equal(acc, one + one)
+
+
+@pytest.mark.parametrize("shape", [
+    # rows, in_dim, out_dim: each pair of tile widths (input's, weights' gradient), each product first, tiles cut at the edges
+    (72, 264, 136),       # 256, 128; the weights' first
+    (1300, 2568, 2056),   # 256, 128; the input's first
+    (72, 264, 520),       # 128, 128; the weights'
+    (72, 264, 1032),      # 128, 128; the input's
+    (72, 264, 2056),      # 128, 256; the input's
+    (1000, 2568, 2056),   # 128, 256; the weights'
+    (2049, 1544, 3080),   # 256, 256; the input's
+    (2049, 2568, 2056),   # 256, 256; the weights'
+])
+def test_linear_gradients_of_one_launch(shape):
+    """Both gradients of a call against each of them alone: same bits, as a result is summed in the same order at any width."""
+    rows, K, N = shape
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x, w, dout = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((rows, K), (N, K), (rows, N)))
+    both = pk.ssd_linear_bwd(x, w, dout)
+    assert torch.equal(both["dx"], pk.ssd_linear_bwd(x, w, dout, want_dw=False)["dx"])
+    assert torch.equal(both["dw"], pk.ssd_linear_bwd(x, w, dout, want_dx=False)["dw"])
