@@ -499,19 +499,47 @@ int residual(const BlockDims& d, float eps, void* nxt, const void* cur, const vo
     return SSD_OK;
 }
 
+// Zeros for the small parameter gradients of a block, to which every segment adds: one launch.
+struct SmallGrads {
+    float* p[7];
+    int n[7];
+};
+__global__ __launch_bounds__(256) void k_clear_small(SmallGrads sg) {
+    float* p = sg.p[blockIdx.y];
+    const int n = p ? sg.n[blockIdx.y] : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e = (blockIdx.x * 4 + i) * 256 + threadIdx.x;
+        if (e < n) p[e] = 0.f;
+    }
+}
+hipError_t clear_small(const BlockDims& d, const magc_block_grads_t& g, bool pre_norm, hipStream_t st) {
+    const SmallGrads sg = {{g.dconv_w, g.dconv_b, g.ddt_bias, g.dA, g.dD, g.dnorm_w, pre_norm ? g.dpre_norm_w : nullptr},
+                           {4 * d.conv_dim, d.conv_dim, d.H, d.H, d.H, d.d_inner, d.dm}};
+    const int most = 4 * d.conv_dim > d.dm ? 4 * d.conv_dim : d.dm;  // conv_dim > d_inner
+    hipLaunchKernelGGL(k_clear_small, dim3((most + 1023) / 1024, 7), dim3(256), 0, st, sg);
+    return hipGetLastError();
+}
+hipError_t clear_weights(const BlockDims& d, const magc_block_grads_t& g, hipStream_t st) {
+    const hipError_t e = launch_fill_zero(g.dW_in, (size_t)d.d_in_proj * d.dm, st);
+    return e != hipSuccess ? e : launch_fill_zero(g.dW_out, (size_t)d.dm * d.d_inner, st);
+}
+
 // The reverse of every step of a segment, given its forward activations (zx, y from the caller; x / B / C
 // and the normalised y in the workspace): du of the segment (+ res, if given: the gradient that goes round the block in a
 // residual stream; du_seg may be res), parameter gradients added to `g`, the adjoints of the two states entering the segment.
-// normed: the normalised input of the projection is still in its place.  du_tmp: rows of d_model for a gradient that res is
+// fresh_w: the gradients of the two weight matrices are stored, not added to (the first segment of a call; 2560 x (10576 +
+// 5120) of them are 161 MB to clear and to read).  normed: the normalised input of the projection is still in its place.  du_tmp: rows of d_model for a gradient that res is
 // added to in a pass of its own.
 int backward_segment(const BlockDims& d, const magc_block_shape_t* sh, const magc_block_params_t* p, const magc_block_grads_t* g,
                      char* ws, const BlockWs& w, const char* zx, const char* y, const void* u_seg, const void* dout_seg, void* du_seg,
                      int64_t rows, const float* ssm_in, const void* conv_in, const float* dssm_out, const float* dconv_out,
-                     float* dssm_in, float* dconv_in, hipStream_t st, const void* res = nullptr, void* du_tmp = nullptr, bool normed = false) {
-    const uint32_t acc = SSD_FLAG_ACCUM_PARAM;
+                     float* dssm_in, float* dconv_in, hipStream_t st, bool fresh_w, const void* res = nullptr, void* du_tmp = nullptr,
+                     bool normed = false) {
+    const uint32_t acc = SSD_FLAG_ACCUM_PARAM, acc_w = fresh_w ? 0 : acc;
     char* dzx = ws + w.dzx;
     // output projection
-    BLK_TRY(ssd_linear_bwd(rows, d.d_inner, d.dm, ws + w.yn, 0, p->W_out, dout_seg, 0, ws + w.dyn, 0, g->dW_out, acc, st));
+    BLK_TRY(ssd_linear_bwd(rows, d.d_inner, d.dm, ws + w.yn, 0, p->W_out, dout_seg, 0, ws + w.dyn, 0, g->dW_out, acc_w, st));
     // gated normalisation: dy, and dz straight into its columns of d zxbcdt
     const ssd_norm_shape_t ns = norm_shape(d, rows, sh->eps);
     BLK_TRY(ssd_gated_norm_bwd(&ns, y, zx, p->norm_w, ws + w.dyn, ws + w.dy, dzx, g->dnorm_w, ws + w.inner, w.inner_bytes, acc, st));
@@ -536,11 +564,11 @@ int backward_segment(const BlockDims& d, const magc_block_shape_t* sh, const mag
     // a grid cell have used the buffer since this layer's forward steps)
     void* du = res ? du_tmp : du_seg;
     if (!p->pre_norm_w) {
-        BLK_TRY(ssd_linear_bwd(rows, d.dm, d.d_in_proj, u_seg, 0, p->W_in, dzx, 0, du, 0, g->dW_in, acc, st));
+        BLK_TRY(ssd_linear_bwd(rows, d.dm, d.d_in_proj, u_seg, 0, p->W_in, dzx, 0, du, 0, g->dW_in, acc_w, st));
     } else {
         const void* un = ws + w.un;
         if (!normed) BLK_TRY(seg_pre_norm(d, sh->eps, p, ws, w, u_seg, rows, &un, st));
-        BLK_TRY(ssd_linear_bwd(rows, d.dm, d.d_in_proj, un, 0, p->W_in, dzx, 0, ws + w.dun, 0, g->dW_in, acc, st));
+        BLK_TRY(ssd_linear_bwd(rows, d.dm, d.d_in_proj, un, 0, p->W_in, dzx, 0, ws + w.dun, 0, g->dW_in, acc_w, st));
         const ssd_norm_shape_t ps = pre_norm_shape(d, rows, sh->eps);
         if (res && norm_bwd_residual_supported(&ps, u_seg, ws + w.dun, res, du_seg))
             return norm_bwd_residual(&ps, u_seg, p->pre_norm_w, ws + w.dun, res, du_seg, g->dpre_norm_w, ws + w.inner, w.inner_bytes, acc, st);
@@ -663,16 +691,10 @@ extern "C" int magc_block_bwd(const magc_block_shape_t* sh, const magc_block_par
     if (!g || !g->dW_in || !g->dconv_w || !g->dconv_b || !g->ddt_bias || !g->dA || !g->dD || !g->dnorm_w || !g->dW_out) return SSD_ERR_NULL;
     if (p->pre_norm_w && !g->dpre_norm_w) return SSD_ERR_NULL;
     hipStream_t st = (hipStream_t)hip_stream;
-    if (!(flags & SSD_FLAG_ACCUM_PARAM)) {  // every segment adds to the parameter gradients
-        BLK_HIP(launch_fill_zero(g->dW_in, (size_t)d.d_in_proj * d.dm, st));
-        BLK_HIP(launch_fill_zero(g->dconv_w, (size_t)d.conv_dim * 4, st));
-        BLK_HIP(launch_fill_zero(g->dconv_b, (size_t)d.conv_dim, st));
-        BLK_HIP(launch_fill_zero(g->ddt_bias, (size_t)d.H, st));
-        BLK_HIP(launch_fill_zero(g->dA, (size_t)d.H, st));
-        BLK_HIP(launch_fill_zero(g->dD, (size_t)d.H, st));
-        BLK_HIP(launch_fill_zero(g->dnorm_w, (size_t)d.d_inner, st));
-        BLK_HIP(launch_fill_zero(g->dW_out, (size_t)d.dm * d.d_inner, st));
-        if (p->pre_norm_w) BLK_HIP(launch_fill_zero(g->dpre_norm_w, (size_t)d.dm, st));
+    const bool clear = !(flags & SSD_FLAG_ACCUM_PARAM);
+    if (clear) {
+        BLK_HIP(clear_small(d, *g, p->pre_norm_w != nullptr, st));
+        if (d.L == 0) BLK_HIP(clear_weights(d, *g, st));
     }
     if (d.L == 0) {  // the state adjoints pass through
         if (dinit_ssm) BLK_HIP(dfinal_ssm ? launch_copy_f32(dinit_ssm, dfinal_ssm, d.HPN, st) : launch_fill_zero(dinit_ssm, d.HPN, st));
@@ -700,7 +722,8 @@ extern "C" int magc_block_bwd(const magc_block_shape_t* sh, const magc_block_par
         // Recompute_Forward: zxbcdt, (x | B | C), dt, y, normalised y of this segment
         BLK_TRY(forward_segment(d, sh, p, ws, w, ws + w.zx, ws + w.y, u_seg, rows, ssm_in, conv_in, nullptr, nullptr, st));
         BLK_TRY(backward_segment(d, sh, p, g, ws, w, ws + w.zx, ws + w.y, u_seg, (const char*)dout + (size_t)t0 * d.dm * 2,
-                                 (char*)du + (size_t)t0 * d.dm * 2, rows, ssm_in, conv_in, dssm_out, dconv_out, dssm_in, dconv_in, st, nullptr, nullptr, true));
+                                 (char*)du + (size_t)t0 * d.dm * 2, rows, ssm_in, conv_in, dssm_out, dconv_out, dssm_in, dconv_in, st,
+                                 clear && last, nullptr, nullptr, true));
     }
     return SSD_OK;
 }
@@ -867,19 +890,18 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
             return SSD_ERR_NULL;
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t row = (size_t)d.b.dm * 2;
-    if (!(flags & SSD_FLAG_ACCUM_PARAM)) {  // every cell adds to the parameter gradients of its layers
+    const bool clear = !(flags & SSD_FLAG_ACCUM_PARAM);
+    // layer j is the only one to add to its weights' gradients (tied layers share them)
+    auto own = [&](int j) {
+        for (int i = 0; i < d.NL; ++i)
+            if (i != j && (grads[i].dW_in == grads[j].dW_in || grads[i].dW_out == grads[j].dW_out)) return false;
+        return true;
+    };
+    if (clear)
         for (int j = 0; j < d.NL; ++j) {
-            BLK_HIP(launch_fill_zero(grads[j].dW_in, (size_t)d.b.d_in_proj * d.b.dm, st));
-            BLK_HIP(launch_fill_zero(grads[j].dconv_w, (size_t)d.b.conv_dim * 4, st));
-            BLK_HIP(launch_fill_zero(grads[j].dconv_b, (size_t)d.b.conv_dim, st));
-            BLK_HIP(launch_fill_zero(grads[j].ddt_bias, (size_t)d.b.H, st));
-            BLK_HIP(launch_fill_zero(grads[j].dA, (size_t)d.b.H, st));
-            BLK_HIP(launch_fill_zero(grads[j].dD, (size_t)d.b.H, st));
-            BLK_HIP(launch_fill_zero(grads[j].dnorm_w, (size_t)d.b.d_inner, st));
-            BLK_HIP(launch_fill_zero(grads[j].dW_out, (size_t)d.b.dm * d.b.d_inner, st));
-            if (params[j].pre_norm_w) BLK_HIP(launch_fill_zero(grads[j].dpre_norm_w, (size_t)d.b.dm, st));
+            BLK_HIP(clear_small(d.b, grads[j], params[j].pre_norm_w != nullptr, st));
+            if (d.b.L == 0 || !own(j)) BLK_HIP(clear_weights(d.b, grads[j], st));
         }
-    }
     if (d.b.L == 0) return SSD_OK;
     if (!x0 || !dout || !dx0 || (d.ngl > 1 && !l_ckpt) || (d.b.nseg > 1 && (!ssm_ckpt || !conv_ckpt))) return SSD_ERR_NULL;
     const StackWs w = stack_layout(sh, d, true);
@@ -940,7 +962,7 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
                 const float* dconv_r = last ? nullptr : (const float*)(ws + w.dconv + ((size_t)j * 2 + ((k + 1) & 1)) * d.conv_adj);
                 char* dnext = (j == 0) ? (char*)dx0 + (size_t)t0 * row : ws + w.dcur;
                 BLK_TRY(backward_segment(dc, &c, &params[j], &grads[j], bws, bw, zx, y, xj, dcur, dnext, rows, ssm_in, conv_in, dssm_r,
-                                         dconv_r, k ? dssm_w : nullptr, k ? dconv_w : nullptr, st, dcur, ws + w.du, top));
+                                         dconv_r, k ? dssm_w : nullptr, k ? dconv_w : nullptr, st, clear && last && own(j), dcur, ws + w.du, top));
                 dcur = dnext;
             }
         }
