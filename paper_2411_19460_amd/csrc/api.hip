@@ -379,14 +379,16 @@ static int lane_cap() {
 //    of those hold less than four full ones do.  With four, 65536 tokens of 24 heads in segments of 1024 take 2410 us
 //    instead of 1627, 32768 of 80 heads 2107 instead of 1866, 4096 fp32 tokens of 24 heads in segments of 256 578 instead
 //    of 432.
-//  - A sequence of few units altogether (ONE_SPAN_UNITS) is one span: nothing to order, no events.  Matrix-core kernels, 80
-//    heads: 8192 tokens (2560 units) 424 us instead of 526 on lanes, 12288 (3840) 655 instead of 679; 32768 of 24 heads (3072)
-//    555 instead of 649.  Beyond it lanes still cost more where there are few segments (16384 of 80 heads, 5120 units: 856
-//    us, as one span 779); at 24576 (7680) it is 2 %.
+//  - A sequence of few units altogether (ONE_SPAN_UNITS) is one span: nothing to order, no events, full launches, and no more
+//    scratch than on lanes (fewer partial sums: 304 MB instead of 379 for 16384 tokens of 80 heads).  Matrix-core kernels, us
+//    on lanes -> as one span.  At the line, 5120 units: 16384 of 80 heads 863 -> 794 (chunks of 128 1022 -> 955, forward only
+//    232 -> 190), 2 x 8192 of 64 722 -> 634.  Below: 32768 of 32 (4096 units) 765 -> 681, 49152 of 24 (4608) 887 -> 828, in
+//    chunks of 128 1092 -> 988, 31000 of 32 in chunks of 64 1353 -> 1248.  Above it goes either way: 24576 of 80 (7680) 1222 ->
+//    1200, 40000 of 2 x 24 (7500) 1306 -> 1346, 65536 of 32 (8192) 1369 -> 1480.
 // Only the number of segments counts, not where the last one ends: the workspace query goes over these plans.
 void plan_dims(Dims* d, bool mfma, bool one_stream) {
     if (d->L == 0) return;
-    constexpr int64_t SPAN_UNITS = 640, ONE_SPAN_UNITS = 3840;
+    constexpr int64_t SPAN_UNITS = 640, ONE_SPAN_UNITS = 5120;
     const int64_t unit = d->Bt * d->H * ((d->Q + 63) / 64);  // quarter units: 64 tokens of a head
     const int64_t seg_units = d->nc_seg * unit / 4, all_units = d->nseg * seg_units;
     const int64_t inflight = seg_units >= SPAN_UNITS ? 4 : INFLIGHT;

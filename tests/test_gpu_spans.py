@@ -153,3 +153,25 @@ def test_generic_kernels_beyond_their_usual_sizes(case):
     for k, got, want in [("y", y, f["y"]), ("final_state", fin, f["final_state"])] + [
             (k, g[k], go[k]) for k in ("dx", "ddt", "dA", "dB", "dC", "dD", "dinit_state")]:
         check(k, host(got), want, TOL[dtype])
+
+
+@pytest.mark.parametrize("L,H,seg,Q", [
+    (16384, 80, 4096, 256),    # 5120 chunks of a head: the most that is one span
+    (16385, 80, 8192, 256),    # one row more: lanes
+    (40959, 32, 5120, 128),    # as many in eight segments, ragged
+])
+def test_the_largest_single_span_against_one_segment(L, H, seg, Q):
+    """Where the checkpoints fall does not change the result.  Tolerance: that of either run against the oracle."""
+    g = torch.Generator(device="cuda").manual_seed(11)
+    normal = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    x, Bm, Cm, dy = normal(1, L, H, 64), normal(1, L, 1, 128), normal(1, L, 1, 128), normal(1, L, H, 64)
+    dt = (torch.rand((1, L, H), generator=g, device="cuda") * 0.1).to(torch.bfloat16)
+    A, D = -torch.rand(H, generator=g, device="cuda") * 15 - 1, torch.randn(H, generator=g, device="cuda")
+    out = []
+    for s in (seg, -(-L // Q) * Q):
+        y, fin, bnd = pk.ssd_fwd(x, dt, A, Bm, Cm, D, Q, s)
+        b = pk.ssd_bwd(x, dt, A, Bm, Cm, D, dy, Q, s, boundary_states=bnd)
+        out.append({"y": y, "final": fin, **{k: b[k] for k in ("dx", "ddt", "dA", "dB", "dC", "dD")}})
+    torch.cuda.synchronize()
+    for k, t in out[0].items():
+        check(k, host(t), host(out[1][k]), TOL["bf16"])
