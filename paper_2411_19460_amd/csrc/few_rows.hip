@@ -29,6 +29,9 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ float through_bf16(float v) { return (float)(__bf16)v; }
 
 // Streaming accesses: data that is gone from the last-level cache before it is read again would only push out of it what is not.
+// Input product, output product and recurrence of a 2.7B block with 16 sequences, the layers whose weights do not stay in the
+// cache: 17.9, 10.7, 19.1 us with plain accesses, 15.8, 10.3, 16.7 so; with one sequence 14.0, 8.6 -> 13.5, 8.5.  A template argument:
+// as a branch around the loads it would end in a wait for them.
 template <bool STREAM, typename V>
 __device__ __forceinline__ V fetch(const V* p) {
     return STREAM ? __builtin_nontemporal_load(p) : *p;
