@@ -57,7 +57,6 @@ struct SegParams {
     int seg_chunks;                    // chunks per checkpoint segment (== nc when the span is one segment)
     int64_t xs_b, ys_b, dys_b, dxs_b;  // batch strides of x, y, dy, dx
     int64_t dts_b, bcs_b;              // of dt/ddt and of B/C/dB/dC
-    RawDt raw;                         // dt as it leaves a projection (raw.dt set: dt is not read)
     const uint8_t* reset;              // optional [Bt][tokens of the segment]: non-zero = a packed sequence starts here
     int64_t reset_bs;                  // its batch stride
     uint32_t flags;
@@ -141,6 +140,9 @@ struct SegParams {
     // optional cross-stream ordering of the state scans (consecutive segments run on different streams):
     // the scan waits for ev_wait and records ev_record when it has been enqueued
     hipEvent_t ev_wait, ev_record;
+    // dt as it leaves a projection (raw.dt set: dt is not read).  Last: in the middle it moved what the small kernels load first
+    // off its cache lines (512 fp32 tokens of 4 heads, eight launches: 64.2 -> 64.7 us)
+    RawDt raw;
 #ifdef SSDK_STAMPS
     unsigned long long* stamps;  // diagnostics build: cycle stamps of the head loops (see SSDK_STAMP)
 #endif
