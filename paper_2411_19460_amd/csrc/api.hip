@@ -59,6 +59,7 @@ int check_shape(const ssd_shape_t* sh, Dims* d) {
     d->nc = d->nc_seg = sh->seqlen > 0 ? (int)(sh->segment / sh->chunk) : 0;
     d->nseg = sh->seqlen > 0 ? (sh->seqlen + sh->segment - 1) / sh->segment : 0;
     d->F = d->nl = 1;
+    d->dg_f32 = false;
     d->nspan = d->nseg;
     d->nct = (sh->seqlen + sh->chunk - 1) / sh->chunk;
     d->bf16 = sh->dtype == SSD_BF16;
@@ -115,12 +116,17 @@ HeadSlices part_slices(const Dims& d, bool mfma, int wg_target) {
 // and add up.  Otherwise every pass gets a workgroup per compute unit and the three alternate.  Slices (dx, dG, head sums) by
 // this rule, 32 chunks of 24 heads: (8, 8, 4) -> (3, 3, 1): 75.2 -> 63.6 us, and the finalisation 19.0 -> 13.6; 16 chunks of
 // 80 heads, (16, 16, 8) -> (5, 5, 2): 114 -> 103 and 19.1 -> 14.2.
+// The slices' partial sums of dG are bf16 where there are as many as before, and rounded once more when they have been added
+// up.  Sums of two to seven such numbers often lie halfway between two others, so that fewer slices alone take dB and dC
+// further from 64 bits (eight -> three of 24 heads: 2.90e-3 -> 2.93e-3).  Fewer slices are therefore kept in fp32, 2.41e-3, at
+// 2 us of 118 for 8192 tokens of 24 heads; likewise in a span that lanes would cut into more slices (plan_dims).
 void fit_splits(SegParams& sp, const Dims& d, bool mfma, int wg_target) {
     const int64_t nc = sp.nc;
     const int a0 = dg_slices(d, mfma, wg_target).split(nc), p0 = part_slices(d, mfma, wg_target).split(nc);
     sp.dual_split = 0;
     sp.dg_split = a0;
     sp.part_split = p0;
+    sp.dg_f32 = mfma && d.dg_f32;
     if (!mfma || d.Q < 128 || wg_target < 256 || nc <= 0) return;
     // thousands of cycles of a workgroup around its heads and for each of them: dx, dG, head sums
     struct Cost { int64_t around[3], head[3]; };
@@ -137,8 +143,10 @@ void fit_splits(SegParams& sp, const Dims& d, bool mfma, int wg_target) {
     int64_t least = base * work / units + longest(a0, p0) / 2;
     for (int a = 1; a <= a0 && base * 2 * (a + 1) <= units; ++a) {
         if (d.hpg % a) continue;
+        const bool f32 = d.dg_f32 || (a > 1 && a < a0);  // fits: see ws_layout
         for (int p = 1; p <= p0 && base * 2 * (a + p) <= units; ++p)
-            if (d.hpg % p == 0 && longest(a, p) < least) least = longest(a, p), sp.dual_split = sp.dg_split = a, sp.part_split = p;
+            if (d.hpg % p == 0 && longest(a, p) < least)
+                least = longest(a, p), sp.dual_split = sp.dg_split = a, sp.part_split = p, sp.dg_f32 = f32;
     }
 }
 
@@ -170,9 +178,12 @@ WsLayout ws_layout(const Dims& d, bool bwd, bool mfma, int wg_target, bool fp32c
     if (bwd) {
         if (!mfma || fp32cs) w.dstates = take((size_t)d.Bt * d.nc * d.H * PN * 4);
         if (mfma) w.dstates_bf = take((size_t)d.Bt * d.nc * d.H * PN * 2);
-        {   // one partial sum per head slice: fp32 (generic kernels) or bf16 (MFMA kernels)
-            const size_t per = (size_t)d.Q * d.Q * (mfma ? 2 : 4);
-            w.dG = take((size_t)d.Bt * dg.slots(d.nc) * d.G * per);
+        {   // one partial sum per head slice: fp32 (generic kernels), bf16 (MFMA kernels), or fp32 of at most half a round of
+            // slices (fit_splits): at chunks of 256 no more than the general rule's bf16 ones
+            const int64_t bg = d.Bt * d.G, all = bg * d.nc * d.hpg;
+            int64_t slots = bg * dg.slots(d.nc) * (mfma && !d.dg_f32 ? 1 : 2);
+            if (mfma && d.Q == 128 && wg_target >= 256 && slots < 512) slots = all < 512 ? (slots > all ? slots : all) : 512;
+            w.dG = take((size_t)slots * d.Q * d.Q * 2);
         }
         w.dbc_part = take((size_t)d.Bt * part.slots(d.nc) * d.G * 2 * d.Q * d.N * 4);
         w.gterm = take(tok * (mfma ? 1 : 2 * nn));
@@ -388,7 +399,7 @@ static int lane_cap() {
 // Only the number of segments counts, not where the last one ends: the workspace query goes over these plans.
 void plan_dims(Dims* d, bool mfma, bool one_stream) {
     if (d->L == 0) return;
-    constexpr int64_t SPAN_UNITS = 640, ONE_SPAN_UNITS = 5120;
+    constexpr int64_t SPAN_UNITS = 640, LANE_UNITS = 3840, ONE_SPAN_UNITS = 5120;
     const int64_t unit = d->Bt * d->H * ((d->Q + 63) / 64);  // quarter units: 64 tokens of a head
     const int64_t seg_units = d->nc_seg * unit / 4, all_units = d->nseg * seg_units;
     const int64_t inflight = seg_units >= SPAN_UNITS ? 4 : INFLIGHT;
@@ -396,6 +407,7 @@ void plan_dims(Dims* d, bool mfma, bool one_stream) {
     if (!one_stream && d->nseg > 1) {
         if (d->nseg <= inflight && (all_units <= SPAN_UNITS || (mfma && all_units <= ONE_SPAN_UNITS))) {
             d->F = (int)d->nseg;
+            d->dg_f32 = mfma && all_units > LANE_UNITS;
         } else {
             while (d->F < inflight && d->F * seg_units < SPAN_UNITS) d->F *= 2;
             const int64_t spans = (d->nseg + d->F - 1) / d->F;

@@ -7,7 +7,7 @@
 //   mk_dG       : one workgroup per (batch, chunk, group, head slice); the whole lower triangle of dG
 //                 (36 tiles of 32 x 32 when Q = 256, four or five per wave) stays in accumulators while the workgroup walks
 //                 the heads of its slice; dY and x tiles are staged in LDS once per head (next head
-//                 prefetched in registers).  Writes one bf16 partial sum per slice and, per head, the
+//                 prefetched in registers).  Writes one partial sum per slice (bf16 or fp32) and, per head, the
 //                 chunk-local part of the gradient of cum: row sums minus column sums of
 //                 E = (dY x^T) (.) M, each element entering both with the same value, so that their
 //                 cancellation in the reverse cumulative sum is exact.
@@ -286,6 +286,18 @@ __device__ __forceinline__ void dg_emit_sums(const SegParams& sp, const DgLds<Q>
     }
 }
 
+template <int Q, typename T>
+__device__ __forceinline__ void dg_put(T* out, const f32x16 (&acc)[DgMap<Q>::MAXT], int cnt, int w, int lane) {
+    typedef DgMap<Q> M;
+#pragma unroll
+    for (int k = 0; k < M::MAXT; ++k)
+        if (k < cnt) {
+            T* o = out + ((M::ti(w, k) * M::NT + M::tj(w, k)) * 32 + 4 * (lane >> 5)) * 32 + (lane & 31);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[(8 * (r >> 2) + (r & 3)) * 32] = (T)acc[k][r];
+        }
+}
+
 template <int Q>
 __device__ __forceinline__ void dg_body(const SegParams& sp, DgLds<Q>& L, int z, int nblk) {
     typedef DgMap<Q> M;
@@ -353,16 +365,11 @@ __device__ __forceinline__ void dg_body(const SegParams& sp, DgLds<Q>& L, int z,
     }
     __syncthreads();
     dg_emit_sums<Q>(sp, L, rsrc, b, c, h0 + hps - 1, w, lane);
-    // partial sum of this slice, bf16, tile by tile: tile (ti, tj) is the 32 x 32 row-major block number ti NT + tj,
+    // partial sum of this slice, tile by tile: tile (ti, tj) is the 32 x 32 row-major block number ti NT + tj,
     // so that the pass that sums the slices reads whole cache lines (tiles above the diagonal are never touched)
-    __bf16* out = (__bf16*)sp.dG + ((((int64_t)b * sp.nc + c) * sp.G + g) * ns + slice) * ((int64_t)Q * Q);
-#pragma unroll
-    for (int k = 0; k < MAXT; ++k)
-        if (k < cnt) {
-            __bf16* o = out + ((M::ti(w, k) * M::NT + M::tj(w, k)) * 32 + 4 * (lane >> 5)) * 32 + (lane & 31);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[(8 * (r >> 2) + (r & 3)) * 32] = (__bf16)acc[k][r];
-        }
+    const int64_t out = ((((int64_t)b * sp.nc + c) * sp.G + g) * ns + slice) * ((int64_t)Q * Q);
+    if (sp.dg_f32) dg_put<Q>((float*)sp.dG + out, acc, cnt, w, lane);
+    else dg_put<Q>((__bf16*)sp.dG + out, acc, cnt, w, lane);
 }
 
 template <int Q>
@@ -632,6 +639,29 @@ struct FinLds {
     char slab[64 * BPITCH];  // rows of B / C along the contraction, 64 at a time
 };
 
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+
+// sm[q] += the vectors p<q>[0], p<q>[stride], ... of ns slices, U slices of both in flight
+template <int U, typename V>
+__device__ __forceinline__ void add_slices(float (&sm)[2][8], const V* p0, const V* p1, int stride, int ns) {
+    int sl = 0;
+    for (; sl + U <= ns; sl += U) {
+        V v[2][U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            v[0][u] = p0[(int64_t)(sl + u) * stride];
+            v[1][u] = p1[(int64_t)(sl + u) * stride];
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sm[q][e] += (float)v[q][u][e];
+    }
+    if constexpr (U > 1) add_slices<U / 2>(sm, p0 + (int64_t)sl * stride, p1 + (int64_t)sl * stride, stride, ns - sl);
+}
+
 // Small footprint on purpose (37 KB of LDS): the kernel only streams partial sums.
 template <int Q>
 __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, int z) {
@@ -648,7 +678,7 @@ __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, in
     const bf16_t* rhs = (role == 0 ? (const bf16_t*)sp.Bm : (const bf16_t*)sp.Cm) + bbase;
     const int k_lo = role == 0 ? 0 : R, k_hi = role == 0 ? R : NT - 1;  // tiles along the contraction
     const int ns = sp.dg_split;
-    const bf16_t* dg = (const bf16_t*)sp.dG + bcg * ns * ((int64_t)Q * Q);
+    const int64_t dg = bcg * ns * ((int64_t)Q * Q);
     const int ps = sp.part_split;
     const float* part = sp.dbc_part + (bcg * ps * 2 + role) * ((int64_t)Q * N_);
     f32x16 acc = zero16();
@@ -669,7 +699,7 @@ __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, in
     // flight per wave; one 16-byte piece per lane and item
     const int nitems = 2 * (k_hi - k_lo + 1);
     for (int it = w; it < nitems; it += 2 * (NTH / 64)) {
-        const bf16_t* src[2];
+        int64_t src[2];  // elements
         char* dst[2];
         const bool two = it + NTH / 64 < nitems;
 #pragma unroll
@@ -686,28 +716,9 @@ __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, in
         for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int e = 0; e < 8; ++e) sm[q][e] = 0.f;
-        int sl = 0;
-        for (; sl + 8 <= ns; sl += 8) {  // summation order stays slice 0, 1, 2, ...
-            bf16x8 vv[2][8];
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int u = 0; u < 8; ++u) vv[q][u] = *(const bf16x8*)(src[q] + (int64_t)(sl + u) * Q * Q);
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) sm[q][e] += (float)vv[q][u][e];
-        }
-        for (; sl < ns; ++sl) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const bf16x8 vv = *(const bf16x8*)(src[q] + (int64_t)sl * Q * Q);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) sm[q][e] += (float)vv[e];
-            }
-        }
+        // summation order: slice 0, 1, 2, ...
+        if (sp.dg_f32) add_slices<4>(sm, (const f32x8*)((const float*)sp.dG + src[0]), (const f32x8*)((const float*)sp.dG + src[1]), Q * Q / 8, ns);
+        else add_slices<8>(sm, (const bf16x8*)((const bf16_t*)sp.dG + src[0]), (const bf16x8*)((const bf16_t*)sp.dG + src[1]), Q * Q / 8, ns);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             bf16x8 o;

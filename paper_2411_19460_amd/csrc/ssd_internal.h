@@ -79,7 +79,7 @@ struct SegParams {
     float* states;     // generic path only: [Bt][nc+1][H][P][N]  slot c: state entering chunk c; slot nc: state leaving the segment
     float* dstates;    // generic path only: [Bt][nc][H][P][N]    slot c: adjoint of the state leaving chunk c
     float* Gm;         // [Bt][nc][G][Q][Q]    C_i . B_j   (generic path: fp32)
-    float* dG;         // generic path: [Bt][nc][G][dg_split][Q][Q] fp32 per-slice sums of masked dY X^T; MFMA path: [Bt][nc][G][dg_split][Q/32][Q/32][32][32] bf16 per-slice sums, tile by tile
+    float* dG;         // generic path: [Bt][nc][G][dg_split][Q][Q] fp32 per-slice sums of masked dY X^T; MFMA path: [Bt][nc][G][dg_split][Q/32][Q/32][32][32] per-slice sums, tile by tile, bf16 or (dg_f32) fp32
     // Per-token scalars; on the generic path gterm, sterm, erow, ecol, fterm and dDrow are partial sums over pieces of 32
     // columns (or rows) of a tile, piece k at k tok_stride.
     int64_t tok_stride;
@@ -102,6 +102,7 @@ struct SegParams {
     bf16_t* states_bf;   // [Bt][nc][H][P][N] chunk states, replaced in place by the states entering the chunks (bf16 only)
     bf16_t* dstates_bf;  // [Bt][nc][H][P][N] local state adjoints, replaced in place by the adjoints of the leaving states
     int dg_split;        // number of head slices whose dG / dB / dC partial sums are kept apart
+    int dg_f32;          // MFMA path: the partial sums of dG are kept in fp32 (see fit_splits)
     int dual_split;      // number of head slices per (batch, chunk, group) in the dual-form kernels (backward, 0: chosen at the launch)
     int part_split;      // number of head slices of the dB / dC head sums
     int outer_split;     // number of head slices of the chunk-state / local-adjoint kernel
@@ -178,6 +179,7 @@ struct Dims {
     // the launch plan (plan_dims): span k = segments [k F, (k + 1) F), on lane k % nl
     int nc_seg;         // chunks per segment
     int F, nl;          // segments per span, spans in flight
+    bool dg_f32;        // workspace for partial sums of dG in fp32 on the matrix-core path
     int64_t nspan;
     int64_t nct;        // chunks of the sequence; nc above: chunks of the largest span
     size_t esz;
