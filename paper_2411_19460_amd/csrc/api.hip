@@ -390,12 +390,18 @@ static int lane_cap() {
 //    of those hold less than four full ones do.  With four, 65536 tokens of 24 heads in segments of 1024 take 2410 us
 //    instead of 1627, 32768 of 80 heads 2107 instead of 1866, 4096 fp32 tokens of 24 heads in segments of 256 578 instead
 //    of 432.
-//  - A sequence of few units altogether (ONE_SPAN_UNITS) is one span: nothing to order, no events, full launches, and no more
-//    scratch than on lanes (fewer partial sums: 304 MB instead of 379 for 16384 tokens of 80 heads).  Matrix-core kernels, us
-//    on lanes -> as one span.  At the line, 5120 units: 16384 of 80 heads 863 -> 794 (chunks of 128 1022 -> 955, forward only
-//    232 -> 190), 2 x 8192 of 64 722 -> 634.  Below: 32768 of 32 (4096 units) 765 -> 681, 49152 of 24 (4608) 887 -> 828, in
-//    chunks of 128 1092 -> 988, 31000 of 32 in chunks of 64 1353 -> 1248.  Above it goes either way: 24576 of 80 (7680) 1222 ->
-//    1200, 40000 of 2 x 24 (7500) 1306 -> 1346, 65536 of 32 (8192) 1369 -> 1480.
+//  - A sequence of few units altogether (ONE_SPAN_UNITS), in at most eight segments of less than SPAN_UNITS each or at most four
+//    longer ones, is one span: nothing to order, no events, full launches, and no more scratch than on lanes (fewer partial
+//    sums: 337 MB instead of 379 for 16384 tokens of 80 heads).  Matrix-core kernels, us on lanes -> as one span, forward +
+//    backward.  Near the line: 16091 tokens of 80 heads in four segments 246 + 607 -> 191 + 637, chunks of 128 301 + 700 -> 234 +
+//    720, in two segments 307 + 843 -> 235 + 721; 53211 of 24 heads 257 + 692 -> 233 + 650, chunks of 128 320 + 820 -> 272 + 853.
+//    So the backward pass alone goes either way there (in 110 shapes, 8 % longer to 25 % shorter); the two together take 2 %
+//    longer in two of the shapes (20187 of 64 in four segments, 2 x 26587 of 24 in chunks of 128) and up to 25 % less in the
+//    others.  Beyond the line they go either way too: 24576 of 80 (7680 units) 1222 -> 1200, 40000 of 2 x 24 (7500) 1306 ->
+//    1346, 65536 of 32 (8192) 1369 -> 1480.
+//  - Fewer than ten heads (over the batch) stay on lanes from LANE_UNITS on: the state scan is serial in the chunks of a span and
+//    has eight workgroups a head.  163072 tokens of 8 heads 350 + 948 on lanes, 356 + 996 as one span, 326400 of 4 570 + 1360
+//    and 525 + 1558, 1305600 of 1 1778 + 4426 and 1690 + 5222; of 10 heads, 130560 tokens, 333 + 903 and 299 + 906.
 // Only the number of segments counts, not where the last one ends: the workspace query goes over these plans.
 void plan_dims(Dims* d, bool mfma, bool one_stream) {
     if (d->L == 0) return;
@@ -405,9 +411,9 @@ void plan_dims(Dims* d, bool mfma, bool one_stream) {
     const int64_t inflight = seg_units >= SPAN_UNITS ? 4 : INFLIGHT;
     d->F = d->nl = 1;
     if (!one_stream && d->nseg > 1) {
-        if (d->nseg <= inflight && (all_units <= SPAN_UNITS || (mfma && all_units <= ONE_SPAN_UNITS))) {
+        if (d->nseg <= inflight && (all_units <= SPAN_UNITS || (mfma && all_units <= (d->Bt * d->H < 10 ? LANE_UNITS : ONE_SPAN_UNITS)))) {
             d->F = (int)d->nseg;
-            d->dg_f32 = mfma && all_units > LANE_UNITS;
+            d->dg_f32 = mfma && all_units > LANE_UNITS && d->nseg > 2;  // two segments on two lanes have the same slices
         } else {
             while (d->F < inflight && d->F * seg_units < SPAN_UNITS) d->F *= 2;
             const int64_t spans = (d->nseg + d->F - 1) / d->F;

@@ -159,6 +159,8 @@ def test_generic_kernels_beyond_their_usual_sizes(case):
     (16384, 80, 4096, 256),    # 5120 chunks of a head: the most that is one span
     (16385, 80, 8192, 256),    # one row more: lanes
     (40959, 32, 5120, 128),    # as many in eight segments, ragged
+    (90000, 12, 22528, 256),   # few heads
+    (122000, 9, 30720, 256),   # too few: lanes
 ])
 def test_the_largest_single_span_against_one_segment(L, H, seg, Q):
     """Where the checkpoints fall does not change the result.  Tolerance: that of either run against the oracle."""
