@@ -65,7 +65,11 @@ def test_generation_step_from_given_states(shape):
     # layers, d_model, H, P, N, sequences
     (3, 2560, 80, 64, 128, 1),   # 242 MB of weights: the last layer's stream
     (3, 2560, 80, 64, 128, 2),
-    (3, 2560, 80, 64, 128, 5),   # and 63 MB of states: they stream in every layer, four rows per half wave
+    (3, 2560, 80, 64, 128, 4),   # the same on the matrix cores, rows in three parts
+    (3, 2560, 80, 64, 128, 5),   # in two
+    (3, 2560, 80, 64, 128, 7),   # and 55 MB of states: they stream in every layer, four rows per half wave
+    (3, 2560, 80, 64, 128, 16),  # 126 MB of states, eight rows; rows of the products as they are
+    (13, 64, 120, 64, 128, 1),   # 51 MB of states, a row per half wave
     (4, 1024, 32, 64, 256, 8),   # 67 MB of states of 256 columns
     (7, 64, 120, 64, 248, 1),    # 53 MB of states, a row per half wave, the last columns missing
 ])

@@ -17,6 +17,8 @@ pytestmark = pytest.mark.gpu
     (1, 31 * 256 + 1, 24, 1, 256, 2048),   # one slice of the head sums
     (1, 40 * 256 - 200, 10, 1, 256, 4096),  # forward slices of two heads
     (2, 3001, 14, 2, 128, 1024),           # chunks of 128: two workgroups of a forward launch on a compute unit
+    (1, 4000, 80, 1, 64, 4096),            # chunks of 64: eight slices where the general rule takes five
+    (2, 2500, 18, 2, 64, 4096),            # chunk states and adjoints in three where it takes one
 ])
 def test_slices_of_a_launch_on_its_own(case):
     Bt, L, H, G, Q, seg = case

@@ -158,7 +158,8 @@ def test_generic_kernels_beyond_their_usual_sizes(case):
 @pytest.mark.parametrize("L,H,seg,Q", [
     (16384, 80, 4096, 256),    # 5120 chunks of a head: the most that is one span
     (16385, 80, 8192, 256),    # one row more: lanes
-    (40959, 32, 5120, 128),    # as many in eight segments, ragged
+    (39000, 32, 4992, 128),    # nearly as many in eight segments, ragged
+    (40959, 32, 5120, 128),    # segments too long for eight of them to be one span: lanes
     (90000, 12, 22528, 256),   # few heads
     (122000, 9, 30720, 256),   # too few: lanes
 ])
