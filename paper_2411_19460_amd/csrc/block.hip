@@ -10,8 +10,10 @@
 // every step, handing the two state adjoints to the segment on the left.
 // Everything is a sequence of calls to the library's own entry points plus small kernels for softplus of dt
 // (the convolution writes x, B and C as the three dense tensors the scan reads, and reads their gradients
-// the same way); all on the caller's stream.
+// the same way); all on the caller's stream, but for the output projections of several segments (block_fwd).
 #include <string.h>
+
+#include <mutex>
 
 #include "column_sums.h"
 
@@ -22,6 +24,39 @@ typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 
 constexpr int DECODE_ROWS = 16;  // calls of at most this many tokens run the scan as the plain recurrence
 constexpr int DT_ROWS = 16;  // rows per workgroup of the dt kernels (granularity of the ddt_bias partial sums)
+
+std::mutex g_side_mu;
+
+// Created on first use on a device (or by ssd_init), under a lock; a partial failure releases what was created.
+SideStream* side_for_current_device() {
+    static SideStream sides[64];
+    static bool ok[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+    std::lock_guard<std::mutex> lock(g_side_mu);
+    if (ok[dev]) return &sides[dev];
+    SideStream q;
+    memset(&q, 0, sizeof(q));
+    bool good = hipStreamCreateWithFlags(&q.st, hipStreamNonBlocking) == hipSuccess;
+    hipEvent_t* evs[] = {&q.fork, &q.join};
+    for (hipEvent_t* e : evs) good = good && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
+    if (!good) {
+        for (hipEvent_t* e : evs)
+            if (*e) (void)hipEventDestroy(*e);
+        if (q.st) (void)hipStreamDestroy(q.st);
+        return nullptr;
+    }
+    sides[dev] = q;
+    ok[dev] = true;
+    return &sides[dev];
+}
+
+}  // namespace
+
+// A library stream of default priority, forked from and joined into the caller's stream with events.
+SideStream* side_stream() { return serial_mode() ? nullptr : side_for_current_device(); }
+
+namespace {
 
 // dt[r,h] = softplus(raw[r,h] + bias[h]); raw is a column slice (rows raw_rs apart), dt dense.  For the recurrence of a few
 // tokens; the scan's kernels form dt themselves (RawDt).
@@ -529,8 +564,8 @@ hipError_t clear_weights(const BlockDims& d, const magc_block_grads_t& g, hipStr
 // and the normalised y in the workspace): du of the segment (+ res, if given: the gradient that goes round the block in a
 // residual stream; du_seg may be res), parameter gradients added to `g`, the adjoints of the two states entering the segment.
 // fresh_w: the gradients of the two weight matrices are stored, not added to (the first segment of a call; 2560 x (10576 +
-// 5120) of them are 161 MB to clear and to read).  normed: the normalised input of the projection is still in its place.  du_tmp: rows of d_model for a gradient that res is
-// added to in a pass of its own.
+// 5120) of them are 161 MB to clear and to read).  normed: the normalised input of the projection is still in its place.
+// du_tmp: rows of d_model for a gradient that res is added to in a pass of its own.
 int backward_segment(const BlockDims& d, const magc_block_shape_t* sh, const magc_block_params_t* p, const magc_block_grads_t* g,
                      char* ws, const BlockWs& w, const char* zx, const char* y, const void* u_seg, const void* dout_seg, void* du_seg,
                      int64_t rows, const float* ssm_in, const void* conv_in, const float* dssm_out, const float* dconv_out,
@@ -975,11 +1010,14 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
 // step (each layer finds what the layers behind it left).  So the first layers' weights are fetched plainly, as many as fit
 // beside what else a step writes, and the others by streaming loads, which leave the cache as it is; states likewise stream
 // once they are no small part of it (reading and writing back what the step before wrote costs more than it saves).
-// Microseconds a step of eight layers, plain -> all streamed -> this: 80 heads (645 MB of weights), 1 / 3 / 16 sequences 208 /
-// 282 / 389 -> 197 / 263 / 346 -> 191 / 256 / 338; 64 heads (414 MB), 16: 334 -> 297 -> 280; weights that fit, 32 heads
-// (105 MB), 16: 161 -> 157 -> 150, 3: 131 -> 139 -> 131.
-// States, plain against streamed: 42 MB (80 heads, 2 sequences) 222.3 / 223.2, 59 MB (32, 7) 133.1 / 131.5, 67 MB (64, 4)
-// 231 / 218, 168 MB (64, 16) 301 / 280.
+// The full gain is that of a loop that runs nothing else: the cache then lives from step to step.  Microseconds a step of
+// eight layers, plain -> all streamed -> this: 80 heads (645 MB of weights), 1 / 3 / 16 sequences 208 / 282 / 389 -> 197 / 263 /
+// 346 -> 191 / 256 / 338; 64 heads (414 MB), 16: 334 -> 297 -> 280; weights that fit, 32 heads (105 MB), 16: 161 -> 157 -> 150,
+// 3: 131 -> 139 -> 131.  States, plain against streamed: 42 MB (80 heads, 2 sequences) 222.3 / 223.2, 59 MB (32, 7) 133.1 /
+// 131.5, 67 MB (64, 4) 231 / 218, 168 MB (64, 16) 301 / 280.
+// Where something else has been through the cache it is less, and no loss.  Plain -> this behind a copy of 1 GiB: 80
+// heads, 1 / 3 / 16 sequences 226 / 301 / 399 -> 217 / 289 / 368, 64, 16: 347 -> 321, 32, 7 / 16: 168 / 203 -> 158 / 176;
+// behind a copy that has just written the states: 242 / 307 / 397 -> 232 / 294 / 366, 339 -> 307, 166 / 170 -> 167 / 169.
 void cache_plan(const StackDims& d, int nseq, int j, FewSeqs* sq) {
     const int64_t cache = (int64_t)224 << 20;  // 32 MiB are left to activations and what runs between the steps
     const int64_t weights = (int64_t)(d.b.d_in_proj + d.b.d_inner) * d.b.dm * 2, states = (int64_t)d.NL * nseq * d.b.HPN * 4;

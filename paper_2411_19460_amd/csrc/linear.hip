@@ -10,13 +10,11 @@
 // dw, w for dx).  Both kinds are staged in LDS exactly as they lie in memory (16-byte vectors); k-major
 // tiles are read back as plain 16-byte operands, the others through the transposing LDS read.
 // One scheme of tiles, three widths: 256 x 256, 256 x 192 or 256 x 128 per workgroup (eight waves of 64 x 128 / 96 / 64, one
-// workgroup per compute unit, loads straight to LDS two K steps ahead); the two gradient products share a launch, and the launch rule below chooses the one whose tiles
-// fit the machine best.  Workgroup ids are remapped so that each XCD works on a compact
-// block of the tile grid (its L2 then holds the A and B panels that block shares).
+// workgroup per compute unit, loads straight to LDS two K steps ahead); the two gradient products share a launch, and the
+// launch rule below chooses the one whose tiles fit the machine best.  Workgroup ids are remapped so that each XCD works on a
+// compact block of the tile grid (its L2 then holds the A and B panels that block shares).
 #include <stdint.h>
 #include <string.h>
-
-#include <mutex>
 
 #include "mfma_common.h"
 
@@ -128,7 +126,9 @@ struct Tile {
     }
     // Piece I of a K step, memory -> LDS.  The wave's 64 pieces land at m0 in lane order.  As assembly because the compiler
     // drains every load in flight to LDS before each LDS read it can see; there is no output register, and the step waits for
-    // the loads itself.
+    // the loads itself.  m0 is a register the compiler reserves for itself: it warns that it may not keep a value of its own
+    // there across this statement.  It has none in these kernels; it would with an array that is indexed at run time in
+    // registers, or another access straight to LDS, a message or a global barrier: those must not come in here.
     template <int I>
     static __device__ __forceinline__ void load(u32x4 r, int64_t ld, uint32_t voff, uint32_t lds, int w) {
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
@@ -214,8 +214,12 @@ struct Big {
     __device__ __forceinline__ void read_b(const BigCtx& cx, int buf, int set, int j, int q) {
         b[set][q & 1][q >> 1] = TB::operand(lds + NA * TA::BYTES + buf * TB::BYTES, cx.wn * 32 * WJ + j * 32 + (q & 1) * 16, q >> 1, cx.lane);
     }
-    static __device__ __forceinline__ u32x4 span_a(const BigCtx& cx, int k0) { return TA::span(cx.a_org + (int64_t)k0 * cx.a_kstep, cx.lda, cx.rows_a); }
-    static __device__ __forceinline__ u32x4 span_b(const BigCtx& cx, int k0) { return TB::span(cx.b_org + (int64_t)k0 * cx.b_kstep, cx.ldb, cx.rows_b); }
+    static __device__ __forceinline__ u32x4 span_a(const BigCtx& cx, int k0) {
+        return TA::span(cx.a_org + (int64_t)k0 * cx.a_kstep, cx.lda, cx.rows_a);
+    }
+    static __device__ __forceinline__ u32x4 span_b(const BigCtx& cx, int k0) {
+        return TB::span(cx.b_org + (int64_t)k0 * cx.b_kstep, cx.ldb, cx.rows_b);
+    }
     template <int I>
     __device__ __forceinline__ void load_a(const BigCtx& cx, u32x4 s, int buf) {
         TA::template load<I>(s, cx.lda, cx.va, lds0 + buf * TA::BYTES, cx.w);
@@ -402,8 +406,11 @@ __global__ __launch_bounds__(GTHR, 1) void k_gemm_big(GemmParams gp) {
 // first .. run the second.  They are independent (both read dout; they write dx and dw), and one alone often leaves compute
 // units idle: a segment of 4096 rows gives the input gradient of the 2.7B block's input projection 160 tiles for 256 units.
 // As two launches on two streams they met only behind a fork and a join, some 20 us a pair, and in whatever order the queues
-// were served: us at 4096 rows, two launches -> one, 2560 <-> 10576 375 -> 372, 2560 <-> 5120 227 -> 174, 1024 <-> 4384 95 -> 87,
-// 1024 <-> 2048 73 -> 53; 600 rows 154 -> 145, 81 -> 60, 61 -> 50, 40 -> 19.
+// were served: us at 4096 rows, two launches -> one, 2560 <-> 10576 375 -> 363, 2560 <-> 5120 227 -> 182, 1024 <-> 4384 95 -> 90,
+// 1024 <-> 2048 73 -> 49; 600 rows 154 -> 145, 81 -> 50, 61 -> 49, 40 -> 16.
+// With a tile of each kind in one kernel the registers of <4, 4> and <2, 4> do not quite suffice: 9 and 5 of them are kept in
+// 28 and 24 bytes of scratch, all in the last steps of a tile (the forward kernel of the same tile, 248 registers, keeps
+// none).  Such accesses only make the waits of those steps, which count outstanding loads, stricter.
 template <int WX, int WW>
 __global__ __launch_bounds__(GTHR, 1) void k_gemm_grads(GemmParams px, GemmParams pw, int dw_first, int first) {
     const bool second = (int)blockIdx.x >= first;
@@ -485,9 +492,9 @@ int forward_width(const GemmParams& gp) {
 // two fifths of a chain of ragged end, and no less than a short tile in front of a long one.  Over six pairs of widths from
 // 768 to 10576 and 100 ... 16384 rows the rule is 1.5 % off the best of the four combinations (6 % with the K steps alone).
 // The product of the longer tiles goes first: the others then fill the units that its last round leaves idle, instead of the
-// long ones running on alone.  2560 <-> 10576 (longer: the input's), 4096 rows: 379 us, the other way round 458; 2560 <-> 5120
-// (longer: the weights'), 4096 rows 186, the other way round 223.
-// (256, 256), chosen: 2560 <-> 10576, 200 rows 185, 128; 1024 <-> 4384, 4096 rows 92, 89.
+// long ones running on alone.  2560 <-> 10576 (longer: the input's), 4096 rows: 363 us, the other way round 424; 2560 <-> 5120
+// (longer: the weights'), 4096 rows 182, the other way round 217.
+// Both at 256 columns -> as chosen: 2560 <-> 10576, 200 rows 185 -> 121 us; 1024 <-> 4384, 4096 rows 92 -> 90.
 int64_t tile_cost(const GemmParams& gp, int wj) {
     const int64_t around = gp.c_f32 ? (wj == 4 ? 2000 : 1100) : (wj == 4 ? 400 : 200);
     return (int64_t)((gp.K + BKK - 1) / BKK) * (wj == 4 ? 100 : 66) + around;
@@ -508,39 +515,6 @@ void backward_widths(const GemmParams* dx, const GemmParams* dw, int& wx, int& w
             if (t < best) best = t, wx = a, ww = b, dw_first = cb > ca;
         }
 }
-
-std::mutex g_side_mu;
-
-// Created on first use on a device (or by ssd_init), under a lock; a partial failure releases what was created.
-SideStream* side_for_current_device() {
-    static SideStream sides[64];
-    static bool ok[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
-    std::lock_guard<std::mutex> lock(g_side_mu);
-    if (ok[dev]) return &sides[dev];
-    SideStream q;
-    memset(&q, 0, sizeof(q));
-    bool good = hipStreamCreateWithFlags(&q.st, hipStreamNonBlocking) == hipSuccess;
-    hipEvent_t* evs[] = {&q.fork, &q.join};
-    for (hipEvent_t* e : evs) good = good && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
-    if (!good) {
-        for (hipEvent_t* e : evs)
-            if (*e) (void)hipEventDestroy(*e);
-        if (q.st) (void)hipStreamDestroy(q.st);
-        return nullptr;
-    }
-    sides[dev] = q;
-    ok[dev] = true;
-    return &sides[dev];
-}
-
-}  // namespace
-
-// A library stream of default priority, forked from and joined into the caller's stream with events.
-SideStream* side_stream() { return serial_mode() ? nullptr : side_for_current_device(); }
-
-namespace {
 
 int check(int64_t rows, int32_t in_dim, int32_t out_dim, int64_t ldx, int64_t ldo) {
     if (rows < 0 || rows > 0x7fffffff || in_dim <= 0 || out_dim <= 0) return SSD_ERR_SHAPE;
