@@ -695,8 +695,8 @@ __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, in
         const int v = tid + NTH * k, row = v >> 4, seg = v & 15;
         sv[k] = rows_load(rows, (uint32_t)(64 * p_lo + row) * (uint32_t)bt * 2 + seg * 16);
     }
-    // sum the slices of the needed dG tiles: items (tile, half of its rows), two items and eight slices of each in
-    // flight per wave; one 16-byte piece per lane and item
+    // sum the slices of the needed dG tiles: items (tile, half of its rows), two items and eight bf16 or four fp32 slices of
+    // each in flight per wave; eight elements per lane and item
     const int nitems = 2 * (k_hi - k_lo + 1);
     for (int it = w; it < nitems; it += 2 * (NTH / 64)) {
         int64_t src[2];  // elements
