@@ -196,7 +196,8 @@ struct BlockWs {
     size_t inner_bytes;
 };
 
-BlockWs layout(const BlockDims& d, bool bwd) {
+// ckpt_s: the forward scan stores checkpoints inside a segment (see Inner).
+BlockWs layout(const BlockDims& d, bool bwd, int64_t ckpt_s = 0) {
     BlockWs w;
     memset(&w, 0, sizeof(w));
     size_t off = 0;
@@ -220,6 +221,13 @@ BlockWs layout(const BlockDims& d, bool bwd) {
     size_t inner = 0;  // the backward pass also runs the forward scan (recomputation)
     for (int pass = 0; pass <= (bwd ? 1 : 0); ++pass) {
         const size_t a = ssd_workspace_bytes(&ss, pass), b = ssd_workspace_bytes(&st, pass);
+        inner = a > inner ? a : inner;
+        inner = b > inner ? b : inner;
+    }
+    if (ckpt_s) {
+        ssd_shape_t sc = ss, tc = st;
+        sc.segment = tc.segment = ckpt_s;
+        const size_t a = ssd_workspace_bytes(&sc, 0), b = ssd_workspace_bytes(&tc, 0);
         inner = a > inner ? a : inner;
         inner = b > inner ? b : inner;
     }
@@ -301,10 +309,18 @@ RawDt raw_dt(const BlockDims& d, const magc_block_params_t* p, const char* zx) {
     return {zx + (size_t)d.off_dt * 2, (int64_t)d.d_in_proj, p->dt_bias};
 }
 
+// Checkpoints inside what a call walks as one segment: every s tokens, the first where the call starts (conv: not that one).
+struct Inner {
+    int64_t s;
+    float* ssm;
+    void* conv;
+};
+
 // ssm_out may be ssm_in: one segment's scan reads an element of it before it writes it, in one thread
 int seg_scan(const BlockDims& d, const magc_block_params_t* p, char* ws, const BlockWs& w, const char* zx, int64_t rows, const float* ssm_in,
-             float* ssm_out, char* y, hipStream_t st, bool recur_ok = false) {
-    const ssd_shape_t ss = seg_shape(d, rows);
+             float* ssm_out, char* y, hipStream_t st, bool recur_ok = false, const Inner* inner = nullptr) {
+    ssd_shape_t ss = seg_shape(d, rows);
+    if (inner) ss.segment = inner->s;
     if (recur_ok && rows <= DECODE_ROWS && ssm_out) {
         // a few tokens (inference only: see block_fwd): the recurrence token by token on the state itself instead of a padded chunk
         hipLaunchKernelGGL(k_dt_fwd, dim3((unsigned)((rows + DT_ROWS - 1) / DT_ROWS)), dim3(256), 0, st,
@@ -314,8 +330,25 @@ int seg_scan(const BlockDims& d, const magc_block_params_t* p, char* ws, const B
             BLK_HIP(ssm_in ? launch_copy_f32(ssm_out, ssm_in, d.HPN, st) : launch_fill_zero(ssm_out, d.HPN, st));
         return ssd_decode(&ss, ws + w.x, ws + w.dt, p->A, ws + w.B, ws + w.C, p->D, ssm_out, y, 0, st);
     }
-    return scan_fwd(&ss, ws + w.x, nullptr, raw_dt(d, p, zx), p->A, ws + w.B, ws + w.C, p->D, ssm_in, y, ssm_out, nullptr, ws + w.inner,
-                    w.inner_bytes, 0, st);
+    return scan_fwd(&ss, ws + w.x, nullptr, raw_dt(d, p, zx), p->A, ws + w.B, ws + w.C, p->D, ssm_in, y, ssm_out, inner ? inner->ssm : nullptr,
+                    ws + w.inner, w.inner_bytes, 0, st);
+}
+
+// Convolution state in front of tokens s, 2 s, ..: the last three inputs of the convolution, out of zxbcdt or of the state in
+// front of the rows (null: zeros).
+__global__ __launch_bounds__(256) void k_conv_ckpt(const bf16_t* xbc, int64_t row_stride, const bf16_t* state, int64_t s, int channels, bf16_t* ckpt) {
+    const int64_t k = blockIdx.y + 1, t = k * s - 3 + blockIdx.z;
+    const int c = blockIdx.x * 256 + threadIdx.x;
+    if (c >= channels) return;
+    const bf16_t zero = float_to_bf16(0.f);
+    ckpt[(k * 3 + blockIdx.z) * channels + c] = t >= 0 ? xbc[t * row_stride + c] : state ? state[(3 + t) * channels + c] : zero;
+}
+hipError_t conv_checkpoints(const BlockDims& d, const char* zx, const void* conv_in, int64_t rows, const Inner& inner, hipStream_t st) {
+    const int64_t n = (rows + inner.s - 1) / inner.s - 1;
+    if (n < 1) return hipSuccess;
+    hipLaunchKernelGGL(k_conv_ckpt, dim3((d.conv_dim + 255) / 256, (unsigned)n, 3), dim3(256), 0, st, (const bf16_t*)(zx + (size_t)d.off_xbc * 2),
+                       (int64_t)d.d_in_proj, (const bf16_t*)conv_in, inner.s, d.conv_dim, (bf16_t*)inner.conv);
+    return hipGetLastError();
 }
 
 int seg_norm(const BlockDims& d, const magc_block_shape_t* sh, const magc_block_params_t* p, char* ws, const BlockWs& w, const char* zx,
@@ -327,10 +360,11 @@ int seg_norm(const BlockDims& d, const magc_block_shape_t* sh, const magc_block_
 // All of them: everything up to y and the normalised y, from the two states entering the segment.
 int forward_segment(const BlockDims& d, const magc_block_shape_t* sh, const magc_block_params_t* p, char* ws, const BlockWs& w,
                     char* zx, char* y, const void* u_seg, int64_t rows, const float* ssm_in, const void* conv_in, float* ssm_out,
-                    void* conv_out, hipStream_t st, bool recur_ok = false, bool normed = false) {
+                    void* conv_out, hipStream_t st, bool recur_ok = false, bool normed = false, const Inner* inner = nullptr) {
     BLK_TRY(seg_in_proj(d, sh->eps, p, ws, w, u_seg, rows, zx, st, normed));
+    if (inner) BLK_HIP(conv_checkpoints(d, zx, conv_in, rows, *inner, st));
     BLK_TRY(seg_mid(d, p, ws, w, zx, rows, conv_in, conv_out, st));
-    BLK_TRY(seg_scan(d, p, ws, w, zx, rows, ssm_in, ssm_out, y, st, recur_ok));
+    BLK_TRY(seg_scan(d, p, ws, w, zx, rows, ssm_in, ssm_out, y, st, recur_ok, inner));
     BLK_TRY(seg_norm(d, sh, p, ws, w, zx, y, rows, st));
     return SSD_OK;
 }
@@ -630,10 +664,12 @@ extern "C" size_t magc_block_workspace_bytes(const magc_block_shape_t* sh, int32
 // few_ok: calls of a few tokens may take the generation kernels.  Not while a training pass records checkpoints:
 // those kernels round at other places than the chunked path that the backward pass recomputes the segment with,
 // and the result would depend (in its last bits) on how the sequence is cut into segments.
-// normed: the normalised input of the (first) segment is in the workspace already.
+// normed: the normalised input of the (first) segment is in the workspace already.  inner: checkpoints inside the one segment
+// of the call; the workspace has the scratch of a scan with them.
 static int block_fwd(const magc_block_shape_t* sh, const magc_block_params_t* p, const void* u, const float* init_ssm,
                      const void* init_conv, void* out, float* ssm_ckpt, void* conv_ckpt, float* final_ssm, void* final_conv,
-                     void* workspace, size_t workspace_bytes, bool few_ok, void* hip_stream, bool normed = false) {
+                     void* workspace, size_t workspace_bytes, bool few_ok, void* hip_stream, bool normed = false,
+                     const Inner* inner = nullptr) {
     BlockDims d;
     BLK_TRY(check(sh, &d));
     if (!p || !p->W_in || !p->conv_w || !p->conv_b || !p->dt_bias || !p->A || !p->D || !p->norm_w || !p->W_out) return SSD_ERR_NULL;
@@ -648,7 +684,7 @@ static int block_fwd(const magc_block_shape_t* sh, const magc_block_params_t* p,
         return SSD_OK;
     }
     if (!u || !out) return SSD_ERR_NULL;
-    const BlockWs w = layout(d, false);
+    const BlockWs w = layout(d, false, inner ? inner->s : 0);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < w.total) return SSD_ERR_WORKSPACE;
     char* ws = (char*)workspace;
     // Several segments: a segment's output projection and the next segment's input projection do not depend on
@@ -677,7 +713,8 @@ static int block_fwd(const magc_block_shape_t* sh, const magc_block_params_t* p,
             continue;
         }
         if (!side) {
-            BLK_TRY(forward_segment(d, sh, p, ws, w, ws + w.zx, ws + w.y, u_seg, rows, ssm_in, conv_in, ssm_out, conv_out, st, few_ok, normed && k == 0));
+            BLK_TRY(forward_segment(d, sh, p, ws, w, ws + w.zx, ws + w.y, u_seg, rows, ssm_in, conv_in, ssm_out, conv_out, st, few_ok, normed && k == 0,
+                                    inner));
             BLK_TRY(ssd_linear_fwd(rows, d.d_inner, d.dm, ws + w.yn, 0, p->W_out, out_seg, 0, st));
             continue;
         }
@@ -775,15 +812,43 @@ extern "C" int magc_block_bwd(const magc_block_shape_t* sh, const magc_block_par
 namespace ssdk {
 namespace {
 
+// Segments of a few thousand tokens are walked together: the steps of a layer run on as many rows as make `work` elements of
+// zxbcdt at most (or on one segment, if that is more).  A product's last round of tiles leaves compute units idle, every
+// segment reads and adds to the weights' gradients, and short launches are all ramp; more rows a launch cost scratch.
+//   Training: 8192 rows at the 2.7B width (10576 columns).  Scratch is that of a cell of so many tokens.
+//   Inference, where nothing is kept and where a prompt is cut concerns nobody: twice that, in equal passes.
+// One segment a launch -> training with 4096, 8192, 16384 rows of the 2.7B width (ms, forward + backward, 1-3 layers):
+//   16384 tokens, 80 heads, segment 4096:  13.0 -> 13.0, 12.2, 11.7;  segment 1024: 24.2 -> 13.0 (4096)
+//   20000 tokens, 24 heads, segment 2048:  11.8 -> 6.0, 5.4, 5.4;     30000, 32 heads, segment 4096: 10.6 -> 8.4, 7.3, 6.9
+// and inference with 4096, 8192, 16384:
+//   6001 tokens, 80 heads, segment 4096: 2.73 -> 2.71, 2.23, 2.23;    13001, 80 heads, segment 2048: 7.0 -> 5.6, 5.2, 4.9
+//   30001 tokens, 24 heads, segment 4096:  5.3 -> 3.7, 3.6, 3.3
+constexpr int64_t TRAIN_WORK = (int64_t)8192 * 10576, INFER_WORK = 2 * TRAIN_WORK;
+int64_t rows_together(const BlockDims& d, int64_t work) {
+    const int64_t k = work / d.d_in_proj / d.s, n = d.nseg > 0 ? d.nseg : 1;
+    return (k < 1 ? 1 : k < n ? k : n) * d.s;
+}
+// Rows of an inference pass: equal ones, whole chunks.
+int64_t pass_rows(const BlockDims& d, int64_t most) {
+    const int64_t n = (d.L + most - 1) / most, per = n > 0 ? (d.L + n - 1) / n : most, rows = (per + d.Q - 1) / d.Q * d.Q;
+    return n > 1 ? rows : most;
+}
+
 struct StackDims {
     BlockDims b;
     int NL, l, ngl;  // layers, layer interval, layer groups
     size_t act, conv_state, conv_adj;
 };
 
-int check_stack(const magc_blockstack_shape_t* sh, StackDims* d) {
+// work: see rows_together; d->b.s is what is walked as one segment, `wide` the shape with it, `own` the caller's dimensions.
+int check_stack(const magc_blockstack_shape_t* sh, StackDims* d, int64_t work, magc_blockstack_shape_t* wide, BlockDims* own) {
     if (!sh) return SSD_ERR_NULL;
-    const int rc = check(&sh->block, &d->b);
+    int rc = check(&sh->block, own);
+    if (rc != SSD_OK) return rc;
+    *wide = *sh;
+    const int64_t rows = rows_together(*own, work);
+    if (rows != own->s) wide->block.segment = rows;
+    rc = check(&wide->block, &d->b);
     if (rc != SSD_OK) return rc;
     if (sh->nlayers <= 0 || sh->layer_interval <= 0 || sh->layer_interval > sh->nlayers) return SSD_ERR_SHAPE;
     d->NL = sh->nlayers;
@@ -806,7 +871,7 @@ struct StackWs {
     size_t zx_bytes, y_bytes;  // per layer of a cell
 };
 
-StackWs stack_layout(const magc_blockstack_shape_t* sh, const StackDims& d, bool bwd) {
+StackWs stack_layout(const magc_blockstack_shape_t* sh, const StackDims& d, bool bwd, int64_t ckpt_s = 0) {
     StackWs w;
     memset(&w, 0, sizeof(w));
     size_t off = 0;
@@ -840,6 +905,10 @@ StackWs stack_layout(const magc_blockstack_shape_t* sh, const StackDims& d, bool
     }
     const size_t f = magc_block_workspace_bytes(&c, 0);  // the forward pass calls the block's forward entry point
     inner = f > inner ? f : inner;
+    if (ckpt_s) {
+        const size_t k = layout(d.b, false, ckpt_s).total;
+        inner = k > inner ? k : inner;
+    }
     if (bwd) {  // the backward pass lays a block workspace out in this region itself
         const size_t own = layout(d.b, true).total;
         inner = own > inner ? own : inner;
@@ -862,29 +931,40 @@ bool params_ok(const magc_block_params_t* p, int n) {
 
 extern "C" size_t magc_blockstack_workspace_bytes(const magc_blockstack_shape_t* sh, int32_t is_backward) {
     StackDims d;
-    if (check_stack(sh, &d) != SSD_OK) return 0;
-    const magc_block_shape_t c = cell_shape(sh, d.b.s);
+    magc_blockstack_shape_t wide;
+    BlockDims own;
+    if (check_stack(sh, &d, TRAIN_WORK, &wide, &own) != SSD_OK) return 0;
+    const magc_block_shape_t c = cell_shape(sh, own.s);
     if (magc_block_workspace_bytes(&c, is_backward) == 0) return 0;
-    return stack_layout(sh, d, is_backward != 0).total;
+    size_t t = stack_layout(&wide, d, is_backward != 0, is_backward ? 0 : own.s).total;
+    if (!is_backward) {  // the two forward passes, one that records checkpoints and one that keeps nothing
+        if (check_stack(sh, &d, INFER_WORK, &wide, &own) != SSD_OK) return 0;
+        const size_t n = stack_layout(&wide, d, false).total;
+        t = n > t ? n : t;
+    }
+    return t;
 }
 
 extern "C" int magc_blockstack_fwd(const magc_blockstack_shape_t* sh, const magc_block_params_t* params, const void* x0, void* out,
                                    void* l_ckpt, float* ssm_ckpt, void* conv_ckpt, void* workspace, size_t workspace_bytes,
                                    void* hip_stream) {
     StackDims d;
-    BLK_TRY(check_stack(sh, &d));
+    magc_blockstack_shape_t wide;
+    BlockDims own;
+    BLK_TRY(check_stack(sh, &d, TRAIN_WORK, &wide, &own));
     if (!params_ok(params, d.NL)) return SSD_ERR_NULL;
     if (d.b.L == 0) return SSD_OK;
-    if (!x0 || !out || (d.ngl > 1 && !l_ckpt) || (d.b.nseg > 1 && (!ssm_ckpt || !conv_ckpt))) return SSD_ERR_NULL;
-    const StackWs w = stack_layout(sh, d, false);
+    if (!x0 || !out || (d.ngl > 1 && !l_ckpt) || (own.nseg > 1 && (!ssm_ckpt || !conv_ckpt))) return SSD_ERR_NULL;
+    const StackWs w = stack_layout(&wide, d, false, own.s);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < w.total) return SSD_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
     const size_t row = (size_t)d.b.dm * 2;
-    for (int64_t k = 0; k < d.b.nseg; ++k) {
-        const int64_t t0 = k * d.b.s, rows = d.b.L - t0 < d.b.s ? d.b.L - t0 : d.b.s;
-        const magc_block_shape_t c = cell_shape(sh, rows);
-        const bool last = k + 1 == d.b.nseg;
+    for (int64_t t0 = 0; t0 < d.b.L; t0 += d.b.s) {
+        const int64_t rows = d.b.L - t0 < d.b.s ? d.b.L - t0 : d.b.s;
+        const int64_t k = t0 / own.s, next = (t0 + d.b.s) / own.s;  // the caller's segments that start these rows and the next
+        const magc_block_shape_t c = cell_shape(&wide, rows);
+        const bool last = t0 + rows == d.b.L, several = rows > own.s;
         const char* cur = (const char*)x0 + (size_t)t0 * row;
         BlockDims dc;
         BLK_TRY(check(&c, &dc));
@@ -892,15 +972,20 @@ extern "C" int magc_blockstack_fwd(const magc_blockstack_shape_t* sh, const magc
         bool normed = false;
         for (int j = 0; j < d.NL; ++j) {
             // sequence-axis checkpoints of layer j: slot k = the states entering segment k (slot 0 unused: zeros)
-            float* sj = ssm_ckpt ? ssm_ckpt + (size_t)j * d.b.nseg * d.b.HPN : nullptr;
-            char* cj = conv_ckpt ? (char*)conv_ckpt + (size_t)j * d.b.nseg * d.conv_state : nullptr;
+            float* sj = ssm_ckpt ? ssm_ckpt + (size_t)j * own.nseg * d.b.HPN : nullptr;
+            char* cj = conv_ckpt ? (char*)conv_ckpt + (size_t)j * own.nseg * d.conv_state : nullptr;
             const float* ssm_in = k ? sj + (size_t)k * d.b.HPN : nullptr;
             const void* conv_in = k ? cj + (size_t)k * d.conv_state : nullptr;
-            float* ssm_out = last ? (float*)(ws + w.fin_ssm) : sj + (size_t)(k + 1) * d.b.HPN;
-            void* conv_out = last ? (void*)(ws + w.fin_conv) : (void*)(cj + (size_t)(k + 1) * d.conv_state);
+            float* ssm_out = last ? (float*)(ws + w.fin_ssm) : sj + (size_t)next * d.b.HPN;
+            void* conv_out = last ? (void*)(ws + w.fin_conv) : (void*)(cj + (size_t)next * d.conv_state);
             char* y = ws + w.act[j & 1];
+            Inner inner = {own.s, nullptr, nullptr};
+            if (several) {
+                inner.ssm = sj + (size_t)k * d.b.HPN;
+                inner.conv = cj + (size_t)k * d.conv_state;
+            }
             BLK_TRY(block_fwd(&c, &params[j], cur, ssm_in, conv_in, y, nullptr, nullptr, ssm_out, conv_out, ws + w.inner, w.inner_bytes,
-                              false, st, normed));
+                              false, st, normed, several ? &inner : nullptr));
             // the input of the next layer: the stack's output, a layer-axis checkpoint, or a buffer
             char* nxt = j + 1 == d.NL ? (char*)out + (size_t)t0 * row
                                       : (j + 1) % d.l == 0 ? (char*)l_ckpt + ((size_t)((j + 1) / d.l - 1) * d.b.L + t0) * row : y;
@@ -916,7 +1001,9 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
                                    const magc_block_grads_t* grads, void* workspace, size_t workspace_bytes, uint32_t flags,
                                    void* hip_stream) {
     StackDims d;
-    BLK_TRY(check_stack(sh, &d));
+    magc_blockstack_shape_t wide;
+    BlockDims own_b;
+    BLK_TRY(check_stack(sh, &d, TRAIN_WORK, &wide, &own_b));
     if (flags & ~(uint32_t)SSD_FLAG_ACCUM_PARAM) return SSD_ERR_ARG;
     if (!params_ok(params, d.NL) || !grads) return SSD_ERR_NULL;
     for (int j = 0; j < d.NL; ++j)
@@ -938,8 +1025,8 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
             if (d.b.L == 0 || !own(j)) BLK_HIP(clear_weights(d.b, grads[j], st));
         }
     if (d.b.L == 0) return SSD_OK;
-    if (!x0 || !dout || !dx0 || (d.ngl > 1 && !l_ckpt) || (d.b.nseg > 1 && (!ssm_ckpt || !conv_ckpt))) return SSD_ERR_NULL;
-    const StackWs w = stack_layout(sh, d, true);
+    if (!x0 || !dout || !dx0 || (d.ngl > 1 && !l_ckpt) || (own_b.nseg > 1 && (!ssm_ckpt || !conv_ckpt))) return SSD_ERR_NULL;
+    const StackWs w = stack_layout(&wide, d, true);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < w.total) return SSD_ERR_WORKSPACE;
     char* ws = (char*)workspace;
     // a cell's layer uses the block's own workspace layout inside the inner region (buffers of one segment;
@@ -949,7 +1036,8 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
     char* bws = ws + w.inner;
     for (int64_t k = d.b.nseg - 1; k >= 0; --k) {
         const int64_t t0 = k * d.b.s, rows = d.b.L - t0 < d.b.s ? d.b.L - t0 : d.b.s;
-        const magc_block_shape_t c = cell_shape(sh, rows);
+        const int64_t k0 = t0 / own_b.s;  // the caller's segment that starts these rows
+        const magc_block_shape_t c = cell_shape(&wide, rows);
         BlockDims dc;
         BLK_TRY(check(&c, &dc));
         const bool last = k + 1 == d.b.nseg;
@@ -961,8 +1049,8 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
             const char* xin = m ? (const char*)l_ckpt + ((size_t)(m - 1) * d.b.L + t0) * row : (const char*)x0 + (size_t)t0 * row;
             bool normed = false;
             for (int j = j0; j <= j1; ++j) {
-                const float* ssm_in = k ? ssm_ckpt + ((size_t)j * d.b.nseg + k) * d.b.HPN : nullptr;
-                const void* conv_in = k ? (const char*)conv_ckpt + ((size_t)j * d.b.nseg + k) * d.conv_state : nullptr;
+                const float* ssm_in = k ? ssm_ckpt + ((size_t)j * own_b.nseg + k0) * d.b.HPN : nullptr;
+                const void* conv_in = k ? (const char*)conv_ckpt + ((size_t)j * own_b.nseg + k0) * d.conv_state : nullptr;
                 char* zx = ws + w.zx + (size_t)(j - j0) * w.zx_bytes;
                 char* y = ws + w.y + (size_t)(j - j0) * w.y_bytes;
                 BLK_TRY(seg_in_proj(dc, c.eps, &params[j], bws, bw, xin, rows, zx, st, normed));
@@ -981,8 +1069,8 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
             for (int j = j1; j >= j0; --j) {
                 const char* xj = j == j0 ? (m ? (const char*)l_ckpt + ((size_t)(m - 1) * d.b.L + t0) * row : (const char*)x0 + (size_t)t0 * row)
                                          : ws + w.xs + (size_t)(j - j0) * d.act;
-                const float* ssm_in = k ? ssm_ckpt + ((size_t)j * d.b.nseg + k) * d.b.HPN : nullptr;
-                const void* conv_in = k ? (const char*)conv_ckpt + ((size_t)j * d.b.nseg + k) * d.conv_state : nullptr;
+                const float* ssm_in = k ? ssm_ckpt + ((size_t)j * own_b.nseg + k0) * d.b.HPN : nullptr;
+                const void* conv_in = k ? (const char*)conv_ckpt + ((size_t)j * own_b.nseg + k0) * d.conv_state : nullptr;
                 const char* zx = ws + w.zx + (size_t)(j - j0) * w.zx_bytes;
                 const char* y = ws + w.y + (size_t)(j - j0) * w.y_bytes;
                 // the cheap steps again from zxbcdt_j and y_j: (x | B | C), the normalised y.  The cell's top layer was
@@ -1032,7 +1120,9 @@ extern "C" int magc_blockstack_infer(const magc_blockstack_shape_t* sh, const ma
                                      float* ssm_state, void* conv_state, int32_t fresh, void* workspace, size_t workspace_bytes,
                                      void* hip_stream) {
     StackDims d;
-    BLK_TRY(check_stack(sh, &d));
+    magc_blockstack_shape_t wide;
+    BlockDims own;
+    BLK_TRY(check_stack(sh, &d, INFER_WORK, &wide, &own));
     if (!params_ok(params, d.NL) || !ssm_state || !conv_state) return SSD_ERR_NULL;
     hipStream_t st = (hipStream_t)hip_stream;
     if (d.b.L == 0) {
@@ -1043,19 +1133,20 @@ extern "C" int magc_blockstack_infer(const magc_blockstack_shape_t* sh, const ma
         return SSD_OK;
     }
     if (!x0 || !out) return SSD_ERR_NULL;
-    const StackWs w = stack_layout(sh, d, false);
+    const StackWs w = stack_layout(&wide, d, false);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < w.total) return SSD_ERR_WORKSPACE;
     char* ws = (char*)workspace;
     const size_t row = (size_t)d.b.dm * 2;
-    for (int64_t k = 0; k < d.b.nseg; ++k) {
-        const int64_t t0 = k * d.b.s, rows = d.b.L - t0 < d.b.s ? d.b.L - t0 : d.b.s;
-        const magc_block_shape_t c = cell_shape(sh, rows);
+    const int64_t step = pass_rows(d.b, d.b.s);
+    for (int64_t t0 = 0; t0 < d.b.L; t0 += step) {
+        const int64_t rows = d.b.L - t0 < step ? d.b.L - t0 : step;
+        const magc_block_shape_t c = cell_shape(&wide, rows);
         BlockDims dc;
         BLK_TRY(check(&c, &dc));
         const BlockWs bw = layout(dc, false);  // for the few-token path, which lays a block workspace out itself
         if (bw.total > w.inner_bytes) return SSD_ERR_WORKSPACE;
         char* bws = ws + w.inner;
-        const bool zero = fresh && k == 0;
+        const bool zero = fresh && t0 == 0;
         bool normed = false;  // the layer before has left this one's normalised input
         bool packed = false;  // the layer before has left this one's packed input
         const char* cur = (const char*)x0 + (size_t)t0 * row;
@@ -1100,7 +1191,9 @@ extern "C" int magc_blockstack_decode(const magc_blockstack_shape_t* sh_in, cons
     one.block.seqlen = 1;
     const magc_blockstack_shape_t* sh = &one;
     StackDims d;
-    BLK_TRY(check_stack(sh, &d));
+    magc_blockstack_shape_t wide;
+    BlockDims own;
+    BLK_TRY(check_stack(sh, &d, INFER_WORK, &wide, &own));  // one segment: as it is
     if (nseq < 0 || nseq > FEW_ROWS) return SSD_ERR_SHAPE;
     if (!params_ok(params, d.NL)) return SSD_ERR_NULL;
     if (nseq == 0) return SSD_OK;
