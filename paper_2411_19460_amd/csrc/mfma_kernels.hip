@@ -43,77 +43,95 @@ __device__ __forceinline__ float wave_prefix(float v) {
     return v;
 }
 
-// Decay preparation: cum (chunk-local inclusive cumsum of dt*A), dt in fp32, ein, eout.  A wave takes one chunk and head,
-// lane l the tokens E l .. E l + E - 1: nothing waits for other waves (over LDS the prefix sums took sixteen barriers), and
-// the four waves of a workgroup read neighbouring heads, i.e. the same cache lines of dt.  10007 tokens of 80 heads with the
-// scores: 18.9 -> 11.4 us.
-constexpr int PREP_HEADS = NTH / 64;
+// Decay preparation of one chunk and head by one wave, lane l the tokens E l .. E l + E - 1: cum (chunk-local inclusive cumsum of
+// dt*A), dt in fp32, ein, eout.  Nothing waits for other waves (over LDS the prefix sums took sixteen barriers), and the waves
+// of a workgroup take neighbouring heads, i.e. read the same cache lines of dt.  In two halves, so that the loads can be under
+// way while something else is worked on.
 template <int Q>
-__device__ __forceinline__ void prep_body(const SegParams& sp, int c, int h, int b) {
-    constexpr int E = Q / 64;
+struct Prep {
+    static constexpr int E = Q / 64;
     typedef float vec __attribute__((ext_vector_type(E)));
-    const int lane = threadIdx.x & 63, rows = chunk_rows(sp, c, Q);
-    if (h >= sp.H) return;
-    const bool raw = sp.raw.dt;
-    const int64_t rs = raw ? sp.raw.rs : sp.H;
-    const bf16_t* dt = (raw ? (const bf16_t*)sp.raw.dt : (const bf16_t*)sp.dt + (int64_t)b * sp.dts_b) + (int64_t)c * Q * rs + h;
-    const uint8_t* reset = sp.reset ? sp.reset + (int64_t)b * sp.reset_bs + (int64_t)c * Q : nullptr;
-    const float A = sp.A[h];
-    float d[E], a[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int i = E * lane + e, il = i < rows ? i : rows - 1;
-        d[e] = bf16_to_float(dt[il * rs]);
-        a[e] = reset && reset[il] ? RESET_LOG_DECAY : 0.f;
-    }
-    if (raw) {  // uniform
-        const float bias = sp.raw.bias[h];
-#pragma unroll
-        for (int e = 0; e < E; ++e) d[e] = bf16_to_float(float_to_bf16(softplus(d[e] + bias)));
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-        if (E * lane + e >= rows) d[e] = a[e] = 0.f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) a[e] += d[e] * A;
-    // prefix sums by doubling: token i adds token i - off, off = 1, 2, 4, ...
-#pragma unroll
-    for (int off = 1; off < Q; off <<= 1) {
-        float v[E];
+    bf16_t dt[E];
+
+    __device__ __forceinline__ void load(const SegParams& sp, int b, int c, int h, int lane, int rows) {
+        const bool raw = sp.raw.dt;
+        const int64_t rs = raw ? sp.raw.rs : sp.H;
+        const bf16_t* src = (raw ? (const bf16_t*)sp.raw.dt : (const bf16_t*)sp.dt + (int64_t)b * sp.dts_b) + (int64_t)c * Q * rs + h;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int src = off < E ? e - off : e;  // element, and how many lanes to the left of this one it lies
-            const int left = off < E ? (src < 0 ? 1 : 0) : off / E;
-            v[e] = left ? __shfl_up(a[(src + E) % E], left, 64) : a[(src + E) % E];
-            if (lane < left) v[e] = 0.f;
+            const int i = E * lane + e, il = i < rows ? i : rows - 1;
+            dt[e] = src[il * rs];
+        }
+    }
+    // vc: cum, vd: dt; returns cum at the end of the chunk
+    __device__ __forceinline__ float form(const SegParams& sp, int b, int c, int h, int lane, int rows, vec& vc, vec& vd) const {
+        float d[E], a[E];
+        const float A = sp.A[h];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            d[e] = bf16_to_float(dt[e]);
+            a[e] = 0.f;
+        }
+        if (sp.raw.dt) {  // uniform
+            const float bias = sp.raw.bias[h];
+#pragma unroll
+            for (int e = 0; e < E; ++e) d[e] = bf16_to_float(float_to_bf16(softplus(d[e] + bias)));
+        }
+        if (sp.reset) {  // uniform
+            const uint8_t* reset = sp.reset + (int64_t)b * sp.reset_bs + (int64_t)c * Q;
+#pragma unroll
+            for (int e = 0; e < E; ++e) a[e] = reset[E * lane + e < rows ? E * lane + e : rows - 1] ? RESET_LOG_DECAY : 0.f;
         }
 #pragma unroll
-        for (int e = 0; e < E; ++e) a[e] += v[e];
-    }
-    // cum at the end of the lane's 64-token block and of the one in front of it
-    constexpr int LPB = 64 / E;  // lanes of a block
-    const float end = __shfl(a[E - 1], lane | (LPB - 1), 64), prev = __shfl(a[E - 1], (lane | (LPB - 1)) - LPB, 64);
-    const float start = lane >= LPB ? prev : 0.f;
-    vec vc, vd, vi, vo;
+        for (int e = 0; e < E; ++e)
+            if (E * lane + e >= rows) d[e] = a[e] = 0.f;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        vc[e] = a[e];
-        vd[e] = d[e];
-        vi[e] = __expf(a[e] - start);
-        vo[e] = __expf(end - a[e]);
+        for (int e = 0; e < E; ++e) a[e] += d[e] * A;
+        // prefix sums by doubling: token i adds token i - off, off = 1, 2, 4, ...
+#pragma unroll
+        for (int off = 1; off < Q; off <<= 1) {
+            float v[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int src = off < E ? e - off : e;  // element, and how many lanes to the left of this one it lies
+                const int left = off < E ? (src < 0 ? 1 : 0) : off / E;
+                v[e] = left ? __shfl_up(a[(src + E) % E], left, 64) : a[(src + E) % E];
+                if (lane < left) v[e] = 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < E; ++e) a[e] += v[e];
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            vc[e] = a[e];
+            vd[e] = d[e];
+        }
+        return __shfl(a[E - 1], 63, 64);
     }
-    const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q + E * lane;
-    *(vec*)(sp.cum + o) = vc;
-    *(vec*)(sp.dtf + o) = vd;
-    *(vec*)(sp.ein + o) = vi;
-    *(vec*)(sp.eout + o) = vo;
-}
+    __device__ __forceinline__ void store(const SegParams& sp, int b, int c, int h, int lane, const vec& vc, const vec& vd) const {
+        // cum at the end of the lane's 64-token block and of the one in front of it
+        constexpr int LPB = 64 / E;  // lanes of a block
+        const float end = __shfl(vc[E - 1], lane | (LPB - 1), 64), prev = __shfl(vc[E - 1], (lane | (LPB - 1)) - LPB, 64);
+        const float start = lane >= LPB ? prev : 0.f;
+        vec vi, vo;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            vi[e] = __expf(vc[e] - start);
+            vo[e] = __expf(end - vc[e]);
+        }
+        const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q + E * lane;
+        *(vec*)(sp.cum + o) = vc;
+        *(vec*)(sp.dtf + o) = vd;
+        *(vec*)(sp.ein + o) = vi;
+        *(vec*)(sp.eout + o) = vo;
+    }
+};
 
 // ---------------------------------------------------------------------------------------------
 // Scores of one chunk and group: G[i][j] = C_i . B_j and its transpose, bf16, for the 64 x 64 blocks
 // on and below the diagonal.  Layout in the scratch area: G [Q][Q] then GT [Q][Q].
 template <int Q>
-__device__ __forceinline__ void cb_body(const SegParams& sp, int z, int pair) {
+__device__ __forceinline__ void cb_body(const SegParams& sp, int z, int pair, int w, int lane) {  // four waves
     constexpr int NB = Q / BLK;
     const int g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc);
     int I = 0, rem = pair;  // pair enumerates the block pairs (I, J <= I)
@@ -123,7 +141,6 @@ __device__ __forceinline__ void cb_body(const SegParams& sp, int z, int pair) {
     }
     const int J = rem;
     if (I >= NB) return;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int i0 = I * BLK + (w >> 1) * 32, j0 = J * BLK + (w & 1) * 32;
     const int64_t ts = (int64_t)sp.G * N_;
     const bf16_t* Cm = (const bf16_t*)sp.Cm + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
@@ -155,22 +172,6 @@ __device__ __forceinline__ void cb_body(const SegParams& sp, int z, int pair) {
     }
 }
 
-// The two steps that need nothing but the inputs -- decay preparation and scores -- as one launch: the first n_prep
-// workgroups do one chunk of PREP_HEADS heads of the former each, the rest one 64 x 64 block pair of the latter.
-template <int Q>
-__global__ __launch_bounds__(NTH) void mk_prep_cb(SegParams sp, int n_prep) {
-    constexpr int NPAIR = (Q / BLK) * (Q / BLK + 1) / 2;
-    int z = blockIdx.x;
-    if (z < n_prep) {
-        const int c = z % sp.nc, nh = (sp.H + PREP_HEADS - 1) / PREP_HEADS;
-        z /= sp.nc;
-        prep_body<Q>(sp, c, z % nh * PREP_HEADS + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), z / nh);
-    } else {
-        z -= n_prep;
-        cb_body<Q>(sp, z / NPAIR, z % NPAIR);
-    }
-}
-
 // ---------------------------------------------------------------------------------------------
 // role 0: states_bf[b,c,h]  = sum_j exp(T - cum_j) dt_j x_j (x) B_j      (chunk state, bf16 [P][N])
 // role 1: dstates_bf[b,c,h] = sum_i exp(cum_i) dY_i (x) C_i              (local state adjoint)
@@ -181,60 +182,61 @@ __global__ __launch_bounds__(NTH) void mk_prep_cb(SegParams sp, int n_prep) {
 // the head: they go through LDS once and each wave keeps its Q/16 operand fragments in registers
 // for every head of the slice.  Per head the token-major tile (x or dY, weighted per token) is
 // prefetched in registers during the previous head, staged in LDS and read with transpose loads.
-template <int Q>
-union OuterLds {
-    char bc[Q * BPITCH];  // B or C rows of the chunk (prologue only: each wave takes its fragments, then the space is xt)
-    char xt[Q * XPITCH];  // weight * x or weight * dY
-};
+// The weights come from the decay preparation, which needs nothing but the inputs either: a wave does a head of the slice,
+// eight heads ahead of their use (role 0 stores it for the kernels that follow), and the scores of the chunks are further workgroups
+// of this launch.  As a launch in front of this one, which read the weights from memory, against now (us, two launches -> one):
+// 10007 tokens of 80 heads 11.9 + 35.2 -> 37.8; 8192 of 24 8.8 + 13.1 -> 16.3, both roles 8.8 + 19.7 -> 23.2; 65536 tokens of
+// 80 heads forward + backward, four segments in flight, 3110 -> 3048.
+constexpr int OUTER_THR = 512, PREP_HEADS = OUTER_THR / 64;
 
-constexpr int OUTER_THR = 512;
+template <int Q>
+struct OuterLds {
+    union {
+        char bc[Q * BPITCH];  // B or C rows of the chunk (prologue only: each wave takes its fragments, then the space is xt)
+        char xt[Q * XPITCH];  // weight * x or weight * dY
+    };
+    float wt[PREP_HEADS][Q];  // weights of eight heads
+};
 
 template <int Q>
 struct OuterPre {
     static constexpr int NV = Q * 8 / OUTER_THR > 0 ? Q * 8 / OUTER_THR : 1;
     bf16x8 t[NV];
-    float cv[NV], dv[NV];  // cum and dt of the vector's token
-    float T;               // cum at the end of the chunk
 };
 
-// Loads only: no arithmetic on the loaded values here, so that nothing waits for them before the
-// next head's staging (the weights are formed in outer_weight at that point).
+// Loads only: nothing waits for them before the next head's staging.
 template <int Q>
 __device__ __forceinline__ void outer_load(OuterPre<Q>& pr, const SegParams& sp, int role, int b, int c, int h, int tid) {
     const int64_t xt = (int64_t)sp.H * P_;
     const int64_t xrow = ((int64_t)c * Q * sp.H + h) * P_;
     const bf16_t* src = role == 0 ? (const bf16_t*)sp.x + (int64_t)b * sp.xs_b + xrow
                                   : (const bf16_t*)sp.dy + (int64_t)b * sp.dys_b + xrow;
-    const int64_t cbase = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
-    pr.T = sp.cum[cbase + Q - 1];
     // addresses = a wave-uniform base (scalar registers) + one 32-bit byte offset per lane
     const int t8 = tid % (Q * 8);  // Q = 64: one vector per thread
     const uint32_t rowbytes = (uint32_t)xt * 2, off = (uint32_t)(t8 >> 3) * rowbytes + (uint32_t)(t8 & 7) * 16;
     const rsrc_t rows = make_rows(src, chunk_rows(sp, c, Q), rowbytes);
-    const uint32_t roff = (uint32_t)(t8 >> 3) * 4;
 #pragma unroll
     for (int k = 0; k < OuterPre<Q>::NV; ++k) {
         // one reader per launch: streaming load (keeps the L2 for the kernels of other segments that do share tiles)
         pr.t[k] = rows_load<AUX_NT>(rows, off + k * (OUTER_THR / 8) * rowbytes);
-        pr.cv[k] = *(const float*)((const char*)(sp.cum + cbase + k * (OUTER_THR / 8)) + (size_t)roff);
-        pr.dv[k] = *(const float*)((const char*)(sp.dtf + cbase + k * (OUTER_THR / 8)) + (size_t)roff);
     }
 }
 
-template <int Q>
-__device__ __forceinline__ float outer_weight(const OuterPre<Q>& pr, int role, int k) {
-    return role == 0 ? __expf(pr.T - pr.cv[k]) * pr.dv[k] : __expf(pr.cv[k]);
-}
-
-// Two workgroups per compute unit (70 KB of LDS, at most 128 registers): one stages its next head while the
+// Two workgroups per compute unit (78 KB of LDS, at most 128 registers): one stages its next head while the
 // other contracts.
 template <int Q, bool F32OUT>
-__global__ __launch_bounds__(OUTER_THR, 2) void mk_chunk_outer(SegParams sp, int nroles) {
+__global__ __launch_bounds__(OUTER_THR, 4) void mk_chunk_outer(SegParams sp, int nroles, int n_outer) {
     constexpr int KS = Q / 16;
     __shared__ __attribute__((aligned(16))) OuterLds<Q> L;
     int z = blockIdx.x;
     [[maybe_unused]] const int zlog = z;
-    if ((gridDim.x & 7) == 0) z = (z & 7) * (gridDim.x >> 3) + (z >> 3);
+    if (z >= n_outer) {  // scores: two block pairs a workgroup
+        constexpr int NPAIR = (Q / BLK) * (Q / BLK + 1) / 2;
+        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = 2 * (z - n_outer) + (w >> 2);
+        if (i < sp.Bt * sp.nc * sp.G * NPAIR) cb_body<Q>(sp, i / NPAIR, i % NPAIR, w & 3, threadIdx.x & 63);
+        return;
+    }
+    if ((n_outer & 7) == 0) z = (z & 7) * (n_outer >> 3) + (z >> 3);
     const int ns = sp.outer_split, slice = z % ns;
     z /= ns;
     const int role = z % nroles;
@@ -243,15 +245,35 @@ __global__ __launch_bounds__(OUTER_THR, 2) void mk_chunk_outer(SegParams sp, int
     const int hps = sp.hpg / ns, h0 = g * sp.hpg + slice * hps;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), ph = w >> 2, nt = w & 3;
     const int64_t bt = (int64_t)sp.G * N_;
+    const int nrows = chunk_rows(sp, c, Q);
+    Prep<Q> pp;
+    if (w < hps) pp.load(sp, b, c, h0 + w, lane, nrows);
     OuterPre<Q> pr;
     outer_load<Q>(pr, sp, role, b, c, h0, tid);
+    // what is derived from such a value is formed where it is used and not kept in registers over the loop
+    auto opaque = [](int v) {
+        asm volatile("" : "+v"(v));
+        return v;
+    };
+    // the weights of this wave's head of the eight from hh on
+    auto weights = [&](int hh) {
+        if (hh + w >= hps) return;
+        const int ln = opaque(lane);
+        typename Prep<Q>::vec vc, vd, vw;
+        const float T = pp.form(sp, b, c, h0 + hh + w, ln, nrows, vc, vd);
+#pragma unroll
+        for (int e = 0; e < Q / 64; ++e) vw[e] = role == 0 ? __expf(T - vc[e]) * vd[e] : __expf(vc[e]);
+        *(typename Prep<Q>::vec*)(&L.wt[w][Q / 64 * ln]) = vw;
+        if (role == 0) pp.store(sp, b, c, h0 + hh + w, ln, vc, vd);
+    };
     // prologue: B (role 0) or C (role 1) rows -> LDS -> this wave's fragments
     const bf16_t* rhs = (role == 0 ? (const bf16_t*)sp.Bm : (const bf16_t*)sp.Cm) + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
-    const rsrc_t rows = make_rows(rhs, chunk_rows(sp, c, Q), (uint32_t)bt * 2);
+    const rsrc_t rows = make_rows(rhs, nrows, (uint32_t)bt * 2);
     for (int v = tid; v < Q * 16; v += OUTER_THR) {
         const int row = v >> 4, seg = v & 15;
         *(bf16x8*)(L.bc + row * BPITCH + seg * 16) = rows_load(rows, (uint32_t)row * (uint32_t)bt * 2 + seg * 16);
     }
+    weights(0);
     __syncthreads();
     bf16x8 fb[KS];
 #pragma unroll
@@ -264,27 +286,30 @@ __global__ __launch_bounds__(OUTER_THR, 2) void mk_chunk_outer(SegParams sp, int
 #pragma unroll
         for (int k = 0; k < OuterPre<Q>::NV; ++k) {
             const int v = tid + OUTER_THR * k, row = v >> 3, seg = v & 7;
-            if (v < Q * 8) *(bf16x8*)(L.xt + row * XPITCH + seg * 16) = scale8(pr.t[k], outer_weight<Q>(pr, role, k));
+            if (v < Q * 8) *(bf16x8*)(L.xt + row * XPITCH + seg * 16) = scale8(pr.t[k], L.wt[hh % PREP_HEADS][row]);
         }
         SSDK_STAMP(4, 2);
         __syncthreads();
         SSDK_STAMP(4, 3);
-        if (hh + 1 < hps) outer_load<Q>(pr, sp, role, b, c, h + 1, tid);
+        if (hh % PREP_HEADS == PREP_HEADS - 1 && hh + 1 + w < hps) pp.load(sp, b, c, h + 1 + w, lane, nrows);
+        if (hh + 1 < hps) outer_load<Q>(pr, sp, role, b, c, h + 1, opaque(tid));
         SSDK_STAMP(4, 4);
         f32x16 acc = zero16();
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) acc = mfma(frag_tr(L.xt, XPITCH, 16 * ks, 32 * ph, lane), fb[ks], acc);
         const int64_t so = (((int64_t)b * sp.nc + c) * sp.H + h) * (P_ * N_);
+        const int ls = opaque(lane);
         if (F32OUT) {  // fp32 scan input, in an array of its own
             float* out = (role == 0 ? sp.states : sp.dstates) + so;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) out[(32 * ph + acc_row(r, lane)) * N_ + 32 * nt + (lane & 31)] = acc[r];
+            for (int r = 0; r < 16; ++r) out[(32 * ph + acc_row(r, ls)) * N_ + 32 * nt + (ls & 31)] = acc[r];
         } else {
             // bf16, into the slot where the scan will put the state entering the chunk (total adjoint leaving it)
             __bf16* out = (__bf16*)(role == 0 ? sp.states_bf : sp.dstates_bf) + so;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) out[(32 * ph + acc_row(r, lane)) * N_ + 32 * nt + (lane & 31)] = (__bf16)acc[r];
+            for (int r = 0; r < 16; ++r) out[(32 * ph + acc_row(r, ls)) * N_ + 32 * nt + (ls & 31)] = (__bf16)acc[r];
         }
+        if (hh % PREP_HEADS == PREP_HEADS - 1) weights(hh + 1);  // of the next eight heads: the last of these is staged
         SSDK_STAMP(4, 5);
     }
 }
@@ -433,18 +458,19 @@ hipError_t scan(const SegParams& sp, hipStream_t st) {
 template <int Q>
 hipError_t fwd_q(const SegParams& sp, bool need_y, hipStream_t st) {
     constexpr int NB = Q / BLK;
-    const int n_prep = sp.nc * ((sp.H + PREP_HEADS - 1) / PREP_HEADS) * sp.Bt, n_cb = sp.Bt * sp.nc * sp.G * (NB * (NB + 1) / 2);
-    SSDK_LAUNCH(K_MFMA_PREP_CB, st, mk_prep_cb<Q>, dim3(n_prep + n_cb), dim3(NTH), sp, n_prep);
-    {   // chunk states; on the backward path (need_y false) the local state adjoints ride in the same launch
+    const int n_cb = sp.Bt * sp.nc * sp.G * (NB * (NB + 1) / 2);
+    {   // decay preparation, scores, chunk states; on the backward path (need_y false) the local state adjoints ride in the same launch
         SegParams so = sp;
         const int nroles = need_y ? 1 : 2;
         // alone on the machine (10007 tokens of 80 heads, eight slices -> ten: 40.2 -> 35.9 us); with others in flight as mk_dual
         const int64_t base = (int64_t)sp.Bt * sp.nc * sp.G * nroles;
         so.outer_split = sp.wg_target < 256 ? pick_split(sp.hpg, base, sp.wg_target) : pick_rounds(sp.hpg, base, 2, 140);
+        const int n_outer = sp.Bt * sp.nc * sp.G * nroles * so.outer_split;
+        const dim3 grid(n_outer + (n_cb + 1) / 2);
         if (sp.flags & SSD_FLAG_FP32_CHUNK_STATES)
-            SSDK_LAUNCH(need_y ? K_MFMA_CHUNK_STATE : K_MFMA_DSTATE, st, (mk_chunk_outer<Q, true>), dim3(sp.Bt * sp.nc * sp.G * nroles * so.outer_split), dim3(OUTER_THR), so, nroles);
+            SSDK_LAUNCH(need_y ? K_MFMA_CHUNK_STATE : K_MFMA_DSTATE, st, (mk_chunk_outer<Q, true>), grid, dim3(OUTER_THR), so, nroles, n_outer);
         else
-            SSDK_LAUNCH(need_y ? K_MFMA_CHUNK_STATE : K_MFMA_DSTATE, st, (mk_chunk_outer<Q, false>), dim3(sp.Bt * sp.nc * sp.G * nroles * so.outer_split), dim3(OUTER_THR), so, nroles);
+            SSDK_LAUNCH(need_y ? K_MFMA_CHUNK_STATE : K_MFMA_DSTATE, st, (mk_chunk_outer<Q, false>), grid, dim3(OUTER_THR), so, nroles, n_outer);
     }
     if (!need_y) return hipSuccess;  // the backward pass restores the entering states in the launch of its own scan
     // the scan is the only step that needs the previous segment (its leaving state)

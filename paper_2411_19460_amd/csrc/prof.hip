@@ -19,7 +19,7 @@ std::vector<hipEvent_t> g_pool;
 const char* const g_names[K_COUNT] = {
     "chunk_state", "state_scan_fwd", "chunk_out", "state_scan_bwd", "bwd_main", "param_reduce", "dBC", "fill", "copy",
     "mfma_chunk_state", "mfma_chunk_out", "mfma_dstate_local", "mfma_bwd_main", "mfma_dG", "mfma_dBC", "mfma_bwd_trio",
-    "mfma_prep_cb", "mfma_final_ddt"};
+    "mfma_final_ddt"};
 
 hipEvent_t take_event() {
     if (!g_pool.empty()) {
