@@ -24,13 +24,14 @@ int pick_split(int heads_per_group, int64_t base, int target) {
 // us, as above -> this, 2000 tokens of 80 heads 64 -> 56, 4000 of 80 111 -> 90, 10007 of 24 / 32 / 64 / 80 92 / 112 / 209 / 263 ->
 // 79 / 95 / 167 / 210, backward 287 -> 267 and 281 / 345 / 710 / 882 -> 260 / 310 / 628 / 794; no longer, but for
 // what the runs of one side differ by, at any of 35 sizes, 500 ... 60000 tokens.
+// The slices need not divide the heads (only those that do -> any, forward + backward: 3333 tokens of 64 heads 185 -> 163 us;
+// prefill of 10007 tokens of 80 heads 132.3 -> 127.7).
 int pick_rounds(int heads_per_group, int64_t base, int per_unit, int prologue) {
     constexpr int64_t UNITS = 256;
     int best = 1;
     int64_t least = INT64_MAX;
     for (int ns = 1; ns <= heads_per_group; ++ns) {
-        if (heads_per_group % ns) continue;
-        const int64_t n = base * ns, hps = heads_per_group / ns;
+        const int64_t n = base * ns, hps = (heads_per_group + ns - 1) / ns;  // of the longer slices
         const int64_t t = n <= UNITS && per_unit == 2 ? 65 * hps + prologue : (n + UNITS * per_unit - 1) / (UNITS * per_unit) * (100 * hps + prologue);
         if (t < least) least = t, best = ns;
     }
@@ -111,6 +112,14 @@ HeadSlices part_slices(const Dims& d, bool mfma, int wg_target) {
     const int64_t nt = (d.Q + 63) / 64, nn = (d.N + 63) / 64, bg = d.Bt * d.G;
     return mfma ? HeadSlices(d, d.hpg, bg * 2, wg_target) : HeadSlices(d, GENERIC_SLICES, bg * 2 * nt * nn, 256);
 }
+// Room for the partial sums of dG of a span, in bf16 chunks of scores: one per head slice, two where they are fp32 (generic
+// kernels, and fit_splits: of at most half a round of slices, at chunks of 256 mostly no more than the general rule's bf16 ones).
+int64_t dg_places(const Dims& d, bool mfma, int wg_target) {
+    const int64_t bg = d.Bt * d.G, all = bg * d.nc * d.hpg;
+    const int64_t n = bg * dg_slices(d, mfma, wg_target).slots(d.nc) * (mfma && !d.dg_f32 ? 1 : 2);
+    if (!mfma || d.Q != 128 || wg_target < 256 || n >= 512) return n;
+    return all < 512 ? (n > all ? n : all) : 512;
+}
 }  // namespace
 
 // Slices of the three head-walking passes of the backward sweep (one launch, chunks of 128 and 256) for sp's span of the sequence.
@@ -135,8 +144,8 @@ void fit_splits(SegParams& sp, const Dims& d, bool mfma, int wg_target) {
     // thousands of cycles of a workgroup around its heads and for each of them: dx, dG, head sums
     struct Cost { int64_t around[3], head[3]; };
     const Cost c = d.Q == 256 ? Cost{{8, 11, 13}, {10, 12, 5}} : Cost{{6, 8, 9}, {11, 8, 5}};
-    const int64_t base = d.Bt * nc * d.G, units = d.Q == 256 ? 256 : 512;
-    auto one = [&](int pass, int64_t slices) { return c.around[pass] + c.head[pass] * (d.hpg / slices); };
+    const int64_t base = d.Bt * nc * d.G, units = d.Q == 256 ? 256 : 512, places = dg_places(d, mfma, wg_target);
+    auto one = [&](int pass, int64_t slices) { return c.around[pass] + c.head[pass] * ((d.hpg + slices - 1) / slices); };
     auto longest = [&](int64_t a, int64_t p) {
         int64_t t = one(0, a);
         t = one(1, a) > t ? one(1, a) : t;
@@ -146,10 +155,10 @@ void fit_splits(SegParams& sp, const Dims& d, bool mfma, int wg_target) {
     const int64_t work = a0 * (one(0, a0) + one(1, a0)) + 2 * p0 * one(2, p0);
     int64_t least = base * work / units + longest(a0, p0) / 2;
     for (int a = 1; a <= a0 && base * 2 * (a + 1) <= units; ++a) {
-        if (d.hpg % a) continue;
-        const bool f32 = d.dg_f32 || (a > 1 && a < a0);  // fits: see ws_layout
+        const bool f32 = d.dg_f32 || (a > 1 && a < a0);
+        if (base * a * (f32 ? 2 : 1) > places) continue;
         for (int p = 1; p <= p0 && base * 2 * (a + p) <= units; ++p)
-            if (d.hpg % p == 0 && longest(a, p) < least)
+            if (longest(a, p) < least)
                 least = longest(a, p), sp.dual_split = sp.dg_split = a, sp.part_split = p, sp.dg_f32 = f32;
     }
 }
@@ -178,17 +187,11 @@ WsLayout ws_layout(const Dims& d, bool bwd, bool mfma, int wg_target, bool fp32c
     if (mfma) w.eout = take(tok);
     if (mfma) w.states_bf = take((size_t)d.Bt * d.nc * d.H * PN * 2);
     const int64_t nt = (d.Q + 63) / 64, nn = (d.N + 63) / 64, np = (d.P + 63) / 64;  // 64 x 64 tiles of the generic kernels
-    const HeadSlices dg = dg_slices(d, mfma, wg_target), part = part_slices(d, mfma, wg_target);
+    const HeadSlices part = part_slices(d, mfma, wg_target);
     if (bwd) {
         if (!mfma || fp32cs) w.dstates = take((size_t)d.Bt * d.nc * d.H * PN * 4);
         if (mfma) w.dstates_bf = take((size_t)d.Bt * d.nc * d.H * PN * 2);
-        {   // one partial sum per head slice: fp32 (generic kernels), bf16 (MFMA kernels), or fp32 of at most half a round of
-            // slices (fit_splits): at chunks of 256 no more than the general rule's bf16 ones
-            const int64_t bg = d.Bt * d.G, all = bg * d.nc * d.hpg;
-            int64_t slots = bg * dg.slots(d.nc) * (mfma && !d.dg_f32 ? 1 : 2);
-            if (mfma && d.Q == 128 && wg_target >= 256 && slots < 512) slots = all < 512 ? (slots > all ? slots : all) : 512;
-            w.dG = take((size_t)slots * d.Q * d.Q * 2);
-        }
+        w.dG = take((size_t)dg_places(d, mfma, wg_target) * d.Q * d.Q * 2);
         w.dbc_part = take((size_t)d.Bt * part.slots(d.nc) * d.G * 2 * d.Q * d.N * 4);
         w.gterm = take(tok * (mfma ? 1 : 2 * nn));
         w.sterm = take(tok * (mfma ? 1 : 2 * nn));

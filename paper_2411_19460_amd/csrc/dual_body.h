@@ -333,7 +333,8 @@ __device__ __forceinline__ void dual_body(const SegParams& sp, DualLds<Q>& L, in
     const int ns = sp.dual_split, slice = z % ns;
     z /= ns;
     const int g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc);
-    const int hps = sp.hpg / ns, h0 = g * sp.hpg + slice * hps;
+    const Slice sl = slice_of(sp.hpg, ns, slice);
+    const int hps = sl.n, h0 = g * sp.hpg + sl.first;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Q = 256: waves w and w + 4 share a SIMD and take tiles t and 7 - t (equal causal work per SIMD)
     const int T = (Q == 256 && w >= 4) ? 11 - w : w;

@@ -307,7 +307,8 @@ __device__ __forceinline__ void dg_body(const SegParams& sp, DgLds<Q>& L, int z,
     const int ns = sp.dg_split, slice = z % ns;
     z /= ns;
     const int g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc);
-    const int hps = sp.hpg / ns, h0 = g * sp.hpg + slice * hps;
+    const Slice sl = slice_of(sp.hpg, ns, slice);
+    const int hps = sl.n, h0 = g * sp.hpg + sl.first;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cnt = M::count(w), slot0 = M::slot0(w);
     // prologue: the scores of the owned tiles in accumulator layout
@@ -469,7 +470,8 @@ __device__ __forceinline__ void part_body(const SegParams& sp, PartLds<Q>& LL, i
     const int role = z & 1;
     z >>= 1;
     const int g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc);
-    const int hps = sp.hpg / ns, h0 = g * sp.hpg + slice * hps;
+    const Slice sl = slice_of(sp.hpg, ns, slice);
+    const int hps = sl.n, h0 = g * sp.hpg + sl.first;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), rg = w >> 1, nh = w & 1;
     f32x16 acc[RT][2];
 #pragma unroll

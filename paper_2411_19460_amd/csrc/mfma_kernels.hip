@@ -242,7 +242,8 @@ __global__ __launch_bounds__(OUTER_THR, 4) void mk_chunk_outer(SegParams sp, int
     const int role = z % nroles;
     z /= nroles;
     const int g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc);
-    const int hps = sp.hpg / ns, h0 = g * sp.hpg + slice * hps;
+    const Slice sl = slice_of(sp.hpg, ns, slice);
+    const int hps = sl.n, h0 = g * sp.hpg + sl.first;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), ph = w >> 2, nt = w & 3;
     const int64_t bt = (int64_t)sp.G * N_;
     const int nrows = chunk_rows(sp, c, Q);

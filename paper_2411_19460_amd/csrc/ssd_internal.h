@@ -257,6 +257,14 @@ hipError_t mfma_launch_dual(const SegParams& sp, int epi, hipStream_t st);
 hipError_t mfma_launch_grad_bc(const SegParams& sp, hipStream_t st);
 // Smallest divisor ns of heads_per_group with base * ns >= target workgroups (else heads_per_group).
 int pick_split(int heads_per_group, int64_t base, int target);
+// The heads of slice i of ns: slices of equal length, or of two lengths one apart, the longer first.
+struct Slice {
+    int first, n;
+};
+__host__ __device__ inline Slice slice_of(int heads, int ns, int i) {
+    const int q = heads / ns, r = heads - q * ns;
+    return {q * i + (i < r ? i : r), q + (i < r ? 1 : 0)};
+}
 // Slices for a launch that has the machine to itself (see api.hip).
 int pick_rounds(int heads_per_group, int64_t base, int per_unit, int prologue);
 

@@ -1,0 +1,24 @@
+"""Head slices of two lengths one apart (the slices need not divide the heads of a group): every tensor against the oracle."""
+import pytest
+
+from test_gpu_slices import test_few_slices_round_the_score_gradients_once as check_rounding
+from test_gpu_slices import test_slices_of_a_launch_on_its_own as check_slices
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("case", [
+    # Bt, L, H, G, Q, segment
+    (1, 3333, 64, 1, 256, 4096),       # 14 chunks: slices of three and four heads forward, six and seven for dx and dG
+    (1, 32 * 256 - 9, 23, 1, 256, 8192),  # a prime number of heads
+    (2, 2000, 22, 2, 256, 2048),       # eleven heads a group
+    (1, 3001, 13, 1, 128, 1024),
+    (1, 2000, 7, 1, 64, 2048),
+])
+def test_slices_of_two_lengths(case):
+    check_slices(case)
+
+
+@pytest.mark.parametrize("case", [(1, 3333, 64, 1, 256, 4096), (1, 32 * 256 - 9, 23, 1, 256, 8192)])
+def test_their_partial_sums_are_rounded_once(case):
+    check_rounding(case)
