@@ -717,10 +717,12 @@ int ssdk::scan_bwd(const ssd_shape_t* shape, const void* x, const void* dt, cons
         sp.dA = dA;
         sp.dD = dD;
         sp.dcarry = sps[0].dcarry;
+        sp.param_count = i ? sps[0].param_count : (int*)sp.dA_part;  // the block's own array for one span's partial sums is free
+        sp.param_stride = d.Bt * d.nc < 32 ? (int)(d.Bt * d.nc) : 32;  // what fits there, a cache line each at most
         sp.dA_part = part_all;
         sp.dD_part = (float*)((char*)part_all + align_up((size_t)d.Bt * d.nct * d.H * 4));
         sp.nc_total = (int)d.nct;  // every chunk of the sequence writes a dA / dD partial sum
-        sp.defer_param = 1;
+        sp.accumulate = (flags & SSD_FLAG_ACCUM_PARAM) ? 1 : 0;
     }
     if (!fork_lanes(pp, nl, st)) return SSD_ERR_LAUNCH;
     for (int64_t q = d.nspan - 1, it = 0; q >= 0; --q, ++it) {
@@ -754,6 +756,7 @@ int ssdk::scan_bwd(const ssd_shape_t* shape, const void* x, const void* dt, cons
                 sp.state_in_bs = d.nseg * (int64_t)HPN;
             }
         }
+        sp.first_span = it == 0;
         sp.dcarry_in = it == 0 ? dfinal_state : sp.dcarry;
         sp.ev_wait = sp.ev_record = nullptr;
         hipError_t e = mfma ? mfma_forward_segment(sp, false, sk) : generic_forward_segment(sp, d.bf16, false, sk);
@@ -769,8 +772,6 @@ int ssdk::scan_bwd(const ssd_shape_t* shape, const void* x, const void* dt, cons
         }
     }
     if (!join_lanes(pp, nl, st)) return SSD_ERR_LAUNCH;
-    sps[0].accumulate = (flags & SSD_FLAG_ACCUM_PARAM) ? 1 : 0;
-    if (launch_param_reduce(sps[0], st) != hipSuccess) return SSD_ERR_LAUNCH;
     return SSD_OK;
 }
 

@@ -438,6 +438,7 @@ __global__ __launch_bounds__(NTHREADS) void k_state_scan(SegParams sp) {
         if (sp.state_out16) sp.state_out16[(int64_t)b * sp.state_out16_bs + bh] = float_to_bf16(hc);
         return;
     }
+    if (sp.first_span && e == 0 && b == 0) sp.param_count[(int64_t)h * sp.param_stride] = 0;
     const int64_t ce = (int64_t)b * HPN + bh;
     float g = sp.dcarry_in ? sp.dcarry_in[ce] : 0.f;
     float* dS = sp.dstates + (int64_t)b * nc * HPN + bh;
@@ -839,8 +840,8 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_final(SegParams sp, Vec vec, i
         z -= n_dbc;
         const int h = z % sp.H, c = (z / sp.H) % sp.nc, b = z / (sp.H * sp.nc);
         const int n32 = 2 * ((N + TM - 1) / TM), p32 = 2 * ((sp.P + TM - 1) / TM);
-        ddt_finalize_body(
-            sp, D, c, h, b,
+        ddt_finalize_body<4>(
+            sp, &D, c, h, b,
             [&](int64_t o, int i) {
                 const int64_t ts = sp.tok_stride;
                 const int own = 2 * (i / TM);  // tiles right of (above) a token's own 64 x 64 tile do not exist
@@ -951,36 +952,6 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_final(SegParams sp, Vec vec, i
     }
 }
 
-// One block per head: strided partial sums, then a fixed-shape tree (deterministic).
-__global__ void k_param_reduce(SegParams sp) {
-    __shared__ float sa[256], sd[256];
-    const int h = blockIdx.x, t = threadIdx.x;
-    float a = 0.f, d = 0.f;
-    for (int64_t bc = t; bc < (int64_t)sp.Bt * sp.nc_total; bc += 256) {
-        a += sp.dA_part[bc * sp.H + h];
-        d += sp.dD_part[bc * sp.H + h];
-    }
-    sa[t] = a;
-    sd[t] = d;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (t < off) {
-            sa[t] += sa[t + off];
-            sd[t] += sd[t + off];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        if (sp.accumulate) {
-            sp.dA[h] += sa[0];
-            sp.dD[h] += sd[0];
-        } else {
-            sp.dA[h] = sa[0];
-            sp.dD[h] = sd[0];
-        }
-    }
-}
-
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 // 16-byte (fp32) / 8-byte (bf16) loads along P and N: sizes and every pointer and stride multiples of four elements
@@ -1026,7 +997,6 @@ hipError_t bwd_segment(const SegParams& sp0, hipStream_t st) {
     SSDK_LAUNCH_LDS(K_BWD_MAIN, st, k_bwd_walk<T>, dim3(n_part + n_dg + n_u), dim3(NTHREADS), lds_bytes(per_token), sp, vec_of<T>(sp), n_part, n_dg);
     const int n_dbc = bcg * 2 * NN * NT;
     SSDK_LAUNCH(K_DBC, st, k_bwd_final<T>, dim3(n_dbc + sp.Bt * sp.nc * sp.H), dim3(NTHREADS), sp, vec_of<T>(sp), n_dbc);
-    if (!sp.defer_param) SSDK_LAUNCH(K_PARAM, st, k_param_reduce, dim3(sp.H), dim3(256), sp);
     return hipSuccess;
 }
 
@@ -1048,11 +1018,6 @@ hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t s
 
 hipError_t generic_forward_segment(const SegParams& sp, bool is_bf16, bool need_y, hipStream_t st) {
     return is_bf16 ? fwd_segment<bf16_t>(sp, need_y, st) : fwd_segment<float>(sp, need_y, st);
-}
-
-hipError_t launch_param_reduce(const SegParams& sp, hipStream_t st) {
-    SSDK_LAUNCH(K_PARAM, st, k_param_reduce, dim3(sp.H), dim3(256), sp);
-    return hipSuccess;
 }
 
 hipError_t generic_backward_segment(const SegParams& sp, bool is_bf16, hipStream_t st) {

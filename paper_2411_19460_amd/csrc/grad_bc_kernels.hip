@@ -788,24 +788,19 @@ __device__ __forceinline__ void final_body(const SegParams& sp, FinLds<Q>& L, in
 
 // The two steps behind the head-walking passes -- dB / dC from the partial sums, and ddt with the chunk's dA / dD
 // partial sums from the per-token scalars -- as one launch (both run 256 threads per workgroup): the
-// first n_final workgroups do the former, the rest one (chunk, head) of the latter each.
-template <int Q>
-union FinDdtLds {
-    FinLds<Q> fin;
-    DdtLds ddt;
-};
-
+// first n_final workgroups do the former, a wave of the rest one (chunk, head) of the latter each.
 template <int Q>
 __global__ __launch_bounds__(NTH) void mk_final_ddt(SegParams sp, int n_final) {
-    __shared__ __attribute__((aligned(16))) FinDdtLds<Q> L;
+    __shared__ __attribute__((aligned(16))) FinLds<Q> L;
     int z = blockIdx.x;
     if (z < n_final) {
-        final_body<Q>(sp, L.fin, z);
+        final_body<Q>(sp, L, z);
     } else {
-        z -= n_final;
+        z = (z - n_final) * (NTH / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // a wave has up to 256 tokens, the longest chunk here
         const int c = z % sp.nc;
         z /= sp.nc;
-        ddt_finalize_body(sp, L.ddt, c, z % sp.H, z / sp.H, [&](int64_t o, int) { return ddt_load_mfma(sp, o); },
+        if (z >= sp.H * sp.Bt) return;
+        ddt_finalize_body<1>(sp, nullptr, c, z % sp.H, z / sp.H, [&](int64_t o, int) { return ddt_load_mfma(sp, o); },
                           [&](int64_t idx, float v) { ((bf16_t*)sp.ddt)[idx] = float_to_bf16(v); });
     }
 }
@@ -824,7 +819,7 @@ hipError_t grad_bc_q(const SegParams& sp0, hipStream_t st) {
         SSDK_LAUNCH(K_MFMA_DBC, st, mk_dBC_part<Q>, dim3(n_part), dim3(PartCfg<Q>::NTHR), sp);
     }
     const int n_final = sp.Bt * sp.nc * sp.G * 2 * (Q / 32);
-    SSDK_LAUNCH(K_MFMA_FINAL_DDT, st, mk_final_ddt<Q>, dim3(n_final + sp.nc * sp.H * sp.Bt), dim3(NTH), sp, n_final);
+    SSDK_LAUNCH(K_MFMA_FINAL_DDT, st, mk_final_ddt<Q>, dim3(n_final + (sp.nc * sp.H * sp.Bt + NTH / 64 - 1) / (NTH / 64)), dim3(NTH), sp, n_final);
     return hipSuccess;
 }
 

@@ -403,6 +403,7 @@ __global__ __launch_bounds__(NTH) void mk_scan(SegParams sp) {
         if (sp.state_out16) st_state(sp.state_out16 + (int64_t)b * sp.state_out16_bs + bh, hc);
         return;
     }
+    if (sp.first_span && blockIdx.x == 0 && b == 0 && threadIdx.x == 0) sp.param_count[(int64_t)h * sp.param_stride] = 0;
     const int64_t ce = (int64_t)b * HPN + bh;
     f32x4 g = sp.dcarry_in ? ld_state(sp.dcarry_in + ce) : (f32x4)(0.f);
     constexpr int UB = 4;  // two arrays a chunk on the way back
@@ -496,13 +497,7 @@ hipError_t bwd_q(const SegParams& sp0, hipStream_t st) {
     const bool trio = Q >= 128;
     if (!trio) e = mfma_launch_dual(sp, 2, st);
     if (e != hipSuccess) return e;
-    e = mfma_launch_grad_bc(sp, st);   // ddt and the dA / dD partial sums ride in its last launch
-    if (e != hipSuccess) return e;
-    if (!sp.defer_param) {
-        e = launch_param_reduce(sp, st);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return mfma_launch_grad_bc(sp, st);  // ddt, dA and dD ride in its last launch
 }
 
 }  // namespace

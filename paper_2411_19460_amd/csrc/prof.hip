@@ -17,7 +17,7 @@ int g_only = -1;  // >= 0: record this kernel id only
 std::vector<Rec> g_recs;
 std::vector<hipEvent_t> g_pool;
 const char* const g_names[K_COUNT] = {
-    "chunk_state", "state_scan_fwd", "chunk_out", "state_scan_bwd", "bwd_main", "param_reduce", "dBC", "fill", "copy",
+    "chunk_state", "state_scan_fwd", "chunk_out", "state_scan_bwd", "bwd_main", "dBC", "fill", "copy",
     "mfma_chunk_state", "mfma_chunk_out", "mfma_dstate_local", "mfma_bwd_main", "mfma_dG", "mfma_dBC", "mfma_bwd_trio",
     "mfma_final_ddt"};
 

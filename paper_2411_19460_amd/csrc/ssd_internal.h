@@ -60,6 +60,7 @@ struct SegParams {
     const uint8_t* reset;              // optional [Bt][tokens of the segment]: non-zero = a packed sequence starts here
     int64_t reset_bs;                  // its batch stride
     uint32_t flags;
+    int accumulate;                    // bwd: 1 = add the call's dA / dD to what is there
     // inputs / outputs
     const void* x;
     const void* dt;
@@ -91,11 +92,12 @@ struct SegParams {
     float* fterm;      // [Bt][H][nc][Q]
     float* dDrow;      // [Bt][H][nc][Q]
     float* tail_part;  // [Bt][H][nc][nslice]
-    float* dA_part;    // [Bt][nc][H]
-    float* dD_part;    // [Bt][nc][H]
+    float* dA_part;    // [Bt][nc_total][H]
+    float* dD_part;    // [Bt][nc_total][H]
     float* dcarry;     // [Bt][H][P][N] adjoint of the state entering the span to the right of the current one
     const float* dcarry_in;  // where the reverse scan starts from: dcarry, the caller's dfinal_state, or NULL for zeros
     int nslice;
+    int param_stride;  // see param_count
     // extra scratch of the MFMA path
     float* ein;        // [Bt][H][nc][Q] exp(cum_i - cum at the start of i's 64-token block)
     float* eout;       // [Bt][H][nc][Q] exp(cum at the end of j's 64-token block - cum_j)
@@ -108,6 +110,7 @@ struct SegParams {
     int outer_split;     // number of head slices of the chunk-state / local-adjoint kernel
     int part_alternate;  // the head-sum pass alternates between the halves of its slice (see part_body)
     int wg_target;       // least number of workgroups a persistent-over-heads launch should have
+    int first_span;      // bwd: 1 = the first span of a call that the reverse scan walks
     float* dbc_part;     // [Bt][nc][G][part_split][2][Q][N] per-slice head terms of dC (0) and dB (1)
     // state plumbing for the scans (all fp32, element strides between batches)
     const float* state_in;   // state entering the span, or NULL for zeros
@@ -133,11 +136,13 @@ struct SegParams {
     float* dinit_out;        // bwd: where the adjoint of the entering state goes at segment 0, or NULL
     float* dA;
     float* dD;
-    int accumulate;          // bwd: 1 = add this segment's dA/dD to what is there
-    // dA / dD partial sums: slot (b, chunk0 + c, h) of an array with nc_total chunks per batch.  The
-    // defaults (chunk0 = 0, nc_total = nc) keep them per segment; defer_param = 1 leaves the final
-    // reduction over all chunks to the caller (launch_param_reduce), so segments may run concurrently.
-    int chunk0, nc_total, defer_param;
+    // dA / dD partial sums: slot (b, chunk0 + c, h) of an array with nc_total chunks per batch, by default (0 and nc) one
+    // span's; where one array serves all spans of a call, they may run concurrently.  param_count[h param_stride]: chunks of
+    // head h that have left theirs, a cache line apart where they fit so (24 heads in one line took 7 us of a launch of 15).
+    // The reverse scan of a call's first span, which every finalisation follows, sets it to zero (first_span); the chunk that
+    // makes it full sums them (ddt_finalize.h).
+    int chunk0, nc_total;
+    int* param_count;
     // optional cross-stream ordering of the state scans (consecutive segments run on different streams):
     // the scan waits for ev_wait and records ev_record when it has been enqueued
     hipEvent_t ev_wait, ev_record;
@@ -217,7 +222,7 @@ bool use_mfma(const ssd_shape_t& sh, uint32_t flags);
 
 // Kernel ids for the optional event timing (see prof.hip).
 enum KernelId {
-    K_CHUNK_STATE, K_SCAN_FWD, K_CHUNK_OUT, K_SCAN_BWD, K_BWD_MAIN, K_PARAM, K_DBC, K_FILL, K_COPY,
+    K_CHUNK_STATE, K_SCAN_FWD, K_CHUNK_OUT, K_SCAN_BWD, K_BWD_MAIN, K_DBC, K_FILL, K_COPY,
     K_MFMA_CHUNK_STATE, K_MFMA_CHUNK_OUT, K_MFMA_DSTATE, K_MFMA_BWD_MAIN, K_MFMA_DG, K_MFMA_DBC, K_MFMA_BWD_TRIO,
     K_MFMA_FINAL_DDT, K_COUNT
 };
@@ -244,8 +249,6 @@ hipError_t launch_fill_zero(float* p, size_t n, hipStream_t st);
 hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t st);
 hipError_t generic_forward_segment(const SegParams& sp, bool is_bf16, bool need_y, hipStream_t st);
 hipError_t generic_backward_segment(const SegParams& sp, bool is_bf16, hipStream_t st);
-// dA, dD = (or +=, under sp.accumulate) the sum of the partial sums of all sp.nc_total chunks.
-hipError_t launch_param_reduce(const SegParams& sp, hipStream_t st);
 
 // MFMA path (bf16, P = 64, N = 128, Q in {64, 128, 256}).
 bool mfma_path_supported(const ssd_shape_t& s);

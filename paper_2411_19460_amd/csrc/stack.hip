@@ -181,6 +181,9 @@ extern "C" int magc_stack_bwd(const ssd_shape_t* shape, int32_t nlayers, int32_t
     base_params(sp, c, SSD_FLAG_RESIDUAL);
     bind_workspace(sp, wl, wsb + w.ssd, true);
     fit_splits(sp, c, mfma, sp.wg_target);
+    sp.param_count = (int*)sp.dcarry;  // the adjoints are carried in dh: their own array is free
+    sp.param_stride = f.P * f.N < 32 ? f.P * f.N : 32;
+    sp.first_span = 1;                 // every cell of the grid sums its own chunks
 
     auto set_layer = [&](int j, int64_t k) {
         const int64_t t0 = k * f.s;
@@ -260,8 +263,7 @@ extern "C" int magc_stack_bwd(const ssd_shape_t* shape, int32_t nlayers, int32_t
                 e = mfma ? mfma_forward_segment(sp, false, st) : generic_forward_segment(sp, c.bf16, false, st);
                 if (e != hipSuccess) return SSD_ERR_LAUNCH;
                 float* dhj = dh + (int64_t)j * f.Bt * HPN;
-                sp.dcarry_in = dhj;
-                sp.dinit_out = dhj;
+                sp.dcarry_in = sp.dcarry = dhj;
                 sp.accumulate = (k == f.nseg - 1) ? 0 : 1;
                 e = mfma ? mfma_backward_segment(sp, st) : generic_backward_segment(sp, c.bf16, st);
                 if (e != hipSuccess) return SSD_ERR_LAUNCH;
