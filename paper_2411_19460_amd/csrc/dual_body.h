@@ -76,8 +76,9 @@ __device__ __forceinline__ bf16x8 frag_lds_rows(const char* tile, int pitch, int
     return *(const bf16x8*)(tile + (row0 + (lane & 31)) * pitch + (k0 + 8 * (lane >> 5)) * 2);
 }
 
+// piece 0: the state and the tokens' scalars, 1: the tile, 2 (reverse): the wave's own rows of x
 template <int Q, bool REV>
-__device__ __forceinline__ void load_pre(Pre<Q>& pr, const SegParams& sp, int b, int c, int h, int tid, int tok0) {
+__device__ __forceinline__ void load_pre(Pre<Q>& pr, const SegParams& sp, int b, int c, int h, int tid, int tok0, int piece) {
     typedef DualCfg<Q> CF;
     const int64_t xt = (int64_t)sp.H * P_;
     const int64_t cbase = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
@@ -89,25 +90,30 @@ __device__ __forceinline__ void load_pre(Pre<Q>& pr, const SegParams& sp, int b,
     constexpr int RSTEP = CF::NTHR / 8;  // rows between a thread's consecutive vectors
     const int nv = chunk_rows(sp, c, Q);
     const rsrc_t rows = make_rows(src, nv, rowbytes);
+    if (piece == 0) {
 #pragma unroll
-    for (int k = 0; k < CF::XV; ++k) {
-        pr.xt[k] = rows_load(rows, xoff + k * RSTEP * rowbytes);
-        const float* f1 = (REV ? sp.ein : sp.dtf) + cbase + k * RSTEP;
-        pr.sc[k] = *(const float*)((const char*)f1 + (size_t)roff);
-        if (!REV) pr.sc2[k] = *(const float*)((const char*)(sp.eout + cbase + k * RSTEP) + (size_t)roff);
-    }
-    const bf16_t* S = (REV ? sp.dstates_bf : sp.states_bf) + (((int64_t)b * sp.nc + c) * sp.H + h) * (P_ * N_);
-    const uint32_t soff = (uint32_t)tid * 16;
-    // the state tile has this one reader: streaming load
+        for (int k = 0; k < CF::XV; ++k) {
+            const float* f1 = (REV ? sp.ein : sp.dtf) + cbase + k * RSTEP;
+            pr.sc[k] = *(const float*)((const char*)f1 + (size_t)roff);
+            if (!REV) pr.sc2[k] = *(const float*)((const char*)(sp.eout + cbase + k * RSTEP) + (size_t)roff);
+        }
+        const bf16_t* S = (REV ? sp.dstates_bf : sp.states_bf) + (((int64_t)b * sp.nc + c) * sp.H + h) * (P_ * N_);
+        const uint32_t soff = (uint32_t)tid * 16;
+        // the state tile has this one reader: streaming load
 #pragma unroll
-    for (int k = 0; k < CF::SV; ++k) pr.sv[k] = __builtin_nontemporal_load((const bf16x8*)((const char*)S + (size_t)k * CF::NTHR * 16 + (size_t)soff));
-    if (tid < Q) {
-        pr.cum = sp.cum[cbase + tid];
-        pr.dtf = sp.dtf[cbase + tid];
-        pr.fac = REV ? sp.eout[cbase + tid] : sp.ein[cbase + tid];
+        for (int k = 0; k < CF::SV; ++k) pr.sv[k] = __builtin_nontemporal_load((const bf16x8*)((const char*)S + (size_t)k * CF::NTHR * 16 + (size_t)soff));
+        if (tid < Q) {
+            pr.cum = sp.cum[cbase + tid];
+            pr.dtf = sp.dtf[cbase + tid];
+            pr.fac = REV ? sp.eout[cbase + tid] : sp.ein[cbase + tid];
+        }
+        pr.Dh = sp.D[h];
     }
-    pr.Dh = sp.D[h];
-    if (REV) {  // lane -> (row lane / 8, 16-byte piece lane % 8) of each 8-row group of the wave's tile
+    if (piece == 1) {
+#pragma unroll
+        for (int k = 0; k < CF::XV; ++k) pr.xt[k] = rows_load(rows, xoff + k * RSTEP * rowbytes);
+    }
+    if (REV && piece == 2) {  // lane -> (row lane / 8, 16-byte piece lane % 8) of each 8-row group of the wave's tile
         const bf16_t* xg = (const bf16_t*)sp.x + (int64_t)b * sp.xs_b + ((int64_t)c * Q * sp.H + h) * P_;
         const uint32_t ooff = (uint32_t)(tok0 + ((tid >> 3) & 7)) * rowbytes + (uint32_t)(tid & 7) * 16;
         const rsrc_t xr = make_rows(xg, nv, rowbytes);
@@ -176,9 +182,9 @@ __device__ __forceinline__ void tile_load(bf16x8 (&go)[GO_MAX], bf16x8 (&gd)[4],
     for (int ks = 0; ks < RF_N; ++ks) rf[ks] = frag_tokens(rowop, bcbytes, tok0, 16 * ks, lane);
 }
 
-template <int Q, int EPI>
+template <int Q, int EPI, class Ask>
 __device__ __forceinline__ void tile_compute(const bf16x8 (&go)[GO_MAX], const bf16x8 (&gd)[4], const bf16x8 (&rf)[RF_N],
-                                             DualLds<Q>& L, const HeadCtx& cx, int T, int lane, int w) {
+                                             DualLds<Q>& L, const HeadCtx& cx, int T, int lane, int w, Ask ask) {
     constexpr bool REV = EPI == 2;
     constexpr int NB = Q / BLK;
     const int I = T >> 1, odd = T & 1, tok0 = 32 * T;
@@ -206,6 +212,7 @@ __device__ __forceinline__ void tile_compute(const bf16x8 (&go)[GO_MAX], const b
             a1 = n1;
         }
     }
+    ask(1);
     // off-diagonal 64-token blocks, Horner in the block decays (forward: K = 0 .. I-1; reverse: K = NB-1 .. I+1)
 #pragma unroll
     for (int n = 0; n < NB - 1; ++n) {
@@ -239,6 +246,7 @@ __device__ __forceinline__ void tile_compute(const bf16x8 (&go)[GO_MAX], const b
         acc0[r] *= lane_fac;
         acc1[r] *= lane_fac;
     }
+    if (REV) ask(2);
     // diagonal block: the mask and the decay (and, forward, dt_j) are evaluated per element.  Forward,
     // an even tile stops after its own 32 tokens; reverse, an odd tile starts at its own.  The operand
     // reads of a step are issued before the arithmetic that builds its masked scores.
@@ -348,7 +356,8 @@ __device__ __forceinline__ void dual_body(const SegParams& sp, DualLds<Q>& L, in
     HeadCtx cx;
     tile_load<Q, REV>(go, gd, rf, Mat, make_rows(rowop, chunk_rows(sp, c, Q), (uint32_t)bt * 2), (uint32_t)bt * 2, T, lane);
     Pre<Q> pr;
-    load_pre<Q, REV>(pr, sp, b, c, h0, tid, 32 * T);
+#pragma unroll
+    for (int piece = 0; piece < 3; ++piece) load_pre<Q, REV>(pr, sp, b, c, h0, tid, 32 * T, piece);
     for (int hh = 0; hh < hps; ++hh) {
         const int h = h0 + hh;
         // the thread index as the optimiser cannot see through: addresses derived from it are formed anew
@@ -363,7 +372,13 @@ __device__ __forceinline__ void dual_body(const SegParams& sp, DualLds<Q>& L, in
         SSDK_STAMP(EPI == 2 ? 0 : 3, 2);
         __syncthreads();
         SSDK_STAMP(EPI == 2 ? 0 : 3, 3);
-        if (hh + 1 < hps) load_pre<Q, REV>(pr, sp, b, c, h + 1, tv, 32 * T);
+        // the next head is asked for in pieces between the products: at once, the loads of all waves stood in line for up to
+        // 2000 cycles of a head's 10000
+        auto ask = [&](int piece) {
+            if (hh + 1 < hps) load_pre<Q, REV>(pr, sp, b, c, h + 1, tv, 32 * T, piece);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        ask(0);
         SSDK_STAMP(EPI == 2 ? 0 : 3, 4);
         const int64_t cbase = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
         const int64_t xrow = ((int64_t)c * Q * sp.H + h) * P_;
@@ -372,7 +387,7 @@ __device__ __forceinline__ void dual_body(const SegParams& sp, DualLds<Q>& L, in
         cx.fterm = sp.fterm + cbase;
         cx.dDrow = sp.dDrow + cbase;
         cx.xt = xt;
-        tile_compute<Q, EPI>(go, gd, rf, L, cx, T, lane, w);
+        tile_compute<Q, EPI>(go, gd, rf, L, cx, T, lane, w, ask);
         SSDK_STAMP(EPI == 2 ? 0 : 3, 5);
     }
 }
