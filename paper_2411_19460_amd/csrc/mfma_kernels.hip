@@ -187,13 +187,16 @@ __device__ __forceinline__ void cb_body(const SegParams& sp, int z, int pair, in
 // of this launch.  As a launch in front of this one, which read the weights from memory, against now (us, two launches -> one):
 // 10007 tokens of 80 heads 11.9 + 35.2 -> 37.8; 8192 of 24 8.8 + 13.1 -> 16.3, both roles 8.8 + 19.7 -> 23.2; 65536 tokens of
 // 80 heads forward + backward, four segments in flight, 3110 -> 3048.
-constexpr int OUTER_THR = 512, PREP_HEADS = OUTER_THR / 64;
+constexpr int OUTER_THR = 512, PREP_HEADS = OUTER_THR / 64, OUT_PITCH = 64 + 16;
 
 template <int Q>
 struct OuterLds {
     union {
-        char bc[Q * BPITCH];  // B or C rows of the chunk (prologue only: each wave takes its fragments, then the space is xt)
-        char xt[Q * XPITCH];  // weight * x or weight * dY
+        char bc[Q * BPITCH];  // B or C rows of the chunk (prologue only: each wave takes its fragments, then the space is free)
+        struct {
+            char xt[Q * XPITCH];                          // weight * x or weight * dY
+            char out[OUTER_THR / 64][32 * OUT_PITCH];     // a wave's 32 x 32 tile on its way to whole rows (bf16)
+        };
     };
     float wt[PREP_HEADS][Q];  // weights of eight heads
 };
@@ -297,18 +300,33 @@ __global__ __launch_bounds__(OUTER_THR, 4) void mk_chunk_outer(SegParams sp, int
         SSDK_STAMP(4, 4);
         f32x16 acc = zero16();
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) acc = mfma(frag_tr(L.xt, XPITCH, 16 * ks, 32 * ph, lane), fb[ks], acc);
-        const int64_t so = (((int64_t)b * sp.nc + c) * sp.H + h) * (P_ * N_);
+        for (int ks = 0; ks < KS; ++ks) acc = mfma(fb[ks], frag_tr(L.xt, XPITCH, 16 * ks, 32 * ph, lane), acc);
+        // a lane holds four times four neighbours of a row
+        const int64_t so = (((int64_t)b * sp.nc + c) * sp.H + h) * (P_ * N_) + 32 * ph * N_ + 32 * nt;
         const int ls = opaque(lane);
         if (F32OUT) {  // fp32 scan input, in an array of its own
             float* out = (role == 0 ? sp.states : sp.dstates) + so;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) out[(32 * ph + acc_row(r, ls)) * N_ + 32 * nt + (ls & 31)] = acc[r];
+            for (int q = 0; q < 4; ++q)
+                *(f32x4*)(out + (ls & 31) * N_ + 8 * q + 4 * (ls >> 5)) = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
         } else {
-            // bf16, into the slot where the scan will put the state entering the chunk (total adjoint leaving it)
+            // bf16, into the slot where the scan will put the state entering the chunk (total adjoint leaving it); through
+            // LDS, two stores of 16 bytes a lane instead of sixteen of two bytes
             __bf16* out = (__bf16*)(role == 0 ? sp.states_bf : sp.dstates_bf) + so;
+            char* patch = L.out[w];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) out[(32 * ph + acc_row(r, ls)) * N_ + 32 * nt + (ls & 31)] = (__bf16)acc[r];
+            for (int q = 0; q < 4; ++q) {
+                bf16x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = (__bf16)acc[4 * q + e];
+                *(bf16x4*)(patch + (ls & 31) * OUT_PITCH + (8 * q + 4 * (ls >> 5)) * 2) = v;
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                const int row = 16 * it + (ls >> 2), seg = ls & 3;
+                *(bf16x8*)(out + row * N_ + 8 * seg) = *(const bf16x8*)(patch + row * OUT_PITCH + 16 * seg);
+            }
         }
         if (hh % PREP_HEADS == PREP_HEADS - 1) weights(hh + 1);  // of the next eight heads: the last of these is staged
         SSDK_STAMP(4, 5);
@@ -321,7 +339,6 @@ __global__ __launch_bounds__(OUTER_THR, 4) void mk_chunk_outer(SegParams sp, int
 // contraction kernels read, nothing else.  Bound by the trips of the chunk states through memory: the recurrence is serial,
 // so the loads of a block of chunks are under way while the block before it is worked on.  (Two elements per thread, twice
 // the waves: no faster at 24 heads, 10 % slower at 64.)
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x4 ld_state(const float* p) { return *(const f32x4*)p; }
 __device__ __forceinline__ f32x4 ld_state(const bf16_t* p) { return __builtin_convertvector(*(const bf16x4*)p, f32x4); }
 __device__ __forceinline__ void st_state(float* p, f32x4 v) { *(f32x4*)p = v; }
