@@ -476,7 +476,7 @@ template <typename T>
 __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp, Vec vec) {
     const int Q = sp.Q, N = sp.N, P = sp.P;
     Tiles& L = *(Tiles*)dyn_lds;
-    float *cum = (float*)(dyn_lds + sizeof(Tiles)), *dtf = cum + Q;
+    float *cum = (float*)(dyn_lds + sizeof(Tiles)), *dtf = cum + Q, *rowf = dtf + Q, *srow = rowf + TM;
     const int p0 = blockIdx.y * TM, i0 = ((int)gridDim.z - 1 - (int)blockIdx.z) * TM;  // the longest rows first
     const int z = blockIdx.x, h = z % sp.H, c = (z / sp.H) % sp.nc, b = z / (sp.H * sp.nc), g = h / sp.hpg, V = chunk_rows(sp, c, Q);
     if (i0 >= V) return;
@@ -495,7 +495,9 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp, Vec vec
     auto lb = [&](float (&v)[4], int r, int k, int k0) { ld_r4<T>(v, sp.x, xbase + p0, xt, r, k0, k, P - p0, V); };
     // Tokens before the tile: exp(cum_i - cum_k) = exp(cum_i - cum_ref) exp(cum_ref - cum_k) with the token in front of
     // the tile as reference, both <= 1: one exp per token instead of one per score; the first factor scales the rows at
-    // the end.  Only the diagonal tile takes an exp per score.
+    // the end.  Only the diagonal tile takes an exp per score.  The entering state's weight exp(cum_i) too is applied to the
+    // rows of its product.  (Weights in the operands of that product and the rows' exps in every lane: 600 instructions a
+    // wave more, 4096 tokens of 24 heads 36.6 us, now 32.)
     const float ref = i0 > 0 ? sp.cum[cbase + i0 - 1] : 0.f;
     tile_gemm<true, false>(
         acc, 0, i0, la,
@@ -508,15 +510,16 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp, Vec vec
                 const float c_ = sp.cum[cbase + i], d_ = sp.dtf[cbase + i];
                 cum[i] = c_;
                 dtf[i] = i < i0 ? decay(ref - c_) * d_ : d_;
+                if (i >= i0) {
+                    rowf[i - i0] = decay(c_ - ref);
+                    srow[i - i0] = expf(c_);
+                }
             }
             __syncthreads();
         });
     if (i0 > 0)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int i = i0 + tile_row(r);
-            acc[r] *= decay(cum[i < V ? i : i0] - ref);
-        }
+        for (int r = 0; r < 16; ++r) acc[r] *= i0 + tile_row(r) < V ? rowf[tile_row(r)] : 0.f;
     tile_gemm<true, false>(
         acc, i0, kend, la,
         [&](float (&v)[4], int r, int k) {
@@ -525,14 +528,12 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp, Vec vec
             for (int e = 0; e < 4; ++e) v[e] = (i < V && k + e <= i) ? v[e] * expf(cum[i] - cum[k + e]) * dtf[k + e] : 0.f;
         },
         lb, NoWeight{}, L, buf);
+    f32x16 t = zero_acc();
     tile_gemm<true, true>(
-        acc, 0, N, [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, sp.Cm, bbase, bt, i0, r, k0, k, V, N, vec.bc); },
-        [&](float (&v)[4], int r, int) {
-            const float w = i0 + r < V ? expf(cum[i0 + r]) : 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] *= w;
-        },
+        t, 0, N, [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, sp.Cm, bbase, bt, i0, r, k0, k, V, N, vec.bc); }, NoWeight{},
         [&](float (&v)[4], int r, int k, int k0) { ld_k4<float>(v, Hprev, (int64_t)p0 * N, N, 0, r, k0, k, P - p0, N, (N & 3) == 0); }, NoWeight{}, L, buf);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = fmaf(t[r], i0 + tile_row(r) < V ? srow[tile_row(r)] : 0.f, acc[r]);
     const float Dh = sp.D[h] + ((sp.flags & SSD_FLAG_RESIDUAL) ? 1.f : 0.f);
     const int p = p0 + tile_col();
 #pragma unroll
@@ -551,7 +552,7 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp, Vec vec
 struct WalkLds {
     Tiles t;
     union {
-        float ch[1];  // walk_u: cum [Q], dt [Q]
+        float ch[1];  // walk_u: cum [Q], dt [Q], the rows' factors [2][TM]
         struct { float row[2][TM], col[2][TM], dcol[2][TM]; } hd;
     };
 };
@@ -568,7 +569,7 @@ __device__ __forceinline__ void walk_u(const SegParams& sp, const Vec& vec, Walk
     const int h = z % sp.H, c = (z / sp.H) % sp.nc, b = z / (sp.H * sp.nc), g = h / sp.hpg, V = chunk_rows(sp, c, Q);
     if (j0 >= V) return;
     const int64_t cbase = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
-    float *cum = L.ch, *dtf = L.ch + Q;
+    float *cum = L.ch, *dtf = L.ch + Q, *rowf = dtf + Q, *srow = rowf + TM;
     const float T_ = sp.cum[cbase + Q - 1];
     const float* Gm = sp.Gm + (((int64_t)b * sp.nc + c) * sp.G + g) * Q * Q;
     const float* dHnext = sp.dstates + (((int64_t)b * sp.nc + c) * sp.H + h) * P * N;
@@ -596,12 +597,16 @@ __device__ __forceinline__ void walk_u(const SegParams& sp, const Vec& vec, Walk
                 const float c_ = sp.cum[cbase + i];
                 cum[i] = i < j1 ? c_ : decay(c_ - ref);
                 dtf[i] = sp.dtf[cbase + i];
+                if (i >= j0 && i < j1) {
+                    rowf[i - j0] = decay(ref - c_);
+                    srow[i - j0] = expf(T_ - c_);
+                }
             }
             __syncthreads();
         });
     if (j1 < V)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] *= decay(ref - cum[j0 + tile_row(r)]);
+        for (int r = 0; r < 16; ++r) acc[r] *= rowf[tile_row(r)];
     tile_gemm<false, false>(
         acc, j0, j1, la,
         [&](float (&v)[4], int r, int k) {
@@ -610,14 +615,12 @@ __device__ __forceinline__ void walk_u(const SegParams& sp, const Vec& vec, Walk
             for (int e = 0; e < 4; ++e) v[e] = (j < V && k + e < V && k + e >= j) ? v[e] * expf(cum[k + e] - cum[j]) : 0.f;
         },
         lb, NoWeight{}, L.t, buf);
+    f32x16 t = zero_acc();
     tile_gemm<true, true>(
-        acc, 0, N, [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, sp.Bm, bbase, bt, j0, r, k0, k, V, N, vec.bc); },
-        [&](float (&v)[4], int r, int) {
-            const float w = j0 + r < V ? expf(T_ - cum[j0 + r]) : 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] *= w;
-        },
+        t, 0, N, [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, sp.Bm, bbase, bt, j0, r, k0, k, V, N, vec.bc); }, NoWeight{},
         [&](float (&v)[4], int r, int k, int k0) { ld_k4<float>(v, dHnext, (int64_t)p0 * N, N, 0, r, k0, k, P - p0, N, (N & 3) == 0); }, NoWeight{}, L.t, buf);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = fmaf(t[r], j0 + tile_row(r) < V ? srow[tile_row(r)] : 0.f, acc[r]);
     const int p = p0 + tile_col();
     f32x16 dyx;
 #pragma unroll
@@ -742,70 +745,72 @@ __device__ __forceinline__ void walk_part(const SegParams& sp, const Vec& vec, W
     if (r0 >= V) return;
     const int hps = sp.hpg / ns, h0 = g * sp.hpg + slice * hps, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int64_t xt = (int64_t)sp.H * P;
-    const int n = n0 + tile_col();
+    // The products come out with a lane per token and the columns n along the registers: a token's weight is one factor
+    // after the product, and its dot product stays inside the lane.
+    const int i = r0 + tile_col(), il = i < V ? i : V - 1;
     float cf[16];  // C_i[n] (role 1: B_j[n])
     {
-        const int64_t bbase = (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N;
-        const int64_t bt = (int64_t)sp.G * N;
+        const int64_t o = (int64_t)b * sp.bcs_b + (((int64_t)c * Q + il) * sp.G + g) * N;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int i = r0 + tile_row(r);
-            cf[r] = (i < V && n < N) ? IO<T>::ld(role ? sp.Bm : sp.Cm, bbase + (int64_t)i * bt + n) : 0.f;
+            const int n = n0 + tile_row(r);
+            cf[r] = n < N ? IO<T>::ld(role ? sp.Bm : sp.Cm, o + n) : 0.f;
         }
     }
     const int KS = (P + TK - 1) / TK;
-    float ra[2][4], rb[2][4], rw[2], rd[2], rT = 0.f;
-    auto load = [&](int s) {
+    float ra[2][4], rb[2][4], rc = 0.f, rd = 0.f, rT = 0.f;
+    auto load = [&](int s) {  // with the first step of a head, its cum and dt
         const int h = h0 + s / KS, k0 = (s % KS) * TK;
         const int64_t xbase = (int64_t)b * (role ? sp.xs_b : sp.dys_b) + ((int64_t)c * Q * sp.H + h) * P;
         const float* S = role ? sp.dstates + (((int64_t)b * sp.nc + c) * sp.H + h) * P * N : sp.states + (((int64_t)b * (sp.nc + 1) + c) * sp.H + h) * P * N;
         tile_load<true>(ra, k0, [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, role ? sp.x : sp.dy, xbase, xt, r0, r, k0, k, V, P, vec.x); });
         tile_load<false>(rb, k0, [&](float (&v)[4], int r, int k, int k0) { ld_r4<float>(v, S, n0, N, r, k0, k, N - n0, P); });
-        const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            int row, k;
-            place<true>(tid, q, row, k);
-            const int i = r0 + row < V ? r0 + row : V - 1;
-            rw[q] = sp.cum[o + i];
-            rd[q] = sp.dtf[o + i];
+        if (k0 == 0) {
+            const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
+            rc = sp.cum[o + il];
+            rd = sp.dtf[o + il];
+            rT = sp.cum[o + Q - 1];
         }
-        rT = sp.cum[o + Q - 1];
     };
     f32x16 tot = zero_acc(), d = zero_acc();
+    float wgt = 0.f;
     load(0);
     for (int s = 0; s < hps * KS; ++s) {
         const int hh = s / KS, ks = s % KS, buf = s & 1;
-        const float wq[2] = {role ? decay(rT - rw[0]) * rd[0] : expf(rw[0]), role ? decay(rT - rw[1]) * rd[1] : expf(rw[1])};
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) ra[q][e] *= wq[q];
+        if (ks == 0) wgt = role ? decay(rT - rc) * rd : expf(rc);
         tile_store<true>(ra, L.t.a[buf], 0, NoWeight{});
         tile_store<false>(rb, L.t.b[buf], 0, NoWeight{});
         __syncthreads();
         if (s + 1 < hps * KS) load(s + 1);
-        tile_mma(d, L.t.a[buf], L.t.b[buf]);
+        tile_mma(d, L.t.b[buf], L.t.a[buf]);
         if (ks == KS - 1) {
+            float d0 = 0.f, d1 = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                tot[r] += d[r];
-                d[r] *= cf[r];
+            for (int r = 0; r < 16; r += 2) {
+                tot[r] = fmaf(d[r], wgt, tot[r]);
+                tot[r + 1] = fmaf(d[r + 1], wgt, tot[r + 1]);
+                d0 = fmaf(d[r], cf[r], d0);
+                d1 = fmaf(d[r + 1], cf[r + 1], d1);
             }
-            const float rs = row_sums(d, lane);
-            if ((lane & 1) == 0) {
-                const int i = r0 + tile_row((lane & 31) >> 1);
-                if (i < V)
-                    (role ? sp.sterm : sp.gterm)[(2 * (n0 / TM) + (w & 1)) * sp.tok_stride + (((int64_t)b * sp.H + h0 + hh) * sp.nc + c) * Q + i] = rs;
-            }
+            d0 += d1;
+            d0 += __shfl_xor(d0, 32, 64);
+            if (lane < 32 && i < V)
+                (role ? sp.sterm : sp.gterm)[(2 * (n0 / TM) + (w >> 1)) * sp.tok_stride + (((int64_t)b * sp.H + h0 + hh) * sp.nc + c) * Q + i] = d0 * wgt;
             d = zero_acc();
         }
     }
-    float* out = sp.dbc_part + (((((int64_t)b * sp.nc + c) * sp.G + g) * ns + slice) * 2 + role) * ((int64_t)Q * N);
+    if (i >= V) return;
+    float* out = sp.dbc_part + (((((int64_t)b * sp.nc + c) * sp.G + g) * ns + slice) * 2 + role) * ((int64_t)Q * N) + (int64_t)i * N;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int i = r0 + tile_row(r);
-        if (i < V && n < N) out[(int64_t)i * N + n] = tot[r];
+    for (int q = 0; q < 4; ++q) {
+        const int n = n0 + tile_row(4 * q);
+        if ((N & 3) == 0) {
+            if (n < N) *(float4*)(out + n) = make_float4(tot[4 * q], tot[4 * q + 1], tot[4 * q + 2], tot[4 * q + 3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (n + e < N) out[n + e] = tot[4 * q + e];
+        }
     }
 }
 
@@ -980,7 +985,7 @@ hipError_t fwd_segment(const SegParams& sp, bool need_y, hipStream_t st) {
     const hipError_t e = scores_states<T>(sp, 1, st);
     if (e != hipSuccess) return e;
     SSDK_LAUNCH(K_SCAN_FWD, st, k_state_scan<false>, dim3(cdiv(sp.P * sp.N, NTHREADS), sp.H, sp.Bt), dim3(NTHREADS), sp);
-    SSDK_LAUNCH_LDS(K_CHUNK_OUT, st, k_chunk_out<T>, dim3(sp.Bt * sp.nc * sp.H, cdiv(sp.P, TM), cdiv(sp.Q, TM)), dim3(NTHREADS), lds_bytes(2 * sp.Q), sp, vec_of<T>(sp));
+    SSDK_LAUNCH_LDS(K_CHUNK_OUT, st, k_chunk_out<T>, dim3(sp.Bt * sp.nc * sp.H, cdiv(sp.P, TM), cdiv(sp.Q, TM)), dim3(NTHREADS), lds_bytes(2 * sp.Q + 2 * TM), sp, vec_of<T>(sp));
     return hipSuccess;
 }
 
@@ -993,7 +998,7 @@ hipError_t bwd_segment(const SegParams& sp0, hipStream_t st) {
     if (e != hipSuccess) return e;
     SSDK_LAUNCH(K_SCAN_BWD, st, k_state_scan<true>, dim3(cdiv(sp.P * sp.N, NTHREADS), sp.H, sp.Bt), dim3(NTHREADS), sp);
     const int n_part = bcg * sp.part_split * 2 * NN * NT, n_dg = bcg * sp.dg_split * (NT * (NT + 1) / 2), n_u = sp.Bt * sp.nc * sp.H * NT * cdiv(sp.P, TM);
-    const int per_token = 2 * sp.Q > 6 * TM ? 2 * sp.Q : 6 * TM;
+    const int per_token = 2 * sp.Q + 2 * TM > 6 * TM ? 2 * sp.Q + 2 * TM : 6 * TM;
     SSDK_LAUNCH_LDS(K_BWD_MAIN, st, k_bwd_walk<T>, dim3(n_part + n_dg + n_u), dim3(NTHREADS), lds_bytes(per_token), sp, vec_of<T>(sp), n_part, n_dg);
     const int n_dbc = bcg * 2 * NN * NT;
     SSDK_LAUNCH(K_DBC, st, k_bwd_final<T>, dim3(n_dbc + sp.Bt * sp.nc * sp.H), dim3(NTHREADS), sp, vec_of<T>(sp), n_dbc);
