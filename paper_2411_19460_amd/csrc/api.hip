@@ -143,7 +143,7 @@ void fit_splits(SegParams& sp, const Dims& d, bool mfma, int wg_target) {
     if (!mfma || d.Q < 128 || wg_target < 256 || nc <= 0) return;
     // hundreds of cycles of a workgroup around its heads and for each of them: dx, dG, head sums
     struct Cost { int64_t around[3], head[3]; };
-    const Cost c = d.Q == 256 ? Cost{{80, 110, 130}, {93, 106, 43}} : Cost{{60, 80, 90}, {110, 80, 45}};
+    const Cost c = d.Q == 256 ? Cost{{80, 110, 130}, {93, 106, 47}} : Cost{{60, 80, 90}, {110, 80, 50}};
     const int64_t base = d.Bt * nc * d.G, units = d.Q == 256 ? 256 : 512, places = dg_places(d, mfma, wg_target);
     auto one = [&](int pass, int64_t slices) { return c.around[pass] + c.head[pass] * ((d.hpg + slices - 1) / slices); };
     auto longest = [&](int64_t a, int64_t p) {

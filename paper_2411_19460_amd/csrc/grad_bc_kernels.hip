@@ -395,14 +395,10 @@ __global__ __launch_bounds__(64 * DgMap<Q>::NWV) void mk_dG(SegParams sp) {
 //   role 0:  part[i][n] = sum_h exp(cum_h,i) (dY_h,i . Hprev_h[:, n])
 //   role 1:  part[j][n] = sum_h exp(T_h - cum_h,j) dt_h,j (x_h,j . dHnext_h[:, n])
 // and, per head, the two per-token dot products through the chunk-boundary states that enter the
-// gradient of cum, which are the products of the sums above along n against C_i (role 0) or B_j (role 1):
+// gradient of cum (same staged operands, contracted the other way round):
 //   role 0:  gterm_i = exp(cum_i)          dY_i . (Hprev  C_i)
 //   role 1:  sterm_j = exp(T - cum_j) dt_j x_j  . (dHnext B_j)
-// Wave w owns RT row tiles (row group w / 2) and one half of the state columns (w % 2).  The products come out with a
-// lane per token, so that its weight is one factor in fp32 (the operands are staged as they are) and a dot product stays
-// inside the lane.  A second product of the state with C or B for them, and weights rounded into the operands, took the
-// matrix cores and the LDS twice the work: 4700 cycles a head, now 4300, of them 1000 on the matrix cores and 1900 on
-// the vector ALUs.
+// Wave w owns RT row tiles (row group w / 2) and one half of the state columns (w % 2).
 template <int Q>
 struct PartCfg {
     static constexpr int RT = Q >= 128 ? 2 : 1;       // 32-row tiles per wave
@@ -414,10 +410,8 @@ struct PartCfg {
 
 template <int Q>
 struct PartBuf {
-    char tile[Q * XPITCH];  // dY or x, token-major
+    char tile[Q * XPITCH];  // weight * dY or weight * x, token-major
     char st[P_ * BPITCH];   // Hprev or dHnext, [p][n] bf16
-    float wgt[Q];           // the tokens' weights: exp(cum) or exp(T - cum) dt
-    float dot[2][Q];        // a token's dot product, halves of the state columns
 };
 // Two buffers: a head is contracted out of one while the next head is staged into the other (one barrier per head).
 template <int Q>
@@ -428,33 +422,30 @@ struct PartLds {
 template <int Q>
 struct PartPre {
     bf16x8 t[PartCfg<Q>::TV];
-    float cum, dt, T;  // of the thread's token; cum at the end of the chunk
+    float cv[PartCfg<Q>::TV], dv[PartCfg<Q>::TV];  // cum and dt of the vector's token
+    float T;                                       // cum at the end of the chunk
     bf16x8 sv[PartCfg<Q>::SV];
 };
 
 template <int Q>
-__device__ __forceinline__ void part_load_tile(PartPre<Q>& pr, const SegParams& sp, int role, int b, int c, int h, int tid) {
+__device__ __forceinline__ void part_load(PartPre<Q>& pr, const SegParams& sp, int role, int b, int c, int h, int tid) {
     typedef PartCfg<Q> CF;
     const int64_t xt = (int64_t)sp.H * P_;
     const int64_t xrow = ((int64_t)c * Q * sp.H + h) * P_;
     const bf16_t* src = role == 0 ? (const bf16_t*)sp.dy + (int64_t)b * sp.dys_b + xrow
                                   : (const bf16_t*)sp.x + (int64_t)b * sp.xs_b + xrow;
-    // addresses = a wave-uniform base (scalar registers) + one 32-bit byte offset per lane
-    const uint32_t rowbytes = (uint32_t)xt * 2, off = (uint32_t)(tid >> 3) * rowbytes + (uint32_t)(tid & 7) * 16;
-    const rsrc_t rows = make_rows(src, chunk_rows(sp, c, Q), rowbytes);
-#pragma unroll
-    for (int k = 0; k < CF::TV; ++k) pr.t[k] = rows_load(rows, off + k * (CF::NTHR / 8) * rowbytes);
-}
-
-template <int Q>
-__device__ __forceinline__ void part_load_rest(PartPre<Q>& pr, const SegParams& sp, int role, int b, int c, int h, int tid) {
-    typedef PartCfg<Q> CF;
     const int64_t cbase = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
     // loads only: no arithmetic on the loaded values here, so that nothing waits for them early
     pr.T = sp.cum[cbase + Q - 1];
-    if (tid < Q) {
-        pr.cum = sp.cum[cbase + tid];
-        pr.dt = sp.dtf[cbase + tid];
+    // addresses = a wave-uniform base (scalar registers) + one 32-bit byte offset per lane
+    const uint32_t rowbytes = (uint32_t)xt * 2, off = (uint32_t)(tid >> 3) * rowbytes + (uint32_t)(tid & 7) * 16;
+    const uint32_t roff = (uint32_t)(tid >> 3) * 4;
+    const rsrc_t rows = make_rows(src, chunk_rows(sp, c, Q), rowbytes);
+#pragma unroll
+    for (int k = 0; k < CF::TV; ++k) {
+        pr.t[k] = rows_load(rows, off + k * (CF::NTHR / 8) * rowbytes);
+        pr.cv[k] = *(const float*)((const char*)(sp.cum + cbase + k * (CF::NTHR / 8)) + (size_t)roff);
+        pr.dv[k] = *(const float*)((const char*)(sp.dtf + cbase + k * (CF::NTHR / 8)) + (size_t)roff);
     }
     const bf16_t* S = (role == 0 ? sp.states_bf : sp.dstates_bf) + (((int64_t)b * sp.nc + c) * sp.H + h) * (P_ * N_);
     const uint32_t soff = (uint32_t)tid * 16;
@@ -469,9 +460,9 @@ __device__ __forceinline__ void part_store(const PartPre<Q>& pr, PartBuf<Q>& L, 
 #pragma unroll
     for (int k = 0; k < CF::TV; ++k) {
         const int v = tid + CF::NTHR * k, row = v >> 3, seg = v & 7;
-        *(bf16x8*)(L.tile + row * XPITCH + seg * 16) = pr.t[k];
+        const float wgt = role == 0 ? __expf(pr.cv[k]) : __expf(pr.T - pr.cv[k]) * pr.dv[k];
+        *(bf16x8*)(L.tile + row * XPITCH + seg * 16) = scale8(pr.t[k], wgt);
     }
-    if (tid < Q) L.wgt[tid] = role == 0 ? __expf(pr.cum) : __expf(pr.T - pr.cum) * pr.dt;
 #pragma unroll
     for (int k = 0; k < CF::SV; ++k) {
         const int v = tid + CF::NTHR * k, row = v >> 4, seg = v & 15;
@@ -496,20 +487,16 @@ __device__ __forceinline__ void part_body(const SegParams& sp, PartLds<Q>& LL, i
     f32x16 acc[RT][2];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) acc[rt][0] = acc[rt][1] = zero16();
-    // the rows of C (role 0) or B (role 1) of the wave's tokens and columns, as its accumulators lie
-    u32x2 rowop[RT][2][4];
-    {
-        const uint32_t bt = (uint32_t)sp.G * N_ * 2;
-        const bf16_t* op = (role ? (const bf16_t*)sp.Bm : (const bf16_t*)sp.Cm) + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
-        const rsrc_t rows = make_rows(op, chunk_rows(sp, c, Q), bt);
+    // wave w < Q/32 also owns token tile w of the per-token dot product through the state:
+    // its rows of C (role 0) or B (role 1) stay in registers
+    const bool has_dots = w < Q / 32;
+    bf16x8 rf[N_ / 16];
+    if (has_dots) {
+        const int64_t bt = (int64_t)sp.G * N_;
+        const bf16_t* rowop = (role ? (const bf16_t*)sp.Bm : (const bf16_t*)sp.Cm) + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
+        const rsrc_t rows = make_rows(rowop, chunk_rows(sp, c, Q), (uint32_t)bt * 2);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    rowop[rt][nt][q] = __builtin_amdgcn_raw_buffer_load_b64(
-                        rows, (uint32_t)(32 * (rg * RT + rt) + (lane & 31)) * bt + (uint32_t)(64 * nh + 32 * nt + 8 * q + 4 * (lane >> 5)) * 2, 0, 0);
+        for (int ks = 0; ks < N_ / 16; ++ks) rf[ks] = frag_tokens(rows, (uint32_t)bt * 2, 32 * w, 16 * ks, lane);
     }
     // Order of the heads.  When this pass runs beside the other two head-walking passes with half as many slices
     // (twice the heads per workgroup, at about twice their pace per head), it alternates between the two half
@@ -518,80 +505,97 @@ __device__ __forceinline__ void part_body(const SegParams& sp, PartLds<Q>& LL, i
     const bool alt = sp.part_alternate && (hps & 1) == 0;
     auto head_at = [&](int i) { return h0 + (alt ? (i >> 1) + (i & 1) * (hps >> 1) : i); };
     PartPre<Q> pr;
-    auto emit = [&](int hh) {
-        const PartBuf<Q>& L = LL.b[hh & 1];
-        if (tid < Q) (role ? sp.sterm : sp.gterm)[(((int64_t)b * sp.H + head_at(hh)) * sp.nc + c) * Q + tid] = L.dot[0][tid] + L.dot[1][tid];
-    };
-    part_load_tile<Q>(pr, sp, role, b, c, head_at(0), tid);
-    part_load_rest<Q>(pr, sp, role, b, c, head_at(0), tid);
+    part_load<Q>(pr, sp, role, b, c, head_at(0), tid);
     part_store<Q>(pr, LL.b[0], role, tid);
-    if (hps > 1) {
-        part_load_tile<Q>(pr, sp, role, b, c, head_at(1), tid);
-        part_load_rest<Q>(pr, sp, role, b, c, head_at(1), tid);
-    }
+    if (hps > 1) part_load<Q>(pr, sp, role, b, c, head_at(1), tid);
     __syncthreads();
-    // one of the two waves of a SIMD goes first, so that its products run beside the other's arithmetic (0.3 % of 64k tokens)
-    if (w < CF::NWV / 2) __builtin_amdgcn_s_setprio(1);
+    // The two waves of a SIMD (w and w + NWV / 2) take the phases of a head in different orders -- the later one stages the
+    // next head (vector ALU work) first, the other last -- so that one is on the vector ALUs while the other feeds the
+    // matrix core.  The next head goes into the other LDS buffer, which nobody reads during this iteration.
+    const bool stage_first = w >= CF::NWV / 2;
     for (int hh = 0; hh < hps; ++hh) {
         SSDK_STAMP(2, 0);
         const PartBuf<Q>& L = LL.b[hh & 1];
-        // the next head goes into the other buffer, which nobody reads during this iteration
-        if (hh + 1 < hps) part_store<Q>(pr, LL.b[(hh + 1) & 1], role, tid);
-        SSDK_STAMP(2, 1);
-        // the tokens' dot products of the head before, now that both halves are there
-        if (hh > 0) emit(hh - 1);
-        bf16x8 fs[2][4];
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) fs[nt][ks] = frag_tr(L.st, BPITCH, 16 * ks, 64 * nh + 32 * nt, lane);
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const int tok = 32 * (rg * RT + rt) + (lane & 31);
-            // the head after the next is asked for in two pieces between the products: at once, the loads of all waves stood
-            // in line for 1000 cycles of an iteration's 4700
-            if (hh + 2 < hps) {
-                if (rt == 0) part_load_rest<Q>(pr, sp, role, b, c, head_at(hh + 2), tid);
-                if (rt == RT - 1) part_load_tile<Q>(pr, sp, role, b, c, head_at(hh + 2), tid);
-            }
-            bf16x8 fa[4];
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) fa[ks] = lds_rows(L.tile, XPITCH, 32 * (rg * RT + rt), 16 * ks, lane);
-            const float wgt = L.wgt[tok];
-            float d0 = 0.f, d1 = 0.f;
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                f32x16 t = zero16();
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) t = mfma(fs[nt][ks], fa[ks], t);
-#pragma unroll
-                for (int r = 0; r < 16; r += 2) {
-                    acc[rt][nt][r] = fmaf(t[r], wgt, acc[rt][nt][r]);
-                    acc[rt][nt][r + 1] = fmaf(t[r + 1], wgt, acc[rt][nt][r + 1]);
-                    uint32_t o2 = rowop[rt][nt][r >> 2][(r >> 1) & 1];
-                    asm volatile("" : "+v"(o2));  // unpacked here: 64 registers more outside the loop do not fit
-                    d0 = fmaf(t[r], __builtin_bit_cast(float, o2 << 16), d0);
-                    d1 = fmaf(t[r + 1], __builtin_bit_cast(float, o2 & 0xffff0000u), d1);
-                }
-            }
-            d0 += d1;
-            d0 += __shfl_xor(d0, 32, 64);
-            LL.b[hh & 1].dot[nh][tok] = d0 * wgt;  // both halves of the wave hold the sum
+        if (stage_first) {
+            if (hh + 1 < hps) part_store<Q>(pr, LL.b[(hh + 1) & 1], role, tid);
+            if (hh + 2 < hps) part_load<Q>(pr, sp, role, b, c, head_at(hh + 2), tid);
         }
+        {   // operand reads run one contraction step ahead of their MFMAs
+            bf16x8 fb0 = frag_tr(L.st, BPITCH, 0, 64 * nh, lane), fb1 = frag_tr(L.st, BPITCH, 0, 64 * nh + 32, lane);
+            bf16x8 fa[RT];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) fa[rt] = lds_rows(L.tile, XPITCH, 32 * (rg * RT + rt), 0, lane);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                bf16x8 nb0 = fb0, nb1 = fb1, na[RT];
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) na[rt] = fa[rt];
+                if (ks + 1 < 4) {
+                    nb0 = frag_tr(L.st, BPITCH, 16 * (ks + 1), 64 * nh, lane);
+                    nb1 = frag_tr(L.st, BPITCH, 16 * (ks + 1), 64 * nh + 32, lane);
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) na[rt] = lds_rows(L.tile, XPITCH, 32 * (rg * RT + rt), 16 * (ks + 1), lane);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    acc[rt][0] = mfma(fa[rt], fb0, acc[rt][0]);
+                    acc[rt][1] = mfma(fa[rt], fb1, acc[rt][1]);
+                }
+                fb0 = nb0;
+                fb1 = nb1;
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) fa[rt] = na[rt];
+            }
+        }
+        SSDK_STAMP(2, 1);
+        if (has_dots) {
+            // z^T[p][i] = (state C_i)[p] (role 1: (state B_j)[p]); the staged tile already carries the token's weight
+            f32x16 z0 = zero16(), z1 = zero16();
+            bf16x8 a0 = lds_rows(L.st, BPITCH, 0, 0, lane), a1 = lds_rows(L.st, BPITCH, 32, 0, lane);
+#pragma unroll
+            for (int ks = 0; ks < N_ / 16; ++ks) {
+                bf16x8 n0 = a0, n1 = a1;
+                if (ks + 1 < N_ / 16) {
+                    n0 = lds_rows(L.st, BPITCH, 0, 16 * (ks + 1), lane);
+                    n1 = lds_rows(L.st, BPITCH, 32, 16 * (ks + 1), lane);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                z0 = mfma(a0, rf[ks], z0);
+                z1 = mfma(a1, rf[ks], z1);
+                a0 = n0;
+                a1 = n1;
+            }
+            const int tok = 32 * w + (lane & 31);
+            float sdot = 0.f;
+#pragma unroll
+            for (int pt = 0; pt < 2; ++pt)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const bf16x4 o = *(const bf16x4*)(L.tile + tok * XPITCH + (32 * pt + 8 * q + 4 * (lane >> 5)) * 2);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sdot += (float)o[e] * (pt ? z1 : z0)[4 * q + e];
+                }
+            sdot += __shfl_xor(sdot, 32, 64);
+            if (lane < 32) (role ? sp.sterm : sp.gterm)[(((int64_t)b * sp.H + head_at(hh)) * sp.nc + c) * Q + tok] = sdot;
+        }
+        SSDK_STAMP(2, 2);
+        // the next head: its loads were issued a whole head ago; stage it into the other buffer, then ask for the one after
+        if (!stage_first && hh + 1 < hps) part_store<Q>(pr, LL.b[(hh + 1) & 1], role, tid);
+        SSDK_STAMP(2, 3);
+        if (!stage_first && hh + 2 < hps) part_load<Q>(pr, sp, role, b, c, head_at(hh + 2), tid);
         SSDK_STAMP(2, 4);
         __syncthreads();
         SSDK_STAMP(2, 5);
     }
     float* part = sp.dbc_part + (((((int64_t)b * sp.nc + c) * sp.G + g) * ns + slice) * 2 + role) * ((int64_t)Q * N_);
-    emit(hps - 1);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *(f32x4*)(part + (32 * (rg * RT + rt) + (lane & 31)) * N_ + 64 * nh + 32 * nt + 8 * q + 4 * (lane >> 5)) =
-                    f32x4{acc[rt][nt][4 * q], acc[rt][nt][4 * q + 1], acc[rt][nt][4 * q + 2], acc[rt][nt][4 * q + 3]};
+            for (int r = 0; r < 16; ++r)
+                part[(int64_t)(32 * (rg * RT + rt) + acc_row(r, lane)) * N_ + 64 * nh + 32 * nt + (lane & 31)] = acc[rt][nt][r];
 }
 
 template <int Q>

@@ -52,7 +52,6 @@ static __device__ __forceinline__ bf16x8 frag_tr(const char* tile, int pitch, in
 // Zeros for every operand: a copy of the last row, infinite, would be a NaN under the dt = 0 of a row that does not exist.
 // Offsets are 32-bit: a chunk has at most 256 rows of H x 64 bf16 (< 4 GB for any H taken).
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 static __device__ __forceinline__ rsrc_t make_rows(const void* base, int rows, uint32_t rowbytes) {
     return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (uint32_t)rows * rowbytes, 0x00020000);
