@@ -825,7 +825,8 @@ namespace {
 //   30001 tokens, 24 heads, segment 4096:  5.3 -> 3.7, 3.6, 3.3
 constexpr int64_t TRAIN_WORK = (int64_t)8192 * 10576, INFER_WORK = 2 * TRAIN_WORK;
 int64_t rows_together(const BlockDims& d, int64_t work) {
-    const int64_t k = work / d.d_in_proj / d.s, n = d.nseg > 0 ? d.nseg : 1;
+    constexpr int64_t MOST = 65535;  // segments of a few tokens of a tiny block: the second dimension of a grid counts them
+    const int64_t w = work / d.d_in_proj / d.s, k = w < MOST ? w : MOST, n = d.nseg > 0 ? d.nseg : 1;
     return (k < 1 ? 1 : k < n ? k : n) * d.s;
 }
 // Rows of an inference pass: equal ones, whole chunks.
