@@ -384,7 +384,10 @@ int magc_block_bwd(const magc_block_shape_t* shape, const magc_block_params_t* p
  *            m * layer_interval (the first group restarts from x0); may be NULL if there is one group
  *   ssm_ckpt [nlayers, nseg, H, P, N] fp32, conv_ckpt [nlayers, nseg, 3, d_inner + 2 G N] bf16 (slot 0 of
  *            every layer unused: zero initial states); may be NULL if nseg == 1
- *   workspace: magc_blockstack_workspace_bytes bytes, 256-byte aligned: the activations of one cell
+ *   workspace: magc_blockstack_workspace_bytes bytes, 256-byte aligned: the activations of one cell, or of as many
+ *            consecutive segments of it as make 8192 x 10576 elements of the input projection's output (16384 x 10576
+ *            where nothing is kept): they are walked together, which changes gradients by their rounding where launches
+ *            are cut, and nothing else
  * The sequence starts from zero states in every layer; parameter gradients are overwritten or added to under
  * SSD_FLAG_ACCUM_PARAM.  Errors as for magc_block_*; layer_interval must lie in 1 .. nlayers.
  */
