@@ -384,10 +384,10 @@ int magc_block_bwd(const magc_block_shape_t* shape, const magc_block_params_t* p
  *            m * layer_interval (the first group restarts from x0); may be NULL if there is one group
  *   ssm_ckpt [nlayers, nseg, H, P, N] fp32, conv_ckpt [nlayers, nseg, 3, d_inner + 2 G N] bf16 (slot 0 of
  *            every layer unused: zero initial states); may be NULL if nseg == 1
- *   workspace: magc_blockstack_workspace_bytes bytes, 256-byte aligned: the activations of one cell, or of as many
- *            consecutive segments of it as make 8192 x 10576 elements of the input projection's output (16384 x 10576
- *            where nothing is kept): they are walked together, which changes gradients by their rounding where launches
- *            are cut, and nothing else
+ *   workspace: magc_blockstack_workspace_bytes bytes, 256-byte aligned: the activations of one cell, i.e. of one of the
+ *            caller's segments; that much serves every sequence, and every shorter one.  The forward pass uses more if
+ *            workspace_bytes says that there is more: as many consecutive segments as fit are walked together, up to 8192 x
+ *            10576 elements of the input projection's output, with the same output and checkpoints.
  * The sequence starts from zero states in every layer; parameter gradients are overwritten or added to under
  * SSD_FLAG_ACCUM_PARAM.  Errors as for magc_block_*; layer_interval must lie in 1 .. nlayers.
  */
@@ -396,6 +396,9 @@ typedef struct {
     int32_t nlayers, layer_interval;
 } magc_blockstack_shape_t;
 size_t magc_blockstack_workspace_bytes(const magc_blockstack_shape_t* shape, int32_t is_backward);
+/* What magc_blockstack_fwd (keeps_checkpoints != 0) or magc_blockstack_infer (0) uses of a workspace of `limit` bytes, or of the
+ * least that they take if that is more.  0: an invalid shape. */
+size_t magc_blockstack_pass_bytes(const magc_blockstack_shape_t* shape, int32_t keeps_checkpoints, size_t limit);
 int magc_blockstack_fwd(const magc_blockstack_shape_t* shape, const magc_block_params_t* params, const void* x0, void* out,
                         void* l_ckpt, float* ssm_ckpt, void* conv_ckpt, void* workspace, size_t workspace_bytes,
                         void* hip_stream);
@@ -410,8 +413,9 @@ int magc_blockstack_bwd(const magc_blockstack_shape_t* shape, const magc_block_p
  * live in two caller-owned device arrays,
  *   ssm_state [nlayers, H, P, N] fp32 and conv_state [nlayers, 3, d_inner + 2 G N] bf16,
  * which the call reads (fresh != 0: takes as zeros without reading them) and replaces by the states behind its
- * last token: a prompt of any length (walked in pieces of block.segment tokens through all layers), then calls
- * of one or a few tokens, continue one sequence.  x0, out [block.seqlen, d_model] bf16 (may be the same
+ * last token: a prompt of any length (walked through all layers in equal pieces of as many tokens as the workspace
+ * has room for, up to 16384 x 10576 elements of the input projection's output; in the scratch of a segment that is a third
+ * more than a segment at least), then calls of one or a few tokens, continue one sequence.  x0, out [block.seqlen, d_model] bf16 (may be the same
  * buffer); layer_interval is ignored (give any value in 1 .. nlayers).
  *   workspace: magc_blockstack_workspace_bytes(shape, 0) bytes, 256-byte aligned
  * Enqueued on hip_stream in order, nothing allocated, no other stream used.  Errors as for magc_blockstack_fwd.

@@ -22,7 +22,7 @@ EXPORTS = ("ssd_workspace_bytes", "ssd_workspace_bytes_flags", "ssd_fwd", "ssd_b
            "ssd_conv1d_workspace_bytes", "ssd_conv1d_fwd", "ssd_conv1d_bwd",
            "ssd_gated_norm_workspace_bytes", "ssd_gated_norm_fwd", "ssd_gated_norm_bwd", "ssd_linear_fwd", "ssd_linear_bwd",
            "magc_block_workspace_bytes", "magc_block_fwd", "magc_block_bwd",
-           "magc_blockstack_workspace_bytes", "magc_blockstack_fwd", "magc_blockstack_bwd", "magc_blockstack_infer", "magc_blockstack_decode",
+           "magc_blockstack_workspace_bytes", "magc_blockstack_pass_bytes", "magc_blockstack_fwd", "magc_blockstack_bwd", "magc_blockstack_infer", "magc_blockstack_decode",
            "magc_stack_workspace_bytes", "magc_stack_fwd",
            "magc_stack_bwd", "magc_plan", "ssd_strerror", "ssd_prof_enable", "ssd_prof_read", "ssd_prof_kernel_name", "ssd_prof_serialize", "ssd_prof_mfma_peak", "ssd_prof_clock_probe")
 
@@ -140,6 +140,8 @@ def lib():
         sshp = ctypes.POINTER(magc_blockstack_shape_t)
         L.magc_blockstack_workspace_bytes.restype = sz
         L.magc_blockstack_workspace_bytes.argtypes = [sshp, i32]
+        L.magc_blockstack_pass_bytes.restype = sz
+        L.magc_blockstack_pass_bytes.argtypes = [sshp, i32, sz]
         L.magc_blockstack_fwd.restype = ctypes.c_int
         L.magc_blockstack_fwd.argtypes = [sshp, bpar] + [vp] * 5 + [vp, sz, vp]
         L.magc_blockstack_infer.restype = ctypes.c_int
@@ -635,7 +637,11 @@ def magc_blockstack_fwd(x0, layers, nheads, headdim, ngroups, dstate, chunk, seg
     l_ckpt = torch.empty((max(ngl - 1, 1), L, dm), dtype=torch.bfloat16, device=dev)
     ssm_ckpt = torch.zeros((NL, nseg, nheads, headdim, dstate), dtype=torch.float32, device=dev)
     conv_ckpt = torch.zeros((NL, nseg, 3, conv_dim), dtype=torch.bfloat16, device=dev)
-    ws = _workspace(int(lib().magc_blockstack_workspace_bytes(ctypes.byref(sshape), 0)), dev)
+    ref = ctypes.byref(sshape)
+    least, back = (int(lib().magc_blockstack_workspace_bytes(ref, b)) for b in (0, 1))
+    # as many segments at a time as fit where the backward pass of this grid has one cell (or 16 MiB, for tiny stacks): a training
+    # step has the peak that the grid was chosen for
+    ws = _workspace(max(least, int(lib().magc_blockstack_pass_bytes(ref, 1, max(back, 1 << 24)))), dev)
     rc = lib().magc_blockstack_fwd(ctypes.byref(sshape), pars, _ptr(x0), _ptr(out), _ptr(l_ckpt), _ptr(ssm_ckpt), _ptr(conv_ckpt),
                                    _ptr(ws), ws.numel(), _stream(x0))
     if rc != 0:

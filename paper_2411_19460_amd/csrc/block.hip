@@ -197,7 +197,10 @@ struct BlockWs {
 };
 
 // ckpt_s: the forward scan stores checkpoints inside a segment (see Inner).
-BlockWs layout(const BlockDims& d, bool bwd, int64_t ckpt_s = 0) {
+// lean: for a piece of a stack's pass, all on one stream, whose block output takes y's place once the normalised y is formed.  The
+// normalised y takes the place of x, which the scan was the last to read, and the projection's normalised input that of the
+// scan's scratch.
+BlockWs layout(const BlockDims& d, bool bwd, int64_t ckpt_s = 0, bool lean = false) {
     BlockWs w;
     memset(&w, 0, sizeof(w));
     size_t off = 0;
@@ -207,14 +210,14 @@ BlockWs layout(const BlockDims& d, bool bwd, int64_t ckpt_s = 0) {
         return o;
     };
     const size_t s = (size_t)d.s;
-    w.un = take(s * d.dm * 2);
+    if (!lean) w.un = take(s * d.dm * 2);
     w.zx = take(s * d.d_in_proj * 2);
     w.x = take(s * d.d_inner * 2);
     w.B = take(s * d.gn * 2);
     w.C = take(s * d.gn * 2);
     w.dt = take(s * d.H * 2);
-    w.y = take(s * d.d_inner * 2);
-    w.yn = take(s * d.d_inner * 2);
+    w.y = take(s * (lean && d.dm > d.d_inner ? d.dm : d.d_inner) * 2);
+    w.yn = lean ? w.x : take(s * d.d_inner * 2);
     // scratch of the inner calls: for a whole segment and for the short last one (a segment of its own length)
     const ssd_shape_t ss = seg_shape(d, d.s);
     const ssd_shape_t st = seg_shape(d, d.L % d.s ? d.L % d.s : d.s);
@@ -231,6 +234,7 @@ BlockWs layout(const BlockDims& d, bool bwd, int64_t ckpt_s = 0) {
         inner = a > inner ? a : inner;
         inner = b > inner ? b : inner;
     }
+    if (lean && inner < s * d.dm * 2) inner = s * d.dm * 2;
     if (bwd) {
         w.dun = take(s * d.dm * 2);
         w.dyn = take(s * d.d_inner * 2);
@@ -251,15 +255,16 @@ BlockWs layout(const BlockDims& d, bool bwd, int64_t ckpt_s = 0) {
         inner = c > inner ? c : inner;
         inner = e > inner ? e : inner;
     }
-    if (!bwd) {
+    if (!bwd && !lean) {
         w.xp = take((size_t)FEW_ROWS * d.dm * 2);
         w.gp = take((size_t)FEW_ROWS * d.d_inner * 2);
         w.xsq = take((size_t)FEW_ROWS * ((d.dm + 15) / 16) * 4);
         w.gsq = take((size_t)FEW_ROWS * d.H * ((d.P + 7) / 8) * 4);
     }
-    for (int i = 0; i < 2; ++i) w.cssm[i] = take(d.HPN * 4);
-    for (int i = 0; i < 2; ++i) w.cconv[i] = take((size_t)3 * d.conv_dim * 2);
+    for (int i = 0; i < 2 && !lean; ++i) w.cssm[i] = take(d.HPN * 4);
+    for (int i = 0; i < 2 && !lean; ++i) w.cconv[i] = take((size_t)3 * d.conv_dim * 2);
     w.inner = take(inner);
+    if (lean) w.un = w.inner;
     w.inner_bytes = inner;
     w.total = off;
     return w;
@@ -665,11 +670,11 @@ extern "C" size_t magc_block_workspace_bytes(const magc_block_shape_t* sh, int32
 // those kernels round at other places than the chunked path that the backward pass recomputes the segment with,
 // and the result would depend (in its last bits) on how the sequence is cut into segments.
 // normed: the normalised input of the (first) segment is in the workspace already.  inner: checkpoints inside the one segment
-// of the call; the workspace has the scratch of a scan with them.
+// of the call; the workspace has the scratch of a scan with them.  lean: see layout; one segment.
 static int block_fwd(const magc_block_shape_t* sh, const magc_block_params_t* p, const void* u, const float* init_ssm,
                      const void* init_conv, void* out, float* ssm_ckpt, void* conv_ckpt, float* final_ssm, void* final_conv,
                      void* workspace, size_t workspace_bytes, bool few_ok, void* hip_stream, bool normed = false,
-                     const Inner* inner = nullptr) {
+                     const Inner* inner = nullptr, bool lean = false) {
     BlockDims d;
     BLK_TRY(check(sh, &d));
     if (!p || !p->W_in || !p->conv_w || !p->conv_b || !p->dt_bias || !p->A || !p->D || !p->norm_w || !p->W_out) return SSD_ERR_NULL;
@@ -684,7 +689,7 @@ static int block_fwd(const magc_block_shape_t* sh, const magc_block_params_t* p,
         return SSD_OK;
     }
     if (!u || !out) return SSD_ERR_NULL;
-    const BlockWs w = layout(d, false, inner ? inner->s : 0);
+    const BlockWs w = layout(d, false, inner ? inner->s : 0, lean);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < w.total) return SSD_ERR_WORKSPACE;
     char* ws = (char*)workspace;
     // Several segments: a segment's output projection and the next segment's input projection do not depend on
@@ -812,44 +817,15 @@ extern "C" int magc_block_bwd(const magc_block_shape_t* sh, const magc_block_par
 namespace ssdk {
 namespace {
 
-// Segments of a few thousand tokens are walked together: the steps of a layer run on as many rows as make `work` elements of
-// zxbcdt at most (or on one segment, if that is more).  A product's last round of tiles leaves compute units idle, every
-// segment reads and adds to the weights' gradients, and short launches are all ramp; more rows a launch cost scratch.
-//   Training: 8192 rows at the 2.7B width (10576 columns).  Scratch is that of a cell of so many tokens.
-//   Inference, where nothing is kept and where a prompt is cut concerns nobody: twice that, in equal passes.
-// One segment a launch -> training with 4096, 8192, 16384 rows of the 2.7B width (ms, forward + backward, 1-3 layers):
-//   16384 tokens, 80 heads, segment 4096:  13.0 -> 13.0, 12.2, 11.7;  segment 1024: 24.2 -> 13.0 (4096)
-//   20000 tokens, 24 heads, segment 2048:  11.8 -> 6.0, 5.4, 5.4;     30000, 32 heads, segment 4096: 10.6 -> 8.4, 7.3, 6.9
-// and inference with 4096, 8192, 16384:
-//   6001 tokens, 80 heads, segment 4096: 2.73 -> 2.71, 2.23, 2.23;    13001, 80 heads, segment 2048: 7.0 -> 5.6, 5.2, 4.9
-//   30001 tokens, 24 heads, segment 4096:  5.3 -> 3.7, 3.6, 3.3
-constexpr int64_t TRAIN_WORK = (int64_t)8192 * 10576, INFER_WORK = 2 * TRAIN_WORK;
-int64_t rows_together(const BlockDims& d, int64_t work) {
-    constexpr int64_t MOST = 65535;  // segments of a few tokens of a tiny block: the second dimension of a grid counts them
-    const int64_t w = work / d.d_in_proj / d.s, k = w < MOST ? w : MOST, n = d.nseg > 0 ? d.nseg : 1;
-    return (k < 1 ? 1 : k < n ? k : n) * d.s;
-}
-// Rows of an inference pass: equal ones, whole chunks.
-int64_t pass_rows(const BlockDims& d, int64_t most) {
-    const int64_t n = (d.L + most - 1) / most, per = n > 0 ? (d.L + n - 1) / n : most, rows = (per + d.Q - 1) / d.Q * d.Q;
-    return n > 1 ? rows : most;
-}
-
 struct StackDims {
     BlockDims b;
     int NL, l, ngl;  // layers, layer interval, layer groups
     size_t act, conv_state, conv_adj;
 };
 
-// work: see rows_together; d->b.s is what is walked as one segment, `wide` the shape with it, `own` the caller's dimensions.
-int check_stack(const magc_blockstack_shape_t* sh, StackDims* d, int64_t work, magc_blockstack_shape_t* wide, BlockDims* own) {
+int check_stack(const magc_blockstack_shape_t* sh, StackDims* d) {
     if (!sh) return SSD_ERR_NULL;
-    int rc = check(&sh->block, own);
-    if (rc != SSD_OK) return rc;
-    *wide = *sh;
-    const int64_t rows = rows_together(*own, work);
-    if (rows != own->s) wide->block.segment = rows;
-    rc = check(&wide->block, &d->b);
+    const int rc = check(&sh->block, &d->b);
     if (rc != SSD_OK) return rc;
     if (sh->nlayers <= 0 || sh->layer_interval <= 0 || sh->layer_interval > sh->nlayers) return SSD_ERR_SHAPE;
     d->NL = sh->nlayers;
@@ -861,6 +837,19 @@ int check_stack(const magc_blockstack_shape_t* sh, StackDims* d, int64_t work, m
     return SSD_OK;
 }
 
+// The backward pass walks segments of up to 8192 rows of the 2.7B width (10576 columns of zxbcdt) together: the caller's dimensions
+// in `own`, and in `wide` and d those with what is walked as one segment.
+int check_wide(const magc_blockstack_shape_t* sh, StackDims* d, magc_blockstack_shape_t* wide, BlockDims* own) {
+    BLK_TRY(check_stack(sh, d));
+    *own = d->b;
+    *wide = *sh;
+    const int64_t w = (int64_t)8192 * 10576 / own->d_in_proj / own->s, k = w < 65535 ? w : 65535, n = own->nseg > 0 ? own->nseg : 1;
+    const int64_t rows = (k < 1 ? 1 : k < n ? k : n) * own->s;
+    if (rows == own->s) return SSD_OK;
+    wide->block.segment = rows;
+    return check_stack(wide, d);
+}
+
 magc_block_shape_t cell_shape(const magc_blockstack_shape_t* sh, int64_t rows) {
     magc_block_shape_t c = sh->block;
     c.seqlen = rows;  // one segment: the cell
@@ -868,11 +857,11 @@ magc_block_shape_t cell_shape(const magc_blockstack_shape_t* sh, int64_t rows) {
 }
 
 struct StackWs {
-    size_t act[2], xs, zx, y, dcur, du, dssm, dconv, fin_ssm, fin_conv, inner, inner_bytes, total;
+    size_t act[2], stream, xs, zx, y, dcur, du, dssm, dconv, fin_ssm, fin_conv, inner, inner_bytes, total;
     size_t zx_bytes, y_bytes;  // per layer of a cell
 };
 
-StackWs stack_layout(const magc_blockstack_shape_t* sh, const StackDims& d, bool bwd, int64_t ckpt_s = 0) {
+StackWs stack_layout(const magc_blockstack_shape_t* sh, const StackDims& d, bool bwd) {
     StackWs w;
     memset(&w, 0, sizeof(w));
     size_t off = 0;
@@ -906,10 +895,6 @@ StackWs stack_layout(const magc_blockstack_shape_t* sh, const StackDims& d, bool
     }
     const size_t f = magc_block_workspace_bytes(&c, 0);  // the forward pass calls the block's forward entry point
     inner = f > inner ? f : inner;
-    if (ckpt_s) {
-        const size_t k = layout(d.b, false, ckpt_s).total;
-        inner = k > inner ? k : inner;
-    }
     if (bwd) {  // the backward pass lays a block workspace out in this region itself
         const size_t own = layout(d.b, true).total;
         inner = own > inner ? own : inner;
@@ -918,6 +903,81 @@ StackWs stack_layout(const magc_blockstack_shape_t* sh, const StackDims& d, bool
     w.inner_bytes = inner;
     w.total = off;
     return w;
+}
+
+// A forward pass over the stack takes as many tokens at a time as the workspace given has room for: a product's last round of tiles
+// leaves compute units idle, and short launches are all ramp.
+//   The least that a workspace may be is the scratch of one of the caller's segments, laid out as the block's own (stack_layout);
+// where the residual stream can live in the caller's output and the buffers of a piece share their places (layout), half as many
+// tokens again fit there.
+//   With checkpoints, whole segments, up to 8192 rows of the 2.7B width (10576 columns of zxbcdt); the scan puts the checkpoints
+// down on its way.  Where nothing is kept: whole chunks, up to twice that, in equal pieces.
+// One segment a launch -> 4096, 8192, 16384 rows (ms, forward, nothing kept, four blocks):
+//   6001 tokens, 80 heads, segment 4096: 2.73 -> 2.71, 2.23, 2.23;    13001, 80 heads, segment 2048: 7.0 -> 5.6, 5.2, 4.9
+//   30001 tokens, 24 heads, segment 4096:  5.3 -> 3.7, 3.6, 3.3
+constexpr int64_t KEEP_WORK = (int64_t)8192 * 10576, INFER_WORK = 2 * KEEP_WORK;
+struct Pass {
+    magc_blockstack_shape_t shape, few;  // the stack with a piece as its segment; few: of at most FEW_ROWS tokens, which take the
+                                         // block's own layout (the kernels of a few rows read y where they write the output)
+    StackDims d;
+    StackWs w;
+    bool lean;
+};
+
+// Lays out pieces of `rows` tokens (ckpt_s: checkpoints inside a piece); false where a step does not take so many rows.
+// out_ok: the caller's output is aligned as the steps take their input.
+bool lay_out_pass(const magc_blockstack_shape_t* sh, int64_t rows, int64_t ckpt_s, bool out_ok, Pass* p) {
+    p->lean = true;
+    p->shape = p->few = *sh;
+    p->shape.block.segment = rows;
+    StackDims few;
+    p->few.block.segment = (FEW_ROWS + sh->block.chunk - 1) / sh->block.chunk * sh->block.chunk;
+    p->few.block.seqlen = FEW_ROWS;
+    if (check_stack(&p->shape, &p->d) != SSD_OK || check_stack(&p->few, &few) != SSD_OK) return false;
+    const ssd_shape_t ss = seg_shape(p->d.b, rows);
+    const ssd_conv_shape_t cs = conv_shape(p->d.b, rows);
+    if (!ssd_workspace_bytes(&ss, 0) || !ssd_conv1d_workspace_bytes(&cs)) return false;
+    StackWs& w = p->w;
+    memset(&w, 0, sizeof(w));
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        const size_t o = off;
+        off += al(bytes);
+        return o;
+    };
+    w.stream = take(out_ok ? 0 : p->d.act);
+    for (int i = 0; i < 2; ++i) w.act[i] = take((size_t)FEW_ROWS * p->d.b.dm * 2);
+    w.fin_ssm = take(p->d.b.HPN * 4);
+    w.fin_conv = take(p->d.conv_state);
+    const size_t a = layout(p->d.b, false, ckpt_s, true).total, b = layout(few.b, false).total;
+    w.inner_bytes = a > b ? a : b;
+    w.inner = take(w.inner_bytes);
+    w.total = off;
+    return true;
+}
+
+// keep: the pass leaves checkpoints.  d: the stack with the caller's segment.
+Pass plan_pass(const magc_blockstack_shape_t* sh, const StackDims& d, const StackWs& least, bool keep, const void* out, size_t bytes) {
+    Pass p = {*sh, *sh, d, least, false};
+    if (d.b.nseg <= 1) return p;
+    constexpr int64_t SEGMENTS = 65535;  // as many as the second dimension of a grid counts
+    const int64_t unit = keep ? d.b.s : d.b.Q, all = (d.b.L + unit - 1) / unit;
+    int64_t lo = d.b.s / unit, hi = (keep ? KEEP_WORK : INFER_WORK) / (d.b.d_in_proj > d.b.dm ? d.b.d_in_proj : d.b.dm) / unit;
+    hi = hi < all ? hi : all;
+    if (keep) hi = hi < SEGMENTS ? hi : SEGMENTS;
+    auto fits = [&](int64_t n, Pass* q) { return lay_out_pass(sh, n * unit, keep ? d.b.s : 0, ((uintptr_t)out & 15) == 0, q) && q->w.total <= bytes; };
+    Pass q;
+    while (lo < hi) {  // the most that fit
+        const int64_t n = hi - (hi - lo) / 2;
+        if (fits(n, &q)) lo = n;
+        else hi = n - 1;
+    }
+    if (!keep) {  // equal pieces
+        const int64_t pieces = (all + lo - 1) / lo;
+        lo = (all + pieces - 1) / pieces;
+    }
+    if (fits(lo, &q)) return q;
+    return p;
 }
 
 bool params_ok(const magc_block_params_t* p, int n) {
@@ -932,64 +992,72 @@ bool params_ok(const magc_block_params_t* p, int n) {
 
 extern "C" size_t magc_blockstack_workspace_bytes(const magc_blockstack_shape_t* sh, int32_t is_backward) {
     StackDims d;
+    if (check_stack(sh, &d) != SSD_OK) return 0;
+    const magc_block_shape_t c = cell_shape(sh, d.b.s);
+    if (magc_block_workspace_bytes(&c, is_backward) == 0) return 0;
+    if (!is_backward) return stack_layout(sh, d, false).total;
     magc_blockstack_shape_t wide;
     BlockDims own;
-    if (check_stack(sh, &d, TRAIN_WORK, &wide, &own) != SSD_OK) return 0;
-    const magc_block_shape_t c = cell_shape(sh, own.s);
-    if (magc_block_workspace_bytes(&c, is_backward) == 0) return 0;
-    size_t t = stack_layout(&wide, d, is_backward != 0, is_backward ? 0 : own.s).total;
-    if (!is_backward) {  // the two forward passes, one that records checkpoints and one that keeps nothing
-        if (check_stack(sh, &d, INFER_WORK, &wide, &own) != SSD_OK) return 0;
-        const size_t n = stack_layout(&wide, d, false).total;
-        t = n > t ? n : t;
-    }
-    return t;
+    return check_wide(sh, &d, &wide, &own) == SSD_OK ? stack_layout(&wide, d, true).total : 0;
+}
+
+extern "C" size_t magc_blockstack_pass_bytes(const magc_blockstack_shape_t* sh, int32_t keeps_checkpoints, size_t limit) {
+    StackDims d;
+    const size_t least = magc_blockstack_workspace_bytes(sh, 0);
+    if (!least || check_stack(sh, &d) != SSD_OK) return 0;
+    return plan_pass(sh, d, stack_layout(sh, d, false), keeps_checkpoints != 0, nullptr, limit > least ? limit : least).w.total;
 }
 
 extern "C" int magc_blockstack_fwd(const magc_blockstack_shape_t* sh, const magc_block_params_t* params, const void* x0, void* out,
                                    void* l_ckpt, float* ssm_ckpt, void* conv_ckpt, void* workspace, size_t workspace_bytes,
                                    void* hip_stream) {
     StackDims d;
-    magc_blockstack_shape_t wide;
-    BlockDims own;
-    BLK_TRY(check_stack(sh, &d, TRAIN_WORK, &wide, &own));
+    BLK_TRY(check_stack(sh, &d));
     if (!params_ok(params, d.NL)) return SSD_ERR_NULL;
     if (d.b.L == 0) return SSD_OK;
-    if (!x0 || !out || (d.ngl > 1 && !l_ckpt) || (own.nseg > 1 && (!ssm_ckpt || !conv_ckpt))) return SSD_ERR_NULL;
-    const StackWs w = stack_layout(&wide, d, false, own.s);
-    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < w.total) return SSD_ERR_WORKSPACE;
+    if (!x0 || !out || (d.ngl > 1 && !l_ckpt) || (d.b.nseg > 1 && (!ssm_ckpt || !conv_ckpt))) return SSD_ERR_NULL;
+    const StackWs least = stack_layout(sh, d, false);
+    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < least.total) return SSD_ERR_WORKSPACE;
+    const Pass p = plan_pass(sh, d, least, true, out, workspace_bytes);
+    const StackWs& w = p.w;
     hipStream_t st = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
     const size_t row = (size_t)d.b.dm * 2;
-    for (int64_t t0 = 0; t0 < d.b.L; t0 += d.b.s) {
-        const int64_t rows = d.b.L - t0 < d.b.s ? d.b.L - t0 : d.b.s;
-        const int64_t k = t0 / own.s, next = (t0 + d.b.s) / own.s;  // the caller's segments that start these rows and the next
-        const magc_block_shape_t c = cell_shape(&wide, rows);
-        const bool last = t0 + rows == d.b.L, several = rows > own.s;
+    for (int64_t t0 = 0; t0 < d.b.L; t0 += p.d.b.s) {
+        const int64_t rows = d.b.L - t0 < p.d.b.s ? d.b.L - t0 : p.d.b.s;
+        const int64_t k = t0 / d.b.s, next = (t0 + p.d.b.s) / d.b.s;  // the caller's segments that start these rows and the next
+        const magc_block_shape_t c = cell_shape(&p.shape, rows);
+        const bool last = t0 + rows == d.b.L, several = rows > d.b.s;
         const char* cur = (const char*)x0 + (size_t)t0 * row;
         BlockDims dc;
         BLK_TRY(check(&c, &dc));
-        char* un = ws + w.inner + layout(dc, false).un;  // where the next layer's block looks for its normalised input
+        const BlockWs bw = layout(dc, false, several ? d.b.s : 0, p.lean);
+        if (bw.total > w.inner_bytes) return SSD_ERR_WORKSPACE;
+        char* out_rows = (char*)out + (size_t)t0 * row;
+        char* stream = ((uintptr_t)out & 15) ? ws + w.stream : out_rows;
+        char* un = ws + w.inner + bw.un;  // where the next layer's block looks for its normalised input
         bool normed = false;
         for (int j = 0; j < d.NL; ++j) {
             // sequence-axis checkpoints of layer j: slot k = the states entering segment k (slot 0 unused: zeros)
-            float* sj = ssm_ckpt ? ssm_ckpt + (size_t)j * own.nseg * d.b.HPN : nullptr;
-            char* cj = conv_ckpt ? (char*)conv_ckpt + (size_t)j * own.nseg * d.conv_state : nullptr;
+            float* sj = ssm_ckpt ? ssm_ckpt + (size_t)j * d.b.nseg * d.b.HPN : nullptr;
+            char* cj = conv_ckpt ? (char*)conv_ckpt + (size_t)j * d.b.nseg * d.conv_state : nullptr;
             const float* ssm_in = k ? sj + (size_t)k * d.b.HPN : nullptr;
             const void* conv_in = k ? cj + (size_t)k * d.conv_state : nullptr;
             float* ssm_out = last ? (float*)(ws + w.fin_ssm) : sj + (size_t)next * d.b.HPN;
             void* conv_out = last ? (void*)(ws + w.fin_conv) : (void*)(cj + (size_t)next * d.conv_state);
-            char* y = ws + w.act[j & 1];
-            Inner inner = {own.s, nullptr, nullptr};
+            char* y = p.lean ? ws + w.inner + bw.y : ws + w.act[j & 1];
+            Inner inner = {d.b.s, nullptr, nullptr};
             if (several) {
                 inner.ssm = sj + (size_t)k * d.b.HPN;
                 inner.conv = cj + (size_t)k * d.conv_state;
             }
             BLK_TRY(block_fwd(&c, &params[j], cur, ssm_in, conv_in, y, nullptr, nullptr, ssm_out, conv_out, ws + w.inner, w.inner_bytes,
-                              false, st, normed, several ? &inner : nullptr));
+                              false, st, normed, several ? &inner : nullptr, p.lean));
             // the input of the next layer: the stack's output, a layer-axis checkpoint, or a buffer
-            char* nxt = j + 1 == d.NL ? (char*)out + (size_t)t0 * row
-                                      : (j + 1) % d.l == 0 ? (char*)l_ckpt + ((size_t)((j + 1) / d.l - 1) * d.b.L + t0) * row : y;
+            char* nxt = j + 1 == d.NL ? out_rows
+                                      : (j + 1) % d.l == 0 ? (char*)l_ckpt + ((size_t)((j + 1) / d.l - 1) * d.b.L + t0) * row
+                                      : p.lean         ? stream
+                                                       : y;
             BLK_TRY(residual(dc, c.eps, nxt, cur, y, rows, j + 1 < d.NL ? params[j + 1].pre_norm_w : nullptr, un, nullptr, nullptr, 0, &normed, st));
             cur = nxt;
         }
@@ -1004,7 +1072,7 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
     StackDims d;
     magc_blockstack_shape_t wide;
     BlockDims own_b;
-    BLK_TRY(check_stack(sh, &d, TRAIN_WORK, &wide, &own_b));
+    BLK_TRY(check_wide(sh, &d, &wide, &own_b));
     if (flags & ~(uint32_t)SSD_FLAG_ACCUM_PARAM) return SSD_ERR_ARG;
     if (!params_ok(params, d.NL) || !grads) return SSD_ERR_NULL;
     for (int j = 0; j < d.NL; ++j)
@@ -1121,9 +1189,7 @@ extern "C" int magc_blockstack_infer(const magc_blockstack_shape_t* sh, const ma
                                      float* ssm_state, void* conv_state, int32_t fresh, void* workspace, size_t workspace_bytes,
                                      void* hip_stream) {
     StackDims d;
-    magc_blockstack_shape_t wide;
-    BlockDims own;
-    BLK_TRY(check_stack(sh, &d, INFER_WORK, &wide, &own));
+    BLK_TRY(check_stack(sh, &d));
     if (!params_ok(params, d.NL) || !ssm_state || !conv_state) return SSD_ERR_NULL;
     hipStream_t st = (hipStream_t)hip_stream;
     if (d.b.L == 0) {
@@ -1134,20 +1200,24 @@ extern "C" int magc_blockstack_infer(const magc_blockstack_shape_t* sh, const ma
         return SSD_OK;
     }
     if (!x0 || !out) return SSD_ERR_NULL;
-    const StackWs w = stack_layout(&wide, d, false);
-    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < w.total) return SSD_ERR_WORKSPACE;
+    const StackWs least = stack_layout(sh, d, false);
+    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < least.total) return SSD_ERR_WORKSPACE;
+    const Pass p = plan_pass(sh, d, least, false, out, workspace_bytes);
+    const StackWs& w = p.w;
     char* ws = (char*)workspace;
     const size_t row = (size_t)d.b.dm * 2;
-    const int64_t step = pass_rows(d.b, d.b.s);
-    for (int64_t t0 = 0; t0 < d.b.L; t0 += step) {
-        const int64_t rows = d.b.L - t0 < step ? d.b.L - t0 : step;
-        const magc_block_shape_t c = cell_shape(&wide, rows);
+    for (int64_t t0 = 0; t0 < d.b.L; t0 += p.d.b.s) {
+        const int64_t rows = d.b.L - t0 < p.d.b.s ? d.b.L - t0 : p.d.b.s;
+        const bool lean = p.lean && rows > FEW_ROWS;
+        const magc_block_shape_t c = cell_shape(p.lean && !lean ? &p.few : &p.shape, rows);
         BlockDims dc;
         BLK_TRY(check(&c, &dc));
-        const BlockWs bw = layout(dc, false);  // for the few-token path, which lays a block workspace out itself
+        const BlockWs bw = layout(dc, false, 0, lean);  // for the few-token path, which lays a block workspace out itself
         if (bw.total > w.inner_bytes) return SSD_ERR_WORKSPACE;
         char* bws = ws + w.inner;
         const bool zero = fresh && t0 == 0;
+        char* out_rows = (char*)out + (size_t)t0 * row;
+        char* stream = ((uintptr_t)out & 15) ? ws + w.stream : out_rows;
         bool normed = false;  // the layer before has left this one's normalised input
         bool packed = false;  // the layer before has left this one's packed input
         const char* cur = (const char*)x0 + (size_t)t0 * row;
@@ -1155,8 +1225,8 @@ extern "C" int magc_blockstack_infer(const magc_blockstack_shape_t* sh, const ma
             float* sj = ssm_state + (size_t)j * d.b.HPN;
             char* cj = (char*)conv_state + (size_t)j * d.conv_state;
             float* ssm_out = sj;  // in place: the recurrence of a few tokens, or one segment's scan
-            char* y = ws + w.act[j & 1];
-            char* nxt = j + 1 == d.NL ? (char*)out + (size_t)t0 * row : y;  // x_{j+1} = x_j + Block_j(x_j)
+            char* y = lean ? bws + bw.y : ws + w.act[j & 1];
+            char* nxt = j + 1 == d.NL ? out_rows : lean ? stream : y;  // x_{j+1} = x_j + Block_j(x_j)
             if (few_path(dc, &params[j], rows, ssm_out, cur, nxt)) {
                 // generation: the residual and the move of the convolution state ride on the output product
                 FewSeqs sq;
@@ -1173,7 +1243,7 @@ extern "C" int magc_blockstack_infer(const magc_blockstack_shape_t* sh, const ma
                                     ws + w.fin_conv, nxt, cur, sq, st));
             } else {
                 BLK_TRY(block_fwd(&c, &params[j], cur, zero ? nullptr : sj, zero ? nullptr : cj, y, nullptr, nullptr, ssm_out, ws + w.fin_conv,
-                                  ws + w.inner, w.inner_bytes, true, st, normed));
+                                  ws + w.inner, w.inner_bytes, true, st, normed, nullptr, lean));
                 BLK_TRY(residual(dc, c.eps, nxt, cur, y, rows, j + 1 < d.NL ? params[j + 1].pre_norm_w : nullptr, bws + bw.un, ws + w.fin_conv, cj,
                                  d.conv_state, &normed, st));
             }
@@ -1192,9 +1262,7 @@ extern "C" int magc_blockstack_decode(const magc_blockstack_shape_t* sh_in, cons
     one.block.seqlen = 1;
     const magc_blockstack_shape_t* sh = &one;
     StackDims d;
-    magc_blockstack_shape_t wide;
-    BlockDims own;
-    BLK_TRY(check_stack(sh, &d, INFER_WORK, &wide, &own));  // one segment: as it is
+    BLK_TRY(check_stack(sh, &d));
     if (nseq < 0 || nseq > FEW_ROWS) return SSD_ERR_SHAPE;
     if (!params_ok(params, d.NL)) return SSD_ERR_NULL;
     if (nseq == 0) return SSD_OK;
