@@ -837,19 +837,6 @@ int check_stack(const magc_blockstack_shape_t* sh, StackDims* d) {
     return SSD_OK;
 }
 
-// The backward pass walks segments of up to 8192 rows of the 2.7B width (10576 columns of zxbcdt) together: the caller's dimensions
-// in `own`, and in `wide` and d those with what is walked as one segment.
-int check_wide(const magc_blockstack_shape_t* sh, StackDims* d, magc_blockstack_shape_t* wide, BlockDims* own) {
-    BLK_TRY(check_stack(sh, d));
-    *own = d->b;
-    *wide = *sh;
-    const int64_t w = (int64_t)8192 * 10576 / own->d_in_proj / own->s, k = w < 65535 ? w : 65535, n = own->nseg > 0 ? own->nseg : 1;
-    const int64_t rows = (k < 1 ? 1 : k < n ? k : n) * own->s;
-    if (rows == own->s) return SSD_OK;
-    wide->block.segment = rows;
-    return check_stack(wide, d);
-}
-
 magc_block_shape_t cell_shape(const magc_blockstack_shape_t* sh, int64_t rows) {
     magc_block_shape_t c = sh->block;
     c.seqlen = rows;  // one segment: the cell
@@ -906,7 +893,8 @@ StackWs stack_layout(const magc_blockstack_shape_t* sh, const StackDims& d, bool
 }
 
 // A forward pass over the stack takes as many tokens at a time as the workspace given has room for: a product's last round of tiles
-// leaves compute units idle, and short launches are all ramp.
+// leaves compute units idle, and short launches are all ramp.  The backward pass walks the caller's segments: a segment's scratch
+// is what the interval was chosen for, and how partial sums of gradients are cut and stored goes by the chunks of a launch.
 //   The least that a workspace may be is the scratch of one of the caller's segments, laid out as the block's own (stack_layout);
 // where the residual stream can live in the caller's output and the buffers of a piece share their places (layout), half as many
 // tokens again fit there.
@@ -995,10 +983,7 @@ extern "C" size_t magc_blockstack_workspace_bytes(const magc_blockstack_shape_t*
     if (check_stack(sh, &d) != SSD_OK) return 0;
     const magc_block_shape_t c = cell_shape(sh, d.b.s);
     if (magc_block_workspace_bytes(&c, is_backward) == 0) return 0;
-    if (!is_backward) return stack_layout(sh, d, false).total;
-    magc_blockstack_shape_t wide;
-    BlockDims own;
-    return check_wide(sh, &d, &wide, &own) == SSD_OK ? stack_layout(&wide, d, true).total : 0;
+    return stack_layout(sh, d, is_backward != 0).total;
 }
 
 extern "C" size_t magc_blockstack_pass_bytes(const magc_blockstack_shape_t* sh, int32_t keeps_checkpoints, size_t limit) {
@@ -1070,9 +1055,7 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
                                    const magc_block_grads_t* grads, void* workspace, size_t workspace_bytes, uint32_t flags,
                                    void* hip_stream) {
     StackDims d;
-    magc_blockstack_shape_t wide;
-    BlockDims own_b;
-    BLK_TRY(check_wide(sh, &d, &wide, &own_b));
+    BLK_TRY(check_stack(sh, &d));
     if (flags & ~(uint32_t)SSD_FLAG_ACCUM_PARAM) return SSD_ERR_ARG;
     if (!params_ok(params, d.NL) || !grads) return SSD_ERR_NULL;
     for (int j = 0; j < d.NL; ++j)
@@ -1094,8 +1077,8 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
             if (d.b.L == 0 || !own(j)) BLK_HIP(clear_weights(d.b, grads[j], st));
         }
     if (d.b.L == 0) return SSD_OK;
-    if (!x0 || !dout || !dx0 || (d.ngl > 1 && !l_ckpt) || (own_b.nseg > 1 && (!ssm_ckpt || !conv_ckpt))) return SSD_ERR_NULL;
-    const StackWs w = stack_layout(&wide, d, true);
+    if (!x0 || !dout || !dx0 || (d.ngl > 1 && !l_ckpt) || (d.b.nseg > 1 && (!ssm_ckpt || !conv_ckpt))) return SSD_ERR_NULL;
+    const StackWs w = stack_layout(sh, d, true);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < w.total) return SSD_ERR_WORKSPACE;
     char* ws = (char*)workspace;
     // a cell's layer uses the block's own workspace layout inside the inner region (buffers of one segment;
@@ -1105,8 +1088,7 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
     char* bws = ws + w.inner;
     for (int64_t k = d.b.nseg - 1; k >= 0; --k) {
         const int64_t t0 = k * d.b.s, rows = d.b.L - t0 < d.b.s ? d.b.L - t0 : d.b.s;
-        const int64_t k0 = t0 / own_b.s;  // the caller's segment that starts these rows
-        const magc_block_shape_t c = cell_shape(&wide, rows);
+        const magc_block_shape_t c = cell_shape(sh, rows);
         BlockDims dc;
         BLK_TRY(check(&c, &dc));
         const bool last = k + 1 == d.b.nseg;
@@ -1118,8 +1100,8 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
             const char* xin = m ? (const char*)l_ckpt + ((size_t)(m - 1) * d.b.L + t0) * row : (const char*)x0 + (size_t)t0 * row;
             bool normed = false;
             for (int j = j0; j <= j1; ++j) {
-                const float* ssm_in = k ? ssm_ckpt + ((size_t)j * own_b.nseg + k0) * d.b.HPN : nullptr;
-                const void* conv_in = k ? (const char*)conv_ckpt + ((size_t)j * own_b.nseg + k0) * d.conv_state : nullptr;
+                const float* ssm_in = k ? ssm_ckpt + ((size_t)j * d.b.nseg + k) * d.b.HPN : nullptr;
+                const void* conv_in = k ? (const char*)conv_ckpt + ((size_t)j * d.b.nseg + k) * d.conv_state : nullptr;
                 char* zx = ws + w.zx + (size_t)(j - j0) * w.zx_bytes;
                 char* y = ws + w.y + (size_t)(j - j0) * w.y_bytes;
                 BLK_TRY(seg_in_proj(dc, c.eps, &params[j], bws, bw, xin, rows, zx, st, normed));
@@ -1138,8 +1120,8 @@ extern "C" int magc_blockstack_bwd(const magc_blockstack_shape_t* sh, const magc
             for (int j = j1; j >= j0; --j) {
                 const char* xj = j == j0 ? (m ? (const char*)l_ckpt + ((size_t)(m - 1) * d.b.L + t0) * row : (const char*)x0 + (size_t)t0 * row)
                                          : ws + w.xs + (size_t)(j - j0) * d.act;
-                const float* ssm_in = k ? ssm_ckpt + ((size_t)j * own_b.nseg + k0) * d.b.HPN : nullptr;
-                const void* conv_in = k ? (const char*)conv_ckpt + ((size_t)j * own_b.nseg + k0) * d.conv_state : nullptr;
+                const float* ssm_in = k ? ssm_ckpt + ((size_t)j * d.b.nseg + k) * d.b.HPN : nullptr;
+                const void* conv_in = k ? (const char*)conv_ckpt + ((size_t)j * d.b.nseg + k) * d.conv_state : nullptr;
                 const char* zx = ws + w.zx + (size_t)(j - j0) * w.zx_bytes;
                 const char* y = ws + w.y + (size_t)(j - j0) * w.y_bytes;
                 // the cheap steps again from zxbcdt_j and y_j: (x | B | C), the normalised y.  The cell's top layer was

@@ -182,7 +182,10 @@ def test_block_pieces_validate_before_any_launch():
     assert L.magc_blockstack_workspace_bytes(ctypes.byref(binding.magc_blockstack_shape_t(bs, 4, 5)), 0) == 0     # interval above the layer count
     # segments that are walked together are no more than a grid's second dimension counts, however small the block
     tiny = [binding.magc_blockstack_shape_t(binding.magc_block_shape_t(8, 8, 1, 8, 1, 1, 1e-5, n, 1), 1, 1) for n in (200000, 400000)]
-    assert len({L.magc_blockstack_workspace_bytes(ctypes.byref(t), 1) for t in tiny}) == 1
+    for size in (lambda t: L.magc_blockstack_workspace_bytes(t, 0), lambda t: L.magc_blockstack_workspace_bytes(t, 1),
+                 lambda t: L.magc_blockstack_pass_bytes(t, 1, 1 << 60)):
+        got = [size(ctypes.byref(t)) for t in tiny]
+        assert got[0] == got[1] > 0
     pars = (binding.magc_block_params_t * 4)()
     assert L.magc_blockstack_infer(ctypes.byref(ss), pars, fake, fake, fake, fake, 0, fake, 1 << 40, None) == ERR_NULL      # parameters missing
     for k in binding.BLOCK_PARAMS[:-1]:

@@ -1,6 +1,7 @@
-"""A stack walks several segments as one set of launches (block.hip: rows_together), and a long prompt in equal passes.  Neither the
-result nor the checkpoints may depend on it: sequences just longer than what is walked together, against one segment for the whole
-sequence, and the checkpoints against the states that inference leaves behind the same tokens."""
+"""The forward passes of a stack walk several segments as one set of launches (block.hip: plan_pass), and a long prompt in equal
+pieces.  Neither the result nor the checkpoints may depend on it: sequences just longer than what may be walked together, against
+one segment for the whole sequence, and the checkpoints against the states that inference leaves behind the same tokens.  The
+backward pass walks the caller's segments."""
 import pytest
 import torch
 

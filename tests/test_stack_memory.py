@@ -1,4 +1,5 @@
-"""What a stack of blocks takes in scratch (host only: the library's own size queries)."""
+"""What a stack of blocks takes in scratch: the activations of one grid cell, whatever the length of the sequence (host only: the
+library's own size queries)."""
 import ctypes
 
 import pytest
@@ -24,9 +25,10 @@ def block_need(sh, back):
 
 
 def sizes(H, Q=256, G=1, hd=P, n=N, dm=None):
-    """Bytes: of a layer input, per token; of both states of a layer."""
+    """Bytes: of a kept layer input and of what a cell keeps, per layer and token; of both states of a layer; of their adjoints."""
     dm, di, gn = dm or 32 * H, H * hd, G * n
-    return dm * 2, H * hd * n * 4 + 3 * (di + 2 * gn) * 2
+    conv, d_in = di + 2 * gn, 2 * di + 2 * gn + H
+    return dm * 2, (dm + d_in + di) * 2, H * hd * n * 4 + 3 * conv * 2, H * hd * n * 4 + 3 * conv * 4
 
 
 @pytest.mark.parametrize("case", [
@@ -38,15 +40,38 @@ def sizes(H, Q=256, G=1, hd=P, n=N, dm=None):
     (8, 400000, 2, 1, 1, dict(Q=2, n=256)),            # short chunks, large states
     (8, 5000000, 4096, 1, 1, dict(hd=1, G=8, n=1, dm=8)),  # the narrowest block there is
 ])
-def test_forward_scratch_is_that_of_one_segment(case):
+def test_scratch_is_that_of_one_cell(case):
     H, L, seg, nl, l, more = case
-    c_l, c_s = sizes(H, **more)
+    c_l, c_grid, c_s, c_adj = sizes(H, **more)
     sh = _stack(H, L, seg, nl, l, **more)
-    # the block's own scratch, two buffers of activations, sixteen convolution states of a generation step; every array on a
-    # boundary of 256 bytes
-    fixed = 2 * seg * c_l + 17 * c_s + 256 * 16
+    # a cell's kept tensors, the block's own scratch, four buffers of activations, the adjoints of all layers, sixteen convolution
+    # states of a generation step; every array on a boundary of 256 bytes
+    fixed = 4 * seg * c_l + 17 * c_s + 256 * (4 * nl + 16)
     assert 0 < need(H, L, seg, nl, l, **more) <= block_need(sh, False) + fixed
-    assert len({need(H, k * seg, seg, nl, l, **more) for k in (16, 17, 64, 1000)}) == 1       # not the length of the sequence
+    assert 0 < need(H, L, seg, nl, l, back=True, **more) <= l * seg * c_grid + max(block_need(sh, b) for b in (False, True)) + 2 * nl * c_adj + fixed
+    for back in (False, True):       # and nothing else: not the length of the sequence
+        assert len({need(H, k * seg, seg, nl, l, back=back, **more) for k in (16, 17, 64, 1000)}) == 1
+
+
+@pytest.mark.parametrize("H", [24, 80])
+@pytest.mark.parametrize("nl", [24, 64])
+def test_what_the_planner_chooses_fits_what_it_says(H, nl):
+    """Checkpoints and scratch of the grids that magc_plan returns, for the least memory and for budgets above it, against its
+    own total.  The model has no term for the state adjoints of the layers, nor for the buffers that do not grow with the
+    interval, and its scratch term is linear in the segment: what a block really takes at that segment is added."""
+    c_l, c_grid, c_s, c_adj = sizes(H)
+    c_state = block_need(_stack(H, 4096, 4096), True) // 4096
+    for S in (4096, 16384, 65536, 262144):
+        plan = lambda budget: pk.magc_plan(nl, S, c_l, c_s, c_grid, c_state, s_multiple=256, budget=budget, integer_counts=True)  # noqa: E731
+        least = plan(0.0)[1]["m_total"]
+        for times in (0.0, 1.5, 3.0):
+            rc, p = plan(times * least)
+            assert rc == 0
+            l, s = p["l"], p["s"]
+            kept = nl * -(-S // s) * c_s + (-(-nl // l) - 1) * S * c_l
+            scratch = max(need(H, S, s, nl, l, back=b) for b in (False, True))
+            short = max(0, max(block_need(_stack(H, n, n), True) for n in {s, S % s or s}) - s * c_state)
+            assert kept + scratch <= p["m_total"] + short + 2 * nl * c_adj + 4 * s * c_l + 17 * c_s + 65536, (S, times, l, s)
 
 
 @pytest.mark.parametrize("dims", [dict(Q=64), dict(Q=128), dict(Q=256), dict(Q=128, G=2), dict(Q=256, hd=16, n=16)])
@@ -54,8 +79,9 @@ def test_scratch_for_the_longest_sequence_serves_shorter_ones(dims):
     Q = dims["Q"]
     for H in (8, 24, 32, 80):
         for nseg in (1, 2, 4):
-            got = [need(H, L, nseg * Q, **dims) for L in range(Q // 2, 48 * Q, Q // 2)]
-            assert min(got) > 0 and got == sorted(got), (H, nseg)
+            for back in (False, True):
+                got = [need(H, L, nseg * Q, back=back, **dims) for L in range(Q // 2, 48 * Q, Q // 2)]
+                assert min(got) > 0 and got == sorted(got), (H, nseg, back)
 
 
 def uses(limit, *a, keep, **k):
