@@ -113,9 +113,10 @@ HeadSlices part_slices(const Dims& d, bool mfma, int wg_target) {
     return mfma ? HeadSlices(d, d.hpg, bg * 2, wg_target) : HeadSlices(d, GENERIC_SLICES, bg * 2 * nt * nn, 256);
 }
 // Room for the partial sums of dG of a span, in bf16 chunks of scores: one per head slice, two where they are fp32 (generic
-// kernels, and fit_splits: of at most half a round of slices, at chunks of 256 mostly no more than the general rule's bf16 ones).
+// kernels, and fit_splits: of at most half a round of slices, at chunks of 256 mostly no more than the general rule's bf16 ones;
+// at chunks of 128, where a round is twice as many, there is room for those of any one round).
 int64_t dg_places(const Dims& d, bool mfma, int wg_target) {
-    const int64_t bg = d.Bt * d.G, all = bg * d.nc * d.hpg;
+    const int64_t bg = d.Bt * d.G, all = 2 * bg * d.nc * d.hpg;
     const int64_t n = bg * dg_slices(d, mfma, wg_target).slots(d.nc) * (mfma && !d.dg_f32 ? 1 : 2);
     if (!mfma || d.Q != 128 || wg_target < 256 || n >= 512) return n;
     return all < 512 ? (n > all ? n : all) : 512;
@@ -129,10 +130,12 @@ int64_t dg_places(const Dims& d, bool mfma, int wg_target) {
 // and add up.  Otherwise every pass gets a workgroup per compute unit and the three alternate.  Slices (dx, dG, head sums) by
 // this rule, 32 chunks of 24 heads: (8, 8, 4) -> (3, 3, 1): 75.2 -> 63.6 us, and the finalisation 19.0 -> 13.6; 16 chunks of
 // 80 heads, (16, 16, 8) -> (5, 5, 2): 114 -> 103 and 19.1 -> 14.2.
-// The slices' partial sums of dG are bf16 where there are as many as before, and rounded once more when they have been added
-// up.  Sums of two to seven such numbers often lie halfway between two others, so that fewer slices alone take dB and dC
-// further from 64 bits (eight -> three of 24 heads: 2.90e-3 -> 2.93e-3).  Fewer slices are therefore kept in fp32, 2.41e-3, at
-// 2 us of 118 for 8192 tokens of 24 heads; likewise in a span that lanes would cut into more slices (plan_dims).
+// The slices' partial sums of dG are bf16 in the general rule, and rounded once more when they have been added up.  Sums of two
+// to seven such numbers often lie halfway between two others, so that fewer slices alone take dB and dC further from 64 bits
+// (eight -> three of 24 heads: 2.90e-3 -> 2.93e-3).  In one round they are therefore fp32 wherever there is room, 2.41e-3, at 2 us
+// of 118 for 8192 tokens of 24 heads (chunks of 128: 1.5 of 67-79, 1920 tokens of 24 heads and 2944 of 8), and of two choices that
+// end together the one with fp32 sums is taken (31 chunks of 48 heads, forward and backward: 284 -> 271); bf16 only for as many
+// slices as the general rule's.  Likewise fp32 in a span that lanes would cut into more slices (plan_dims).
 void fit_splits(SegParams& sp, const Dims& d, bool mfma, int wg_target) {
     const int64_t nc = sp.nc;
     const int a0 = dg_slices(d, mfma, wg_target).split(nc), p0 = part_slices(d, mfma, wg_target).split(nc);
@@ -155,10 +158,10 @@ void fit_splits(SegParams& sp, const Dims& d, bool mfma, int wg_target) {
     const int64_t work = a0 * (one(0, a0) + one(1, a0)) + 2 * p0 * one(2, p0);
     int64_t least = base * work / units + longest(a0, p0) / 2;
     for (int a = 1; a <= a0 && base * 2 * (a + 1) <= units; ++a) {
-        const bool f32 = d.dg_f32 || (a > 1 && a < a0);
-        if (base * a * (f32 ? 2 : 1) > places) continue;
+        const bool f32 = d.dg_f32 || (a > 1 && base * a * 2 <= places);
+        if (!f32 && ((a > 1 && a < a0) || base * a > places)) continue;
         for (int p = 1; p <= p0 && base * 2 * (a + p) <= units; ++p)
-            if (longest(a, p) < least)
+            if (longest(a, p) < least || (longest(a, p) == least && f32 && !sp.dg_f32))
                 least = longest(a, p), sp.dual_split = sp.dg_split = a, sp.part_split = p, sp.dg_f32 = f32;
     }
 }

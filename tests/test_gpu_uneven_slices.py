@@ -22,3 +22,13 @@ def test_slices_of_two_lengths(case):
 @pytest.mark.parametrize("case", [(1, 3333, 64, 1, 256, 4096), (1, 32 * 256 - 9, 23, 1, 256, 8192)])
 def test_their_partial_sums_are_rounded_once(case):
     check_rounding(case)
+
+
+@pytest.mark.parametrize("case", [
+    # Bt, L, H, G, Q, segment
+    (1, 15 * 128, 24, 1, 128, 4096),   # twelve slices, as many as the general rule's, where eight are no longer in the launch
+    (1, 23 * 128, 8, 1, 128, 1024),    # a slice for every head
+    (1, 31 * 256, 48, 1, 256, 4096),   # one round that ends with the general rule's launch
+])
+def test_one_round_keeps_its_partial_sums_in_fp32(case):
+    check_rounding(case)
