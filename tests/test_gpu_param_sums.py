@@ -47,6 +47,15 @@ def test_the_last_chunk_sums(case):
     assert bool(((first["dD"].double() - prod.sum((0, 1, 3))).abs() <= bound).all())
 
 
+@pytest.mark.parametrize("case", [
+    ("bf16", 1, 600 * 64 + 7, 2, 64, 128, 64, 8192),   # 601 chunks: eight loads a lane in flight, and the rest
+    ("bf16", 1, 512 * 64, 1, 64, 128, 64, 4096),       # exactly eight
+    ("f32", 1, 2051 * 8 + 3, 1, 4, 4, 8, 4096),        # 2052 chunks, 256 threads
+])
+def test_more_chunks_than_loads_in_flight(case):
+    test_the_last_chunk_sums(case)
+
+
 def test_stack_with_less_than_a_line_of_state_per_head():
     """The counts of the heads lie in what one head's state of 2 x 3 elements leaves room for."""
     cfg = synth.SSDConfig("stack", "f32", 2, 96, 5, 2, 3, 1, 16, 32, nlayers=2, index=98)
