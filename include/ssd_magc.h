@@ -396,8 +396,8 @@ typedef struct {
     int32_t nlayers, layer_interval;
 } magc_blockstack_shape_t;
 size_t magc_blockstack_workspace_bytes(const magc_blockstack_shape_t* shape, int32_t is_backward);
-/* What magc_blockstack_fwd (keeps_checkpoints != 0) or magc_blockstack_infer (0) uses of a workspace of `limit` bytes, or of the
- * least that they take if that is more.  0: an invalid shape. */
+/* What magc_blockstack_fwd (keeps_checkpoints != 0) or magc_blockstack_infer (0), with x0 and out on 16-byte boundaries, uses of a
+ * workspace of `limit` bytes, or of the least that they take if that is more.  0: an invalid shape. */
 size_t magc_blockstack_pass_bytes(const magc_blockstack_shape_t* shape, int32_t keeps_checkpoints, size_t limit);
 int magc_blockstack_fwd(const magc_blockstack_shape_t* shape, const magc_block_params_t* params, const void* x0, void* out,
                         void* l_ckpt, float* ssm_ckpt, void* conv_ckpt, void* workspace, size_t workspace_bytes,
@@ -414,9 +414,9 @@ int magc_blockstack_bwd(const magc_blockstack_shape_t* shape, const magc_block_p
  *   ssm_state [nlayers, H, P, N] fp32 and conv_state [nlayers, 3, d_inner + 2 G N] bf16,
  * which the call reads (fresh != 0: takes as zeros without reading them) and replaces by the states behind its
  * last token: a prompt of any length (walked through all layers in equal pieces of as many tokens as the workspace
- * has room for, up to 16384 x 10576 elements of the input projection's output; in the scratch of a segment that is a third
- * more than a segment at least), then calls of one or a few tokens, continue one sequence.  x0, out [block.seqlen, d_model] bf16 (may be the same
- * buffer); layer_interval is ignored (give any value in 1 .. nlayers).
+ * has room for, up to 16384 x 10576 elements of the input projection's output; in the scratch of a segment about half as
+ * many again as block.segment), then calls of one or a few tokens, continue one sequence.  x0, out [block.seqlen, d_model]
+ * bf16 (may be the same buffer); layer_interval is ignored (give any value in 1 .. nlayers).
  *   workspace: magc_blockstack_workspace_bytes(shape, 0) bytes, 256-byte aligned
  * Enqueued on hip_stream in order, nothing allocated, no other stream used.  Errors as for magc_blockstack_fwd.
  */
