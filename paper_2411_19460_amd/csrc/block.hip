@@ -903,6 +903,8 @@ StackWs stack_layout(const magc_blockstack_shape_t* sh, const StackDims& d, bool
 // One segment a launch -> 4096, 8192, 16384 rows (ms, forward, nothing kept, four blocks):
 //   6001 tokens, 80 heads, segment 4096: 2.73 -> 2.71, 2.23, 2.23;    13001, 80 heads, segment 2048: 7.0 -> 5.6, 5.2, 4.9
 //   30001 tokens, 24 heads, segment 4096:  5.3 -> 3.7, 3.6, 3.3
+// and in the scratch of a segment of 4096: 6001 tokens of 80 heads 2.76 -> 2.26 (one piece), 65536 tokens through eight blocks 52.8 ->
+// 47.0 (pieces of 6144).
 constexpr int64_t KEEP_WORK = (int64_t)8192 * 10576, INFER_WORK = 2 * KEEP_WORK;
 struct Pass {
     magc_blockstack_shape_t shape, few;  // the stack with a piece as its segment; few: of at most FEW_ROWS tokens, which take the
@@ -1039,10 +1041,9 @@ extern "C" int magc_blockstack_fwd(const magc_blockstack_shape_t* sh, const magc
             BLK_TRY(block_fwd(&c, &params[j], cur, ssm_in, conv_in, y, nullptr, nullptr, ssm_out, conv_out, ws + w.inner, w.inner_bytes,
                               false, st, normed, several ? &inner : nullptr, p.lean));
             // the input of the next layer: the stack's output, a layer-axis checkpoint, or a buffer
-            char* nxt = j + 1 == d.NL ? out_rows
-                                      : (j + 1) % d.l == 0 ? (char*)l_ckpt + ((size_t)((j + 1) / d.l - 1) * d.b.L + t0) * row
-                                      : p.lean         ? stream
-                                                       : y;
+            char* nxt = p.lean ? stream : y;
+            if (j + 1 == d.NL) nxt = out_rows;
+            else if ((j + 1) % d.l == 0) nxt = (char*)l_ckpt + ((size_t)((j + 1) / d.l - 1) * d.b.L + t0) * row;
             BLK_TRY(residual(dc, c.eps, nxt, cur, y, rows, j + 1 < d.NL ? params[j + 1].pre_norm_w : nullptr, un, nullptr, nullptr, 0, &normed, st));
             cur = nxt;
         }
