@@ -18,11 +18,6 @@ struct DdtIn {
     float g, s, f, d;
 };
 
-static __device__ __forceinline__ float wave_sum(float v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 // W waves per (chunk c, head h, batch b), of one workgroup: 4, for chunks of up to 1024 tokens, or 1 for up to 256 (no barrier
 // then: the waves of the workgroup have chunks of their own).  load(offset of the chunk and head + i, i) returns what
 // the passes before left for token i; store(index into ddt, value) writes one element of ddt in its storage type.
@@ -58,16 +53,12 @@ __device__ __forceinline__ void ddt_finalize_body(const SegParams& sp, DdtLds* l
         f[e] = v.f;
         d[e] = v.d;
     }
-    float incl = run;
-    for (int off = 1; off < 64; off <<= 1) {
-        const float v = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += v;
-    }
+    const float incl = wave_prefix(run);
     const float* tp = sp.tail_part + (((int64_t)b * sp.H + h) * sp.nc + c) * sp.nslice;
     float tail = 0.f;
     for (int k = tid; k < sp.nslice; k += T) tail += tp[k];
-    tail = wave_sum(tail);
-    ssum = wave_sum(ssum);
+    tail = wave_total(tail);
+    ssum = wave_total(ssum);
     if constexpr (W > 1) {
         if (lane == 63) {
             L.tot[w] = incl;
@@ -93,8 +84,8 @@ __device__ __forceinline__ void ddt_finalize_body(const SegParams& sp, DdtLds* l
         }
     }
     auto param_sums = [&] {
-        pa = wave_sum(pa);
-        pd = wave_sum(pd);
+        pa = wave_total(pa);
+        pd = wave_total(pd);
         if constexpr (W > 1) {
             if (lane == 0) {
                 L.pa[w] = pa;

@@ -22,12 +22,17 @@
 // All contractions run on v_mfma_f32_32x32x2_f32: full fp32 products and sums at twice the rate of plain FMAs, and
 // with one LDS operand read per four of them instead of five reads per four FMAs, which is what bounded the tiles
 // this replaces.  A workgroup of four waves owns a 64 x 64 tile; K goes by in steps of 32, staged through two LDS
-// buffers (one barrier a step) as [row][k] with the next step's global loads in flight during the MFMAs.  The weights
+// buffers (one barrier a step) with two steps of global loads in flight, 16 bytes a lane (chain()).  The weights
 // (decays, dt, masks) are applied between the load and the LDS store.  Sums over the heads of a group are cut into head
-// slices so that a sequence of a few chunks still fills the machine (1999 tokens of 24 heads in two segments, forward +
-// backward: 1340 us with FMA tiles, serial heads and launches of their own for every segment, 253 us now).  Small problems are
-// bound by launches: three forward, five backward here for segments that share them (512 tokens of 4 heads in two segments: 216
-// us with 14 for each segment, 64 us now).
+// slices so that a sequence of a few chunks still fills the machine.  1999 tokens of 24 heads in two segments, forward +
+// backward: 1340 us with FMA tiles, serial heads and launches of their own for every segment, 229 with tiles loaded element by
+// element across the contraction and row sums by lane shuffles, 170 now: 28 + 11.5 + 16 of them are the MFMAs of the walk, the
+// output and the states at their rate, beside as many vector instructions.  Small problems are bound by launches and what a
+// kernel's first loads take: three forward, four backward (512 tokens of 4 heads in two segments: 216 us with 14 for each segment,
+// 62 before, 46 now).
+#include <numeric>
+#include <type_traits>
+
 #include "ddt_finalize.h"
 #include "ssd_internal.h"
 
@@ -41,21 +46,12 @@ struct IO<float> {
     static __device__ __forceinline__ float ld(const void* p, size_t i) { return ((const float*)p)[i]; }
     static __device__ __forceinline__ float round(float v) { return v; }
     static __device__ __forceinline__ void st(void* p, int64_t i, float v) { ((float*)p)[i] = v; }
-    static __device__ __forceinline__ void ld4(float (&v)[4], const void* p, size_t i) {  // i a multiple of 4, 16-byte aligned
-        const float4 q = *(const float4*)((const float*)p + i);
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-    }
 };
 template <>
 struct IO<bf16_t> {
     static __device__ __forceinline__ float ld(const void* p, size_t i) { return bf16_to_float(((const bf16_t*)p)[i]); }
     static __device__ __forceinline__ float round(float v) { return bf16_to_float(float_to_bf16(v)); }
     static __device__ __forceinline__ void st(void* p, int64_t i, float v) { ((bf16_t*)p)[i] = float_to_bf16(v); }
-    static __device__ __forceinline__ void ld4(float (&v)[4], const void* p, size_t i) {
-        const uint2 q = *(const uint2*)((const bf16_t*)p + i);
-        v[0] = __builtin_bit_cast(float, q.x << 16); v[1] = __builtin_bit_cast(float, q.x & 0xffff0000u);
-        v[2] = __builtin_bit_cast(float, q.y << 16); v[3] = __builtin_bit_cast(float, q.y & 0xffff0000u);
-    }
 };
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -63,118 +59,142 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // exp of a difference of sums of dt A: at most 0 but for rounding.  A NaN stays one (fminf would take the number).
 __device__ __forceinline__ float decay(float v) { return expf(v > 0.f ? 0.f : v); }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 constexpr int NTHREADS = 256;
 constexpr int TM = 64;   // tile edge
 constexpr int TK = 32;   // contraction step
-constexpr int KP = 36;   // floats per LDS row (32 + 4 pad: 16-byte aligned, and eight rows cover the banks)
 constexpr int QMAX = 1024;
 constexpr int SLICES = GENERIC_SLICES;
 static_assert(SLICES == 4, "the sums over slices are written out");
 
+// An operand of a contraction step in LDS, laid out as it lies in memory: [64 rows][32 k] where k is contiguous there (KC),
+// else [32 k][64 rows].  The pitches keep 16-byte rows aligned and the reads of a half wave in distinct banks, and both come to
+// the same size, so that a buffer serves either.
+constexpr int KPITCH = 36, RPITCH = 72, OPERAND = TM * KPITCH;
+static_assert(OPERAND == TK * RPITCH, "one buffer");
+
 struct Tiles {
-    float a[2][TM][KP], b[2][TM][KP];
+    float a[2][OPERAND], b[2][OPERAND];
 };
 // LDS of the kernels that also keep per-token arrays of the chunk: the tiles, then `n` floats (sized at launch, so that
 // four workgroups fit a compute unit up to chunks of 256 tokens).
 inline size_t lds_bytes(int n) { return sizeof(Tiles) + (size_t)n * sizeof(float); }
 extern __shared__ __attribute__((aligned(16))) char dyn_lds[];
 
-// Four consecutive k (from k0 + k) of row row0 + r, k contiguous in memory; outside [0, rows) x [0, ks) reads as zero.
-// The address is a wave-uniform base plus a 32-bit offset inside the tile, and out-of-range indices are clamped and
-// their values dropped: no branches, so that a tile's loads leave together.  row0 < rows and k0 < ks.
+// The part of a matrix that a contraction step takes, from its first element on: `outer` rows `stride` bytes apart (rows of a
+// k-contiguous operand, else k), `inner` contiguous elements of each.  A buffer descriptor, wave-uniform: whatever lies outside
+// reads as zero, without branches or clamped indices, so that a step's loads leave together.  (64 rows of 65535 heads of 256
+// channels of fp32 stay below 4 GB.)
+struct Part {
+    const void* p;
+    uint32_t stride;
+    int outer, inner;
+};
 template <typename T>
-__device__ __forceinline__ void ld_k4(float (&v)[4], const void* p, int64_t base, int64_t row_stride, int row0, int r, int k0, int k, int rows,
-                                      int ks, bool vec) {
-    const T* u = (const T*)p + (base + row0 * row_stride + k0);
-    const int rl = rows - row0 - 1, kl = ks - k0;
-    if (vec && rl >= TM - 1 && kl >= TK) {  // uniform: a tile inside the matrix
-        IO<T>::ld4(v, u, (uint32_t)r * (uint32_t)row_stride + (uint32_t)k);
-        return;
-    }
-    const uint32_t o = (uint32_t)(r < rl ? r : rl) * (uint32_t)row_stride;
-    if (vec) {  // ks is a multiple of 4 and rows are 4-element aligned
-        IO<T>::ld4(v, u, o + (uint32_t)(k < kl ? k : 0));
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = r <= rl && k < kl ? v[e] : 0.f;
+__device__ __forceinline__ Part part_of(const void* p, int64_t first, int64_t stride, int outer, int inner) {
+    return {(const T*)p + first, (uint32_t)stride * (uint32_t)sizeof(T), outer, inner};
+}
+// (By value: a cast of a vector's element in place reads the vector's first.)
+__device__ __forceinline__ uint32_t bits_of(float v) { return __builtin_bit_cast(uint32_t, v); }
+__device__ __forceinline__ float float_of(uint32_t v) { return __builtin_bit_cast(float, v); }
+// Four elements as they come from memory: fp32, or bf16 in two registers (VEC) or in the low halves of four.  Nothing is done to
+// them before they are put down: that would wait for them.
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// VEC: `inner` and the elements in front of every row are multiples of four.
+template <typename T, bool VEC>
+__device__ __forceinline__ u32x4 fetch4(__amdgpu_buffer_rsrc_t r, uint32_t bytes, uint32_t row, int lo, int inner) {
+    u32x4 v;
+    if constexpr (VEC) {
+        const uint32_t o = lo < inner ? row + (uint32_t)lo * (uint32_t)sizeof(T) : bytes;
+        if constexpr (sizeof(T) == 4) {
+            v = __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0);
+        } else {
+            const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(r, o, 0, 0);
+            v[0] = q[0];
+            v[1] = q[1];
+        }
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float q = IO<T>::ld(u, o + (uint32_t)(k + e < kl ? k + e : 0));
-            v[e] = r <= rl && k + e < kl ? q : 0.f;
+            const uint32_t o = lo + e < inner ? row + (uint32_t)(lo + e) * (uint32_t)sizeof(T) : bytes;
+            if constexpr (sizeof(T) == 4) v[e] = __builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0);
+            else v[e] = __builtin_amdgcn_raw_buffer_load_b16(r, o, 0, 0);
         }
     }
+    return v;
 }
-// The same with the row index contiguous in memory.
-template <typename T>
-__device__ __forceinline__ void ld_r4(float (&v)[4], const void* p, int64_t base, int64_t k_stride, int r, int k0, int k, int rows, int ks) {
-    const T* u = (const T*)p + (base + k0 * k_stride);
-    const int kl = ks - k0;
-    if (rows >= TM && kl >= TK) {  // uniform
-        const uint32_t o = (uint32_t)k * (uint32_t)k_stride + (uint32_t)r;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = IO<T>::ld(u, o + (uint32_t)e * (uint32_t)k_stride);
-        return;
-    }
-    const uint32_t row = (uint32_t)(r < rows ? r : 0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float q = IO<T>::ld(u, row + (uint32_t)(k + e < kl ? k + e : 0) * (uint32_t)k_stride);
-        v[e] = r < rows && k + e < kl ? q : 0.f;
-    }
+template <typename T, bool VEC>
+__device__ __forceinline__ f32x4 unpack(const u32x4& v) {
+    if constexpr (sizeof(T) == 4) return __builtin_bit_cast(f32x4, v);
+    else if constexpr (VEC) return f32x4{float_of(v[0] << 16), float_of(v[0] & 0xffff0000u), float_of(v[1] << 16), float_of(v[1] & 0xffff0000u)};
+    else return f32x4{float_of(v[0] << 16), float_of(v[1] << 16), float_of(v[2] << 16), float_of(v[3] << 16)};
 }
 
-// The thread index as the optimiser cannot see through: what is derived from it is formed anew in every turn of a loop
+// A value (the thread index) that the optimiser cannot see through: what is derived from it is formed anew in every turn of a loop
 // instead of being kept in registers across it (half of the walks' registers otherwise).
-__device__ __forceinline__ int opaque_tid() {
-    int t = threadIdx.x;
+__device__ __forceinline__ int opaque(int t) {
     asm volatile("" : "+v"(t));
     return t;
 }
 
-// Where a thread's two groups of four k lie in a [64][32] tile: KC = k contiguous in memory, else the row index is
-// (lanes run along what is contiguous).
+// Where a thread's two pieces of four elements lie: row hi of 32, elements lo .. lo + 3, and 32 rows (k-contiguous operand) or 32
+// elements further on.
+__device__ __forceinline__ int piece_hi(int tid) { return tid >> 3; }
+__device__ __forceinline__ int piece_lo(int tid) { return (tid & 7) * 4; }
+
+// (kc as an argument, not a template one: where the products of a chain differ in it, the loads stay outside of branches.)
+template <typename T, bool VEC>
+__device__ __forceinline__ void fetch(u32x4 (&r)[2], bool kc, const Part& s, bool live) {
+    const int tid = opaque(threadIdx.x), lo = piece_lo(tid);
+    const uint32_t row = (uint32_t)piece_hi(tid) * s.stride, bytes = live ? (uint32_t)s.outer * s.stride : 0u;
+    // uniform by construction; said again, or a part that the compiler has in vector registers makes it loop over the lanes' values
+    const uint64_t p = (uint64_t)s.p;
+    const uint32_t a0 = __builtin_amdgcn_readfirstlane((uint32_t)p), a1 = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)((uint64_t)a1 << 32 | a0), 0, bytes, 0x00020000);
+    r[0] = fetch4<T, VEC>(rs, bytes, row, lo, s.inner);
+    r[1] = fetch4<T, VEC>(rs, bytes, row + (kc ? 32u * s.stride : 0u), lo + (kc ? 0 : 32), s.inner);
+}
+// wt(v, hi, lo, piece) weights a piece in place on its way to LDS.
+template <typename T, bool VEC, class W>
+__device__ __forceinline__ void put(const u32x4 (&r)[2], bool kc, float* L, W wt) {
+    const int tid = opaque(threadIdx.x), hi = piece_hi(tid), lo = piece_lo(tid);
+    float* at = L + hi * (kc ? KPITCH : RPITCH) + lo;
+    f32x4 v = unpack<T, VEC>(r[0]);
+    wt(v, hi, lo, 0);
+    *(f32x4*)at = v;
+    v = unpack<T, VEC>(r[1]);
+    wt(v, hi, lo, 1);
+    *(f32x4*)(at + (kc ? 32 * KPITCH : 32)) = v;
+}
+// Four consecutive values of a per-token array (VEC: 16-byte aligned).
+template <bool VEC>
+__device__ __forceinline__ f32x4 ld4(const float* p) {
+    if (VEC) return *(const f32x4*)p;
+    return f32x4{p[0], p[1], p[2], p[3]};
+}
+struct NoWeight {
+    __device__ __forceinline__ void operator()(f32x4&, int, int, int) const {}
+};
+
+// acc += the wave's 32 x 32 quadrant of a 64 x 32 by 32 x 64 product (rows 32 (w / 2) .. of A, columns 32 (w % 2) .. of B).  Lane
+// half h takes k = 8 j + 4 h .. + 3 of each row; the e-th MFMA contracts k = 8 j + e and 8 j + 4 + e.
 template <bool KC>
-__device__ __forceinline__ void place(int tid, int s, int& row, int& k) {
-    const int t = tid + NTHREADS * s;
-    row = KC ? t >> 3 : t & 63;
-    k = KC ? (t & 7) * 4 : (t >> 6) * 4;
+__device__ __forceinline__ f32x4 operand4(const float* L, int row, int k) {
+    if (KC) return *(const f32x4*)(L + row * KPITCH + k);
+    const float* p = L + k * RPITCH + row;
+    return f32x4{p[0], p[RPITCH], p[2 * RPITCH], p[3 * RPITCH]};
 }
-
-template <bool KC, class F>
-__device__ __forceinline__ void tile_load(float (&r)[2][4], int k0, F ld) {
-    const int tid = opaque_tid();
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        int row, k;
-        place<KC>(tid, s, row, k);
-        ld(r[s], row, k, k0);
-    }
-}
-template <bool KC, class W>
-__device__ __forceinline__ void tile_store(float (&r)[2][4], float (*L)[KP], int k0, W wt) {
-    const int tid = opaque_tid();
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        int row, k;
-        place<KC>(tid, s, row, k);
-        wt(r[s], row, k0 + k);
-        *(float4*)(&L[row][k]) = make_float4(r[s][0], r[s][1], r[s][2], r[s][3]);
-    }
-}
-
-// acc += the wave's 32 x 32 quadrant of a [64][32] x [64][32]^T product.  Lane half h takes k = 8 j + 4 h .. + 3 of each
-// row with one 16-byte read; the e-th MFMA contracts k = 8 j + e and 8 j + 4 + e.
-__device__ __forceinline__ void tile_mma(f32x16& acc, const float (*A)[KP], const float (*B)[KP]) {
+template <bool AKC, bool BKC>
+__device__ __forceinline__ void tile_mma(f32x16& acc, const float* A, const float* B) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, half = lane >> 5;
-    const float* pa = &A[32 * (w >> 1) + (lane & 31)][4 * half];
-    const float* pb = &B[32 * (w & 1) + (lane & 31)][4 * half];
+    const int ra = 32 * (w >> 1) + (lane & 31), rb = 32 * (w & 1) + (lane & 31);
 #pragma unroll
     for (int j = 0; j < TK / 8; ++j) {
-        const float4 a = *(const float4*)(pa + 8 * j), b = *(const float4*)(pb + 8 * j);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
+        const f32x4 a = operand4<AKC>(A, ra, 8 * j + 4 * half), b = operand4<BKC>(B, rb, 8 * j + 4 * half);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
     }
 }
 
@@ -192,67 +212,81 @@ __device__ __forceinline__ f32x16 zero_acc() {
     return z;
 }
 
-struct Staged {
-    float a[2][4], b[2][4];
-};
-
-// acc += A B^T over k in [kbeg, kend), kbeg a multiple of 4.  la / lb load four k of a row (zeros outside), wa / wb then
-// weight them in place.  `buf` alternates between the LDS buffers across calls: one barrier per step suffices.
-// between() runs once the first loads are under way: what fills the arrays the weights are read from (its barriers
-// included) costs no round trip to memory of its own.
-template <bool AKC, bool BKC, class LA, class WA, class LB, class WB, class FB>
-__device__ __forceinline__ void tile_gemm(f32x16& acc, int kbeg, int kend, LA la, WA wa, LB lb, WB wb, Tiles& L, int& buf, FB between) {
-    Staged R0, R1;  // two steps of loads in flight
-    auto load = [&](Staged& R, int k0) {
-        tile_load<AKC>(R.a, k0, la);
-        tile_load<BKC>(R.b, k0, lb);
-    };
-    auto step = [&](Staged& R, int k0) {
-        tile_store<AKC>(R.a, L.a[buf], k0, wa);
-        tile_store<BKC>(R.b, L.b[buf], k0, wb);
+// A chain of contraction steps: load(stage, s, live) asks for step s, put(stage, s, la, lb) weights it and leaves it in LDS,
+// use(s, la, lb) contracts it.  AHEAD steps are on their way from memory while one is contracted, and a tile's products -- through
+// the state, with other tokens, on the diagonal -- are one chain, so that it fills once.  A step beyond the end is asked for like the
+// others, with live = false: nothing is fetched, but the count of loads in flight stays known, where a branch around them would have
+// every step wait for all of them.  (Two steps in flight as it seemed, with such branches, and a chain for each product, k_chunk_out
+// took 35.7 us of 1999 tokens of 24 heads and the backward walk 110: now 30 and 78, of which their MFMAs alone are 11.5 and 28.  Three
+// steps in flight are no faster, and the longer code costs small problems 2 us of 10.)
+// Two LDS buffers: one barrier a step.  between() runs once the first loads are under way: what fills the arrays the weights are
+// read from (its barriers included) costs no round trip to memory of its own.
+template <int AHEAD, class Stage, class LD, class PUT, class USE, class FB>
+__device__ __forceinline__ void chain(int steps, Tiles& L, LD load, PUT put_, USE use, FB between) {
+    Stage R[AHEAD];
+    int buf = 0;
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a) load(R[a], a, a < steps);
+    between();
+    auto step = [&](int a, int s) {
+        put_(R[a], s, L.a[buf], L.b[buf]);
         __syncthreads();
-        if (k0 + 2 * TK < kend) load(R, k0 + 2 * TK);
-        tile_mma(acc, L.a[buf], L.b[buf]);
+        load(R[a], s + AHEAD, s + AHEAD < steps);
+        use(s, L.a[buf], L.b[buf]);
         buf ^= 1;
     };
-    if (kbeg < kend) load(R0, kbeg);
-    if (kbeg + TK < kend) load(R1, kbeg + TK);
-    between();
-    for (int k0 = kbeg; k0 < kend; k0 += 2 * TK) {
-        step(R0, k0);
-        if (k0 + TK < kend) step(R1, k0 + TK);
+    int s0 = 0;
+    for (; s0 + AHEAD <= steps; s0 += AHEAD) {  // no way out in the middle: the same for the count of loads
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a) step(a, s0 + a);
     }
+#pragma unroll
+    for (int a = 0; a < AHEAD - 1; ++a)
+        if (s0 + a < steps) step(a, s0 + a);
 }
-template <bool AKC, bool BKC, class LA, class WA, class LB, class WB>
-__device__ __forceinline__ void tile_gemm(f32x16& acc, int kbeg, int kend, LA la, WA wa, LB lb, WB wb, Tiles& L, int& buf) {
-    tile_gemm<AKC, BKC>(acc, kbeg, kend, la, wa, lb, wb, L, buf, [] {});
-}
-struct NoWeight {
-    __device__ __forceinline__ void operator()(float (&)[4], int, int) const {}
+struct Staged {
+    u32x4 a[2], b[2];
 };
+__device__ __forceinline__ int least(int a, int b) { return a < b ? a : b; }
 
+// A lane's value of v from the lane that CTRL permutes it with.
+template <int CTRL>
+__device__ __forceinline__ float from_lane(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
 // Sum of each of the 16 registers over the 32 lanes of a half wave, by recursive halving; lane l (of the half) ends
-// with the sum of register l / 2.
+// with the sum of register l / 2.  On the exchanges of the vector ALUs: rows of sixteen lanes swapped between two registers, then
+// inside the rows (by lane shuffles through LDS it was 550 instructions, a quarter of the dG walk).
 __device__ __forceinline__ float row_sums(const f32x16& v, int lane) {
     float a[8], b[4], c[2];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-        const float keep = lane & 16 ? v[r + 8] : v[r], give = lane & 16 ? v[r] : v[r + 8];
-        a[r] = keep + __shfl_xor(give, 16, 64);
+        const u32x2 q = __builtin_amdgcn_permlane16_swap(bits_of(v[r]), bits_of(v[r + 8]), false, false);
+        a[r] = float_of(q[0]) + float_of(q[1]);
     }
+    const bool h8 = lane & 8, h4 = lane & 4, h2 = lane & 2;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const float keep = lane & 8 ? a[r + 4] : a[r], give = lane & 8 ? a[r] : a[r + 4];
-        b[r] = keep + __shfl_xor(give, 8, 64);
-    }
+    for (int r = 0; r < 4; ++r) b[r] = (h8 ? a[r + 4] : a[r]) + from_lane<0x140>(h8 ? a[r] : a[r + 4]);  // row_mirror
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const float keep = lane & 4 ? b[r + 2] : b[r], give = lane & 4 ? b[r] : b[r + 2];
-        c[r] = keep + __shfl_xor(give, 4, 64);
+    for (int r = 0; r < 2; ++r) c[r] = (h4 ? b[r + 2] : b[r]) + from_lane<0x141>(h4 ? b[r] : b[r + 2]);  // row_half_mirror
+    const float d = (h2 ? c[1] : c[0]) + from_lane<0x4E>(h2 ? c[0] : c[1]);                              // quad_perm 2 3 0 1
+    return d + from_lane<0xB1>(d);                                                                       // quad_perm 1 0 3 2
+}
+
+// Four values each of a per-row array of a tile, for this lane's accumulator registers.
+__device__ __forceinline__ void rows_of(const float* L, float (&v)[16]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const f32x4 t = *(const f32x4*)(L + tile_row(4 * q));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * q + e] = t[e];
     }
-    const float keep = lane & 2 ? c[1] : c[0], give = lane & 2 ? c[0] : c[1];
-    const float d = keep + __shfl_xor(give, 2, 64);
-    return d + __shfl_xor(d, 1, 64);
+}
+__device__ __forceinline__ void scale_rows(f32x16& acc, const float* L) {
+    float f[16];
+    rows_of(L, f);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] *= f[r];
 }
 
 __global__ void k_fill_zero(float* p, size_t n) {
@@ -267,14 +301,26 @@ __global__ void k_copy_f32(float* dst, const float* src, size_t n) {
     for (; i < n; i += stride) dst[i] = src[i];
 }
 
-// Which 16-byte loads along the contiguous dimension are possible.
-struct Vec {
-    bool x, bc;  // rows of x, dY (and dx, y are stored by element); rows of B, C and the states
+// Workgroups are dealt to the eight XCDs in turn, and each XCD has a cache (4 MB) of its own.  The work of a launch is listed chunk by
+// chunk (and slice of heads by slice), and every XCD takes a contiguous part of the list: what works on the same rows, scores and
+// states finds them in one cache.
+__device__ __forceinline__ int xcd_order(int id, int n) {
+    const int q = n >> 3;
+    return id < 8 * q ? (id & 7) * q + (id >> 3) : id;
+}
+
+// (batch, chunk, workgroup of the chunk) from a place in the list.  Divisions that do not wait for one another.
+struct Place {
+    int b, c, z;
 };
+__device__ __forceinline__ Place place(int id, int per, int nc) {
+    const uint32_t u = id, q = u / (uint32_t)per, b = u / ((uint32_t)per * (uint32_t)nc);
+    return {(int)b, (int)(q - b * nc), (int)(u - q * per)};
+}
 
 // ---------------------------------------------------------------------------------------------
 // Step 1, one launch: the scores and the chunk states (backward: and the local state adjoints).
-// The first n_cb workgroups each do one 64 x 64 tile of  Gm[b,c,g,i,j] = C_i . B_j  on or below the diagonal; the
+// Of a chunk's workgroups the first each do one 64 x 64 tile of  Gm[b,c,g,i,j] = C_i . B_j  on or below the diagonal; the
 // others one 64 x 64 tile of
 //   role 0: states[b,c,h,p,n]  = sum_j exp(T - cum_j) dt_j x_j[p] B_j[n]
 //   role 1: dstates[b,c,h,p,n] = sum_i exp(cum_i) dY_i[p] C_i[n]
@@ -282,27 +328,38 @@ struct Vec {
 // (0, 0) of role 0 stores cum and dt for the steps that follow.
 // RAW: dt as it leaves a projection.  A template argument: as a branch it took 0.5 us of the 8.4 and 26.6 that the kernel
 // takes of 512 and 2048 tokens (fp32, 8 and 24 heads).
-template <typename T, bool RAW>
-__global__ __launch_bounds__(NTHREADS, 4) void k_scores_states(SegParams sp, Vec vec, int n_cb, int nroles) {
+template <typename T, bool RAW, bool VEC>
+__global__ __launch_bounds__(NTHREADS, 4) void k_scores_states(SegParams sp, int nroles) {
     Tiles& L = *(Tiles*)dyn_lds;
     float* red = (float*)(dyn_lds + sizeof(Tiles));  // [4], then the tokens' weights [Q]
     float* wt = red + NTHREADS / 64;
     const int Q = sp.Q, N = sp.N, P = sp.P;
     const int64_t bt = (int64_t)sp.G * N;
-    int z = blockIdx.x, buf = 0;
+    const int NT = (Q + TM - 1) / TM, npair = NT * (NT + 1) / 2, NP = (P + TM - 1) / TM, NN = (N + TM - 1) / TM;
+    const int n_cb = sp.G * npair, per = n_cb + sp.H * nroles * NN * NP;  // of a chunk
+    const Place at = place(xcd_order(blockIdx.x, gridDim.x), per, sp.nc);
+    const int c = at.c, b = at.b, V = chunk_rows(sp, c, Q);
+    int z = at.z;
     f32x16 acc = zero_acc();
     if (z < n_cb) {
-        const int NT = (Q + TM - 1) / TM, npair = NT * (NT + 1) / 2;
         int pair = z % npair, I = 0;
-        z /= npair;
+        const int g = z / npair;
         while (pair > I) pair -= ++I;
         const int i0 = I * TM, j0 = pair * TM;
-        const int g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc), V = chunk_rows(sp, c, Q);
         if (i0 >= V) return;
         const int64_t base = (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N;
-        tile_gemm<true, true>(
-            acc, 0, N, [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, sp.Cm, base, bt, i0, r, k0, k, V, N, vec.bc); }, NoWeight{},
-            [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, sp.Bm, base, bt, j0, r, k0, k, V, N, vec.bc); }, NoWeight{}, L, buf);
+        chain<2, Staged>(
+            (N + TK - 1) / TK, L,
+            [&](Staged& R, int s, bool live) {
+                const int k0 = s * TK;
+                fetch<T, VEC>(R.a, true, part_of<T>(sp.Cm, base + i0 * bt + k0, bt, least(TM, V - i0), N - k0), live);
+                fetch<T, VEC>(R.b, true, part_of<T>(sp.Bm, base + j0 * bt + k0, bt, least(TM, V - j0), N - k0), live);
+            },
+            [&](const Staged& R, int, float* la, float* lb) {
+                put<T, VEC>(R.a, true, la, NoWeight{});
+                put<T, VEC>(R.b, true, lb, NoWeight{});
+            },
+            [&](int, const float* la, const float* lb) { tile_mma<true, true>(acc, la, lb); }, [] {});
         float* out = sp.Gm + (((int64_t)b * sp.nc + c) * sp.G + g) * Q * Q;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -312,42 +369,49 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_scores_states(SegParams sp, Vec
         return;
     }
     z -= n_cb;
-    const int NP = (P + TM - 1) / TM, NN = (N + TM - 1) / TM;
     const int n0 = (z % NN) * TM;
     z /= NN;
     const int p0 = (z % NP) * TM;
     z /= NP;
-    const int role = z % nroles;
-    z /= nroles;
-    const int h = z % sp.H, c = (z / sp.H) % sp.nc, b = z / (sp.H * sp.nc), g = h / sp.hpg, V = chunk_rows(sp, c, Q);
+    const int role = z % nroles, h = z / nroles, g = h / sp.hpg;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    auto form_cum = [&] {  // thread t owns the E consecutive tokens from t E on
-        const int E = (Q + NTHREADS - 1) / NTHREADS;
-        const float A = sp.A[h];
-        float d[QMAX / NTHREADS], a[QMAX / NTHREADS], run = 0.f;
-        for (int e = 0; e < QMAX / NTHREADS; ++e) {
-            const int i = tid * E + e;
-            const bool live = e < E && i < V;
-            if (RAW) d[e] = live ? IO<T>::round(softplus(IO<T>::ld(sp.raw.dt, ((int64_t)c * Q + i) * sp.raw.rs + h) + sp.raw.bias[h])) : 0.f;
-            else d[e] = live ? IO<T>::ld(sp.dt, (int64_t)b * sp.dts_b + ((int64_t)c * Q + i) * sp.H + h) : 0.f;
-            run += d[e] * A + ((live && sp.reset && sp.reset[(int64_t)b * sp.reset_bs + (int64_t)c * Q + i]) ? RESET_LOG_DECAY : 0.f);
+    // Thread t owns the E consecutive tokens from t E on.  What they need from memory is asked for in front of everything else.
+    constexpr int EM = QMAX / NTHREADS;
+    const int E = (Q + NTHREADS - 1) / NTHREADS;
+    float d[EM], flag[EM];
+#pragma unroll
+    for (int e = 0; e < EM; ++e) {
+        d[e] = flag[e] = 0.f;
+        if (e < E) {  // uniform
+            const int i = least(tid * E + e, V - 1);
+            d[e] = RAW ? IO<T>::ld(sp.raw.dt, ((int64_t)c * Q + i) * sp.raw.rs + h) : IO<T>::ld(sp.dt, (int64_t)b * sp.dts_b + ((int64_t)c * Q + i) * sp.H + h);
+            if (sp.reset) flag[e] = sp.reset[(int64_t)b * sp.reset_bs + (int64_t)c * Q + i] ? RESET_LOG_DECAY : 0.f;
+        }
+    }
+    const float A = sp.A[h], bias = RAW ? sp.raw.bias[h] : 0.f;
+    auto form_cum = [&] {
+        float a[EM], run = 0.f;
+#pragma unroll
+        for (int e = 0; e < EM; ++e) {
+            const bool live = e < E && tid * E + e < V;
+            if (RAW) d[e] = IO<T>::round(softplus(d[e] + bias));
+            d[e] = live ? d[e] : 0.f;
+            run += d[e] * A + (live ? flag[e] : 0.f);
             a[e] = run;
         }
-        float incl = run;  // inclusive scan of the threads' totals over the wave, then over the waves
-        for (int off = 1; off < 64; off <<= 1) {
-            const float v = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += v;
-        }
+        const float incl = wave_prefix(run);  // over the wave, then over the waves
         if (lane == 63) red[w] = incl;
         __syncthreads();
         float before = incl - run, total = 0.f;
+#pragma unroll
         for (int q = 0; q < NTHREADS / 64; ++q) {
             before += q < w ? red[q] : 0.f;
             total += red[q];
         }
         const bool keep = role == 0 && n0 == 0 && p0 == 0;
         const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
-        for (int e = 0; e < QMAX / NTHREADS; ++e) {
+#pragma unroll
+        for (int e = 0; e < EM; ++e) {
             const int i = tid * E + e;
             if (e < E && i < Q) {
                 const float cum = before + a[e];
@@ -365,14 +429,18 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_scores_states(SegParams sp, Vec
     const int64_t xt = (int64_t)sp.H * P;
     const int64_t xbase = (int64_t)b * (role == 0 ? sp.xs_b : sp.dys_b) + ((int64_t)c * Q * sp.H + h) * P + p0;
     const int64_t bbase = (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N + n0;
-    tile_gemm<false, false>(
-        acc, 0, V, [&](float (&v)[4], int r, int k, int k0) { ld_r4<T>(v, lhs, xbase, xt, r, k0, k, P - p0, V); },
-        [&](float (&v)[4], int, int k) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (k + e < Q) v[e] *= wt[k + e];
+    chain<2, Staged>(
+        (V + TK - 1) / TK, L,
+        [&](Staged& R, int s, bool live) {
+            const int k0 = s * TK;
+            fetch<T, VEC>(R.a, false, part_of<T>(lhs, xbase + k0 * xt, xt, least(TK, V - k0), P - p0), live);
+            fetch<T, VEC>(R.b, false, part_of<T>(rhs, bbase + k0 * bt, bt, least(TK, V - k0), N - n0), live);
         },
-        [&](float (&v)[4], int r, int k, int k0) { ld_r4<T>(v, rhs, bbase, bt, r, k0, k, N - n0, V); }, NoWeight{}, L, buf, form_cum);
+        [&](const Staged& R, int s, float* la, float* lb) {
+            put<T, VEC>(R.a, false, la, [&](f32x4& v, int hi, int, int) { v *= s * TK + hi < Q ? wt[s * TK + hi] : 0.f; });
+            put<T, VEC>(R.b, false, lb, NoWeight{});
+        },
+        [&](int, const float* la, const float* lb) { tile_mma<false, false>(acc, la, lb); }, form_cum);
     float* out = role == 0 ? sp.states + (((int64_t)b * (sp.nc + 1) + c) * sp.H + h) * P * N
                            : sp.dstates + (((int64_t)b * sp.nc + c) * sp.H + h) * P * N;
 #pragma unroll
@@ -472,16 +540,25 @@ __global__ __launch_bounds__(NTHREADS) void k_state_scan(SegParams sp) {
 
 // ---------------------------------------------------------------------------------------------
 // Step 3 forward: y = (G o decay o dt) X + exp(cum) C Hprev^T + D x   (+ x under the residual flag); one 64 x 64 tile.
-template <typename T>
-__global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp, Vec vec) {
+//
+// One chain of steps: through the state, the tokens before the tile, the diagonal tile.  With the token in front of the tile as
+// reference, exp(cum_i - cum_k) = exp(cum_i - ref) exp(ref - cum_k), both factors <= 1: one exp per token instead of one per score,
+// the first factor scales the rows; only the diagonal tile takes an exp per score.  The state's weight exp(cum_i) is applied to the
+// rows of its product.
+template <typename T, bool VEC>
+__global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp) {
     const int Q = sp.Q, N = sp.N, P = sp.P;
     Tiles& L = *(Tiles*)dyn_lds;
-    float *cum = (float*)(dyn_lds + sizeof(Tiles)), *dtf = cum + Q, *rowf = dtf + Q, *srow = rowf + TM;
-    const int p0 = blockIdx.y * TM, i0 = ((int)gridDim.z - 1 - (int)blockIdx.z) * TM;  // the longest rows first
-    const int z = blockIdx.x, h = z % sp.H, c = (z / sp.H) % sp.nc, b = z / (sp.H * sp.nc), g = h / sp.hpg, V = chunk_rows(sp, c, Q);
+    float *rowf = (float*)(dyn_lds + sizeof(Tiles)), *rowm = rowf + TM, *colm = rowm + TK, *srow = colm + TK, *cum = srow + TM, *dtf = cum + Q;
+    const int NT = (Q + TM - 1) / TM, NP = (P + TM - 1) / TM;
+    const Place at = place(xcd_order(blockIdx.x, gridDim.x), NP * sp.H * NT, sp.nc);
+    const int c = at.c, b = at.b, V = chunk_rows(sp, c, Q);
+    const uint32_t q = (uint32_t)at.z / (uint32_t)NP, it = (uint32_t)at.z / (uint32_t)(NP * sp.H);
+    const int p0 = (at.z - (int)q * NP) * TM, h = (int)(q - it * sp.H), g = (uint32_t)h / (uint32_t)sp.hpg;
+    const int i0 = (NT - 1 - (int)it) * TM;  // the longest rows first
     if (i0 >= V) return;
     const int64_t cbase = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
-    const int kend = i0 + TM < V ? i0 + TM : V;
+    const int kend = i0 + TM < V ? i0 + TM : V, rows = kend - i0;
     const float* Gm = sp.Gm + (((int64_t)b * sp.nc + c) * sp.G + g) * Q * Q;
     const float* Hprev = sp.states + (((int64_t)b * (sp.nc + 1) + c) * sp.H + h) * P * N;
     const int64_t xrow = ((int64_t)c * Q * sp.H + h) * P;
@@ -489,61 +566,97 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp, Vec vec
     const int64_t xt = (int64_t)sp.H * P;
     const int64_t bbase = (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N;
     const int64_t bt = (int64_t)sp.G * N;
-    int buf = 0;
-    f32x16 acc = zero_acc();
-    auto la = [&](float (&v)[4], int r, int k, int k0) { ld_k4<float>(v, Gm, 0, Q, i0, r, k0, k, V, Q, (Q & 3) == 0); };
-    auto lb = [&](float (&v)[4], int r, int k, int k0) { ld_r4<T>(v, sp.x, xbase + p0, xt, r, k0, k, P - p0, V); };
-    // Tokens before the tile: exp(cum_i - cum_k) = exp(cum_i - cum_ref) exp(cum_ref - cum_k) with the token in front of
-    // the tile as reference, both <= 1: one exp per token instead of one per score; the first factor scales the rows at
-    // the end.  Only the diagonal tile takes an exp per score.  The entering state's weight exp(cum_i) too is applied to the
-    // rows of its product.  (Weights in the operands of that product and the rows' exps in every lane: 600 instructions a
-    // wave more, 4096 tokens of 24 heads 36.6 us, now 32.)
+    const float Dh = sp.D[h] + ((sp.flags & SSD_FLAG_RESIDUAL) ? 1.f : 0.f);
+    // what the weights are made from: asked for in front of everything else
+    const int tid = threadIdx.x, mine = least(tid, kend - 1), row = least(tid & (TM - 1), rows - 1);
+    const float c0 = sp.cum[cbase + mine], d0 = sp.dtf[cbase + mine];
+    const float ci = sp.cum[cbase + i0 + row], di = sp.dtf[cbase + i0 + row], cm = sp.cum[cbase + i0 + least(TK, rows) - 1];
     const float ref = i0 > 0 ? sp.cum[cbase + i0 - 1] : 0.f;
-    tile_gemm<true, false>(
-        acc, 0, i0, la,
-        [&](float (&v)[4], int, int k) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] *= dtf[k + e];
+    const int nS = (N + TK - 1) / TK, nO = i0 / TK, nD = (rows + TK - 1) / TK;
+    f32x16 acc = zero_acc(), t = zero_acc();
+    chain<2, Staged>(
+        nS + nO + nD, L,
+        [&](Staged& R, int s, bool live) {
+            const bool st = s < nS;
+            const int k0 = (st ? s : s - nS) * TK;
+            const Part sa = part_of<T>(sp.Cm, bbase + i0 * bt + k0, bt, rows, N - k0), ta = part_of<float>(Gm, (int64_t)i0 * Q + k0, Q, rows, Q - k0);
+            const Part sb = part_of<float>(Hprev, (int64_t)p0 * N + k0, N, least(TM, P - p0), N - k0);
+            const Part tb = part_of<T>(sp.x, xbase + p0 + k0 * xt, xt, least(TK, V - k0), P - p0);
+            if constexpr (sizeof(T) == 4) {
+                fetch<float, VEC>(R.a, true, st ? sa : ta, live);
+                fetch<float, VEC>(R.b, st, st ? sb : tb, live);
+            } else if (st) {
+                fetch<T, VEC>(R.a, true, sa, live);
+                fetch<float, VEC>(R.b, true, sb, live);
+            } else {
+                fetch<float, VEC>(R.a, true, ta, live);
+                fetch<T, VEC>(R.b, false, tb, live);
+            }
         },
-        lb, NoWeight{}, L, buf, [&] {
-            for (int i = threadIdx.x; i < kend; i += NTHREADS) {
-                const float c_ = sp.cum[cbase + i], d_ = sp.dtf[cbase + i];
-                cum[i] = c_;
-                dtf[i] = i < i0 ? decay(ref - c_) * d_ : d_;
-                if (i >= i0) {
-                    rowf[i - i0] = decay(c_ - ref);
-                    srow[i - i0] = expf(c_);
+        [&](const Staged& R, int s, float* la, float* lb) {
+            if (s < nS) {
+                put<T, VEC>(R.a, true, la, NoWeight{});
+                put<float, VEC>(R.b, true, lb, NoWeight{});
+                return;
+            }
+            const int k0 = (s - nS) * TK;
+            put<T, VEC>(R.b, false, lb, NoWeight{});
+            if (s < nS + nO) {
+                put<float, VEC>(R.a, true, la, [&](f32x4& v, int, int k, int) { v *= ld4<VEC>(dtf + k0 + k); });
+            } else {
+                // Two steps of 32 tokens.  Of the first, the tile's upper rows take an exponential per score and the lower ones a
+                // factor per row and one per token, split at the step's last token; the second is the lower rows' own.
+                const int half = k0 > i0;
+                put<float, VEC>(R.a, true, la, [&](f32x4& v, int r, int k, int piece) {
+                    if (piece == half) {
+                        const float ci = cum[i0 + 32 * half + r];
+                        const f32x4 ck = ld4<VEC>(cum + k0 + k), dk = ld4<VEC>(dtf + k0 + k);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float f = expf(ci - ck[e]) * dk[e];
+                            v[e] = k + e <= r ? v[e] * f : 0.f;
+                        }
+                    } else if (piece == 1) {
+                        v *= rowm[r] * *(const f32x4*)(colm + k);
+                    } else {
+                        v = (f32x4)(0.f);
+                    }
+                });
+            }
+        },
+        [&](int s, const float* la, const float* lb) {
+            if (s < nS) {
+                tile_mma<true, true>(t, la, lb);
+            } else {
+                if (s == nS + nO && i0 > 0) scale_rows(acc, rowf);
+                tile_mma<true, false>(acc, la, lb);
+                if (s == nS + nO + (tid >> 7)) {  // the step whose tokens are the wave's rows, the last with a share in its sums: their x is here
+                    float f[16];
+                    rows_of(srow, f);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[r] = fmaf(Dh, lb[(tile_row(r) & (TK - 1)) * RPITCH + tile_col()], fmaf(t[r], f[r], acc[r]));
                 }
             }
-            __syncthreads();
-        });
-    if (i0 > 0)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] *= i0 + tile_row(r) < V ? rowf[tile_row(r)] : 0.f;
-    tile_gemm<true, false>(
-        acc, i0, kend, la,
-        [&](float (&v)[4], int r, int k) {
-            const int i = i0 + r;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (i < V && k + e <= i) ? v[e] * expf(cum[i] - cum[k + e]) * dtf[k + e] : 0.f;
         },
-        lb, NoWeight{}, L, buf);
-    f32x16 t = zero_acc();
-    tile_gemm<true, true>(
-        t, 0, N, [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, sp.Cm, bbase, bt, i0, r, k0, k, V, N, vec.bc); }, NoWeight{},
-        [&](float (&v)[4], int r, int k, int k0) { ld_k4<float>(v, Hprev, (int64_t)p0 * N, N, 0, r, k0, k, P - p0, N, (N & 3) == 0); }, NoWeight{}, L, buf);
+        [&] {
+            // (not needed before the second step of the chain: its barriers suffice)
+            auto keep = [&](int i, float c_, float d_) {
+                cum[i] = c_;
+                dtf[i] = i < i0 ? decay(ref - c_) * d_ : d_;
+            };
+            if (tid < kend) keep(tid, c0, d0);
+            for (int i = tid + NTHREADS; i < kend; i += NTHREADS) keep(i, sp.cum[cbase + i], sp.dtf[cbase + i]);
+            if (tid < TM) {
+                rowf[tid] = decay(ci - ref);  // rows that do not exist: those of the last one
+                srow[tid] = expf(ci);
+                if (tid < TK) colm[tid] = decay(cm - ci) * di;
+                else rowm[tid - TK] = decay(ci - cm);
+            }
+        });
+    const int left = opaque(V - i0), p = p0 + tile_col();
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = fmaf(t[r], i0 + tile_row(r) < V ? srow[tile_row(r)] : 0.f, acc[r]);
-    const float Dh = sp.D[h] + ((sp.flags & SSD_FLAG_RESIDUAL) ? 1.f : 0.f);
-    const int p = p0 + tile_col();
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int i = i0 + tile_row(r);
-        if (i < V && p < P) {
-            const int64_t o = (int64_t)i * xt + p;
-            IO<T>::st(sp.y, ybase + o, acc[r] + Dh * IO<T>::ld(sp.x, xbase + o));
-        }
-    }
+    for (int r = 0; r < 16; ++r)
+        if (tile_row(r) < left && p < P) IO<T>::st(sp.y, ybase + (int64_t)(i0 + tile_row(r)) * xt + p, acc[r]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -552,24 +665,21 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp, Vec vec
 struct WalkLds {
     Tiles t;
     union {
-        float ch[1];  // walk_u: cum [Q], dt [Q], the rows' factors [2][TM]
+        float ch[1];  // walk_u: the factors of rows and tokens [2 TM], cum [Q], dt [Q]
         struct { float row[2][TM], col[2][TM], dcol[2][TM]; } hd;
     };
 };
 
 // u rows j0.. of one (chunk, head): transposed masked scores (without dt) times dY, then the leaving-adjoint term;
 // dx = dt u + D dY, and per token x . u (fterm) and dY . x (dDrow)
-template <typename T>
-__device__ __forceinline__ void walk_u(const SegParams& sp, const Vec& vec, WalkLds& L, int z) {
-    const int Q = sp.Q, N = sp.N, P = sp.P, NT = (Q + TM - 1) / TM, NP = (P + TM - 1) / TM;
-    const int j0 = (z % NT) * TM;  // tile 0 has the longest contraction
-    z /= NT;
-    const int p0 = (z % NP) * TM;
-    z /= NP;
-    const int h = z % sp.H, c = (z / sp.H) % sp.nc, b = z / (sp.H * sp.nc), g = h / sp.hpg, V = chunk_rows(sp, c, Q);
+template <typename T, bool VEC>
+__device__ __forceinline__ void walk_u(const SegParams& sp, WalkLds& L, int b, int c, int h, int z) {
+    const int Q = sp.Q, N = sp.N, P = sp.P, NP = (P + TM - 1) / TM;
+    const int p0 = (z % NP) * TM, j0 = (z / NP) * TM;  // tile 0 has the longest contraction
+    const int g = h / sp.hpg, V = chunk_rows(sp, c, Q);
     if (j0 >= V) return;
     const int64_t cbase = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
-    float *cum = L.ch, *dtf = L.ch + Q, *rowf = dtf + Q, *srow = rowf + TM;
+    float *rowf = L.ch, *rowm = rowf + TM, *colm = rowm + TK, *cum = colm + TK, *dtf = cum + Q;
     const float T_ = sp.cum[cbase + Q - 1];
     const float* Gm = sp.Gm + (((int64_t)b * sp.nc + c) * sp.G + g) * Q * Q;
     const float* dHnext = sp.dstates + (((int64_t)b * sp.nc + c) * sp.H + h) * P * N;
@@ -579,61 +689,106 @@ __device__ __forceinline__ void walk_u(const SegParams& sp, const Vec& vec, Walk
     const int64_t bbase = (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N;
     const int64_t bt = (int64_t)sp.G * N;
     const float Dh = sp.D[h] + ((sp.flags & SSD_FLAG_RESIDUAL) ? 1.f : 0.f);
-    int buf = 0;
-    f32x16 acc = zero_acc();
-    auto la = [&](float (&v)[4], int r, int k, int k0) { ld_r4<float>(v, Gm, j0, Q, r, k0, k, V - j0, V); };
-    auto lb = [&](float (&v)[4], int r, int k, int k0) { ld_r4<T>(v, sp.dy, dybase + p0, xt, r, k0, k, P - p0, V); };
-    // tokens behind the tile: the decay split at the tile's last token, as in k_chunk_out
-    const int j1 = j0 + TM < V ? j0 + TM : V;
-    const float ref = sp.cum[cbase + j1 - 1];
-    tile_gemm<false, false>(
-        acc, j1, V, la,
-        [&](float (&v)[4], int, int k) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] *= k + e < V ? cum[k + e] : 0.f;
-        },
-        lb, NoWeight{}, L.t, buf, [&] {
-            for (int i = threadIdx.x; i < V; i += NTHREADS) {
-                const float c_ = sp.cum[cbase + i];
-                cum[i] = i < j1 ? c_ : decay(c_ - ref);
-                dtf[i] = sp.dtf[cbase + i];
-                if (i >= j0 && i < j1) {
-                    rowf[i - j0] = decay(ref - c_);
-                    srow[i - j0] = expf(T_ - c_);
-                }
-            }
-            __syncthreads();
-        });
-    if (j1 < V)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] *= rowf[tile_row(r)];
-    tile_gemm<false, false>(
-        acc, j0, j1, la,
-        [&](float (&v)[4], int r, int k) {
-            const int j = j0 + r;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (j < V && k + e < V && k + e >= j) ? v[e] * expf(cum[k + e] - cum[j]) : 0.f;
-        },
-        lb, NoWeight{}, L.t, buf);
-    f32x16 t = zero_acc();
-    tile_gemm<true, true>(
-        t, 0, N, [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, sp.Bm, bbase, bt, j0, r, k0, k, V, N, vec.bc); }, NoWeight{},
-        [&](float (&v)[4], int r, int k, int k0) { ld_k4<float>(v, dHnext, (int64_t)p0 * N, N, 0, r, k0, k, P - p0, N, (N & 3) == 0); }, NoWeight{}, L.t, buf);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = fmaf(t[r], j0 + tile_row(r) < V ? srow[tile_row(r)] : 0.f, acc[r]);
+    // through the adjoint, tokens behind the tile, the diagonal tile, the decay split at the tile's last token: k_chunk_out's chain
+    const int j1 = j0 + TM < V ? j0 + TM : V, rows = j1 - j0;
+    // what the weights are made from: asked for in front of everything else
+    const int tid = threadIdx.x, mine = least(tid, V - 1), row = least(tid & (TM - 1), rows - 1);
+    const float c0 = sp.cum[cbase + mine], d0 = sp.dtf[cbase + mine];
+    const float cj = sp.cum[cbase + j0 + row], cm = sp.cum[cbase + j0 + least(TK, rows) - 1], ref = sp.cum[cbase + j1 - 1];
+    const int nS = (N + TK - 1) / TK, nO = (V - j1 + TK - 1) / TK, nD = (rows + TK - 1) / TK;
     const int p = p0 + tile_col();
+    f32x16 acc = zero_acc();
+    float xv[16], dyv[16];
+    chain<2, Staged>(
+        nS + nO + nD, L.t,
+        [&](Staged& R, int s, bool live) {
+            const bool st = s < nS;
+            const int k0 = st ? s * TK : (s < nS + nO ? j1 + (s - nS) * TK : j0 + (s - nS - nO) * TK);
+            const Part sa = part_of<T>(sp.Bm, bbase + j0 * bt + k0, bt, rows, N - k0), ta = part_of<float>(Gm, (int64_t)k0 * Q + j0, Q, least(TK, V - k0), Q - j0);
+            const Part sb = part_of<float>(dHnext, (int64_t)p0 * N + k0, N, least(TM, P - p0), N - k0);
+            const Part tb = part_of<T>(sp.dy, dybase + p0 + k0 * xt, xt, least(TK, V - k0), P - p0);
+            if constexpr (sizeof(T) == 4) {
+                fetch<float, VEC>(R.a, st, st ? sa : ta, live);
+                fetch<float, VEC>(R.b, st, st ? sb : tb, live);
+            } else if (st) {
+                fetch<T, VEC>(R.a, true, sa, live);
+                fetch<float, VEC>(R.b, true, sb, live);
+            } else {
+                fetch<float, VEC>(R.a, false, ta, live);
+                fetch<T, VEC>(R.b, false, tb, live);
+            }
+        },
+        [&](const Staged& R, int s, float* la, float* lb) {
+            if (s < nS) {
+                put<T, VEC>(R.a, true, la, NoWeight{});
+                put<float, VEC>(R.b, true, lb, NoWeight{});
+                return;
+            }
+            put<T, VEC>(R.b, false, lb, NoWeight{});
+            if (s < nS + nO) {
+                const int k0 = j1 + (s - nS) * TK;
+                put<float, VEC>(R.a, false, la, [&](f32x4& v, int k, int, int) { v *= k0 + k < V ? cum[k0 + k] : 0.f; });
+            } else {
+                // the first step is the tile's upper rows' own; of the second, the lower rows take an exponential per score, the
+                // upper ones a factor per row and one per token
+                const int half = s > nS + nO, k0 = j0 + half * TK;
+                put<float, VEC>(R.a, false, la, [&](f32x4& v, int k, int r, int piece) {
+                    if (piece == half) {
+                        const float ck = cum[least(k0 + k, V - 1)];
+                        const f32x4 cj = ld4<VEC>(cum + k0 + r);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float f = expf(ck - cj[e]);
+                            v[e] = k >= r + e && k0 + k < V ? v[e] * f : 0.f;
+                        }
+                    } else if (piece == 0) {
+                        v *= colm[k] * *(const f32x4*)(rowm + r);
+                    } else {
+                        v = (f32x4)(0.f);
+                    }
+                });
+            }
+        },
+        [&](int s, const float* la, const float* lb) {
+            if (s < nS) {
+                tile_mma<true, true>(acc, la, lb);
+            } else {
+                if (s == nS) acc *= decay(T_ - ref);
+                if (s == nS + nO) scale_rows(acc, rowf);
+                tile_mma<false, false>(acc, la, lb);
+            }
+        },
+        [&] {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int64_t o = (int64_t)least(j0 + tile_row(r), V - 1) * xt + least(p, P - 1);  // clamped: no branches
+                dyv[r] = IO<T>::ld(sp.dy, dybase + o);
+                xv[r] = IO<T>::ld(sp.x, xbase + o);
+            }
+            // (not needed before the second step of the chain: its barriers suffice)
+            auto keep = [&](int i, float c_, float d_) {
+                cum[i] = i < j1 ? c_ : decay(c_ - ref);
+                dtf[i] = d_;
+            };
+            if (tid < V) keep(tid, c0, d0);
+            for (int i = tid + NTHREADS; i < V; i += NTHREADS) keep(i, sp.cum[cbase + i], sp.dtf[cbase + i]);
+            if (tid < TM) {
+                rowf[tid] = decay(ref - cj);  // rows that do not exist: those of the last one
+                if (tid < TK) rowm[tid] = decay(cm - cj);
+                else colm[tid - TK] = tid < rows ? decay(cj - cm) : 0.f;
+            }
+        });
     f32x16 dyx;
+    const int left = opaque(V - j0);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int j = j0 + tile_row(r);
-        const bool live = j < V && p < P;
-        const int64_t o = live ? (int64_t)j * xt + p : (int64_t)j0 * xt;
-        const float dyv = IO<T>::ld(sp.dy, dybase + o), xv = IO<T>::ld(sp.x, xbase + o);
-        if (live) IO<T>::st(sp.dx, dxbase + o, dtf[j] * acc[r] + Dh * dyv);
-        acc[r] *= live ? xv : 0.f;
-        dyx[r] = live ? dyv * xv : 0.f;
+        const bool live = tile_row(r) < left && p < P;
+        if (live) IO<T>::st(sp.dx, dxbase + (int64_t)j * xt + p, dtf[j] * acc[r] + Dh * dyv[r]);
+        acc[r] = live ? acc[r] * xv[r] : 0.f;
+        dyx[r] = live ? dyv[r] * xv[r] : 0.f;
     }
-    const int lane = threadIdx.x & 63, piece = 2 * (p0 / TM) + ((threadIdx.x >> 6) & 1);
+    const int lane = tid & 63, piece = 2 * (p0 / TM) + ((tid >> 6) & 1);
     const float f = row_sums(acc, lane), d = row_sums(dyx, lane);
     if ((lane & 1) == 0) {  // lane l of a half holds the sum of register (l % 32) / 2
         const int j = j0 + tile_row((lane & 31) >> 1);
@@ -647,62 +802,83 @@ __device__ __forceinline__ void walk_u(const SegParams& sp, const Vec& vec, Walk
 
 // One 64 x 64 tile (on or below the diagonal) of dG[b,c,g,i,j] = sum over the heads of a slice of
 // exp(cum_i - cum_j) dt_j (dY_i . x_j), and per head the row and column sums of E = that (.) G
-template <typename T>
-__device__ __forceinline__ void walk_dg(const SegParams& sp, const Vec& vec, WalkLds& L, int z) {
-    const int Q = sp.Q, P = sp.P, NT = (Q + TM - 1) / TM, npair = NT * (NT + 1) / 2;
-    int pair = z % npair, I = 0;
-    z /= npair;
-    while (pair > I) pair -= ++I;
-    const int i0 = I * TM, j0 = pair * TM, ns = sp.dg_split, slice = z % ns;
-    z /= ns;
-    const int g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc), V = chunk_rows(sp, c, Q);
+template <typename T, bool VEC, bool DIAG>
+__device__ __forceinline__ void walk_dg(const SegParams& sp, WalkLds& L, int b, int c, int g, int slice, int I, int J) {
+    const int Q = sp.Q, P = sp.P, V = chunk_rows(sp, c, Q), ns = sp.dg_split;
+    const int i0 = I * TM, j0 = J * TM;
     if (i0 >= V) return;
     const int hps = sp.hpg / ns, h0 = g * sp.hpg + slice * hps, tid = threadIdx.x, lane = tid & 63;
     const int64_t xt = (int64_t)sp.H * P;
     const float* Gm = sp.Gm + (((int64_t)b * sp.nc + c) * sp.G + g) * Q * Q;
     const int col = tile_col(), j = j0 + col;
-    float gv[16];
+    float gv[16];  // the tile's scores: clamped indices, no branches, and zeros where there is none
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int i = i0 + tile_row(r);
-        gv[r] = (i < V && j <= i) ? Gm[(int64_t)i * Q + j] : 0.f;
-    }
-    f32x16 tot = zero_acc();
+    for (int r = 0; r < 16; ++r) gv[r] = Gm[(int64_t)least(i0 + tile_row(r), V - 1) * Q + least(j, Q - 1)];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) gv[r] = i0 + tile_row(r) < V && j <= i0 + tile_row(r) ? gv[r] : 0.f;
+    f32x16 tot = zero_acc(), t = zero_acc();
     const int KS = (P + TK - 1) / TK;
-    float ra[2][4], rb[2][4], rc = 0.f, rf = 0.f;
-    auto load = [&](int s) {  // contraction step s % KS of head s / KS; with the first one, that head's cum and dt
-        const int h = h0 + s / KS, k0 = (s % KS) * TK;
-        const int64_t xrow = ((int64_t)c * Q * sp.H + h) * P;
-        const int64_t xbase = (int64_t)b * sp.xs_b + xrow, dybase = (int64_t)b * sp.dys_b + xrow;
-        tile_load<true>(ra, k0, [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, sp.dy, dybase, xt, i0, r, k0, k, V, P, vec.x); });
-        tile_load<true>(rb, k0, [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, sp.x, xbase, xt, j0, r, k0, k, V, P, vec.x); });
-        if (k0 == 0 && tid < 3 * TM) {
-            const int t = tid & (TM - 1), q = (tid < TM ? i0 : j0) + t;
-            const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
-            rc = q < V ? (tid < 2 * TM ? sp.cum : sp.dtf)[o + q] : 0.f;
-            rf = i0 > j0 ? sp.cum[o + i0 - 1] : 0.f;
-        }
+    struct Stage : Staged {
+        float c, f;  // the head's cum or dt, and its cum in front of the rows
     };
-    f32x16 t = zero_acc();
-    load(0);
-    for (int s = 0; s < hps * KS; ++s) {
-        const int hh = s / KS, ks = s % KS, buf = s & 1, hb = hh & 1;
-        tile_store<true>(ra, L.t.a[buf], 0, NoWeight{});
-        tile_store<true>(rb, L.t.b[buf], 0, NoWeight{});
-        // off the diagonal the decay is a row factor times a column factor, split at the token in front of the rows
-        if (ks == 0 && i0 > j0 && tid < 2 * TM) rc = decay(tid < TM ? rc - rf : rf - rc);
-        if (ks == 0 && tid < 3 * TM) (tid < TM ? L.hd.row[hb] : (tid < 2 * TM ? L.hd.col[hb] : L.hd.dcol[hb]))[tid & (TM - 1)] = rc;
-        __syncthreads();
-        if (s + 1 < hps * KS) load(s + 1);
-        tile_mma(t, L.t.a[buf], L.t.b[buf]);
-        if (ks == KS - 1) {
-            const float cj = L.hd.col[hb][col], dj = L.hd.dcol[hb][col], fj = cj * dj;
+    int lh = 0, lk = 0, sh = 0, sk = 0, uh = 0, uk = 0;  // head of the slice and step of that head: of the next load, put and use
+    auto next = [&](int& hh, int& ks) {
+        if (++ks == KS) ks = 0, ++hh;
+    };
+    chain<2, Stage>(
+        hps * KS, L.t,
+        [&](Stage& R, int, bool live) {
+            const int h = __builtin_amdgcn_readfirstlane(live ? h0 + lh : h0), k0 = __builtin_amdgcn_readfirstlane(lk * TK);
+            const int64_t xrow = ((int64_t)c * Q * sp.H + h) * P + k0;
+            fetch<T, VEC>(R.a, true, part_of<T>(sp.dy, (int64_t)b * sp.dys_b + xrow + i0 * xt, xt, least(TM, V - i0), P - k0), live);
+            fetch<T, VEC>(R.b, true, part_of<T>(sp.x, (int64_t)b * sp.xs_b + xrow + j0 * xt, xt, least(TM, V - j0), P - k0), live);
+            const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;  // (every step: see chain)
+            R.c = (tid < 2 * TM ? sp.cum : sp.dtf)[o + least((tid < TM ? i0 : j0) + (tid & (TM - 1)), V - 1)];
+            if (!DIAG) R.f = sp.cum[o + i0 - 1];
+            next(lh, lk);
+        },
+        [&](Stage& R, int, float* la, float* lb) {
+            put<T, VEC>(R.a, true, la, NoWeight{});
+            put<T, VEC>(R.b, true, lb, NoWeight{});
+            const int hb = sh & 1;
+            if (sk == 0 && tid < 3 * TM) {
+                // off the diagonal the decay is a row factor times a column factor, split at the token in front of the rows
+                const float v = !DIAG && tid < 2 * TM ? decay(tid < TM ? R.c - R.f : R.f - R.c) : R.c;
+                (tid < TM ? L.hd.row[hb] : (tid < 2 * TM ? L.hd.col[hb] : L.hd.dcol[hb]))[tid & (TM - 1)] = v;
+            }
+            next(sh, sk);
+        },
+        [&](int, const float* la, const float* lb) {
+            tile_mma<true, true>(t, la, lb);
+            const int hh = uh, hb = uh & 1;
+            next(uh, uk);
+            if (uk != 0) return;
+            float cj = L.hd.col[hb][col];
+            asm volatile("" : "+v"(cj));  // or the exponentials move up into every step
+            const float dj = L.hd.dcol[hb][col], fj = cj * dj;
             float cs = 0.f;
+            const int left = opaque(V - i0);  // or a mask of every register stays in scalar registers
+            float f[16];
+            rows_of(L.hd.row[hb], f);
+            if constexpr (!DIAG) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) t[r] *= f[r] * fj;
+                if (i0 + TM > V) {  // uniform
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) t[r] = tile_row(r) < left ? t[r] : 0.f;
+                }
+            } else {
+                const int above = opaque(col);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const bool live = tile_row(r) < left && tile_row(r) >= above;
+                    f[r] = decay(f[r] - cj) * dj;
+                    t[r] = live ? t[r] * f[r] : 0.f;
+                    if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four exponentials at a time: sixteen take the registers of a wave
+                }
+            }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int row = tile_row(r), i = i0 + row;
-                const float f = i0 > j0 ? L.hd.row[hb][row] * fj : decay(L.hd.row[hb][row] - cj) * dj;
-                t[r] = (i < V && j <= i) ? t[r] * f : 0.f;
                 tot[r] += t[r];
                 t[r] *= gv[r];
                 cs += t[r];
@@ -714,11 +890,11 @@ __device__ __forceinline__ void walk_dg(const SegParams& sp, const Vec& vec, Wal
             const float rs = row_sums(t, lane);
             if ((lane & 1) == 0) {
                 const int i = i0 + tile_row((lane & 31) >> 1);
-                if (i < V) sp.erow[(2 * pair + (w & 1)) * sp.tok_stride + cbase + i] = rs;
+                if (i < V) sp.erow[(2 * J + (w & 1)) * sp.tok_stride + cbase + i] = rs;
             }
             t = zero_acc();
-        }
-    }
+        },
+        [] {});
     float* out = sp.dG + ((((int64_t)b * sp.nc + c) * sp.G + g) * ns + slice) * Q * Q;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -730,18 +906,12 @@ __device__ __forceinline__ void walk_dg(const SegParams& sp, const Vec& vec, Wal
 // One 64 x 64 tile of the head sums of a slice, with the per-token dot products through the boundary states:
 //   role 0: part[i][n] = sum_h exp(cum_i) (dY_i . Hprev[:, n]),            gterm_i = exp(cum_i) dY_i . (Hprev C_i)
 //   role 1: part[j][n] = sum_h exp(T - cum_j) dt_j (x_j . dHnext[:, n]),   sterm_j = exp(T - cum_j) dt_j x_j . (dHnext B_j)
-template <typename T>
-__device__ __forceinline__ void walk_part(const SegParams& sp, const Vec& vec, WalkLds& L, int z) {
-    const int Q = sp.Q, N = sp.N, P = sp.P, NT = (Q + TM - 1) / TM, NN = (N + TM - 1) / TM;
+template <typename T, bool VEC>
+__device__ __forceinline__ void walk_part(const SegParams& sp, WalkLds& L, int b, int c, int g, int slice, int z) {
+    const int Q = sp.Q, N = sp.N, P = sp.P, NT = (Q + TM - 1) / TM, NN = (N + TM - 1) / TM, V = chunk_rows(sp, c, Q), ns = sp.part_split;
     const int r0 = (z % NT) * TM;
     z /= NT;
-    const int n0 = (z % NN) * TM;
-    z /= NN;
-    const int role = z & 1;
-    z >>= 1;
-    const int ns = sp.part_split, slice = z % ns;
-    z /= ns;
-    const int g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc), V = chunk_rows(sp, c, Q);
+    const int n0 = (z % NN) * TM, role = z / NN;
     if (r0 >= V) return;
     const int hps = sp.hpg / ns, h0 = g * sp.hpg + slice * hps, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int64_t xt = (int64_t)sp.H * P;
@@ -758,32 +928,40 @@ __device__ __forceinline__ void walk_part(const SegParams& sp, const Vec& vec, W
         }
     }
     const int KS = (P + TK - 1) / TK;
-    float ra[2][4], rb[2][4], rc = 0.f, rd = 0.f, rT = 0.f;
-    auto load = [&](int s) {  // with the first step of a head, its cum and dt
-        const int h = h0 + s / KS, k0 = (s % KS) * TK;
-        const int64_t xbase = (int64_t)b * (role ? sp.xs_b : sp.dys_b) + ((int64_t)c * Q * sp.H + h) * P;
-        const float* S = role ? sp.dstates + (((int64_t)b * sp.nc + c) * sp.H + h) * P * N : sp.states + (((int64_t)b * (sp.nc + 1) + c) * sp.H + h) * P * N;
-        tile_load<true>(ra, k0, [&](float (&v)[4], int r, int k, int k0) { ld_k4<T>(v, role ? sp.x : sp.dy, xbase, xt, r0, r, k0, k, V, P, vec.x); });
-        tile_load<false>(rb, k0, [&](float (&v)[4], int r, int k, int k0) { ld_r4<float>(v, S, n0, N, r, k0, k, N - n0, P); });
-        if (k0 == 0) {
-            const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;
-            rc = sp.cum[o + il];
-            rd = sp.dtf[o + il];
-            rT = sp.cum[o + Q - 1];
-        }
+    struct Stage : Staged {
+        float c, d, T_;  // the head's cum and dt, its cum at the end
+    };
+    int lh = 0, lk = 0, sk = 0, uh = 0, uk = 0;  // head of the slice and step of that head: of the next load, put and use
+    auto next = [&](int& hh, int& ks) {
+        if (++ks == KS) ks = 0, ++hh;
     };
     f32x16 tot = zero_acc(), d = zero_acc();
     float wgt = 0.f;
-    load(0);
-    for (int s = 0; s < hps * KS; ++s) {
-        const int hh = s / KS, ks = s % KS, buf = s & 1;
-        if (ks == 0) wgt = role ? decay(rT - rc) * rd : expf(rc);
-        tile_store<true>(ra, L.t.a[buf], 0, NoWeight{});
-        tile_store<false>(rb, L.t.b[buf], 0, NoWeight{});
-        __syncthreads();
-        if (s + 1 < hps * KS) load(s + 1);
-        tile_mma(d, L.t.b[buf], L.t.a[buf]);
-        if (ks == KS - 1) {
+    chain<2, Stage>(
+        hps * KS, L.t,
+        [&](Stage& R, int, bool live) {
+            const int h = __builtin_amdgcn_readfirstlane(live ? h0 + lh : h0), k0 = __builtin_amdgcn_readfirstlane(lk * TK);
+            const int64_t first = (int64_t)b * (role ? sp.xs_b : sp.dys_b) + (((int64_t)c * Q + r0) * sp.H + h) * P + k0;
+            const float* S = role ? sp.dstates + (((int64_t)b * sp.nc + c) * sp.H + h) * P * N : sp.states + (((int64_t)b * (sp.nc + 1) + c) * sp.H + h) * P * N;
+            fetch<T, VEC>(R.a, true, part_of<T>(role ? sp.x : sp.dy, first, xt, least(TM, V - r0), P - k0), live);
+            fetch<float, VEC>(R.b, false, part_of<float>(S, (int64_t)k0 * N + n0, N, least(TK, P - k0), N - n0), live);
+            const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;  // (every step: see chain)
+            R.c = sp.cum[o + il];
+            R.d = sp.dtf[o + il];
+            R.T_ = sp.cum[o + Q - 1];
+            next(lh, lk);
+        },
+        [&](Stage& R, int, float* la, float* lb) {
+            if (sk == 0) wgt = role ? decay(R.T_ - R.c) * R.d : expf(R.c);
+            if (++sk == KS) sk = 0;
+            put<T, VEC>(R.a, true, la, NoWeight{});
+            put<float, VEC>(R.b, false, lb, NoWeight{});
+        },
+        [&](int, const float* la, const float* lb) {
+            tile_mma<false, true>(d, lb, la);
+            const int hh = uh;
+            next(uh, uk);
+            if (uk != 0) return;
             float d0 = 0.f, d1 = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; r += 2) {
@@ -797,8 +975,8 @@ __device__ __forceinline__ void walk_part(const SegParams& sp, const Vec& vec, W
             if (lane < 32 && i < V)
                 (role ? sp.sterm : sp.gterm)[(2 * (n0 / TM) + (w >> 1)) * sp.tok_stride + (((int64_t)b * sp.H + h0 + hh) * sp.nc + c) * Q + i] = d0 * wgt;
             d = zero_acc();
-        }
-    }
+        },
+        [] {});
     if (i >= V) return;
     float* out = sp.dbc_part + (((((int64_t)b * sp.nc + c) * sp.G + g) * ns + slice) * 2 + role) * ((int64_t)Q * N) + (int64_t)i * N;
 #pragma unroll
@@ -814,36 +992,47 @@ __device__ __forceinline__ void walk_part(const SegParams& sp, const Vec& vec, W
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(NTHREADS, 3) void k_bwd_walk(SegParams sp, Vec vec, int n_part, int n_dg) {
+// The list: batch, chunk, group, and of the heads as many slices as the two slicings have boundaries in common.
+template <typename T, bool VEC>
+__global__ __launch_bounds__(NTHREADS, 3) void k_bwd_walk(SegParams sp, int ns) {
     WalkLds& L = *(WalkLds*)dyn_lds;
-    const int z = blockIdx.x;  // the workgroups that walk several heads first
-    if (z < n_part) walk_part<T>(sp, vec, L, z);
-    else if (z < n_part + n_dg) walk_dg<T>(sp, vec, L, z - n_part);
-    else walk_u<T>(sp, vec, L, z - n_part - n_dg);
+    const int NT = (sp.Q + TM - 1) / TM, NN = (sp.N + TM - 1) / TM, NP = (sp.P + TM - 1) / TM, npair = NT * (NT + 1) / 2;
+    const int ps = sp.part_split / ns, ds = sp.dg_split / ns, hs = sp.hpg / ns;  // slices, and heads, of one of these
+    const int w_part = 2 * NN * NT, w_u = NT * NP, n_part = ps * w_part, n_dg = ds * npair, per = n_part + n_dg + hs * w_u;
+    const Place at = place(xcd_order(blockIdx.x, gridDim.x), per, ns * sp.G * sp.nc);
+    const Place gs = place(at.c, ns, sp.G);  // b: chunk, c: group, z: slice
+    const int b = at.b, c = gs.b, g = gs.c, s = gs.z;
+    int z = at.z;
+    // the workgroups that walk several heads first
+    if (z < n_part) {
+        walk_part<T, VEC>(sp, L, b, c, g, s * ps + z / w_part, z % w_part);
+        return;
+    }
+    z -= n_part;
+    if (z < n_dg) {
+        int J = z % npair, I = 0;
+        while (J > I) J -= ++I;
+        if (I == J) walk_dg<T, VEC, true>(sp, L, b, c, g, s * ds + z / npair, I, J);
+        else walk_dg<T, VEC, false>(sp, L, b, c, g, s * ds + z / npair, I, J);
+        return;
+    }
+    z -= n_dg;
+    walk_u<T, VEC>(sp, L, b, c, g * sp.hpg + s * hs + z % hs, z / hs);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Step 4 backward, one launch: 64 x 64 tiles of dC (role 0) / dB (role 1) from the slices' partial sums (see the
 // formulas at the top of the file), and per (chunk, head) ddt with the chunk's dA / dD partial sums.
-__device__ __forceinline__ void add_slices(float (&v)[4], const float (&q)[SLICES][4], int n) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        v[e] = q[0][e];
-#pragma unroll
-        for (int s = 1; s < SLICES; ++s) v[e] += s < n ? q[s][e] : 0.f;
-    }
-}
-
-template <typename T>
-__global__ __launch_bounds__(NTHREADS) void k_bwd_final(SegParams sp, Vec vec, int n_dbc) {
+template <typename T, bool VEC>
+__global__ __launch_bounds__(NTHREADS) void k_bwd_final(SegParams sp) {
     __shared__ __attribute__((aligned(16))) Tiles L;
     __shared__ DdtLds D;
-    const int Q = sp.Q, N = sp.N;
-    int z = blockIdx.x;
+    const int Q = sp.Q, N = sp.N, NT = (Q + TM - 1) / TM, NN = (N + TM - 1) / TM, n_dbc = sp.G * 2 * NN * NT, per = n_dbc + sp.H;
+    const Place at = place(xcd_order(blockIdx.x, gridDim.x), per, sp.nc);
+    const int c = at.c, b = at.b;
+    int z = at.z;
     if (z >= n_dbc) {
-        z -= n_dbc;
-        const int h = z % sp.H, c = (z / sp.H) % sp.nc, b = z / (sp.H * sp.nc);
+        const int h = z - n_dbc;
         const int n32 = 2 * ((N + TM - 1) / TM), p32 = 2 * ((sp.P + TM - 1) / TM);
         ddt_finalize_body<4>(
             sp, &D, c, h, b,
@@ -882,21 +1071,17 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_final(SegParams sp, Vec vec, i
             [&](int64_t idx, float v) { IO<T>::st(sp.ddt, idx, v); });
         return;
     }
-    const int NT = (Q + TM - 1) / TM, NN = (N + TM - 1) / TM;
     const int r0 = (z % NT) * TM;
     z /= NT;
     const int n0 = (z % NN) * TM;
     z /= NN;
-    const int role = z & 1;
-    z >>= 1;
-    const int g = z % sp.G, c = (z / sp.G) % sp.nc, b = z / (sp.G * sp.nc), V = chunk_rows(sp, c, Q);
+    const int role = z & 1, g = z >> 1, V = chunk_rows(sp, c, Q);
     if (r0 >= V) return;
     const int64_t bcg = ((int64_t)b * sp.nc + c) * sp.G + g, QQ = (int64_t)Q * Q;
     const int dns = sp.dg_split, pns = sp.part_split;
     const float* dG = sp.dG + bcg * dns * QQ;
     const int64_t bbase = (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N;
     const int64_t bt = (int64_t)sp.G * N;
-    int buf = 0;
     f32x16 acc;
     const int n = n0 + tile_col();
     {   // start from the slices' head sums: their loads and the first tiles' are one round trip
@@ -916,39 +1101,45 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_final(SegParams sp, Vec vec, i
             for (int s = 1; s < SLICES; ++s) acc[r] += pv[s][r];
         }
     }
-    if (role == 0) {
-        const int kend = r0 + TM < V ? r0 + TM : V;
-        tile_gemm<true, false>(
-            acc, 0, kend,
-            [&](float (&v)[4], int r, int k, int k0) {
-                float q[SLICES][4];
+    struct Stage {
+        u32x4 a[SLICES][2], b[2];
+    };
+    // dG (role 0), or its transpose, with the slices added up on the way, times rows of B (role 1: C)
+    auto walk = [&](auto rows_along_k, int first, int steps, const void* rhs) {
+        constexpr bool KC = decltype(rows_along_k)::value;
+        chain<2, Stage>(
+            steps, L,
+            [&](Stage& R, int s, bool live) {
+                const int k0 = first + s * TK, kn = least(TK, V - k0);
 #pragma unroll
-                for (int s = 0; s < SLICES; ++s)
-                    ld_k4<float>(q[s], dG, s < dns ? s * QQ : 0, Q, r0, r, k0, k, V, V, (Q & 3) == 0 && (V & 3) == 0);
-                add_slices(v, q, dns);
+                for (int q = 0; q < SLICES; ++q) {
+                    const float* G = dG + (q < dns ? q * QQ : 0);
+                    if (KC) fetch<float, VEC>(R.a[q], true, part_of<float>(G, (int64_t)r0 * Q + k0, Q, least(TM, V - r0), Q - k0), live);
+                    else fetch<float, VEC>(R.a[q], false, part_of<float>(G, (int64_t)k0 * Q + r0, Q, kn, Q - r0), live);
+                }
+                fetch<T, VEC>(R.b, false, part_of<T>(rhs, bbase + n0 + k0 * bt, bt, kn, N - n0), live);
             },
-            [&](float (&v)[4], int r, int k) {
+            [&](Stage& R, int s, float* la, float* lb) {
+                u32x4 v[2];
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (k + e > r0 + r) v[e] = 0.f;
-            },
-            [&](float (&v)[4], int r, int k, int k0) { ld_r4<T>(v, sp.Bm, bbase + n0, bt, r, k0, k, N - n0, V); }, NoWeight{}, L, buf);
-    } else {
-        tile_gemm<false, false>(
-            acc, r0, V,
-            [&](float (&v)[4], int r, int k, int k0) {
-                float q[SLICES][4];
+                for (int e = 0; e < 2; ++e) {
+                    f32x4 t = unpack<float, VEC>(R.a[0][e]);
 #pragma unroll
-                for (int s = 0; s < SLICES; ++s) ld_r4<float>(q[s], dG, (s < dns ? s * QQ : 0) + r0, Q, r, k0, k, V - r0, V);
-                add_slices(v, q, dns);
-            },
-            [&](float (&v)[4], int r, int k) {
+                    for (int q = 1; q < SLICES; ++q) t += q < dns ? unpack<float, VEC>(R.a[q][e]) : (f32x4)(0.f);
+                    v[e] = __builtin_bit_cast(u32x4, t);
+                }
+                put<float, VEC>(v, KC, la, [&](f32x4& t, int hi, int lo, int piece) {  // on or below the diagonal
+                    const int k = first + s * TK, r = r0 + 32 * piece;
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (k + e < r0 + r) v[e] = 0.f;
+                    for (int e = 0; e < 4; ++e)
+                        if (KC ? k + lo + e > r + hi : k + hi < r + lo + e) t[e] = 0.f;
+                });
+                put<T, VEC>(R.b, false, lb, NoWeight{});
             },
-            [&](float (&v)[4], int r, int k, int k0) { ld_r4<T>(v, sp.Cm, bbase + n0, bt, r, k0, k, N - n0, V); }, NoWeight{}, L, buf);
-    }
+            [&](int, const float* la, const float* lb) { tile_mma<KC, false>(acc, la, lb); }, [] {});
+    };
+    if (role == 0) walk(std::true_type{}, 0, (least(r0 + TM, V) + TK - 1) / TK, sp.Bm);
+    else walk(std::false_type{}, r0, (V - r0 + TK - 1) / TK, sp.Cm);
     void* out = role == 0 ? sp.dC : sp.dB;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -959,50 +1150,56 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_final(SegParams sp, Vec vec, i
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-// 16-byte (fp32) / 8-byte (bf16) loads along P and N: sizes and every pointer and stride multiples of four elements
+// 16-byte (fp32) / 8-byte (bf16) loads: sizes and every pointer and stride multiples of four elements
 template <typename T>
-Vec vec_of(const SegParams& sp) {
+bool vec_ok(const SegParams& sp) {
     const uintptr_t m = 4 * sizeof(T) - 1;
-    Vec v;
-    v.x = sp.P % 4 == 0 && (((uintptr_t)sp.x | (uintptr_t)sp.dy) & m) == 0 && (sp.xs_b | sp.dys_b) % 4 == 0;
-    v.bc = sp.N % 4 == 0 && (((uintptr_t)sp.Bm | (uintptr_t)sp.Cm) & m) == 0 && sp.bcs_b % 4 == 0;
-    return v;
+    return ((sp.P | sp.N | sp.Q) & 3) == 0 && (((uintptr_t)sp.x | (uintptr_t)sp.dy | (uintptr_t)sp.Bm | (uintptr_t)sp.Cm) & m) == 0 &&
+           ((sp.xs_b | sp.dys_b | sp.bcs_b) & 3) == 0;
 }
 
-template <typename T>
+template <typename T, bool VEC>
 hipError_t scores_states(const SegParams& sp, int nroles, hipStream_t st) {
     const int NT = cdiv(sp.Q, TM);
     const int n_cb = sp.Bt * sp.nc * sp.G * (NT * (NT + 1) / 2);
     const int n_st = sp.Bt * sp.nc * sp.H * nroles * cdiv(sp.N, TM) * cdiv(sp.P, TM);
-    if (sp.raw.dt) SSDK_LAUNCH_LDS(K_CHUNK_STATE, st, (k_scores_states<T, true>), dim3(n_cb + n_st), dim3(NTHREADS), lds_bytes(sp.Q + NTHREADS / 64), sp, vec_of<T>(sp), n_cb, nroles);
-    else SSDK_LAUNCH_LDS(K_CHUNK_STATE, st, (k_scores_states<T, false>), dim3(n_cb + n_st), dim3(NTHREADS), lds_bytes(sp.Q + NTHREADS / 64), sp, vec_of<T>(sp), n_cb, nroles);
+    if (sp.raw.dt) SSDK_LAUNCH_LDS(K_CHUNK_STATE, st, (k_scores_states<T, true, VEC>), dim3(n_cb + n_st), dim3(NTHREADS), lds_bytes(sp.Q + NTHREADS / 64), sp, nroles);
+    else SSDK_LAUNCH_LDS(K_CHUNK_STATE, st, (k_scores_states<T, false, VEC>), dim3(n_cb + n_st), dim3(NTHREADS), lds_bytes(sp.Q + NTHREADS / 64), sp, nroles);
     return hipSuccess;
 }
 
-template <typename T>
-hipError_t fwd_segment(const SegParams& sp, bool need_y, hipStream_t st) {
-    if (!need_y) return hipSuccess;  // the backward pass restores the states inside its own launches
-    const hipError_t e = scores_states<T>(sp, 1, st);
+template <typename T, bool VEC>
+hipError_t fwd_segment(const SegParams& sp, hipStream_t st) {
+    const hipError_t e = scores_states<T, VEC>(sp, 1, st);
     if (e != hipSuccess) return e;
     SSDK_LAUNCH(K_SCAN_FWD, st, k_state_scan<false>, dim3(cdiv(sp.P * sp.N, NTHREADS), sp.H, sp.Bt), dim3(NTHREADS), sp);
-    SSDK_LAUNCH_LDS(K_CHUNK_OUT, st, k_chunk_out<T>, dim3(sp.Bt * sp.nc * sp.H, cdiv(sp.P, TM), cdiv(sp.Q, TM)), dim3(NTHREADS), lds_bytes(2 * sp.Q + 2 * TM), sp, vec_of<T>(sp));
+    SSDK_LAUNCH_LDS(K_CHUNK_OUT, st, (k_chunk_out<T, VEC>), dim3(sp.Bt * sp.nc * sp.H * cdiv(sp.P, TM) * cdiv(sp.Q, TM)), dim3(NTHREADS), lds_bytes(2 * sp.Q + 3 * TM), sp);
     return hipSuccess;
 }
 
-template <typename T>
+template <typename T, bool VEC>
 hipError_t bwd_segment(const SegParams& sp0, hipStream_t st) {
     SegParams sp = sp0;
     sp.nslice = cdiv(sp.P * sp.N, NTHREADS) * (NTHREADS / 64);  // partial sums written by k_state_scan: one per wave
     const int NT = cdiv(sp.Q, TM), NN = cdiv(sp.N, TM), bcg = sp.Bt * sp.nc * sp.G;
-    const hipError_t e = scores_states<T>(sp, 2, st);
+    const hipError_t e = scores_states<T, VEC>(sp, 2, st);
     if (e != hipSuccess) return e;
     SSDK_LAUNCH(K_SCAN_BWD, st, k_state_scan<true>, dim3(cdiv(sp.P * sp.N, NTHREADS), sp.H, sp.Bt), dim3(NTHREADS), sp);
     const int n_part = bcg * sp.part_split * 2 * NN * NT, n_dg = bcg * sp.dg_split * (NT * (NT + 1) / 2), n_u = sp.Bt * sp.nc * sp.H * NT * cdiv(sp.P, TM);
     const int per_token = 2 * sp.Q + 2 * TM > 6 * TM ? 2 * sp.Q + 2 * TM : 6 * TM;
-    SSDK_LAUNCH_LDS(K_BWD_MAIN, st, k_bwd_walk<T>, dim3(n_part + n_dg + n_u), dim3(NTHREADS), lds_bytes(per_token), sp, vec_of<T>(sp), n_part, n_dg);
+    SSDK_LAUNCH_LDS(K_BWD_MAIN, st, (k_bwd_walk<T, VEC>), dim3(n_part + n_dg + n_u), dim3(NTHREADS), lds_bytes(per_token), sp, std::gcd(sp.part_split, sp.dg_split));
     const int n_dbc = bcg * 2 * NN * NT;
-    SSDK_LAUNCH(K_DBC, st, k_bwd_final<T>, dim3(n_dbc + sp.Bt * sp.nc * sp.H), dim3(NTHREADS), sp, vec_of<T>(sp), n_dbc);
+    SSDK_LAUNCH(K_DBC, st, (k_bwd_final<T, VEC>), dim3(n_dbc + sp.Bt * sp.nc * sp.H), dim3(NTHREADS), sp);
     return hipSuccess;
+}
+
+template <typename T>
+hipError_t fwd_any(const SegParams& sp, hipStream_t st) {
+    return vec_ok<T>(sp) ? fwd_segment<T, true>(sp, st) : fwd_segment<T, false>(sp, st);
+}
+template <typename T>
+hipError_t bwd_any(const SegParams& sp, hipStream_t st) {
+    return vec_ok<T>(sp) ? bwd_segment<T, true>(sp, st) : bwd_segment<T, false>(sp, st);
 }
 
 }  // namespace
@@ -1022,11 +1219,12 @@ hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t s
 }
 
 hipError_t generic_forward_segment(const SegParams& sp, bool is_bf16, bool need_y, hipStream_t st) {
-    return is_bf16 ? fwd_segment<bf16_t>(sp, need_y, st) : fwd_segment<float>(sp, need_y, st);
+    if (!need_y) return hipSuccess;  // the backward pass restores the states inside its own launches
+    return is_bf16 ? fwd_any<bf16_t>(sp, st) : fwd_any<float>(sp, st);
 }
 
 hipError_t generic_backward_segment(const SegParams& sp, bool is_bf16, hipStream_t st) {
-    return is_bf16 ? bwd_segment<bf16_t>(sp, st) : bwd_segment<float>(sp, st);
+    return is_bf16 ? bwd_any<bf16_t>(sp, st) : bwd_any<float>(sp, st);
 }
 
 }  // namespace ssdk

@@ -27,22 +27,6 @@ namespace {
 using namespace mf;
 
 // ---------------------------------------------------------------------------------------------
-// Sums over a wave by lane exchanges of the vector ALUs: rows of 16 lanes, then across the rows.  Every lane ends with
-// the sum of the lanes up to its own (lane 63: of all).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_add(float v) {
-    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xF, true));
-}
-__device__ __forceinline__ float wave_prefix(float v) {
-    v = dpp_add<0x111, 0xF>(v);  // row_shr:1
-    v = dpp_add<0x112, 0xF>(v);
-    v = dpp_add<0x114, 0xF>(v);
-    v = dpp_add<0x118, 0xF>(v);
-    v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
 // Decay preparation of one chunk and head by one wave, lane l the tokens E l .. E l + E - 1: cum (chunk-local inclusive cumsum of
 // dt*A), dt in fp32, ein, eout.  Nothing waits for other waves (over LDS the prefix sums took sixteen barriers), and the waves
 // of a workgroup take neighbouring heads, i.e. read the same cache lines of dt.  In two halves, so that the loads can be under

@@ -48,6 +48,26 @@ struct RawDt {
 // max(v, 0) + log(1 + e^-|v|): no overflow
 static __device__ __forceinline__ float softplus(float v) { return fmaxf(v, 0.f) + log1pf(__expf(-fabsf(v))); }
 
+// Sums over a wave by lane exchanges of the vector ALUs: rows of 16 lanes, then across the rows.  Every lane ends with
+// the sum of the lanes up to its own (lane 63: of all).
+template <int CTRL, int ROWS>
+static __device__ __forceinline__ float dpp_add(float v) {
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xF, true));
+}
+static __device__ __forceinline__ float wave_prefix(float v) {
+    v = dpp_add<0x111, 0xF>(v);  // row_shr:1
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+// The sum over the wave, in every lane.
+static __device__ __forceinline__ float wave_total(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_prefix(v)), 63));
+}
+
 // One span of one layer, as the kernels see it: one or several consecutive checkpoint segments that share their
 // launches.  Tensor pointers are already offset to the first token of the span; batch strides are those of the
 // full tensors (elements).
