@@ -58,7 +58,6 @@ struct Pre {
     float sc[DualCfg<Q>::XV], sc2[DualCfg<Q>::XV];  // per-token scale factors, multiplied at staging time
     bf16x8 sv[DualCfg<Q>::SV];
     float cum, dtf, fac;
-    float Dh;       // D of the head
     bf16x8 own[4];  // reverse: the wave's own 32 rows of x as whole rows (for the epilogue's dot products)
 };
 
@@ -107,7 +106,6 @@ __device__ __forceinline__ void load_pre(Pre<Q>& pr, const SegParams& sp, int b,
             pr.dtf = sp.dtf[cbase + tid];
             pr.fac = REV ? sp.eout[cbase + tid] : sp.ein[cbase + tid];
         }
-        pr.Dh = sp.D[h];
     }
     if (piece == 1) {
 #pragma unroll
@@ -358,6 +356,7 @@ __device__ __forceinline__ void dual_body(const SegParams& sp, DualLds<Q>& L, in
     Pre<Q> pr;
 #pragma unroll
     for (int piece = 0; piece < 3; ++piece) load_pre<Q, REV>(pr, sp, b, c, h0, tid, 32 * T, piece);
+    wait_loads();
     for (int hh = 0; hh < hps; ++hh) {
         const int h = h0 + hh;
         // the thread index as the optimiser cannot see through: addresses derived from it are formed anew
@@ -367,7 +366,9 @@ __device__ __forceinline__ void dual_body(const SegParams& sp, DualLds<Q>& L, in
         SSDK_STAMP(EPI == 2 ? 0 : 3, 0);
         __syncthreads();  // every wave is done with the previous head's tiles
         SSDK_STAMP(EPI == 2 ? 0 : 3, 1);
-        cx.Dh = pr.Dh + ((sp.flags & SSD_FLAG_RESIDUAL) ? 1.f : 0.f);
+        // (scalar memory: as a vector load of the next head it was copied at the end of a head, and the copy waited for every load
+        // in flight in front of the head's stores, and the next head's staging for those)
+        cx.Dh = ((const __attribute__((address_space(4))) float*)sp.D)[h] + ((sp.flags & SSD_FLAG_RESIDUAL) ? 1.f : 0.f);
         store_pre<Q, REV>(pr, L, tv, w);
         SSDK_STAMP(EPI == 2 ? 0 : 3, 2);
         __syncthreads();

@@ -266,6 +266,7 @@ __global__ __launch_bounds__(OUTER_THR, 4) void mk_chunk_outer(SegParams sp, int
     bf16x8 fb[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) fb[ks] = frag_tr(L.bc, BPITCH, 16 * ks, 32 * nt, lane);
+    wait_loads();
     for (int hh = 0; hh < hps; ++hh) {
         const int h = h0 + hh;
         SSDK_STAMP(4, 0);
