@@ -51,11 +51,8 @@ struct FewParams {
     float eps;
 };
 
-// out[r, n] = sum_k f(x)[r, k] w[n, k] (+ res[r, n]) for r < rows <= R.  A wave owns CPW columns n and walks k
-// with 16-byte loads, so every weight is read once, in full cache lines; the few input rows come from the
-// caches.  MODE 0: f(x) = x.  MODE 1: f(x) = x / sqrt(mean x^2 + eps) * in_w.
-// A wave sees whole rows, so the mean comes out of the same loop and scales the finished sums.  With few rows
-// the operands of two k steps are requested before either is used (twice the bytes in flight per wave).
+// out[r, n] = sum_k f(x)[r, k] w[n, k] (+ res[r, n]) for r < rows <= R.  MODE 0: f(x) = x.  MODE 1: f(x) = x / sqrt(mean x^2 +
+// eps) * in_w; a workgroup sees whole rows, so the mean comes out of the same loop and scales the finished sums.
 // Workgroup ids are dealt round-robin over the 8 XCDs: neighbouring columns, which share cache lines of everything but w,
 // go to one XCD.
 __device__ __forceinline__ int xcd_block() {
@@ -83,7 +80,7 @@ struct FewOperands {
     int64_t cs_bs;
     const float *conv_w, *conv_b, *dt_bias;
     int off_xbc, off_dt, conv_dim;
-    int ks;       // matrix-core kernel: waves
+    int ks;       // waves of a workgroup
     bool stream;  // w by streaming loads
 };
 
@@ -133,136 +130,188 @@ __device__ __forceinline__ void move_pieces(const FewOperands& fo, int threads) 
     }
 }
 
-template <int MODE, int R, int CPW, bool STREAM>
-struct FewStep {
-    bf16x8 wv[CPW], xv[R];
-    float iw[MODE ? 8 : 1];
+// Rows that one or two tokens multiply: the vector ALUs.  A workgroup owns `cols` consecutive columns and its waves share out the
+// row in pieces of 512 k (16 bytes a lane); a wave keeps f(x) of its pieces in registers and walks the columns four at a time, the
+// eight behind them under way, so that w streams through without a pause while every other operand is read once a workgroup.  The
+// partial sums of the columns meet in LDS once, at the end, where the threads that finish a column have had everything else
+// they need since the start.  What bounds it is w from memory (5.5 TB/s of reads, 9.9 and 4.8 us for a 2.7B block's two), and what a
+// launch takes until its first load has landed.  us of the two products of a 2.7B block, one token, in their places of a step (input with
+// normalisation, convolution step and softplus; output with normalisation and residual): a workgroup per four columns with the row
+// over its four waves, which fetched f(x) anew and paid two trips to memory in a row, 13.6 and 8.6, now 12.5 and 7.5; a step of eight blocks
+// 203 -> 192, with two sequences 223 -> 197, at the width of 64 heads 143 -> 138 and 173 -> 155.
+constexpr int FEW_PIECE = 512, FEW_WAVES = 10, FEW_COLS = 64;
 
-    __device__ __forceinline__ void load(const FewParams& fp, const __bf16* w0, int k) {
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint32_t bits_of(float v) { return __builtin_bit_cast(uint32_t, v); }
+__device__ __forceinline__ float sum2(u32x2 q) {
+    const uint32_t a = q[0], b = q[1];
+    return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+}
+// Sums of four values over the wave; the lanes 16 c .. 16 c + 15 have that of value c.
+__device__ __forceinline__ float four_sums(const float (&a)[4]) {
+    const float s0 = sum2(__builtin_amdgcn_permlane32_swap(bits_of(a[0]), bits_of(a[2]), false, false));
+    const float s1 = sum2(__builtin_amdgcn_permlane32_swap(bits_of(a[1]), bits_of(a[3]), false, false));
+    float v = sum2(__builtin_amdgcn_permlane16_swap(bits_of(s0), bits_of(s1), false, false));
+    v = dpp_add<0x140, 0xF>(v);  // row_mirror
+    v = dpp_add<0x141, 0xF>(v);  // row_half_mirror
+    v = dpp_add<0x4E, 0xF>(v);   // quad_perm 2 3 0 1
+    return dpp_add<0xB1, 0xF>(v);
+}
+
+// PPW: pieces of a wave that it keeps f(x) of (longer rows go by in turns).  STEP: with the convolution step (fo.cs).  Template
+// arguments like MODE: a branch around loads ends in a wait for them.
+template <int MODE, int R, int PPW, bool STEP, bool STREAM>
+__global__ __launch_bounds__(FEW_WAVES * 64) void k_linear_few(FewParams fp, FewOperands fo, int cols) {
+    __shared__ float red[FEW_COLS * R][FEW_WAVES], sq[R][FEW_WAVES];
+    const int NW = fo.ks, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n0 = blockIdx.x * cols, nc = fp.N - n0 < cols ? fp.N - n0 : cols, nb = (nc + 3) >> 2;
+    // columns and pieces beyond the end: nothing is fetched, zeros come back
+    const uint32_t rowbytes = (uint32_t)fp.K * 2, bytes = (uint32_t)nc * rowbytes;
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)(fp.w + (int64_t)n0 * fp.K), 0, bytes, 0x00020000);
+    // (row fr, column n0 + fc) that thread tid finishes
+    auto place = [&](int t, int& r, int& c) {
+        r = R == 1 ? 0 : t / cols;
+        c = t - r * cols;
+        return r < fp.rows && c < nc;
+    };
+    int fr, fc;
+    const bool finish = place(tid, fr, fc);
+    const int frl = finish ? fr : 0, fnl = n0 + (finish ? fc : 0);
+    const int range = FEW_PIECE * PPW * NW;
+    float ss[R];
 #pragma unroll
-        for (int c = 0; c < CPW; ++c) wv[c] = fetch<STREAM>((const bf16x8*)(w0 + (int64_t)c * fp.K + k));
-        if (MODE) {
-            const f32x4 a = *(const f32x4*)(fp.in_w + k), b = *(const f32x4*)(fp.in_w + k + 4);
+    for (int r = 0; r < R; ++r) ss[r] = 0.f;
+    StepTaps taps;
+    float res = 0.f;
+    for (int kb = 0; kb < fp.K; kb += range) {
+        uint32_t off[PPW];
+        bf16x8 xv[R][PPW];
+        f32x4 iw[MODE ? PPW : 1][2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                iw[e] = a[e];
-                iw[4 + e] = b[e];
+        for (int j = 0; j < PPW; ++j) {
+            const int k = kb + FEW_PIECE * (w + NW * j) + 8 * lane, kc = k < fp.K ? k : 0;
+            off[j] = k < fp.K ? (uint32_t)k * 2 : bytes;
+#pragma unroll
+            for (int r = 0; r < R; ++r) xv[r][j] = *(const bf16x8*)(fp.x + (r < fp.rows ? r : 0) * fp.ldx + kc);
+            if (MODE) {
+                iw[j][0] = *(const f32x4*)(fp.in_w + kc);
+                iw[j][1] = *(const f32x4*)(fp.in_w + kc + 4);
             }
         }
+        u32x4 W[2][4][PPW];
+        auto load = [&](u32x4 (&b)[4][PPW], int n) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (r < fp.rows) xv[r] = *(const bf16x8*)(fp.x + r * fp.ldx + k);
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int j = 0; j < PPW; ++j) b[c][j] = __builtin_amdgcn_raw_buffer_load_b128(rw, off[j] + (uint32_t)(4 * n + c) * rowbytes, 0, STREAM ? 2 : 0);
+        };
+        load(W[0], 0);
+        load(W[1], 1);
+        if (kb == 0) {
+            if (STEP) taps = step_taps(fo, frl, fnl);
+            if (fp.res) res = (float)fp.res[frl * fp.ldres + fnl];
         }
-    }
-
-    __device__ __forceinline__ void use(const FewParams& fp, float (&acc)[R][CPW], float (&ss)[R]) const {
+        float f[R][PPW][8];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (r < fp.rows) {
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < PPW; ++j) {
+                const bool in = off[j] < bytes && r < fp.rows;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    float v = (float)xv[r][e];
+                    float v = in ? (float)xv[r][j][e] : 0.f;
                     if (MODE) {
                         ss[r] = fmaf(v, v, ss[r]);
-                        v *= iw[e];
+                        v *= in ? iw[j][e >> 2][e & 3] : 0.f;
                     }
-#pragma unroll
-                    for (int c = 0; c < CPW; ++c) acc[r][c] = fmaf(v, (float)wv[c][e], acc[r][c]);
+                    f[r][j][e] = v;
                 }
             }
+        auto use = [&](const u32x4 (&b)[4][PPW], int n) {
+            float acc[R][4];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[r][c] = 0.f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int j = 0; j < PPW; ++j) {
+                    const bf16x8 v = __builtin_bit_cast(bf16x8, b[c][j]);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+#pragma unroll
+                        for (int r = 0; r < R; ++r) acc[r][c] = fmaf(f[r][j][e], (float)v[e], acc[r][c]);
+                }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float v = four_sums(acc[r]);
+                float* at = &red[(4 * n + (lane >> 4)) * R + r][w];
+                if ((lane & 15) == 0) *at = kb ? *at + v : v;
+            }
+        };
+        int n = 0;
+        for (; n + 2 <= nb; n += 2) {
+            use(W[0], n);
+            load(W[0], n + 2);
+            use(W[1], n + 1);
+            load(W[1], n + 3);
         }
+        if (n < nb) use(W[0], n);
     }
-};
-
-// KS waves of a workgroup share a wave's columns and take every KS-th k step each (a wave that walks all of a
-// long row alone waits for one load after the other: more, shorter waves keep more bytes in flight); their
-// partial sums meet in LDS.
-// STEP: with the convolution step (fo.cs).  A template argument like MODE: a branch around loads ends in a wait for them.
-template <int MODE, int R, int CPW, int KS, bool STEP, bool STREAM>
-__global__ __launch_bounds__(256) void k_linear_few(FewParams fp, FewOperands fo) {
-    __shared__ float red[4][R * (CPW + 1)];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int slot = wv / KS, kp = wv % KS;  // which columns of the workgroup, which share of k
-    const int n0 = (blockIdx.x * (4 / KS) + slot) * CPW;
-    const bool live = n0 < fp.N;
-    float acc[R][CPW], ss[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        ss[r] = 0.f;
-#pragma unroll
-        for (int c = 0; c < CPW; ++c) acc[r][c] = 0.f;
-    }
-    // after the sums: lane r CPW + c of the wave with kp = 0 finishes (row r, column n0 + c)
-    const int fr = lane / CPW, fn = n0 + lane % CPW;
-    const bool finish = live && kp == 0 && lane < R * CPW && fr < fp.rows && fn < fp.N;
-    const __bf16* w0 = fp.w + (int64_t)n0 * fp.K;
-    constexpr int KSTEP = 512 * KS;  // k between a wave's consecutive steps
-    if (live) {
-        for (int k = lane * 8 + 512 * kp; k < fp.K; k += 2 * KSTEP) {
-            FewStep<MODE, R, CPW, STREAM> a, b;
-            const bool two = k + KSTEP < fp.K;
-            a.load(fp, w0, k);
-            if (two) b.load(fp, w0, k + KSTEP);
-            a.use(fp, acc, ss);
-            if (two) b.use(fp, acc, ss);
-        }
-    }
-    // asked for here, behind the sums: held over the loop it would cost the fifth wave per SIMD (2 us over 54 MB of w)
-    StepTaps taps;
-    if (STEP) taps = step_taps(fo, fr < fp.rows ? fr : 0, fn < fp.N ? fn : fp.N - 1);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (MODE) ss[r] = wave_sum(ss[r]);
-#pragma unroll
-        for (int c = 0; c < CPW; ++c) acc[r][c] = wave_sum(acc[r][c]);
-    }
-    if (lane == 0) {
+    if (MODE) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            red[wv][r * (CPW + 1) + CPW] = ss[r];
-#pragma unroll
-            for (int c = 0; c < CPW; ++c) red[wv][r * (CPW + 1) + c] = acc[r][c];
+            const float t = wave_total(ss[r]);
+            if (lane == 0) sq[r][w] = t;
         }
     }
     __syncthreads();
-    move_pieces(fo, 256);
-    if (!finish) return;
-    float v = 0.f, sq = 0.f;
-#pragma unroll
-    for (int q = 0; q < KS; ++q) {  // fixed order: the result does not depend on which wave finished first
-        sq += red[slot * KS + q][fr * (CPW + 1) + CPW];
-        v += red[slot * KS + q][fr * (CPW + 1) + lane % CPW];
+    for (int t = tid; t < R * cols; t += 64 * NW) {
+        int r, c;
+        if (!place(t, r, c)) continue;
+        float v = 0.f, q2 = 0.f;
+        for (int q = 0; q < NW; ++q) {  // fixed order: the result does not depend on which wave finished first
+            v += red[c * R + r][q];
+            if (MODE) q2 += sq[r][q];
+        }
+        const int n = n0 + c;
+        if (MODE) v *= rsqrtf(q2 / (float)fp.K + fp.eps);
+        if (fp.res) v += t == tid ? res : (float)fp.res[r * fp.ldres + n];
+        const __bf16 ob = (__bf16)v;
+        fp.out[r * fp.ldo + n] = STEP ? step_finish(fo, t == tid ? taps : step_taps(fo, r, n), r, n, ob) : ob;
     }
-    if (MODE) v *= rsqrtf(sq / (float)fp.K + fp.eps);
-    if (fp.res) v += (float)fp.res[fr * fp.ldres + fn];
-    const __bf16 ob = (__bf16)v;
-    fp.out[fr * fp.ldo + fn] = STEP ? step_finish(fo, taps, fr, fn, ob) : ob;
+    move_pieces(fo, 64 * NW);
 }
 
-template <int MODE, int CPW, int KS, bool STEP, bool STREAM>
-hipError_t launch_few_cks(const FewParams& fp, const FewOperands& fo, hipStream_t st) {
-    const int slots = (fp.N + CPW - 1) / CPW;  // groups of CPW columns
-    const dim3 grid((unsigned)((slots + 4 / KS - 1) / (4 / KS))), block(256);
-    if (fp.rows <= 1) hipLaunchKernelGGL((k_linear_few<MODE, 1, CPW, KS, STEP, STREAM>), grid, block, 0, st, fp, fo);
-    else hipLaunchKernelGGL((k_linear_few<MODE, FEW_ROWS_VALU, CPW, KS, STEP, STREAM>), grid, block, 0, st, fp, fo);
+template <int MODE, int PPW, bool STEP, bool STREAM>
+hipError_t launch_few_kernel(const FewParams& fp, const FewOperands& fo, int cols, hipStream_t st) {
+    const dim3 grid((unsigned)((fp.N + cols - 1) / cols)), block(64 * fo.ks);
+    if (fp.rows <= 1) hipLaunchKernelGGL((k_linear_few<MODE, 1, PPW, STEP, STREAM>), grid, block, 0, st, fp, fo, cols);
+    else hipLaunchKernelGGL((k_linear_few<MODE, FEW_ROWS_VALU, PPW, STEP, STREAM>), grid, block, 0, st, fp, fo, cols);
     return hipGetLastError();
 }
 
-template <int MODE, int CPW, int KS>
-hipError_t launch_few_ck(const FewParams& fp, const FewOperands& fo, hipStream_t st) {
-    if (fo.stream) return fo.cs ? launch_few_cks<MODE, CPW, KS, true, true>(fp, fo, st) : launch_few_cks<MODE, CPW, KS, false, true>(fp, fo, st);
-    return fo.cs ? launch_few_cks<MODE, CPW, KS, true, false>(fp, fo, st) : launch_few_cks<MODE, CPW, KS, false, false>(fp, fo, st);
+template <int MODE, int PPW>
+hipError_t launch_few_pieces(const FewParams& fp, const FewOperands& fo, int cols, hipStream_t st) {
+    if (fo.stream) return fo.cs ? launch_few_kernel<MODE, PPW, true, true>(fp, fo, cols, st) : launch_few_kernel<MODE, PPW, false, true>(fp, fo, cols, st);
+    return fo.cs ? launch_few_kernel<MODE, PPW, true, false>(fp, fo, cols, st) : launch_few_kernel<MODE, PPW, false, false>(fp, fo, cols, st);
 }
 
-// Long rows (the block's two products): four columns per wave share the fetched (and transformed) input rows --
-// with one column per wave the input rows, re-read by every wave, are more cache traffic than the weights --
-// and k is split over the four waves of the workgroup, which keeps as many waves as there are columns.  Short
-// rows: no split.
+// As many waves a workgroup as share the row evenly, each with one piece of it up to rows of 5120 and two beyond, and as few columns
+// as give every compute unit about ten waves (80 KB of w under way), the same number of workgroups in each: eight a unit with some
+// units holding twice as many as others took 3 % of a step.
 template <int MODE>
-hipError_t launch_few(const FewParams& fp, const FewOperands& fo, hipStream_t st) {
-    if (fp.N >= 8192) return fp.K >= 2048 ? launch_few_ck<MODE, 4, 4>(fp, fo, st) : launch_few_ck<MODE, 2, 1>(fp, fo, st);
-    if (fp.N >= 4096) return fp.K >= 2048 ? launch_few_ck<MODE, 1, 2>(fp, fo, st) : launch_few_ck<MODE, 1, 1>(fp, fo, st);
-    return fp.K >= 2048 ? launch_few_ck<MODE, 4, 4>(fp, fo, st) : launch_few_ck<MODE, 1, 1>(fp, fo, st);
+hipError_t launch_few(const FewParams& fp, FewOperands fo, hipStream_t st) {
+    const int pieces = (fp.K + FEW_PIECE - 1) / FEW_PIECE, ppw = pieces <= FEW_WAVES ? 1 : 2;
+    const int need = (pieces + ppw - 1) / ppw, turns = (need + FEW_WAVES - 1) / FEW_WAVES;
+    fo.ks = (need + turns - 1) / turns;
+    const int units = 256 * ((10 + fo.ks / 2) / fo.ks);
+    int cols = (fp.N + units - 1) / units;
+    cols = cols < FEW_COLS ? cols : FEW_COLS;
+    if (ppw == 1) return launch_few_pieces<MODE, 1>(fp, fo, cols, st);
+    return launch_few_pieces<MODE, 2>(fp, fo, cols, st);
 }
 
 // More than a few rows (several sequences generated together): the same product on the matrix cores.  A
