@@ -80,7 +80,7 @@ struct FewOperands {
     int64_t cs_bs;
     const float *conv_w, *conv_b, *dt_bias;
     int off_xbc, off_dt, conv_dim;
-    int ks;       // waves of a workgroup
+    int ks, cols;  // waves of a workgroup, columns of one
     bool stream;  // w by streaming loads
 };
 
@@ -314,22 +314,25 @@ hipError_t launch_few(const FewParams& fp, FewOperands fo, hipStream_t st) {
     return launch_few_pieces<MODE, 2>(fp, fo, cols, st);
 }
 
-// More than a few rows (several sequences generated together): the same product on the matrix cores.  A
-// workgroup owns 16 columns of w; its KS waves share out pieces of 256 k and each runs 16 x 16 x 32 MFMAs with the
-// (at most 16) input rows as the other operand, so the arithmetic is out of the way and the kernel again only
-// streams w; the partial tiles meet in LDS.
-// What bounds it is the number of cache lines an access touches: w is fetched as half rows of 512 contiguous bytes per
-// half wave and turned into operands through LDS, and the input rows come in operand order (16 bytes per row and eight k,
-// rows adjacent: `packed_at`) from the kernel before.  2560 x 10576 / 5120 x 2560 with 16 rows: 22 / 15 us with operands
-// fetched straight from w's rows (16 lines an access), 16 / 11 with w through LDS, 13.4 / 8.6 with packed input too; reading
-// w alone takes 9.9 / 5.9.
+// More than a few rows (several sequences generated together): the same product on the matrix cores.  A workgroup owns `cols`
+// consecutive columns; its waves share out the row in pieces of 256 k, one each up to rows of 2560 and two up to 5120, and keep the (at
+// most 16) input rows of theirs as operands in registers while they walk the columns in tiles of 16, the next piece of w under way,
+// one 16 x 16 x 32 MFMA per 32 k.  The partial tiles meet in LDS once, at the end.  The arithmetic is out of the way and the kernel
+// again only streams w.  What bounds it is the number of cache lines an access touches: w is fetched as half rows of 512 contiguous
+// bytes per half wave and turned into operands through LDS, and the input rows come in operand order (16 bytes per row and eight k,
+// rows adjacent: `packed_at`) from the kernel before.  2560 x 10576 / 5120 x 2560 with 16 rows: 22 / 15 us with operands fetched
+// straight from w's rows (16 lines an access), 16 / 11 with w through LDS, 13.4 / 8.6 with packed input too; reading w alone takes
+// 9.9 / 5.9.  Then the way to the first load: everything the launch waits for is asked for before anything is waited for, w first (a
+// sum that the compiler had moved in front of it, or a loop around a row that needs one turn, costs a trip to memory).  In their
+// places of a step of 16 sequences a workgroup of eight waves per tile, two or three pieces to a wave one behind the other, took 15.7 /
+// 10.3 us, this 13.2 / 9.6; the step of eight blocks 340 -> 315, with three sequences 257 -> 225.
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
 // Where (row, k) lies in the packed order.
 __device__ __forceinline__ int64_t packed_at(int row, int k) { return ((int64_t)(k >> 3) * 16 + row) * 8 + (k & 7); }
 
 constexpr int PIECE = 256, WPITCH = PIECE * 2 + 16;  // k per piece; bytes per LDS row of a piece of w
-constexpr int MFMA_WAVES = 8, MAX_GROUPS = 8;
+constexpr int MFMA_WAVES = 10, MFMA_TILES = 4, MFMA_COLS = 16, MAX_GROUPS = 8;  // waves, tiles of a workgroup at most
 // Up to eight rows leave rows of a tile free: they carry what rounding the operand x in_w to bf16 left of the live rows, and
 // the finished sums of a row's parts are added.  Up to four rows take three parts (rows r, r + 4, r + 8: all 24 bits, what the
 // vector ALUs compute one and two rows with), up to eight two (r, r + 8: 16 bits); more rows one.  The extra parts cost
@@ -348,65 +351,37 @@ __device__ __forceinline__ void pack_operand(__bf16* pack, int row, int k, float
     pack[packed_at(row + part_step(parts), k)] = mid;
     if (parts == 3) pack[packed_at(row + 8, k)] = (__bf16)(v - (float)mid);
 }
-inline size_t few_mfma_lds(int ks) { return (size_t)ks * 16 * WPITCH + (size_t)ks * 1024 + 16 * 17 * 4; }
+inline size_t few_mfma_lds(int ks, int tiles) { return (size_t)ks * 16 * WPITCH + (size_t)tiles * ks * 1024 + 16 * 17 * 4; }
 static_assert(MAX_GROUPS * 16 <= 16 * 17, "");
 
 // SRC 0: rows of x.  SRC 1: RMS normalisation over all of K times in_w, its squares summed on the way (the operand is
 // x in_w, 1 / rms scales the finished sums).  SRC 2: packed rows, already times in_w, with `ssq` the partial
 // sums of squares of their producer (nparts per group of K / groups, row r of part i at ssq[16 i + r]).  SRC 3: packed rows,
 // no normalisation.  PARTS: row_parts(rows) (SRC 0: 1, rows of x are bf16 values as they are).
-template <int SRC, bool STEP, int PARTS, bool STREAM>
+// PPW: pieces of a wave that it keeps operands of; longer rows go by in turns (SRC 1: one, two of them and what their
+// normalisation takes do not fit the registers).
+template <int SRC, bool STEP, int PARTS, bool STREAM, int PPW, bool TURNS>
 __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams fp, FewOperands fo) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    const int KS = fo.ks, nthr = 64 * KS, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int KS = fo.ks, nthr = 64 * KS, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     char* wt = lds + wv * 16 * WPITCH;
-    float* part = (float*)(lds + KS * 16 * WPITCH);  // [KS][256]
-    float* rs = part + KS * 256;                     // [groups][16]: 1 / rms, or (one group) [16][17]: shares of the squares
-    const int blk = xcd_block(), n0 = blk * 16;
+    const int blk = xcd_block(), n0 = blk * fo.cols, tiles = (fo.cols + 15) / 16, ncols = fp.N - n0 < fo.cols ? fp.N - n0 : fo.cols;
+    float* part = (float*)(lds + KS * 16 * WPITCH);  // [tiles][KS][256]
+    float* rs = part + tiles * KS * 256;             // [groups][16]: 1 / rms, or (one group) [16][17]: shares of the squares
     const int col = lane & 15, kq = lane >> 4;   // operand lanes: row of x / column of w, quarter of a 32-wide k step
     const int r2 = lane >> 5, l32 = lane & 31;   // fetching lanes: two columns of w at a time, 32 vectors of a piece each
-    const int pieces = (fp.K + PIECE - 1) / PIECE;
     constexpr int pstep = part_step(PARTS);
     const int xrow = SRC == 1 ? col & (pstep - 1) : col;
     const __bf16* xr = fp.x + (SRC >= 2 ? (int64_t)0 : (int64_t)(xrow < fp.rows ? xrow : 0) * fp.ldx);
     constexpr bool norm = SRC == 2;
-    constexpr int PU = 10;  // partial sums of squares asked for ahead of everything else (per thread)
+    // columns and k beyond the end: nothing is fetched, zeros come back
+    const uint32_t rowbytes = (uint32_t)fp.K * 2, bytes = (uint32_t)ncols * rowbytes;
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)(fp.w + (int64_t)n0 * fp.K), 0, bytes, 0x00020000);
+    // the packed operand: zeros from its end on
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)fp.x, 0, SRC >= 2 ? (uint32_t)fp.K * 32 : 0, 0x00020000);
+    constexpr int PU = 10;  // partial sums of squares asked for ahead (per thread)
     float sp[PU];
     const int TQ = nthr < 256 ? nthr >> 4 : 16;  // threads that share a row's sum
-    if (norm) {
-#pragma unroll
-        for (int u = 0; u < PU; ++u) {
-            const int i = (tid >> 4) + TQ * u;
-            sp[u] = fo.ssq[16 * (i < fo.nparts ? i : 0) + (tid & 15)];
-        }
-    }
-    bf16x8 v[8], a[8];
-    f32x4 iw[SRC == 1 ? 8 : 1][2];
-    auto load = [&](int pc) {
-        const int kk = pc * PIECE + 8 * l32, kc = kk < fp.K ? kk : 0;  // K is a multiple of 8; beyond it the other operand is zero
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int n = n0 + 2 * j + r2;
-            v[j] = fetch<STREAM>((const bf16x8*)(fp.w + (int64_t)(n < fp.N ? n : fp.N - 1) * fp.K + kc));
-        }
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            int k = pc * PIECE + 32 * s + 8 * kq;
-            k = k < fp.K ? k : 0;
-            a[s] = *(const bf16x8*)(SRC >= 2 ? xr + packed_at(col, k) : xr + k);
-            if (SRC == 1) {
-                iw[s][0] = *(const f32x4*)(fp.in_w + k);
-                iw[s][1] = *(const f32x4*)(fp.in_w + k + 4);
-            }
-        }
-    };
-    StepTaps taps;
-    {   // the (row, column) thread tid finishes
-        const int l = tid >> 2, r = 4 * (l >> 4) + (tid & 3), n = n0 + (l & 15);
-        if (STEP) taps = step_taps(fo, r < fp.rows ? r : 0, n < fp.N ? n : fp.N - 1);
-    }
-    int pc = wv;
-    if (pc < pieces) load(pc);
     // One group: its 1 / rms scales the finished sums, so nothing waits for it here.  Several: each piece of k lies inside
     // one group and is scaled before it is added.
     const bool norm_late = norm && fo.groups == 1;
@@ -415,85 +390,172 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
         float t = 0.f;
         if (ahead) {
 #pragma unroll
-            for (int u = 0; u < PU; ++u) t += (tid >> 4) + TQ * u < fo.nparts ? sp[u] : 0.f;
+            for (int u = 0; u < PU; ++u) {
+                float s = sp[u];
+                asm volatile("" : "+v"(s));  // here: the sum is not to move to where everything would wait for these loads
+                t += (tid >> 4) + TQ * u < fo.nparts ? s : 0.f;
+            }
         }
         for (int i = (tid >> 4) + (ahead ? TQ * PU : 0); i < fo.nparts; i += TQ) t += q[16 * i + (tid & 15)];
         return t;
     };
-    if (norm && !norm_late) {
-        for (int g = 0; g < fo.groups; ++g) {
-            if (tid < 256) part[(tid & 15) * 16 + (tid >> 4)] = row_share(g, g == 0);
-            __syncthreads();
-            if (tid < 16) {
-                float t = 0.f;
-                for (int q = 0; q < TQ; ++q) t += part[tid * 16 + q];
-                rs[g * 16 + tid] = rsqrtf(t / (float)(fp.K / fo.groups) + fp.eps);
+    // the (row, column) of output t: a wave of t has four rows, all 16 columns
+    auto row_of = [&](int t) { return 4 * ((t >> 6) & 3) + (t & 3); };
+    auto col_of = [&](int t) { return 16 * (t >> 8) + ((t >> 2) & 15); };  // (from n0 on)
+    StepTaps taps;  // of the thread's first output
+    float ss = 0.f;
+    uint32_t off[PPW];
+    u32x4 v[8];
+    auto aim = [&](int kb) {
+#pragma unroll
+        for (int j = 0; j < PPW; ++j) {
+            const int kk = kb + (wv + KS * j) * PIECE + 8 * l32;
+            off[j] = kk < fp.K ? (uint32_t)kk * 2 + (uint32_t)r2 * rowbytes : bytes;
+        }
+    };
+    auto load = [&](int t, int j) {
+        const uint32_t o = off[j] + (uint32_t)t * 16 * rowbytes;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, o + (uint32_t)(2 * i) * rowbytes, 0, STREAM ? 2 : 0);
+    };
+    aim(0);
+    load(0, 0);
+    bf16x8 a[PPW][8];
+    auto operands = [&](int kb) {
+#pragma unroll
+        for (int j = 0; j < PPW; ++j)
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const int k = kb + (wv + KS * j) * PIECE + 32 * s + 8 * kq;
+                if (SRC >= 2) a[j][s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rx, (uint32_t)packed_at(col, k) * 2, 0, 0));
+                if (SRC == 0) a[j][s] = *(const bf16x8*)(xr + (k < fp.K ? k : 0));
             }
-            __syncthreads();
+    };
+    operands(0);
+    __builtin_amdgcn_sched_barrier(0);  // first what the whole product waits for
+    auto taps_of = [&](int t) {
+        const int r = row_of(t), n = n0 + col_of(t);
+        return step_taps(fo, r < fp.rows ? r : 0, n < fp.N ? n : fp.N - 1);
+    };
+    if (STEP) taps = taps_of(tid);
+    if (norm) {
+#pragma unroll
+        for (int u = 0; u < PU; ++u) {
+            const int i = (tid >> 4) + TQ * u;
+            sp[u] = fo.ssq[16 * (i < fo.nparts ? i : 0) + (tid & 15)];
         }
     }
-    f32x4v acc = {0.f, 0.f, 0.f, 0.f};
-    float ss = 0.f;
-    for (; pc < pieces; pc += KS) {
+    for (int kb = 0;;) {
+        if (TURNS && kb) operands(kb);
+        if (norm && !norm_late && kb == 0) {
+            for (int g = 0; g < fo.groups; ++g) {
+                if (tid < 256) part[(tid & 15) * 16 + (tid >> 4)] = row_share(g, g == 0);
+                __syncthreads();
+                if (tid < 16) {
+                    float t = 0.f;
+                    for (int q = 0; q < TQ; ++q) t += part[tid * 16 + q];
+                    rs[g * 16 + tid] = rsqrtf(t / (float)(fp.K / fo.groups) + fp.eps);
+                }
+                __syncthreads();
+            }
+        }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) *(bf16x8*)(wt + (2 * j + r2) * WPITCH + 16 * l32) = v[j];
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // a wave's own rows: no barrier
-        f32x4v t = {0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < PPW; ++j)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const bool in = pc * PIECE + 32 * s + 8 * kq < fp.K;
-            bf16x8 av;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
+            for (int h = 0; h < 8; h += 4) {
+                const int k0 = kb + (wv + KS * j) * PIECE + 32 * h + 8 * kq;
+                f32x4 iw[4][2];
                 if (SRC == 1) {
-                    const float x = in ? (float)a[s][e] : 0.f;
-                    ss = fmaf(x, x, ss);
-                    float xw = x * iw[s][e >> 2][e & 3];
-                    av[e] = (__bf16)xw;
-                    if (PARTS > 1) {
-                        xw = rest_of(xw, av[e]);
-                        if (col >= pstep) av[e] = (__bf16)xw;
+                    __builtin_amdgcn_sched_barrier(0);  // not all of the loads at once: registers
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        const int kc = k0 + 32 * s < fp.K ? k0 + 32 * s : 0;
+                        a[j][h + s] = *(const bf16x8*)(xr + kc);
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) iw[s][e] = *(const f32x4*)(fp.in_w + kc + 4 * e);
                     }
-                    if (PARTS > 2) {
-                        xw = rest_of(xw, av[e]);
-                        if (col >= 2 * pstep) av[e] = (__bf16)xw;
+                }
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const bool in = k0 + 32 * s < fp.K;
+                    bf16x8 av = a[j][h + s];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        if (SRC == 1) {
+                            const float x = in ? (float)av[e] : 0.f;
+                            ss = fmaf(x, x, ss);
+                            float xw = in ? x * iw[s][e >> 2][e & 3] : 0.f;
+                            av[e] = (__bf16)xw;
+                            if (PARTS > 1) {
+                                xw = rest_of(xw, av[e]);
+                                if (col >= pstep) av[e] = (__bf16)xw;
+                            }
+                            if (PARTS > 2) {
+                                xw = rest_of(xw, av[e]);
+                                if (col >= 2 * pstep) av[e] = (__bf16)xw;
+                            }
+                        } else if (SRC == 0 && !in) {
+                            av[e] = (__bf16)0.f;
+                        }
                     }
-                } else {
-                    av[e] = in ? a[s][e] : (__bf16)0.f;
+                    u32x4 words = __builtin_bit_cast(u32x4, av);
+                    if (SRC == 1) asm volatile("" : "+v"(words));  // packed from here on: eight registers each otherwise
+                    a[j][h + s] = __builtin_bit_cast(bf16x8, words);
                 }
             }
-            // t[i] = out[row 4 kq + i][column n0 + col]
-            t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, *(const bf16x8*)(wt + col * WPITCH + 64 * s + 16 * kq), t, 0, 0, 0);
-        }
-        if (norm && !norm_late) {
-            const float4 q = *(const float4*)(rs + (int)((int64_t)pc * PIECE * fo.groups / fp.K) * 16 + 4 * (kq & (pstep / 4 - 1)));
-            acc[0] += t[0] * q.x;
-            acc[1] += t[1] * q.y;
-            acc[2] += t[2] * q.z;
-            acc[3] += t[3] * q.w;
-        } else {
+        for (int t = 0; t < tiles; ++t) {
+            f32x4v acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] += t[i];
+            for (int j = 0; j < PPW; ++j) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) *(u32x4*)(wt + (2 * i + r2) * WPITCH + 16 * l32) = v[i];
+                if (j + 1 < PPW || t + 1 < tiles) load(j + 1 < PPW ? t : t + 1, j + 1 < PPW ? j + 1 : 0);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // a wave's own rows: no barrier
+                f32x4v d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < 8; ++s)  // d[i] = out[row 4 kq + i][column col of the tile]
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j][s], *(const bf16x8*)(wt + col * WPITCH + 64 * s + 16 * kq), d, 0, 0, 0);
+                asm volatile("" ::: "memory");  // the next rows come in behind these reads
+                if (norm && !norm_late) {
+                    const int g = (int)((int64_t)(kb + (wv + KS * j) * PIECE) * fo.groups / fp.K);
+                    const float4 q = *(const float4*)(rs + (g < fo.groups ? g : 0) * 16 + 4 * (kq & (pstep / 4 - 1)));
+                    acc[0] += d[0] * q.x;
+                    acc[1] += d[1] * q.y;
+                    acc[2] += d[2] * q.z;
+                    acc[3] += d[3] * q.w;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[i] += d[i];
+                }
+            }
+            f32x4v* at = (f32x4v*)(part + (t * KS + wv) * 256 + lane * 4);
+            if (TURNS && kb) acc += *at;
+            *at = acc;
         }
-        if (pc + KS < pieces) load(pc + KS);
+        kb += PIECE * PPW * KS;
+        if (!TURNS || kb >= fp.K) break;
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the compiler would otherwise have the first turn wait as well
+        aim(kb);
+        load(0, 0);
     }
     if (SRC == 1) {  // the row's squares of this wave's pieces
         ss += __shfl_xor(ss, 16, 64);
         ss += __shfl_xor(ss, 32, 64);
         if (lane < 16) ((float*)wt)[lane] = ss;  // the wave's rows of w are used up
     }
-    *(f32x4v*)(part + wv * 256 + lane * 4) = acc;
     if (norm_late && tid < 256) rs[(tid & 15) * 17 + (tid >> 4)] = row_share(0, true);
     __syncthreads();
-    for (int t = tid; t < 256; t += nthr) {
+    auto finish = [&](int t, const StepTaps& tap) {
+        const float* p = part + (t >> 8) * KS * 256;
+        const int tt = t & 255;
         float o = 0.f;
-        for (int q = 0; q < KS; ++q) o += part[q * 256 + t];
-        if (PARTS > 1 && t < 128) {  // row r + pstep
-            for (int q = 0; q < KS; ++q) o += part[q * 256 + t + 16 * pstep];
-            if (PARTS > 2 && t < 64)  // row r + 8
-                for (int q = 0; q < KS; ++q) o += part[q * 256 + t + 128];
+        for (int q = 0; q < KS; ++q) o += p[q * 256 + tt];
+        if (PARTS > 1 && tt < 128) {  // row r + pstep
+            for (int q = 0; q < KS; ++q) o += p[q * 256 + tt + 16 * pstep];
+            if (PARTS > 2 && tt < 64)  // row r + 8
+                for (int q = 0; q < KS; ++q) o += p[q * 256 + tt + 128];
         }
-        const int l = t >> 2, r = 4 * (l >> 4) + (t & 3), n = n0 + (l & 15);  // a wave of t: four rows, all 16 columns
+        const int r = row_of(t), n = n0 + col_of(t);
         if (SRC == 1) {
             float m = 0.f;
             for (int q = 0; q < KS; ++q) m += ((const float*)(lds + q * 16 * WPITCH))[r];
@@ -504,60 +566,93 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
             for (int q = 0; q < TQ; ++q) m += rs[r * 17 + q];
             o *= rsqrtf(m / (float)fp.K + fp.eps);
         }
-        const bool live = r < fp.rows && n < fp.N;
+        const bool live = r < fp.rows && n < n0 + ncols;
         if (live && fp.res) o += (float)fp.res[r * fp.ldres + n];
         const __bf16 ob = (__bf16)o;
-        if (live) fp.out[r * fp.ldo + n] = STEP ? step_finish(fo, t == tid ? taps : step_taps(fo, r, n), r, n, ob) : ob;
+        if (live) fp.out[r * fp.ldo + n] = STEP ? step_finish(fo, tap, r, n, ob) : ob;
         if (fo.pack_out) {  // the next product's operand, and the squares its normalisation needs
             const float x = live ? (float)ob : 0.f;
             if (live) pack_operand(fo.pack_out, r, n, fo.pack_w ? x * fo.pack_w[n] : x, SRC ? PARTS : row_parts(fp.rows));
             float q = x * x;
             for (int off = 4; off < 64; off <<= 1) q += __shfl_xor(q, off, 64);
-            if ((l & 15) == 0) fo.pack_ssq[16 * blk + r] = q;
+            if (((t >> 2) & 15) == 0 && n < fp.N) fo.pack_ssq[16 * (n >> 4) + r] = q;
         }
+    };
+    for (int t = tid; t < tiles * 256; t += nthr) {  // (whole waves)
+        if (STEP && t != tid) taps = taps_of(t);
+        finish(t, taps);
     }
     move_pieces(fo, nthr);
 }
 
-template <int SRC, bool STEP, int PARTS, bool STREAM>
+template <int SRC, bool STEP, int PARTS, bool STREAM, int PPW, bool TURNS>
 hipError_t launch_few_mfma_kernel(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
-    static bool raised[64];  // per device: long rows take more dynamic LDS than the default limit
+    static bool raised[64];  // per device: more dynamic LDS than the default limit
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!raised[dev]) {
-        const hipError_t e = hipFuncSetAttribute((const void*)k_linear_few_mfma<SRC, STEP, PARTS, STREAM>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)few_mfma_lds(MFMA_WAVES));
+        const hipError_t e = hipFuncSetAttribute((const void*)k_linear_few_mfma<SRC, STEP, PARTS, STREAM, PPW, TURNS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)few_mfma_lds(MFMA_WAVES, MFMA_TILES));
         if (e != hipSuccess) return e;
         raised[dev] = true;
     }
-    hipLaunchKernelGGL((k_linear_few_mfma<SRC, STEP, PARTS, STREAM>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
+    hipLaunchKernelGGL((k_linear_few_mfma<SRC, STEP, PARTS, STREAM, PPW, TURNS>), dim3(wgs), dim3(fo.ks * 64), lds, st, fp, fo);
     return hipGetLastError();
 }
 
-template <int SRC, int PARTS>
-hipError_t launch_few_mfma_parts(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
+template <int SRC, int PARTS, int PPW, bool TURNS>
+hipError_t launch_few_mfma_pieces(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
     if (fo.stream)
-        return fo.cs ? launch_few_mfma_kernel<SRC, true, PARTS, true>(fp, fo, wgs, lds, st) : launch_few_mfma_kernel<SRC, false, PARTS, true>(fp, fo, wgs, lds, st);
-    return fo.cs ? launch_few_mfma_kernel<SRC, true, PARTS, false>(fp, fo, wgs, lds, st) : launch_few_mfma_kernel<SRC, false, PARTS, false>(fp, fo, wgs, lds, st);
+        return fo.cs ? launch_few_mfma_kernel<SRC, true, PARTS, true, PPW, TURNS>(fp, fo, wgs, lds, st)
+                     : launch_few_mfma_kernel<SRC, false, PARTS, true, PPW, TURNS>(fp, fo, wgs, lds, st);
+    return fo.cs ? launch_few_mfma_kernel<SRC, true, PARTS, false, PPW, TURNS>(fp, fo, wgs, lds, st)
+                 : launch_few_mfma_kernel<SRC, false, PARTS, false, PPW, TURNS>(fp, fo, wgs, lds, st);
+}
+
+template <int SRC, int PARTS>
+hipError_t launch_few_mfma_parts(const FewParams& fp, const FewOperands& fo, int ppw, int wgs, size_t lds, hipStream_t st) {
+    constexpr int most = SRC == 1 ? 1 : 2;
+    if (fp.K > PIECE * most * fo.ks) return launch_few_mfma_pieces<SRC, PARTS, most, true>(fp, fo, wgs, lds, st);
+    return ppw == most ? launch_few_mfma_pieces<SRC, PARTS, most, false>(fp, fo, wgs, lds, st) : launch_few_mfma_pieces<SRC, PARTS, 1, false>(fp, fo, wgs, lds, st);
 }
 
 template <int SRC>
-hipError_t launch_few_mfma_src(const FewParams& fp, const FewOperands& fo, int wgs, size_t lds, hipStream_t st) {
+hipError_t launch_few_mfma_src(const FewParams& fp, const FewOperands& fo, int ppw, int wgs, size_t lds, hipStream_t st) {
     const int parts = row_parts(fp.rows);
-    if (parts == 3) return launch_few_mfma_parts<SRC, 3>(fp, fo, wgs, lds, st);
-    if (parts == 2) return launch_few_mfma_parts<SRC, 2>(fp, fo, wgs, lds, st);
-    return launch_few_mfma_parts<SRC, 1>(fp, fo, wgs, lds, st);
+    if (parts == 3) return launch_few_mfma_parts<SRC, 3>(fp, fo, ppw, wgs, lds, st);
+    if (parts == 2) return launch_few_mfma_parts<SRC, 2>(fp, fo, ppw, wgs, lds, st);
+    return launch_few_mfma_parts<SRC, 1>(fp, fo, ppw, wgs, lds, st);
+}
+
+// Waves by the row, as launch_few; one round of workgroups, the same number in every compute unit, of at least MFMA_COLS columns: with
+// less of w than that to each, the operands of the rows would be most of what they fetch.
+struct FewSplit {
+    int ks, ppw, cols, wgs;
+};
+FewSplit few_split(int K, int N, bool two, bool whole) {  // two pieces a wave where one is not enough; whole tiles
+    FewSplit f;
+    const int pieces = (K + PIECE - 1) / PIECE;
+    f.ppw = two && pieces > MFMA_WAVES ? 2 : 1;
+    const int need = (pieces + f.ppw - 1) / f.ppw, turns = (need + MFMA_WAVES - 1) / MFMA_WAVES;
+    f.ks = (need + turns - 1) / turns;
+    const int units = 256 * ((10 + f.ks / 2) / f.ks), cols = (N + units - 1) / units;
+    f.cols = cols < MFMA_COLS ? MFMA_COLS : cols < 16 * MFMA_TILES ? cols : 16 * MFMA_TILES;
+    if (whole) f.cols = (f.cols + 15) / 16 * 16;
+    f.wgs = (N + f.cols - 1) / f.cols;
+    return f;
 }
 
 hipError_t launch_few_mfma(const FewParams& fp, FewOperands fo, int src, hipStream_t st) {
-    const int wgs = (fp.N + 15) / 16, pieces = (fp.K + PIECE - 1) / PIECE, ks = pieces < MFMA_WAVES ? pieces : MFMA_WAVES;
-    const size_t lds = few_mfma_lds(ks);
-    fo.ks = ks;
+    const FewSplit f = few_split(fp.K, fp.N, src != 1, fo.pack_out != nullptr);
+    const int ppw = f.ppw, wgs = f.wgs;
+    const size_t lds = few_mfma_lds(f.ks, (f.cols + 15) / 16);
+    fo.ks = f.ks;
+    fo.cols = f.cols;
     if (src == 2 && !fo.ssq) src = 3;
-    if (src == 0) return launch_few_mfma_parts<0, 1>(fp, fo, wgs, lds, st);
-    if (src == 1) return launch_few_mfma_src<1>(fp, fo, wgs, lds, st);
-    if (src == 2) return launch_few_mfma_src<2>(fp, fo, wgs, lds, st);
-    return launch_few_mfma_src<3>(fp, fo, wgs, lds, st);
+    if (src == 0) return launch_few_mfma_parts<0, 1>(fp, fo, ppw, wgs, lds, st);
+    if (src == 1) return launch_few_mfma_src<1>(fp, fo, ppw, wgs, lds, st);
+    if (src == 2) return launch_few_mfma_src<2>(fp, fo, ppw, wgs, lds, st);
+    return launch_few_mfma_src<3>(fp, fo, ppw, wgs, lds, st);
 }
 
 struct MidParams {
@@ -790,7 +885,7 @@ bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 }  // namespace
 
 bool few_rows_supported(const FewRowsJob& j) {
-    if (j.rows < 1 || j.rows > FEW_ROWS || j.K <= 0 || j.N <= 0 || ((j.K | j.N) & 7)) return false;
+    if (j.rows < 1 || j.rows > FEW_ROWS || j.K <= 0 || j.N <= 0 || ((j.K | j.N) & 7) || j.K > 1 << 24) return false;  // (offsets within a workgroup's columns of w: 32 bits)
     if (!j.x || !j.w || !j.out || !al16(j.x) || !al16(j.w) || (j.mode != 2 && ((j.ldx & 7) || j.ldx < j.K)) || j.ldo < j.N) return false;
     if (j.mode < 0 || j.mode > 2) return false;
     if (j.mode == 2 || j.pack_out) {
