@@ -4,8 +4,10 @@
 // convolution's channels).  A segment is processed from its stored state exactly as the SSD segment is:
 //     pre[t,c] = bias[c] + sum_{k=0..3} w[c,k] u[t-3+k, c]      (u[-3..-1] = state_in, zeros if absent)
 //     out[t,c] = pre / (1 + exp(-pre))
-// HBM-bound: every thread owns V consecutive channels (16 bytes) and walks TT consecutive tokens with
-// the window in registers, so every input row is read once (plus a three-row halo per TT tokens).
+// HBM-bound: every thread owns V consecutive channels (8 bytes: with 16 the backward kernel's state does not fit the registers) and walks `tt` consecutive tokens with
+// the window in registers, so every input row is read once (plus a three-row halo per run).  The rows come in
+// packed, four at a time and the four behind them under way, by loads without a branch around them (a row index
+// beyond the run is clamped to its last): a load under a condition ends in a wait for all of them.
 #include <string.h>
 
 #include "column_sums.h"
@@ -14,9 +16,9 @@ namespace ssdk {
 namespace {
 
 constexpr int CONV_K = 4;
-constexpr int FWD_TT = 64;    // most tokens per thread, forward
-constexpr int BWD_TT = 256;   // most tokens per thread, backward (also the granularity of the dw / dbias partial sums)
-constexpr int MIN_TT = 16;    // shorter runs re-read too much of the three-token halo
+constexpr int MAX_TT = 64, MIN_TT = 8;  // tokens per thread; shorter runs re-read too much of the three-token halo
+constexpr int U = 4;                    // rows requested together
+constexpr int BWD_WAVES = 4;            // runs of a backward workgroup, whose sums of dw / dbias go out as one
 
 struct ConvParams {
     const void* u;
@@ -68,41 +70,60 @@ __device__ __forceinline__ OutSlot out_slot(const ConvParams& cp, int c0) {
     return o;
 }
 
+typedef uint32_t words2 __attribute__((ext_vector_type(2)));
+
 template <typename T, int V>
 struct Vec;
 template <>
 struct Vec<float, 1> {
     static __device__ __forceinline__ void ld(const void* p, int64_t i, float (&v)[1]) { v[0] = ((const float*)p)[i]; }
     static __device__ __forceinline__ void st(void* p, int64_t i, const float (&v)[1]) { ((float*)p)[i] = v[0]; }
+    typedef float Raw;
+    static __device__ __forceinline__ void open(Raw r, float (&v)[1]) { v[0] = r; }
+    static __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, int at, const float (&v)[1]) { __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), r, at, 0, 0); }
 };
 template <>
-struct Vec<float, 4> {
-    static __device__ __forceinline__ void ld(const void* p, int64_t i, float (&v)[4]) {
-        const float4 t = *(const float4*)((const float*)p + i);
-        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-    }
-    static __device__ __forceinline__ void st(void* p, int64_t i, const float (&v)[4]) {
-        *(float4*)((float*)p + i) = make_float4(v[0], v[1], v[2], v[3]);
+struct Vec<float, 2> {
+    typedef float2 Raw;
+    static __device__ __forceinline__ void open(Raw r, float (&v)[2]) { v[0] = r.x; v[1] = r.y; }
+    static __device__ __forceinline__ void ld(const void* p, int64_t i, float (&v)[2]) { open(*(const Raw*)((const float*)p + i), v); }
+    static __device__ __forceinline__ void st(void* p, int64_t i, const float (&v)[2]) { *(float2*)((float*)p + i) = make_float2(v[0], v[1]); }
+    static __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, int at, const float (&v)[2]) {
+        __builtin_amdgcn_raw_buffer_store_b64(words2{__float_as_uint(v[0]), __float_as_uint(v[1])}, r, at, 0, 0);
     }
 };
 template <>
 struct Vec<bf16_t, 1> {
     static __device__ __forceinline__ void ld(const void* p, int64_t i, float (&v)[1]) { v[0] = bf16_to_float(((const bf16_t*)p)[i]); }
     static __device__ __forceinline__ void st(void* p, int64_t i, const float (&v)[1]) { ((bf16_t*)p)[i] = float_to_bf16(v[0]); }
+    typedef bf16_t Raw;
+    static __device__ __forceinline__ void open(Raw r, float (&v)[1]) { v[0] = bf16_to_float(r); }
+    static __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, int at, const float (&v)[1]) { __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, float_to_bf16(v[0])), r, at, 0, 0); }
 };
 template <>
-struct Vec<bf16_t, 8> {
-    typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-    static __device__ __forceinline__ void ld(const void* p, int64_t i, float (&v)[8]) {
-        const b8 t = *(const b8*)((const __bf16*)p + i);
+struct Vec<bf16_t, 4> {
+    typedef words2 Raw;  // words: bf16 elements would take a register each
+    typedef __bf16 b4 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ void open(Raw r, float (&v)[4]) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (float)t[e];
+        for (int e = 0; e < 2; ++e) {
+            const uint32_t word = r[e];
+            v[2 * e] = __uint_as_float(word << 16);
+            v[2 * e + 1] = __uint_as_float(word & 0xffff0000u);
+        }
     }
-    static __device__ __forceinline__ void st(void* p, int64_t i, const float (&v)[8]) {
-        b8 t;
+    static __device__ __forceinline__ void ld(const void* p, int64_t i, float (&v)[4]) { open(*(const Raw*)((const bf16_t*)p + i), v); }
+    static __device__ __forceinline__ void st(void* p, int64_t i, const float (&v)[4]) {
+        b4 t;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) t[e] = (__bf16)v[e];
-        *(b8*)((__bf16*)p + i) = t;
+        for (int e = 0; e < 4; ++e) t[e] = (__bf16)v[e];
+        *(b4*)((bf16_t*)p + i) = t;
+    }
+    static __device__ __forceinline__ void put(__amdgpu_buffer_rsrc_t r, int at, const float (&v)[4]) {
+        b4 t;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = (__bf16)v[e];
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(words2, t), r, at, 0, 0);
     }
 };
 
@@ -116,59 +137,107 @@ __device__ __forceinline__ float dsilu(float z) {
     return s * (1.f + z * (1.f - s));
 }
 
-// Row t of u for this thread's channels: from the tensor (t >= 0), the entering state (t >= -3) or zeros.
+// The three rows in front of row t0 of u for this thread's channels: of the tensor, the entering state, or zeros (then something that is
+// there is loaded and not used: a load under a condition would be waited for at the condition's end).
 template <typename T, int V>
-__device__ __forceinline__ void load_row(const ConvParams& cp, int64_t b, int64_t t, int c0, float (&v)[V]) {
-    if (t >= 0 && t < cp.L) {
-        Vec<T, V>::ld(cp.u, b * cp.u_bs + t * cp.u_rs + c0, v);
-    } else if (t < 0 && t >= -3 && cp.state_in) {
-        Vec<T, V>::ld(cp.state_in, (b * 3 + (t + 3)) * cp.C + c0, v);
-    } else {
+__device__ __forceinline__ void load_before(const ConvParams& cp, int64_t b, int64_t t0, int c0, typename Vec<T, V>::Raw (&v)[3]) {
 #pragma unroll
-        for (int e = 0; e < V; ++e) v[e] = 0.f;
+    for (int j = 0; j < 3; ++j) {
+        const int64_t t = t0 - 3 + j;
+        const T* p = t >= 0 ? (const T*)cp.u + b * cp.u_bs + t * cp.u_rs : cp.state_in ? (const T*)cp.state_in + (b * 3 + (t + 3)) * cp.C : (const T*)cp.w;
+        v[j] = *(const typename Vec<T, V>::Raw*)(p + c0);
     }
 }
-
 template <typename T, int V>
+__device__ __forceinline__ void open_before(const ConvParams& cp, int64_t t0, const typename Vec<T, V>::Raw (&r)[3], float (&v)[3][V]) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        Vec<T, V>::open(r[j], v[j]);
+#pragma unroll
+        for (int e = 0; e < V; ++e) v[j][e] = t0 - 3 + j >= 0 || cp.state_in ? v[j][e] : 0.f;
+    }
+}
+// V floats that may not be there: zeros then.
+template <int V>
+__device__ __forceinline__ void load_if(const ConvParams& cp, const float* p, bool there, float (&v)[V]) {
+    const float* q = there ? p : cp.w;
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = q[e];
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = there ? v[e] : 0.f;
+}
+
+// The rows t0 .. of one tensor for this thread's channels, `last` rows behind t0 at most.
+template <typename T, int V, typename Stride>
+struct Rows {
+    typedef typename Vec<T, V>::Raw Raw;
+    const T* p;  // row t0
+    Stride rs;
+    int last;
+    __device__ __forceinline__ void ask(Raw (&r)[U], int row) const {
+#pragma unroll
+        for (int j = 0; j < U; ++j) r[j] = *(const Raw*)(p + (uint64_t)(uint32_t)(row + j < last ? row + j : last) * (uint64_t)rs);
+    }
+};
+
+// What bounds it: the rows from and to memory (2 x 2 bytes a channel and token; 18 us for 4096 x 5376 at the rate of a copy), with the
+// sigmoids at half of that time.  With four rows asked for under a condition each and none ahead, 16 bytes a thread, 4096 x 5376 and 6001
+// x 5376 took 28 and 38 us alone, 34.5 and 40 inside a step; this takes 19 and 25, and 26 and 30.
+// WHOLE: every run has `tt` tokens (the last one starts early and stores some rows a second time, the same values): a store under a
+// condition would make the waits for the rows count on it not being there.
+template <typename T, int V, bool WHOLE>
 __global__ __launch_bounds__(64) void k_conv_fwd(ConvParams cp) {
+    typedef typename Vec<T, V>::Raw Raw;
     const int c0 = (blockIdx.x * 64 + threadIdx.x) * V;
     if (c0 >= cp.C) return;
-    const int64_t b = blockIdx.z, t0 = (int64_t)blockIdx.y * cp.tt;
-    const OutSlot os = out_slot(cp, c0);
+    int64_t b = blockIdx.z, t0 = (int64_t)blockIdx.y * cp.tt;
+    if (WHOLE && t0 > cp.L - cp.tt) t0 = cp.L - cp.tt;
+    const int n = WHOLE ? cp.tt : (int)cp.L;  // tokens of the run
+    const Rows<T, V, int64_t> rows = {(const T*)cp.u + b * cp.u_bs + t0 * cp.u_rs + c0, cp.u_rs, n - 1};
+    Raw ra[U], rb[U];
+    Raw before[3];
+    if (n > 0) rows.ask(ra, 0);
+    load_before<T, V>(cp, b, t0, c0, before);
     float w[V][CONV_K], bias[V];
+    load_if<V>(cp, cp.bias + c0, cp.bias, bias);
 #pragma unroll
     for (int e = 0; e < V; ++e) {
 #pragma unroll
         for (int k = 0; k < CONV_K; ++k) w[e][k] = cp.w[(c0 + e) * CONV_K + k];
-        bias[e] = cp.bias ? cp.bias[c0 + e] : 0.f;
     }
+    if (n > 0) rows.ask(rb, U);
+    const OutSlot os = out_slot(cp, c0);
+    T* out = (T*)os.out + b * os.bs + t0 * os.rs + os.c;
     float win[3][V];  // u[t-3], u[t-2], u[t-1]
-#pragma unroll
-    for (int j = 0; j < 3; ++j) load_row<T, V>(cp, b, t0 - 3 + j, c0, win[j]);
-    const int64_t t1 = t0 + cp.tt < cp.L ? t0 + cp.tt : cp.L;
-    constexpr int U = 4;  // four rows requested together, then consumed in order
-    for (int64_t t = t0; t < t1; t += U) {
-        float cur[U][V];
-#pragma unroll
-        for (int j = 0; j < U; ++j)
-            if (t + j < t1) Vec<T, V>::ld(cp.u, b * cp.u_bs + (t + j) * cp.u_rs + c0, cur[j]);
+    open_before<T, V>(cp, t0, before, win);
+    auto use = [&](const Raw (&r)[U], int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            if (t + j >= t1) break;
-            float o[V];
+            if (WHOLE || t + j < n) {
+                float cur[V], o[V];
+                Vec<T, V>::open(r[j], cur);
 #pragma unroll
-            for (int e = 0; e < V; ++e) {
-                const float pre = bias[e] + w[e][0] * win[0][e] + w[e][1] * win[1][e] + w[e][2] * win[2][e] + w[e][3] * cur[j][e];
-                o[e] = silu(pre);
-                win[0][e] = win[1][e];
-                win[1][e] = win[2][e];
-                win[2][e] = cur[j][e];
+                for (int e = 0; e < V; ++e) {
+                    const float pre = bias[e] + w[e][0] * win[0][e] + w[e][1] * win[1][e] + w[e][2] * win[2][e] + w[e][3] * cur[e];
+                    o[e] = silu(pre);
+                    win[0][e] = win[1][e];
+                    win[1][e] = win[2][e];
+                    win[2][e] = cur[e];
+                }
+                Vec<T, V>::st(out, 0, o);
+                out += os.rs;
+                __builtin_amdgcn_sched_barrier(0);  // a row at a time: registers
             }
-            Vec<T, V>::st(os.out, b * os.bs + (t + j) * os.rs + os.c, o);
         }
+    };
+    for (int t = 0; t < n; t += 2 * U) {
+        use(ra, t);
+        rows.ask(ra, t + 2 * U);
+        use(rb, t + U);
+        rows.ask(rb, t + 3 * U);
     }
     // the state leaving the segment: the last three rows of [state_in ; u]
-    if (cp.state_out && t1 == cp.L) {
+    if (cp.state_out && t0 + n == cp.L) {
 #pragma unroll
         for (int j = 0; j < 3; ++j) Vec<T, V>::st(cp.state_out, (b * 3 + j) * cp.C + c0, win[j]);
     }
@@ -177,110 +246,135 @@ __global__ __launch_bounds__(64) void k_conv_fwd(ConvParams cp) {
 // Backward.  g[t] = dout[t] silu'(pre[t]);  du[t] = sum_k w[k] g[t+3-k]  (g beyond the segment is 0; what
 // the segment on the right contributes to the last three rows arrives as dstate_out);
 // dw[k] = sum_t g[t] u[t-3+k];  dbias = sum_t g[t];  dstate_in[j] = du[-3+j].
+// The waves of a workgroup take consecutive runs of the same channels and add up their sums in LDS.  Stores of rows that are not there go to
+// an empty descriptor (see k_conv_fwd).  What bounds it: three rows' traffic a token (27 us for 4096 x 5376 at the rate of a copy), and
+// nearly as long the vector ALUs.  4096 x 5376 bf16 inside a step, with a wave a workgroup, a row at a time and every run's sums to
+// memory (a fifth of the traffic): 50 us and 6.7 for the sums' reduction; now 38 and 5.4.
 template <typename T, int V>
-__global__ __launch_bounds__(64) void k_conv_bwd(ConvParams cp) {
-    const int c0 = (blockIdx.x * 64 + threadIdx.x) * V;
+__global__ __launch_bounds__(64 * BWD_WAVES, 2) void k_conv_bwd(ConvParams cp) {
+    typedef typename Vec<T, V>::Raw Raw;
+    __shared__ float sums[BWD_WAVES][5 * V][64];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int first_c = blockIdx.x * 64 * V, c0 = first_c + lane * V;
     if (c0 >= cp.C) return;
-    const int64_t b = blockIdx.z, t0 = (int64_t)blockIdx.y * cp.tt;
-    const OutSlot os = out_slot(cp, c0);
-    float w[V][CONV_K], bias[V];
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-#pragma unroll
-        for (int k = 0; k < CONV_K; ++k) w[e][k] = cp.w[(c0 + e) * CONV_K + k];
-        bias[e] = cp.bias ? cp.bias[c0 + e] : 0.f;
-    }
+    const int64_t b = blockIdx.z, first = ((int64_t)blockIdx.y * BWD_WAVES + wv) * cp.tt;  // first own token
     float acc[5][V];
 #pragma unroll
     for (int k = 0; k < 5; ++k)
 #pragma unroll
         for (int e = 0; e < V; ++e) acc[k][e] = 0.f;
-    float win[3][V];  // u[t-3], u[t-2], u[t-1]
+    if (first < cp.L || first == 0) {
+        // the run: tokens 0 .. n - 1 from t0 on, of which those in front of `skip` are another's
+        const int64_t t0 = first > cp.L - cp.tt ? (cp.L > cp.tt ? cp.L - cp.tt : 0) : first;
+        const int n = (int)(cp.L < cp.tt ? cp.L : cp.tt), skip = (int)(first - t0);
+        const int left = (int)(cp.L - t0 < n + 3 ? cp.L - t0 : n + 3);  // and those whose g they need
+        const OutSlot os = out_slot(cp, c0);
+        const Rows<T, V, int64_t> ru = {(const T*)cp.u + b * cp.u_bs + t0 * cp.u_rs + c0, cp.u_rs, left - 1};
+        const Rows<T, V, uint32_t> rd = {(const T*)os.dout + b * os.bs + t0 * os.rs + os.c, (uint32_t)os.rs, left - 1};
+        Raw ua[U], ub[U], da[U], db[U];
+        if (left > 0) ru.ask(ua, 0), rd.ask(da, 0);
+        Raw before[3];
+        load_before<T, V>(cp, b, t0, c0, before);
+        float w[V][CONV_K], bias[V];
+        load_if<V>(cp, cp.bias + c0, cp.bias, bias);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) load_row<T, V>(cp, b, t0 - 3 + j, c0, win[j]);
-    float gw[3][V];   // g[t-3], g[t-2], g[t-1]; before the tile (or the sequence) they are not needed: zeros
+        for (int e = 0; e < V; ++e) {
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
+            for (int k = 0; k < CONV_K; ++k) w[e][k] = cp.w[(c0 + e) * CONV_K + k];
+        }
+        // what arrives from the right for the last three rows, and for those of the entering state that a sequence shorter than three
+        // tokens passes straight through to the state it leaves (row j of it: row L - 3 + j of [state_in ; u])
+        float right[3][V];
 #pragma unroll
-        for (int e = 0; e < V; ++e) gw[j][e] = 0.f;
-    const int64_t t1 = t0 + cp.tt < cp.L ? t0 + cp.tt : cp.L;  // own tokens: [t0, t1)
-    // the first tile also produces the gradient of the entering state, du[-3..-1]; its g window starts at 0 anyway
-    const int64_t first_out = (t0 == 0 && cp.dstate_in) ? -3 : t0;
-    // one token: g[t] from its rows of u and dout (zeros beyond the sequence), then du[t-3]
-    auto token = [&](int64_t t, const float (&cur)[V], const float (&dv)[V]) {
-        float g[V];
-        if (t < cp.L) {
+        for (int j = 0; j < 3; ++j) load_if<V>(cp, cp.dstate_out + (b * 3 + j) * cp.C + c0, cp.dstate_out && t0 + n > cp.L - 3, right[j]);
+        if (left > 0) ru.ask(ub, U), rd.ask(db, U);
+        float win[3][V];  // u[t-3], u[t-2], u[t-1]
+        open_before<T, V>(cp, t0, before, win);
+        float gw[3][V];   // g[t-3], g[t-2], g[t-1]; before the run (or the sequence) they are not needed: zeros
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int e = 0; e < V; ++e) gw[j][e] = 0.f;
+        const T* du = (const T*)cp.du + b * cp.u_bs + (t0 - 3) * cp.u_rs + first_c;  // row t - 3
+        const int width = (cp.C - first_c < 64 * V ? cp.C - first_c : 64 * V) * (int)sizeof(T);
+        float few[5][V];  // sums of eight tokens: a chain of all of them would round more often on its way
+        // one token: g[t] from its rows of u and dout (zeros beyond the sequence), then du[t-3]
+        auto token = [&](int t, const Raw& ur, const Raw& dr) __attribute__((always_inline)) {
+            float cur[V], dv[V], g[V], o[V];
+            Vec<T, V>::open(ur, cur);
+            Vec<T, V>::open(dr, dv);
+            const bool in = t < left;
 #pragma unroll
             for (int e = 0; e < V; ++e) {
                 const float pre = bias[e] + w[e][0] * win[0][e] + w[e][1] * win[1][e] + w[e][2] * win[2][e] + w[e][3] * cur[e];
-                g[e] = dv[e] * dsilu(pre);
+                g[e] = in ? dv[e] * dsilu(pre) : 0.f;
             }
-            if (t < t1) {  // own token: its share of dw and dbias
+            if (t < n && t >= skip) {  // own token: its share of dw and dbias
 #pragma unroll
                 for (int e = 0; e < V; ++e) {
-                    acc[0][e] += g[e] * win[0][e];
-                    acc[1][e] += g[e] * win[1][e];
-                    acc[2][e] += g[e] * win[2][e];
-                    acc[3][e] += g[e] * cur[e];
-                    acc[4][e] += g[e];
+                    few[0][e] += g[e] * win[0][e];
+                    few[1][e] += g[e] * win[1][e];
+                    few[2][e] += g[e] * win[2][e];
+                    few[3][e] += g[e] * cur[e];
+                    few[4][e] += g[e];
                 }
             }
-        } else {
-#pragma unroll
-            for (int e = 0; e < V; ++e) g[e] = 0.f;
-        }
-        // du[t-3] = w3 g[t-3] + w2 g[t-2] + w1 g[t-1] + w0 g[t]
-        const int64_t to = t - 3;
-        if (to >= first_out && to < t1) {
-            float o[V];
+            // du[t-3] = w3 g[t-3] + w2 g[t-2] + w1 g[t-1] + w0 g[t]
+            const int to = t - 3;
 #pragma unroll
             for (int e = 0; e < V; ++e) o[e] = w[e][3] * gw[0][e] + w[e][2] * gw[1][e] + w[e][1] * gw[2][e] + w[e][0] * g[e];
-            if (to >= 0) {
-                if (cp.dstate_out && to >= cp.L - 3) {  // one of the last three rows: add what arrives from the right
-                    const int64_t j = to - (cp.L - 3);
+            const int64_t behind = t0 + to - (cp.L - 3);
+            if (behind >= 0) {
 #pragma unroll
-                    for (int e = 0; e < V; ++e) o[e] += cp.dstate_out[(b * 3 + j) * cp.C + c0 + e];
-                }
-                Vec<T, V>::st(cp.du, b * cp.u_bs + to * cp.u_rs + c0, o);
-            } else {
-                // a row of the entering state; when the sequence is shorter than three tokens, part of the
-                // state passes straight through to state_out and takes dstate_out's gradient with it
-                const int64_t jr = to + 3;  // 0..2
-                if (cp.dstate_out && cp.L < 3 && jr >= cp.L) {
-                    const int64_t j = jr - cp.L;
-#pragma unroll
-                    for (int e = 0; e < V; ++e) o[e] += cp.dstate_out[(b * 3 + j) * cp.C + c0 + e];
-                }
-#pragma unroll
-                for (int e = 0; e < V; ++e) cp.dstate_in[(b * 3 + jr) * cp.C + c0 + e] = o[e];
+                for (int e = 0; e < V; ++e) o[e] += right[0][e], right[0][e] = right[1][e], right[1][e] = right[2][e], right[2][e] = 0.f;
             }
-        }
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)du, 0, to >= 0 && to < n ? width : 0, 0x00020000);
+            Vec<T, V>::put(rsrc, lane * V * (int)sizeof(T), o);
+            du += cp.u_rs;
+            if (t0 == 0 && to < 0 && cp.dstate_in) {  // a row of the entering state
 #pragma unroll
-        for (int e = 0; e < V; ++e) {
-            gw[0][e] = gw[1][e];
-            gw[1][e] = gw[2][e];
-            gw[2][e] = g[e];
-            win[0][e] = win[1][e];
-            win[1][e] = win[2][e];
-            win[2][e] = t < cp.L ? cur[e] : 0.f;
-        }
-    };
-    for (int64_t t = t0; t < t1 + 3; ++t) {
-        float cur[V], dv[V];
-        if (t < cp.L) {
-            Vec<T, V>::ld(cp.u, b * cp.u_bs + t * cp.u_rs + c0, cur);
-            Vec<T, V>::ld(os.dout, b * os.bs + t * os.rs + os.c, dv);
-        } else {
+                for (int e = 0; e < V; ++e) cp.dstate_in[(b * 3 + (to + 3)) * cp.C + c0 + e] = o[e];
+            }
 #pragma unroll
-            for (int e = 0; e < V; ++e) cur[e] = dv[e] = 0.f;
+            for (int e = 0; e < V; ++e) {
+                gw[0][e] = gw[1][e];
+                gw[1][e] = gw[2][e];
+                gw[2][e] = g[e];
+                win[0][e] = win[1][e];
+                win[1][e] = win[2][e];
+                win[2][e] = in ? cur[e] : 0.f;
+            }
+            __builtin_amdgcn_sched_barrier(0);  // a token at a time: registers
+        };
+        for (int t = 0; t < n + 3; t += 2 * U) {
+#pragma unroll
+            for (int k = 0; k < 5; ++k)
+#pragma unroll
+                for (int e = 0; e < V; ++e) few[k][e] = 0.f;
+#pragma unroll
+            for (int j = 0; j < U; ++j) token(t + j, ua[j], da[j]);
+            if (left > 0) ru.ask(ua, t + 2 * U), rd.ask(da, t + 2 * U);
+#pragma unroll
+            for (int j = 0; j < U; ++j) token(t + U + j, ub[j], db[j]);
+            if (left > 0) ru.ask(ub, t + 3 * U), rd.ask(db, t + 3 * U);
+#pragma unroll
+            for (int k = 0; k < 5; ++k)
+#pragma unroll
+                for (int e = 0; e < V; ++e) acc[k][e] += few[k][e];
         }
-        token(t, cur, dv);
     }
-    float* part = cp.part + ((b * cp.ntiles + blockIdx.y) * 5) * (int64_t)cp.C;
 #pragma unroll
     for (int k = 0; k < 5; ++k)
 #pragma unroll
-        for (int e = 0; e < V; ++e) part[(int64_t)k * cp.C + c0 + e] = acc[k][e];
+        for (int e = 0; e < V; ++e) sums[wv][k * V + e][lane] = acc[k][e];
+    __syncthreads();
+    float* part = cp.part + ((b * cp.ntiles + blockIdx.y) * 5) * (int64_t)cp.C;
+    for (int i = wv; i < 5 * V; i += BWD_WAVES) {
+        float t = 0.f;
+#pragma unroll
+        for (int q = 0; q < BWD_WAVES; ++q) t += sums[q][i][lane];
+        part[(int64_t)(i / V) * cp.C + c0 + i % V] = t;
+    }
 }
 
 // dw and dbias from the tiles' partial sums, rows of [5][C], in a fixed order.
@@ -303,23 +397,26 @@ int check(const ssd_conv_shape_t* sh) {
     if (!sh) return SSD_ERR_NULL;
     if (sh->dtype != SSD_F32 && sh->dtype != SSD_BF16) return SSD_ERR_DTYPE;
     if (sh->batch <= 0 || sh->batch > 65535 || sh->seqlen < 0 || sh->channels <= 0) return SSD_ERR_SHAPE;
-    if ((sh->seqlen + FWD_TT - 1) / FWD_TT > 65535) return SSD_ERR_SHAPE;  // grid.y (long sequences run FWD_TT tokens per thread)
+    if ((sh->seqlen + MAX_TT - 1) / MAX_TT > 65535) return SSD_ERR_SHAPE;  // grid.y (long sequences run MAX_TT tokens per thread)
     if (sh->u_row_stride && sh->u_row_stride < sh->channels) return SSD_ERR_SHAPE;
     if (sh->batch_stride && sh->batch_stride < sh->seqlen * (sh->u_row_stride ? sh->u_row_stride : sh->channels)) return SSD_ERR_SHAPE;
     return SSD_OK;
 }
 
-// Tokens per thread: the most (fewest halo re-reads, fewest partial sums) that still gives the launch about
-// 2048 waves -- a segment-sized call would otherwise leave most of the machine idle.
-int pick_tt(const ssd_conv_shape_t* sh, int most) {
-    const int64_t col_waves = ((int64_t)sh->channels / 8 + 63) / 64 * sh->batch;  // waves per token tile
-    int tt = most;
-    while (tt > MIN_TT && (sh->seqlen + tt - 1) / tt * col_waves < 2048) tt >>= 1;
-    return tt;
+// Tokens per thread, `less` fewer than a multiple of 2 U: one round of `waves` waves, evenly filled, unless that makes the runs too short or
+// too long.  Forward with 2048 / 3072 / 4096 / 5120 waves, 6001 x 5376: 25.9, 27.6, 24.9, 24.7 us; backward with 1024 / 2048 / 3072 / 4096:
+// 53.9, 53.9, 48.4, 58.6 (3072 fit, of the others some run behind the rest).
+int pick_tt(const ssd_conv_shape_t* sh, int waves, int less) {
+    const int64_t cols = ((int64_t)sh->channels / 4 + 63) / 64 * sh->batch;  // waves side by side
+    const int64_t runs = cols < waves ? waves / cols : 1, tt = (sh->seqlen + runs - 1) / runs + less;
+    return (tt > MAX_TT - 2 * U ? MAX_TT : tt < MIN_TT ? MIN_TT : (int)(tt + 2 * U - 1) / (2 * U) * (2 * U)) - less;
 }
+constexpr int FWD_FILL = 5120, BWD_FILL = 3072;  // waves that fit the registers of the chip
+int fwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, FWD_FILL, 0); }
+int bwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, BWD_FILL, 3); }  // three tokens more go through the loop
 int ntiles_bwd(const ssd_conv_shape_t* sh) {
-    const int tt = pick_tt(sh, BWD_TT);
-    return (int)((sh->seqlen + tt - 1) / tt);
+    const int64_t tile = (int64_t)BWD_WAVES * bwd_tt(sh);
+    return (int)((sh->seqlen + tile - 1) / tile);
 }
 
 }  // namespace
@@ -357,7 +454,7 @@ bool bind_split(ConvParams& cp, const ConvSplit* sp, bool bwd) {
 int vec_width(const ConvParams& cp, bool bf) {
     int all = cp.C | (int)cp.u_rs;
     if (cp.split) all |= cp.cb[1] | cp.cb[2];
-    return bf ? (all % 8 == 0 ? 8 : 1) : (all % 4 == 0 ? 4 : 1);
+    return bf ? (all % 8 == 0 ? 4 : 1) : (all % 4 == 0 ? 2 : 1);
 }
 
 int conv_fwd_impl(const ssd_conv_shape_t* sh, const void* u, const float* w, const float* bias, const void* state_in, void* out,
@@ -384,12 +481,17 @@ int conv_fwd_impl(const ssd_conv_shape_t* sh, const void* u, const float* w, con
     const bool bf = sh->dtype == SSD_BF16;
     const int V = vec_width(cp, bf);
     // an empty sequence still hands the state on: one tile, whose token loop is empty
-    cp.tt = pick_tt(sh, FWD_TT);
+    cp.tt = fwd_tt(sh);
     const dim3 grid((cp.C / V + 63) / 64, (unsigned)(cp.L > 0 ? (cp.L + cp.tt - 1) / cp.tt : 1), (unsigned)sh->batch);
-    if (bf && V == 8) hipLaunchKernelGGL((k_conv_fwd<bf16_t, 8>), grid, dim3(64), 0, st, cp);
-    else if (bf) hipLaunchKernelGGL((k_conv_fwd<bf16_t, 1>), grid, dim3(64), 0, st, cp);
-    else if (V == 4) hipLaunchKernelGGL((k_conv_fwd<float, 4>), grid, dim3(64), 0, st, cp);
-    else hipLaunchKernelGGL((k_conv_fwd<float, 1>), grid, dim3(64), 0, st, cp);
+    const bool whole = cp.L >= cp.tt;
+#define CONV_FWD(T, W) \
+    if (whole) hipLaunchKernelGGL((k_conv_fwd<T, W, true>), grid, dim3(64), 0, st, cp); \
+    else hipLaunchKernelGGL((k_conv_fwd<T, W, false>), grid, dim3(64), 0, st, cp)
+    if (bf && V == 4) CONV_FWD(bf16_t, 4);
+    else if (bf) CONV_FWD(bf16_t, 1);
+    else if (V == 2) CONV_FWD(float, 2);
+    else CONV_FWD(float, 1);
+#undef CONV_FWD
     return hipGetLastError() == hipSuccess ? SSD_OK : SSD_ERR_LAUNCH;
 }
 
@@ -419,17 +521,17 @@ int conv_bwd_impl(const ssd_conv_shape_t* sh, const void* u, const float* w, con
     cp.u_rs = sh->u_row_stride ? sh->u_row_stride : sh->channels;
     cp.u_bs = sh->batch_stride ? sh->batch_stride : sh->seqlen * cp.u_rs;
     cp.o_bs = sh->batch_stride ? sh->batch_stride : sh->seqlen * sh->channels;
-    cp.tt = pick_tt(sh, BWD_TT);
+    cp.tt = bwd_tt(sh);
     cp.ntiles = ntiles_bwd(sh) > 0 ? ntiles_bwd(sh) : 1;
     if (!bind_split(cp, split, true)) return SSD_ERR_ARG;
     hipStream_t st = (hipStream_t)hip_stream;
     const bool bf = sh->dtype == SSD_BF16;
     const int V = vec_width(cp, bf);
     const dim3 grid((cp.C / V + 63) / 64, (unsigned)cp.ntiles, (unsigned)sh->batch);
-    if (bf && V == 8) hipLaunchKernelGGL((k_conv_bwd<bf16_t, 8>), grid, dim3(64), 0, st, cp);
-    else if (bf) hipLaunchKernelGGL((k_conv_bwd<bf16_t, 1>), grid, dim3(64), 0, st, cp);
-    else if (V == 4) hipLaunchKernelGGL((k_conv_bwd<float, 4>), grid, dim3(64), 0, st, cp);
-    else hipLaunchKernelGGL((k_conv_bwd<float, 1>), grid, dim3(64), 0, st, cp);
+    if (bf && V == 4) hipLaunchKernelGGL((k_conv_bwd<bf16_t, 4>), grid, dim3(64 * BWD_WAVES), 0, st, cp);
+    else if (bf) hipLaunchKernelGGL((k_conv_bwd<bf16_t, 1>), grid, dim3(64 * BWD_WAVES), 0, st, cp);
+    else if (V == 2) hipLaunchKernelGGL((k_conv_bwd<float, 2>), grid, dim3(64 * BWD_WAVES), 0, st, cp);
+    else hipLaunchKernelGGL((k_conv_bwd<float, 1>), grid, dim3(64 * BWD_WAVES), 0, st, cp);
     if (hipGetLastError() != hipSuccess) return SSD_ERR_LAUNCH;
     hipLaunchKernelGGL(k_conv_reduce, dim3((5 * cp.C + 63) / 64), dim3(COLSUM_THREADS), 0, st, cp.part, (int64_t)sh->batch * cp.ntiles,
                        cp.C, dw, dbias, (flags & SSD_FLAG_ACCUM_PARAM) ? 1 : 0);
