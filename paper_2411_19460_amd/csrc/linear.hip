@@ -11,8 +11,8 @@
 // tiles are read back as plain 16-byte operands, the others through the transposing LDS read.
 // One scheme of tiles, three widths: 256 x 256, 256 x 192 or 256 x 128 per workgroup (eight waves of 64 x 128 / 96 / 64, one
 // workgroup per compute unit, loads straight to LDS two K steps ahead); the two gradient products share a launch, and the
-// launch rule below chooses the one whose tiles fit the machine best.  Workgroup ids are remapped so that each XCD works on a
-// compact block of the tile grid (its L2 then holds the A and B panels that block shares).
+// launch rule below chooses the one, or for the forward product the two, whose tiles fit the machine best.  Workgroup ids are
+// remapped so that each XCD works on a compact block of the tile grid (its L2 then holds the A and B panels that block shares).
 #include <stdint.h>
 #include <string.h>
 
@@ -138,6 +138,7 @@ struct Tile {
     // The last, partial K step through registers: k beyond the contraction's end has to read as zero.
     static __device__ __forceinline__ void load_part(const bf16_t* origin, int64_t ld, int left, int k_left, char* lds, int tid) {
         bf16x8 v[LOADS];
+        asm volatile("" : "+v"(tid));  // the addresses are worked out here: ahead of the K steps they take 20 to 30 of their registers
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
             const int r = row(tid) + RSTEP * i, c = piece(tid) * 8;
@@ -402,15 +403,21 @@ __global__ __launch_bounds__(GTHR, 1) void k_gemm_big(GemmParams gp) {
     gemm_tile<true, true, WJ>(gp, blockIdx.x);
 }
 
+// The first columns in tiles of one width, which fill their rounds, the others in tiles of a narrower one: workgroups first .. run these.
+template <int W1, int W2>
+__global__ __launch_bounds__(GTHR, 1) void k_gemm_mixed(GemmParams p1, GemmParams p2, int first) {
+    if ((int)blockIdx.x < first) gemm_tile<true, true, W1>(p1, blockIdx.x);
+    else gemm_tile<true, true, W2>(p2, blockIdx.x - first);
+}
+
 // The gradient products of a call, of the input (64 WX columns a tile) and of the weights (64 WW), in one launch: workgroups
 // first .. run the second.  They are independent (both read dout; they write dx and dw), and one alone often leaves compute
 // units idle: a segment of 4096 rows gives the input gradient of the 2.7B block's input projection 160 tiles for 256 units.
 // As two launches on two streams they met only behind a fork and a join, some 20 us a pair, and in whatever order the queues
 // were served: us at 4096 rows, two launches -> one, 2560 <-> 10576 375 -> 363, 2560 <-> 5120 227 -> 182, 1024 <-> 4384 95 -> 90,
 // 1024 <-> 2048 73 -> 49; 600 rows 154 -> 145, 81 -> 50, 61 -> 49, 40 -> 16.
-// With a tile of each kind in one kernel the registers of <4, 4> and <2, 4> do not quite suffice: 9 and 5 of them are kept in
-// 28 and 24 bytes of scratch, all in the last steps of a tile (the forward kernel of the same tile, 248 registers, keeps
-// none).  Such accesses only make the waits of those steps, which count outstanding loads, stricter.
+// A tile of each kind in one kernel fits the registers (240; with the addresses of a partial K step worked out ahead of the steps it
+// did not, see load_part).
 template <int WX, int WW>
 __global__ __launch_bounds__(GTHR, 1) void k_gemm_grads(GemmParams px, GemmParams pw, int dw_first, int first) {
     const bool second = (int)blockIdx.x >= first;
@@ -453,6 +460,22 @@ hipError_t launch_big(GemmParams gp, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int W1, int W2>
+hipError_t launch_mixed(GemmParams gp, int n1, hipStream_t st) {
+    constexpr int L1 = big_lds<true, true, W1>(), L2 = big_lds<true, true, W2>(), LDS = L1 > L2 ? L1 : L2;  // (128 columns have three buffers of both)
+    static bool raised[64];
+    const hipError_t e = allow_lds((const void*)k_gemm_mixed<W1, W2>, LDS, raised);
+    if (e != hipSuccess) return e;
+    GemmParams p2 = gp;
+    gp.N = n1;
+    p2.N -= n1;
+    p2.B += (int64_t)n1 * gp.ldb;
+    p2.C = (bf16_t*)gp.C + n1;
+    const int t1 = set_tiles(gp, W1), t2 = set_tiles(p2, W2);
+    hipLaunchKernelGGL((k_gemm_mixed<W1, W2>), dim3(t1 + t2), dim3(GTHR), LDS, st, gp, p2, t1);
+    return hipGetLastError();
+}
+
 // Without dx or dw: the other alone.
 template <int WX, int WW>
 hipError_t launch_grads(GemmParams px, GemmParams pw, bool dx, bool dw, bool dw_first, hipStream_t st) {
@@ -475,13 +498,31 @@ constexpr int64_t UNITS = 256;
 int64_t tile_count(const GemmParams& gp, int wj) { return (int64_t)((gp.M + 255) / 256) * ((gp.N + 64 * wj - 1) / (64 * wj)); }
 constexpr int WIDTH_PCT[5] = {0, 0, 68, 83, 100};  // of a K step, by WJ
 
-int forward_width(const GemmParams& gp) {
-    int best = 4;
+// Columns up to n1 in tiles of width w, the others (where n1 < N) in tiles of the next narrower one.  One width leaves the last round as
+// empty as it falls out: 4096 x 2560 -> 10576 is 2.6 rounds of 256 columns and takes three; two rounds of them and one of 192 columns for
+// the rest are full.  The units that the wide tiles leave idle in their last round take a narrow one there.  us with one width -> with two:
+// 4096 x 2560 -> 10576 190 -> 187, 8192 x 2560 -> 10576 366 -> 350, 8192 x 5120 -> 2560 182 -> 174, 4096 x 1024 -> 4384 42 -> 38.
+struct ForwardPlan {
+    int w, n1;
+};
+ForwardPlan forward_plan(const GemmParams& gp) {
+    ForwardPlan best = {4, gp.N};
     int64_t t = INT64_MAX;
-    for (int wj = 4; wj >= 2; --wj) {
-        const int64_t c = (tile_count(gp, wj) + UNITS - 1) / UNITS * WIDTH_PCT[wj];
-        if (c < t) t = c, best = wj;
+    for (int w = 4; w >= 2; --w) {
+        const int64_t c = (tile_count(gp, w) + UNITS - 1) / UNITS * WIDTH_PCT[w];
+        if (c < t) t = c, best = {w, gp.N};
     }
+    if (tile_count(gp, 4) > 50 * UNITS) return best;
+    t -= t / 50;  // for less than 2 % (and so in more than 50 rounds) it is not worth a second kind
+    const int64_t tm = (gp.M + 255) / 256;
+    for (int w1 = 4; w1 > 2; --w1)
+        for (int64_t r = (gp.N - 1) / (64 * w1) * tm / UNITS; r > 0; --r) {
+            const int64_t n1 = UNITS * r / tm * 64 * w1, spare = UNITS * r - UNITS * r / tm * tm;
+            if (n1 <= 0 || n1 >= gp.N) continue;
+            const int64_t rest = tm * ((gp.N - n1 + 64 * (w1 - 1) - 1) / (64 * (w1 - 1))) - spare;
+            const int64_t c = r * WIDTH_PCT[w1] + (rest > 0 ? (rest + UNITS - 1) / UNITS * WIDTH_PCT[w1 - 1] : 0);
+            if (c < t) t = c, best = {w1, (int)n1};
+        }
     return best;
 }
 
@@ -562,9 +603,11 @@ extern "C" int ssd_linear_fwd(int64_t rows, int32_t in_dim, int32_t out_dim, con
     gp.M = (int)rows;
     gp.N = out_dim;
     gp.K = in_dim;
-    const int wj = forward_width(gp);
-    const hipStream_t st = (hipStream_t)hip_stream;
-    const hipError_t e = wj == 4 ? launch_big<4>(gp, st) : wj == 3 ? launch_big<3>(gp, st) : launch_big<2>(gp, st);
+    const ForwardPlan f = forward_plan(gp);
+    hipStream_t st = (hipStream_t)hip_stream;
+    hipError_t e;
+    if (f.n1 < gp.N) e = f.w == 4 ? launch_mixed<4, 3>(gp, f.n1, st) : launch_mixed<3, 2>(gp, f.n1, st);
+    else e = f.w == 4 ? launch_big<4>(gp, st) : f.w == 3 ? launch_big<3>(gp, st) : launch_big<2>(gp, st);
     return e == hipSuccess ? SSD_OK : SSD_ERR_LAUNCH;
 }
 
