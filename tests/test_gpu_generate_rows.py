@@ -1,7 +1,7 @@
 """One generation step for a few sequences at the sizes where its kernels change: two rows (vector ALUs) and three (matrix
 cores), widths that are no multiple of a 256-wide piece, two groups whose norms scale the pieces, state rows of more than
-128 columns, eight rows per half wave from 768 pairs of head and sequence on, rows of more than 2048 elements whose pieces
-a wave takes in turn, more partial sums of squares than are asked for ahead.  Checked against the oracle run on each sequence
+128 columns, eight rows per half wave from 768 pairs of head and sequence on, rows of more than 2560 elements, of which
+a wave takes two pieces, more partial sums of squares than are asked for ahead.  Checked against the oracle run on each sequence
 alone."""
 import numpy as np
 import pytest
@@ -31,7 +31,7 @@ def test_generation_rows(shape):
 
 @pytest.mark.parametrize("shape", [
     # d_model, H, P, G, N, pre-norm, sequences
-    (2560, 80, 64, 1, 128, True, 1),     # vector ALUs, four columns a wave and k over four waves, convolution step included
+    (2560, 80, 64, 1, 128, True, 1),     # vector ALUs, the row shared out among the waves, convolution step included
     (2560, 80, 64, 2, 128, True, 2),     # the same for two rows; two groups
     (2560, 80, 64, 1, 128, True, 16),    # eight state rows per half wave; a wave's second piece of k (K = 2560 and 5120)
     (2560, 80, 64, 2, 128, True, 16),    # second pieces scaled by their group's norm
@@ -96,7 +96,7 @@ def test_generation_step_of_stacks_larger_than_the_cache(shape):
 @pytest.mark.parametrize("rows", [3, 16])
 @pytest.mark.parametrize("K", [2048, 2056, 5120])
 def test_products_of_few_long_rows(rows, K):
-    """K at which each of the eight waves has its one piece of 256, one wave a second piece of eight, and all of them several."""
+    """K of eight pieces of 256, of eight and one of eight k, and of twenty: two a wave."""
     x, w, _ = draw_linear(4, rows, K, 136)
     out = pk.ssd_linear_fwd(dev_linear(x), dev_linear(w))
     torch.cuda.synchronize()
