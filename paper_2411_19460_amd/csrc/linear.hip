@@ -58,30 +58,46 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // The MFMAs are issued with the B operand first, so an accumulator tile holds the transposed product: lane
 // -> row m = lane % 16 of C, its four registers -> the consecutive columns 4 (lane / 16) + 0..3.
-// Every lane thus stores 8 bytes (bf16) or 16 bytes (fp32) at a time.  `whole`: the workgroup's tile lies
-// inside C (no bounds checks; N is a multiple of 8, so a group of four columns is inside or outside as one).
-// fp32 results (weight gradients): where they are added to what is there, the old values of four tiles are asked for
-// together, and those of the next four before these are stored.
+// Every lane thus stores 8 bytes (bf16) or 16 bytes (fp32) at a time (N is a multiple of 8, so a group of four columns is inside C or
+// outside as one).
+// fp32 results (weight gradients): where they are added to what is there, the old values of AHEAD columns of tiles are asked for
+// before the first of them is used, without a branch (what lies outside C is aimed beyond the descriptor's end, and without
+// `accumulate` the descriptor is empty): where each of them stands under a condition, the compiler waits for all in flight.  4096 rows,
+// 2560 <-> 10576 (both gradients) 375 -> 367 us, 2560 <-> 5120 180 -> 177; three columns ahead the same.
 template <int WJ>
-__device__ __forceinline__ void store_acc_f32(const GemmParams& gp, const f32x4 (&acc)[4][2 * WJ], int row0, int col0, int lane, bool whole) {
-    const int row_l = row0 + (lane & 15), col_l = col0 + (lane >> 4) * 4;
-    auto at = [&](int i, int j) { return (f32x4*)((float*)gp.C + (int64_t)(row_l + i * 16) * gp.ldc + col_l + j * 16); };
-    auto in = [&](int i, int j) { return whole || (row_l + i * 16 < gp.M && col_l + j * 16 < gp.N); };
-    f32x4 old[2][4];
+__device__ __forceinline__ void store_acc_f32(const GemmParams& gp, const f32x4 (&acc)[4][2 * WJ], int row0, int col0, int lane) {
+    constexpr int AHEAD = 4;
+    const int row_l = lane & 15, col_l = (lane >> 4) * 4;
+    float* org = (float*)gp.C + (int64_t)row0 * gp.ldc + col0;
+    if (gp.ldc > MAX_LD / 2) {  // beyond offsets of 32 bits
+#pragma unroll
+        for (int j = 0; j < 2 * WJ; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                f32x4* at = (f32x4*)(org + (int64_t)(i * 16 + row_l) * gp.ldc + j * 16 + col_l);
+                if (row0 + i * 16 + row_l < gp.M && col0 + j * 16 + col_l < gp.N) *at = acc[i][j] + (gp.accumulate ? *at : (f32x4)(0.f));
+            }
+        return;
+    }
+    const __amdgpu_buffer_rsrc_t from = __builtin_amdgcn_make_buffer_rsrc((void*)org, 0, gp.accumulate ? 0x3fffffff : 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc((void*)org, 0, 0x3fffffff, 0x00020000);
+    uint32_t row[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) row[i] = row0 + i * 16 + row_l < gp.M ? (uint32_t)(i * 16 + row_l) * (uint32_t)(gp.ldc * 4) : 0x80000000u;
+    auto col = [&](int j) { return col0 + j * 16 + col_l < gp.N ? (uint32_t)(j * 16 + col_l) * 4 : 0x40000000u; };
+    f32x4 old[AHEAD][4];
     auto ask = [&](int j) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            old[j & 1][i] = (f32x4)(0.f);
-            if (gp.accumulate && in(i, j)) old[j & 1][i] = *at(i, j);
-        }
+        for (int i = 0; i < 4; ++i) old[j % AHEAD][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(from, row[i] + col(j), 0, 0));
     };
-    ask(0);
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) ask(j);
 #pragma unroll
     for (int j = 0; j < 2 * WJ; ++j) {
-        if (j + 1 < 2 * WJ) ask(j + 1);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (in(i, j)) *at(i, j) = acc[i][j] + old[j & 1][i];
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j] + old[j % AHEAD][i]), to, row[i] + col(j), 0, 0);
+        if (j + AHEAD < 2 * WJ) ask(j + AHEAD);
     }
 }
 
@@ -375,7 +391,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& gp, int id) {
     for (; k0 < gp.K; k0 += BKK) G.template step<false>(cx, k0, direct);
 
     if (gp.c_f32) {
-        store_acc_f32<WJ>(gp, acc, m0 + wm * 64, n0 + wn * 32 * WJ, lane, interior);
+        store_acc_f32<WJ>(gp, acc, m0 + wm * 64, n0 + wn * 32 * WJ, lane);
         return;
     }
     // bf16 result: through LDS (every wave has left its last buffer behind the barrier), so that
