@@ -36,6 +36,7 @@ struct Prep {
     static constexpr int E = Q / 64;
     typedef float vec __attribute__((ext_vector_type(E)));
     bf16_t dt[E];
+    float A, bias;  // of the head: by scalar memory, asked for with the rest
 
     __device__ __forceinline__ void load(const SegParams& sp, int b, int c, int h, int lane, int rows) {
         const bool raw = sp.raw.dt;
@@ -46,18 +47,19 @@ struct Prep {
             const int i = E * lane + e, il = i < rows ? i : rows - 1;
             dt[e] = src[il * rs];
         }
+        typedef const __attribute__((address_space(4))) float* scalars;
+        A = ((scalars)sp.A)[h];
+        bias = ((scalars)(raw ? sp.raw.bias : sp.A))[h];
     }
     // vc: cum, vd: dt; returns cum at the end of the chunk
     __device__ __forceinline__ float form(const SegParams& sp, int b, int c, int h, int lane, int rows, vec& vc, vec& vd) const {
         float d[E], a[E];
-        const float A = sp.A[h];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             d[e] = bf16_to_float(dt[e]);
             a[e] = 0.f;
         }
         if (sp.raw.dt) {  // uniform
-            const float bias = sp.raw.bias[h];
 #pragma unroll
             for (int e = 0; e < E; ++e) d[e] = bf16_to_float(float_to_bf16(softplus(d[e] + bias)));
         }
@@ -236,6 +238,15 @@ __global__ __launch_bounds__(OUTER_THR, 4) void mk_chunk_outer(SegParams sp, int
     const int nrows = chunk_rows(sp, c, Q);
     Prep<Q> pp;
     if (w < hps) pp.load(sp, b, c, h0 + w, lane, nrows);
+    // B (role 0) or C (role 1) rows, then the first head: all under way before the first of them is waited for, and one trip to memory
+    // (with the rows in a loop and A and the bias fetched where they are used three: 8192 tokens of 24 heads, forward and backward,
+    // 164.4 -> 162.5 us)
+    const bf16_t* rhs = (role == 0 ? (const bf16_t*)sp.Bm : (const bf16_t*)sp.Cm) + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
+    const rsrc_t rows = make_rows(rhs, nrows, (uint32_t)bt * 2);
+    constexpr int NB = Q * 16 / OUTER_THR;
+    bf16x8 rv[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) rv[k] = rows_load(rows, (uint32_t)((tid >> 4) + k * (OUTER_THR / 16)) * (uint32_t)bt * 2 + (tid & 15) * 16);
     OuterPre<Q> pr;
     outer_load<Q>(pr, sp, role, b, c, h0, tid);
     // what is derived from such a value is formed where it is used and not kept in registers over the loop
@@ -254,13 +265,9 @@ __global__ __launch_bounds__(OUTER_THR, 4) void mk_chunk_outer(SegParams sp, int
         *(typename Prep<Q>::vec*)(&L.wt[w][Q / 64 * ln]) = vw;
         if (role == 0) pp.store(sp, b, c, h0 + hh + w, ln, vc, vd);
     };
-    // prologue: B (role 0) or C (role 1) rows -> LDS -> this wave's fragments
-    const bf16_t* rhs = (role == 0 ? (const bf16_t*)sp.Bm : (const bf16_t*)sp.Cm) + (int64_t)b * sp.bcs_b + ((int64_t)c * Q * sp.G + g) * N_;
-    const rsrc_t rows = make_rows(rhs, nrows, (uint32_t)bt * 2);
-    for (int v = tid; v < Q * 16; v += OUTER_THR) {
-        const int row = v >> 4, seg = v & 15;
-        *(bf16x8*)(L.bc + row * BPITCH + seg * 16) = rows_load(rows, (uint32_t)row * (uint32_t)bt * 2 + seg * 16);
-    }
+    // prologue: the rows -> LDS -> this wave's fragments
+#pragma unroll
+    for (int k = 0; k < NB; ++k) *(bf16x8*)(L.bc + ((tid >> 4) + k * (OUTER_THR / 16)) * BPITCH + (tid & 15) * 16) = rv[k];
     weights(0);
     __syncthreads();
     bf16x8 fb[KS];
