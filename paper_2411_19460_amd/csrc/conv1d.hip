@@ -403,17 +403,18 @@ int check(const ssd_conv_shape_t* sh) {
     return SSD_OK;
 }
 
-// Tokens per thread, `less` fewer than a multiple of 2 U: one round of `waves` waves, evenly filled, unless that makes the runs too short or
+// Tokens per thread, `less` fewer than a multiple of 2 U and than `most`: one round of `waves` waves, evenly filled, unless that makes the runs too short or
 // too long.  Forward with 2048 / 3072 / 4096 / 5120 waves, 6001 x 5376: 25.9, 27.6, 24.9, 24.7 us; backward with 1024 / 2048 / 3072 / 4096:
 // 53.9, 53.9, 48.4, 58.6 (3072 fit, of the others some run behind the rest).
-int pick_tt(const ssd_conv_shape_t* sh, int waves, int less) {
+int pick_tt(const ssd_conv_shape_t* sh, int waves, int most, int less) {
     const int64_t cols = ((int64_t)sh->channels / 4 + 63) / 64 * sh->batch;  // waves side by side
     const int64_t runs = cols < waves ? waves / cols : 1, tt = (sh->seqlen + runs - 1) / runs + less;
-    return (tt > MAX_TT - 2 * U ? MAX_TT : tt < MIN_TT ? MIN_TT : (int)(tt + 2 * U - 1) / (2 * U) * (2 * U)) - less;
+    return (tt > most - 2 * U ? most : tt < MIN_TT ? MIN_TT : (int)(tt + 2 * U - 1) / (2 * U) * (2 * U)) - less;
 }
 constexpr int FWD_FILL = 5120, BWD_FILL = 3072;  // waves that fit the registers of the chip
-int fwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, FWD_FILL, 0); }
-int bwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, BWD_FILL, 3); }  // three tokens more go through the loop
+int fwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, FWD_FILL, MAX_TT, 0); }
+// (three tokens more go through the loop; a workgroup's sums stand for at least 256 tokens of a long sequence)
+int bwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, BWD_FILL, MAX_TT + 2 * U, 3); }
 int ntiles_bwd(const ssd_conv_shape_t* sh) {
     const int64_t tile = (int64_t)BWD_WAVES * bwd_tt(sh);
     return (int)((sh->seqlen + tile - 1) / tile);

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
     ("bf16", 1, 264, (1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 16, 17, 20, 21, 23)),   # runs of eight and five tokens
     ("f32", 2, 36, (1, 4, 5, 6, 8, 9, 21, 22)),
     ("bf16", 1, 5, (4, 5, 6, 7, 8, 9, 25)),                                          # a channel a thread
-    ("bf16", 160, 256, (1793, 1801)),                                                # runs of 64 and 61
+    ("bf16", 160, 256, (1793, 1801, 2100)),                                          # runs of 64 and 69
     ("bf16", 40, 512, (1001,)),                                                      # runs in between
 ])
 @pytest.mark.parametrize("states", [True, False])
