@@ -407,7 +407,7 @@ int check(const ssd_conv_shape_t* sh) {
 // too long.  Forward with 2048 / 3072 / 4096 / 5120 waves, 6001 x 5376: 25.9, 27.6, 24.9, 24.7 us; backward with 1024 / 2048 / 3072 / 4096:
 // 53.9, 53.9, 48.4, 58.6 (3072 fit, of the others some run behind the rest).
 int pick_tt(const ssd_conv_shape_t* sh, int waves, int most, int less) {
-    const int64_t cols = ((int64_t)sh->channels / 4 + 63) / 64 * sh->batch;  // waves side by side
+    const int64_t cols = ((int64_t)sh->channels + 255) / 256 * sh->batch;  // waves side by side, at least one
     const int64_t runs = cols < waves ? waves / cols : 1, tt = (sh->seqlen + runs - 1) / runs + less;
     return (tt > most - 2 * U ? most : tt < MIN_TT ? MIN_TT : (int)(tt + 2 * U - 1) / (2 * U) * (2 * U)) - less;
 }

@@ -256,3 +256,16 @@ def test_a_kept_shape_descriptor_is_found_by_value_only():
             binding._shape_ref(x, Bm, chunk, segment, None)
     assert binding._shape_ref(x, Bm, 8, seg, None)[0].segment == 16
     assert binding._shape_ref(x, Bm, 8, seg.add_(8), None)[0].segment == 24
+
+
+@pytest.mark.parametrize("channels", [1, 2, 3, 4, 5, 255, 256, 257])
+def test_convolution_scratch_for_any_number_of_channels(channels):
+    """Fewer channels than a thread takes at once make one wave side by side, not none: the division of a launch's waves among the
+    runs of tokens has to stand for them too.  Five sums a channel, of at least one workgroup."""
+    L = binding.lib()
+    for dtype in (0, 1):
+        for batch in (1, 3):
+            for seqlen in (0, 1, 7, 100, 65536):
+                sh = binding.ssd_conv_shape_t(dtype=dtype, channels=channels, batch=batch, seqlen=seqlen, batch_stride=0, u_row_stride=0)
+                got = L.ssd_conv1d_workspace_bytes(ctypes.byref(sh))
+                assert got >= batch * 5 * channels * 4 and got % 256 == 0, (dtype, batch, seqlen, got)

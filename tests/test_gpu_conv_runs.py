@@ -49,3 +49,10 @@ def test_runs(dtype, Bt, C, lengths, states):
         check(f"{L} dstate_in", pick(got["dstate_in"]), go["dstate_in"], TOL[dtype])
         check(f"{L} dw", host(got["dw"]), go["dw"], TOL[dtype])
         check(f"{L} dbias", host(got["dbias"]), go["dbias"], TOL[dtype])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("C", [1, 2, 3, 4])
+def test_few_channels(dtype, C):
+    """Fewer channels than a thread's share of a wider tensor."""
+    test_runs(dtype, 2, C, (1, 2, 7, 8, 9, 40, 300), True)
