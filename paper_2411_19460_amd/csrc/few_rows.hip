@@ -131,7 +131,7 @@ __device__ __forceinline__ void move_pieces(const FewOperands& fo, int threads) 
 }
 
 // Rows that one or two tokens multiply: the vector ALUs.  A workgroup owns `cols` consecutive columns and its waves share out the
-// row in pieces of 512 k (16 bytes a lane); a wave keeps f(x) of its pieces in registers and walks the columns four at a time, the
+// row in pieces of 512 k (16 bytes a lane); a wave keeps f(x) of its piece in registers and walks the columns four at a time, the
 // eight behind them under way, so that w streams through without a pause while every other operand is read once a workgroup.  The
 // partial sums of the columns meet in LDS once, at the end, where the threads that finish a column have had everything else
 // they need since the start.  What bounds it is w from memory (5.5 TB/s of reads, 9.9 and 4.8 us for a 2.7B block's two), and what a
@@ -139,7 +139,7 @@ __device__ __forceinline__ void move_pieces(const FewOperands& fo, int threads) 
 // normalisation, convolution step and softplus; output with normalisation and residual): a workgroup per four columns with the row
 // over its four waves, which fetched f(x) anew and paid two trips to memory in a row, 13.6 and 8.6, now 12.5 and 7.5; a step of eight blocks
 // 203 -> 192, with two sequences 223 -> 197, at the width of 64 heads 143 -> 138 and 173 -> 155.
-constexpr int FEW_PIECE = 512, FEW_WAVES = 10, FEW_COLS = 64;
+constexpr int FEW_PIECE = 512, FEW_WAVES = 12, FEW_COLS = 512;  // k of a piece; waves, columns of a workgroup at most
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -159,13 +159,15 @@ __device__ __forceinline__ float four_sums(const float (&a)[4]) {
     return dpp_add<0xB1, 0xF>(v);
 }
 
-// PPW: pieces of a wave that it keeps f(x) of (longer rows go by in turns).  STEP: with the convolution step (fo.cs).  Template
+// Longer rows than the waves have pieces go by in turns (two pieces of two rows to a wave do not fit the registers: 76 to 148 bytes of
+// scratch a lane, and a step of 96 heads, whose d_inner is 6144, took 8 % longer).  STEP: with the convolution step (fo.cs).  Template
 // arguments like MODE: a branch around loads ends in a wait for them.
-template <int MODE, int R, int PPW, bool STEP, bool STREAM>
+template <int MODE, int R, bool STEP, bool STREAM>
 __global__ __launch_bounds__(FEW_WAVES * 64) void k_linear_few(FewParams fp, FewOperands fo, int cols) {
-    __shared__ float red[FEW_COLS * R][FEW_WAVES], sq[R][FEW_WAVES];
+    extern __shared__ float few_sums[];  // [columns, whole fours][R][NW], then the squares [R][NW]
     const int NW = fo.ks, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n0 = blockIdx.x * cols, nc = fp.N - n0 < cols ? fp.N - n0 : cols, nb = (nc + 3) >> 2;
+    float *red = few_sums, *sq = few_sums + ((cols + 3) & ~3) * R * NW;
     // columns and pieces beyond the end: nothing is fetched, zeros come back
     const uint32_t rowbytes = (uint32_t)fp.K * 2, bytes = (uint32_t)nc * rowbytes;
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)(fp.w + (int64_t)n0 * fp.K), 0, bytes, 0x00020000);
@@ -178,33 +180,27 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void k_linear_few(FewParams fp, Few
     int fr, fc;
     const bool finish = place(tid, fr, fc);
     const int frl = finish ? fr : 0, fnl = n0 + (finish ? fc : 0);
-    const int range = FEW_PIECE * PPW * NW;
+    const int range = FEW_PIECE * NW;
     float ss[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) ss[r] = 0.f;
     StepTaps taps;
     float res = 0.f;
     for (int kb = 0; kb < fp.K; kb += range) {
-        uint32_t off[PPW];
-        bf16x8 xv[R][PPW];
-        f32x4 iw[MODE ? PPW : 1][2];
+        const int k = kb + FEW_PIECE * w + 8 * lane, kc = k < fp.K ? k : 0;
+        const uint32_t off = k < fp.K ? (uint32_t)k * 2 : bytes;
+        bf16x8 xv[R];
+        f32x4 iw[2];
 #pragma unroll
-        for (int j = 0; j < PPW; ++j) {
-            const int k = kb + FEW_PIECE * (w + NW * j) + 8 * lane, kc = k < fp.K ? k : 0;
-            off[j] = k < fp.K ? (uint32_t)k * 2 : bytes;
-#pragma unroll
-            for (int r = 0; r < R; ++r) xv[r][j] = *(const bf16x8*)(fp.x + (r < fp.rows ? r : 0) * fp.ldx + kc);
-            if (MODE) {
-                iw[j][0] = *(const f32x4*)(fp.in_w + kc);
-                iw[j][1] = *(const f32x4*)(fp.in_w + kc + 4);
-            }
+        for (int r = 0; r < R; ++r) xv[r] = *(const bf16x8*)(fp.x + (r < fp.rows ? r : 0) * fp.ldx + kc);
+        if (MODE) {
+            iw[0] = *(const f32x4*)(fp.in_w + kc);
+            iw[1] = *(const f32x4*)(fp.in_w + kc + 4);
         }
-        u32x4 W[2][4][PPW];
-        auto load = [&](u32x4 (&b)[4][PPW], int n) {
+        u32x4 W[2][4];
+        auto load = [&](u32x4 (&b)[4], int n) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int j = 0; j < PPW; ++j) b[c][j] = __builtin_amdgcn_raw_buffer_load_b128(rw, off[j] + (uint32_t)(4 * n + c) * rowbytes, 0, STREAM ? 2 : 0);
+            for (int c = 0; c < 4; ++c) b[c] = __builtin_amdgcn_raw_buffer_load_b128(rw, off + (uint32_t)(4 * n + c) * rowbytes, 0, STREAM ? 2 : 0);
         };
         load(W[0], 0);
         load(W[1], 1);
@@ -212,42 +208,38 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void k_linear_few(FewParams fp, Few
             if (STEP) taps = step_taps(fo, frl, fnl);
             if (fp.res) res = (float)fp.res[frl * fp.ldres + fnl];
         }
-        float f[R][PPW][8];
+        float f[R][8];
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+        for (int r = 0; r < R; ++r) {
+            const bool in = off < bytes && r < fp.rows;
 #pragma unroll
-            for (int j = 0; j < PPW; ++j) {
-                const bool in = off[j] < bytes && r < fp.rows;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    float v = in ? (float)xv[r][j][e] : 0.f;
-                    if (MODE) {
-                        ss[r] = fmaf(v, v, ss[r]);
-                        v *= in ? iw[j][e >> 2][e & 3] : 0.f;
-                    }
-                    f[r][j][e] = v;
+            for (int e = 0; e < 8; ++e) {
+                float v = in ? (float)xv[r][e] : 0.f;
+                if (MODE) {
+                    ss[r] = fmaf(v, v, ss[r]);
+                    v *= in ? iw[e >> 2][e & 3] : 0.f;
                 }
+                f[r][e] = v;
             }
-        auto use = [&](const u32x4 (&b)[4][PPW], int n) {
+        }
+        auto use = [&](const u32x4 (&b)[4], int n) {
             float acc[R][4];
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
                 for (int c = 0; c < 4; ++c) acc[r][c] = 0.f;
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
+            for (int c = 0; c < 4; ++c) {
+                const bf16x8 v = __builtin_bit_cast(bf16x8, b[c]);
 #pragma unroll
-                for (int j = 0; j < PPW; ++j) {
-                    const bf16x8 v = __builtin_bit_cast(bf16x8, b[c][j]);
+                for (int e = 0; e < 8; ++e)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-#pragma unroll
-                        for (int r = 0; r < R; ++r) acc[r][c] = fmaf(f[r][j][e], (float)v[e], acc[r][c]);
-                }
+                    for (int r = 0; r < R; ++r) acc[r][c] = fmaf(f[r][e], (float)v[e], acc[r][c]);
+            }
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const float v = four_sums(acc[r]);
-                float* at = &red[(4 * n + (lane >> 4)) * R + r][w];
+                float* at = red + ((4 * n + (lane >> 4)) * R + r) * NW + w;
                 if ((lane & 15) == 0) *at = kb ? *at + v : v;
             }
         };
@@ -264,7 +256,7 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void k_linear_few(FewParams fp, Few
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const float t = wave_total(ss[r]);
-            if (lane == 0) sq[r][w] = t;
+            if (lane == 0) sq[r * NW + w] = t;
         }
     }
     __syncthreads();
@@ -273,8 +265,8 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void k_linear_few(FewParams fp, Few
         if (!place(t, r, c)) continue;
         float v = 0.f, q2 = 0.f;
         for (int q = 0; q < NW; ++q) {  // fixed order: the result does not depend on which wave finished first
-            v += red[c * R + r][q];
-            if (MODE) q2 += sq[r][q];
+            v += red[(c * R + r) * NW + q];
+            if (MODE) q2 += sq[r * NW + q];
         }
         const int n = n0 + c;
         if (MODE) v *= rsqrtf(q2 / (float)fp.K + fp.eps);
@@ -285,33 +277,40 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void k_linear_few(FewParams fp, Few
     move_pieces(fo, 64 * NW);
 }
 
-template <int MODE, int PPW, bool STEP, bool STREAM>
+template <int MODE, bool STEP, bool STREAM>
 hipError_t launch_few_kernel(const FewParams& fp, const FewOperands& fo, int cols, hipStream_t st) {
     const dim3 grid((unsigned)((fp.N + cols - 1) / cols)), block(64 * fo.ks);
-    if (fp.rows <= 1) hipLaunchKernelGGL((k_linear_few<MODE, 1, PPW, STEP, STREAM>), grid, block, 0, st, fp, fo, cols);
-    else hipLaunchKernelGGL((k_linear_few<MODE, FEW_ROWS_VALU, PPW, STEP, STREAM>), grid, block, 0, st, fp, fo, cols);
+    const size_t lds = (size_t)((cols + 3) / 4 * 4 + 1) * (fp.rows <= 1 ? 1 : FEW_ROWS_VALU) * fo.ks * sizeof(float);  // 49 KB at most
+    if (fp.rows <= 1) hipLaunchKernelGGL((k_linear_few<MODE, 1, STEP, STREAM>), grid, block, lds, st, fp, fo, cols);
+    else hipLaunchKernelGGL((k_linear_few<MODE, FEW_ROWS_VALU, STEP, STREAM>), grid, block, lds, st, fp, fo, cols);
     return hipGetLastError();
 }
 
-template <int MODE, int PPW>
-hipError_t launch_few_pieces(const FewParams& fp, const FewOperands& fo, int cols, hipStream_t st) {
-    if (fo.stream) return fo.cs ? launch_few_kernel<MODE, PPW, true, true>(fp, fo, cols, st) : launch_few_kernel<MODE, PPW, false, true>(fp, fo, cols, st);
-    return fo.cs ? launch_few_kernel<MODE, PPW, true, false>(fp, fo, cols, st) : launch_few_kernel<MODE, PPW, false, false>(fp, fo, cols, st);
+// N columns of K elements in as many rounds of `units` workgroups as they need with at most `most` columns each, all rounds full.  A
+// workgroup's columns are addressed by 32 bits, with as much again beyond their end.
+int even_columns(int N, int K, int units, int most) {
+    most = most < (1 << 30) / K ? most : (1 << 30) / K;
+    const int64_t round = (int64_t)units * most, all = (N + round - 1) / round * units;
+    return (int)((N + all - 1) / all);
 }
 
-// As many waves a workgroup as share the row evenly, each with one piece of it up to rows of 5120 and two beyond, and as few columns
-// as give every compute unit about ten waves (80 KB of w under way), the same number of workgroups in each: eight a unit with some
-// units holding twice as many as others took 3 % of a step.
+// As many waves a workgroup as share the row evenly, with one piece of it each, and as few columns, at least four, as give every compute
+// unit about ten waves (80 KB of w under way), the same number of workgroups in each: eight a unit with some units holding twice as many as
+// others took 3 % of a step.
+// A product that stands alone has nothing but the way to its first load to hide, and more waves do: sixteen, where the registers hold
+// them (one row; two up to 2560 k).  2560 x 10576 11.9 -> 11.6 us, 1536 x 3352 4.6 -> 4.4, 768 x 10576 with two rows 6.4 -> 6.0.  And where it
+// is many columns wide, small workgroups that start one after another keep the memory busier than a round that ends together: 5120 x 50288
+// 92 -> 84, with two rows 2560 x 50288 40.6 -> 37.5 (but 5120 x 50288 93 -> 100, and 768 x 32768 11.2 -> 11.8 with one).
 template <int MODE>
 hipError_t launch_few(const FewParams& fp, FewOperands fo, hipStream_t st) {
-    const int pieces = (fp.K + FEW_PIECE - 1) / FEW_PIECE, ppw = pieces <= FEW_WAVES ? 1 : 2;
-    const int need = (pieces + ppw - 1) / ppw, turns = (need + FEW_WAVES - 1) / FEW_WAVES;
-    fo.ks = (need + turns - 1) / turns;
-    const int units = 256 * ((10 + fo.ks / 2) / fo.ks);
-    int cols = (fp.N + units - 1) / units;
-    cols = cols < FEW_COLS ? cols : FEW_COLS;
-    if (ppw == 1) return launch_few_pieces<MODE, 1>(fp, fo, cols, st);
-    return launch_few_pieces<MODE, 2>(fp, fo, cols, st);
+    const int pieces = (fp.K + FEW_PIECE - 1) / FEW_PIECE, turns = (pieces + FEW_WAVES - 1) / FEW_WAVES;
+    fo.ks = (pieces + turns - 1) / turns;
+    const bool alone = MODE == 0 && !fo.cs, roomy = fp.rows <= 1 ? turns == 1 : pieces <= 5;
+    const int units = 256 * (((alone && roomy ? 16 : 10) + fo.ks / 2) / fo.ks);
+    int cols = even_columns(fp.N, fp.K, units, alone && roomy && fp.N >= 16384 && fp.K >= 1024 ? 8 : FEW_COLS);
+    cols = cols < 4 ? 4 : cols;
+    if (fo.stream) return fo.cs ? launch_few_kernel<MODE, true, true>(fp, fo, cols, st) : launch_few_kernel<MODE, false, true>(fp, fo, cols, st);
+    return fo.cs ? launch_few_kernel<MODE, true, false>(fp, fo, cols, st) : launch_few_kernel<MODE, false, false>(fp, fo, cols, st);
 }
 
 // More than a few rows (several sequences generated together): the same product on the matrix cores.  A workgroup owns `cols`
