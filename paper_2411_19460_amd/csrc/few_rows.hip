@@ -314,7 +314,7 @@ hipError_t launch_few(const FewParams& fp, FewOperands fo, hipStream_t st) {
 }
 
 // More than a few rows (several sequences generated together): the same product on the matrix cores.  A workgroup owns `cols`
-// consecutive columns; its waves share out the row in pieces of 256 k, one each up to rows of 2560 and two up to 5120, and keep the (at
+// consecutive columns; its waves share out the row in pieces of 256 k, one each up to rows of 3072 and two up to 6144, and keep the (at
 // most 16) input rows of theirs as operands in registers while they walk the columns in tiles of 16, the next piece of w under way,
 // one 16 x 16 x 32 MFMA per 32 k.  The partial tiles meet in LDS once, at the end.  The arithmetic is out of the way and the kernel
 // again only streams w.  What bounds it is the number of cache lines an access touches: w is fetched as half rows of 512 contiguous
@@ -331,7 +331,8 @@ typedef float f32x4v __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int64_t packed_at(int row, int k) { return ((int64_t)(k >> 3) * 16 + row) * 8 + (k & 7); }
 
 constexpr int PIECE = 256, WPITCH = PIECE * 2 + 16;  // k per piece; bytes per LDS row of a piece of w
-constexpr int MFMA_WAVES = 10, MFMA_TILES = 4, MFMA_COLS = 16, MAX_GROUPS = 8;  // waves, tiles of a workgroup at most
+constexpr int MFMA_WAVES = 12, MFMA_COLS = 16, MAX_GROUPS = 8;  // waves of a workgroup at most, columns at least
+__host__ __device__ constexpr int mfma_tiles(int ks) { return ks > 10 ? 4 : 6; }  // tiles of 16 columns at most: LDS
 // Up to eight rows leave rows of a tile free: they carry what rounding the operand x in_w to bf16 left of the live rows, and
 // the finished sums of a row's parts are added.  Up to four rows take three parts (rows r, r + 4, r + 8: all 24 bits, what the
 // vector ALUs compute one and two rows with), up to eight two (r, r + 8: 16 bits); more rows one.  The extra parts cost
@@ -352,6 +353,7 @@ __device__ __forceinline__ void pack_operand(__bf16* pack, int row, int k, float
 }
 inline size_t few_mfma_lds(int ks, int tiles) { return (size_t)ks * 16 * WPITCH + (size_t)tiles * ks * 1024 + 16 * 17 * 4; }
 static_assert(MAX_GROUPS * 16 <= 16 * 17, "");
+static_assert(10 * 16 * WPITCH + mfma_tiles(10) * 10 * 1024 <= MFMA_WAVES * 16 * WPITCH + mfma_tiles(MFMA_WAVES) * MFMA_WAVES * 1024, "");
 
 // SRC 0: rows of x.  SRC 1: RMS normalisation over all of K times in_w, its squares summed on the way (the operand is
 // x in_w, 1 / rms scales the finished sums).  SRC 2: packed rows, already times in_w, with `ssq` the partial
@@ -591,7 +593,7 @@ hipError_t launch_few_mfma_kernel(const FewParams& fp, const FewOperands& fo, in
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!raised[dev]) {
         const hipError_t e = hipFuncSetAttribute((const void*)k_linear_few_mfma<SRC, STEP, PARTS, STREAM, PPW, TURNS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)few_mfma_lds(MFMA_WAVES, MFMA_TILES));
+                                                 (int)few_mfma_lds(MFMA_WAVES, mfma_tiles(MFMA_WAVES)));
         if (e != hipSuccess) return e;
         raised[dev] = true;
     }
@@ -623,8 +625,10 @@ hipError_t launch_few_mfma_src(const FewParams& fp, const FewOperands& fo, int p
     return launch_few_mfma_parts<SRC, 1>(fp, fo, ppw, wgs, lds, st);
 }
 
-// Waves by the row, as launch_few; one round of workgroups, the same number in every compute unit, of at least MFMA_COLS columns: with
-// less of w than that to each, the operands of the rows would be most of what they fetch.
+// Waves by the row, as launch_few: up to twelve where that saves a second turn, else up to ten.  (With ten at most the rows of a block of 96 heads,
+// of 3072 and 6144, went by in two turns of six waves: three blocks for three sequences 131 us, 112 so; 6144 x 2560 alone 9.1 and 8.6.  In more turns
+// anyway, three turns of eleven waves are 4 % slower than four of eight.)  One round of workgroups (or as many as are full), the same number in every
+// compute unit, of at least MFMA_COLS columns: with less of w than that to each, the operands of the rows would be most of what they fetch.
 struct FewSplit {
     int ks, ppw, cols, wgs;
 };
@@ -632,10 +636,10 @@ FewSplit few_split(int K, int N, bool two, bool whole) {  // two pieces a wave w
     FewSplit f;
     const int pieces = (K + PIECE - 1) / PIECE;
     f.ppw = two && pieces > MFMA_WAVES ? 2 : 1;
-    const int need = (pieces + f.ppw - 1) / f.ppw, turns = (need + MFMA_WAVES - 1) / MFMA_WAVES;
+    const int need = (pieces + f.ppw - 1) / f.ppw, turns = need <= MFMA_WAVES ? 1 : (need + 9) / 10;
     f.ks = (need + turns - 1) / turns;
-    const int units = 256 * ((10 + f.ks / 2) / f.ks), cols = (N + units - 1) / units;
-    f.cols = cols < MFMA_COLS ? MFMA_COLS : cols < 16 * MFMA_TILES ? cols : 16 * MFMA_TILES;
+    const int cols = even_columns(N, K, 256 * ((10 + f.ks / 2) / f.ks), 16 * mfma_tiles(f.ks));
+    f.cols = cols < MFMA_COLS ? MFMA_COLS : cols;
     if (whole) f.cols = (f.cols + 15) / 16 * 16;
     f.wgs = (N + f.cols - 1) / f.cols;
     return f;
