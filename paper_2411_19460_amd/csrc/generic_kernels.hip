@@ -80,6 +80,8 @@ struct Tiles {
 // LDS of the kernels that also keep per-token arrays of the chunk: the tiles, then `n` floats (sized at launch, so that
 // four workgroups fit a compute unit up to chunks of 256 tokens).
 inline size_t lds_bytes(int n) { return sizeof(Tiles) + (size_t)n * sizeof(float); }
+// Tokens of a chunk's tiles: what an array needs that is read for whole tiles, rows that do not exist included.
+__host__ __device__ __forceinline__ int whole_tiles(int Q) { return (Q + TM - 1) / TM * TM; }
 extern __shared__ __attribute__((aligned(16))) char dyn_lds[];
 
 // The part of a matrix that a contraction step takes, from its first element on: `outer` rows `stride` bytes apart (rows of a
@@ -549,7 +551,7 @@ template <typename T, bool VEC>
 __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp) {
     const int Q = sp.Q, N = sp.N, P = sp.P;
     Tiles& L = *(Tiles*)dyn_lds;
-    float *rowf = (float*)(dyn_lds + sizeof(Tiles)), *rowm = rowf + TM, *colm = rowm + TK, *srow = colm + TK, *cum = srow + TM, *dtf = cum + Q;
+    float *rowf = (float*)(dyn_lds + sizeof(Tiles)), *rowm = rowf + TM, *colm = rowm + TK, *srow = colm + TK, *cum = srow + TM, *dtf = cum + whole_tiles(Q);
     const int NT = (Q + TM - 1) / TM, NP = (P + TM - 1) / TM;
     const Place at = place(xcd_order(blockIdx.x, gridDim.x), NP * sp.H * NT, sp.nc);
     const int c = at.c, b = at.b, V = chunk_rows(sp, c, Q);
@@ -1173,7 +1175,7 @@ hipError_t fwd_segment(const SegParams& sp, hipStream_t st) {
     const hipError_t e = scores_states<T, VEC>(sp, 1, st);
     if (e != hipSuccess) return e;
     SSDK_LAUNCH(K_SCAN_FWD, st, k_state_scan<false>, dim3(cdiv(sp.P * sp.N, NTHREADS), sp.H, sp.Bt), dim3(NTHREADS), sp);
-    SSDK_LAUNCH_LDS(K_CHUNK_OUT, st, (k_chunk_out<T, VEC>), dim3(sp.Bt * sp.nc * sp.H * cdiv(sp.P, TM) * cdiv(sp.Q, TM)), dim3(NTHREADS), lds_bytes(2 * sp.Q + 3 * TM), sp);
+    SSDK_LAUNCH_LDS(K_CHUNK_OUT, st, (k_chunk_out<T, VEC>), dim3(sp.Bt * sp.nc * sp.H * cdiv(sp.P, TM) * cdiv(sp.Q, TM)), dim3(NTHREADS), lds_bytes(2 * whole_tiles(sp.Q) + 3 * TM), sp);
     return hipSuccess;
 }
 
