@@ -553,7 +553,7 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp) {
     Tiles& L = *(Tiles*)dyn_lds;
     float *rowf = (float*)(dyn_lds + sizeof(Tiles)), *rowm = rowf + TM, *colm = rowm + TK, *srow = colm + TK, *cum = srow + TM, *dtf = cum + whole_tiles(Q);
     const int NT = (Q + TM - 1) / TM, NP = (P + TM - 1) / TM;
-    const Place at = place(xcd_order(blockIdx.x, gridDim.x), NP * sp.H * NT, sp.nc);
+    const Place at = place(xcd_order(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y), NP * sp.H * NT, sp.nc);
     const int c = at.c, b = at.b, V = chunk_rows(sp, c, Q);
     const uint32_t q = (uint32_t)at.z / (uint32_t)NP, it = (uint32_t)at.z / (uint32_t)(NP * sp.H);
     const int p0 = (at.z - (int)q * NP) * TM, h = (int)(q - it * sp.H), g = (uint32_t)h / (uint32_t)sp.hpg;
@@ -1175,7 +1175,8 @@ hipError_t fwd_segment(const SegParams& sp, hipStream_t st) {
     const hipError_t e = scores_states<T, VEC>(sp, 1, st);
     if (e != hipSuccess) return e;
     SSDK_LAUNCH(K_SCAN_FWD, st, k_state_scan<false>, dim3(cdiv(sp.P * sp.N, NTHREADS), sp.H, sp.Bt), dim3(NTHREADS), sp);
-    SSDK_LAUNCH_LDS(K_CHUNK_OUT, st, (k_chunk_out<T, VEC>), dim3(sp.Bt * sp.nc * sp.H * cdiv(sp.P, TM) * cdiv(sp.Q, TM)), dim3(NTHREADS), lds_bytes(2 * whole_tiles(sp.Q) + 3 * TM), sp);
+    // (two dimensions of the grid: a launch has at most 2^32 threads in one)
+    SSDK_LAUNCH_LDS(K_CHUNK_OUT, st, (k_chunk_out<T, VEC>), dim3(sp.Bt * sp.nc * sp.H, cdiv(sp.P, TM) * cdiv(sp.Q, TM)), dim3(NTHREADS), lds_bytes(2 * whole_tiles(sp.Q) + 3 * TM), sp);
     return hipSuccess;
 }
 

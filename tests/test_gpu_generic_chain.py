@@ -2,7 +2,9 @@
 has no second diagonal step), rows in and out of groups of four (16-byte loads or element by element), head slices that the two
 slicings share and do not share; every tensor against the oracle."""
 import pytest
+import torch
 
+import paper_2411_19460_amd as pk
 from paper_2411_19460_amd import synth
 from parity_util import check, dev_inputs, host, run_gpu, run_oracle
 
@@ -34,3 +36,19 @@ def test_steps_and_halves_of_tiles(case):
         check(k, host(g[k]), go[k], tol)
     for k in ("ddt", "dA", "dD"):         # sums over the chunk of such sums
         check(k, host(g[k]), go[k], 4 * tol)
+
+
+def test_as_many_tiles_as_a_launch_has_threads_for():
+    """2^24 workgroups of 256 threads in one span, more than one dimension of a grid takes: 1048576 tokens of 1024 heads.  A head's output
+    does not depend on the others: the first and the last two against a call on them alone."""
+    L, H, Q, g = 1 << 20, 1024, 128, torch.Generator(device="cuda")
+    g.manual_seed(5)
+    x = torch.randn((1, L, H, 1), generator=g, device="cuda", dtype=torch.bfloat16)
+    dt = torch.rand((1, L, H), generator=g, device="cuda", dtype=torch.bfloat16) * 0.1 + 0.001
+    A, D = -torch.rand(H, generator=g, device="cuda") * 8 - 1, torch.randn(H, generator=g, device="cuda")
+    B, C = (torch.randn((1, L, 1, 1), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    y, fin, _ = pk.ssd_fwd(x, dt, A, B, C, D, Q)
+    for h in (slice(0, 2), slice(H - 2, H)):
+        y2, fin2, _ = pk.ssd_fwd(x[:, :, h].contiguous(), dt[:, :, h].contiguous(), A[h], B, C, D[h], Q)
+        torch.cuda.synchronize()
+        assert torch.equal(y[:, :, h], y2) and torch.equal(fin[:, h], fin2)
