@@ -31,10 +31,11 @@ struct ConvParams {
     float* dstate_in;   // [Bt][3][C] fp32 or null
     const float* w;     // [C][4]
     const float* bias;  // [C] or null
-    float* part;        // [Bt][ntiles][5][C] partial sums of dw (k = 0..3) and dbias
+    float* part;        // [nwg][5][C] partial sums of dw (k = 0..3) and dbias
     int64_t L, u_bs, o_bs;  // tokens; batch stride of u / du and of out / dout in elements
     int64_t u_rs;           // elements between consecutive tokens of u / du (out / dout: C)
-    int C, ntiles;
+    int C;
+    uint32_t batch, nruns, nwg;  // backward: sequences, runs of one, workgroups side by side that share them out
     int tt;             // tokens per thread of this launch
     // out / dout as three dense tensors side by side instead of one: channels [cb[k], cb[k+1]) live in
     // part[k] with rows cb[k+1] - cb[k] apart (the block's x | B | C, each the shape the scan wants)
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(64) void k_conv_fwd(ConvParams cp) {
 // Backward.  g[t] = dout[t] silu'(pre[t]);  du[t] = sum_k w[k] g[t+3-k]  (g beyond the segment is 0; what
 // the segment on the right contributes to the last three rows arrives as dstate_out);
 // dw[k] = sum_t g[t] u[t-3+k];  dbias = sum_t g[t];  dstate_in[j] = du[-3+j].
-// The waves of a workgroup take consecutive runs of the same channels and add up their sums in LDS.  Stores of rows that are not there go to
+// The waves of a workgroup take consecutive runs of the same channels, of one sequence or of several, and add up their sums in LDS.  Stores of rows that are not there go to
 // an empty descriptor (see k_conv_fwd).  What bounds it: three rows' traffic a token (27 us for 4096 x 5376 at the rate of a copy), and
 // nearly as long the vector ALUs.  4096 x 5376 bf16 inside a step, with a wave a workgroup, a row at a time and every run's sums to
 // memory (a fifth of the traffic): 50 us and 6.7 for the sums' reduction; now 38 and 5.4.
@@ -257,13 +258,16 @@ __global__ __launch_bounds__(64 * BWD_WAVES, 2) void k_conv_bwd(ConvParams cp) {
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int first_c = blockIdx.x * 64 * V, c0 = first_c + lane * V;
     if (c0 >= cp.C) return;
-    const int64_t b = blockIdx.z, first = ((int64_t)blockIdx.y * BWD_WAVES + wv) * cp.tt;  // first own token
+    const uint32_t wg = blockIdx.z * gridDim.y + blockIdx.y;
+    if (wg >= cp.nwg) return;
+    const uint32_t run = wg * BWD_WAVES + wv, seq = run / cp.nruns;
+    const int64_t b = seq, first = (int64_t)(run - seq * cp.nruns) * cp.tt;  // first own token
     float acc[5][V];
 #pragma unroll
     for (int k = 0; k < 5; ++k)
 #pragma unroll
         for (int e = 0; e < V; ++e) acc[k][e] = 0.f;
-    if (first < cp.L || first == 0) {
+    if (seq < cp.batch) {
         // the run: tokens 0 .. n - 1 from t0 on, of which those in front of `skip` are another's
         const int64_t t0 = first > cp.L - cp.tt ? (cp.L > cp.tt ? cp.L - cp.tt : 0) : first;
         const int n = (int)(cp.L < cp.tt ? cp.L : cp.tt), skip = (int)(first - t0);
@@ -368,7 +372,7 @@ __global__ __launch_bounds__(64 * BWD_WAVES, 2) void k_conv_bwd(ConvParams cp) {
 #pragma unroll
         for (int e = 0; e < V; ++e) sums[wv][k * V + e][lane] = acc[k][e];
     __syncthreads();
-    float* part = cp.part + ((b * cp.ntiles + blockIdx.y) * 5) * (int64_t)cp.C;
+    float* part = cp.part + ((int64_t)wg * 5) * cp.C;
     for (int i = wv; i < 5 * V; i += BWD_WAVES) {
         float t = 0.f;
 #pragma unroll
@@ -415,10 +419,9 @@ constexpr int FWD_FILL = 5120, BWD_FILL = 3072;  // waves that fit the registers
 int fwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, FWD_FILL, MAX_TT, 0); }
 // (three tokens more go through the loop; a workgroup's sums stand for at least 256 tokens of a long sequence)
 int bwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, BWD_FILL, MAX_TT + 2 * U, 3); }
-int ntiles_bwd(const ssd_conv_shape_t* sh) {
-    const int64_t tile = (int64_t)BWD_WAVES * bwd_tt(sh);
-    return (int)((sh->seqlen + tile - 1) / tile);
-}
+// Runs of a sequence (an empty one has one too) and workgroups for all of them: 65535 sequences of 65535 MAX_TT tokens stay below 2^32 runs.
+uint32_t bwd_runs(const ssd_conv_shape_t* sh) { return sh->seqlen ? (uint32_t)((sh->seqlen + bwd_tt(sh) - 1) / bwd_tt(sh)) : 1; }
+uint32_t bwd_wgs(const ssd_conv_shape_t* sh) { return (uint32_t)(((uint64_t)sh->batch * bwd_runs(sh) + BWD_WAVES - 1) / BWD_WAVES); }
 
 }  // namespace
 }  // namespace ssdk
@@ -427,7 +430,7 @@ using namespace ssdk;
 
 extern "C" size_t ssd_conv1d_workspace_bytes(const ssd_conv_shape_t* sh) {
     if (check(sh) != SSD_OK) return 0;
-    const size_t n = (size_t)sh->batch * (size_t)(ntiles_bwd(sh) > 0 ? ntiles_bwd(sh) : 1) * 5 * (size_t)sh->channels * 4;
+    const size_t n = (size_t)bwd_wgs(sh) * 5 * (size_t)sh->channels * 4;
     return (n + 255) & ~(size_t)255;
 }
 
@@ -523,19 +526,22 @@ int conv_bwd_impl(const ssd_conv_shape_t* sh, const void* u, const float* w, con
     cp.u_bs = sh->batch_stride ? sh->batch_stride : sh->seqlen * cp.u_rs;
     cp.o_bs = sh->batch_stride ? sh->batch_stride : sh->seqlen * sh->channels;
     cp.tt = bwd_tt(sh);
-    cp.ntiles = ntiles_bwd(sh) > 0 ? ntiles_bwd(sh) : 1;
+    cp.batch = (uint32_t)sh->batch;
+    cp.nruns = bwd_runs(sh);
+    cp.nwg = bwd_wgs(sh);
     if (!bind_split(cp, split, true)) return SSD_ERR_ARG;
     hipStream_t st = (hipStream_t)hip_stream;
     const bool bf = sh->dtype == SSD_BF16;
     const int V = vec_width(cp, bf);
-    const dim3 grid((cp.C / V + 63) / 64, (unsigned)cp.ntiles, (unsigned)sh->batch);
+    const uint32_t deep = (cp.nwg + 65534) / 65535;
+    const dim3 grid((cp.C / V + 63) / 64, (cp.nwg + deep - 1) / deep, deep);
     if (bf && V == 4) hipLaunchKernelGGL((k_conv_bwd<bf16_t, 4>), grid, dim3(64 * BWD_WAVES), 0, st, cp);
     else if (bf) hipLaunchKernelGGL((k_conv_bwd<bf16_t, 1>), grid, dim3(64 * BWD_WAVES), 0, st, cp);
     else if (V == 2) hipLaunchKernelGGL((k_conv_bwd<float, 2>), grid, dim3(64 * BWD_WAVES), 0, st, cp);
     else hipLaunchKernelGGL((k_conv_bwd<float, 1>), grid, dim3(64 * BWD_WAVES), 0, st, cp);
     if (hipGetLastError() != hipSuccess) return SSD_ERR_LAUNCH;
-    hipLaunchKernelGGL(k_conv_reduce, dim3((5 * cp.C + 63) / 64), dim3(COLSUM_THREADS), 0, st, cp.part, (int64_t)sh->batch * cp.ntiles,
-                       cp.C, dw, dbias, (flags & SSD_FLAG_ACCUM_PARAM) ? 1 : 0);
+    hipLaunchKernelGGL(k_conv_reduce, dim3((5 * cp.C + 63) / 64), dim3(COLSUM_THREADS), 0, st, cp.part, (int64_t)cp.nwg, cp.C,
+                       dw, dbias, (flags & SSD_FLAG_ACCUM_PARAM) ? 1 : 0);
     return hipGetLastError() == hipSuccess ? SSD_OK : SSD_ERR_LAUNCH;
 }
 

@@ -56,3 +56,20 @@ def test_runs(dtype, Bt, C, lengths, states):
 def test_few_channels(dtype, C):
     """Fewer channels than a thread's share of a wider tensor."""
     test_runs(dtype, 2, C, (1, 2, 7, 8, 9, 40, 300), True)
+
+
+@pytest.mark.parametrize("dtype,Bt,C,L", [("bf16", 7, 264, 1), ("bf16", 9, 2048, 64), ("f32", 6, 1536, 30), ("bf16", 5, 8, 0), ("bf16", 258, 512, 100)])
+def test_waves_of_a_workgroup_on_several_sequences(dtype, Bt, C, L):
+    """A sequence with fewer runs than a workgroup has waves shares it with its neighbours: every sequence has gradients, the last workgroup
+    waves without any.  Tolerance as for every use of the convolution."""
+    T = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L)
+    normal = lambda *shape, t=torch.float32: torch.randn(shape, generator=g, device="cuda", dtype=t)  # noqa: E731
+    w, bias, u, dout, st, dso = normal(C, 4) * 0.5, normal(C), normal(Bt, L, C, t=T), normal(Bt, L, C, t=T), normal(Bt, 3, C, t=T), normal(Bt, 3, C)
+    got = pk.ssd_conv1d_bwd(u, w, bias, st, dout, dso)
+    torch.cuda.synchronize()
+    go = conv_ref.conv1d_silu_bwd(host(u), host(w), host(bias), host(st), host(dout), host(dso))
+    for k in ("du", "dstate_in", "dw", "dbias"):
+        if got[k].numel():
+            check(k, host(got[k]), go[k], TOL[dtype])
