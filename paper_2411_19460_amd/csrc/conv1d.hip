@@ -250,7 +250,8 @@ __global__ __launch_bounds__(64) void k_conv_fwd(ConvParams cp) {
 // The waves of a workgroup take consecutive runs of the same channels, of one sequence or of several, and add up their sums in LDS.  Stores of rows that are not there go to
 // an empty descriptor (see k_conv_fwd).  What bounds it: three rows' traffic a token (27 us for 4096 x 5376 at the rate of a copy), and
 // nearly as long the vector ALUs.  4096 x 5376 bf16 inside a step, with a wave a workgroup, a row at a time and every run's sums to
-// memory (a fifth of the traffic): 50 us and 6.7 for the sums' reduction; now 38 and 5.4.
+// memory (a fifth of the traffic): 50 us and 6.7 for the sums' reduction; now 38 and 5.4.  64 sequences of 64 tokens, 5376 and 10752 channels, both
+launches: 57 and 144 us with the waves of a workgroup bound to one sequence, which had no runs for them, now 39 and 64.
 template <typename T, int V>
 __global__ __launch_bounds__(64 * BWD_WAVES, 2) void k_conv_bwd(ConvParams cp) {
     typedef typename Vec<T, V>::Raw Raw;
@@ -409,16 +410,18 @@ int check(const ssd_conv_shape_t* sh) {
 
 // Tokens per thread, `less` fewer than a multiple of 2 U and than `most`: one round of `waves` waves, evenly filled, unless that makes the runs too short or
 // too long.  Forward with 2048 / 3072 / 4096 / 5120 waves, 6001 x 5376: 25.9, 27.6, 24.9, 24.7 us; backward with 1024 / 2048 / 3072 / 4096:
-// 53.9, 53.9, 48.4, 58.6 (3072 fit, of the others some run behind the rest).
-int pick_tt(const ssd_conv_shape_t* sh, int waves, int most, int less) {
-    const int64_t cols = ((int64_t)sh->channels + 255) / 256 * sh->batch;  // waves side by side, at least one
+// 53.9, 53.9, 48.4, 58.6 (3072 fit, of the others some run behind the rest).  Waves of V channels a thread: with four counted for two (fp32)
+// or one, runs were too short, and the launch twice or four times as many waves as fit: 4096 x 1792 fp32 13.2 us, now 12.0.
+int pick_tt(const ssd_conv_shape_t* sh, int V, int waves, int most, int less) {
+    const int64_t cols = ((int64_t)sh->channels + 64 * V - 1) / (64 * V) * sh->batch;  // waves side by side, at least one
     const int64_t runs = cols < waves ? waves / cols : 1, tt = (sh->seqlen + runs - 1) / runs + less;
     return (tt > most - 2 * U ? most : tt < MIN_TT ? MIN_TT : (int)(tt + 2 * U - 1) / (2 * U) * (2 * U)) - less;
 }
 constexpr int FWD_FILL = 5120, BWD_FILL = 3072;  // waves that fit the registers of the chip
-int fwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, FWD_FILL, MAX_TT, 0); }
-// (three tokens more go through the loop; a workgroup's sums stand for at least 256 tokens of a long sequence)
-int bwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, BWD_FILL, MAX_TT + 2 * U, 3); }
+int fwd_tt(const ssd_conv_shape_t* sh, int V) { return pick_tt(sh, V, FWD_FILL, MAX_TT, 0); }
+// (three tokens more go through the loop; a workgroup's sums stand for at least 256 tokens of a long sequence; the workspace's size
+// follows, and a caller asks for it without the layout that decides how many channels a thread takes)
+int bwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, 4, BWD_FILL, MAX_TT + 2 * U, 3); }
 // Runs of a sequence (an empty one has one too) and workgroups for all of them: 65535 sequences of 65535 MAX_TT tokens stay below 2^32 runs.
 uint32_t bwd_runs(const ssd_conv_shape_t* sh) { return sh->seqlen ? (uint32_t)((sh->seqlen + bwd_tt(sh) - 1) / bwd_tt(sh)) : 1; }
 uint32_t bwd_wgs(const ssd_conv_shape_t* sh) { return (uint32_t)(((uint64_t)sh->batch * bwd_runs(sh) + BWD_WAVES - 1) / BWD_WAVES); }
@@ -485,7 +488,7 @@ int conv_fwd_impl(const ssd_conv_shape_t* sh, const void* u, const float* w, con
     const bool bf = sh->dtype == SSD_BF16;
     const int V = vec_width(cp, bf);
     // an empty sequence still hands the state on: one tile, whose token loop is empty
-    cp.tt = fwd_tt(sh);
+    cp.tt = fwd_tt(sh, V);
     const dim3 grid((cp.C / V + 63) / 64, (unsigned)(cp.L > 0 ? (cp.L + cp.tt - 1) / cp.tt : 1), (unsigned)sh->batch);
     const bool whole = cp.L >= cp.tt;
 #define CONV_FWD(T, W) \
