@@ -251,7 +251,7 @@ __global__ __launch_bounds__(64) void k_conv_fwd(ConvParams cp) {
 // an empty descriptor (see k_conv_fwd).  What bounds it: three rows' traffic a token (27 us for 4096 x 5376 at the rate of a copy), and
 // nearly as long the vector ALUs.  4096 x 5376 bf16 inside a step, with a wave a workgroup, a row at a time and every run's sums to
 // memory (a fifth of the traffic): 50 us and 6.7 for the sums' reduction; now 38 and 5.4.  64 sequences of 64 tokens, 5376 and 10752 channels, both
-launches: 57 and 144 us with the waves of a workgroup bound to one sequence, which had no runs for them, now 39 and 64.
+// launches: 57 and 144 us with the waves of a workgroup bound to one sequence, which had no runs for them, now 39 and 64.
 template <typename T, int V>
 __global__ __launch_bounds__(64 * BWD_WAVES, 2) void k_conv_bwd(ConvParams cp) {
     typedef typename Vec<T, V>::Raw Raw;
