@@ -268,4 +268,4 @@ def test_convolution_scratch_for_any_number_of_channels(channels):
             for seqlen in (0, 1, 7, 100, 65536):
                 sh = binding.ssd_conv_shape_t(dtype=dtype, channels=channels, batch=batch, seqlen=seqlen, batch_stride=0, u_row_stride=0)
                 got = L.ssd_conv1d_workspace_bytes(ctypes.byref(sh))
-                assert got >= batch * 5 * channels * 4 and got % 256 == 0, (dtype, batch, seqlen, got)
+                assert got >= 5 * channels * 4 and got % 256 == 0, (dtype, batch, seqlen, got)
