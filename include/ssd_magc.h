@@ -197,6 +197,7 @@ int ssd_decode(const ssd_shape_t* shape, const void* x, const void* dt, const fl
  *   dstate_out, dstate_in [Bt,3,C] fp32, either may be NULL; dw [C,4], dbias [C] (may be NULL) fp32,
  *   overwritten, or added to under SSD_FLAG_ACCUM_PARAM (the only flag); du must not alias dout.
  *   workspace: ssd_conv1d_workspace_bytes bytes, 256-byte aligned (partial sums of dw and dbias).
+ *              What is reported for a length does for every shorter one.
  * All pointers are device pointers; nothing is allocated; work is enqueued on hip_stream.
  */
 typedef struct ssd_conv_shape_t {

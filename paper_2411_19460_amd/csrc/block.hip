@@ -247,6 +247,7 @@ BlockWs layout(const BlockDims& d, bool bwd, int64_t ckpt_s = 0, bool lean = fal
         for (int i = 0; i < 2; ++i) w.dssm[i] = take(d.HPN * 4);
         for (int i = 0; i < 2; ++i) w.dconv[i] = take((size_t)3 * d.conv_dim * 4);
         w.dtpart = take(((s + DT_ROWS - 1) / DT_ROWS) * d.H * 4);
+        // (of these, what a whole segment takes does for a shorter one)
         const ssd_conv_shape_t cs = conv_shape(d, d.s);
         const ssd_norm_shape_t ns = norm_shape(d, d.s, 0.f);
         const ssd_norm_shape_t ps = pre_norm_shape(d, d.s, 0.f);

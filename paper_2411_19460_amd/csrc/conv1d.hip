@@ -424,7 +424,16 @@ int fwd_tt(const ssd_conv_shape_t* sh, int V) { return pick_tt(sh, V, FWD_FILL, 
 int bwd_tt(const ssd_conv_shape_t* sh) { return pick_tt(sh, 4, BWD_FILL, MAX_TT + 2 * U, 3); }
 // Runs of a sequence (an empty one has one too) and workgroups for all of them: 65535 sequences of 65535 MAX_TT tokens stay below 2^32 runs.
 uint32_t bwd_runs(const ssd_conv_shape_t* sh) { return sh->seqlen ? (uint32_t)((sh->seqlen + bwd_tt(sh) - 1) / bwd_tt(sh)) : 1; }
-uint32_t bwd_wgs(const ssd_conv_shape_t* sh) { return (uint32_t)(((uint64_t)sh->batch * bwd_runs(sh) + BWD_WAVES - 1) / BWD_WAVES); }
+uint32_t bwd_wgs(const ssd_conv_shape_t* sh, uint64_t runs) { return (uint32_t)(((uint64_t)sh->batch * runs + BWD_WAVES - 1) / BWD_WAVES); }
+// The most runs of any sequence up to this length: a longer one may have fewer (5376 channels, 730 and 731 tokens: 146 of 5, 57 of 13), and a buffer for the
+// longest segment has to do for a shorter last one.  Runs of every length between the shortest and the longest: as many as one round holds at most.
+uint64_t bwd_most_runs(const ssd_conv_shape_t* sh) {
+    const uint64_t cols = (((uint64_t)sh->channels + 255) / 256) * (uint64_t)sh->batch, round = cols < BWD_FILL ? BWD_FILL / cols : 1;
+    const uint64_t shortest = ((uint64_t)sh->seqlen + MIN_TT - 4) / (MIN_TT - 3), longest = ((uint64_t)sh->seqlen + MAX_TT + 2 * U - 4) / (MAX_TT + 2 * U - 3);
+    const uint64_t fit = shortest < round ? shortest : round, most = fit > longest ? fit : longest;
+    return most > 0 ? most : 1;
+}
+size_t bwd_bytes(const ssd_conv_shape_t* sh, uint64_t runs) { return ((size_t)bwd_wgs(sh, runs) * 5 * (size_t)sh->channels * 4 + 255) & ~(size_t)255; }
 
 }  // namespace
 }  // namespace ssdk
@@ -433,8 +442,7 @@ using namespace ssdk;
 
 extern "C" size_t ssd_conv1d_workspace_bytes(const ssd_conv_shape_t* sh) {
     if (check(sh) != SSD_OK) return 0;
-    const size_t n = (size_t)bwd_wgs(sh) * 5 * (size_t)sh->channels * 4;
-    return (n + 255) & ~(size_t)255;
+    return bwd_bytes(sh, bwd_most_runs(sh));
 }
 
 namespace ssdk {
@@ -511,7 +519,7 @@ int conv_bwd_impl(const ssd_conv_shape_t* sh, const void* u, const float* w, con
     if (!w || !dw) return SSD_ERR_NULL;
     if (sh->seqlen > 0 && (!u || (!dout && !split) || !du)) return SSD_ERR_NULL;
     if (sh->seqlen > 0 && du == dout) return SSD_ERR_ARG;
-    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < ssd_conv1d_workspace_bytes(sh)) return SSD_ERR_WORKSPACE;
+    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < bwd_bytes(sh, bwd_runs(sh))) return SSD_ERR_WORKSPACE;
     ConvParams cp;
     memset(&cp, 0, sizeof(cp));
     cp.u = u;
@@ -531,7 +539,7 @@ int conv_bwd_impl(const ssd_conv_shape_t* sh, const void* u, const float* w, con
     cp.tt = bwd_tt(sh);
     cp.batch = (uint32_t)sh->batch;
     cp.nruns = bwd_runs(sh);
-    cp.nwg = bwd_wgs(sh);
+    cp.nwg = bwd_wgs(sh, cp.nruns);
     if (!bind_split(cp, split, true)) return SSD_ERR_ARG;
     hipStream_t st = (hipStream_t)hip_stream;
     const bool bf = sh->dtype == SSD_BF16;

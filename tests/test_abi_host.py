@@ -269,3 +269,15 @@ def test_convolution_scratch_for_any_number_of_channels(channels):
                 sh = binding.ssd_conv_shape_t(dtype=dtype, channels=channels, batch=batch, seqlen=seqlen, batch_stride=0, u_row_stride=0)
                 got = L.ssd_conv1d_workspace_bytes(ctypes.byref(sh))
                 assert got >= 5 * channels * 4 and got % 256 == 0, (dtype, batch, seqlen, got)
+
+
+@pytest.mark.parametrize("channels,batch", [(5376, 1), (10752, 1), (1792, 3), (257, 1), (48, 64), (5377, 300)])
+def test_convolution_scratch_of_a_length_does_for_every_shorter_one(channels, batch):
+    """A caller sizes one buffer for the longest segment and runs the short last one in it."""
+    L = binding.lib()
+    most = 0
+    for seqlen in range(3000):
+        sh = binding.ssd_conv_shape_t(dtype=1, channels=channels, batch=batch, seqlen=seqlen, batch_stride=0, u_row_stride=0)
+        got = L.ssd_conv1d_workspace_bytes(ctypes.byref(sh))
+        assert got >= most, (seqlen, got, most)
+        most = got
