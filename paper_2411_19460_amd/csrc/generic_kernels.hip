@@ -100,16 +100,20 @@ __device__ __forceinline__ Part part_of(const void* p, int64_t first, int64_t st
 // (By value: a cast of a vector's element in place reads the vector's first.)
 __device__ __forceinline__ uint32_t bits_of(float v) { return __builtin_bit_cast(uint32_t, v); }
 __device__ __forceinline__ float float_of(uint32_t v) { return __builtin_bit_cast(float, v); }
-// Four elements as they come from memory: fp32, or bf16 in two registers (VEC) or in the low halves of four.  Nothing is done to
+// Four elements as they come from memory: fp32, or bf16 in two registers (not SINGLE) or in the low halves of four.  Nothing is done to
 // them before they are put down: that would wait for them.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-// VEC: `inner` and the elements in front of every row are multiples of four.
-template <typename T, bool VEC>
+// How they are asked for.  ALIGNED: `inner` and the elements in front of every row are multiples of four.  SHIFTED: any multiples of four bytes,
+// all that a load of several words asks for, in rows of four elements at least; four that would reach beyond the end of their row
+// are the row's last four, and move up on their way to LDS.  SINGLE: element by element, four times as many instructions and requests.
+enum Loads { ALIGNED, SHIFTED, SINGLE };
+template <typename T, Loads M>
 __device__ __forceinline__ u32x4 fetch4(__amdgpu_buffer_rsrc_t r, uint32_t bytes, uint32_t row, int lo, int inner) {
     u32x4 v;
-    if constexpr (VEC) {
-        const uint32_t o = lo < inner ? row + (uint32_t)lo * (uint32_t)sizeof(T) : bytes;
+    if constexpr (M != SINGLE) {
+        const int at = M == SHIFTED && lo > inner - 4 ? inner - 4 : lo;
+        const uint32_t o = lo < inner ? row + (uint32_t)at * (uint32_t)sizeof(T) : bytes;
         if constexpr (sizeof(T) == 4) {
             v = __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0);
         } else {
@@ -127,11 +131,18 @@ __device__ __forceinline__ u32x4 fetch4(__amdgpu_buffer_rsrc_t r, uint32_t bytes
     }
     return v;
 }
-template <typename T, bool VEC>
+template <typename T, Loads M>
 __device__ __forceinline__ f32x4 unpack(const u32x4& v) {
     if constexpr (sizeof(T) == 4) return __builtin_bit_cast(f32x4, v);
-    else if constexpr (VEC) return f32x4{float_of(v[0] << 16), float_of(v[0] & 0xffff0000u), float_of(v[1] << 16), float_of(v[1] & 0xffff0000u)};
+    else if constexpr (M != SINGLE) return f32x4{float_of(v[0] << 16), float_of(v[0] & 0xffff0000u), float_of(v[1] << 16), float_of(v[1] & 0xffff0000u)};
     else return f32x4{float_of(v[0] << 16), float_of(v[1] << 16), float_of(v[2] << 16), float_of(v[3] << 16)};
+}
+// Elements lo .. lo + 3 from the last four of a row of `inner` (beyond its end: all of them are zero already).
+__device__ __forceinline__ f32x4 moved_up(f32x4 v, int lo, int inner) {
+    const int by = lo + 4 - inner;
+    const bool two = by > 0 && (by & 2), one = by > 0 && (by & 1);
+    v = f32x4{two ? v[2] : v[0], two ? v[3] : v[1], two ? 0.f : v[2], two ? 0.f : v[3]};
+    return f32x4{one ? v[1] : v[0], one ? v[2] : v[1], one ? v[3] : v[2], one ? 0.f : v[3]};
 }
 
 // A value (the thread index) that the optimiser cannot see through: what is derived from it is formed anew in every turn of a loop
@@ -147,35 +158,36 @@ __device__ __forceinline__ int piece_hi(int tid) { return tid >> 3; }
 __device__ __forceinline__ int piece_lo(int tid) { return (tid & 7) * 4; }
 
 // (kc as an argument, not a template one: where the products of a chain differ in it, the loads stay outside of branches.)
-template <typename T, bool VEC>
+template <typename T, Loads M>
 __device__ __forceinline__ void fetch(u32x4 (&r)[2], bool kc, const Part& s, bool live) {
     const int tid = opaque(threadIdx.x), lo = piece_lo(tid);
-    const uint32_t row = (uint32_t)piece_hi(tid) * s.stride, bytes = live ? (uint32_t)s.outer * s.stride : 0u;
+    // the last elements of a row that is longer than four: its last four begin in front of the part
+    const uint32_t back = M == SHIFTED && s.inner < 4 ? 4 * (uint32_t)sizeof(T) : 0u;
+    const uint32_t row = (uint32_t)piece_hi(tid) * s.stride + back, bytes = live ? (uint32_t)s.outer * s.stride + back : 0u;
     // uniform by construction; said again, or a part that the compiler has in vector registers makes it loop over the lanes' values
-    const uint64_t p = (uint64_t)s.p;
+    const uint64_t p = (uint64_t)s.p - back;
     const uint32_t a0 = __builtin_amdgcn_readfirstlane((uint32_t)p), a1 = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)((uint64_t)a1 << 32 | a0), 0, bytes, 0x00020000);
-    r[0] = fetch4<T, VEC>(rs, bytes, row, lo, s.inner);
-    r[1] = fetch4<T, VEC>(rs, bytes, row + (kc ? 32u * s.stride : 0u), lo + (kc ? 0 : 32), s.inner);
+    r[0] = fetch4<T, M>(rs, bytes, row, lo, s.inner);
+    r[1] = fetch4<T, M>(rs, bytes, row + (kc ? 32u * s.stride : 0u), lo + (kc ? 0 : 32), s.inner);
 }
-// wt(v, hi, lo, piece) weights a piece in place on its way to LDS.
-template <typename T, bool VEC, class W>
-__device__ __forceinline__ void put(const u32x4 (&r)[2], bool kc, float* L, W wt) {
+// wt(v, hi, lo, piece) weights a piece in place on its way to LDS.  `inner`: the part's.
+template <typename T, Loads M, class W>
+__device__ __forceinline__ void put(const u32x4 (&r)[2], bool kc, float* L, int inner, W wt) {
     const int tid = opaque(threadIdx.x), hi = piece_hi(tid), lo = piece_lo(tid);
+    const bool shifted = M == SHIFTED && inner < (kc ? 32 : 64);  // uniform
     float* at = L + hi * (kc ? KPITCH : RPITCH) + lo;
-    f32x4 v = unpack<T, VEC>(r[0]);
+    f32x4 v = unpack<T, M>(r[0]);
+    if (shifted) v = moved_up(v, lo, inner);
     wt(v, hi, lo, 0);
     *(f32x4*)at = v;
-    v = unpack<T, VEC>(r[1]);
+    v = unpack<T, M>(r[1]);
+    if (shifted) v = moved_up(v, lo + (kc ? 0 : 32), inner);
     wt(v, hi, lo, 1);
     *(f32x4*)(at + (kc ? 32 * KPITCH : 32)) = v;
 }
-// Four consecutive values of a per-token array (VEC: 16-byte aligned).
-template <bool VEC>
-__device__ __forceinline__ f32x4 ld4(const float* p) {
-    if (VEC) return *(const f32x4*)p;
-    return f32x4{p[0], p[1], p[2], p[3]};
-}
+// Four consecutive values of a per-token array in LDS, from a multiple of four on.
+__device__ __forceinline__ f32x4 ld4(const float* p) { return *(const f32x4*)p; }
 struct NoWeight {
     __device__ __forceinline__ void operator()(f32x4&, int, int, int) const {}
 };
@@ -330,7 +342,7 @@ __device__ __forceinline__ Place place(int id, int per, int nc) {
 // (0, 0) of role 0 stores cum and dt for the steps that follow.
 // RAW: dt as it leaves a projection.  A template argument: as a branch it took 0.5 us of the 8.4 and 26.6 that the kernel
 // takes of 512 and 2048 tokens (fp32, 8 and 24 heads).
-template <typename T, bool RAW, bool VEC>
+template <typename T, bool RAW, Loads LT, Loads LF>
 __global__ __launch_bounds__(NTHREADS, 4) void k_scores_states(SegParams sp, int nroles) {
     Tiles& L = *(Tiles*)dyn_lds;
     float* red = (float*)(dyn_lds + sizeof(Tiles));  // [4], then the tokens' weights [Q]
@@ -354,12 +366,12 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_scores_states(SegParams sp, int
             (N + TK - 1) / TK, L,
             [&](Staged& R, int s, bool live) {
                 const int k0 = s * TK;
-                fetch<T, VEC>(R.a, true, part_of<T>(sp.Cm, base + i0 * bt + k0, bt, least(TM, V - i0), N - k0), live);
-                fetch<T, VEC>(R.b, true, part_of<T>(sp.Bm, base + j0 * bt + k0, bt, least(TM, V - j0), N - k0), live);
+                fetch<T, LT>(R.a, true, part_of<T>(sp.Cm, base + i0 * bt + k0, bt, least(TM, V - i0), N - k0), live);
+                fetch<T, LT>(R.b, true, part_of<T>(sp.Bm, base + j0 * bt + k0, bt, least(TM, V - j0), N - k0), live);
             },
-            [&](const Staged& R, int, float* la, float* lb) {
-                put<T, VEC>(R.a, true, la, NoWeight{});
-                put<T, VEC>(R.b, true, lb, NoWeight{});
+            [&](const Staged& R, int s, float* la, float* lb) {
+                put<T, LT>(R.a, true, la, N - s * TK, NoWeight{});
+                put<T, LT>(R.b, true, lb, N - s * TK, NoWeight{});
             },
             [&](int, const float* la, const float* lb) { tile_mma<true, true>(acc, la, lb); }, [] {});
         float* out = sp.Gm + (((int64_t)b * sp.nc + c) * sp.G + g) * Q * Q;
@@ -435,12 +447,12 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_scores_states(SegParams sp, int
         (V + TK - 1) / TK, L,
         [&](Staged& R, int s, bool live) {
             const int k0 = s * TK;
-            fetch<T, VEC>(R.a, false, part_of<T>(lhs, xbase + k0 * xt, xt, least(TK, V - k0), P - p0), live);
-            fetch<T, VEC>(R.b, false, part_of<T>(rhs, bbase + k0 * bt, bt, least(TK, V - k0), N - n0), live);
+            fetch<T, LT>(R.a, false, part_of<T>(lhs, xbase + k0 * xt, xt, least(TK, V - k0), P - p0), live);
+            fetch<T, LT>(R.b, false, part_of<T>(rhs, bbase + k0 * bt, bt, least(TK, V - k0), N - n0), live);
         },
         [&](const Staged& R, int s, float* la, float* lb) {
-            put<T, VEC>(R.a, false, la, [&](f32x4& v, int hi, int, int) { v *= s * TK + hi < Q ? wt[s * TK + hi] : 0.f; });
-            put<T, VEC>(R.b, false, lb, NoWeight{});
+            put<T, LT>(R.a, false, la, P - p0, [&](f32x4& v, int hi, int, int) { v *= s * TK + hi < Q ? wt[s * TK + hi] : 0.f; });
+            put<T, LT>(R.b, false, lb, N - n0, NoWeight{});
         },
         [&](int, const float* la, const float* lb) { tile_mma<false, false>(acc, la, lb); }, form_cum);
     float* out = role == 0 ? sp.states + (((int64_t)b * (sp.nc + 1) + c) * sp.H + h) * P * N
@@ -547,7 +559,7 @@ __global__ __launch_bounds__(NTHREADS) void k_state_scan(SegParams sp) {
 // reference, exp(cum_i - cum_k) = exp(cum_i - ref) exp(ref - cum_k), both factors <= 1: one exp per token instead of one per score,
 // the first factor scales the rows; only the diagonal tile takes an exp per score.  The state's weight exp(cum_i) is applied to the
 // rows of its product.
-template <typename T, bool VEC>
+template <typename T, Loads LT, Loads LF>
 __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp) {
     const int Q = sp.Q, N = sp.N, P = sp.P;
     Tiles& L = *(Tiles*)dyn_lds;
@@ -585,34 +597,34 @@ __global__ __launch_bounds__(NTHREADS, 4) void k_chunk_out(SegParams sp) {
             const Part sb = part_of<float>(Hprev, (int64_t)p0 * N + k0, N, least(TM, P - p0), N - k0);
             const Part tb = part_of<T>(sp.x, xbase + p0 + k0 * xt, xt, least(TK, V - k0), P - p0);
             if constexpr (sizeof(T) == 4) {
-                fetch<float, VEC>(R.a, true, st ? sa : ta, live);
-                fetch<float, VEC>(R.b, st, st ? sb : tb, live);
+                fetch<float, LF>(R.a, true, st ? sa : ta, live);
+                fetch<float, LF>(R.b, st, st ? sb : tb, live);
             } else if (st) {
-                fetch<T, VEC>(R.a, true, sa, live);
-                fetch<float, VEC>(R.b, true, sb, live);
+                fetch<T, LT>(R.a, true, sa, live);
+                fetch<float, LF>(R.b, true, sb, live);
             } else {
-                fetch<float, VEC>(R.a, true, ta, live);
-                fetch<T, VEC>(R.b, false, tb, live);
+                fetch<float, LF>(R.a, true, ta, live);
+                fetch<T, LT>(R.b, false, tb, live);
             }
         },
         [&](const Staged& R, int s, float* la, float* lb) {
             if (s < nS) {
-                put<T, VEC>(R.a, true, la, NoWeight{});
-                put<float, VEC>(R.b, true, lb, NoWeight{});
+                put<T, LT>(R.a, true, la, N - s * TK, NoWeight{});
+                put<float, LF>(R.b, true, lb, N - s * TK, NoWeight{});
                 return;
             }
             const int k0 = (s - nS) * TK;
-            put<T, VEC>(R.b, false, lb, NoWeight{});
+            put<T, LT>(R.b, false, lb, P - p0, NoWeight{});
             if (s < nS + nO) {
-                put<float, VEC>(R.a, true, la, [&](f32x4& v, int, int k, int) { v *= ld4<VEC>(dtf + k0 + k); });
+                put<float, LF>(R.a, true, la, Q - k0, [&](f32x4& v, int, int k, int) { v *= ld4(dtf + k0 + k); });
             } else {
                 // Two steps of 32 tokens.  Of the first, the tile's upper rows take an exponential per score and the lower ones a
                 // factor per row and one per token, split at the step's last token; the second is the lower rows' own.
                 const int half = k0 > i0;
-                put<float, VEC>(R.a, true, la, [&](f32x4& v, int r, int k, int piece) {
+                put<float, LF>(R.a, true, la, Q - k0, [&](f32x4& v, int r, int k, int piece) {
                     if (piece == half) {
                         const float ci = cum[i0 + 32 * half + r];
-                        const f32x4 ck = ld4<VEC>(cum + k0 + k), dk = ld4<VEC>(dtf + k0 + k);
+                        const f32x4 ck = ld4(cum + k0 + k), dk = ld4(dtf + k0 + k);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const float f = expf(ci - ck[e]) * dk[e];
@@ -674,7 +686,7 @@ struct WalkLds {
 
 // u rows j0.. of one (chunk, head): transposed masked scores (without dt) times dY, then the leaving-adjoint term;
 // dx = dt u + D dY, and per token x . u (fterm) and dY . x (dDrow)
-template <typename T, bool VEC>
+template <typename T, Loads LT, Loads LF>
 __device__ __forceinline__ void walk_u(const SegParams& sp, WalkLds& L, int b, int c, int h, int z) {
     const int Q = sp.Q, N = sp.N, P = sp.P, NP = (P + TM - 1) / TM;
     const int p0 = (z % NP) * TM, j0 = (z / NP) * TM;  // tile 0 has the longest contraction
@@ -710,34 +722,34 @@ __device__ __forceinline__ void walk_u(const SegParams& sp, WalkLds& L, int b, i
             const Part sb = part_of<float>(dHnext, (int64_t)p0 * N + k0, N, least(TM, P - p0), N - k0);
             const Part tb = part_of<T>(sp.dy, dybase + p0 + k0 * xt, xt, least(TK, V - k0), P - p0);
             if constexpr (sizeof(T) == 4) {
-                fetch<float, VEC>(R.a, st, st ? sa : ta, live);
-                fetch<float, VEC>(R.b, st, st ? sb : tb, live);
+                fetch<float, LF>(R.a, st, st ? sa : ta, live);
+                fetch<float, LF>(R.b, st, st ? sb : tb, live);
             } else if (st) {
-                fetch<T, VEC>(R.a, true, sa, live);
-                fetch<float, VEC>(R.b, true, sb, live);
+                fetch<T, LT>(R.a, true, sa, live);
+                fetch<float, LF>(R.b, true, sb, live);
             } else {
-                fetch<float, VEC>(R.a, false, ta, live);
-                fetch<T, VEC>(R.b, false, tb, live);
+                fetch<float, LF>(R.a, false, ta, live);
+                fetch<T, LT>(R.b, false, tb, live);
             }
         },
         [&](const Staged& R, int s, float* la, float* lb) {
             if (s < nS) {
-                put<T, VEC>(R.a, true, la, NoWeight{});
-                put<float, VEC>(R.b, true, lb, NoWeight{});
+                put<T, LT>(R.a, true, la, N - s * TK, NoWeight{});
+                put<float, LF>(R.b, true, lb, N - s * TK, NoWeight{});
                 return;
             }
-            put<T, VEC>(R.b, false, lb, NoWeight{});
+            put<T, LT>(R.b, false, lb, P - p0, NoWeight{});
             if (s < nS + nO) {
                 const int k0 = j1 + (s - nS) * TK;
-                put<float, VEC>(R.a, false, la, [&](f32x4& v, int k, int, int) { v *= k0 + k < V ? cum[k0 + k] : 0.f; });
+                put<float, LF>(R.a, false, la, Q - j0, [&](f32x4& v, int k, int, int) { v *= k0 + k < V ? cum[k0 + k] : 0.f; });
             } else {
                 // the first step is the tile's upper rows' own; of the second, the lower rows take an exponential per score, the
                 // upper ones a factor per row and one per token
                 const int half = s > nS + nO, k0 = j0 + half * TK;
-                put<float, VEC>(R.a, false, la, [&](f32x4& v, int k, int r, int piece) {
+                put<float, LF>(R.a, false, la, Q - j0, [&](f32x4& v, int k, int r, int piece) {
                     if (piece == half) {
                         const float ck = cum[least(k0 + k, V - 1)];
-                        const f32x4 cj = ld4<VEC>(cum + k0 + r);
+                        const f32x4 cj = ld4(cum + k0 + r);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const float f = expf(ck - cj[e]);
@@ -804,7 +816,7 @@ __device__ __forceinline__ void walk_u(const SegParams& sp, WalkLds& L, int b, i
 
 // One 64 x 64 tile (on or below the diagonal) of dG[b,c,g,i,j] = sum over the heads of a slice of
 // exp(cum_i - cum_j) dt_j (dY_i . x_j), and per head the row and column sums of E = that (.) G
-template <typename T, bool VEC, bool DIAG>
+template <typename T, Loads LT, Loads LF, bool DIAG>
 __device__ __forceinline__ void walk_dg(const SegParams& sp, WalkLds& L, int b, int c, int g, int slice, int I, int J) {
     const int Q = sp.Q, P = sp.P, V = chunk_rows(sp, c, Q), ns = sp.dg_split;
     const int i0 = I * TM, j0 = J * TM;
@@ -832,16 +844,16 @@ __device__ __forceinline__ void walk_dg(const SegParams& sp, WalkLds& L, int b, 
         [&](Stage& R, int, bool live) {
             const int h = __builtin_amdgcn_readfirstlane(live ? h0 + lh : h0), k0 = __builtin_amdgcn_readfirstlane(lk * TK);
             const int64_t xrow = ((int64_t)c * Q * sp.H + h) * P + k0;
-            fetch<T, VEC>(R.a, true, part_of<T>(sp.dy, (int64_t)b * sp.dys_b + xrow + i0 * xt, xt, least(TM, V - i0), P - k0), live);
-            fetch<T, VEC>(R.b, true, part_of<T>(sp.x, (int64_t)b * sp.xs_b + xrow + j0 * xt, xt, least(TM, V - j0), P - k0), live);
+            fetch<T, LT>(R.a, true, part_of<T>(sp.dy, (int64_t)b * sp.dys_b + xrow + i0 * xt, xt, least(TM, V - i0), P - k0), live);
+            fetch<T, LT>(R.b, true, part_of<T>(sp.x, (int64_t)b * sp.xs_b + xrow + j0 * xt, xt, least(TM, V - j0), P - k0), live);
             const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;  // (every step: see chain)
             R.c = (tid < 2 * TM ? sp.cum : sp.dtf)[o + least((tid < TM ? i0 : j0) + (tid & (TM - 1)), V - 1)];
             if (!DIAG) R.f = sp.cum[o + i0 - 1];
             next(lh, lk);
         },
         [&](Stage& R, int, float* la, float* lb) {
-            put<T, VEC>(R.a, true, la, NoWeight{});
-            put<T, VEC>(R.b, true, lb, NoWeight{});
+            put<T, LT>(R.a, true, la, P - sk * TK, NoWeight{});
+            put<T, LT>(R.b, true, lb, P - sk * TK, NoWeight{});
             const int hb = sh & 1;
             if (sk == 0 && tid < 3 * TM) {
                 // off the diagonal the decay is a row factor times a column factor, split at the token in front of the rows
@@ -908,7 +920,7 @@ __device__ __forceinline__ void walk_dg(const SegParams& sp, WalkLds& L, int b, 
 // One 64 x 64 tile of the head sums of a slice, with the per-token dot products through the boundary states:
 //   role 0: part[i][n] = sum_h exp(cum_i) (dY_i . Hprev[:, n]),            gterm_i = exp(cum_i) dY_i . (Hprev C_i)
 //   role 1: part[j][n] = sum_h exp(T - cum_j) dt_j (x_j . dHnext[:, n]),   sterm_j = exp(T - cum_j) dt_j x_j . (dHnext B_j)
-template <typename T, bool VEC>
+template <typename T, Loads LT, Loads LF>
 __device__ __forceinline__ void walk_part(const SegParams& sp, WalkLds& L, int b, int c, int g, int slice, int z) {
     const int Q = sp.Q, N = sp.N, P = sp.P, NT = (Q + TM - 1) / TM, NN = (N + TM - 1) / TM, V = chunk_rows(sp, c, Q), ns = sp.part_split;
     const int r0 = (z % NT) * TM;
@@ -945,8 +957,8 @@ __device__ __forceinline__ void walk_part(const SegParams& sp, WalkLds& L, int b
             const int h = __builtin_amdgcn_readfirstlane(live ? h0 + lh : h0), k0 = __builtin_amdgcn_readfirstlane(lk * TK);
             const int64_t first = (int64_t)b * (role ? sp.xs_b : sp.dys_b) + (((int64_t)c * Q + r0) * sp.H + h) * P + k0;
             const float* S = role ? sp.dstates + (((int64_t)b * sp.nc + c) * sp.H + h) * P * N : sp.states + (((int64_t)b * (sp.nc + 1) + c) * sp.H + h) * P * N;
-            fetch<T, VEC>(R.a, true, part_of<T>(role ? sp.x : sp.dy, first, xt, least(TM, V - r0), P - k0), live);
-            fetch<float, VEC>(R.b, false, part_of<float>(S, (int64_t)k0 * N + n0, N, least(TK, P - k0), N - n0), live);
+            fetch<T, LT>(R.a, true, part_of<T>(role ? sp.x : sp.dy, first, xt, least(TM, V - r0), P - k0), live);
+            fetch<float, LF>(R.b, false, part_of<float>(S, (int64_t)k0 * N + n0, N, least(TK, P - k0), N - n0), live);
             const int64_t o = (((int64_t)b * sp.H + h) * sp.nc + c) * Q;  // (every step: see chain)
             R.c = sp.cum[o + il];
             R.d = sp.dtf[o + il];
@@ -955,9 +967,9 @@ __device__ __forceinline__ void walk_part(const SegParams& sp, WalkLds& L, int b
         },
         [&](Stage& R, int, float* la, float* lb) {
             if (sk == 0) wgt = role ? decay(R.T_ - R.c) * R.d : expf(R.c);
+            put<T, LT>(R.a, true, la, P - sk * TK, NoWeight{});
+            put<float, LF>(R.b, false, lb, N - n0, NoWeight{});
             if (++sk == KS) sk = 0;
-            put<T, VEC>(R.a, true, la, NoWeight{});
-            put<float, VEC>(R.b, false, lb, NoWeight{});
         },
         [&](int, const float* la, const float* lb) {
             tile_mma<false, true>(d, lb, la);
@@ -995,7 +1007,7 @@ __device__ __forceinline__ void walk_part(const SegParams& sp, WalkLds& L, int b
 }
 
 // The list: batch, chunk, group, and of the heads as many slices as the two slicings have boundaries in common.
-template <typename T, bool VEC>
+template <typename T, Loads LT, Loads LF>
 __global__ __launch_bounds__(NTHREADS, 3) void k_bwd_walk(SegParams sp, int ns) {
     WalkLds& L = *(WalkLds*)dyn_lds;
     const int NT = (sp.Q + TM - 1) / TM, NN = (sp.N + TM - 1) / TM, NP = (sp.P + TM - 1) / TM, npair = NT * (NT + 1) / 2;
@@ -1007,25 +1019,25 @@ __global__ __launch_bounds__(NTHREADS, 3) void k_bwd_walk(SegParams sp, int ns) 
     int z = at.z;
     // the workgroups that walk several heads first
     if (z < n_part) {
-        walk_part<T, VEC>(sp, L, b, c, g, s * ps + z / w_part, z % w_part);
+        walk_part<T, LT, LF>(sp, L, b, c, g, s * ps + z / w_part, z % w_part);
         return;
     }
     z -= n_part;
     if (z < n_dg) {
         int J = z % npair, I = 0;
         while (J > I) J -= ++I;
-        if (I == J) walk_dg<T, VEC, true>(sp, L, b, c, g, s * ds + z / npair, I, J);
-        else walk_dg<T, VEC, false>(sp, L, b, c, g, s * ds + z / npair, I, J);
+        if (I == J) walk_dg<T, LT, LF, true>(sp, L, b, c, g, s * ds + z / npair, I, J);
+        else walk_dg<T, LT, LF, false>(sp, L, b, c, g, s * ds + z / npair, I, J);
         return;
     }
     z -= n_dg;
-    walk_u<T, VEC>(sp, L, b, c, g * sp.hpg + s * hs + z % hs, z / hs);
+    walk_u<T, LT, LF>(sp, L, b, c, g * sp.hpg + s * hs + z % hs, z / hs);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Step 4 backward, one launch: 64 x 64 tiles of dC (role 0) / dB (role 1) from the slices' partial sums (see the
 // formulas at the top of the file), and per (chunk, head) ddt with the chunk's dA / dD partial sums.
-template <typename T, bool VEC>
+template <typename T, Loads LT, Loads LF>
 __global__ __launch_bounds__(NTHREADS) void k_bwd_final(SegParams sp) {
     __shared__ __attribute__((aligned(16))) Tiles L;
     __shared__ DdtLds D;
@@ -1116,27 +1128,27 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_final(SegParams sp) {
 #pragma unroll
                 for (int q = 0; q < SLICES; ++q) {
                     const float* G = dG + (q < dns ? q * QQ : 0);
-                    if (KC) fetch<float, VEC>(R.a[q], true, part_of<float>(G, (int64_t)r0 * Q + k0, Q, least(TM, V - r0), Q - k0), live);
-                    else fetch<float, VEC>(R.a[q], false, part_of<float>(G, (int64_t)k0 * Q + r0, Q, kn, Q - r0), live);
+                    if (KC) fetch<float, LF>(R.a[q], true, part_of<float>(G, (int64_t)r0 * Q + k0, Q, least(TM, V - r0), Q - k0), live);
+                    else fetch<float, LF>(R.a[q], false, part_of<float>(G, (int64_t)k0 * Q + r0, Q, kn, Q - r0), live);
                 }
-                fetch<T, VEC>(R.b, false, part_of<T>(rhs, bbase + n0 + k0 * bt, bt, kn, N - n0), live);
+                fetch<T, LT>(R.b, false, part_of<T>(rhs, bbase + n0 + k0 * bt, bt, kn, N - n0), live);
             },
             [&](Stage& R, int s, float* la, float* lb) {
                 u32x4 v[2];
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
-                    f32x4 t = unpack<float, VEC>(R.a[0][e]);
+                    f32x4 t = unpack<float, LF>(R.a[0][e]);
 #pragma unroll
-                    for (int q = 1; q < SLICES; ++q) t += q < dns ? unpack<float, VEC>(R.a[q][e]) : (f32x4)(0.f);
+                    for (int q = 1; q < SLICES; ++q) t += q < dns ? unpack<float, LF>(R.a[q][e]) : (f32x4)(0.f);
                     v[e] = __builtin_bit_cast(u32x4, t);
                 }
-                put<float, VEC>(v, KC, la, [&](f32x4& t, int hi, int lo, int piece) {  // on or below the diagonal
+                put<float, LF>(v, KC, la, KC ? Q - (first + s * TK) : Q - r0, [&](f32x4& t, int hi, int lo, int piece) {  // on or below the diagonal
                     const int k = first + s * TK, r = r0 + 32 * piece;
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         if (KC ? k + lo + e > r + hi : k + hi < r + lo + e) t[e] = 0.f;
                 });
-                put<T, VEC>(R.b, false, lb, NoWeight{});
+                put<T, LT>(R.b, false, lb, N - n0, NoWeight{});
             },
             [&](int, const float* la, const float* lb) { tile_mma<KC, false>(acc, la, lb); }, [] {});
     };
@@ -1152,57 +1164,65 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_final(SegParams sp) {
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-// 16-byte (fp32) / 8-byte (bf16) loads: sizes and every pointer and stride multiples of four elements
+// How T's tensors, and the fp32 arrays of the passes before, are asked for: sizes, strides and every pointer in elements of four, or in words, or neither.
 template <typename T>
-bool vec_ok(const SegParams& sp) {
-    const uintptr_t m = 4 * sizeof(T) - 1;
-    return ((sp.P | sp.N | sp.Q) & 3) == 0 && (((uintptr_t)sp.x | (uintptr_t)sp.dy | (uintptr_t)sp.Bm | (uintptr_t)sp.Cm) & m) == 0 &&
-           ((sp.xs_b | sp.dys_b | sp.bcs_b) & 3) == 0;
+bool in_units(const SegParams& sp, int unit) {  // of x, dY, B and C
+    const uintptr_t m = unit * sizeof(T) - 1;
+    return (sp.P | sp.N) % unit == 0 && (((uintptr_t)sp.x | (uintptr_t)sp.dy | (uintptr_t)sp.Bm | (uintptr_t)sp.Cm) & m) == 0 &&
+           (sp.xs_b | sp.dys_b | sp.bcs_b) % unit == 0;
 }
-
-template <typename T, bool VEC>
+template <typename T, Loads LT, Loads LF>
 hipError_t scores_states(const SegParams& sp, int nroles, hipStream_t st) {
     const int NT = cdiv(sp.Q, TM);
     const int n_cb = sp.Bt * sp.nc * sp.G * (NT * (NT + 1) / 2);
     const int n_st = sp.Bt * sp.nc * sp.H * nroles * cdiv(sp.N, TM) * cdiv(sp.P, TM);
-    if (sp.raw.dt) SSDK_LAUNCH_LDS(K_CHUNK_STATE, st, (k_scores_states<T, true, VEC>), dim3(n_cb + n_st), dim3(NTHREADS), lds_bytes(sp.Q + NTHREADS / 64), sp, nroles);
-    else SSDK_LAUNCH_LDS(K_CHUNK_STATE, st, (k_scores_states<T, false, VEC>), dim3(n_cb + n_st), dim3(NTHREADS), lds_bytes(sp.Q + NTHREADS / 64), sp, nroles);
+    if (sp.raw.dt) SSDK_LAUNCH_LDS(K_CHUNK_STATE, st, (k_scores_states<T, true, LT, LF>), dim3(n_cb + n_st), dim3(NTHREADS), lds_bytes(sp.Q + NTHREADS / 64), sp, nroles);
+    else SSDK_LAUNCH_LDS(K_CHUNK_STATE, st, (k_scores_states<T, false, LT, LF>), dim3(n_cb + n_st), dim3(NTHREADS), lds_bytes(sp.Q + NTHREADS / 64), sp, nroles);
     return hipSuccess;
 }
 
-template <typename T, bool VEC>
+template <typename T, Loads LT, Loads LF>
 hipError_t fwd_segment(const SegParams& sp, hipStream_t st) {
-    const hipError_t e = scores_states<T, VEC>(sp, 1, st);
+    const hipError_t e = scores_states<T, LT, LF>(sp, 1, st);
     if (e != hipSuccess) return e;
     SSDK_LAUNCH(K_SCAN_FWD, st, k_state_scan<false>, dim3(cdiv(sp.P * sp.N, NTHREADS), sp.H, sp.Bt), dim3(NTHREADS), sp);
     // (two dimensions of the grid: a launch has at most 2^32 threads in one)
-    SSDK_LAUNCH_LDS(K_CHUNK_OUT, st, (k_chunk_out<T, VEC>), dim3(sp.Bt * sp.nc * sp.H, cdiv(sp.P, TM) * cdiv(sp.Q, TM)), dim3(NTHREADS), lds_bytes(2 * whole_tiles(sp.Q) + 3 * TM), sp);
+    SSDK_LAUNCH_LDS(K_CHUNK_OUT, st, (k_chunk_out<T, LT, LF>), dim3(sp.Bt * sp.nc * sp.H, cdiv(sp.P, TM) * cdiv(sp.Q, TM)), dim3(NTHREADS), lds_bytes(2 * whole_tiles(sp.Q) + 3 * TM), sp);
     return hipSuccess;
 }
 
-template <typename T, bool VEC>
+template <typename T, Loads LT, Loads LF>
 hipError_t bwd_segment(const SegParams& sp0, hipStream_t st) {
     SegParams sp = sp0;
     sp.nslice = cdiv(sp.P * sp.N, NTHREADS) * (NTHREADS / 64);  // partial sums written by k_state_scan: one per wave
     const int NT = cdiv(sp.Q, TM), NN = cdiv(sp.N, TM), bcg = sp.Bt * sp.nc * sp.G;
-    const hipError_t e = scores_states<T, VEC>(sp, 2, st);
+    const hipError_t e = scores_states<T, LT, LF>(sp, 2, st);
     if (e != hipSuccess) return e;
     SSDK_LAUNCH(K_SCAN_BWD, st, k_state_scan<true>, dim3(cdiv(sp.P * sp.N, NTHREADS), sp.H, sp.Bt), dim3(NTHREADS), sp);
     const int n_part = bcg * sp.part_split * 2 * NN * NT, n_dg = bcg * sp.dg_split * (NT * (NT + 1) / 2), n_u = sp.Bt * sp.nc * sp.H * NT * cdiv(sp.P, TM);
     const int per_token = 2 * sp.Q + 2 * TM > 6 * TM ? 2 * sp.Q + 2 * TM : 6 * TM;
-    SSDK_LAUNCH_LDS(K_BWD_MAIN, st, (k_bwd_walk<T, VEC>), dim3(n_part + n_dg + n_u), dim3(NTHREADS), lds_bytes(per_token), sp, std::gcd(sp.part_split, sp.dg_split));
+    SSDK_LAUNCH_LDS(K_BWD_MAIN, st, (k_bwd_walk<T, LT, LF>), dim3(n_part + n_dg + n_u), dim3(NTHREADS), lds_bytes(per_token), sp, std::gcd(sp.part_split, sp.dg_split));
     const int n_dbc = bcg * 2 * NN * NT;
-    SSDK_LAUNCH(K_DBC, st, (k_bwd_final<T, VEC>), dim3(n_dbc + sp.Bt * sp.nc * sp.H), dim3(NTHREADS), sp);
+    SSDK_LAUNCH(K_DBC, st, (k_bwd_final<T, LT, LF>), dim3(n_dbc + sp.Bt * sp.nc * sp.H), dim3(NTHREADS), sp);
     return hipSuccess;
 }
 
-template <typename T>
-hipError_t fwd_any(const SegParams& sp, hipStream_t st) {
-    return vec_ok<T>(sp) ? fwd_segment<T, true>(sp, st) : fwd_segment<T, false>(sp, st);
+template <typename T, Loads LT, Loads LF>
+hipError_t segment(const SegParams& sp, bool bwd, hipStream_t st) {
+    return bwd ? bwd_segment<T, LT, LF>(sp, st) : fwd_segment<T, LT, LF>(sp, st);
 }
+// ALIGNED wherever it can be: it takes no care of a row's end.  SHIFTED for all else that is whole words apart: rows of scores in chunks of any length
+// (in fours with every other operand, or all of them singly: chunks of 63 / 101 / 127 tokens, fp32, 24 heads, 2000 / 2000 / 8192 tokens backward 204
+// / 205 / 594 us, with each operand by a flag of its own and single loads of the scores 160 / 180 / 498, so 149 / 152 / 428), odd widths and
+// addresses (256 tokens, one element off, 180 -> 130; states of 31, 101 -> 85).  bf16 at odd widths or addresses has only SINGLE loads for
+// its own tensors (states of 31 103 -> 90 us, from the fp32 arrays alone); rows of one to three elements have none of four.
 template <typename T>
-hipError_t bwd_any(const SegParams& sp, hipStream_t st) {
-    return vec_ok<T>(sp) ? bwd_segment<T, true>(sp, st) : bwd_segment<T, false>(sp, st);
+hipError_t any_segment(const SegParams& sp, bool bwd, hipStream_t st) {
+    if (sp.Q % 4 == 0 && in_units<T>(sp, 4)) return segment<T, ALIGNED, ALIGNED>(sp, bwd, st);
+    if (sp.P < 4 || sp.N < 4 || sp.Q < 4) return segment<T, SINGLE, SINGLE>(sp, bwd, st);
+    if (in_units<T>(sp, 4 / sizeof(T))) return segment<T, SHIFTED, SHIFTED>(sp, bwd, st);
+    if constexpr (sizeof(T) == 2) return segment<T, SINGLE, SHIFTED>(sp, bwd, st);
+    return segment<T, SINGLE, SINGLE>(sp, bwd, st);
 }
 
 }  // namespace
@@ -1223,11 +1243,11 @@ hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t s
 
 hipError_t generic_forward_segment(const SegParams& sp, bool is_bf16, bool need_y, hipStream_t st) {
     if (!need_y) return hipSuccess;  // the backward pass restores the states inside its own launches
-    return is_bf16 ? fwd_any<bf16_t>(sp, st) : fwd_any<float>(sp, st);
+    return is_bf16 ? any_segment<bf16_t>(sp, false, st) : any_segment<float>(sp, false, st);
 }
 
 hipError_t generic_backward_segment(const SegParams& sp, bool is_bf16, hipStream_t st) {
-    return is_bf16 ? bwd_any<bf16_t>(sp, st) : bwd_any<float>(sp, st);
+    return is_bf16 ? any_segment<bf16_t>(sp, true, st) : any_segment<float>(sp, true, st);
 }
 
 }  // namespace ssdk
