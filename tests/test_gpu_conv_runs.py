@@ -73,3 +73,9 @@ def test_waves_of_a_workgroup_on_several_sequences(dtype, Bt, C, L):
     for k in ("du", "dstate_in", "dw", "dbias"):
         if got[k].numel():
             check(k, host(got[k]), go[k], TOL[dtype])
+
+
+@pytest.mark.parametrize("dtype,Bt,C", [("f32", 1400, 512), ("bf16", 700, 2048), ("bf16", 520, 645)])
+def test_sequences_of_part_of_a_run(dtype, Bt, C):
+    """So many sequences that one run is a sequence, which ends inside a group of four or eight rows, or at its end."""
+    test_runs(dtype, Bt, C, (1, 3, 4, 5, 9, 12, 13, 20, 21, 45, 63), True)
