@@ -30,3 +30,22 @@ def test_two_widths(rows, K, N, wide):
     worst = ((out.float() - want).abs() / (want.abs() + 1)).max()
     assert worst <= 2 ** -8, worst          # a rounding of the result is half of this
     check("out", host(out[-300:]), host(want[-300:]), TOL["bf16"])
+
+
+@pytest.mark.parametrize("rows,K,N", [(4000, 200, 10568), (4100, 136, 4384), (8192, 72, 2560), (16300, 72, 10304)])
+def test_result_inside_a_wider_tensor(rows, K, N):
+    """The second width's origin and both widths' right edges in rows that go on behind them: the columns around the result, and a row
+    in front of it and one behind, stay as they are, and the result is that of a dense one, bit by bit."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    x = torch.randn((rows, K), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((N, K), generator=g, device="cuda") * K ** -0.5).to(torch.bfloat16)
+    wide = torch.full((rows + 2, N + 40), 7.0, device="cuda", dtype=torch.bfloat16)
+    out = wide[1:-1, 16:16 + N]
+    pk.ssd_linear_fwd(x, w, out=out)
+    dense = pk.ssd_linear_fwd(x, w)
+    torch.cuda.synchronize()
+    assert torch.equal(out, dense)
+    around = wide.clone()
+    around[1:-1, 16:16 + N] = 7.0
+    assert bool((around == 7.0).all())
