@@ -298,17 +298,29 @@ int even_columns(int N, int K, int units, int most) {
 // unit about ten waves (80 KB of w under way), the same number of workgroups in each: eight a unit with some units holding twice as many as
 // others took 3 % of a step.
 // A product that stands alone has nothing but the way to its first load to hide, and more waves do: sixteen, where the registers hold
-// them (one row; two up to 2560 k).  2560 x 10576 11.9 -> 11.6 us, 1536 x 3352 4.6 -> 4.4, 768 x 10576 with two rows 6.4 -> 6.0.  And where it
-// is many columns wide, small workgroups that start one after another keep the memory busier than a round that ends together: 5120 x 50288
-// 92 -> 84, with two rows 2560 x 50288 40.6 -> 37.5 (but 5120 x 50288 93 -> 100, and 768 x 32768 11.2 -> 11.8 with one).
+// them.  1536 x 3352 4.6 -> 4.4 us, 768 x 10576 with two rows 6.4 -> 6.0.  Better still are workgroups of four columns that start one after
+// another, as many as fit: they keep the memory busier than a round that ends together, and do not meet on the same channels where 16 or
+// 32 columns are a power of two of bytes.  us by rounds -> so: 5120 x 50288 85 -> 80, 8192 x 8192 24.9 -> 20.9, 16384 x 4096 26.1 -> 21.4; up to 4096
+// columns one workgroup a unit, of whole fours, is a round that starts at once (5120 x 2560 5.2 with four columns, 4.6 with twelve).  Two rows,
+// with twice the work to a load of w, are so where columns are many or rows long (8192 x 8192 25.8 -> 21.9, 4096 x 50288 72.5 -> 66.5, but 3072
+// -> 6144 7.8 -> 8.1), and take four or five waves at most where they are many, and eight columns where five waves or two leave a unit's last
+// ones idle (5120 x 50288 89.9 -> 85.3).
 template <int MODE>
 hipError_t launch_few(const FewParams& fp, FewOperands fo, hipStream_t st) {
-    const int pieces = (fp.K + FEW_PIECE - 1) / FEW_PIECE, turns = (pieces + FEW_WAVES - 1) / FEW_WAVES;
+    const int pieces = (fp.K + FEW_PIECE - 1) / FEW_PIECE;
+    const bool alone = MODE == 0 && !fo.cs, two = fp.rows > 1, wide = fp.N >= 12288;
+    const bool small = alone && pieces > 1 && (!two || wide || pieces > FEW_WAVES);
+    const int most = !small ? FEW_WAVES : two && wide ? (pieces % 5 ? 4 : 5) : pieces > FEW_WAVES ? 8 : FEW_WAVES, turns = (pieces + most - 1) / most;
     fo.ks = (pieces + turns - 1) / turns;
-    const bool alone = MODE == 0 && !fo.cs, roomy = fp.rows <= 1 ? turns == 1 : pieces <= 5;
-    const int units = 256 * (((alone && roomy ? 16 : 10) + fo.ks / 2) / fo.ks);
-    int cols = even_columns(fp.N, fp.K, units, alone && roomy && fp.N >= 16384 && fp.K >= 1024 ? 8 : FEW_COLS);
-    cols = cols < 4 ? 4 : cols;
+    int cols = 4;
+    if (small) {
+        if (two && wide && (fo.ks == 5 || fo.ks <= 2)) cols = 8;
+        if (!two && turns == 1 && fp.N <= 4096) cols = (fp.N + 1023) / 1024 * 4;
+        if (cols < fp.N >> 22) cols = fp.N >> 22;  // a launch has at most 2^32 threads
+    } else {
+        cols = even_columns(fp.N, fp.K, 256 * (((alone && (!two || pieces <= 5) ? 16 : 10) + fo.ks / 2) / fo.ks), FEW_COLS);
+        cols = cols < 4 ? 4 : cols;
+    }
     if (fo.stream) return fo.cs ? launch_few_kernel<MODE, true, true>(fp, fo, cols, st) : launch_few_kernel<MODE, false, true>(fp, fo, cols, st);
     return fo.cs ? launch_few_kernel<MODE, true, false>(fp, fo, cols, st) : launch_few_kernel<MODE, false, false>(fp, fo, cols, st);
 }
@@ -360,7 +372,8 @@ static_assert(10 * 16 * WPITCH + mfma_tiles(10) * 10 * 1024 <= MFMA_WAVES * 16 *
 // sums of squares of their producer (nparts per group of K / groups, row r of part i at ssq[16 i + r]).  SRC 3: packed rows,
 // no normalisation.  PARTS: row_parts(rows) (SRC 0: 1, rows of x are bf16 values as they are).
 // PPW: pieces of a wave that it keeps operands of; longer rows go by in turns (SRC 1: one, two of them and what their
-// normalisation takes do not fit the registers).
+// normalisation takes do not fit the registers).  The first of w of a turn is asked for in front of the last tile of the turn before: with three
+// rows 5120 x 50288 in five turns of four waves 89 us, 94 where it was asked for behind it.
 template <int SRC, bool STEP, int PARTS, bool STREAM, int PPW, bool TURNS>
 __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams fp, FewOperands fo) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -447,7 +460,6 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
         }
     }
     for (int kb = 0;;) {
-        if (TURNS && kb) operands(kb);
         if (norm && !norm_late && kb == 0) {
             for (int g = 0; g < fo.groups; ++g) {
                 if (tid < 256) part[(tid & 15) * 16 + (tid >> 4)] = row_share(g, g == 0);
@@ -510,7 +522,12 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
             for (int j = 0; j < PPW; ++j) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) *(u32x4*)(wt + (2 * i + r2) * WPITCH + 16 * l32) = v[i];
-                if (j + 1 < PPW || t + 1 < tiles) load(j + 1 < PPW ? t : t + 1, j + 1 < PPW ? j + 1 : 0);
+                if (j + 1 < PPW || t + 1 < tiles) {
+                    load(j + 1 < PPW ? t : t + 1, j + 1 < PPW ? j + 1 : 0);
+                } else if (TURNS && kb + PIECE * PPW * KS < fp.K) {  // the next turn's first
+                    aim(kb + PIECE * PPW * KS);
+                    load(0, 0);
+                }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // a wave's own rows: no barrier
                 f32x4v d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -535,9 +552,9 @@ __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams f
         }
         kb += PIECE * PPW * KS;
         if (!TURNS || kb >= fp.K) break;
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the compiler would otherwise have the first turn wait as well
-        aim(kb);
-        load(0, 0);
+        operands(kb);
+        // vmcnt(0): the compiler would otherwise have the first turn wait as well, where it has more under way
+        if (SRC != 0 || STEP) __builtin_amdgcn_s_waitcnt(0x0F70);
     }
     if (SRC == 1) {  // the row's squares of this wave's pieces
         ss += __shfl_xor(ss, 16, 64);
@@ -613,6 +630,8 @@ hipError_t launch_few_mfma_pieces(const FewParams& fp, const FewOperands& fo, in
 template <int SRC, int PARTS>
 hipError_t launch_few_mfma_parts(const FewParams& fp, const FewOperands& fo, int ppw, int wgs, size_t lds, hipStream_t st) {
     constexpr int most = SRC == 1 ? 1 : 2;
+    if constexpr (SRC == 0)
+        if (ppw == 1 && fp.K > PIECE * fo.ks) return launch_few_mfma_pieces<SRC, PARTS, 1, true>(fp, fo, wgs, lds, st);
     if (fp.K > PIECE * most * fo.ks) return launch_few_mfma_pieces<SRC, PARTS, most, true>(fp, fo, wgs, lds, st);
     return ppw == most ? launch_few_mfma_pieces<SRC, PARTS, most, false>(fp, fo, wgs, lds, st) : launch_few_mfma_pieces<SRC, PARTS, 1, false>(fp, fo, wgs, lds, st);
 }
@@ -627,26 +646,36 @@ hipError_t launch_few_mfma_src(const FewParams& fp, const FewOperands& fo, int p
 
 // Waves by the row, as launch_few: up to twelve where that saves a second turn, else up to ten.  (With ten at most the rows of a block of 96 heads,
 // of 3072 and 6144, went by in two turns of six waves: three blocks for three sequences 131 us, 112 so; 6144 x 2560 alone 9.1 and 8.6.  In more turns
-// anyway, three turns of eleven waves are 4 % slower than four of eight.)  One round of workgroups (or as many as are full), the same number in every
-// compute unit, of at least MFMA_COLS columns: with less of w than that to each, the operands of the rows would be most of what they fetch.
+// anyway, three turns of eleven waves are 4 % slower than four of eight, and four of seven 6 % faster than three of ten that do not have work for
+// all: 14336 x 4096 with sixteen rows 27.4 and 25.9.)  One round of workgroups (or as many as are full), the same number in every compute unit, of at least
+// MFMA_COLS columns: with less of w than that to each, the operands of the rows would be most of what they fetch.
+// A product that stands alone takes single tiles of a few waves, which start one after another (see launch_few), where its rows cost little to fetch
+// again: up to eight where four waves hold a row, up to four where a round would be long.  us by rounds -> so: 1024 x 50288 with three rows 21.3
+// -> 17.8, 2048 x 50288 34.4 -> 31.6, 4096 x 50288 75 -> 72, 5120 x 50288 97 -> 92, 16384 x 16384 101 -> 88; with eight rows 1024 x 50288 21.4 -> 18.1
+// but 2560 x 50288 40.8 -> 45.4 (eight waves of a piece each, 4096 x 50288, 78 -> 75).  With more rows three tiles are better than the five or six of a
+// round where four waves hold a row (1024 x 131072 43 -> 40).
 struct FewSplit {
     int ks, ppw, cols, wgs;
 };
-FewSplit few_split(int K, int N, bool two, bool whole) {  // two pieces a wave where one is not enough; whole tiles
+FewSplit few_split(int K, int N, bool two, bool whole, int lone) {  // two pieces a wave where one is not enough; whole tiles; rows of a product alone (else 0)
     FewSplit f;
     const int pieces = (K + PIECE - 1) / PIECE;
-    f.ppw = two && pieces > MFMA_WAVES ? 2 : 1;
-    const int need = (pieces + f.ppw - 1) / f.ppw, turns = need <= MFMA_WAVES ? 1 : (need + 9) / 10;
-    f.ks = (need + turns - 1) / turns;
+    const bool longer = (lone <= 4 || K % 2048 == 0) && (N >= 32768 || (int64_t)N * K >= 1 << 27), single = lone && lone <= 8 && pieces > 1 && (pieces <= 4 || longer);
+    f.ppw = two && !single && (pieces > MFMA_WAVES || (pieces > 10 && N > 256 * 64)) ? 2 : 1;  // (twelve waves have four tiles: one round, or six waves with six)
+    const int need = (pieces + f.ppw - 1) / f.ppw;
+    auto waves = [&](int turns) { return (need + turns - 1) / turns; };
+    int turns = single ? (need % 8 ? (need + 3) / 4 : need / 8) : need <= MFMA_WAVES ? 1 : (need + 9) / 10;
+    if (!single && turns > 1 && waves(turns + 1) > 5 && waves(turns + 1) * (turns + 1) < waves(turns) * turns) ++turns;
+    f.ks = waves(turns);
     const int cols = even_columns(N, K, 256 * ((10 + f.ks / 2) / f.ks), 16 * mfma_tiles(f.ks));
-    f.cols = cols < MFMA_COLS ? MFMA_COLS : cols;
+    f.cols = single || cols < MFMA_COLS ? MFMA_COLS : lone && pieces <= 4 && cols > 48 ? 48 : cols;
     if (whole) f.cols = (f.cols + 15) / 16 * 16;
     f.wgs = (N + f.cols - 1) / f.cols;
     return f;
 }
 
 hipError_t launch_few_mfma(const FewParams& fp, FewOperands fo, int src, hipStream_t st) {
-    const FewSplit f = few_split(fp.K, fp.N, src != 1, fo.pack_out != nullptr);
+    const FewSplit f = few_split(fp.K, fp.N, src != 1, fo.pack_out != nullptr, src == 0 && !fo.cs ? fp.rows : 0);
     const int ppw = f.ppw, wgs = f.wgs;
     const size_t lds = few_mfma_lds(f.ks, (f.cols + 15) / 16);
     fo.ks = f.ks;

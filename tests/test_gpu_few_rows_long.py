@@ -74,3 +74,27 @@ def test_tokens_of_one_sequence(shape, tokens):
     for j in range(NL):
         check(f"layer {j} ssm state", host(st["ssm_state"][j]), fo["ssm_states"][j], tol)
         check(f"layer {j} conv state", host(st["conv_state"][j]), fo["conv_states"][j], tol)
+
+
+@pytest.mark.parametrize("K,N,rows", [
+    (264, 520, (3, 8, 9)),           # single tiles: two waves of a row, the last of eight elements
+    (1024, 40, (3, 4, 5, 8, 9)),     # four waves
+    (1032, 32776, (3, 4, 5)),        # five pieces in two turns of three waves
+    (2048, 32768, (3, 4)),           # eight waves
+    (4104, 32776, (4,)),             # seventeen pieces in five turns
+    (7176, 72, (3, 16)),             # two turns of eight waves for twenty-nine pieces, two a wave
+    (14336, 72, (3, 16)),            # four turns of seven waves instead of three of ten
+    (2568, 16392, (3, 16)),          # eleven pieces: two a wave where twelve waves need a second round
+    (6152, 40, (1, 2)),              # the vector ALUs: thirteen pieces in two turns of seven, four columns a workgroup
+    (2568, 12296, (2,)),             # two turns of three
+    (2560, 12296, (2,)),             # five waves, eight columns
+    (8192, 12296, (1, 2)),           # eight waves in two turns, four in four
+    (520, 12296, (1, 2)),            # two waves, eight columns for two rows
+    (1032, 3592, (1,)),              # one workgroup a unit, of sixteen columns
+    (1032, 4104, (1,)),              # of four again
+    (1000, 50296, (16,)),            # three tiles of a row in four waves
+    (4096, 32776, (8,)),             # eight waves, single tiles
+])
+def test_products_alone(K, N, rows):
+    """Tolerance as above."""
+    test_edges(K, N, rows)
