@@ -1128,9 +1128,8 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_final(SegParams sp) {
 #pragma unroll
                 for (int q = 0; q < SLICES; ++q) {
                     const float* G = dG + (q < dns ? q * QQ : 0);
-                    const bool there = live && q < dns;  // (a slice that is not there is asked for, and nothing comes: see chain)
-                    if (KC) fetch<float, LF>(R.a[q], true, part_of<float>(G, (int64_t)r0 * Q + k0, Q, least(TM, V - r0), Q - k0), there);
-                    else fetch<float, LF>(R.a[q], false, part_of<float>(G, (int64_t)k0 * Q + r0, Q, kn, Q - r0), there);
+                    if (KC) fetch<float, LF>(R.a[q], true, part_of<float>(G, (int64_t)r0 * Q + k0, Q, least(TM, V - r0), Q - k0), live);
+                    else fetch<float, LF>(R.a[q], false, part_of<float>(G, (int64_t)k0 * Q + r0, Q, kn, Q - r0), live);
                 }
                 fetch<T, LT>(R.b, false, part_of<T>(rhs, bbase + n0 + k0 * bt, bt, kn, N - n0), live);
             },
