@@ -300,7 +300,7 @@ int even_columns(int N, int K, int units, int most) {
 // A product that stands alone has nothing but the way to its first load to hide, and more waves do: sixteen, where the registers hold
 // them.  1536 x 3352 4.6 -> 4.4 us, 768 x 10576 with two rows 6.4 -> 6.0.  Better still are workgroups of four columns that start one after
 // another, as many as fit: they keep the memory busier than a round that ends together, and do not meet on the same channels where 16 or
-// 32 columns are a power of two of bytes.  us by rounds -> so: 5120 x 50288 85 -> 80, 8192 x 8192 24.9 -> 20.9, 16384 x 4096 26.1 -> 21.4; up to 4096
+// 32 columns are a power of two of bytes.  us by rounds -> so: 5120 x 50288 85 -> 82, 8192 x 8192 24.9 -> 20.9, 16384 x 4096 26.1 -> 21.4; up to 4096
 // columns one workgroup a unit, of whole fours, is a round that starts at once (5120 x 2560 5.2 with four columns, 4.6 with twelve).  Two rows,
 // with twice the work to a load of w, are so where columns are many or rows long (8192 x 8192 25.8 -> 21.9, 4096 x 50288 72.5 -> 66.5, but 3072
 // -> 6144 7.8 -> 8.1), and take four or five waves at most where they are many, and eight columns where five waves or two leave a unit's last
