@@ -373,7 +373,7 @@ static_assert(10 * 16 * WPITCH + mfma_tiles(10) * 10 * 1024 <= MFMA_WAVES * 16 *
 // no normalisation.  PARTS: row_parts(rows) (SRC 0: 1, rows of x are bf16 values as they are).
 // PPW: pieces of a wave that it keeps operands of; longer rows go by in turns (SRC 1: one, two of them and what their
 // normalisation takes do not fit the registers).  The first of w of a turn is asked for in front of the last tile of the turn before: with three
-// rows 5120 x 50288 in five turns of four waves 89 us, 94 where it was asked for behind it.
+// rows 5120 x 50288 at its best split 89 us, 94 where it was asked for behind it.
 template <int SRC, bool STEP, int PARTS, bool STREAM, int PPW, bool TURNS>
 __global__ __launch_bounds__(MFMA_WAVES * 64) void k_linear_few_mfma(FewParams fp, FewOperands fo) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
