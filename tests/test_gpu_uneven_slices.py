@@ -32,3 +32,14 @@ def test_their_partial_sums_are_rounded_once(case):
 ])
 def test_one_round_keeps_its_partial_sums_in_fp32(case):
     check_rounding(case)
+
+
+@pytest.mark.parametrize("case", [
+    # Bt, L, H, G, Q, segment
+    (1, 100, 37, 1, 128, 128),         # one chunk: a slice for every head, the last one on its own behind nine fours
+    (1, 200, 6, 1, 256, 256),          # two behind one four
+    (1, 60, 22, 2, 64, 64),            # eleven a group: three
+    (1, 100, 8, 1, 128, 128),          # two fours
+])
+def test_a_slice_for_every_head_of_one_chunk(case):
+    check_slices(case)
